@@ -300,3 +300,121 @@ def tolerance(case):
     if case["kind"] == "reencode":
         return {"rel": 2e-7, "max": 2e-6} if case["dtype"] == "f32" else {"rel": 7e-3, "max": 1.6e-2}
     return {"rel": 1.4e-2, "max": 0.3}
+
+
+# ---- the same in 64 bits, in plain torch --------------------------------------------------------------------
+def _turn(x, pos, case):
+    """x [tokens, heads, D] turned by the angles of the tokens' positions (a negative position turns back)."""
+    d = x.shape[-1]
+    freq = case["rope_base"] ** (-2.0 * torch.arange(d // 2, dtype=torch.float64, device=x.device) / d)
+    angle = torch.as_tensor(pos, dtype=torch.float64, device=x.device)[:, None, None] * freq
+    c, s = angle.cos(), angle.sin()
+    if case["layout"] == "half":
+        a, b = x[..., : d // 2], x[..., d // 2:]
+        return torch.cat([c * a - s * b, s * a + c * b], dim=-1)
+    a, b = x[..., 0::2], x[..., 1::2]
+    return torch.stack([c * a - s * b, s * a + c * b], dim=-1).reshape(x.shape)
+
+
+def _attend(q, k, v, first, d_out=None):
+    """Causal attention of rotated q, whose first token is key `first`; with d_out also the log-sum-exps and gradients."""
+    hq, hkv, d = q.shape[1], k.shape[1], q.shape[2]
+    g = hq // hkv
+    o, lse, dq = torch.zeros_like(q), q.new_zeros(q.shape[:2]), torch.zeros_like(q)
+    dk, dv = torch.zeros_like(k), torch.zeros_like(v)
+    for h in range(hkv):
+        heads = slice(h * g, (h + 1) * g)
+        step = max(16, (1 << 26) // max(1, len(k) * g))
+        for r in range(0, len(q), step):
+            n = min(step, len(q) - r)
+            keys = first + r + n
+            kh, vh = k[:keys, h], v[:keys, h]
+            qh = q[r: r + n, heads].reshape(n * g, d)
+            sc = (qh @ kh.T / math.sqrt(d)).view(n, g, keys)
+            last = first + r + torch.arange(n, device=q.device)
+            sc.masked_fill_(torch.arange(keys, device=q.device)[None, None, :] > last[:, None, None], -math.inf)
+            norm = torch.logsumexp(sc, dim=-1)
+            p = sc.sub_(norm[..., None]).exp_().view(n * g, keys)
+            oh = p @ vh
+            o[r: r + n, heads], lse[r: r + n, heads] = oh.view(n, g, d), norm
+            if d_out is not None:
+                gh = d_out[r: r + n, heads].reshape(n * g, d)
+                ds = p * (gh @ vh.T - (gh * oh).sum(-1, keepdim=True)) / math.sqrt(d)
+                dq[r: r + n, heads] = (ds @ kh).view(n, g, d)
+                dk[:keys, h] += ds.T @ qh
+                dv[:keys, h] += p.T @ gh
+    return o, lse, dq, dk, dv
+
+
+def exact(case, seed):
+    """What `run` returns for these inputs, in 64 bits, without rounding anything on the way."""
+    st, s = prepare(case, seed), _shape(case)
+    kind = case["kind"]
+    f = {n: t.double() for n, t in st.items() if n in ("q", "k", "v", "kc", "vc", "kf", "vf", "qf", "d_out")}
+    pos = torch.arange(40000, dtype=torch.float64, device="cuda")  # longer than any prompt here
+
+    def encode():
+        o, kl = torch.empty_like(f["q"]), torch.empty_like(f["k"])
+        for a, b in zip(st["offs"][:-1].tolist(), st["offs"][1:].tolist()):
+            kl[a:b] = _turn(f["k"][a:b], pos[: b - a], case)
+            o[a:b] = _attend(_turn(f["q"][a:b], pos[: b - a], case), kl[a:b], f["v"][a:b], 0)[0]
+        return o, kl
+
+    def final(q, kf, vf, k, v):
+        n = len(k)
+        at = pos[n: n + len(q)]
+        return _attend(_turn(q, at, case), torch.cat([k, _turn(kf, at, case)]), torch.cat([v, vf]), n)[0]
+
+    if kind == "encode":
+        o, kl = encode()
+        return [o] if st["k_local"] is None else [o, kl]
+    if kind == "reencode":
+        out = torch.empty(st["k_src"].shape, dtype=torch.float64, device="cuda")
+        for a, b, n in zip(st["src_off"].tolist(), st["dst_off"].tolist(), s["blk"].tolist()):
+            # shift: every key of a block by the block's new first position; absolute: by its own position
+            at = b + pos[:n] if case["mode"] == "absolute" else torch.full((n,), float(b), dtype=torch.float64, device="cuda")
+            for layer in range(case["n_layers"]):
+                out[layer, b: b + n] = _turn(st["k_src"][layer, a: a + n].double(), at, case)
+        return [out]
+    if kind == "final":
+        o = torch.empty_like(f["q"])
+        for i in range(case["n_prompts"]):
+            a, b = st["cu_q"][i: i + 2].tolist()
+            c, e = st["cu_ctx"][i: i + 2].tolist()
+            o[a:b] = final(f["q"][a:b], f["kf"][a:b], f["vf"][a:b], f["kc"][c:e], f["vc"][c:e])
+        return [o]
+    if kind == "cached":
+        o = torch.empty_like(f["q"])
+        for i in range(case["n_prompts"]):
+            ks, vs, at = [], [], 0
+            for blk in range(*st["cu_blk"][i: i + 2].tolist()):
+                a, n = int(st["off"][blk]), int(st["lens"][blk])
+                ks.append(_turn(f["kc"][a: a + n], torch.full((n,), float(at), dtype=torch.float64, device="cuda"), case))
+                vs.append(f["vc"][a: a + n])
+                at += n
+            a, b = st["cu_q"][i: i + 2].tolist()
+            o[a:b] = final(f["q"][a:b], f["kf"][a:b], f["vf"][a:b], torch.cat(ks), torch.cat(vs))
+        return [o]
+    if kind == "train":
+        out = [torch.zeros_like(f["q"]), torch.zeros(st["lse"].shape, dtype=torch.float64, device="cuda")]
+        out += [torch.zeros_like(f[n]) for n in ("q", "k", "v")]
+        o, lse, dq, dk, dv = out
+        for i in range(case["n_prompts"]):
+            lo, hi = st["cu_blk"][i: i + 2].tolist()
+            t0, t1 = int(st["offs"][lo]), int(st["offs"][hi])
+            at = pos[: t1 - t0]
+            q, k = _turn(f["q"][t0:t1], at, case), _turn(f["k"][t0:t1], at, case)
+            for blk in range(lo, hi):
+                a, b = st["offs"][blk: blk + 2].tolist()
+                key0 = t0 if blk == hi - 1 else a  # only the last block sees the others
+                got = _attend(q[a - t0: b - t0], k[key0 - t0: b - t0], f["v"][key0:b], a - key0, f["d_out"][a:b])
+                o[a:b], lse[a:b], dq[a:b] = got[:3]
+                dk[key0:b] += got[3]
+                dv[key0:b] += got[4]
+            dq[t0:t1], dk[t0:t1] = _turn(dq[t0:t1], -at, case), _turn(dk[t0:t1], -at, case)
+        return out
+    o, kl = encode()
+    k_ctx = torch.empty_like(kl)
+    for a, n in zip(st["start"].tolist(), st["lens"].tolist()):
+        k_ctx[a: a + n] = _turn(kl[a: a + n], torch.full((n,), float(a), dtype=torch.float64, device="cuda"), case)
+    return [o, kl, k_ctx, final(f["qf"], f["kf"], f["vf"], k_ctx, f["v"])]
