@@ -49,11 +49,21 @@ struct BGeo {
   static_assert(IPW >= 1 && 32 / QRPI == KCH, "tile geometry");
 };
 
-// row `row` of a tile, 16-byte chunk `chunk`: every tile here uses the one swizzle
+// Where a row's 16-byte chunks go: chunk c of row r at c ^ row_swizzle(r).  Both reads of a tile have to
+// spread over the banks: a row read (a lane per row, the same chunk) by 16-byte chunk over 16 rows of 256
+// bytes, a transpose read (four rows, the same 64 bytes of each) by 64-byte granule over those four.  So
+// the row's LOW bits move the granule and its high bits the chunk inside it, every row its own way.
+// (With the row number itself, low bits moving the chunk, the four rows of a transpose read shared one
+// granule's banks: half of the LDS cycles of the dk/dv kernel and a third of the dq kernel's were conflicts.)
+template <int D>
+__device__ __forceinline__ int row_swizzle(int row) {
+  constexpr int BITS = D == 128 ? 4 : 3, GB = BITS - 2;  // bits of a chunk number; of a granule's
+  const int h = (row / BGeo<D>::LPR) & (BGeo<D>::CPR - 1);
+  return ((h & ((1 << GB) - 1)) << 2) | (h >> GB);
+}
 template <int D>
 __device__ __forceinline__ uint32_t tile_ofs(int row, int chunk) {
-  using G = BGeo<D>;
-  return (uint32_t)(row * G::ROWB + ((chunk ^ ((row / G::LPR) & (G::CPR - 1))) << 4));
+  return (uint32_t)(row * BGeo<D>::ROWB + ((chunk ^ row_swizzle<D>(row)) << 4));
 }
 
 // A gradient in the rotated frame, held in accumulator layout (lane = row `col`, register v of slab dt =
@@ -219,7 +229,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   for (int u = 0; u < G::IPW; ++u) {
     const int row = (wave * G::IPW + u) * G::RPI + lane / G::CPR, pos = lane % G::CPR;
     c_row[u] = row;
-    c_chunk[u] = (uint32_t)(pos ^ ((row / G::LPR) & (G::CPR - 1))) << 4;
+    c_chunk[u] = (uint32_t)(pos ^ row_swizzle<D>(row)) << 4;
   }
   const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + wave * G::IPW * 1024;
   auto issue_copy = [&](int t, int buf) __attribute__((always_inline)) {
@@ -454,7 +464,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   // rows as A operand: row `col`, chunk 2 kk + hf, i.e. byte (32 kk) ^ row_x inside the row (worked
   // out at each use: eight more address registers would not fit two waves per SIMD)
   const uint32_t row_b = (uint32_t)col * G::ROWB;
-  const uint32_t row_x = (uint32_t)(hf ^ ((col / G::LPR) & (G::CPR - 1))) << 4;
+  const uint32_t row_x = (uint32_t)(hf ^ row_swizzle<D>(col)) << 4;
   uint32_t t_rd[2][G::DT];
   {
     const int trow = hf * 4 + ((lane & 15) >> 2);
@@ -482,7 +492,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
       const int rt = (wave * IPW + u) * G::RPI + lane / G::CPR, pos = lane % G::CPR;
       const uint32_t r = (uint32_t)min(r0 + rt, n_rows - 1);  // rows beyond the block repeat its last row
       const uint32_t tok = fast_div(r, p.group_div), g = r - tok * (uint32_t)Gq;
-      const uint32_t chunk = (uint32_t)(pos ^ ((rt / G::LPR) & (G::CPR - 1))) << 4;
+      const uint32_t chunk = (uint32_t)(pos ^ row_swizzle<D>(rt)) << 4;
       lds_dma16(qb, (tok * q_st + g * q_sh) * 2u + chunk, lds_copy + (uint32_t)buf * BUFB + u * 1024);
       lds_dma16(db, (tok * do_st + g * do_sh) * 2u + chunk, lds_copy + (uint32_t)buf * BUFB + TB + u * 1024);
     }
