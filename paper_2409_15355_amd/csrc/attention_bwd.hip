@@ -41,29 +41,68 @@ struct BGeo {
   static constexpr int DT = D / 32;
   static constexpr int CPR = D / 8;
   static constexpr int ROWB = D * 2;
-  static constexpr int LPR = 256 / ROWB;
-  static constexpr int TILEB = kBKeys * ROWB;
   static constexpr int RPI = 1024 / ROWB;             // rows filled by one LDS-direct wave instruction
+  static constexpr int GRPB = 1024 + 16 * (RPI / 4);  // bytes from one such group of rows to the next (see tile_ofs)
+  static constexpr int TILEB = kBKeys / RPI * GRPB;
+  static constexpr int SLICEB = 16 / RPI * GRPB;      // sixteen rows
   static constexpr int IPW = kBKeys / RPI / kBWaves;  // such instructions per wave and tile
   static constexpr int QRPI = 64 / CPR;               // whole rows per plain load instruction
   static_assert(IPW >= 1 && 32 / QRPI == KCH, "tile geometry");
 };
 
-// Where a row's 16-byte chunks go: chunk c of row r at c ^ row_swizzle(r).  Both reads of a tile have to
-// spread over the banks: a row read (a lane per row, the same chunk) by 16-byte chunk over 16 rows of 256
-// bytes, a transpose read (four rows, the same 64 bytes of each) by 64-byte granule over those four.  So
-// the row's LOW bits move the granule and its high bits the chunk inside it, every row its own way.
-// (With the row number itself, low bits moving the chunk, the four rows of a transpose read shared one
-// granule's banks: half of the LDS cycles of the dk/dv kernel and a third of the dq kernel's were conflicts.)
+// Where row `row` of a tile keeps its 16-byte chunk `chunk`.  Both reads of a tile have to spread over the
+// LDS banks: a row read (a lane per row, the same chunk of 16 rows) by 16-byte chunk, a transpose read
+// (four rows, the same 64 bytes of each) by 64-byte granule.  So a row's low bits move the granule (an
+// XOR), and what is left tells the rows apart inside it: at D = 128 the 16 bytes by which the groups of
+// four rows are spaced beyond their 1 KB, at D = 64 the 32 bytes between groups of eight and one more
+// XOR of the chunk's low bit.  (With the XOR of the row number over all chunk bits, the four rows of a
+// transpose read shared one granule's banks: half of the dk/dv kernel's LDS cycles were conflicts.)
+// The XORs reach a chunk's granule and lowest bit only, so the two chunk pairs of a granule, the 16-row
+// steps of a transpose read and the tiles of a buffer lie at constant distances from each other: a
+// kernel keeps one address per granule, and the rest are offsets inside the instructions.
 template <int D>
-__device__ __forceinline__ int row_swizzle(int row) {
-  constexpr int BITS = D == 128 ? 4 : 3, GB = BITS - 2;  // bits of a chunk number; of a granule's
-  const int h = (row / BGeo<D>::LPR) & (BGeo<D>::CPR - 1);
-  return ((h & ((1 << GB) - 1)) << 2) | (h >> GB);
-}
+__device__ __forceinline__ int granule_xor(int row) { return D == 128 ? row & 3 : (row >> 1) & 1; }
+template <int D>
+__device__ __forceinline__ int low_xor(int row) { return D == 128 ? 0 : (row >> 2) & 1; }
 template <int D>
 __device__ __forceinline__ uint32_t tile_ofs(int row, int chunk) {
-  return (uint32_t)(row * BGeo<D>::ROWB + ((chunk ^ row_swizzle<D>(row)) << 4));
+  using G = BGeo<D>;
+  return (uint32_t)((row / G::RPI) * G::GRPB + (row % G::RPI) * G::ROWB +
+                    ((chunk ^ (granule_xor<D>(row) << 2) ^ low_xor<D>(row)) << 4));
+}
+// Row read as A operand, k-step kk: row `col`, chunk 2 kk + hf.  base[kk / 2] + row_read_ofs(kk).
+template <int D>
+__device__ __forceinline__ void row_read_bases(uint32_t (&base)[D / 32], int col, int hf) {
+#pragma unroll
+  for (int g = 0; g < D / 32; ++g) base[g] = tile_ofs<D>(col, g * 4 + hf);
+}
+__device__ __forceinline__ constexpr uint32_t row_read_ofs(int kk) { return (uint32_t)(kk & 1) * 32u; }
+// Transposed A operand, 16-row step kc, half `h` of its 8-byte pieces: base[dt] + tr_read_ofs(kc, h).
+template <int D>
+__device__ __forceinline__ void tr_read_bases(uint32_t (&base)[D / 32], int lane) {
+  const int trow = (lane >> 5) * 4 + ((lane & 15) >> 2);
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt) {
+    const int byte = dt * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    base[dt] = tile_ofs<D>(trow, byte >> 4) + (byte & 15);
+  }
+}
+template <int D>
+__device__ __forceinline__ constexpr uint32_t tr_read_ofs(int kc, int h) {
+  return (uint32_t)((kc * 16 + h * 8) / BGeo<D>::RPI * BGeo<D>::GRPB);
+}
+template <int D>
+__device__ __forceinline__ bf16x8_t row_frag(const lds_char *at, int kk) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(at + row_read_ofs(kk));
+}
+template <int D>
+__device__ __forceinline__ bf16x8_t tr_frag(lds_char *at, int kc) {
+  typedef __attribute__((address_space(3))) s16x4_t lds_s16x4;
+  typedef short s16x8_t __attribute__((ext_vector_type(8)));
+  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at + tr_read_ofs<D>(kc, 0)));
+  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at + tr_read_ofs<D>(kc, 1)));
+  const s16x8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8_t, both);
 }
 
 // A gradient in the rotated frame, held in accumulator layout (lane = row `col`, register v of slab dt =
@@ -204,43 +243,27 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- per-lane LDS read offsets inside a tile ---------------------------------------------------
-  uint32_t k_rd[G::KCH];  // rows as A operand: row `col`, chunk 2 kk + hf
-#pragma unroll
-  for (int kk = 0; kk < G::KCH; ++kk) k_rd[kk] = tile_ofs<D>(col, kk * 2 + hf);
-  // transposed A operand (16-row step 0): 8-byte piece of row trow (+8), head dims 32 dt + ...
-  uint32_t t_rd[2][G::DT];
-  {
-    const int trow = hf * 4 + ((lane & 15) >> 2);
-#pragma unroll
-    for (int dt = 0; dt < G::DT; ++dt) {
-      const int byte = dt * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
-      t_rd[0][dt] = tile_ofs<D>(trow, byte >> 4) + (byte & 15);
-      t_rd[1][dt] = tile_ofs<D>(trow + 8, byte >> 4) + (byte & 15);
-    }
-  }
+  uint32_t k_rd[G::DT], t_rd[G::DT];
+  row_read_bases<D>(k_rd, col, hf);
+  tr_read_bases<D>(t_rd, lane);
 
   // ---- tile fill (K and V rows of 32 keys; rows beyond the valid ones repeat the last valid row) ----
   const char *k_base = (const char *)(p.kf + (int64_t)k_tok0 * p.kf_st + (int64_t)kvh * p.kf_sh);
   const char *v_base = (const char *)(p.vf + (int64_t)k_tok0 * p.vf_st + (int64_t)kvh * p.vf_sh);
   const uint32_t k_rb = (uint32_t)p.kf_st * 2u, v_rb = (uint32_t)p.vf_st * 2u;
-  int c_row[G::IPW];
-  uint32_t c_chunk[G::IPW];
-#pragma unroll
-  for (int u = 0; u < G::IPW; ++u) {
-    const int row = (wave * G::IPW + u) * G::RPI + lane / G::CPR, pos = lane % G::CPR;
-    c_row[u] = row;
-    c_chunk[u] = (uint32_t)(pos ^ row_swizzle<D>(row)) << 4;
-  }
-  const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + wave * G::IPW * 1024;
+  const int c_row = wave * G::IPW * G::RPI + lane / G::CPR;  // this lane's row of the wave's first instruction
+  // (the XORs of tile_ofs depend on the row's place in its group only)
+  const uint32_t c_chunk = (uint32_t)((lane % G::CPR) ^ (granule_xor<D>(lane / G::CPR) << 2) ^ low_xor<D>(lane / G::CPR)) << 4;
+  const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + wave * G::IPW * G::GRPB;
   auto issue_copy = [&](int t, int buf) __attribute__((always_inline)) {
     const int valid = min(kBKeys, lk - t * kBKeys);
     const char *kp = k_base + (uint64_t)(uint32_t)(t * kBKeys) * (uint64_t)k_rb;
     const char *vp = v_base + (uint64_t)(uint32_t)(t * kBKeys) * (uint64_t)v_rb;
 #pragma unroll
     for (int u = 0; u < G::IPW; ++u) {
-      const uint32_t row = (uint32_t)min(c_row[u], valid - 1);
-      lds_dma16(kp, row * k_rb + c_chunk[u], lds_copy + (uint32_t)buf * (2 * TB) + u * 1024);
-      lds_dma16(vp, row * v_rb + c_chunk[u], lds_copy + (uint32_t)buf * (2 * TB) + TB + u * 1024);
+      const uint32_t row = (uint32_t)min(c_row + u * G::RPI, valid - 1);
+      lds_dma16(kp, row * k_rb + c_chunk, lds_copy + (uint32_t)buf * (2 * TB) + u * G::GRPB);
+      lds_dma16(vp, row * v_rb + c_chunk, lds_copy + (uint32_t)buf * (2 * TB) + TB + u * G::GRPB);
     }
   };
   constexpr int kOpsPerTile = 2 * G::IPW;
@@ -250,8 +273,8 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   dma_wait<0>();
 
   // ---- whole rows -> B-operand fragments (lane = row), 16 rows at a time through this wave's slice ----
-  static_assert(kBWaves * 16 * G::ROWB <= 2 * TB, "the slices fit one tile buffer");
-  const uint32_t s_ofs = 2 * (2 * TB) + wave * (16 * G::ROWB);
+  static_assert(kBWaves * G::SLICEB <= 2 * TB, "the slices fit one tile buffer");
+  const uint32_t s_ofs = 2 * (2 * TB) + wave * G::SLICEB;
   auto rows_to_frags = [&](const u32x4_t (&ld)[G::KCH], bf16x8_t (&out)[G::KCH]) __attribute__((always_inline)) {
     u32x4_t got[2][G::KCH];
 #pragma unroll
@@ -275,8 +298,9 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     }
   };
   // delta of this wave's rows: a row's CPR lanes add up their pieces, one of them hands the sum over
-  // through the slice to the lane that owns the row; the pair (L / ln 2, delta) also goes to memory in
-  // packed-row order per KV head, where the dk/dv kernel finds the 32 pairs of a row tile side by side
+  // through the slice to the lane that owns the row; -L / ln 2 and -delta also go to memory in packed-row
+  // order per KV head, four rows of the one and four of the other in turn: the dk/dv kernel's
+  // accumulators start at them, and read them from its tile as they lie
   float2 my_ld;
   {
 #pragma unroll
@@ -293,7 +317,11 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const int r_in_wave = min(col, max(wave_last_row - wave_row0, 0));  // (lanes beyond the block's rows: its last row)
     my_ld.y = *reinterpret_cast<const __attribute__((address_space(3))) float *>(smem + s_ofs + r_in_wave * 4);
     my_ld.x = my_lse * kLog2e;
-    if (hf == 0 && wave_row0 + col < n_rows) bp.ld[((int64_t)kvh * bp.T + q_tok0) * Gq + wave_row0 + col] = my_ld;
+    if (wave_row0 + col < n_rows) {
+      const int r = wave_row0 + col;
+      float *dst = bp.ld + 2 * (((int64_t)kvh * bp.T + q_tok0) * bp.ld_group) + (r >> 2) * 8 + (r & 3);
+      dst[hf * 4] = hf ? -my_ld.y : -my_ld.x;  // the two halves of the wave hold the same rows
+    }
   }
   bf16x8_t qf[G::KCH], dof[G::KCH];
   rows_to_frags(ld_q, qf);
@@ -313,7 +341,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     wg_barrier();
     if (i + 2 < n_t) issue_copy(i + 2, buf == 0 ? 2 : buf - 1);
     if (i < wave_n_t) {
-      const uint32_t kofs = (uint32_t)buf * (2 * TB), vofs = kofs + TB;
+      lds_char *const bk = smem + (uint32_t)buf * (2 * TB);  // this tile: K rows, then (TB on) V rows
       // S'^T - L: the base-2 exponent of P;  dP^T - delta
       f32x16_t sacc, dpacc;
 #pragma unroll
@@ -323,9 +351,9 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
       }
 #pragma unroll
       for (int kk = 0; kk < G::KCH; ++kk) {
-        const bf16x8_t kfrag = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(smem + (k_rd[kk] + kofs));
+        const bf16x8_t kfrag = row_frag<D>(bk + k_rd[kk / 2], kk);
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag, qf[kk], sacc, 0, 0, 0);
-        const bf16x8_t vfrag = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(smem + (k_rd[kk] + vofs));
+        const bf16x8_t vfrag = row_frag<D>(bk + k_rd[kk / 2] + TB, kk);
         dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag, dof[kk], dpacc, 0, 0, 0);
       }
       const int key0 = i * kBKeys;
@@ -354,14 +382,8 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
 #pragma unroll
       for (int kc = 0; kc < 2; ++kc)
 #pragma unroll
-        for (int dt = 0; dt < G::DT; ++dt) {
-          typedef __attribute__((address_space(3))) s16x4_t lds_s16x4;
-          typedef short s16x8_t __attribute__((ext_vector_type(8)));
-          const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + (t_rd[0][dt] + kofs) + kc * 16 * G::ROWB));
-          const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + (t_rd[1][dt] + kofs) + kc * 16 * G::ROWB));
-          const s16x8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, both), dsf[kc], acc[dt], 0, 0, 0);
-        }
+        for (int dt = 0; dt < G::DT; ++dt)
+          acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag<D>(bk + t_rd[dt], kc), dsf[kc], acc[dt], 0, 0, 0);
     }
     buf = buf == kBBuf - 1 ? 0 : buf + 1;
   }
@@ -375,7 +397,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   const int ecol = ln & 31, ehf = ln >> 5;
   rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(q_tok0 + my_tok) * D), ehf,
                  p.rope_layout != 0, kLn2);
-  lds_char *stage = smem + wave * (32 * G::ROWB);
+  lds_char *stage = smem + wave * G::TILEB;
 #pragma unroll
   for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
@@ -410,13 +432,12 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char *smem = (lds_char *)smem_generic;
   // LDS map: buffer b = bytes [b BUFB, (b + 1) BUFB): a q^ tile, a dO tile (kKvRows packed query rows
-  // each, i.e. RG groups of 32: two independent chains of products per iteration, which a single
-  // wave per SIMD needs to keep the matrix pipe fed), then per wave 1 KB whose first kKvRows * 8
-  // bytes hold the rows' (L / ln 2, delta)
-  constexpr int RG = kKvRows / 32;
-  constexpr uint32_t TB = RG * G::TILEB;
+  // each), then per wave 1 KB whose first 256 bytes hold the rows' (-L / ln 2, -delta), four rows of
+  // the one and four of the other in turn
+  constexpr uint32_t TB = G::TILEB;
   constexpr uint32_t BUFB = 2 * TB + kBWaves * 1024;
-  constexpr int IPW = RG * G::IPW;  // LDS-direct loads per wave, tile and tensor
+  constexpr int IPW = G::IPW;  // LDS-direct loads per wave, tile and tensor
+  static_assert(kKvRows == 32, "one accumulator tile of query rows");
 
   uint32_t id = blockIdx.x;
   {
@@ -461,25 +482,27 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  // rows as A operand: row `col`, chunk 2 kk + hf, i.e. byte (32 kk) ^ row_x inside the row (worked
-  // out at each use: eight more address registers would not fit two waves per SIMD)
-  const uint32_t row_b = (uint32_t)col * G::ROWB;
-  const uint32_t row_x = (uint32_t)(hf ^ row_swizzle<D>(col)) << 4;
-  uint32_t t_rd[2][G::DT];
-  {
-    const int trow = hf * 4 + ((lane & 15) >> 2);
-#pragma unroll
-    for (int dt = 0; dt < G::DT; ++dt) {
-      const int byte = dt * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
-      t_rd[0][dt] = tile_ofs<D>(trow, byte >> 4) + (byte & 15);
-      t_rd[1][dt] = tile_ofs<D>(trow + 8, byte >> 4) + (byte & 15);
-    }
-  }
+  uint32_t r_rd[G::DT], t_rd[G::DT];
+  row_read_bases<D>(r_rd, col, hf);
+  tr_read_bases<D>(t_rd, lane);
 
   // ---- tile fill: kKvRows packed query rows of q^ and of dO, and the rows' (L, delta) ------------------
+  // An instruction moves RPI packed rows.  Where RPI and the group divide one another, those rows lie at
+  // the same distances from the first of them in every instruction: the lanes' offsets are worked out
+  // here, and a tile costs scalar arithmetic only.  Otherwise, and in the last tile of a block (rows
+  // beyond the block repeat its last row), every lane finds its own row.
   const uint32_t q_st = (uint32_t)p.q_st, q_sh = (uint32_t)p.q_sh, do_st = (uint32_t)bp.do_st, do_sh = (uint32_t)bp.do_sh;
-  const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + wave * IPW * 1024;
+  const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + wave * IPW * G::GRPB;
   const uint32_t lds_ld = (uint32_t)(uintptr_t)smem + 2 * TB + wave * 1024;
+  const uint32_t c_chunk = (uint32_t)((lane % G::CPR) ^ (granule_xor<D>(lane / G::CPR) << 2) ^ low_xor<D>(lane / G::CPR)) << 4;
+  const bool regular = Gq % G::RPI == 0 || G::RPI % Gq == 0;
+  uint32_t q_in, do_in;  // this lane's row and chunk, in bytes from an instruction's first row
+  {
+    const uint32_t l = (uint32_t)lane / G::CPR;
+    const uint32_t tok = Gq < G::RPI ? fast_div(l, p.group_div) : 0u, g = l - tok * (uint32_t)Gq;
+    q_in = (tok * q_st + g * q_sh) * 2u + c_chunk;
+    do_in = (tok * do_st + g * do_sh) * 2u + c_chunk;
+  }
   auto issue_copy = [&](int t, int buf) __attribute__((always_inline)) {
     const bool own = t < n_a;
     const int r0 = (own ? tile_a0 + t : t - n_a) * kKvRows;  // first packed row of the tile, inside its block
@@ -487,20 +510,30 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
     const int n_rows = own ? n_rows_a : n_rows_f;
     const char *qb = (const char *)(p.q + (int64_t)tok0 * p.q_st + (int64_t)(kvh * Gq) * p.q_sh);
     const char *db = (const char *)(bp.dout + (int64_t)tok0 * bp.do_st + (int64_t)(kvh * Gq) * bp.do_sh);
+    const uint32_t lds_tile = lds_copy + (uint32_t)buf * BUFB;
+    if (regular && r0 + kKvRows <= n_rows) {
 #pragma unroll
-    for (int u = 0; u < IPW; ++u) {
-      const int rt = (wave * IPW + u) * G::RPI + lane / G::CPR, pos = lane % G::CPR;
-      const uint32_t r = (uint32_t)min(r0 + rt, n_rows - 1);  // rows beyond the block repeat its last row
-      const uint32_t tok = fast_div(r, p.group_div), g = r - tok * (uint32_t)Gq;
-      const uint32_t chunk = (uint32_t)(pos ^ row_swizzle<D>(rt)) << 4;
-      lds_dma16(qb, (tok * q_st + g * q_sh) * 2u + chunk, lds_copy + (uint32_t)buf * BUFB + u * 1024);
-      lds_dma16(db, (tok * do_st + g * do_sh) * 2u + chunk, lds_copy + (uint32_t)buf * BUFB + TB + u * 1024);
+      for (int u = 0; u < IPW; ++u) {
+        const uint32_t r = (uint32_t)(r0 + (wave * IPW + u) * G::RPI);
+        const uint32_t tok = fast_div(r, p.group_div), g = r - tok * (uint32_t)Gq;
+        lds_dma16(qb + (uint64_t)((tok * q_st + g * q_sh) * 2u), q_in, lds_tile + u * G::GRPB);
+        lds_dma16(db + (uint64_t)((tok * do_st + g * do_sh) * 2u), do_in, lds_tile + TB + u * G::GRPB);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < IPW; ++u) {
+        const uint32_t r = (uint32_t)min(r0 + (wave * IPW + u) * G::RPI + lane / G::CPR, n_rows - 1);
+        const uint32_t tok = fast_div(r, p.group_div), g = r - tok * (uint32_t)Gq;
+        lds_dma16(qb, (tok * q_st + g * q_sh) * 2u + c_chunk, lds_tile + u * G::GRPB);
+        lds_dma16(db, (tok * do_st + g * do_sh) * 2u + c_chunk, lds_tile + TB + u * G::GRPB);
+      }
     }
-    // (L, delta) of the rows: contiguous in packed-row order, 16 bytes (two rows) per lane; every wave
-    // fetches its own copy (the upper lanes re-read the same bytes), so that all waves count alike
-    const char *lb = (const char *)(bp.ld + ((int64_t)kvh * bp.T + tok0) * Gq);
-    const uint32_t r = (uint32_t)min(r0 + (lane & (kKvRows / 2 - 1)) * 2, n_rows - 2 + (n_rows & 1));
-    lds_dma16(lb, (r & ~1u) * 8u, lds_ld + (uint32_t)buf * BUFB);
+    // (-L, -delta) of the rows: 32 contiguous bytes per four packed rows, the block's last four perhaps
+    // partly unwritten; every wave fetches its own copy (the upper lanes re-read the same bytes), so
+    // that all waves count alike
+    const char *lb = (const char *)(bp.ld + 2 * (((int64_t)kvh * bp.T + tok0) * bp.ld_group)) + (uint32_t)r0 * 8u;
+    const int last = (n_rows - 1 - r0) / 4 * 2 + 1;  // the last 16-byte piece that belongs to the block
+    lds_dma16(lb, (uint32_t)min(lane & 15, last) * 16u, lds_ld + (uint32_t)buf * BUFB);
   };
   constexpr int kOpsPerTile = 2 * IPW + 1;
   if (0 < n_t) issue_copy(0, 0);
@@ -509,9 +542,8 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   dma_wait<0>();
 
   // ---- k^ and v rows -> B-operand fragments through this wave's slice of buffer 2 -------------------
-  static_assert(kBWaves * 16 * G::ROWB <= 2 * TB, "the slices fit the tiles of one buffer");
-  static_assert(kKvRows * 8 <= 1024 && kKvRows / 2 <= 64, "a wave's (L, delta) copy fits its 1 KB");
-  const uint32_t s_ofs = 2 * BUFB + wave * (16 * G::ROWB);
+  static_assert(kBWaves * G::SLICEB <= 2 * TB, "the slices fit the tiles of one buffer");
+  const uint32_t s_ofs = 2 * BUFB + wave * G::SLICEB;
   auto rows_to_frags = [&](const u32x4_t (&ld)[G::KCH], bf16x8_t (&out)[G::KCH]) __attribute__((always_inline)) {
     u32x4_t got[2][G::KCH];
 #pragma unroll
@@ -558,83 +590,68 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
     const int r0 = (own ? tile_a0 + i : i - n_a) * kKvRows;
     const int n_rows = own ? n_rows_a : n_rows_f;
     // a tile of the block's own rows whose tokens all lie before this wave's first key sees none of them
-    const int last_tok = (int)fast_div((uint32_t)min(r0 + kKvRows - 1, n_rows - 1), p.group_div);
-    if (wave_has_keys && !(own && last_tok < kw0)) {
-      const uint32_t qofs = (uint32_t)buf * BUFB, dofs = qofs + TB;
-      uint32_t rx = row_x;
-      asm volatile("" : "+v"(rx));  // (keeps the eight offsets below from being carried through the loop)
+    // (row = token * group + head: row r's token is at or behind key k exactly if r >= k * group)
+    if (wave_has_keys && !(own && min(r0 + kKvRows, n_rows) <= kw0 * Gq)) {
+      lds_char *const bq = smem + (uint32_t)buf * BUFB;  // this tile: q^ rows, then (TB on) dO rows
       // The accumulators start at minus the rows' log-sum-exp and minus their delta, so that the
       // products come out as the exponent of P and as dP - delta.  Register v of an accumulator is
-      // row (v >> 2) * 8 + hf * 4 + (v & 3) of the group: four runs of four rows, two pairs per 16 bytes.
-      f32x16_t sacc[RG], dpacc[RG];
+      // row (v >> 2) * 8 + hf * 4 + (v & 3): four runs of four rows.
+      f32x16_t sacc, dpacc;
+      {
+        const lds_char *at = bq + 2 * TB + wave * 1024 + hf * 32;
 #pragma unroll
-      for (int rg = 0; rg < RG; ++rg)
+        for (int run = 0; run < 4; ++run) {
+          const f32x4_t nl = *reinterpret_cast<const __attribute__((address_space(3))) f32x4_t *>(at + run * 64);
+          const f32x4_t nd = *reinterpret_cast<const __attribute__((address_space(3))) f32x4_t *>(at + run * 64 + 16);
 #pragma unroll
-        for (int run = 0; run < 4; ++run)
-#pragma unroll
-          for (int h2 = 0; h2 < 2; ++h2) {
-            const f32x4_t two = *reinterpret_cast<const __attribute__((address_space(3))) f32x4_t *>(
-                smem + 2 * TB + wave * 1024 + qofs + (rg * 32 + run * 8 + hf * 4 + h2 * 2) * 8);
-            sacc[rg][run * 4 + h2 * 2] = -two[0];
-            dpacc[rg][run * 4 + h2 * 2] = -two[1];
-            sacc[rg][run * 4 + h2 * 2 + 1] = -two[2];
-            dpacc[rg][run * 4 + h2 * 2 + 1] = -two[3];
+          for (int e = 0; e < 4; ++e) {
+            sacc[run * 4 + e] = nl[e];
+            dpacc[run * 4 + e] = nd[e];
           }
-#pragma unroll
-      for (int kk = 0; kk < G::KCH; ++kk)
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) {
-          const bf16x8_t qfrag = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(
-              smem + (row_b + (((uint32_t)kk * 32u) ^ rx) + qofs) + rg * 32 * G::ROWB);
-          sacc[rg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qfrag, kf[kk], sacc[rg], 0, 0, 0);
-          const bf16x8_t dfrag = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(
-              smem + (row_b + (((uint32_t)kk * 32u) ^ rx) + dofs) + rg * 32 * G::ROWB);
-          dpacc[rg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dfrag, vf[kk], dpacc[rg], 0, 0, 0);
         }
-      // which rows this key may not see: rows beyond the block, and (own block) tokens before the key
+      }
+      // Rows this key may not see: rows beyond the block, and (own block) tokens before the key.  Their
+      // exponent starts, and so ends, at minus infinity: P = 0, and with a finite dP dS = 0 too.  Done
+      // here, under one branch that most tiles do not take, the products and exponentials below are the
+      // same straight code for every tile (with the tests behind the exponentials, each under a branch of
+      // its own, a tile took 312 vector instructions instead of some 120).
       const bool ragged = r0 + kKvRows > n_rows;
-      const int first_tok = (int)fast_div((uint32_t)r0, p.group_div);
-      const bool diagonal = own && first_tok < kw0 + 32;
-      bf16x8_t pf[2 * RG], dsf[2 * RG];
+      const bool diagonal = own && r0 < (kw0 + 31) * Gq;
+      if (ragged || diagonal) {
+        const int lo = own ? max(my_key * Gq - r0, 0) : 0;
+        const uint32_t span = (uint32_t)max(n_rows - r0 - lo, 0);
 #pragma unroll
-      for (int rg = 0; rg < RG; ++rg) {
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          u32x4_t wp, wd;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            float pv[2], dsv[2];
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-              const int v = e * 8 + 2 * j + h2;
-              float pr = __builtin_amdgcn_exp2f(sacc[rg][v]);
-              const int row = r0 + rg * 32 + (v >> 2) * 8 + hf * 4 + (v & 3);
-              if (ragged && row >= n_rows) pr = 0.f;
-              if (diagonal && (int)fast_div((uint32_t)row, p.group_div) < my_key) pr = 0.f;
-              pv[h2] = pr;
-              dsv[h2] = pr * dpacc[rg][v];
-            }
-            wp[j] = pack_bf16(pv[0], pv[1]);
-            wd[j] = pack_bf16(dsv[0], dsv[1]);
-          }
-          pf[rg * 2 + e] = __builtin_bit_cast(bf16x8_t, wp);
-          dsf[rg * 2 + e] = __builtin_bit_cast(bf16x8_t, wd);
+        for (int v = 0; v < 16; ++v) {
+          const bool out = (uint32_t)((v >> 2) * 8 + (v & 3) + hf * 4 - lo) >= span;
+          sacc[v] = out ? -INFINITY : sacc[v];
+          dpacc[v] = out ? 0.f : dpacc[v];
         }
       }
 #pragma unroll
-      for (int kc = 0; kc < 2 * RG; ++kc)
+      for (int kk = 0; kk < G::KCH; ++kk) {
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(bq + r_rd[kk / 2], kk), kf[kk], sacc, 0, 0, 0);
+        dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(bq + r_rd[kk / 2] + TB, kk), vf[kk], dpacc, 0, 0, 0);
+      }
+      bf16x8_t pf[2], dsf[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        u32x4_t wp, wd;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int v = e * 8 + 2 * j;
+          const float p0 = __builtin_amdgcn_exp2f(sacc[v]), p1 = __builtin_amdgcn_exp2f(sacc[v + 1]);
+          wp[j] = pack_bf16(p0, p1);
+          wd[j] = pack_bf16(p0 * dpacc[v], p1 * dpacc[v + 1]);
+        }
+        pf[e] = __builtin_bit_cast(bf16x8_t, wp);
+        dsf[e] = __builtin_bit_cast(bf16x8_t, wd);
+      }
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc)
 #pragma unroll
         for (int dt = 0; dt < G::DT; ++dt) {
-          typedef __attribute__((address_space(3))) s16x4_t lds_s16x4;
-          typedef short s16x8_t __attribute__((ext_vector_type(8)));
-          const s16x4_t dlo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + (t_rd[0][dt] + dofs) + kc * 16 * G::ROWB));
-          const s16x4_t dhi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + (t_rd[1][dt] + dofs) + kc * 16 * G::ROWB));
-          const s16x8_t dboth = __builtin_shufflevector(dlo, dhi, 0, 1, 2, 3, 4, 5, 6, 7);
-          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, dboth), pf[kc], dv[dt], 0, 0, 0);
-          const s16x4_t qlo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + (t_rd[0][dt] + qofs) + kc * 16 * G::ROWB));
-          const s16x4_t qhi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + (t_rd[1][dt] + qofs) + kc * 16 * G::ROWB));
-          const s16x8_t qboth = __builtin_shufflevector(qlo, qhi, 0, 1, 2, 3, 4, 5, 6, 7);
-          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, qboth), dsf[kc], dk[dt], 0, 0, 0);
+          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag<D>(bq + t_rd[dt] + TB, kc), pf[kc], dv[dt], 0, 0, 0);
+          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag<D>(bq + t_rd[dt], kc), dsf[kc], dk[dt], 0, 0, 0);
         }
     }
     buf = buf == kBBuf - 1 ? 0 : buf + 1;
@@ -649,7 +666,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   const int ecol = ln & 31, ehf = ln >> 5;
   rotate_back<D>(dk, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(k_tok0 + min(kw0 + ecol, lk - 1)) * D), ehf,
                  p.rope_layout != 0, kLn2 / p.scale_log2e);
-  lds_char *stage = smem + wave * (32 * G::ROWB);
+  lds_char *stage = smem + wave * G::TILEB;
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
@@ -686,7 +703,7 @@ hipError_t launch_dkv_t(const AttnParams &p, const BwdKvMeta &meta, const BwdPar
   const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads;
   if (n_wg == 0) return hipSuccess;
   if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
-  constexpr size_t lds = (size_t)kBBuf * (2 * (kKvRows / 32) * BGeo<D>::TILEB + kBWaves * 1024);
+  constexpr size_t lds = (size_t)kBBuf * (2 * BGeo<D>::TILEB + kBWaves * 1024);
   static_assert(lds <= 160 * 1024, "gfx950 has 160 KB of LDS per workgroup");
   // more than 64 KB of dynamic LDS has to be asked for once per kernel (setting it twice, from two
   // host threads at once, is harmless)

@@ -61,6 +61,9 @@ int32_t move_heads(const ba_heads *h, const ba_tensor *real, void *padded, int64
   return BA_OK;
 }
 
+// rows of (log-sum-exp, delta) per token and KV head in the backward pass's workspace
+int32_t ld_group(int32_t group) { return (group + 3) & ~3; }
+
 }  // namespace
 
 extern "C" {
@@ -236,8 +239,9 @@ size_t ba_block_attention_prompts_backward_workspace_bytes(const ba_heads *heads
     pad_bytes = 4 * padded_rows_bytes(heads, T) + padded_lse_bytes(heads, T);
     hq = hkv * kPadGroup;
   }
-  // rotated scaled q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row (+ padding)
-  return pad_bytes + align256(T * hq * D * 2) + align256(T * hkv * D * 2) + align256(T * D * 4) + align256(T * hq * 8 + 16);
+  // rotated scaled q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row
+  return pad_bytes + align256(T * hq * D * 2) + align256(T * hkv * D * 2) + align256(T * D * 4) +
+         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8);
 }
 
 int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k,
@@ -312,7 +316,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   wsp += align256((size_t)T * hkv * D * 2);
   float *q_table = (float *)wsp;
   wsp += align256((size_t)T * D * 4);
-  float2 *ld = (float2 *)wsp;
+  float *ld = (float *)wsp;
 
   ba::RopeTable rt;
   build_rope_table(heads, &rt);
@@ -336,6 +340,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   bp.o_sh = o->stride_head;
   bp.lse = lse;
   bp.ld = ld;
+  bp.ld_group = ld_group(G);
   bp.T = T;
   bp.dq = (uint16_t *)dq_out->ptr;
   bp.dq_st = dq_out->stride_tok;

@@ -200,8 +200,10 @@ struct BwdParams {
   const uint16_t *o;     // the forward output, [T][n_q_heads][D] with these strides
   int64_t o_st, o_sh;
   const float *lse;      // [T][n_q_heads]: the forward pass's log-sum-exps
-  float2 *ld;            // [n_kv_heads][T][group]: (log-sum-exp / ln 2, delta) of query head kvh * group + g,
-                         // written by the dq kernel, read by the dk/dv kernel
+  float *ld;             // -log-sum-exp / ln 2 and -delta per packed row, written by the dq kernel, read by the dk/dv
+                         // kernel: per KV head and block, from 2 * (kvh * T + first token) * ld_group floats on, four
+                         // rows of the one and four rows of the other in turn
+  int32_t ld_group;      // the group rounded up to a multiple of four (keeps every block's start 16-byte aligned)
   int64_t T;
   uint16_t *dq, *dk, *dv;  // the gradients, with these strides
   int64_t dq_st, dq_sh, dk_st, dk_sh, dv_st, dv_sh;
