@@ -6,7 +6,8 @@
 // Nothing of the forward pass is kept but O and the rows' log-sum-exps L: P is recomputed as
 // exp(S - L).  Two kernels, so that every sum has one owner and no atomics are needed:
 //   - bwd_dq_kernel: a workgroup owns 128 packed query rows (as the forward kernel for short items
-//     does) and walks the key tiles its rows see; it accumulates dq^.
+//     does) and walks the key tiles its rows see; it accumulates dq^.  It rotates its query rows itself and
+//     leaves them in memory for the other kernel, with -L / ln 2 and -delta of every row.
 //   - bwd_dkv_kernel: a workgroup owns 128 keys of one block and KV head and walks the 32-row
 //     query tiles that see them (the rest of its own block, and the prompt's last block if it is a
 //     passage); it accumulates dk^ and dV over all query heads of the group.
@@ -189,14 +190,16 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   const int my_tok = (int)fast_div((uint32_t)my_row, p.group_div);
   const int my_key = dq + my_tok;
 
-  // ---- whole rows of q^ and dO for this wave, requested first (see the forward kernel) -----------
-  auto walk_rows = [&](uint32_t st, uint32_t sh, auto &&visit) __attribute__((always_inline)) {
+  // ---- whole rows of q and dO for this wave, requested first (see the forward kernel) ------------
+  // (Ofs: 32 bits where the host has checked that the offsets fit, 64 for q, whose strides are anyone's)
+  auto walk_rows = [&](auto st, auto sh, auto &&visit) __attribute__((always_inline)) {
+    typedef decltype(st) Ofs;
     const int wr_r0 = wave_row0 + lane / G::CPR;
     const int wr_tok0 = (int)fast_div((uint32_t)wr_r0, p.group_div);
     const int wr_g0 = wr_r0 - wr_tok0 * Gq;
-    uint32_t off = (uint32_t)wr_tok0 * st + (uint32_t)wr_g0 * sh;
+    Ofs off = (Ofs)wr_tok0 * st + (Ofs)wr_g0 * sh;
     int g = wr_g0;
-    const uint32_t d_in = 4u * sh, d_wrap = st + (uint32_t)(4 - Gq) * sh;
+    const Ofs d_in = 4 * sh, d_wrap = st + (Ofs)(4 - Gq) * sh;
 #pragma unroll
     for (int u = 0; u < G::KCH; ++u) {
       visit(u, off, wr_r0);
@@ -212,18 +215,18 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   u32x4_t ld_q[G::KCH], ld_do[G::KCH];
   {
     const char *qbase = (const char *)(p.q + (int64_t)q_tok0 * p.q_st + (int64_t)(kvh * Gq) * p.q_sh);
-    const uint32_t st = (uint32_t)p.q_st, sh = (uint32_t)p.q_sh;
-    const uint32_t last_off = (uint32_t)(lq - 1) * st + (uint32_t)(Gq - 1) * sh;
-    walk_rows(st, sh, [&](int u, uint32_t off, int wr_r0) __attribute__((always_inline)) {
-      const uint32_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
-      ld_q[u] = *reinterpret_cast<const u32x4_t *>(qbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
+    const int64_t st = p.q_st, sh = p.q_sh;
+    const int64_t last_off = (int64_t)(lq - 1) * st + (int64_t)(Gq - 1) * sh;
+    walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
+      const int64_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
+      ld_q[u] = *reinterpret_cast<const u32x4_t *>(qbase + (o * 2 + (lane % G::CPR) * 16));
     });
   }
   {
     const char *dbase = (const char *)(bp.dout + (int64_t)q_tok0 * bp.do_st + (int64_t)(kvh * Gq) * bp.do_sh);
     const uint32_t st = (uint32_t)bp.do_st, sh = (uint32_t)bp.do_sh;
     const uint32_t last_off = (uint32_t)(lq - 1) * st + (uint32_t)(Gq - 1) * sh;
-    walk_rows(st, sh, [&](int u, uint32_t off, int wr_r0) __attribute__((always_inline)) {
+    walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       const uint32_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
       ld_do[u] = *reinterpret_cast<const u32x4_t *>(dbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
     });
@@ -234,7 +237,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const char *obase = (const char *)(bp.o + (int64_t)q_tok0 * bp.o_st + (int64_t)(kvh * Gq) * bp.o_sh);
     const uint32_t st = (uint32_t)bp.o_st, sh = (uint32_t)bp.o_sh;
     const uint32_t last_off = (uint32_t)(lq - 1) * st + (uint32_t)(Gq - 1) * sh;
-    walk_rows(st, sh, [&](int u, uint32_t off, int wr_r0) __attribute__((always_inline)) {
+    walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       const uint32_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
       ld_o[u] = *reinterpret_cast<const u32x4_t *>(obase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
     });
@@ -267,15 +270,38 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     }
   };
   constexpr int kOpsPerTile = 2 * G::IPW;
-  issue_copy(0, 0);  // (buffer 2 holds the waves' slices until the first barrier)
+  // the pre-pass's table rows of this wave's tokens (at most 8: groups of four or more), 16-byte piece c of
+  // row t at c ^ (t & 7), into this wave's slice of buffer 2; they come in here, the rows themselves pass
+  // through the slice behind them
+  constexpr uint32_t TROW = D * 4;
+  constexpr int TCH = TROW / 16, kTabOps = 8 * TROW / 1024;
+  static_assert(kBWaves * G::SLICEB <= 2 * TB && 8 * TROW <= G::SLICEB, "the slices fit one tile buffer");
+  const uint32_t s_ofs = 2 * (2 * TB) + wave * G::SLICEB;
+  const int first_tok_wave = first_key_wave - dq;
+  {
+    const char *tbase = (const char *)(p.q_table + (int64_t)q_tok0 * D);
+#pragma unroll
+    for (int u = 0; u < kTabOps; ++u) {
+      const int t = u * (1024 / TROW) + lane / TCH, pc = lane % TCH;
+      const uint32_t tok = (uint32_t)min(first_tok_wave + t, lq - 1);
+      lds_dma16(tbase, tok * TROW + (uint32_t)((pc ^ (t & 7)) << 4), (uint32_t)(uintptr_t)smem + s_ofs + u * 1024);
+    }
+  }
+  issue_copy(0, 0);
   if (1 < n_t) issue_copy(1, 1);
   __builtin_amdgcn_sched_barrier(0);
   dma_wait<0>();
 
   // ---- whole rows -> B-operand fragments (lane = row), 16 rows at a time through this wave's slice ----
-  static_assert(kBWaves * G::SLICEB <= 2 * TB, "the slices fit one tile buffer");
-  const uint32_t s_ofs = 2 * (2 * TB) + wave * G::SLICEB;
-  auto rows_to_frags = [&](const u32x4_t (&ld)[G::KCH], bf16x8_t (&out)[G::KCH]) __attribute__((always_inline)) {
+  f32x4_t cs[2 * G::KCH];
+  {
+    const int tl = max(my_tok - first_tok_wave, 0);  // this lane's row of the table slice
+#pragma unroll
+    for (int j = 0; j < 2 * G::KCH; ++j)
+      cs[j] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4_t *>(
+          smem + s_ofs + (uint32_t)tl * TROW + (uint32_t)((fragment_table_piece(j, hf, p.rope_layout != 0) ^ (tl & 7)) << 4));
+  }
+  auto rows_to_frags = [&](const u32x4_t (&ld)[G::KCH], u32x4_t (&out)[G::KCH]) __attribute__((always_inline)) {
     u32x4_t got[2][G::KCH];
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -289,13 +315,9 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
             smem + s_ofs + tile_ofs<D>(col & 15, kk * 2 + hf));
     }
 #pragma unroll
-    for (int kk = 0; kk < G::KCH; ++kk) {
-      u32x4_t w;
+    for (int kk = 0; kk < G::KCH; ++kk)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (col >> 4) ? got[1][kk][e] : got[0][kk][e];
-      asm volatile("" : "+v"(w));
-      out[kk] = __builtin_bit_cast(bf16x8_t, w);
-    }
+      for (int e = 0; e < 4; ++e) out[kk][e] = (col >> 4) ? got[1][kk][e] : got[0][kk][e];
   };
   // delta of this wave's rows: a row's CPR lanes add up their pieces, one of them hands the sum over
   // through the slice to the lane that owns the row; -L / ln 2 and -delta also go to memory in packed-row
@@ -303,17 +325,19 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   // accumulators start at them, and read them from its tile as they lie
   float2 my_ld;
   {
+    float mine = 0.f;  // lane j of a run of CPR lanes takes the sum of the run's j-th row
 #pragma unroll
     for (int u = 0; u < G::KCH; ++u) {
       float part = 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         part += bf16_lo(ld_o[u][e]) * bf16_lo(ld_do[u][e]) + bf16_hi(ld_o[u][e]) * bf16_hi(ld_do[u][e]);
-#pragma unroll
-      for (int m = 1; m < G::CPR; m <<= 1) part += __shfl_xor(part, m, 64);
-      if (lane % G::CPR == 0)
-        *reinterpret_cast<__attribute__((address_space(3))) float *>(smem + s_ofs + (u * G::QRPI + lane / G::CPR) * 4) = part;
+      part = sum_over_lanes<G::CPR>(part);
+      mine = lane % G::CPR == u ? part : mine;
     }
+    if (lane % G::CPR < G::KCH)
+      *reinterpret_cast<__attribute__((address_space(3))) float *>(
+          smem + s_ofs + ((lane % G::CPR) * G::QRPI + lane / G::CPR) * 4) = mine;
     const int r_in_wave = min(col, max(wave_last_row - wave_row0, 0));  // (lanes beyond the block's rows: its last row)
     my_ld.y = *reinterpret_cast<const __attribute__((address_space(3))) float *>(smem + s_ofs + r_in_wave * 4);
     my_ld.x = my_lse * kLog2e;
@@ -323,9 +347,26 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
       dst[hf * 4] = hf ? -my_ld.y : -my_ld.x;  // the two halves of the wave hold the same rows
     }
   }
+  // q^ = the rows rotated and scaled, this kernel's operand and, in memory, what the dk/dv kernel walks
   bf16x8_t qf[G::KCH], dof[G::KCH];
-  rows_to_frags(ld_q, qf);
-  rows_to_frags(ld_do, dof);
+  {
+    u32x4_t raw[G::KCH];
+    rows_to_frags(ld_q, raw);
+    rotate_fragments<G::KCH>(raw, cs, p.rope_layout != 0);
+    uint16_t *dst = bp.q_rot + ((int64_t)(q_tok0 + my_tok) * p.n_q_heads + kvh * Gq + (my_row - my_tok * Gq)) * D + hf * 8;
+    const bool mine = wave_row0 + col < n_rows;
+#pragma unroll
+    for (int kk = 0; kk < G::KCH; ++kk) {
+      if (mine) *reinterpret_cast<u32x4_t *>(dst + kk * 16) = raw[kk];
+      qf[kk] = __builtin_bit_cast(bf16x8_t, raw[kk]);
+    }
+    rows_to_frags(ld_do, raw);
+#pragma unroll
+    for (int kk = 0; kk < G::KCH; ++kk) {
+      asm volatile("" : "+v"(raw[kk]));
+      dof[kk] = __builtin_bit_cast(bf16x8_t, raw[kk]);
+    }
+  }
 
   f32x16_t acc[G::DT];
 #pragma unroll
@@ -337,7 +378,10 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   int buf = 0;
 #pragma unroll 1
   for (int i = 0; i < n_t; ++i) {
-    if (i + 1 < n_t) dma_wait<kOpsPerTile>(); else dma_wait<0>();
+    // (tiles 0 and 1 have landed; waiting here would be for the stores of q^)
+    if (i >= 2) {
+      if (i + 1 < n_t) dma_wait<kOpsPerTile>(); else dma_wait<0>();
+    }
     wg_barrier();
     if (i + 2 < n_t) issue_copy(i + 2, buf == 0 ? 2 : buf - 1);
     if (i < wave_n_t) {
@@ -418,7 +462,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
       w[u] = *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t *>(
           stage + tile_ofs<D>(u * G::QRPI + ln / G::CPR, ln % G::CPR));
     char *obase = (char *)(bp.dq + (int64_t)q_tok0 * bp.dq_st + (int64_t)(kvh * Gq) * bp.dq_sh);
-    walk_rows((uint32_t)bp.dq_st, (uint32_t)bp.dq_sh, [&](int u, uint32_t off, int wr_r0) __attribute__((always_inline)) {
+    walk_rows((uint32_t)bp.dq_st, (uint32_t)bp.dq_sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       if (wr_r0 < n_rows - u * G::QRPI)
         *reinterpret_cast<u32x4_t *>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u)) = w[u];
     });
@@ -491,7 +535,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   // the same distances from the first of them in every instruction: the lanes' offsets are worked out
   // here, and a tile costs scalar arithmetic only.  Otherwise, and in the last tile of a block (rows
   // beyond the block repeat its last row), every lane finds its own row.
-  const uint32_t q_st = (uint32_t)p.q_st, q_sh = (uint32_t)p.q_sh, do_st = (uint32_t)bp.do_st, do_sh = (uint32_t)bp.do_sh;
+  const uint32_t q_st = (uint32_t)(p.n_q_heads * D), q_sh = D, do_st = (uint32_t)bp.do_st, do_sh = (uint32_t)bp.do_sh;
   const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + wave * IPW * G::GRPB;
   const uint32_t lds_ld = (uint32_t)(uintptr_t)smem + 2 * TB + wave * 1024;
   const uint32_t c_chunk = (uint32_t)((lane % G::CPR) ^ (granule_xor<D>(lane / G::CPR) << 2) ^ low_xor<D>(lane / G::CPR)) << 4;
@@ -508,7 +552,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
     const int r0 = (own ? tile_a0 + t : t - n_a) * kKvRows;  // first packed row of the tile, inside its block
     const int tok0 = own ? k_tok0 : f_tok0;
     const int n_rows = own ? n_rows_a : n_rows_f;
-    const char *qb = (const char *)(p.q + (int64_t)tok0 * p.q_st + (int64_t)(kvh * Gq) * p.q_sh);
+    const char *qb = (const char *)(bp.q_rot + ((int64_t)tok0 * p.n_q_heads + kvh * Gq) * D);
     const char *db = (const char *)(bp.dout + (int64_t)tok0 * bp.do_st + (int64_t)(kvh * Gq) * bp.do_sh);
     const uint32_t lds_tile = lds_copy + (uint32_t)buf * BUFB;
     if (regular && r0 + kKvRows <= n_rows) {
@@ -610,11 +654,15 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
           }
         }
       }
-      // Rows this key may not see: rows beyond the block, and (own block) tokens before the key.  Their
-      // exponent starts, and so ends, at minus infinity: P = 0, and with a finite dP dS = 0 too.  Done
-      // here, under one branch that most tiles do not take, the products and exponentials below are the
-      // same straight code for every tile (with the tests behind the exponentials, each under a branch of
-      // its own, a tile took 312 vector instructions instead of some 120).
+#pragma unroll
+      for (int kk = 0; kk < G::KCH; ++kk) {
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(bq + r_rd[kk / 2], kk), kf[kk], sacc, 0, 0, 0);
+        dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(bq + r_rd[kk / 2] + TB, kk), vf[kk], dpacc, 0, 0, 0);
+      }
+      // Rows this key may not see: rows beyond the block, and (own block) tokens before the key; their P and
+      // dS become 0 whatever the products gave.  Under one branch, which most tiles do not take, the
+      // exponentials below are the same straight code for every tile (with the tests behind them, each
+      // under a branch of its own, a tile took 312 vector instructions instead of some 120).
       const bool ragged = r0 + kKvRows > n_rows;
       const bool diagonal = own && r0 < (kw0 + 31) * Gq;
       if (ragged || diagonal) {
@@ -626,11 +674,6 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
           sacc[v] = out ? -INFINITY : sacc[v];
           dpacc[v] = out ? 0.f : dpacc[v];
         }
-      }
-#pragma unroll
-      for (int kk = 0; kk < G::KCH; ++kk) {
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(bq + r_rd[kk / 2], kk), kf[kk], sacc, 0, 0, 0);
-        dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(bq + r_rd[kk / 2] + TB, kk), vf[kk], dpacc, 0, 0, 0);
       }
       bf16x8_t pf[2], dsf[2];
 #pragma unroll

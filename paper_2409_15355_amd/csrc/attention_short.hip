@@ -255,15 +255,13 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
 
   // ---- rotate (or just scale) the Q rows into the fragments ---------------------------------------
   dma_wait<0>();  // the table rows and the first tile (this wave's share) have landed
-  // The table first: entry j of a table row = (cos, sin) of pair j.  Interleaved pairs: fragment kk
-  // holds pairs kk * 8 + hf * 4 + (0..3); half-split pairs: fragments kk and kk + KCH/2 hold dims
-  // kk * 16 + hf * 8 + (0..7) and their partners, i.e. pairs of those same numbers.
+  // the table first
   f32x4_t cs[2 * G::KCH];
   if (p.q_table) {
     const bool halves = p.rope_layout != 0;
 #pragma unroll
     for (int j = 0; j < 2 * G::KCH; ++j) {
-      const int c = halves ? (j / 4) * 8 + (j & 3) + hf * 4 : (j / 2) * 4 + (j & 1) + hf * 2;
+      const int c = fragment_table_piece(j, hf, halves);
       cs[j] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4_t *>(
           smem + tab_ofs + (uint32_t)(tab_tl * TROW + ((c ^ (tab_tl & 7)) << 4)));
     }
@@ -295,32 +293,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   }
   bf16x8_t qf[G::KCH];
   if (p.q_table) {
-    const bool halves = p.rope_layout != 0;
-    if (!halves) {
-#pragma unroll
-      for (int kk = 0; kk < G::KCH; ++kk) {
-        const f32x4_t cs0 = cs[2 * kk], cs1 = cs[2 * kk + 1];
-        const float c[4] = {cs0[0], cs0[2], cs1[0], cs1[2]}, sn[4] = {cs0[1], cs0[3], cs1[1], cs1[3]};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x = bf16_lo(raw[kk][e]), y = bf16_hi(raw[kk][e]);
-          raw[kk][e] = pack_bf16(c[e] * x - sn[e] * y, sn[e] * x + c[e] * y);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < G::KCH / 2; ++kk) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const f32x4_t t = cs[4 * kk + e];  // pairs kk * 16 + hf * 8 + 2 e and the next
-          const float c0 = t[0], s0 = t[1], c1 = t[2], s1 = t[3];
-          const uint32_t wa = raw[kk][e], wb = raw[kk + G::KCH / 2][e];
-          const float xa0 = bf16_lo(wa), xa1 = bf16_hi(wa), xb0 = bf16_lo(wb), xb1 = bf16_hi(wb);
-          raw[kk][e] = pack_bf16(c0 * xa0 - s0 * xb0, c1 * xa1 - s1 * xb1);
-          raw[kk + G::KCH / 2][e] = pack_bf16(s0 * xa0 + c0 * xb0, s1 * xa1 + c1 * xb1);
-        }
-      }
-    }
+    rotate_fragments<G::KCH>(raw, cs, p.rope_layout != 0);
   } else if (!p.q_ready) {
     const float c2 = p.scale_log2e;
 #pragma unroll

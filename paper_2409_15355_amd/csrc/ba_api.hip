@@ -164,8 +164,7 @@ int32_t run_reencode(ba::ReencParams p, const ba::RopeTable &rt, int n_blocks, c
 int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_tensor *q, uint16_t *q_rot,
                          const ba_tensor *k, const ba_tensor *k_rot, int n, const int32_t *start,
                          const int32_t *pos0, hipStream_t stream, const ba::RopeRots *rots,
-                         const ba::RopeRotsSmall *rots_small, float *rot_dst, int n_rot, float *q_table, bool rows_too,
-                         int table_rows) {
+                         const ba::RopeRotsSmall *rots_small, float *rot_dst, int n_rot, float *q_table, int table_rows) {
   const int64_t tokens = (int64_t)start[n] - start[0];
   if (tokens <= 0) return BA_OK;
   ba::RopePrepassParams p;
@@ -190,7 +189,7 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
   p.layout = h->rope_layout;
   // few tokens: one head per thread (more, shorter threads); many: sin/cos shared by several heads
   p.heads_per_thread = tokens >= 16384 ? 8 : (tokens >= 2048 ? 2 : 1);
-  p.do_q = q_table ? (rows_too ? 3 : 2) : 1;  // a table of factors for the attention core, rotated rows, or both
+  p.do_q = q_table ? 2 : 1;  // a table of factors for the attention core, or rotated rows
   p.q_table = q_table;
   if (table_rows > 0) {  // the table by position (every segment starts at position 0), no rotated rows
     p.do_q = 4;
@@ -408,7 +407,7 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
       // local positions: every block starts at 0, so one table of factors by position serves all blocks
       // (as many rows as the longest block has tokens; written by the first launch)
       if ((rc = run_rope_prepass(heads, rt, q, nullptr, k, &k_use, n, meta[0].offs, nullptr, stream, nullptr, nullptr,
-                                 nullptr, 0, q_table, false, table_written ? -1 : (int)longest_block)))
+                                 nullptr, 0, q_table, table_written ? -1 : (int)longest_block)))
         return rc;
       table_written = true;
     }

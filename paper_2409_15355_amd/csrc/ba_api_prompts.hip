@@ -325,8 +325,8 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   for (int n = 0; n <= n_prompts; ++n) starts[n] = block_offsets[cu_blk[n]];
   for (int n0 = 0; n0 < n_prompts; n0 += ba::kRopeMaxSegs) {
     const int n = std::min(ba::kRopeMaxSegs, n_prompts - n0);
-    if ((rc = run_rope_prepass(heads, rt, q, q_rot, k, &k_rot, n, starts.data() + n0, nullptr, stream, nullptr, nullptr,
-                               nullptr, 0, q_table, true)))
+    if ((rc = run_rope_prepass(heads, rt, q, nullptr, k, &k_rot, n, starts.data() + n0, nullptr, stream, nullptr, nullptr,
+                               nullptr, 0, q_table)))
       return rc;
   }
 
@@ -339,6 +339,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   bp.o_st = o->stride_tok;
   bp.o_sh = o->stride_head;
   bp.lse = lse;
+  bp.q_rot = q_rot;
   bp.ld = ld;
   bp.ld_group = ld_group(G);
   bp.T = T;
@@ -356,9 +357,9 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
 
   ba::AttnParams ap;
   memset(&ap, 0, sizeof(ap));
-  ap.q = q_rot;
-  ap.q_st = (int64_t)hq * D;
-  ap.q_sh = D;
+  ap.q = (const uint16_t *)q->ptr;
+  ap.q_st = q->stride_tok;
+  ap.q_sh = q->stride_head;
   ap.kf = (const uint16_t *)k_rot.ptr;
   ap.kf_st = k_rot.stride_tok;
   ap.kf_sh = k_rot.stride_head;

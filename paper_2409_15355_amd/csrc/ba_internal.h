@@ -92,7 +92,6 @@ struct RopePrepassParams {
   float *rot_dst;    // [n_rot][D/2][2]: (cos, sin) of rot_angle[b] * theta_j, or null
   int32_t n_rot;
   float *q_table;    // do_q == 2: instead of rotating Q rows, write q_scale * (cos, sin) per token: [tokens][D/2][2];
-                     // do_q == 3: both the rotated rows and the table;
                      // do_q == 4: the table only, by position: row r = q_scale * (cos, sin) of position r,
                      //            r < table_rows (for calls all of whose segments start at position 0)
   int32_t table_rows;
@@ -200,6 +199,7 @@ struct BwdParams {
   const uint16_t *o;     // the forward output, [T][n_q_heads][D] with these strides
   int64_t o_st, o_sh;
   const float *lse;      // [T][n_q_heads]: the forward pass's log-sum-exps
+  uint16_t *q_rot;       // [T][n_q_heads][D]: q rotated and times scale * log2 e, written by the dq kernel, read by the dk/dv kernel
   float *ld;             // -log-sum-exp / ln 2 and -delta per packed row, written by the dq kernel, read by the dk/dv
                          // kernel: per KV head and block, from 2 * (kvh * T + first token) * ld_group floats on, four
                          // rows of the one and four rows of the other in turn

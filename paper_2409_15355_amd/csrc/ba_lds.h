@@ -2,6 +2,8 @@
 // barriers that go with them, the half-wave exchange, and the search in a table of tile starts.
 #pragma once
 
+#include <type_traits>
+
 #include "ba_device.h"
 
 namespace ba {
@@ -52,6 +54,58 @@ __device__ __forceinline__ void lds_dma16(const char *base, uint32_t offset, uin
 __device__ __forceinline__ void wg_barrier() {
   asm volatile("s_barrier" ::: "memory");
 }
+// Query rows in fragment layout (lane = row; fragment kk holds 16-byte chunk 2 kk + hf) times the row's
+// entry of the pre-pass's table of (cos, sin) times some factor, rounded once.  The table row's 16-byte
+// pieces that a lane needs, in the order of `cs`: fragment_table_piece(j, ...).  Interleaved pairs: fragment kk
+// holds pairs kk * 8 + hf * 4 + (0..3); half-split pairs: fragments kk and kk + KCH/2 hold dims
+// kk * 16 + hf * 8 + (0..7) and their partners, i.e. pairs of those same numbers.
+__device__ __forceinline__ int fragment_table_piece(int j, int hf, bool halves) {
+  return halves ? (j / 4) * 8 + (j & 3) + hf * 4 : (j / 2) * 4 + (j & 1) + hf * 2;
+}
+template <int KCH>
+__device__ __forceinline__ void rotate_fragments(u32x4_t (&raw)[KCH], const f32x4_t (&cs)[2 * KCH], bool halves) {
+  if (!halves) {
+#pragma unroll
+    for (int kk = 0; kk < KCH; ++kk) {
+      const f32x4_t cs0 = cs[2 * kk], cs1 = cs[2 * kk + 1];
+      const float c[4] = {cs0[0], cs0[2], cs1[0], cs1[2]}, sn[4] = {cs0[1], cs0[3], cs1[1], cs1[3]};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = bf16_lo(raw[kk][e]), y = bf16_hi(raw[kk][e]);
+        raw[kk][e] = pack_bf16(c[e] * x - sn[e] * y, sn[e] * x + c[e] * y);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < KCH / 2; ++kk) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x4_t t = cs[4 * kk + e];  // pairs kk * 16 + hf * 8 + 2 e and the next
+        const float c0 = t[0], s0 = t[1], c1 = t[2], s1 = t[3];
+        const uint32_t wa = raw[kk][e], wb = raw[kk + KCH / 2][e];
+        const float xa0 = bf16_lo(wa), xa1 = bf16_hi(wa), xb0 = bf16_lo(wb), xb1 = bf16_hi(wb);
+        raw[kk][e] = pack_bf16(c0 * xa0 - s0 * xb0, c1 * xa1 - s1 * xb1);
+        raw[kk + KCH / 2][e] = pack_bf16(s0 * xa0 + c0 * xb0, s1 * xa1 + c1 * xb1);
+      }
+    }
+  }
+}
+
+// Sum over each run of N consecutive lanes (8 or 16), in every lane of the run: adds of neighbours
+// through the vector unit's own lane permutations, no trip through LDS.
+template <int N>
+__device__ __forceinline__ float sum_over_lanes(float x) {
+  static_assert(N == 8 || N == 16, "runs inside one row of sixteen lanes");
+  auto add = [&](auto ctrl) __attribute__((always_inline)) {
+    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  add(std::integral_constant<int, 0xb1>{});   // lane ^ 1
+  add(std::integral_constant<int, 0x4e>{});   // lane ^ 2
+  add(std::integral_constant<int, 0x141>{});  // the other four of eight (mirrored: they all hold one sum)
+  if constexpr (N == 16) add(std::integral_constant<int, 0x140>{});  // the other eight of sixteen
+  return x;
+}
+
 template <int NEWER>
 __device__ __forceinline__ void dma_wait() {
   static_assert(NEWER >= 0 && NEWER < 64, "vmcnt is a 6-bit counter");
