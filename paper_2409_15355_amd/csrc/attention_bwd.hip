@@ -8,7 +8,7 @@
 //   - bwd_dq_kernel: a workgroup owns 128 packed query rows (as the forward kernel for short items
 //     does) and walks the key tiles its rows see; it accumulates dq^.  It rotates its query rows itself and
 //     leaves them in memory for the other kernel, with -L / ln 2 and -delta of every row.
-//   - bwd_dkv_kernel: a workgroup owns 128 keys of one block and KV head and walks the 32-row
+//   - bwd_dkv_kernel: a workgroup owns 64 keys of one block and KV head and walks the 32-row
 //     query tiles that see them (the rest of its own block, and the prompt's last block if it is a
 //     passage); it accumulates dk^ and dV over all query heads of the group.
 // Each turns its gradient of the rotated tensor back to the un-rotated frame in its epilogue, with the
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   const uint32_t n_rowtiles = (uint32_t)p.total_tiles;
   const int kvh = (int)fast_div(id, p.tiles_div);
   const int rowtile = (int)(id - (uint32_t)kvh * n_rowtiles);
-  const int b = find_segment(meta.tile_start, meta.n, rowtile);
+  const int b = find_block(meta.tile_start, rowtile);
   const int q_tok0 = meta.start[b], lq = meta.len[b], k_tok0 = meta.kstart[b];
   const int jt = rowtile - meta.tile_start[b];
   const int dq = q_tok0 - k_tok0;  // the block's first token, counted in keys
@@ -470,18 +470,32 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
 }
 
 // ---------------------------------------------------------------------------------------------------
+// dk and dV.  The accumulators of 32 keys (dK^ and dV: 128 registers) and their rows (K^ and V: 64) leave
+// one wave no registers to look ahead with and a SIMD no room for more than two such waves, so a pair of
+// waves shares 32 keys, each with half of everything:
+//   wave A: S = q^ K^^T, P = 2^S -> LDS, dV^T += dO^T P        wave B: dP = dO V^T, dS = P o dP, dK^^T += q^^T dS
+// P passes between them in 32 bits, lane for lane (both hold the pair's tile in one layout); the two have
+// eight products before and eight behind the exchange, and fit three waves to a SIMD.
 template <int D>
-__global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, BwdKvMeta meta, BwdParams bp) {
+struct KvGeo {
   using G = BGeo<D>;
+  static constexpr uint32_t TB = G::TILEB;
+  static constexpr uint32_t BUFB = 2 * TB + kBWaves * 128;  // a q^ tile, a dO tile, per wave its rows' -L or -delta
+  static constexpr int IPW = kBKeys / G::RPI / 2;           // LDS-direct loads of one wave per tile (one tensor's half)
+  static constexpr uint32_t PEXB = 4096;                    // a pair's P: 32 x 32 floats
+  static constexpr size_t LDS = 2 * (size_t)BUFB + kBWaves / 2 * PEXB;
+  static_assert(kKvRows == kBKeys && kBwdTileKeys == kBWaves / 2 * 32, "a tile of 32 packed query rows, a pair of waves per 32 keys");
+};
+
+template <int D>
+__global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, BwdKvMeta meta, BwdParams bp) {
+  using G = BGeo<D>;
+  using KG = KvGeo<D>;
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char *smem = (lds_char *)smem_generic;
-  // LDS map: buffer b = bytes [b BUFB, (b + 1) BUFB): a q^ tile, a dO tile (kKvRows packed query rows
-  // each), then per wave 1 KB whose first 256 bytes hold the rows' (-L / ln 2, -delta), four rows of
-  // the one and four of the other in turn
-  constexpr uint32_t TB = G::TILEB;
-  constexpr uint32_t BUFB = 2 * TB + kBWaves * 1024;
-  constexpr int IPW = G::IPW;  // LDS-direct loads per wave, tile and tensor
-  static_assert(kKvRows == 32, "one accumulator tile of query rows");
+  // LDS map: two buffers of BUFB, then the pairs' exchange
+  constexpr uint32_t TB = KG::TB, BUFB = KG::BUFB;
+  constexpr int IPW = KG::IPW;
 
   uint32_t id = blockIdx.x;
   {
@@ -492,36 +506,41 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   const uint32_t n_keytiles = (uint32_t)p.total_tiles;
   const int kvh = (int)fast_div(id, p.tiles_div);
   const int keytile = (int)(id - (uint32_t)kvh * n_keytiles);
-  const int b = find_segment(meta.tile_start, meta.n, keytile);
+  const int b = find_block(meta.tile_start, keytile);
   const int k_tok0 = meta.start[b], lk = meta.len[b];  // the block that owns the keys
   const int f_tok0 = meta.fin_start[b], lf = meta.fin_len[b];  // its prompt's last block, if it is a passage
-  const int k0 = (keytile - meta.tile_start[b]) * kShortTileRows;  // the workgroup's first key, inside the block
+  const int k0 = (keytile - meta.tile_start[b]) * kBwdTileKeys;  // the workgroup's first key, inside the block
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pair = wave >> 1;
+  const bool is_b = wave & 1;
   const int col = lane & 31, hf = lane >> 5;
   const int Gq = p.group;
-  const int kw0 = k0 + wave * 32;  // this wave's first key
+  const int kw0 = k0 + pair * 32;  // this pair's first key
   const bool wave_has_keys = kw0 < lk;
   const int my_key = kw0 + col;    // (may lie beyond the block: such columns are never stored)
 
-  // ---- query row tiles that see these keys: the block's own rows from the first key's token on,
-  //      then every row of the prompt's last block ------------------------------------------------
+  // ---- query row tiles that see these keys: every row of the prompt's last block, then the block's own
+  //      rows, both from the end to the front, down to the first key's token.  The workgroups of a block
+  //      start together and so meet each tile at about the same time, in one XCD's L2; walked from the
+  //      front, each starts at a row of its own and fetches its tiles alone (1692 MB per launch at 33,130
+  //      tokens where q^ and dO are 542) ---------------------------------------------------------------
   const int n_rows_a = lk * Gq, n_rows_f = lf * Gq;
-  const int tile_a0 = (k0 * Gq) / kKvRows;
-  const int n_a = (n_rows_a + kKvRows - 1) / kKvRows - tile_a0;
-  const int n_t = n_a + (n_rows_f + kKvRows - 1) / kKvRows;
+  const int n_f = (n_rows_f + kKvRows - 1) / kKvRows;
+  const int n_t = n_f + (n_rows_a + kKvRows - 1) / kKvRows - (k0 * Gq) / kKvRows;
+  const int own_last = ((n_rows_a - 1) / kKvRows) * kKvRows;  // first row of the block's last tile
+  const int fin_last = (n_f - 1) * kKvRows;
 
-  // ---- this wave's keys as B operands: k^ and v rows, whole, then into fragments through LDS ----
-  u32x4_t ld_k[G::KCH], ld_v[G::KCH];
+  // ---- this wave's operand: the pair's K^ rows (A) or V rows (B), whole, then fragments through LDS ----
+  u32x4_t ld_kv[G::KCH];
   {
-    const char *kb = (const char *)(p.kf + (int64_t)k_tok0 * p.kf_st + (int64_t)kvh * p.kf_sh);
-    const char *vb = (const char *)(p.vf + (int64_t)k_tok0 * p.vf_st + (int64_t)kvh * p.vf_sh);
+    const int64_t st = is_b ? p.vf_st : p.kf_st, sh = is_b ? p.vf_sh : p.kf_sh;
+    const char *base = (const char *)((is_b ? p.vf : p.kf) + (int64_t)k_tok0 * st + (int64_t)kvh * sh);
 #pragma unroll
     for (int u = 0; u < G::KCH; ++u) {
       const uint32_t tok = (uint32_t)min(kw0 + u * G::QRPI + lane / G::CPR, lk - 1);
-      ld_k[u] = *reinterpret_cast<const u32x4_t *>(kb + ((uint64_t)tok * (uint64_t)p.kf_st + (uint32_t)(lane % G::CPR) * 8u) * 2u);
-      ld_v[u] = *reinterpret_cast<const u32x4_t *>(vb + ((uint64_t)tok * (uint64_t)p.vf_st + (uint32_t)(lane % G::CPR) * 8u) * 2u);
+      ld_kv[u] = *reinterpret_cast<const u32x4_t *>(base + ((uint64_t)tok * (uint64_t)st + (uint32_t)(lane % G::CPR) * 8u) * 2u);
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -530,72 +549,74 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   row_read_bases<D>(r_rd, col, hf);
   tr_read_bases<D>(t_rd, lane);
 
-  // ---- tile fill: kKvRows packed query rows of q^ and of dO, and the rows' (L, delta) ------------------
-  // An instruction moves RPI packed rows.  Where RPI and the group divide one another, those rows lie at
-  // the same distances from the first of them in every instruction: the lanes' offsets are worked out
-  // here, and a tile costs scalar arithmetic only.  Otherwise, and in the last tile of a block (rows
-  // beyond the block repeat its last row), every lane finds its own row.
-  const uint32_t q_st = (uint32_t)(p.n_q_heads * D), q_sh = D, do_st = (uint32_t)bp.do_st, do_sh = (uint32_t)bp.do_sh;
-  const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + wave * IPW * G::GRPB;
-  const uint32_t lds_ld = (uint32_t)(uintptr_t)smem + 2 * TB + wave * 1024;
+  // ---- tile fill: kKvRows packed query rows of q^ (the A waves) and of dO (the B waves), and per wave the
+  //      rows' -L / ln 2 or -delta.  Where the group divides 32, every tile begins with a token's first
+  //      head and its rows lie at the same distances from there: the lanes' offsets are worked out once and
+  //      a tile moves one pointer (the copy goes out between two barriers, ahead of the products; with the
+  //      rows divided out per instruction a wave spent 180 scalar instructions on a tile).  Otherwise, and
+  //      in the last tile of a block (rows beyond the block repeat its last row), every lane finds its own ----
+  const uint32_t c_st = is_b ? (uint32_t)bp.do_st : (uint32_t)(p.n_q_heads * D), c_sh = is_b ? (uint32_t)bp.do_sh : (uint32_t)D;
+  const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + (is_b ? TB : 0u) + pair * IPW * G::GRPB;
+  const uint32_t lds_ld = (uint32_t)(uintptr_t)smem + 2 * TB + wave * 128;
+  const int c_row = pair * IPW * G::RPI + lane / G::CPR;  // this lane's row of the wave's first instruction
   const uint32_t c_chunk = (uint32_t)((lane % G::CPR) ^ (granule_xor<D>(lane / G::CPR) << 2) ^ low_xor<D>(lane / G::CPR)) << 4;
-  const bool regular = Gq % G::RPI == 0 || G::RPI % Gq == 0;
-  uint32_t q_in, do_in;  // this lane's row and chunk, in bytes from an instruction's first row
-  {
-    const uint32_t l = (uint32_t)lane / G::CPR;
-    const uint32_t tok = Gq < G::RPI ? fast_div(l, p.group_div) : 0u, g = l - tok * (uint32_t)Gq;
-    q_in = (tok * q_st + g * q_sh) * 2u + c_chunk;
-    do_in = (tok * do_st + g * do_sh) * 2u + c_chunk;
-  }
-  auto issue_copy = [&](int t, int buf) __attribute__((always_inline)) {
-    const bool own = t < n_a;
-    const int r0 = (own ? tile_a0 + t : t - n_a) * kKvRows;  // first packed row of the tile, inside its block
-    const int tok0 = own ? k_tok0 : f_tok0;
-    const int n_rows = own ? n_rows_a : n_rows_f;
-    const char *qb = (const char *)(bp.q_rot + ((int64_t)tok0 * p.n_q_heads + kvh * Gq) * D);
-    const char *db = (const char *)(bp.dout + (int64_t)tok0 * bp.do_st + (int64_t)(kvh * Gq) * bp.do_sh);
-    const uint32_t lds_tile = lds_copy + (uint32_t)buf * BUFB;
-    if (regular && r0 + kKvRows <= n_rows) {
-#pragma unroll
-      for (int u = 0; u < IPW; ++u) {
-        const uint32_t r = (uint32_t)(r0 + (wave * IPW + u) * G::RPI);
-        const uint32_t tok = fast_div(r, p.group_div), g = r - tok * (uint32_t)Gq;
-        lds_dma16(qb + (uint64_t)((tok * q_st + g * q_sh) * 2u), q_in, lds_tile + u * G::GRPB);
-        lds_dma16(db + (uint64_t)((tok * do_st + g * do_sh) * 2u), do_in, lds_tile + TB + u * G::GRPB);
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < IPW; ++u) {
-        const uint32_t r = (uint32_t)min(r0 + (wave * IPW + u) * G::RPI + lane / G::CPR, n_rows - 1);
-        const uint32_t tok = fast_div(r, p.group_div), g = r - tok * (uint32_t)Gq;
-        lds_dma16(qb, (tok * q_st + g * q_sh) * 2u + c_chunk, lds_tile + u * G::GRPB);
-        lds_dma16(db, (tok * do_st + g * do_sh) * 2u + c_chunk, lds_tile + TB + u * G::GRPB);
-      }
-    }
-    // (-L, -delta) of the rows: 32 contiguous bytes per four packed rows, the block's last four perhaps
-    // partly unwritten; every wave fetches its own copy (the upper lanes re-read the same bytes), so
-    // that all waves count alike
-    const char *lb = (const char *)(bp.ld + 2 * (((int64_t)kvh * bp.T + tok0) * bp.ld_group)) + (uint32_t)r0 * 8u;
-    const int last = (n_rows - 1 - r0) / 4 * 2 + 1;  // the last 16-byte piece that belongs to the block
-    lds_dma16(lb, (uint32_t)min(lane & 15, last) * 16u, lds_ld + (uint32_t)buf * BUFB);
+  auto row_ofs = [&](uint32_t r) __attribute__((always_inline)) {  // packed row r, in bytes from its block's first
+    const uint32_t tok = fast_div(r, p.group_div), g = r - tok * (uint32_t)Gq;
+    return (tok * c_st + g * c_sh) * 2u + c_chunk;
   };
-  constexpr int kOpsPerTile = 2 * IPW + 1;
+  const bool regular = kKvRows % Gq == 0;
+  const uint32_t c_step = regular ? (uint32_t)(kKvRows / Gq) * c_st * 2u : 0u;  // bytes from tile to tile
+  uint32_t c_in[IPW];
+#pragma unroll
+  for (int u = 0; u < IPW; ++u) c_in[u] = row_ofs((uint32_t)(c_row + u * G::RPI));
+  const char *c_base = nullptr, *l_base = nullptr;  // the next tile's rows (their block's first, if not regular); its -L, -delta
+  int c_row0 = 0, c_rows = 0;                       // its first packed row inside its block; the block's rows
+  auto enter_block = [&](int tok0, int row0, int rows) __attribute__((always_inline)) {
+    c_row0 = row0;
+    c_rows = rows;
+    c_base = is_b ? (const char *)(bp.dout + (int64_t)tok0 * bp.do_st + (int64_t)(kvh * Gq) * bp.do_sh)
+                  : (const char *)(bp.q_rot + ((int64_t)tok0 * p.n_q_heads + kvh * Gq) * D);
+    c_base += (uint64_t)(uint32_t)(row0 / kKvRows) * c_step;
+    l_base = (const char *)(bp.ld + 2 * (((int64_t)kvh * bp.T + tok0) * bp.ld_group)) + (uint32_t)row0 * 8u;
+  };
+  if (n_f > 0) enter_block(f_tok0, fin_last, n_rows_f);
+  auto issue_copy = [&](int t, int buf) __attribute__((always_inline)) {
+    if (t == n_f) enter_block(k_tok0, own_last, n_rows_a);
+    const uint32_t lds_tile = lds_copy + (uint32_t)buf * BUFB;
+    if (regular && c_row0 + kKvRows <= c_rows) {
+#pragma unroll
+      for (int u = 0; u < IPW; ++u) lds_dma16(c_base, c_in[u], lds_tile + u * G::GRPB);
+    } else {
+      const uint32_t from = regular ? (uint32_t)c_row0 : 0u;  // the row that c_base is at
+#pragma unroll
+      for (int u = 0; u < IPW; ++u)
+        lds_dma16(c_base, row_ofs((uint32_t)min(c_row0 + c_row + u * G::RPI, c_rows - 1) - from), lds_tile + u * G::GRPB);
+    }
+    // four rows of -L and four of -delta in turn, 16 bytes each (the block's last four perhaps partly
+    // unwritten; beyond them the last are read again): eight lanes fetch this wave's kind
+    if (lane < 8)
+      lds_dma16(l_base, (uint32_t)(min(lane, (c_rows - 1 - c_row0) >> 2) * 2 + (is_b ? 1 : 0)) * 16u, lds_ld + (uint32_t)buf * BUFB);
+    c_row0 -= kKvRows;
+    c_base -= c_step;
+    l_base -= kKvRows * 8;
+  };
   if (0 < n_t) issue_copy(0, 0);
-  if (1 < n_t) issue_copy(1, 1);
   __builtin_amdgcn_sched_barrier(0);
   dma_wait<0>();
 
-  // ---- k^ and v rows -> B-operand fragments through this wave's slice of buffer 2 -------------------
+  // ---- rows -> B-operand fragments through this wave's slice of buffer 1 (the first tile goes to buffer 0,
+  //      the second is asked for behind the first barrier) -----------------------------------------------
   static_assert(kBWaves * G::SLICEB <= 2 * TB, "the slices fit the tiles of one buffer");
-  const uint32_t s_ofs = 2 * BUFB + wave * G::SLICEB;
-  auto rows_to_frags = [&](const u32x4_t (&ld)[G::KCH], bf16x8_t (&out)[G::KCH]) __attribute__((always_inline)) {
+  bf16x8_t kv[G::KCH];
+  {
+    const uint32_t s_ofs = BUFB + wave * G::SLICEB;
     u32x4_t got[2][G::KCH];
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
       for (int u = 0; u < G::KCH / 2; ++u)
         *reinterpret_cast<__attribute__((address_space(3))) u32x4_t *>(
-            smem + s_ofs + tile_ofs<D>(u * G::QRPI + lane / G::CPR, lane % G::CPR)) = ld[pass * (G::KCH / 2) + u];
+            smem + s_ofs + tile_ofs<D>(u * G::QRPI + lane / G::CPR, lane % G::CPR)) = ld_kv[pass * (G::KCH / 2) + u];
 #pragma unroll
       for (int kk = 0; kk < G::KCH; ++kk)
         got[pass][kk] = *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t *>(
@@ -607,97 +628,92 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
 #pragma unroll
       for (int e = 0; e < 4; ++e) w[e] = (col >> 4) ? got[1][kk][e] : got[0][kk][e];
       asm volatile("" : "+v"(w));
-      out[kk] = __builtin_bit_cast(bf16x8_t, w);
+      kv[kk] = __builtin_bit_cast(bf16x8_t, w);
     }
-  };
-  bf16x8_t kf[G::KCH], vf[G::KCH];
-  rows_to_frags(ld_k, kf);
-  rows_to_frags(ld_v, vf);
+  }
 
-  f32x16_t dk[G::DT], dv[G::DT];
+  f32x16_t acc[G::DT];  // A: dV^T, B: dK^^T
 #pragma unroll
   for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      dk[dt][v] = 0.f;
-      dv[dt][v] = 0.f;
-    }
+    for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
 
-  // ---- the walk over the query row tiles ------------------------------------------------------------
-  int buf = 0;
+  // ---- the walk over the query row tiles: tile i lives in buffer i % 2.  Its first barrier says that
+  //      every wave's share of tile i has landed and that all are done with tile i - 1 and its P, so the
+  //      copy of tile i + 1 may overwrite that buffer; its second that the A waves' P lies in LDS ----------
+  typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+  lds_char *const pex = smem + 2 * BUFB + pair * KG::PEXB + lane * 16;
+  const uint32_t ofs1 = is_b ? TB : 0u, ofs2 = is_b ? 0u : TB;  // the tile of the products before the exchange, behind it
 #pragma unroll 1
   for (int i = 0; i < n_t; ++i) {
-    if (i + 1 < n_t) dma_wait<kOpsPerTile>(); else dma_wait<0>();
+    dma_wait<0>();
     wg_barrier();
-    if (i + 2 < n_t) issue_copy(i + 2, buf == 0 ? 2 : buf - 1);
-    const bool own = i < n_a;
-    const int r0 = (own ? tile_a0 + i : i - n_a) * kKvRows;
+    if (i + 1 < n_t) issue_copy(i + 1, (i + 1) & 1);
+    const bool own = i >= n_f;
+    const int r0 = own ? own_last - (i - n_f) * kKvRows : fin_last - i * kKvRows;  // the tile's first packed row, inside its block
     const int n_rows = own ? n_rows_a : n_rows_f;
-    // a tile of the block's own rows whose tokens all lie before this wave's first key sees none of them
+    lds_char *const buf = smem + (uint32_t)(i & 1) * BUFB;
+    // a tile of the block's own rows whose tokens all lie before this pair's first key sees none of them
     // (row = token * group + head: row r's token is at or behind key k exactly if r >= k * group)
-    if (wave_has_keys && !(own && min(r0 + kKvRows, n_rows) <= kw0 * Gq)) {
-      lds_char *const bq = smem + (uint32_t)buf * BUFB;  // this tile: q^ rows, then (TB on) dO rows
-      // The accumulators start at minus the rows' log-sum-exp and minus their delta, so that the
-      // products come out as the exponent of P and as dP - delta.  Register v of an accumulator is
-      // row (v >> 2) * 8 + hf * 4 + (v & 3): four runs of four rows.
-      f32x16_t sacc, dpacc;
-      {
-        const lds_char *at = bq + 2 * TB + wave * 1024 + hf * 32;
+    const bool active = wave_has_keys && !(own && min(r0 + kKvRows, n_rows) <= kw0 * Gq);
+    f32x16_t x;  // A: S - L, then P;  B: dP - delta
+    bf16x8_t pf[2];
+    if (active) {
+      // The accumulator starts at minus the rows' log-sum-exp or delta, so that the products come out as
+      // the exponent of P and as dP - delta.  Register v is row (v >> 2) * 8 + hf * 4 + (v & 3).
 #pragma unroll
-        for (int run = 0; run < 4; ++run) {
-          const f32x4_t nl = *reinterpret_cast<const __attribute__((address_space(3))) f32x4_t *>(at + run * 64);
-          const f32x4_t nd = *reinterpret_cast<const __attribute__((address_space(3))) f32x4_t *>(at + run * 64 + 16);
+      for (int run = 0; run < 4; ++run) {
+        const f32x4_t n4 = *(const lds_f32x4 *)(buf + 2 * TB + wave * 128 + run * 32 + hf * 16);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            sacc[run * 4 + e] = nl[e];
-            dpacc[run * 4 + e] = nd[e];
-          }
-        }
+        for (int e = 0; e < 4; ++e) x[run * 4 + e] = n4[e];
       }
 #pragma unroll
-      for (int kk = 0; kk < G::KCH; ++kk) {
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(bq + r_rd[kk / 2], kk), kf[kk], sacc, 0, 0, 0);
-        dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(bq + r_rd[kk / 2] + TB, kk), vf[kk], dpacc, 0, 0, 0);
-      }
+      for (int kk = 0; kk < G::KCH; ++kk)
+        x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(buf + ofs1 + r_rd[kk / 2], kk), kv[kk], x, 0, 0, 0);
       // Rows this key may not see: rows beyond the block, and (own block) tokens before the key; their P and
-      // dS become 0 whatever the products gave.  Under one branch, which most tiles do not take, the
-      // exponentials below are the same straight code for every tile (with the tests behind them, each
-      // under a branch of its own, a tile took 312 vector instructions instead of some 120).
-      const bool ragged = r0 + kKvRows > n_rows;
-      const bool diagonal = own && r0 < (kw0 + 31) * Gq;
-      if (ragged || diagonal) {
+      // dS become 0 whatever the products gave.  Under one branch, which most tiles do not take.
+      if (r0 + kKvRows > n_rows || (own && r0 < (kw0 + 31) * Gq)) {
         const int lo = own ? max(my_key * Gq - r0, 0) : 0;
         const uint32_t span = (uint32_t)max(n_rows - r0 - lo, 0);
+        const float nothing = is_b ? 0.f : -INFINITY;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const bool out = (uint32_t)((v >> 2) * 8 + (v & 3) + hf * 4 - lo) >= span;
-          sacc[v] = out ? -INFINITY : sacc[v];
-          dpacc[v] = out ? 0.f : dpacc[v];
-        }
+        for (int v = 0; v < 16; ++v)
+          x[v] = (uint32_t)((v >> 2) * 8 + (v & 3) + hf * 4 - lo) >= span ? nothing : x[v];
       }
-      bf16x8_t pf[2], dsf[2];
+      if (!is_b) {
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        u32x4_t wp, wd;
+        for (int v = 0; v < 16; ++v) x[v] = __builtin_amdgcn_exp2f(x[v]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int v = e * 8 + 2 * j;
-          const float p0 = __builtin_amdgcn_exp2f(sacc[v]), p1 = __builtin_amdgcn_exp2f(sacc[v + 1]);
-          wp[j] = pack_bf16(p0, p1);
-          wd[j] = pack_bf16(p0 * dpacc[v], p1 * dpacc[v + 1]);
+          const f32x4_t four = {x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3]};
+          *(lds_f32x4 *)(pex + j * 1024) = four;
         }
-        pf[e] = __builtin_bit_cast(bf16x8_t, wp);
-        dsf[e] = __builtin_bit_cast(bf16x8_t, wd);
+      }
+    }
+    lds_wait();
+    wg_barrier();
+    if (active) {
+      if (is_b) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const f32x4_t four = *(const lds_f32x4 *)(pex + j * 1024);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[4 * j + e] *= four[e];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        u32x4_t w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = pack_bf16(x[e * 8 + 2 * j], x[e * 8 + 2 * j + 1]);
+        pf[e] = __builtin_bit_cast(bf16x8_t, w);
       }
 #pragma unroll
       for (int kc = 0; kc < 2; ++kc)
 #pragma unroll
-        for (int dt = 0; dt < G::DT; ++dt) {
-          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag<D>(bq + t_rd[dt] + TB, kc), pf[kc], dv[dt], 0, 0, 0);
-          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag<D>(bq + t_rd[dt], kc), dsf[kc], dk[dt], 0, 0, 0);
-        }
+        for (int dt = 0; dt < G::DT; ++dt)
+          acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag<D>(buf + ofs2 + t_rd[dt], kc), pf[kc], acc[dt], 0, 0, 0);
     }
-    buf = buf == kBBuf - 1 ? 0 : buf + 1;
   }
 
   // ---- epilogue: dV as it is; dk^ = ln 2 * acc (the q^ tiles carry scale * log2 e), turned back to dk
@@ -707,37 +723,32 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dkv_kernel(AttnParams p, Bwd
   int ln = lane;
   asm volatile("" : "+v"(ln));
   const int ecol = ln & 31, ehf = ln >> 5;
-  rotate_back<D>(dk, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(k_tok0 + min(kw0 + ecol, lk - 1)) * D), ehf,
-                 p.rope_layout != 0, kLn2 / p.scale_log2e);
+  if (is_b)
+    rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(k_tok0 + min(kw0 + ecol, lk - 1)) * D), ehf,
+                   p.rope_layout != 0, kLn2 / p.scale_log2e);
+  static_assert(kBWaves * (size_t)G::TILEB <= KG::LDS, "the output staging fits");
   lds_char *stage = smem + wave * G::TILEB;
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
-    for (int dt = 0; dt < G::DT; ++dt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-        const f32x16_t &a = pass == 0 ? dv[dt] : dk[dt];
-        u32x2_t w;
-        w[0] = pack_bf16(a[q4 * 4 + 0], a[q4 * 4 + 1]);
-        w[1] = pack_bf16(a[q4 * 4 + 2], a[q4 * 4 + 3]);
-        *reinterpret_cast<__attribute__((address_space(3))) u32x2_t *>(stage + tile_ofs<D>(ecol, dt * 4 + q4) + ehf * 8) = w;
-      }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    uint16_t *dst = pass == 0 ? bp.dv : bp.dk;
-    const int64_t st = pass == 0 ? bp.dv_st : bp.dk_st, sh = pass == 0 ? bp.dv_sh : bp.dk_sh;
-#pragma unroll
-    for (int u = 0; u < G::KCH; ++u) {
-      const int rr = u * G::QRPI + ln / G::CPR;
-      const u32x4_t w = *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t *>(stage + tile_ofs<D>(rr, ln % G::CPR));
-      if (kw0 + rr < lk)
-        *reinterpret_cast<u32x4_t *>(dst + (int64_t)(k_tok0 + kw0 + rr) * st + (int64_t)kvh * sh + (ln % G::CPR) * 8) = w;
+    for (int q4 = 0; q4 < 4; ++q4) {
+      typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+      u32x2_t w;
+      w[0] = pack_bf16(acc[dt][q4 * 4 + 0], acc[dt][q4 * 4 + 1]);
+      w[1] = pack_bf16(acc[dt][q4 * 4 + 2], acc[dt][q4 * 4 + 3]);
+      *reinterpret_cast<__attribute__((address_space(3))) u32x2_t *>(stage + tile_ofs<D>(ecol, dt * 4 + q4) + ehf * 8) = w;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  uint16_t *dst = is_b ? bp.dk : bp.dv;
+  const int64_t st = is_b ? bp.dk_st : bp.dv_st, sh = is_b ? bp.dk_sh : bp.dv_sh;
+#pragma unroll
+  for (int u = 0; u < G::KCH; ++u) {
+    const int rr = u * G::QRPI + ln / G::CPR;
+    const u32x4_t w = *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t *>(stage + tile_ofs<D>(rr, ln % G::CPR));
+    if (kw0 + rr < lk)
+      *reinterpret_cast<u32x4_t *>(dst + (int64_t)(k_tok0 + kw0 + rr) * st + (int64_t)kvh * sh + (ln % G::CPR) * 8) = w;
   }
 }
 
@@ -746,7 +757,7 @@ hipError_t launch_dkv_t(const AttnParams &p, const BwdKvMeta &meta, const BwdPar
   const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads;
   if (n_wg == 0) return hipSuccess;
   if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
-  constexpr size_t lds = (size_t)kBBuf * (2 * BGeo<D>::TILEB + kBWaves * 1024);
+  constexpr size_t lds = KvGeo<D>::LDS;
   static_assert(lds <= 160 * 1024, "gfx950 has 160 KB of LDS per workgroup");
   // more than 64 KB of dynamic LDS has to be asked for once per kernel (setting it twice, from two
   // host threads at once, is harmless)

@@ -73,31 +73,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   // (per-block encoding: a block's long row tiles first; whole prompts: the host's order)
   const uint32_t id_lo = id - (uint32_t)kvh * n_rowtiles;
   const int rowtile = kPrompt ? (int)id_lo : (int)(n_rowtiles - 1 - id_lo);
-  // block of this row tile: the largest b with tile_start[b] <= rowtile, found in three rounds of
-  // independent table reads (every 32nd entry, every 4th, every one) instead of a bisection's nine
-  // dependent ones: the reads are scalar loads, and a work item this short feels each round trip
-  int b = 0;
-  static_assert(kEncMaxBlocks <= 320, "ten coarse samples cover the table");
-  {
-    // (entries past the last block hold INT_MAX, so no candidate needs a bounds check)
-    int hit[10];
-#pragma unroll
-    for (int k = 1; k < 10; ++k) hit[k] = meta.tile_start[k * 32];
-#pragma unroll
-    for (int k = 1; k < 10; ++k) b += hit[k] <= rowtile ? 32 : 0;
-    int fine = 0;
-#pragma unroll
-    for (int k = 1; k < 8; ++k) hit[k] = meta.tile_start[min(b + 4 * k, kEncMaxBlocks)];
-#pragma unroll
-    for (int k = 1; k < 8; ++k) fine += hit[k] <= rowtile ? 4 : 0;
-    b += fine;
-    fine = 0;
-#pragma unroll
-    for (int k = 1; k < 4; ++k) hit[k] = meta.tile_start[min(b + k, kEncMaxBlocks)];
-#pragma unroll
-    for (int k = 1; k < 4; ++k) fine += hit[k] <= rowtile ? 1 : 0;
-    b += fine;
-  }
+  const int b = find_block(meta.tile_start, rowtile);
   int q_tok0, lq, k_tok0;  // the block's first token, its length, the first key it sees
   if constexpr (kPrompt) {
     q_tok0 = meta.start[b];

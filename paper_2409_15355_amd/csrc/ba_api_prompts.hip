@@ -1,5 +1,6 @@
 // C boundary, whole prompts under the Block-attention mask (Section 2.4): forward and backward entry
 // points, and the route through zero-padded phantom heads for groups of fewer than four query heads.
+#include <limits.h>
 #include <math.h>
 #include <string.h>
 
@@ -411,9 +412,9 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
       meta.fin_start[i] = by_k[b0 + i].fin_start;
       meta.fin_len[i] = by_k[b0 + i].fin_len;
       meta.tile_start[i] = (int32_t)tiles;
-      tiles += ((int64_t)by_k[b0 + i].len + ba::kShortTileRows - 1) / ba::kShortTileRows;
+      tiles += ((int64_t)by_k[b0 + i].len + ba::kBwdTileKeys - 1) / ba::kBwdTileKeys;
     }
-    meta.tile_start[n] = (int32_t)tiles;
+    for (int i = n; i <= ba::kEncMaxBlocks; ++i) meta.tile_start[i] = i == n ? (int32_t)tiles : INT_MAX;
     if (tiles > 0x3fffffff) return fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
     if (tiles == 0) continue;
     ap.total_tiles = (int32_t)tiles;

@@ -122,6 +122,7 @@ constexpr int kProbeRecord = 16;
 constexpr int kTileRows = 256;  // packed (token, head-in-group) query rows per workgroup
 constexpr int kTileKeys = 64;   // keys per K/V tile
 constexpr int kShortTileRows = 128;  // packed query rows per workgroup of the short-block schedule
+constexpr int kBwdTileKeys = 64;     // keys per workgroup of the dk/dv kernel
 // Per-block encoding sends blocks up to this length through the short-block schedule (measured
 // crossover: beyond about 6,000 to 8,000 tokens the deep pipeline of the main core wins).
 constexpr int kShortMaxLen = 6144;
@@ -216,7 +217,7 @@ struct BwdKvMeta {
   int32_t n;
   int32_t start[kEncMaxBlocks];
   int32_t len[kEncMaxBlocks];
-  int32_t tile_start[kEncMaxBlocks + 1];  // in key tiles of kShortTileRows keys
+  int32_t tile_start[kEncMaxBlocks + 1];  // in key tiles of kBwdTileKeys keys; INT_MAX beyond [n]
   int32_t fin_start[kEncMaxBlocks];
   int32_t fin_len[kEncMaxBlocks];          // 0: the block is its prompt's last
 };

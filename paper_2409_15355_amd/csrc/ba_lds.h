@@ -17,6 +17,32 @@ __device__ __forceinline__ int find_segment(const int32_t *tile_start, int n, in
   return lo;
 }
 
+// The same in a table of kEncMaxBlocks + 1 tile starts whose entries past the last block hold INT_MAX, so
+// that no candidate needs a bounds check: three rounds of independent reads (every 32nd entry, every
+// 4th, every one) instead of a bisection's nine dependent ones.  The reads are scalar loads from the
+// kernel arguments, and a short work item feels each round trip.
+__device__ __forceinline__ int find_block(const int32_t *tile_start, int tile) {
+  static_assert(kEncMaxBlocks <= 320, "ten coarse samples cover the table");
+  int b = 0;
+  int hit[10];
+#pragma unroll
+  for (int k = 1; k < 10; ++k) hit[k] = tile_start[k * 32];
+#pragma unroll
+  for (int k = 1; k < 10; ++k) b += hit[k] <= tile ? 32 : 0;
+  int fine = 0;
+#pragma unroll
+  for (int k = 1; k < 8; ++k) hit[k] = tile_start[min(b + 4 * k, kEncMaxBlocks)];
+#pragma unroll
+  for (int k = 1; k < 8; ++k) fine += hit[k] <= tile ? 4 : 0;
+  b += fine;
+  fine = 0;
+#pragma unroll
+  for (int k = 1; k < 4; ++k) hit[k] = tile_start[min(b + k, kEncMaxBlocks)];
+#pragma unroll
+  for (int k = 1; k < 4; ++k) fine += hit[k] <= tile ? 1 : 0;
+  return b + fine;
+}
+
 __device__ __forceinline__ float other_half(float x) {
   // value held by lane ^ 32, combined with ours by the caller
   uint32_t u = __float_as_uint(x);
@@ -54,6 +80,11 @@ __device__ __forceinline__ void lds_dma16(const char *base, uint32_t offset, uin
 __device__ __forceinline__ void wg_barrier() {
   asm volatile("s_barrier" ::: "memory");
 }
+// Wait until this wave's LDS writes (and reads) have been done, ahead of a wg_barrier that publishes them.
+__device__ __forceinline__ void lds_wait() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
 // Query rows in fragment layout (lane = row; fragment kk holds 16-byte chunk 2 kk + hf) times the row's
 // entry of the pre-pass's table of (cos, sin) times some factor, rounded once.  The table row's 16-byte
 // pieces that a lane needs, in the order of `cs`: fragment_table_piece(j, ...).  Interleaved pairs: fragment kk
