@@ -89,7 +89,9 @@ __device__ __forceinline__ void lds_wait() {
 // entry of the pre-pass's table of (cos, sin) times some factor, rounded once.  The table row's 16-byte
 // pieces that a lane needs, in the order of `cs`: fragment_table_piece(j, ...).  Interleaved pairs: fragment kk
 // holds pairs kk * 8 + hf * 4 + (0..3); half-split pairs: fragments kk and kk + KCH/2 hold dims
-// kk * 16 + hf * 8 + (0..7) and their partners, i.e. pairs of those same numbers.
+// kk * 16 + hf * 8 + (0..7) and their partners, i.e. pairs of those same numbers.  (Which product is the
+// fused one is written out: left to the compiler it changes with the code around it, and the forward and
+// the backward pass are to see the same rows.)
 __device__ __forceinline__ int fragment_table_piece(int j, int hf, bool halves) {
   return halves ? (j / 4) * 8 + (j & 3) + hf * 4 : (j / 2) * 4 + (j & 1) + hf * 2;
 }
@@ -103,7 +105,7 @@ __device__ __forceinline__ void rotate_fragments(u32x4_t (&raw)[KCH], const f32x
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float x = bf16_lo(raw[kk][e]), y = bf16_hi(raw[kk][e]);
-        raw[kk][e] = pack_bf16(c[e] * x - sn[e] * y, sn[e] * x + c[e] * y);
+        raw[kk][e] = pack_bf16(__builtin_fmaf(c[e], x, -(sn[e] * y)), __builtin_fmaf(c[e], y, sn[e] * x));
       }
     }
   } else {
@@ -115,8 +117,8 @@ __device__ __forceinline__ void rotate_fragments(u32x4_t (&raw)[KCH], const f32x
         const float c0 = t[0], s0 = t[1], c1 = t[2], s1 = t[3];
         const uint32_t wa = raw[kk][e], wb = raw[kk + KCH / 2][e];
         const float xa0 = bf16_lo(wa), xa1 = bf16_hi(wa), xb0 = bf16_lo(wb), xb1 = bf16_hi(wb);
-        raw[kk][e] = pack_bf16(c0 * xa0 - s0 * xb0, c1 * xa1 - s1 * xb1);
-        raw[kk + KCH / 2][e] = pack_bf16(s0 * xa0 + c0 * xb0, s1 * xa1 + c1 * xb1);
+        raw[kk][e] = pack_bf16(__builtin_fmaf(c0, xa0, -(s0 * xb0)), __builtin_fmaf(c1, xa1, -(s1 * xb1)));
+        raw[kk + KCH / 2][e] = pack_bf16(__builtin_fmaf(s0, xa0, c0 * xb0), __builtin_fmaf(s1, xa1, c1 * xb1));
       }
     }
   }

@@ -21,6 +21,14 @@ namespace {
 
 constexpr int kThreads = 256;
 
+// Eq. 1 on one pair.  Which product is the fused one is written out: left to the compiler it changes with
+// the code around it, and with it the last bit of a key now and then.
+__device__ __forceinline__ float rot_x(float x, float y, float c, float s) { return __builtin_fmaf(c, x, -(s * y)); }
+__device__ __forceinline__ float rot_y(float x, float y, float c, float s) { return __builtin_fmaf(s, x, c * y); }
+__device__ __forceinline__ uint32_t rotated(float x, float y, float c, float s) {
+  return pack_bf16(rot_x(x, y, c, s), rot_y(x, y, c, s));
+}
+
 // Table of rotations for the block-table form of the final block: row b, frequency j holds
 // (cos, sin) of angle[b] * theta_j.  One thread per entry.
 template <int NB>
@@ -126,16 +134,16 @@ __global__ __launch_bounds__(kThreads) void rope_prepass_kernel(RopePrepassParam
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float a0 = bf16_lo(xa[e]), a1 = bf16_hi(xa[e]);
-        ya[e] = pack_bf16(cs[e] * a0 - sn[e] * a1, sn[e] * a0 + cs[e] * a1);
+        ya[e] = rotated(a0, a1, cs[e], sn[e]);
         const float b0 = bf16_lo(xb[e]), b1 = bf16_hi(xb[e]);
-        yb[e] = pack_bf16(cs[4 + e] * b0 - sn[4 + e] * b1, sn[4 + e] * b0 + cs[4 + e] * b1);
+        yb[e] = rotated(b0, b1, cs[4 + e], sn[4 + e]);
       }
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float a0 = bf16_lo(xa[e]), a1 = bf16_hi(xa[e]), b0 = bf16_lo(xb[e]), b1 = bf16_hi(xb[e]);
-        ya[e] = pack_bf16(cs[2 * e] * a0 - sn[2 * e] * b0, cs[2 * e + 1] * a1 - sn[2 * e + 1] * b1);
-        yb[e] = pack_bf16(sn[2 * e] * a0 + cs[2 * e] * b0, sn[2 * e + 1] * a1 + cs[2 * e + 1] * b1);
+        ya[e] = pack_bf16(rot_x(a0, b0, cs[2 * e], sn[2 * e]), rot_x(a1, b1, cs[2 * e + 1], sn[2 * e + 1]));
+        yb[e] = pack_bf16(rot_y(a0, b0, cs[2 * e], sn[2 * e]), rot_y(a1, b1, cs[2 * e + 1], sn[2 * e + 1]));
       }
     }
     *reinterpret_cast<u32x4_t *>(dst + h * dst_sh) = ya;
