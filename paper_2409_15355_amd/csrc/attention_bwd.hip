@@ -199,17 +199,15 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const int wr_g0 = wr_r0 - wr_tok0 * Gq;
     Ofs off = (Ofs)wr_tok0 * st + (Ofs)wr_g0 * sh;
     int g = wr_g0;
-    const Ofs d_in = 4 * sh, d_wrap = st + (Ofs)(4 - Gq) * sh;
+    const int step_tok = (int)fast_div((uint32_t)G::QRPI, p.group_div), step_g = G::QRPI - step_tok * Gq;
+    const Ofs d_in = (Ofs)step_tok * st + (Ofs)step_g * sh, d_wrap = d_in + st - (Ofs)Gq * sh;
 #pragma unroll
     for (int u = 0; u < G::KCH; ++u) {
       visit(u, off, wr_r0);
-#pragma unroll
-      for (int s4 = 0; s4 < G::QRPI / 4; ++s4) {
-        g += 4;
-        const bool wrap = g >= Gq;
-        g = wrap ? g - Gq : g;
-        off += wrap ? d_wrap : d_in;
-      }
+      g += step_g;
+      const bool wrap = g >= Gq;
+      g = wrap ? g - Gq : g;
+      off += wrap ? d_wrap : d_in;
     }
   };
   u32x4_t ld_q[G::KCH], ld_do[G::KCH];
@@ -270,15 +268,15 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     }
   };
   constexpr int kOpsPerTile = 2 * G::IPW;
-  // the pre-pass's table rows of this wave's tokens (at most 8: groups of four or more), 16-byte piece c of
-  // row t at c ^ (t & 7), into this wave's slice of buffer 2; they come in here, the rows themselves pass
-  // through the slice behind them
+  // the pre-pass's table rows of this wave's tokens, 16-byte piece c of row t at c ^ (t & 7), into this
+  // wave's slice of buffer 2; they come in here, the rows themselves pass through the slice behind them.
+  // (Groups of four or more: at most 8 rows.  Smaller groups read their pieces from memory below.)
   constexpr uint32_t TROW = D * 4;
   constexpr int TCH = TROW / 16, kTabOps = 8 * TROW / 1024;
   static_assert(kBWaves * G::SLICEB <= 2 * TB && 8 * TROW <= G::SLICEB, "the slices fit one tile buffer");
   const uint32_t s_ofs = 2 * (2 * TB) + wave * G::SLICEB;
   const int first_tok_wave = first_key_wave - dq;
-  {
+  if (Gq >= 4) {
     const char *tbase = (const char *)(p.q_table + (int64_t)q_tok0 * D);
 #pragma unroll
     for (int u = 0; u < kTabOps; ++u) {
@@ -294,7 +292,11 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
 
   // ---- whole rows -> B-operand fragments (lane = row), 16 rows at a time through this wave's slice ----
   f32x4_t cs[2 * G::KCH];
-  {
+  if (Gq < 4) {
+    const f32x4_t *row = reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(q_tok0 + my_tok) * D);
+#pragma unroll
+    for (int j = 0; j < 2 * G::KCH; ++j) cs[j] = row[fragment_table_piece(j, hf, p.rope_layout != 0)];
+  } else {
     const int tl = max(my_tok - first_tok_wave, 0);  // this lane's row of the table slice
 #pragma unroll
     for (int j = 0; j < 2 * G::KCH; ++j)

@@ -132,7 +132,8 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   // Whole rows move QRPI at a time: this lane's row in step u is wave_row0 + u * QRPI + lane / CPR and
   // its piece chunk lane % CPR.  Its element offset tok * st + g * sh (relative to the block's first
   // token and the group's first head; 32 bits by the host's check) is carried from step to step:
-  // four rows on is either four heads on or, past the group's last head, into the next token.
+  // QRPI rows on is QRPI / G tokens and QRPI % G heads on, the latter perhaps past the group's last head
+  // and into one more token.
   // (worked out afresh by each of the two walks, load and store: kept, the row numbers would occupy
   // registers all through the tile loop)
   auto walk_rows = [&](int ln, uint32_t st, uint32_t sh, auto &&visit) __attribute__((always_inline)) {
@@ -141,17 +142,15 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     const int wr_g0 = wr_r0 - wr_tok0 * Gq;
     uint32_t off = (uint32_t)wr_tok0 * st + (uint32_t)wr_g0 * sh;
     int g = wr_g0;
-    const uint32_t d_in = 4u * sh, d_wrap = st + (uint32_t)(4 - Gq) * sh;
+    const int step_tok = (int)fast_div((uint32_t)QRPI, p.group_div), step_g = QRPI - step_tok * Gq;
+    const uint32_t d_in = (uint32_t)step_tok * st + (uint32_t)step_g * sh, d_wrap = d_in + st - (uint32_t)Gq * sh;
 #pragma unroll
     for (int u = 0; u < G::KCH; ++u) {
       visit(u, off, wr_r0);
-#pragma unroll
-      for (int s4 = 0; s4 < QRPI / 4; ++s4) {
-        g += 4;
-        const bool wrap = g >= Gq;
-        g = wrap ? g - Gq : g;
-        off += wrap ? d_wrap : d_in;
-      }
+      g += step_g;
+      const bool wrap = g >= Gq;
+      g = wrap ? g - Gq : g;
+      off += wrap ? d_wrap : d_in;
     }
   };
   {
@@ -162,10 +161,9 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
       const uint32_t o = wr_r0 < n_rows - u * QRPI ? off : last_off;
       ld[u] = *reinterpret_cast<const u32x4_t *>(qbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
     });
-    if (p.q_table) {
-      // The rows of a wave span at most 8 tokens (the host sends only groups of 4 or more query
-      // heads here).  Chunk c of token row t sits at chunk c ^ (t & 7), which keeps the reads of
-      // different tokens off each other's banks.
+    if (p.q_table && Gq >= 4) {
+      // The rows of a wave span at most 8 tokens.  Chunk c of token row t sits at chunk c ^ (t & 7),
+      // which keeps the reads of different tokens off each other's banks.
       // (a row per token of the call, or, for per-block encoding, a row per position inside the block)
       const char *tbase = (const char *)(p.q_table + (p.q_table_by_pos ? (int64_t)0 : (int64_t)q_tok0 * D));
 #pragma unroll
@@ -233,7 +231,14 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   dma_wait<0>();  // the table rows and the first tile (this wave's share) have landed
   // the table first
   f32x4_t cs[2 * G::KCH];
-  if (p.q_table) {
+  if (p.q_table && Gq < 4) {
+    // Fewer heads than that share a token's row of the table, down to one: hardly any of it would be read
+    // twice, so every lane takes its pieces from where they lie.
+    const int tok = (int)fast_div((uint32_t)min(my_row, n_rows - 1), p.group_div);
+    const f32x4_t *row = reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)((p.q_table_by_pos ? 0 : q_tok0) + tok) * D);
+#pragma unroll
+    for (int j = 0; j < 2 * G::KCH; ++j) cs[j] = row[fragment_table_piece(j, hf, p.rope_layout != 0)];
+  } else if (p.q_table) {
     const bool halves = p.rope_layout != 0;
 #pragma unroll
     for (int j = 0; j < 2 * G::KCH; ++j) {

@@ -392,7 +392,7 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
   // short blocks take the schedule with small workgroups, several to a compute unit; longer ones the main core
   const int64_t widest = std::max(std::max(q->stride_tok, o_out->stride_tok),
                                   (int64_t)G * std::max(q->stride_head, o_out->stride_head));
-  const int64_t short_max = ba::encode_short_max(G, widest);
+  const int64_t short_max = ba::encode_short_max(G, D, widest);
 
   int64_t longest_block = 1;
   for (int b = 0; b < n_blocks; ++b) longest_block = std::max<int64_t>(longest_block, block_offsets[b + 1] - block_offsets[b]);

@@ -21,7 +21,9 @@ using ba::device_fail;
 using ba::num_cus;
 using namespace ba::api;
 
-// ---- fewer than four query heads per KV head in the whole-prompt calls: run as groups of four --------
+// ---- fewer than four query heads per KV head and row offsets beyond 32 bits in the whole-prompt calls:
+//      run as groups of four, through packed copies (which is all that route is for: at strides that fit,
+//      the kernels take any group, without the phantom heads' share of the work) ----------------------
 constexpr int kPadGroup = 4;
 
 // A packed [T][n_kv_heads * 4][D] bf16 tensor in the workspace.
@@ -106,19 +108,18 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
   const int64_t T = block_offsets[n_blocks];
   const int G = heads->n_q_heads / heads->n_kv_heads;
   if (T == 0) return BA_OK;
-  // what the kernel of this call is built for (see its header): groups of at least four query heads
-  // per KV head, and blocks whose row offsets fit 32 bits
+  // what the kernel of this call is built for (see its header): blocks whose row offsets fit 32 bits
   int64_t max_len = 0;
   for (int b = 0; b < n_blocks; ++b) max_len = std::max<int64_t>(max_len, (int64_t)block_offsets[b + 1] - block_offsets[b]);
   const int64_t widest = std::max(std::max(q->stride_tok, o_out->stride_tok),
                                   (int64_t)G * std::max(q->stride_head, o_out->stride_head));
-  if (G < kPadGroup) {
+  const bool fits32 = (max_len + 1) * widest < 0x40000000 && max_len * G <= 0x3fffffff;
+  const size_t need =
+      ba_block_attention_prompts_workspace_bytes(heads, n_prompts, cu_blk, block_offsets, rope_mode, k_rot_out != nullptr);
+  if (G < kPadGroup && (!ws || ws_bytes < need || ((uintptr_t)ws & 255)))
+    return fail(BA_ERR_WORKSPACE, "whole prompts: 256-byte aligned workspace of %zu bytes needed, %zu given", need, ws_bytes);
+  if (G < kPadGroup && !fits32) {
     // run as groups of four: padded q in, padded o and log-sum-exps out, through the workspace
-    const size_t need =
-        ba_block_attention_prompts_workspace_bytes(heads, n_prompts, cu_blk, block_offsets, rope_mode, k_rot_out != nullptr);
-    if (!ws || ws_bytes < need || ((uintptr_t)ws & 255))
-      return fail(BA_ERR_WORKSPACE, "whole prompts: 256-byte aligned workspace of %zu bytes needed, %zu given", need,
-                  ws_bytes);
     const ba_heads h4 = padded_heads(heads);
     char *wsp = (char *)ws;
     const ba_tensor q4 = padded_tensor(wsp, heads);
@@ -138,7 +139,7 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
     }
     return BA_OK;
   }
-  if ((max_len + 1) * widest >= 0x40000000 || max_len * G > 0x3fffffff)
+  if (!fits32)
     return fail(BA_ERR_UNSUPPORTED, "whole-prompt attention: a block of %lld tokens at these strides is too long",
                 (long long)max_len);
 
@@ -147,8 +148,6 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
   ba_tensor k_use = *k;
   float *q_table = nullptr;
   if (rope_mode == BA_ROPE_APPLY) {
-    const size_t need =
-        ba_block_attention_prompts_workspace_bytes(heads, n_prompts, cu_blk, block_offsets, rope_mode, k_rot_out != nullptr);
     if (!ws || ws_bytes < need || ((uintptr_t)ws & 255))
       return fail(BA_ERR_WORKSPACE, "whole prompts: 256-byte aligned workspace of %zu bytes needed, %zu given", need,
                   ws_bytes);
@@ -242,7 +241,7 @@ size_t ba_block_attention_prompts_backward_workspace_bytes(const ba_heads *heads
   }
   // rotated scaled q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row
   return pad_bytes + align256(T * hq * D * 2) + align256(T * hkv * D * 2) + align256(T * D * 4) +
-         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8);
+         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8 + 16);
 }
 
 int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k,
@@ -278,7 +277,8 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   if (!ws || ws_bytes < need || ((uintptr_t)ws & 255))
     return fail(BA_ERR_WORKSPACE, "whole prompts, backward: 256-byte aligned workspace of %zu bytes needed, %zu given",
                 need, ws_bytes);
-  if (G < kPadGroup) {
+  const bool fits32 = (max_len + 1) * widest < 0x40000000 && max_len * G <= 0x3fffffff;
+  if (G < kPadGroup && !fits32) {
     // run as groups of four (see head_pad.hip): the phantom heads' output gradient is zero, so they add
     // nothing to dk and dv, which the padded call writes straight to the caller's tensors
     const ba_heads h4 = padded_heads(heads);
@@ -303,7 +303,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
       return rc;
     return move_heads(heads, dq_out, dq4.ptr, T, false, stream, "backward: head un-padding launch");
   }
-  if ((max_len + 1) * widest >= 0x40000000 || max_len * G > 0x3fffffff)
+  if (!fits32)
     return fail(BA_ERR_UNSUPPORTED, "whole-prompt attention: a block of %lld tokens at these strides is too long",
                 (long long)max_len);
   char *wsp = (char *)ws;

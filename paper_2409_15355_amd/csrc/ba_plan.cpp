@@ -315,11 +315,16 @@ int32_t plan_final_blocks(const ba_heads *h, int32_t n_prompts, const int32_t *c
   return BA_OK;
 }
 
-// Blocks up to kShortMaxLen tokens take the schedule with small workgroups, several to a compute
-// unit; longer ones the main core.  (The short-block kernel assumes at most 8 tokens per 32 packed
-// rows, and addresses the rows of a block with 32-bit element offsets.)
-int64_t encode_short_max(int G, int64_t widest_stride) {
-  return (G >= 4 && ((int64_t)kShortMaxLen + 1) * widest_stride < 0x40000000) ? kShortMaxLen : -1;
+// Blocks up to this length take the schedule with small workgroups, several to a compute unit; longer
+// ones the main core.  (The short-block kernel addresses the rows of a block with 32-bit element
+// offsets.)  Measured with groups of one and two at 16,384 tokens, short-block kernel / main core, us:
+// 8 heads of 128, 8 KV heads, blocks of 128: 44 / 64, 2048: 123 / 137, 6000: 200 / 211; 16 over 8: 55 / 76,
+// 177 / 213, 291 / 300; 4 over 4 of 64: 128: 23 / 29, 512: 31 / 30, 2048: 62 / 56, 6000: 122 / 102 (at
+// head_dim 64 a tile holds so little work that a long walk is a chain of waits for tiles of 32 keys, with
+// no other heads in the group to fill them; the main core's are of 64 and three deep).
+int64_t encode_short_max(int G, int head_dim, int64_t widest_stride) {
+  if (((int64_t)kShortMaxLen + 1) * widest_stride >= 0x40000000) return -1;
+  return head_dim == 64 && G < 4 ? kShortMaxLenFewRows : kShortMaxLen;
 }
 
 int32_t build_encode_metas(const int32_t *block_offsets, int b0, int n, int G, int64_t short_max, EncodeMeta meta[2],
@@ -481,7 +486,7 @@ int64_t ba_schedule_encode_blocks(const ba_heads *heads, int32_t n_blocks, const
   if ((rc = ba::check_heads(heads, true))) return rc;
   if ((rc = ba::check_offsets(n_blocks, block_offsets))) return rc;
   const int G = heads->n_q_heads / heads->n_kv_heads;
-  const int64_t short_max = ba::encode_short_max(G, (int64_t)heads->n_q_heads * heads->head_dim);
+  const int64_t short_max = ba::encode_short_max(G, heads->head_dim, (int64_t)heads->n_q_heads * heads->head_dim);
   ba::ItemSink sink{items, items ? max_items : 0};
   int launch = 0;
   for (int b0 = 0; b0 < n_blocks; b0 += ba::kEncMaxBlocks) {

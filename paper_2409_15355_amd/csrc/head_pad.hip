@@ -1,7 +1,8 @@
-// Whole-prompt attention (Section 2.4) for fewer than four query heads per KV head.
+// Whole-prompt attention (Section 2.4) for fewer than four query heads per KV head whose row offsets
+// (tokens of a block x strides) do not fit 32 bits.
 //
-// The short-block schedule packs the query heads of a KV group next to each other and is laid out
-// for groups of four or more.  A smaller group G is run as a group of four: every KV head gets
+// The kernels address the rows of a block with 32-bit offsets, so such a call goes through packed
+// copies; they are laid out as groups of four: every KV head gets
 // 4 - G phantom query heads whose rows are zero (a zero query has equal scores everywhere: a finite
 // output that is never copied back; a zero output gradient adds nothing to dk and dv).  These two
 // kernels move rows between the caller's [T][n_q_heads] tensors and the padded [T][4 n_kv_heads]

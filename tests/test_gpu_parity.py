@@ -1582,3 +1582,64 @@ def test_phase_marks_of_a_final_block_launch_are_consistent(ba):
     assert ph["workgroup_lifetime"] <= ph["launch_first_entry_to_last_store"] < 1000.0, ph
     # the walk is most of a workgroup's life at this shape (62 or 63 key tiles)
     assert ph["walk"] > 0.8 * ph["workgroup_lifetime"], ph
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(1, 1, 64), (2, 2, 128), (4, 2, 64), (2, 1, 128), (6, 2, 128), (5, 1, 128), (6, 1, 64),
+                                      (12, 1, 64), (12, 1, 128), (32, 1, 128)])
+@pytest.mark.parametrize("layout", [0, 1])
+def test_any_group_size_through_the_small_workgroup_schedules(ba, hq, hkv, d, layout):
+    """Groups of 1 to 32 query heads, those that divide a tile of 32 packed rows and those that do not,
+    over blocks at the edges of row tiles (128 packed rows), key tiles (32, 64) and waves: per-block
+    encoding, whole prompts and their backward pass against the oracle, with the bounds derived above."""
+    torch = torch_mod()
+    base = 10000.0
+    prompts = [[33, 1, 64, 65, 17], [129], [31, 32, 96]]
+    lens = [l for p in prompts for l in p]
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    T = int(offs[-1])
+    qb, kb, vb = gen_qkv(900 + 7 * hq + hkv + d + layout, T, hq, hkv, d)
+    dob = wl.normal_bf16_bits(950 + hq + d, (T, hq, d))
+    heads = ba.Heads(hq, hkv, d, base, rope_layout=layout)
+    f = oracle.bf16_bits_to_f64
+    th = oracle.theta(base, d)
+    o, _ = gpu_encode(ba, heads, qb, kb, vb, offs)
+    ref, _ = oracle.encode_blocks(f(qb), f(kb), f(vb), offs, th, layout=layout)
+    assert_attention_close(host_f64(o), ref, "encode")
+    o, _, lse = gpu_prompts(ba, heads, qb, kb, vb, cu_blk, offs, want_k_rot=False)
+    q, k, v, do = dev_bf16(qb), dev_bf16(kb), dev_bf16(vb), dev_bf16(dob)
+    dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, k, v))
+    # (a workspace full of NaN: nothing may be read that the call has not written)
+    ws = torch.full((ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs),), 255, dtype=torch.uint8, device="cuda")
+    ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs, ws)
+    torch.cuda.synchronize()
+    og, gq, gk, gv = host_f64(o), host_f64(dq), host_f64(dk), host_f64(dv)
+    for n in range(len(prompts)):
+        t0, t1 = int(offs[cu_blk[n]]), int(offs[cu_blk[n + 1]])
+        po = offs[cu_blk[n]:cu_blk[n + 1] + 1] - t0
+        x = [f(b[t0:t1]) for b in (qb, kb, vb, dob)]
+        assert_attention_close(og[t0:t1], oracle.masked_attention_bruteforce(*x[:3], po, th, layout=layout), f"o, prompt {n}")
+        (rq, rk, rv), (aq, ak, av) = oracle_grads(*x, po, th, layout=layout)
+        assert_grad_close(gq[t0:t1], rq, aq, f"dq, prompt {n}")
+        assert_grad_close(gk[t0:t1], rk, ak, f"dk, prompt {n}")
+        assert_grad_close(gv[t0:t1], rv, av, f"dv, prompt {n}")
+
+
+def test_one_query_head_per_kv_head_beyond_32_bit_row_offsets(ba):
+    """o at a token stride of 2^20 elements and a block of 1,030 tokens: offsets the kernels do not address
+    themselves, so the call goes through packed copies; the same bits as with a packed o."""
+    torch = torch_mod()
+    hq, hkv, d = 2, 2, 64
+    offs, cu_blk = np.array([0, 1030, 1040], dtype=np.int32), np.array([0, 2], dtype=np.int32)
+    T = int(offs[-1])
+    qb, kb, vb = gen_qkv(990, T, hq, hkv, d)
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    want, _, want_lse = gpu_prompts(ba, heads, qb, kb, vb, cu_blk, offs, want_k_rot=False)
+    big = torch.zeros(((T - 1) * (1 << 20) + hq * d,), dtype=torch.bfloat16, device="cuda")
+    o = big.as_strided((T, hq, d), (1 << 20, d, 1))
+    lse = torch.full((T, hq), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False), dtype=torch.uint8, device="cuda")
+    ba.ba_block_attention_prompts(heads, dev_bf16(qb), dev_bf16(kb), dev_bf16(vb), o, None, lse, cu_blk, offs, 1, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_bits(o.contiguous()), host_bits(want))
+    assert torch.equal(lse, want_lse)
