@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const int64_t last_off = (int64_t)(lq - 1) * st + (int64_t)(Gq - 1) * sh;
     walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       const int64_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
-      ld_q[u] = *reinterpret_cast<const u32x4_t *>(qbase + (o * 2 + (lane % G::CPR) * 16));
+      ld_q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(qbase + (o * 2 + (lane % G::CPR) * 16)));
     });
   }
   {
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const uint32_t last_off = (uint32_t)(lq - 1) * st + (uint32_t)(Gq - 1) * sh;
     walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       const uint32_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
-      ld_do[u] = *reinterpret_cast<const u32x4_t *>(dbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
+      ld_do[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(dbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u)));
     });
   }
   // ... and of O, for delta = rowsum(dO o O); this lane's row's log-sum-exp (to base-2 units below)
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const uint32_t last_off = (uint32_t)(lq - 1) * st + (uint32_t)(Gq - 1) * sh;
     walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       const uint32_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
-      ld_o[u] = *reinterpret_cast<const u32x4_t *>(obase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
+      ld_o[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(obase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u)));
     });
   }
   const float my_lse = bp.lse[(int64_t)(q_tok0 + my_tok) * p.n_q_heads + kvh * Gq + (my_row - my_tok * Gq)];
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     char *obase = (char *)(bp.dq + (int64_t)q_tok0 * bp.dq_st + (int64_t)(kvh * Gq) * bp.dq_sh);
     walk_rows((uint32_t)bp.dq_st, (uint32_t)bp.dq_sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       if (wr_r0 < n_rows - u * G::QRPI)
-        *reinterpret_cast<u32x4_t *>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u)) = w[u];
+        __builtin_nontemporal_store(w[u], reinterpret_cast<u32x4_t *>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u)));
     });
   }
 }

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     const uint32_t last_off = (uint32_t)(lq - 1) * q_st + (uint32_t)(Gq - 1) * q_sh;  // the block's last row
     walk_rows(lane, q_st, q_sh, [&](int u, uint32_t off, int wr_r0) __attribute__((always_inline)) {
       const uint32_t o = wr_r0 < n_rows - u * QRPI ? off : last_off;
-      ld[u] = *reinterpret_cast<const u32x4_t *>(qbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
+      ld[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(qbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u)));
     });
     if (p.q_table && Gq >= 4) {
       // The rows of a wave span at most 8 tokens.  Chunk c of token row t sits at chunk c ^ (t & 7),
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     char *obase = (char *)(p.o + (int64_t)q_tok0 * p.o_st + (int64_t)(kvh * Gq) * p.o_sh);
     walk_rows(ln, (uint32_t)p.o_st, (uint32_t)p.o_sh, [&](int u, uint32_t off, int wr_r0) __attribute__((always_inline)) {
       if (wr_r0 < n_rows - u * QRPI)
-        *reinterpret_cast<u32x4_t *>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u)) = w[u];
+        __builtin_nontemporal_store(w[u], reinterpret_cast<u32x4_t *>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u)));
     });
   }
   // the row's log-sum-exp of its scaled scores (natural logarithm), for a backward pass
