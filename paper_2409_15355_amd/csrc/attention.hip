@@ -41,6 +41,7 @@ namespace ba {
 namespace {
 
 constexpr int kCombineThreads = 256;
+constexpr int kOneGroupSplits = 8;  // splits that one thread of the merge keeps in flight
 constexpr int kWaves = kTileRows / 32;  // 8: each wave owns one 32-query MFMA column group
 constexpr int kThreads = kWaves * 64;
 constexpr int kXcds = 8;        // MI355X: workgroup ids go round-robin over 8 XCDs
@@ -963,29 +964,29 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(AttnParams p) 
   const int64_t unit = blockIdx.x / BPU;
   const int k = (int)(blockIdx.x % BPU) * KPB + kl;
   // all loads are unconditional and independent, so they go out together
-  constexpr int MAXS = 32;  // the host never asks for more splits
   const int n_mine = (p.n_splits - g + SG - 1) / SG;  // splits g, g + SG, ...
   const float2 *ml = reinterpret_cast<const float2 *>(p.part_ml) + unit * 32 + col;
   const char *po = (const char *)p.part_o + unit * (int64_t)(32 * D * 2) + k * 1024 + lane * 16;
   const int64_t ml_stride = p.part_units * 32, o_stride = p.part_units * (int64_t)(32 * D * 2);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float l = 0.f, m = -INFINITY;
-  if (n_mine <= 8) {
-    // the common case (up to eight splits per thread): every load of the thread is requested before
-    // anything is used, a split beyond the thread's last reads its last one again with weight zero
-    float2 mls[8];
-    u32x4_t os[8];
+  // every load of the thread is requested before anything is used; a split beyond the thread's last
+  // reads its last one again with weight zero
+  auto merge = [&](auto capacity) __attribute__((always_inline)) {
+    constexpr int CAP = decltype(capacity)::value;
+    float2 mls[CAP];
+    u32x4_t os[CAP];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < CAP; ++j) {
       const int s = g + min(j, n_mine - 1) * SG;
       mls[j] = ml[s * ml_stride];
       os[j] = *reinterpret_cast<const u32x4_t *>(po + s * o_stride);
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < CAP; ++j)
       if (j < n_mine) m = fmaxf(m, mls[j].x);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < CAP; ++j) {
       const float w = (j >= n_mine || mls[j].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mls[j].x - m) * mls[j].y;
       l += w;
 #pragma unroll
@@ -994,29 +995,9 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(AttnParams p) 
         acc[2 * i + 1] += w * f16_hi(os[j][i]);
       }
     }
-  } else {
-    float wgt[MAXS];
-#pragma unroll 8
-    for (int j = 0; j < n_mine; ++j) {
-      const int s = g + j * SG;
-      wgt[j & (MAXS - 1)] = ml[s * ml_stride].x;
-      m = fmaxf(m, wgt[j & (MAXS - 1)]);
-    }
-#pragma unroll 8
-    for (int j = 0; j < n_mine; ++j) {
-      const int s = g + j * SG;
-      const float ms = wgt[j & (MAXS - 1)];
-      const float ls = ml[s * ml_stride].y;
-      const float w = (ms == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms - m) * ls;
-      const u32x4_t o = *reinterpret_cast<const u32x4_t *>(po + s * o_stride);
-      l += w;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc[2 * i] += w * f16_lo(o[i]);
-        acc[2 * i + 1] += w * f16_hi(o[i]);
-      }
-    }
-  }
+  };
+  static_assert(kMaxSplits <= 16 * 4 && kOneGroupSplits <= 8, "a thread's share of the splits fits its registers");
+  if (SG == 1 || n_mine <= 8) merge(std::integral_constant<int, 8>{}); else merge(std::integral_constant<int, 16>{});
   const int idx = p.part_idx[unit * 32 + col];
   if constexpr (SG > 1) {
     // (reference, sum, eight partial outputs) of every thread; group 0 merges them in group order
@@ -1123,7 +1104,8 @@ void launch_combine_t(const AttnParams &p, hipStream_t stream) {
 hipError_t launch_combine(const AttnParams &p, hipStream_t stream) {
   if (p.part_units == 0) return hipSuccess;
   if (p.part_units * (p.head_dim / 16) > 0x7fffffff) return hipErrorInvalidValue;
-  const bool many = p.n_splits > 8;  // more splits than one thread keeps in flight: four groups of threads per row
+  if (p.n_splits > kMaxSplits) return hipErrorInvalidValue;
+  const bool many = p.n_splits > kOneGroupSplits;  // more splits than one thread keeps in flight: four groups of threads per row
   if (p.head_dim == 128) {
     if (many) launch_combine_t<128, 4>(p, stream); else launch_combine_t<128, 1>(p, stream);
   } else if (p.head_dim == 64) {

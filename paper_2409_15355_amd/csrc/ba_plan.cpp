@@ -62,17 +62,21 @@ int32_t check_prompt_blocks(int32_t n_prompts, const int32_t *cu_blk, const int3
 
 // One workgroup runs per compute unit, so a launch takes ceil(workgroups / CUs) rounds, each as long
 // as one workgroup: a fixed part (prologue, output, worth about four key tiles) plus its share of the
-// key tiles; every split also adds a little to the merge.  Take the cheapest count, never fewer than
-// four key tiles per split.
+// key tiles; every split also adds to the merge, the less the fewer rows there are (a workgroup's row tile
+// at one KV head is 64 KB per split at D = 128).  Take the cheapest count, never fewer than four key tiles
+// per split.  Few KV heads and a long context want many: measured at 31,950 context tokens, 50 queries, 32
+// splits / 64, us: 4 over 4 heads of 64: 24.3 / 21.0, 8 over 2 of 64: 28.9 / 23.5, 4 over 1 of 128: 30.5 / 24.9;
+// at 8,000 tokens, 64 queries, 4 over 4 of 64, 14 splits (a merge priced as for eight workgroups) / 32: 20.3 / 17.1.
 int choose_splits(int64_t base_wgs, int max_tiles, int n_cu) {
   if (base_wgs <= 0) return 1;
   if (n_cu < 1) n_cu = 1;
-  const int s_max = (int)std::min<int64_t>(32, std::max(1, max_tiles / 4));
+  const int s_max = std::min(kMaxSplits, std::max(1, max_tiles / 4));
+  const double merge = 0.25 * std::min(1.0, (double)base_wgs / 8);
   int best = 1;
   double best_cost = 0;
   for (int s = 1; s <= s_max; ++s) {
     const double rounds = (double)((base_wgs * s + n_cu - 1) / n_cu);
-    const double cost = rounds * (4.0 + (max_tiles + s - 1) / s) + 0.25 * s;
+    const double cost = rounds * (4.0 + (max_tiles + s - 1) / s) + merge * s;
     if (s == 1 || cost < best_cost) {
       best = s;
       best_cost = cost;
@@ -127,7 +131,7 @@ double try_kv_group(const float *speed, int64_t tiles, int n_kv_heads, int n_spl
   double longest[kNumXcds] = {0}, sum[kNumXcds] = {0};
   bool hosts[kNumXcds][kMaxCutHeads] = {};
   for (int h = 0; h < n_kv_heads; ++h) {
-    double w[kMaxSplits], total = 0.0;
+    double w[kMaxCutSplits], total = 0.0;
     for (int s = 0; s < n_splits; ++s) {
       double acc = 0.0;
       for (int64_t t = 0; t < tiles; ++t) acc += speed[xcd_of_work_item(item_id((int)t, h, s, order), n_wg, runs)];
@@ -139,7 +143,7 @@ double try_kv_group(const float *speed, int64_t tiles, int n_kv_heads, int n_spl
       cuts[h][s] = (uint32_t)(acc / total * 65536.0 + 0.5);
       acc += w[s];
     }
-    for (int s = n_splits; s <= kMaxSplits; ++s) cuts[h][s] = 65536;
+    for (int s = n_splits; s <= kMaxCutSplits; ++s) cuts[h][s] = 65536;
     for (int s = 0; s < n_splits; ++s) {
       const double item_tiles = (double)max_nt * (double)(cuts[h][s + 1] - cuts[h][s]) / 65536.0;
       for (int64_t t = 0; t < tiles; ++t) {
@@ -193,13 +197,12 @@ int32_t plan_split_cuts(const float *xcd_speed, int64_t tiles, int n_kv_heads, i
   *kv_group = kDefaultKvGroup;
   *xcd_runs = kIdentityXcdRuns;
   for (int h = 0; h < kMaxCutHeads; ++h)
-    for (int s = 0; s <= kMaxSplits; ++s) cuts[h][s] = 0;
+    for (int s = 0; s <= kMaxCutSplits; ++s) cuts[h][s] = 0;
   if (!xcd_speed || n_splits <= 1 || tiles <= 0) return BA_OK;
-  if (n_splits > kMaxSplits) return fail(BA_ERR_INVALID_ARG, "more than %d splits", kMaxSplits);
   for (int x = 0; x < kNumXcds; ++x)
     if (!(xcd_speed[x] >= 0.5f && xcd_speed[x] <= 2.0f))
       return fail(BA_ERR_INVALID_ARG, "xcd_speed[%d] = %g: relative speeds lie between 0.5 and 2", x, (double)xcd_speed[x]);
-  if (n_kv_heads > kMaxCutHeads || tiles * n_kv_heads * n_splits > 0x7fffffff) return BA_OK;  // equal splits
+  if (n_kv_heads > kMaxCutHeads || n_splits > kMaxCutSplits || tiles * n_kv_heads * n_splits > 0x7fffffff) return BA_OK;  // equal splits
   // The speed of (KV head, split) = the mean speed of the XCDs that run its row tiles (item_id,
   // xcd_of_work_item), and a KV head's key range is shared out in proportion to its splits' speeds.
   // How far that can even out the XCDs depends on the order of the work items: with small groups of

@@ -54,12 +54,13 @@ BA_HD int causal_key_tiles(int last_tok, int tile_keys) { return last_tok / tile
 // `pad` tiles longer than it is: tiles of the causal segment cost more than context tiles (masks on
 // the diagonal, the change of segment, the general path of the loop), so the split that ends with
 // them gets fewer, and all splits of a launch end together.  Splits may be empty (few tiles).
-// (nt < 2^26 and at most 32 splits: the products fit 32 bits)
+// (fewer than 2^30 context and query tokens, so nt <= 2^25, and at most 64 splits: the products fit 32 bits)
 // cuts (nullable): unequal shares, the list of the work item's KV head.  cuts[s] = where split s
 // begins, as a fraction of the (padded) walk in units of 1 / 65536, cuts[0] = 0 <= cuts[1] <= ... <=
 // cuts[n_splits] = 65536: the planner sizes the splits of a KV head by the speed of the XCD each of
 // them runs on, so that all of them end together.
-constexpr int kMaxSplits = 32;
+constexpr int kMaxCutSplits = 32;  // splits whose shares fit the kernel arguments
+constexpr int kMaxSplits = 64;     // splits of a call
 // divs (nullable): the same quotients without hardware divisions (for the kernels).
 BA_HD TileRange split_tile_range(int n_ctx_tiles, int n_causal_tiles, int n_splits, int split,
                                  const unsigned *cuts = nullptr, const SplitDivs *divs = nullptr) {

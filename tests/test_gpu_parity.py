@@ -1643,3 +1643,21 @@ def test_one_query_head_per_kv_head_beyond_32_bit_row_offsets(ba):
     torch.cuda.synchronize()
     assert np.array_equal(host_bits(o.contiguous()), host_bits(want))
     assert torch.equal(lse, want_lse)
+
+
+@pytest.mark.parametrize("hq,hkv,d,ctx,nq", [(4, 1, 128, 14000, 3), (2, 2, 64, 17000, 40), (8, 1, 64, 24000, 1)])
+def test_many_splits_for_few_kv_heads(ba, hq, hkv, d, ctx, nq):
+    """Contexts that a few KV heads cut into more than 32 splits (beyond what a list of unequal shares
+    holds: XCD speeds then leave them equal), merged by four groups of up to sixteen."""
+    base = 500000.0
+    cu_q, cu_ctx = np.array([0, nq], dtype=np.int32), np.array([0, ctx], dtype=np.int32)
+    items = ba.ba_schedule_final_block(ba.Heads(hq, hkv, d, base), cu_q, cu_ctx)
+    assert 32 < max(w.n_splits for w in items) <= 64
+    _, kc, vc = gen_qkv(1000 + hq + d, ctx, hq, hkv, d)
+    qb, kb, vb = gen_qkv(1010 + hq + d, nq, hq, hkv, d)
+    f = oracle.bf16_bits_to_f64
+    ref = oracle.final_block(f(qb), f(kc), f(vc), f(kb), f(vb), cu_q, cu_ctx, oracle.theta(base, d))
+    for speeds in (None, [1.03, 0.97, 1.02, 0.97, 1.03, 1.0, 1.02, 0.95]):
+        heads = ba.Heads(hq, hkv, d, base, xcd_speed=speeds)
+        o = gpu_final(ba, heads, dev_bf16(qb), dev_bf16(kc), dev_bf16(vc), dev_bf16(kb), dev_bf16(vb), cu_q, cu_ctx)
+        assert_attention_close(host_f64(o), ref, f"speeds {speeds}")
