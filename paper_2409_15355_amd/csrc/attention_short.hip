@@ -12,6 +12,11 @@
 //     Per tile a wave computes S^T = K Q^T, the exponentials, and O^T += V^T P^T, in that order,
 //     with one workgroup barrier per tile.  A wave whose rows all lie before a tile's first key
 //     skips that tile's arithmetic.
+//   - Rows of q and o pass once, 32 KB per workgroup, between K/V tiles that the block's other row tiles
+//     read again: they carry the non-temporal hint (160 passages of 100 to 300 tokens, 681 MB: 157 -> 151 us;
+//     101 of it remain with no key tiles walked at all).  A tenth fewer vector instructions changed nothing:
+//     the stream bounds it, not the issue.
+//   - Any group size: a row tile is 32 packed rows to a wave whatever tokens and heads they are.
 //   - Arithmetic, operand layouts, softmax (reference set by the first tile, moved only to avoid
 //     overflow) and rounding are those of the main core, so both give the same numbers for the
 //     same rows.
