@@ -324,10 +324,12 @@ int32_t plan_final_blocks(const ba_heads *h, int32_t n_prompts, const int32_t *c
 // 8 heads of 128, 8 KV heads, blocks of 128: 44 / 64, 2048: 123 / 137, 6000: 200 / 211; 16 over 8: 55 / 76,
 // 177 / 213, 291 / 300; 4 over 4 of 64: 128: 23 / 29, 512: 31 / 30, 2048: 62 / 56, 6000: 122 / 102 (at
 // head_dim 64 a tile holds so little work that a long walk is a chain of waits for tiles of 32 keys, with
-// no other heads in the group to fill them; the main core's are of 64 and three deep).
-int64_t encode_short_max(int G, int head_dim, int64_t widest_stride) {
+// no other heads in the group to fill them; the main core's are of 64 and three deep).  There the longest
+// block decides for the call: a second launch costs more than either schedule gains.
+int64_t encode_short_max(int G, int head_dim, int64_t widest_stride, int64_t longest_block) {
   if (((int64_t)kShortMaxLen + 1) * widest_stride >= 0x40000000) return -1;
-  return head_dim == 64 && G < 4 ? kShortMaxLenFewRows : kShortMaxLen;
+  if (head_dim == 64 && G < 4 && longest_block > kShortMaxLenFewRows) return -1;
+  return kShortMaxLen;
 }
 
 int32_t build_encode_metas(const int32_t *block_offsets, int b0, int n, int G, int64_t short_max, EncodeMeta meta[2],
@@ -489,7 +491,9 @@ int64_t ba_schedule_encode_blocks(const ba_heads *heads, int32_t n_blocks, const
   if ((rc = ba::check_heads(heads, true))) return rc;
   if ((rc = ba::check_offsets(n_blocks, block_offsets))) return rc;
   const int G = heads->n_q_heads / heads->n_kv_heads;
-  const int64_t short_max = ba::encode_short_max(G, heads->head_dim, (int64_t)heads->n_q_heads * heads->head_dim);
+  int64_t longest_block = 0;
+  for (int b = 0; b < n_blocks; ++b) longest_block = std::max<int64_t>(longest_block, (int64_t)block_offsets[b + 1] - block_offsets[b]);
+  const int64_t short_max = ba::encode_short_max(G, heads->head_dim, (int64_t)heads->n_q_heads * heads->head_dim, longest_block);
   ba::ItemSink sink{items, items ? max_items : 0};
   int launch = 0;
   for (int b0 = 0; b0 < n_blocks; b0 += ba::kEncMaxBlocks) {
