@@ -17,9 +17,13 @@
 //     101 of it remain with no key tiles walked at all).  A tenth fewer vector instructions changed nothing:
 //     the stream bounds it, not the issue.
 //   - Any group size: a row tile is 32 packed rows to a wave whatever tokens and heads they are.
-//   - Arithmetic, operand layouts, softmax (reference set by the first tile, moved only to avoid
-//     overflow) and rounding are those of the main core, so both give the same numbers for the
-//     same rows.
+//   - Arithmetic, operand layouts and rounding are those of the main core; the softmax takes its reference
+//     from the first tile and moves it only to avoid overflow.  The main core's tiles are of 64 keys, so
+//     its reference and the order of its sums differ and with them the last bits of an output.  Per-block
+//     encoding of fewer than four query heads per KV head takes either schedule by the whole call, and a
+//     passage's output must not change with its neighbours there: kAsCore gives the main core's numbers,
+//     bit for bit as long as no reference has to move.  (Larger groups take the schedule by a block's own
+//     length, whole prompts have this one only: they keep the cheaper order.)
 #include <type_traits>
 
 #include "ba_device.h"
@@ -55,7 +59,8 @@ struct SGeo {
 // start wherever the table says -- at the block itself for a passage, at the first token of the
 // prompt for its last block (Section 2.4: the lower-triangular mask with only the last block seeing
 // the others); keys and queries then carry positions inside the prompt.
-template <int D, typename Meta>
+// kAsCore: the numbers of the main core (the reference from the first 64 keys, sums by 64 keys).
+template <int D, typename Meta, bool kAsCore>
 __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p, Meta meta) {
   using G = SGeo<D>;
   constexpr bool kPrompt = std::is_same<Meta, PromptMeta>::value;
@@ -279,7 +284,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   }
   bf16x8_t qf[G::KCH];
   if (p.q_table) {
-    rotate_fragments<G::KCH>(raw, cs, p.rope_layout != 0);
+    rotate_fragments<G::KCH, kAsCore>(raw, cs, p.rope_layout != 0);
   } else if (!p.q_ready) {
     const float c2 = p.scale_log2e;
 #pragma unroll
@@ -301,6 +306,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     for (int v = 0; v < 16; ++v) oacc[dt][v] = 0.f;
   float mb = 0.f;     // the row's reference, log2 units
   float l_run = 0.f;  // this lane's share of the running sum of exponentials
+  float s0 = 0.f, s1 = 0.f;  // the tile's two partial sums
 
   auto row_max = [&](const f32x16_t &s) __attribute__((always_inline)) {
     float m0 = s[0];
@@ -308,9 +314,8 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     for (int v = 1; v < 16; ++v) m0 = fmaxf(m0, s[v]);
     return fmaxf(m0, other_half(m0));
   };
-  // P = 2^S' rounded to bf16 (the B operand of PV); returns this lane's fp32 sum of the exponentials
+  // P = 2^S' rounded to bf16 (the B operand of PV), added up in fp32 on top of s0 and s1
   auto exponentials = [&](const f32x16_t &s, bf16x8_t (&pf)[2]) __attribute__((always_inline)) {
-    float s0 = 0.f, s1 = 0.f;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       u32x4_t w;
@@ -324,8 +329,41 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
       }
       pf[e] = __builtin_bit_cast(bf16x8_t, w);
     }
-    return s0 + s1;
   };
+  // K Q'^T of the tile at kofs on top of `start`, keys this lane's row does not see at -infinity (diagonal
+  // and ragged tiles only; all branches are wave-uniform)
+  auto scores = [&](int i, uint32_t kofs, float start) __attribute__((always_inline)) {
+    f32x16_t sacc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sacc[v] = start;
+#pragma unroll
+    for (int kk = 0; kk < G::KCH; ++kk) {
+      const bf16x8_t kfrag = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(smem + (k_rd[kk] + kofs));
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag, qf[kk], sacc, 0, 0, 0);
+    }
+    const int key0 = i * kSKeys;
+    const int valid = min(kSKeys, lk - key0);
+    if (key0 + kSKeys - 1 > first_key_wave || valid < kSKeys) {
+      const int lim = min(my_key - key0 + 1, valid);  // visible keys in this tile
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int key = (v >> 2) * 8 + hf * 4 + (v & 3);
+        if (key >= lim) sacc[v] = -INFINITY;
+      }
+    }
+    return sacc;
+  };
+
+  if (kAsCore) {
+    // The main core's first tile is this schedule's first two (both have been waited for above): the second
+    // one's row maximum is wanted ahead of the first one's exponentials.  Its scores are worked out once more
+    // when its turn comes (kept, they would not fit next to the accumulators): 16,384 tokens of 16 over 8
+    // heads of 128 in blocks of 128 take 60.7 us so, 59.7 with a reference of this schedule's own, 75.8 in the
+    // main core; 4 over 4 of 64, 33,000 tokens in blocks of 200: 34.1, 33.5, 49.6.
+    mb = -INFINITY;
+    if (n_t > 1) wg_barrier();
+    if (wave_n_t > 1) mb = row_max(scores(1, 2 * TB, 0.f));
+  }
 
   // ---- the walk over the key tiles: tile i lives in buffer i % 3.  The barrier at the head of
   //      iteration i says two things: every wave's share of tile i has landed, and every wave is
@@ -340,38 +378,25 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     if (i < wave_n_t) {
       const uint32_t kofs = (uint32_t)buf * (2 * TB), vofs = kofs + TB;
       // S'^T = K Q'^T - reference: the accumulator starts at minus the row's reference, so the MFMA
-      // result is directly the base-2 exponent
-      f32x16_t sacc;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sacc[v] = -mb;
-#pragma unroll
-      for (int kk = 0; kk < G::KCH; ++kk) {
-        const bf16x8_t kfrag = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(smem + (k_rd[kk] + kofs));
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag, qf[kk], sacc, 0, 0, 0);
-      }
-      // mask (diagonal and ragged tiles only); all branches are wave-uniform
-      const int key0 = i * kSKeys;
-      const int valid = min(kSKeys, lk - key0);
-      if (key0 + kSKeys - 1 > first_key_wave || valid < kSKeys) {
-        const int lim = min(my_key - key0 + 1, valid);  // visible keys in this tile
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int key = (v >> 2) * 8 + hf * 4 + (v & 3);
-          if (key >= lim) sacc[v] = -INFINITY;
-        }
-      }
+      // result is directly the base-2 exponent (as the main core: from the second tile of 64 keys on)
+      f32x16_t sacc = scores(i, kofs, kAsCore && i < 2 ? 0.f : -mb);
       if (i == 0) {
         // the first tile sets the reference: its row maximum whatever the sign (nothing visible:
         // stay at 0), so a row's largest exponential so far is exactly 1
-        const float mx = row_max(sacc);
-        const float shift = mx == -INFINITY ? 0.f : mx;
-        mb = shift;
+        const float mx = kAsCore ? fmaxf(mb, row_max(sacc)) : row_max(sacc);
+        mb = mx == -INFINITY ? 0.f : mx;
+      }
+      if (i < (kAsCore ? 2 : 1)) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sacc[v] -= shift;
+        for (int v = 0; v < 16; ++v) sacc[v] -= mb;
       }
       bf16x8_t pf[2];
-      float tsum = exponentials(sacc, pf);
-      if (__builtin_amdgcn_ballot_w64(!(tsum < kRebaseAbove)) != 0) {  // overflow guard: practically never
+      // what the tile's sums start at: nothing, or (as the main core) the first half of a tile of 64 keys
+      const float c0 = kAsCore && (i & 1) ? s0 : 0.f, c1 = kAsCore && (i & 1) ? s1 : 0.f;
+      s0 = c0;
+      s1 = c1;
+      exponentials(sacc, pf);
+      if (__builtin_amdgcn_ballot_w64(!(s0 + s1 < kRebaseAbove)) != 0) {  // overflow guard: practically never
         asm volatile("" ::: "memory");
         const float shift = fmaxf(row_max(sacc), 0.f);  // only ever raise the reference here
         const float alpha = __builtin_amdgcn_exp2f(-shift);
@@ -383,9 +408,11 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
         for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
           for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
-        tsum = exponentials(sacc, pf);
+        s0 = c0 * alpha;
+        s1 = c1 * alpha;
+        exponentials(sacc, pf);
       }
-      l_run += tsum;
+      if (!kAsCore || (i & 1) || i + 1 == wave_n_t) l_run += s0 + s1;
       // O^T += V^T P^T
 #pragma unroll
       for (int kc = 0; kc < 2; ++kc)
@@ -457,13 +484,13 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   }
 }
 
-template <int D, typename Meta>
+template <int D, typename Meta, bool kAsCore>
 hipError_t launch_short_t(const AttnParams &p, const Meta &meta, hipStream_t stream) {
   const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads;
   if (n_wg == 0) return hipSuccess;
   if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
   static_assert(SGeo<D>::LDS <= 64 * 1024, "fits the default dynamic LDS limit");
-  hipLaunchKernelGGL((encode_short_kernel<D, Meta>), dim3((unsigned)n_wg), dim3(kSThreads), SGeo<D>::LDS, stream, p,
+  hipLaunchKernelGGL((encode_short_kernel<D, Meta, kAsCore>), dim3((unsigned)n_wg), dim3(kSThreads), SGeo<D>::LDS, stream, p,
                      meta);
   return hipGetLastError();
 }
@@ -473,15 +500,16 @@ hipError_t launch_short_t(const AttnParams &p, const Meta &meta, hipStream_t str
 
 hipError_t launch_attn_encode_short(const AttnParams &p, const EncodeMeta &meta, hipStream_t stream) {
   if (p.n_splits != 1) return hipErrorInvalidValue;
-  if (p.head_dim == 128) return launch_short_t<128, EncodeMeta>(p, meta, stream);
-  if (p.head_dim == 64) return launch_short_t<64, EncodeMeta>(p, meta, stream);
+  const bool as_core = p.group < kSmallGroup;
+  if (p.head_dim == 128) return as_core ? launch_short_t<128, EncodeMeta, true>(p, meta, stream) : launch_short_t<128, EncodeMeta, false>(p, meta, stream);
+  if (p.head_dim == 64) return as_core ? launch_short_t<64, EncodeMeta, true>(p, meta, stream) : launch_short_t<64, EncodeMeta, false>(p, meta, stream);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_attn_prompt_short(const AttnParams &p, const PromptMeta &meta, hipStream_t stream) {
   if (p.n_splits != 1) return hipErrorInvalidValue;
-  if (p.head_dim == 128) return launch_short_t<128, PromptMeta>(p, meta, stream);
-  if (p.head_dim == 64) return launch_short_t<64, PromptMeta>(p, meta, stream);
+  if (p.head_dim == 128) return launch_short_t<128, PromptMeta, false>(p, meta, stream);
+  if (p.head_dim == 64) return launch_short_t<64, PromptMeta, false>(p, meta, stream);
   return hipErrorInvalidValue;
 }
 

@@ -126,6 +126,8 @@ constexpr int kBwdTileKeys = 64;     // keys per workgroup of the dk/dv kernel
 // Per-block encoding sends blocks up to this length through the short-block schedule (measured
 // crossover: beyond about 6,000 to 8,000 tokens the deep pipeline of the main core wins).
 constexpr int kShortMaxLen = 6144;
+// Per-block encoding with fewer query heads per KV head than this gives the same bits on either schedule.
+constexpr int kSmallGroup = 4;
 // ... and a whole call, by its longest block, at head_dim 64 with fewer than four query heads per KV head
 constexpr int kShortMaxLenFewRows = 512;
 

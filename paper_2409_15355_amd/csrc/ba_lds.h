@@ -91,11 +91,12 @@ __device__ __forceinline__ void lds_wait() {
 // holds pairs kk * 8 + hf * 4 + (0..3); half-split pairs: fragments kk and kk + KCH/2 hold dims
 // kk * 16 + hf * 8 + (0..7) and their partners, i.e. pairs of those same numbers.  (Which product is the
 // fused one is written out: left to the compiler it changes with the code around it, and the forward and
-// the backward pass are to see the same rows.)
+// the backward pass are to see the same rows.  kAsCore: the choice that the main core's rotation compiles to,
+// which differs for the second member of an interleaved pair.)
 __device__ __forceinline__ int fragment_table_piece(int j, int hf, bool halves) {
   return halves ? (j / 4) * 8 + (j & 3) + hf * 4 : (j / 2) * 4 + (j & 1) + hf * 2;
 }
-template <int KCH>
+template <int KCH, bool kAsCore = false>
 __device__ __forceinline__ void rotate_fragments(u32x4_t (&raw)[KCH], const f32x4_t (&cs)[2 * KCH], bool halves) {
   if (!halves) {
 #pragma unroll
@@ -105,7 +106,8 @@ __device__ __forceinline__ void rotate_fragments(u32x4_t (&raw)[KCH], const f32x
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float x = bf16_lo(raw[kk][e]), y = bf16_hi(raw[kk][e]);
-        raw[kk][e] = pack_bf16(__builtin_fmaf(c[e], x, -(sn[e] * y)), __builtin_fmaf(c[e], y, sn[e] * x));
+        raw[kk][e] = pack_bf16(__builtin_fmaf(c[e], x, -(sn[e] * y)),
+                               kAsCore ? __builtin_fmaf(sn[e], x, c[e] * y) : __builtin_fmaf(c[e], y, sn[e] * x));
       }
     }
   } else {

@@ -277,6 +277,49 @@ def test_encode_with_token_strides_too_wide_for_the_short_block_schedule(ba):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(2, 2, 64), (4, 2, 64), (3, 1, 64), (2, 2, 128), (4, 2, 128), (6, 2, 128)])
+@pytest.mark.parametrize("layout,rope_mode", [(0, 1), (1, 1), (0, 0)])
+def test_small_groups_encode_to_the_same_bits_on_either_schedule(ba, hq, hkv, d, layout, rope_mode):
+    """Fewer than four query heads per KV head: which schedule a call takes depends on the whole call, so a
+    block's output must be the same bits on both.  Token strides of 2^18 elements force the main core (the
+    test above); blocks at the edges of both schedules' row tiles (128 and 256 packed rows), key tiles (32
+    and 64) and waves, and the first 64 keys, which set a row's reference."""
+    torch = torch_mod()
+    lens = [1, 31, 32, 33, 63, 64, 65, 97, 128, 129, 257]
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, stride = int(offs[-1]), 1 << 18
+    qb, kb, vb = gen_qkv(260 + hq + d, T, hq, hkv, d)
+    heads = ba.Heads(hq, hkv, d, 500000.0, rope_layout=layout)
+    o, k_local = gpu_encode(ba, heads, qb, kb, vb, offs, rope_mode=rope_mode)
+    q_big, o_big = (torch.zeros(T * stride, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    q, o_wide = q_big.as_strided((T, hq, d), (stride, d, 1)), o_big.as_strided((T, hq, d), (stride, d, 1))
+    q.copy_(dev_bf16(qb))
+    ws = torch.empty(max(1, ba.ba_encode_blocks_workspace_bytes(heads, offs, rope_mode, False)), dtype=torch.uint8, device="cuda")
+    ba.ba_encode_blocks(heads, q, dev_bf16(kb), dev_bf16(vb), o_wide, None, offs, rope_mode, ws)
+    torch.cuda.synchronize()
+    got, want = host_bits(o), host_bits(o_wide.contiguous())
+    for b, L in enumerate(lens):
+        assert np.array_equal(got[offs[b]:offs[b + 1]], want[offs[b]:offs[b + 1]]), f"block of {L}"
+    del q_big, o_big, q, o_wide
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (3, 1), (4, 1)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_a_blocks_encoding_does_not_depend_on_its_neighbours(ba, hq, hkv, d):
+    """One passage's output and rotated keys, alone in a call and next to blocks of 600 and 6,200 tokens (longer
+    than either schedule's line): the same bits, so that a passage may be encoded in any batch."""
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    qb, kb, vb = gen_qkv(280 + hq + d, 7000, hq, hkv, d)
+    first = slice(0, 128)
+    want, want_k = gpu_encode(ba, heads, qb[first], kb[first], vb[first], np.array([0, 128], dtype=np.int32))
+    for offs in ([0, 128, 728], [0, 128, 6328], [0, 128, 728, 6928]):
+        T = offs[-1]
+        o, k_local = gpu_encode(ba, heads, qb[:T], kb[:T], vb[:T], np.array(offs, dtype=np.int32))
+        assert np.array_equal(host_bits(o[:128]), host_bits(want)), offs
+        assert np.array_equal(host_bits(k_local[:128]), host_bits(want_k)), offs
+
+
 def test_encode_short_block_schedule_near_the_end_of_its_row_offsets(ba):
     """A 6,000-token block with q and o at a token stride of 2^17 elements: the largest row offsets
     the short-block schedule accepts (1.5 GB from the block's first row), checked on sampled rows
