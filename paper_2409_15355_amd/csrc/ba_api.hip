@@ -394,7 +394,7 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
                                   (int64_t)G * std::max(q->stride_head, o_out->stride_head));
   int64_t longest_block = 1;
   for (int b = 0; b < n_blocks; ++b) longest_block = std::max<int64_t>(longest_block, block_offsets[b + 1] - block_offsets[b]);
-  const int64_t short_max = ba::encode_short_max(G, D, widest, longest_block);
+  const int64_t short_max = ba::encode_short_max(heads, n_blocks, block_offsets, widest);
 
   bool table_written = false;
   for (int b0 = 0; b0 < n_blocks; b0 += ba::kEncMaxBlocks) {

@@ -126,10 +126,12 @@ constexpr int kBwdTileKeys = 64;     // keys per workgroup of the dk/dv kernel
 // Per-block encoding sends blocks up to this length through the short-block schedule (measured
 // crossover: beyond about 6,000 to 8,000 tokens the deep pipeline of the main core wins).
 constexpr int kShortMaxLen = 6144;
-// Per-block encoding with fewer query heads per KV head than this gives the same bits on either schedule.
+// Per-block encoding with fewer query heads per KV head than this gives the same bits on either schedule, and
+// a call takes one by its amount of work (encode_short_max).
 constexpr int kSmallGroup = 4;
-// ... and a whole call, by its longest block, at head_dim 64 with fewer than four query heads per KV head
-constexpr int kShortMaxLenFewRows = 512;
+constexpr int kSmallGroupShortLen = 512;  // no block longer than this: small workgroups
+constexpr int kFixedTiles = 4;            // what a workgroup of the main core spends besides its walk, in key tiles
+constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 
 struct AttnParams {
   const uint16_t *q;

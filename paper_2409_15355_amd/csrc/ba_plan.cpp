@@ -320,15 +320,31 @@ int32_t plan_final_blocks(const ba_heads *h, int32_t n_prompts, const int32_t *c
 
 // Blocks up to this length take the schedule with small workgroups, several to a compute unit; longer
 // ones the main core.  (The short-block kernel addresses the rows of a block with 32-bit element
-// offsets.)  Measured with groups of one and two at 16,384 tokens, short-block kernel / main core, us:
-// 8 heads of 128, 8 KV heads, blocks of 128: 44 / 64, 2048: 123 / 137, 6000: 200 / 211; 16 over 8: 55 / 76,
-// 177 / 213, 291 / 300; 4 over 4 of 64: 128: 23 / 29, 512: 31 / 30, 2048: 62 / 56, 6000: 122 / 102 (at
-// head_dim 64 a tile holds so little work that a long walk is a chain of waits for tiles of 32 keys, with
-// no other heads in the group to fill them; the main core's are of 64 and three deep).  There the longest
-// block decides for the call: a second launch costs more than either schedule gains.
-int64_t encode_short_max(int G, int head_dim, int64_t widest_stride, int64_t longest_block) {
+// offsets.)
+// Fewer than four query heads per KV head make few row tiles of a block, and both schedules give such a call
+// the same bits, so the call as a whole takes one.  The main core walks a long block faster (a tile of 64 keys
+// in 1.0 us against two of 32 in 1.5, D = 128), but runs one workgroup per compute unit and spends on each
+// what four tiles take: the small workgroups win where there are more of those than compute units to run
+// them.  So the main core has the call if a block is long enough to tell (512 tokens) and its own work (a
+// workgroup's mean walk and the fixed part, over all compute units) comes to no more than two thirds of
+// its longest workgroup.  Main core / small workgroups, us: 8 over 8 heads of 128: one block of 2,048: 52 / 60,
+// of 6,144: 121 / 154, two of 6,144: 222 / 204, 24 of 512: 72 / 59; 4 over 4 of 64: 8 of 2,048: 50 / 60; 3 over 1 of
+// 64: 24 of 1,024: 43 / 32, 8 of 2,048: 44 / 46; 16 over 8 of 128: one of 6,000 and 160 of 200: 362 / 273, and at 2
+// over 2: 134 / 159.  Of 706 calls of such groups (1 to 8,000 row tiles) the rule leaves these with the slower
+// schedule by 2 % or more: 24 blocks of 384 and 512 at 4 over 4 heads of 128 (4 %), two of 6,144 at 24 over 8 (3 %).
+int64_t encode_short_max(const ba_heads *h, int32_t n_blocks, const int32_t *offs, int64_t widest_stride) {
   if (((int64_t)kShortMaxLen + 1) * widest_stride >= 0x40000000) return -1;
-  if (head_dim == 64 && G < 4 && longest_block > kShortMaxLenFewRows) return -1;
+  const int G = h->n_q_heads / h->n_kv_heads;
+  if (G >= kSmallGroup) return kShortMaxLen;
+  int64_t longest = 0, twice_load = 0;  // in key tiles; over the main core's workgroups
+  for (int b = 0; b < n_blocks; ++b) {
+    const int64_t len = (int64_t)offs[b + 1] - offs[b];
+    const int64_t n_t = (len + kTileKeys - 1) / kTileKeys;
+    longest = std::max(longest, len);
+    twice_load += (len * G + kTileRows - 1) / kTileRows * h->n_kv_heads * (n_t + 1 + 2 * kFixedTiles);
+  }
+  const int64_t longest_wg = (longest + kTileKeys - 1) / kTileKeys + kFixedTiles;
+  if (longest > kSmallGroupShortLen && 3 * twice_load <= 4 * kEncodeCus * longest_wg) return -1;
   return kShortMaxLen;
 }
 
@@ -491,9 +507,7 @@ int64_t ba_schedule_encode_blocks(const ba_heads *heads, int32_t n_blocks, const
   if ((rc = ba::check_heads(heads, true))) return rc;
   if ((rc = ba::check_offsets(n_blocks, block_offsets))) return rc;
   const int G = heads->n_q_heads / heads->n_kv_heads;
-  int64_t longest_block = 0;
-  for (int b = 0; b < n_blocks; ++b) longest_block = std::max<int64_t>(longest_block, (int64_t)block_offsets[b + 1] - block_offsets[b]);
-  const int64_t short_max = ba::encode_short_max(G, heads->head_dim, (int64_t)heads->n_q_heads * heads->head_dim, longest_block);
+  const int64_t short_max = ba::encode_short_max(heads, n_blocks, block_offsets, (int64_t)heads->n_q_heads * heads->head_dim);
   ba::ItemSink sink{items, items ? max_items : 0};
   int launch = 0;
   for (int b0 = 0; b0 < n_blocks; b0 += ba::kEncMaxBlocks) {

@@ -97,9 +97,9 @@ int32_t plan_final_blocks(const ba_heads *h, int32_t n_prompts, const int32_t *c
 // the short-block schedule takes, -1 for none.
 int32_t build_encode_metas(const int32_t *block_offsets, int b0, int n, int G, int64_t short_max, EncodeMeta meta[2],
                            int64_t tiles[2]);
-// Longest block the short-block schedule takes in a call of this group size, these strides (elements) and
-// this longest block.
-int64_t encode_short_max(int G, int head_dim, int64_t widest_stride, int64_t longest_block);
+// Longest block of a call that the short-block schedule takes, -1 for none; widest_stride: in elements, of q
+// and o per token.
+int64_t encode_short_max(const ba_heads *h, int32_t n_blocks, const int32_t *offs, int64_t widest_stride);
 
 // Whole prompts (Section 2.4): non-empty blocks with the first key they see and (for passages) their
 // prompt's last block.

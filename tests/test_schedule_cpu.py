@@ -124,6 +124,25 @@ def test_encode_items_cover_the_block_diagonal_mask_exactly(hq, hkv):
             assert {w.tile_rows for w in items if w.problem in (1, 3)} == {128}
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_small_groups_encode_on_the_main_core_where_few_long_blocks_leave_compute_units_idle(d):
+    """Fewer than four query heads per KV head: small workgroups up to 512 tokens a block, and above where there
+    is enough work for them; a few long blocks keep the main core.  One schedule for all of a call's blocks."""
+    tile_rows = lambda hq, hkv, lens: {w.tile_rows for w in ba.ba_schedule_encode_blocks(
+        ba.Heads(hq, hkv, d, 10000.0), np.concatenate([[0], np.cumsum(lens)]))}
+    for g in (1, 2, 3):
+        assert tile_rows(8 * g, 8, [128]) == tile_rows(8 * g, 8, [512]) == {128}
+        assert tile_rows(8 * g, 8, [512, 1, 300]) == {128}
+        assert tile_rows(8 * g, 8, [513]) == tile_rows(8 * g, 8, [2048]) == {256}
+        assert tile_rows(2 * g, 2, [6144]) == tile_rows(2 * g, 2, [6000] + [200] * 40) == {256}
+        assert tile_rows(8 * g, 8, [1000] * 33) == {128}
+    assert tile_rows(16, 8, [6000] + [200] * 160) == tile_rows(8, 8, [6144, 6144]) == {128}
+    assert tile_rows(8, 8, [6144]) == tile_rows(16, 8, [2048, 2048]) == {256}
+    for g in (4, 8):  # (from four on by a block's own length)
+        assert tile_rows(8 * g, 8, [6144]) == tile_rows(g, 1, [513]) == {128}
+        assert tile_rows(g, 1, [6145, 5]) == {128, 256}
+
+
 @pytest.mark.parametrize("hq,hkv", [(32, 8), (8, 2)])
 def test_whole_prompt_items_cover_the_mask_of_section_2_4_exactly(hq, hkv):
     rng = np.random.default_rng(13 + hq)
