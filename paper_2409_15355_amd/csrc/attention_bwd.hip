@@ -153,8 +153,9 @@ __device__ __forceinline__ void rotate_back(f32x16_t (&acc)[D / 32], const f32x4
 // dq.  Bound by memory: q, dO and O in, q^ and dq out are 1.36 GB at 33,130 tokens of 32 heads of 128 (250 us
 // at the 5.4 TB/s such a mix reaches here), and 1.88 GB move with the keys and values (re-read by a block's
 // row tiles where L2 has let go of them).  350 us on rows that a pre-pass of 125 us had rotated; 386 rotating
-// them itself; 357 with the rows that pass once marked non-temporal.  287 of it remain with one key tile each.
-template <int D>
+// them itself; 357 with the rows that pass once marked non-temporal (kPast, in calls larger than the cache).  287
+// of it remain with one key tile each.
+template <int D, bool kPast>
 __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, PromptMeta meta, BwdParams bp) {
   using G = BGeo<D>;
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const int64_t last_off = (int64_t)(lq - 1) * st + (int64_t)(Gq - 1) * sh;
     walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       const int64_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
-      ld_q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(qbase + (o * 2 + (lane % G::CPR) * 16)));
+      ld_q[u] = load_row_piece<kPast>(qbase + (o * 2 + (lane % G::CPR) * 16));
     });
   }
   {
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const uint32_t last_off = (uint32_t)(lq - 1) * st + (uint32_t)(Gq - 1) * sh;
     walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       const uint32_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
-      ld_do[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(dbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u)));
+      ld_do[u] = load_row_piece<kPast>(dbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
     });
   }
   // ... and of O, for delta = rowsum(dO o O); this lane's row's log-sum-exp (to base-2 units below)
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const uint32_t last_off = (uint32_t)(lq - 1) * st + (uint32_t)(Gq - 1) * sh;
     walk_rows(st, sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       const uint32_t o = wr_r0 < n_rows - u * G::QRPI ? off : last_off;
-      ld_o[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(obase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u)));
+      ld_o[u] = load_row_piece<kPast>(obase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
     });
   }
   const float my_lse = bp.lse[(int64_t)(q_tok0 + my_tok) * p.n_q_heads + kvh * Gq + (my_row - my_tok * Gq)];
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     char *obase = (char *)(bp.dq + (int64_t)q_tok0 * bp.dq_st + (int64_t)(kvh * Gq) * bp.dq_sh);
     walk_rows((uint32_t)bp.dq_st, (uint32_t)bp.dq_sh, [&](int u, auto off, int wr_r0) __attribute__((always_inline)) {
       if (wr_r0 < n_rows - u * G::QRPI)
-        __builtin_nontemporal_store(w[u], reinterpret_cast<u32x4_t *>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u)));
+        store_row_piece<kPast>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u), w[u]);
     });
   }
 }
@@ -790,7 +791,10 @@ hipError_t launch_dq_t(const AttnParams &p, const PromptMeta &meta, const BwdPar
   if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
   constexpr size_t lds = (size_t)2 * kBBuf * BGeo<D>::TILEB;
   static_assert(lds <= 64 * 1024, "fits the default dynamic LDS limit");
-  hipLaunchKernelGGL((bwd_dq_kernel<D>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
+  if (p.rows_past_cache)
+    hipLaunchKernelGGL((bwd_dq_kernel<D, true>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
+  else
+    hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
   return hipGetLastError();
 }
 

@@ -13,9 +13,9 @@
 //     with one workgroup barrier per tile.  A wave whose rows all lie before a tile's first key
 //     skips that tile's arithmetic.
 //   - Rows of q and o pass once, 32 KB per workgroup, between K/V tiles that the block's other row tiles
-//     read again: they carry the non-temporal hint (160 passages of 100 to 300 tokens, 681 MB: 157 -> 151 us;
-//     101 of it remain with no key tiles walked at all).  A tenth fewer vector instructions changed nothing:
-//     the stream bounds it, not the issue.
+//     read again: in calls larger than the cache they carry the non-temporal hint (kPast; 160 passages of 100
+//     to 300 tokens, 681 MB: 157 -> 151 us; 101 of it remain with no key tiles walked at all).  A tenth fewer
+//     vector instructions changed nothing: the stream bounds it, not the issue.
 //   - Any group size: a row tile is 32 packed rows to a wave whatever tokens and heads they are.
 //   - Arithmetic, operand layouts and rounding are those of the main core; the softmax takes its reference
 //     from the first tile and moves it only to avoid overflow.  The main core's tiles are of 64 keys, so
@@ -60,7 +60,8 @@ struct SGeo {
 // prompt for its last block (Section 2.4: the lower-triangular mask with only the last block seeing
 // the others); keys and queries then carry positions inside the prompt.
 // kAsCore: the numbers of the main core (the reference from the first 64 keys, sums by 64 keys).
-template <int D, typename Meta, bool kAsCore>
+// kPast: rows of q and o go past the caches (see kCacheBytes).
+template <int D, typename Meta, bool kAsCore, bool kPast>
 __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p, Meta meta) {
   using G = SGeo<D>;
   constexpr bool kPrompt = std::is_same<Meta, PromptMeta>::value;
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     const uint32_t last_off = (uint32_t)(lq - 1) * q_st + (uint32_t)(Gq - 1) * q_sh;  // the block's last row
     walk_rows(lane, q_st, q_sh, [&](int u, uint32_t off, int wr_r0) __attribute__((always_inline)) {
       const uint32_t o = wr_r0 < n_rows - u * QRPI ? off : last_off;
-      ld[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(qbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u)));
+      ld[u] = load_row_piece<kPast>(qbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
     });
     if (p.q_table && Gq >= 4) {
       // The rows of a wave span at most 8 tokens.  Chunk c of token row t sits at chunk c ^ (t & 7),
@@ -472,7 +473,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     char *obase = (char *)(p.o + (int64_t)q_tok0 * p.o_st + (int64_t)(kvh * Gq) * p.o_sh);
     walk_rows(ln, (uint32_t)p.o_st, (uint32_t)p.o_sh, [&](int u, uint32_t off, int wr_r0) __attribute__((always_inline)) {
       if (wr_r0 < n_rows - u * QRPI)
-        __builtin_nontemporal_store(w[u], reinterpret_cast<u32x4_t *>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u)));
+        store_row_piece<kPast>(obase + (off * 2u + (uint32_t)(ln % G::CPR) * 16u), w[u]);
     });
   }
   // the row's log-sum-exp of its scaled scores (natural logarithm), for a backward pass
@@ -484,14 +485,16 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   }
 }
 
-template <int D, typename Meta, bool kAsCore>
+template <int D, bool kAsCore, typename Meta>
 hipError_t launch_short_t(const AttnParams &p, const Meta &meta, hipStream_t stream) {
   const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads;
   if (n_wg == 0) return hipSuccess;
   if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
   static_assert(SGeo<D>::LDS <= 64 * 1024, "fits the default dynamic LDS limit");
-  hipLaunchKernelGGL((encode_short_kernel<D, Meta, kAsCore>), dim3((unsigned)n_wg), dim3(kSThreads), SGeo<D>::LDS, stream, p,
-                     meta);
+  if (p.rows_past_cache)
+    hipLaunchKernelGGL((encode_short_kernel<D, Meta, kAsCore, true>), dim3((unsigned)n_wg), dim3(kSThreads), SGeo<D>::LDS, stream, p, meta);
+  else
+    hipLaunchKernelGGL((encode_short_kernel<D, Meta, kAsCore, false>), dim3((unsigned)n_wg), dim3(kSThreads), SGeo<D>::LDS, stream, p, meta);
   return hipGetLastError();
 }
 
@@ -501,15 +504,15 @@ hipError_t launch_short_t(const AttnParams &p, const Meta &meta, hipStream_t str
 hipError_t launch_attn_encode_short(const AttnParams &p, const EncodeMeta &meta, hipStream_t stream) {
   if (p.n_splits != 1) return hipErrorInvalidValue;
   const bool as_core = p.group < kSmallGroup;
-  if (p.head_dim == 128) return as_core ? launch_short_t<128, EncodeMeta, true>(p, meta, stream) : launch_short_t<128, EncodeMeta, false>(p, meta, stream);
-  if (p.head_dim == 64) return as_core ? launch_short_t<64, EncodeMeta, true>(p, meta, stream) : launch_short_t<64, EncodeMeta, false>(p, meta, stream);
+  if (p.head_dim == 128) return as_core ? launch_short_t<128, true>(p, meta, stream) : launch_short_t<128, false>(p, meta, stream);
+  if (p.head_dim == 64) return as_core ? launch_short_t<64, true>(p, meta, stream) : launch_short_t<64, false>(p, meta, stream);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_attn_prompt_short(const AttnParams &p, const PromptMeta &meta, hipStream_t stream) {
   if (p.n_splits != 1) return hipErrorInvalidValue;
-  if (p.head_dim == 128) return launch_short_t<128, PromptMeta, false>(p, meta, stream);
-  if (p.head_dim == 64) return launch_short_t<64, PromptMeta, false>(p, meta, stream);
+  if (p.head_dim == 128) return launch_short_t<128, false>(p, meta, stream);
+  if (p.head_dim == 64) return launch_short_t<64, false>(p, meta, stream);
   return hipErrorInvalidValue;
 }
 

@@ -392,6 +392,7 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
   // short blocks take the schedule with small workgroups, several to a compute unit; longer ones the main core
   const int64_t widest = std::max(std::max(q->stride_tok, o_out->stride_tok),
                                   (int64_t)G * std::max(q->stride_head, o_out->stride_head));
+  ap.rows_past_cache = (int64_t)block_offsets[n_blocks] * 2 * (heads->n_q_heads + heads->n_kv_heads) * D * 2 > ba::kCacheBytes;  // q, o; k, v
   int64_t longest_block = 1;
   for (int b = 0; b < n_blocks; ++b) longest_block = std::max<int64_t>(longest_block, block_offsets[b + 1] - block_offsets[b]);
   const int64_t short_max = ba::encode_short_max(heads, n_blocks, block_offsets, widest);

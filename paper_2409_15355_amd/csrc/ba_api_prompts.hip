@@ -204,6 +204,7 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
   ap.q_ready = 0;
   ap.rope_layout = heads->rope_layout;
   ap.n_splits = 1;
+  ap.rows_past_cache = T * 2 * (heads->n_q_heads + heads->n_kv_heads) * D * 2 > ba::kCacheBytes;  // q, o; k, v
 
   // Blocks go to the kernel longest key range first (see the planner).
   std::vector<ba::PromptBlock> blks = ba::list_prompt_blocks(n_prompts, cu_blk, block_offsets);
@@ -376,6 +377,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   ap.group_div = ba::make_fast_div((uint32_t)G);
   ap.head_dim = D;
   ap.n_splits = 1;
+  ap.rows_past_cache = T * (5 * hq + 2 * hkv) * D * 2 > ba::kCacheBytes;  // q, dO, O, q^, dq; k, v
 
   const std::vector<ba::PromptBlock> blks = ba::list_prompt_blocks(n_prompts, cu_blk, block_offsets);
   typedef ba::PromptBlock Blk;

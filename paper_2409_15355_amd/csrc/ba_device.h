@@ -28,6 +28,18 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, b);
 }
 
+// 16 bytes of a row that passes once; kHint: past the caches (see kCacheBytes)
+template <bool kHint>
+__device__ __forceinline__ u32x4_t load_row_piece(const char *from) {
+  const u32x4_t *p = reinterpret_cast<const u32x4_t *>(from);
+  return kHint ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool kHint>
+__device__ __forceinline__ void store_row_piece(char *to, const u32x4_t &w) {
+  u32x4_t *p = reinterpret_cast<u32x4_t *>(to);
+  if (kHint) __builtin_nontemporal_store(w, p); else *p = w;
+}
+
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f) {
   const uint32_t t = __umulhi(n, f.mul);
   return (t + ((n - t) >> f.sh1)) >> f.sh2;

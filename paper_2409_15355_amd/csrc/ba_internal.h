@@ -126,6 +126,14 @@ constexpr int kBwdTileKeys = 64;     // keys per workgroup of the dk/dv kernel
 // Per-block encoding sends blocks up to this length through the short-block schedule (measured
 // crossover: beyond about 6,000 to 8,000 tokens the deep pipeline of the main core wins).
 constexpr int kShortMaxLen = 6144;
+// The cache in front of HBM.  Query-side rows pass once, between K/V tiles that are read again; where a call's rows
+// exceed this cache, they carry the non-temporal hint.  Below, the hint sends them past a cache that would
+// have held them (from the kernel before, and for the one behind).  Without / with it, us, and MB of rows:
+// per-block encoding, blocks of 200, 32 over 8 heads of 128: 6,000 tokens (123) 39.0 / 43.0, 12,000 (246) 67.6 / 69.4,
+// 16,000 (328) 95.2 / 88.6; 16 over 8: 16,000 (197) 61.4 / 64.5, 24,000 (295) 94.4 / 87.7; 8 over 2 of 64: 66,000 (169)
+// 61.9 / 65.0.  Forward and backward, prompts of 20 x 200 + 64 tokens, MB in the dq kernel: 16 over 8 of 128: two
+// (200) 287 / 289, three (300) 334 / 328; 32 over 8: two (366) 337 / 332; 8 over 2 of 64: eight (183) 239 / 245.
+constexpr int64_t kCacheBytes = 256 << 20;
 // Per-block encoding with fewer query heads per KV head than this gives the same bits on either schedule, and
 // a call takes one by its amount of work (encode_short_max).
 constexpr int kSmallGroup = 4;
@@ -180,6 +188,7 @@ struct AttnParams {
   ItemDivs item_divs;   // ... and the divisors of item_coords
   SplitDivs split_divs; // divisions by n_splits and 2 n_splits (main core; filled at the launch)
   float *lse;           // short-block schedule: [tokens][n_q_heads] log-sum-exp of the scaled scores, or null
+  int32_t rows_past_cache;  // short-block schedule, dq kernel: the call's rows exceed kCacheBytes
 };
 
 constexpr int kEncMaxBlocks = 320;

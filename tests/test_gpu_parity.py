@@ -1704,3 +1704,42 @@ def test_many_splits_for_few_kv_heads(ba, hq, hkv, d, ctx, nq):
         heads = ba.Heads(hq, hkv, d, base, xcd_speed=speeds)
         o = gpu_final(ba, heads, dev_bf16(qb), dev_bf16(kc), dev_bf16(vc), dev_bf16(kb), dev_bf16(vb), cu_q, cu_ctx)
         assert_attention_close(host_f64(o), ref, f"speeds {speeds}")
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_prompts", [(32, 8, 128, 4), (16, 8, 128, 6), (64, 16, 64, 4), (32, 16, 64, 6)])
+def test_a_call_larger_than_the_cache_gives_the_bits_of_its_parts(ba, hq, hkv, d, n_prompts):
+    """Calls whose rows exceed the cache (256 MB) move them with other loads and stores; which loads must not
+    show: per-block encoding, whole prompts and their gradients of several prompts in one call, against one
+    of them alone (an eighth of a GB and less)."""
+    torch = torch_mod()
+    block = [200] * 20 + [64]
+    offs1 = np.concatenate([[0], np.cumsum(block)]).astype(np.int32)
+    t1 = int(offs1[-1])
+    offs = np.concatenate([[0], np.cumsum(block * n_prompts)]).astype(np.int32)
+    cu_blk = (np.arange(n_prompts + 1) * len(block)).astype(np.int32)
+    T = t1 * n_prompts
+    assert T * 2 * (hq + hkv) * d * 2 > (256 << 20) > 3 * t1 * 2 * (hq + hkv) * d * 2 // 2
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v, do = (torch.randn((T, h, d), generator=gen, device="cuda").to(torch.bfloat16) for h in (hq, hkv, hkv, hq))
+    heads = ba.Heads(hq, hkv, d, 500000.0)
+
+    def everything(rows, offs, cu_blk):
+        x = [t[rows] for t in (q, k, v, do)]
+        o, op = torch.empty_like(x[0]), torch.empty_like(x[0])
+        lse = torch.empty(x[0].shape[:2], dtype=torch.float32, device="cuda")
+        dq, dk, dv = (torch.empty_like(t) for t in x[:3])
+        scratch = lambda n: torch.empty(max(int(n), 256), dtype=torch.uint8, device="cuda")
+        ba.ba_encode_blocks(heads, *x[:3], o, None, offs, ba.ROPE_APPLY, scratch(ba.ba_encode_blocks_workspace_bytes(heads, offs, ba.ROPE_APPLY, False)))
+        ba.ba_block_attention_prompts(heads, *x[:3], op, None, lse, cu_blk, offs, ba.ROPE_APPLY,
+                                      scratch(ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False)))
+        ba.ba_block_attention_prompts_backward(heads, *x[:3], op, lse, x[3], dq, dk, dv, cu_blk, offs,
+                                               scratch(ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs)))
+        torch.cuda.synchronize()
+        return o, op, lse, dq, dk, dv
+
+    whole = everything(slice(0, T), offs, cu_blk)
+    for n in (0, n_prompts - 1):
+        rows = slice(n * t1, (n + 1) * t1)
+        part = everything(rows, offs1, np.array([0, len(block)], dtype=np.int32))
+        for name, a, b in zip(("encode", "prompts", "lse", "dq", "dk", "dv"), whole, part):
+            assert torch.equal(a[rows], b), (name, n)
