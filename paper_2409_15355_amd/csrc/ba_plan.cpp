@@ -70,7 +70,9 @@ int32_t check_prompt_blocks(int32_t n_prompts, const int32_t *cu_blk, const int3
 int choose_splits(int64_t base_wgs, int max_tiles, int n_cu) {
   if (base_wgs <= 0) return 1;
   if (n_cu < 1) n_cu = 1;
-  const int s_max = std::min(kMaxSplits, std::max(1, max_tiles / 4));
+  // (from eight workgroups per split on, 32 splits fill the chip: more would only grow the partials, beyond the
+  // static scratch for contexts of 400,000 tokens and more, and leave the shares by XCD speed, kMaxCutSplits)
+  const int s_max = std::min(base_wgs < 8 ? kMaxSplits : kMaxCutSplits, std::max(1, max_tiles / 4));
   const double merge = 0.25 * std::min(1.0, (double)base_wgs / 8);
   int best = 1;
   double best_cost = 0;

@@ -219,6 +219,29 @@ def test_split_range_arithmetic_partitions_every_walk():
     assert len(seen_splits) >= 6 and max(seen_splits) >= 16
 
 
+def test_splits_of_very_long_contexts_stay_within_the_static_scratch():
+    """From eight workgroups per split on (row tiles x KV heads) never more than 32 splits, whatever the context, so
+    that the partials of such a call do not outgrow the scratch of ba_final_block_attention_static with its
+    length, and with measured XCD speeds its splits are still sized by them; fewer workgroups, up to 64, fit too."""
+    static = ba.STATIC_SCRATCH_BYTES
+    speeds = [1.03, 0.97, 1.02, 0.97, 1.03, 1.0, 1.02, 0.95]
+    for hkv, tiles in [(1, 8), (1, 10), (1, 13), (1, 19), (1, 25), (2, 5), (2, 14), (8, 1), (1, 31), (2, 31), (4, 31)]:
+        for tc in (430000, 600000, 900000, 1600000):
+            cu_q, cu_ctx = [0, 8 * tiles], [0, tc]
+            for speed in (None, speeds):
+                h = ba.Heads(32 * hkv, hkv, 128, 500000.0, xcd_speed=speed)
+                items = ba.ba_schedule_final_block(h, cu_q, cu_ctx)
+                assert items[0].n_splits <= 32, (hkv, tiles, tc)
+                if speed and items[0].n_splits > 1:
+                    assert items[0].kv_head >= 0, (hkv, tiles, tc)   # (a KV head's own shares)
+            assert ba.ba_final_block_attention_workspace_bytes(h, cu_q, cu_ctx) <= static, (hkv, tiles, tc)
+    for base in range(1, 8):
+        for g, hkv, lq in ([(32, 1, 8 * base), (1, base, 256), (32, base, 8)]):
+            for tc in (8000, 31950, 128000, 1600000):
+                h = ba.Heads(g * hkv, hkv, 128, 500000.0)
+                assert ba.ba_final_block_attention_workspace_bytes(h, [0, lq], [0, tc]) <= static, (base, g, hkv, tc)
+
+
 @pytest.mark.parametrize("speeds", [[1.0] * 8, [0.92, 1.0, 1.08, 1.0, 0.95, 1.05, 1.0, 1.0], [0.5, 2.0, 0.5, 2.0, 1.0, 1.0, 1.0, 1.0]])
 def test_splits_sized_by_xcd_speed_still_cover_the_mask_exactly(speeds):
     """ba_heads.xcd_speed moves the boundaries between KV splits (faster XCDs get more key tiles); the
