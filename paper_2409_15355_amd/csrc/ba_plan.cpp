@@ -62,18 +62,22 @@ int32_t check_prompt_blocks(int32_t n_prompts, const int32_t *cu_blk, const int3
 
 // One workgroup runs per compute unit, so a launch takes ceil(workgroups / CUs) rounds, each as long
 // as one workgroup: a fixed part (prologue, output, worth about four key tiles) plus its share of the
-// key tiles; every split also adds to the merge, the less the fewer rows there are (a workgroup's row tile
-// at one KV head is 64 KB per split at D = 128).  Take the cheapest count, never fewer than four key tiles
-// per split.  Few KV heads and a long context want many: measured at 31,950 context tokens, 50 queries, 32
-// splits / 64, us: 4 over 4 heads of 64: 24.3 / 21.0, 8 over 2 of 64: 28.9 / 23.5, 4 over 1 of 128: 30.5 / 24.9;
-// at 8,000 tokens, 64 queries, 4 over 4 of 64, 14 splits (a merge priced as for eight workgroups) / 32: 20.3 / 17.1.
-int choose_splits(int64_t base_wgs, int max_tiles, int n_cu) {
+// key tiles; every split also adds a little to the merge.  Take the cheapest count, never fewer than four
+// key tiles per split.
+// Few workgroups per split and a long context want many splits, and have few rows to merge (64 KB per workgroup
+// and split at D = 128): up to 64 splits, the merge priced by its rows.  32 splits at most / up to 64, us: 50
+// queries, 31,950 tokens: 4 over 4 heads of 64: 24.3 / 21.0, 8 over 2 of 64: 28.9 / 23.5, 4 over 1 of 128: 30.5 / 24.9;
+// 64,000: 6 over 6 of 64: 35.7 / 31.7, 7 over 7: 36.1 / 34.6, 16 over 4 of 128: 49.2 / 43.8.  At D = 128 five workgroups
+// gain only where the merge at its full price leaves a gain (20 over 5, 60 queries: 24,000 tokens 30.1 with 32, 30.9 with 51; 64,000
+// 52.4 / 50.2), six and seven hardly ever (28 over 7, one query: 16,000 24.9 / 25.6, 64,000 48.1 / 49.1).
+// From eight on, 32 splits fill the chip: more would only grow the partials, beyond the static scratch for
+// contexts of 400,000 tokens and more, and leave the shares by XCD speed (kMaxCutSplits).
+int choose_splits(int64_t base_wgs, int max_tiles, int n_cu, int head_dim) {
   if (base_wgs <= 0) return 1;
   if (n_cu < 1) n_cu = 1;
-  // (from eight workgroups per split on, 32 splits fill the chip: more would only grow the partials, beyond the
-  // static scratch for contexts of 400,000 tokens and more, and leave the shares by XCD speed, kMaxCutSplits)
-  const int s_max = std::min(base_wgs < 8 ? kMaxSplits : kMaxCutSplits, std::max(1, max_tiles / 4));
-  const double merge = 0.25 * std::min(1.0, (double)base_wgs / 8);
+  const int64_t row_bytes = base_wgs * head_dim;  // of a split's partials, in units that compare only
+  const int s_max = std::min(base_wgs < 8 && row_bytes <= 5 * 128 ? kMaxSplits : kMaxCutSplits, std::max(1, max_tiles / 4));
+  const double merge = row_bytes <= 4 * 128 ? 0.25 * std::min(1.0, (double)base_wgs / 8) : 0.25;
   int best = 1;
   double best_cost = 0;
   for (int s = 1; s <= s_max; ++s) {
@@ -106,7 +110,7 @@ int32_t plan_final(const ba_heads *h, int32_t n_prompts, const int32_t *cu_q, co
     pl.max_nt = std::max(pl.max_nt, nt);
   }
   pl.lq_total = n_prompts > 0 ? cu_q[n_prompts] : 0;
-  pl.n_splits = choose_splits(pl.total_tiles * h->n_kv_heads, pl.max_nt, n_cu);
+  pl.n_splits = choose_splits(pl.total_tiles * h->n_kv_heads, pl.max_nt, n_cu, h->head_dim);
   if (rope_mode == BA_ROPE_APPLY) {
     if (!have_rot_out) pl.kf_bytes = (size_t)pl.lq_total * h->n_kv_heads * h->head_dim * 2;
     pl.q_bytes = (size_t)pl.lq_total * h->n_q_heads * h->head_dim * 2;  // rotated, pre-scaled queries
@@ -306,7 +310,7 @@ int32_t plan_final_blocks(const ba_heads *h, int32_t n_prompts, const int32_t *c
   if (max_nb > kBlkMaxBlocks)
     return fail(BA_ERR_UNSUPPORTED, "%lld cached blocks in one prompt, at most %d when the kernel reads the block table",
                 (long long)max_nb, kBlkMaxBlocks);
-  pl.n_splits = choose_splits(pl.total_tiles * h->n_kv_heads, pl.max_nt, n_cu);
+  pl.n_splits = choose_splits(pl.total_tiles * h->n_kv_heads, pl.max_nt, n_cu, h->head_dim);
   if (!have_rot_out) pl.kf_bytes = (size_t)pl.lq_total * h->n_kv_heads * h->head_dim * 2;
   pl.q_bytes = (size_t)pl.lq_total * h->n_q_heads * h->head_dim * 2;
   pl.rot_bytes = (size_t)pl.n_blocks * h->head_dim * 4;  // D/2 (cos, sin) pairs per block

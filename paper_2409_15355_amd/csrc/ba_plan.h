@@ -33,7 +33,7 @@ int32_t check_prompt_blocks(int32_t n_prompts, const int32_t *cu_blk, const int3
 
 // Number of KV splits of a final-block launch of base_wgs workgroups (row tiles x KV heads) whose
 // longest walk has max_tiles key tiles, on a device of n_cu compute units.
-int choose_splits(int64_t base_wgs, int max_tiles, int n_cu);
+int choose_splits(int64_t base_wgs, int max_tiles, int n_cu, int head_dim);
 
 struct FinalPlan {
   int64_t lq_total = 0;

@@ -219,6 +219,18 @@ def test_split_range_arithmetic_partitions_every_walk():
     assert len(seen_splits) >= 6 and max(seen_splits) >= 16
 
 
+def test_more_than_32_splits_only_where_they_were_measured_to_pay():
+    """Workgroups per split x head_dim decide: up to four of head_dim 128 and up to seven of 64 take up to 64 splits;
+    five of 128 only over contexts long enough for the merge; six and seven of 128 stay at 32."""
+    splits = lambda hkv, d, lq, tc: ba.ba_schedule_final_block(ba.Heads(4 * hkv, hkv, d, 500000.0), [0, lq], [0, tc])[0].n_splits
+    for tc in (16000, 31950, 64000, 128000):
+        assert splits(4, 128, 60, tc) > 32 and splits(1, 128, 60, tc) > 32
+        assert splits(6, 128, 60, tc) <= 32 and splits(7, 128, 60, tc) <= 32 and splits(3, 128, 128, tc) <= 32
+    for hkv in range(1, 8):
+        assert splits(hkv, 64, 50, 64000) > 32
+    assert splits(5, 128, 60, 16000) <= 32 < splits(5, 128, 60, 64000)
+
+
 def test_splits_of_very_long_contexts_stay_within_the_static_scratch():
     """From eight workgroups per split on (row tiles x KV heads) never more than 32 splits, whatever the context, so
     that the partials of such a call do not outgrow the scratch of ba_final_block_attention_static with its
