@@ -179,7 +179,7 @@ def test_whole_prompts_rejects_bad_arguments_and_sizes_workspace(lib):
     assert call(h, [0, 2, 2], [0, 5, 9]) == -1              # a prompt without a block
     assert call(h, [0, 2], [0, 9, 5]) == -1                 # offsets decrease
     assert call(h, [0, 2], [0, 5, 9], rope=7) == -1         # unknown rope mode
-    assert call(ba.Heads(4, 4, 64), [0, 2], [0, 5, 9]) == -4   # (fewer than four query heads per KV head: run padded) workspace missing
+    assert call(ba.Heads(4, 4, 64), [0, 2], [0, 5, 9]) == -4   # (fewer than four query heads per KV head) workspace missing
     assert call(h, [0, 2], [0, 5, 9]) == -4                 # workspace missing
     assert b"workspace" in lib.ba_last_error()
     # rotated keys + the table of factors (one (cos, sin) pair per token and dimension pair)
@@ -188,7 +188,8 @@ def test_whole_prompts_rejects_bad_arguments_and_sizes_workspace(lib):
     assert ba.ba_block_attention_prompts_workspace_bytes(h, [0, 2], [0, 100, 164], have_k_rot_out=True) == \
         (164 * 128 * 4 + 255) // 256 * 256
     assert ba.ba_block_attention_prompts_workspace_bytes(h, [0, 2], [0, 100, 164], ba.ROPE_NONE) == 0
-    # two query heads per KV head run as groups of four: padded q and o (4 heads per KV head), padded log-sum-exps
+    # two query heads per KV head: also room to run as groups of four where row offsets do not fit 32 bits (padded q
+    # and o, 4 heads per KV head, padded log-sum-exps)
     a256 = lambda n: (n + 255) // 256 * 256
     h2 = ba.Heads(16, 8, 128, 500000.0)
     assert ba.ba_block_attention_prompts_workspace_bytes(h2, [0, 2], [0, 100, 164], ba.ROPE_NONE) == \
@@ -222,7 +223,7 @@ def test_whole_prompts_backward_rejects_bad_arguments_and_sizes_workspace(lib):
     assert call(h, [1, 2], [0, 5, 9]) == -1                   # cu_blk[0] != 0
     assert call(h, [0, 2], [0, 9, 5]) == -1                   # offsets decrease
     assert call(h, [0, 2], [0, 5, 9], lse_p=None) == -1       # no log-sum-exps
-    assert call(ba.Heads(4, 4, 64), [0, 2], [0, 5, 9]) == -4  # (fewer than four query heads per KV head: run padded) workspace missing
+    assert call(ba.Heads(4, 4, 64), [0, 2], [0, 5, 9]) == -4  # (fewer than four query heads per KV head) workspace missing
     assert call(h, [0, 2], [0, 5, 9]) == -4                   # workspace missing
     # rotated q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row + padding
     T = 164

@@ -165,15 +165,21 @@ ENC_CASES = [
     ("ragged-mha-d64", 2, 2, 64, 10000.0, [300, 5, 0, 0, 511, 256]),
     ("gqa8-d128", 8, 1, 128, 10000.0, [33, 100]),
     ("gqa3-odd-group", 6, 2, 64, 10000.0, [90, 171]),
-    # groups of fewer than four query heads take the main core whatever the block length
+    # groups of fewer than four query heads: a block of more than 512 tokens in a call of little work takes the
+    # whole call to the main core
     ("long-mha-d64", 2, 2, 64, 10000.0, [530, 300, 5]),
+    ("long-gqa2-d128", 4, 2, 128, 500000.0, [513, 31, 700]),
+    ("long-gqa3-d64", 6, 2, 64, 10000.0, [90, 600, 171]),
+    ("long-gqa3-d128", 3, 1, 128, 10000.0, [520, 0, 64]),
     ("gqa2", 4, 2, 128, 10000.0, [512, 31]),
     # medium blocks: many key tiles per work item of the short-block schedule
     ("medium-gqa4", 8, 2, 128, 500000.0, [700, 1, 63, 130]),
     ("medium-gqa8-d64", 8, 1, 64, 10000.0, [1000, 333]),
-    # more blocks than one launch's table holds, on either schedule
+    # more blocks than one launch's table holds: small workgroups, and (the longest block beyond 512 tokens, in the
+    # last launch) the main core, whose later launches find the table of the first
     ("700-blocks-gqa4", 4, 1, 64, 10000.0, [1 + (7 * i) % 23 for i in range(700)]),
     ("700-blocks-mha", 2, 2, 64, 10000.0, [1 + (5 * i) % 17 for i in range(700)]),
+    ("700-blocks-mha-main-core", 2, 2, 64, 10000.0, [1 + (5 * i) % 17 for i in range(700)] + [900]),
     # the longest block lies in the second launch, and is longer than the whole first launch: the table of
     # rotation factors (a row per position inside a block) is written by the first launch for all of them
     ("long-block-in-second-launch", 4, 1, 64, 10000.0, [1 + i % 2 for i in range(320)] + [700, 3, 64]),
@@ -522,6 +528,24 @@ def test_late_keys_far_above_first_tile_move_the_reference(ba, where):
             ref, _ = oracle.encode_blocks(f(qb), f(kb), f(vb), offs, th)
             o, _ = gpu_encode(ba, heads, qb, kb, vb, offs)
     assert_attention_close(host_f64(o), ref, "late keys far above the first tile, " + where)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 2, 64), (2, 2, 128), (3, 1, 128)])
+def test_late_keys_move_the_reference_of_small_groups_on_the_short_block_schedule(ba, hq, hkv, d):
+    """The same for fewer than four query heads per KV head in blocks of up to 512 tokens: their reference comes
+    from the first 64 keys, two tiles, and moves in the first or the second half of a later pair."""
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    f = oracle.bf16_bits_to_f64
+    slow = d - 2
+    offs = np.array([0, 500, 760], dtype=np.int32)
+    qb, kb, vb = gen_qkv(930 + hq + d, 760, hq, hkv, d)
+    qb = _with_component(qb, slice(None), slow, 8.0 if d == 64 else 11.25)
+    kb = _with_component(kb, slice(None), slow, 0.0)
+    for low in (slice(0, 64), slice(500, 596)):  # (the second block's first late key: second half of a pair)
+        kb = _with_component(kb, low, slow, -32.0)
+    ref, _ = oracle.encode_blocks(f(qb), f(kb), f(vb), offs, oracle.theta(10000.0, d))
+    o, _ = gpu_encode(ba, heads, qb, kb, vb, offs)
+    assert_attention_close(host_f64(o), ref, "late keys far above the first tile")
 
 
 def test_final_block_rope_none_qpos_override_and_rot_out(ba):
@@ -1016,7 +1040,7 @@ PROMPT_CASES = [
     ("one-block-prompts", 4, 1, 64, 10000.0, [[90], [1], [33]]),
     ("empty-blocks-gqa8", 8, 1, 64, 10000.0, [[0, 65, 0, 20], [32, 0, 96]]),
     ("ragged-gqa4-d128", 4, 1, 128, 10000.0, [[129, 64, 63, 130], [200, 57]]),
-    # fewer than four query heads per KV head (run as groups of four with zero phantom heads)
+    # fewer than four query heads per KV head
     ("config1-mha-d64", 4, 4, 64, 10000.0, [[128, 128, 64]]),
     ("gqa2-d128", 4, 2, 128, 500000.0, [[40, 0, 97, 33], [1, 70]]),
     ("mha-one-head-d128", 1, 1, 128, 10000.0, [[65, 31], [130]]),
@@ -1686,6 +1710,46 @@ def test_one_query_head_per_kv_head_beyond_32_bit_row_offsets(ba):
     torch.cuda.synchronize()
     assert np.array_equal(host_bits(o.contiguous()), host_bits(want))
     assert torch.equal(lse, want_lse)
+
+
+@pytest.mark.parametrize("hq,hkv,wide", [(2, 2, "d_out"), (2, 2, "dq"), (4, 2, "d_out"), (4, 2, "o"), (6, 2, "dq"), (6, 2, "o")])
+def test_gradients_of_small_groups_beyond_32_bit_row_offsets(ba, hq, hkv, wide):
+    """The backward call of the same: one to three query heads per KV head and one of d_out, o and dq at a token
+    stride of 2^20 elements go through padded copies (workspace full of NaN: nothing may be read that
+    the call has not written).  A row's dq is the same bits as with packed tensors; dk and dv add up rows in
+    other tiles and are held against the oracle, as the packed call's are above."""
+    torch = torch_mod()
+    d, base = 64, 10000.0
+    offs, cu_blk = np.array([0, 1030, 1040], dtype=np.int32), np.array([0, 2], dtype=np.int32)
+    T = int(offs[-1])
+    qb, kb, vb = gen_qkv(1100 + hq, T, hq, hkv, d)
+    dob = wl.normal_bf16_bits(1120 + hq, (T, hq, d))
+    heads = ba.Heads(hq, hkv, d, base)
+    o, _, lse = gpu_prompts(ba, heads, qb, kb, vb, cu_blk, offs, want_k_rot=False)
+    q, k, v, do = dev_bf16(qb), dev_bf16(kb), dev_bf16(vb), dev_bf16(dob)
+
+    def spread(t):
+        big = torch.full(((T - 1) * (1 << 20) + hq * d,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        view = big.as_strided((T, hq, d), (1 << 20, d, 1))
+        view.copy_(t)
+        return view
+
+    def backward(o, do, dq):
+        dk, dv = torch.full_like(k, float("nan")), torch.full_like(v, float("nan"))
+        ws = torch.full((ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs),), 255, dtype=torch.uint8, device="cuda")
+        ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs, ws)
+        torch.cuda.synchronize()
+        return dq, dk, dv
+
+    nan = torch.full_like(q, float("nan"))
+    want, _, _ = backward(o, do, nan.clone())
+    dq, dk, dv = backward(spread(o) if wide == "o" else o, spread(do) if wide == "d_out" else do, spread(nan) if wide == "dq" else nan.clone())
+    assert torch.equal(dq.contiguous(), want)
+    f = oracle.bf16_bits_to_f64
+    (rq, rk, rv), (aq, ak, av) = oracle_grads(f(qb), f(kb), f(vb), f(dob), offs, oracle.theta(base, d))
+    assert_grad_close(host_f64(dq.contiguous()), rq, aq, "dq")
+    assert_grad_close(host_f64(dk), rk, ak, "dk")
+    assert_grad_close(host_f64(dv), rv, av, "dv")
 
 
 @pytest.mark.parametrize("hq,hkv,d,ctx,nq", [(4, 1, 128, 14000, 3), (2, 2, 64, 17000, 40), (8, 1, 64, 24000, 1)])

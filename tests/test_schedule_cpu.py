@@ -192,8 +192,8 @@ def test_whole_prompt_items_cover_the_mask_of_section_2_4_exactly(hq, hkv):
 
 
 def test_split_range_arithmetic_partitions_every_walk():
-    """split_tile_range through the final-block query: over every split count the planner can
-    choose (1 .. 32, by varying the compute-unit count), the splits of a row tile partition its walk."""
+    """split_tile_range through the final-block query: over split counts of 1 to 32 (eight KV heads, by varying the
+    compute-unit count; more splits: below), the splits of a row tile partition its walk."""
     h = ba.Heads(8, 8, 64, 10000.0)
     seen_splits = set()
     for n_cu in (1, 2, 3, 5, 8, 13, 16, 24, 32, 64, 100, 256, 1000):
@@ -252,6 +252,34 @@ def test_splits_of_very_long_contexts_stay_within_the_static_scratch():
             for tc in (8000, 31950, 128000, 1600000):
                 h = ba.Heads(g * hkv, hkv, 128, 500000.0)
                 assert ba.ba_final_block_attention_workspace_bytes(h, [0, lq], [0, tc]) <= static, (base, g, hkv, tc)
+
+
+@pytest.mark.parametrize("hkv,d", [(1, 64), (2, 64), (4, 64), (1, 128), (2, 128), (4, 128)])
+def test_walks_cut_into_more_than_32_splits_are_partitioned(hkv, d):
+    """33 to 64 splits (few KV heads, contexts of 8,000 to 60,000 tokens): contiguous, in order, nothing skipped, four
+    key tiles or more on average; with XCD speeds the same equal splits, the speeds' shares hold 32 at most."""
+    speeds = [1.03, 0.97, 1.02, 0.97, 1.03, 1.0, 1.02, 0.95]
+    seen = set()
+    for tc in (8000, 8191, 12345, 16000, 31950, 47777, 60000):
+        for lq in (1, 50, 64):
+            plain, sized = (ba.ba_schedule_final_block(ba.Heads(hkv, hkv, d, 10000.0, xcd_speed=s), [0, lq], [0, tc], 256)
+                            for s in (None, speeds))
+            n = plain[0].n_splits
+            seen.add(n)
+            if n > 32:
+                assert [(w.split, w.ctx_begin, w.ctx_end, w.self_begin, w.self_end) for w in plain] == \
+                    [(w.split, w.ctx_begin, w.ctx_end, w.self_begin, w.self_end) for w in sized]
+            assert n * 4 <= -(-tc // 64) + 1
+            at_ctx = at_self = 0
+            for w in sorted(plain, key=lambda w: w.split):  # (one row tile: 64 rows at most)
+                if w.ctx_end > w.ctx_begin:
+                    assert w.ctx_begin == at_ctx
+                    at_ctx = w.ctx_end
+                if w.self_end > w.self_begin:
+                    assert w.self_begin == at_self and at_ctx == tc
+                    at_self = w.self_end
+            assert at_ctx == tc and at_self == lq
+    assert max(seen) > 32, seen
 
 
 @pytest.mark.parametrize("speeds", [[1.0] * 8, [0.92, 1.0, 1.08, 1.0, 0.95, 1.05, 1.0, 1.0], [0.5, 2.0, 0.5, 2.0, 1.0, 1.0, 1.0, 1.0]])
