@@ -1,7 +1,6 @@
 // C boundary, whole prompts under the Block-attention mask (Section 2.4): forward and backward entry
 // points, and the route through zero-padded phantom heads for groups of fewer than four query heads.
 #include <limits.h>
-#include <math.h>
 #include <string.h>
 
 #include <algorithm>
@@ -354,7 +353,6 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   bp.dv = (uint16_t *)dv_out->ptr;
   bp.dv_st = dv_out->stride_tok;
   bp.dv_sh = dv_out->stride_head;
-  bp.scale = heads->softmax_scale > 0.f ? heads->softmax_scale : 1.0f / sqrtf((float)D);
   hipError_t e;
 
   ba::AttnParams ap;

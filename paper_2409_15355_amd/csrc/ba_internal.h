@@ -223,7 +223,6 @@ struct BwdParams {
   int64_t T;
   uint16_t *dq, *dk, *dv;  // the gradients, with these strides
   int64_t dq_st, dq_sh, dk_st, dk_sh, dv_st, dv_sh;
-  float scale;           // softmax scale
 };
 
 // Owners of keys: blocks in any order, and for a passage the last block of its prompt (whose rows

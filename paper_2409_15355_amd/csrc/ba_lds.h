@@ -71,8 +71,6 @@ __device__ __forceinline__ void lds_dma16(const char *base, uint32_t offset, uin
                : "v"(offset), "s"(base), "s"(lds_base)
                : "memory");
 }
-// Wait until at most NEWER of this wave's vector-memory operations are still in flight
-// (they complete in order), leaving the other counters alone.  gfx9 encoding of s_waitcnt.
 // Workgroup barrier without the memory fence of __syncthreads(): LDS reads that are still in flight
 // (fragments requested ahead of their use) need not drain first.  What a barrier publishes here are
 // LDS-direct copies, and the copying wave has waited for those (dma_wait) before it arrives.
@@ -141,6 +139,8 @@ __device__ __forceinline__ float sum_over_lanes(float x) {
   return x;
 }
 
+// Wait until at most NEWER of this wave's vector-memory operations are still in flight
+// (they complete in order), leaving the other counters alone.  gfx9 encoding of s_waitcnt.
 template <int NEWER>
 __device__ __forceinline__ void dma_wait() {
   static_assert(NEWER >= 0 && NEWER < 64, "vmcnt is a 6-bit counter");
