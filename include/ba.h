@@ -81,7 +81,8 @@ typedef struct ba_heads {
                              MI355X sustain clocks several per cent apart, and a launch ends with
                              its slowest workgroup).  Changes which
                              keys a split covers, hence low-order bits of the result, never the
-                             workspace size.  null = equal splits.                             */
+                             workspace size.  Calls cut into more than 32 splits (long contexts
+                             over few KV heads) keep equal ones.  null = equal splits.         */
 } ba_heads;
 
 /* Library version (major * 10000 + minor * 100 + patch). */
@@ -165,7 +166,9 @@ int32_t ba_profile_end(double *ms_sum, int32_t *launches);
  *   o[t, h] = softmax_s(scale * <q^[t,h], k^[s,kv(h)]>) v[s, kv(h)],  s in [c[b], t].
  * q [T, n_q_heads, D], k, v [T, n_kv_heads, D], o [T, n_q_heads, D], all bf16.
  * block_offsets: host, n_blocks+1 ints, c[0] = 0 <= c[1] <= ... <= c[n_blocks] = T.
- * Blocks are independent, so a batch of prompts is simply a longer block list.
+ * Blocks are independent, so a batch of prompts is simply a longer block list: a block's outputs are the
+ * same bits whatever other blocks the call holds (with fewer than four query heads per KV head as long as
+ * no row's scores rise by 35 or more in log2 units behind its first 64 keys).
  * rope_mode BA_ROPE_APPLY rotates q and k at LOCAL positions (t - c[b]); then the
  * rotated keys -- the cacheable K of Section 2.3 -- are written to k_local_out
  * [T, n_kv_heads, D] if it is non-null, else kept in the workspace.  With

@@ -149,7 +149,7 @@ __device__ __forceinline__ void rotate_back(f32x16_t (&acc)[D / 32], const f32x4
 }
 
 // ---------------------------------------------------------------------------------------------------
-// dq.  Bound by memory: q, dO and O in, q^ and dq out are 1.36 GB at 33,130 tokens of 32 heads of 128 (250 us
+// dq.  Bound by memory: q, dO and O in, q^ and dq out are 1.38 GB at 33,746 tokens of 32 heads of 128 (256 us
 // at the 5.4 TB/s such a mix reaches here), and 1.88 GB move with the keys and values (re-read by a block's
 // row tiles where L2 has let go of them).  350 us on rows that a pre-pass of 125 us had rotated; 386 rotating
 // them itself; 357 with the rows that pass once marked non-temporal (kPast, in calls larger than the cache).  287
@@ -482,9 +482,9 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
 //   wave A: S = q^ K^^T, P = 2^S -> LDS, dV^T += dO^T P        wave B: dP = dO V^T, dS = P o dP, dK^^T += q^^T dS
 // P passes between them in 32 bits, lane for lane (both hold the pair's tile in one layout); the two have
 // eight products before and eight behind the exchange, and fit three waves to a SIMD.
-// Eight prompts of 20 passages of 100 to 300 tokens (33,130 tokens, 32 query heads over 8 of 128, 174 GFLOP
-// of visible pairs): 470 us as one wave per 32 keys with the mask tests among the exponentials, 370 with
-// straight code per tile, 318 to 340 as it is; 990 MB read (q^ and dO once are 542), 138 written.  What is
+// Eight prompts of 20 passages of 100 to 300 tokens and a query block (33,746 tokens, 32 query heads over 8 of
+// 128, 208 GFLOP in four products): 470 us as one wave per 32 keys with the mask tests among the exponentials,
+// 370 with straight code per tile, 315 to 345 as it is; 990 MB read (q^ and dO once are 553), 138 written.  What is
 // left is waiting, for the exchange and between the barriers: without the tile copies 287, without the
 // exponentials 331; a third buffer does not fit three workgroups, and asking for lines two tiles ahead cost 14.
 template <int D>
@@ -535,8 +535,8 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   // ---- query row tiles that see these keys: every row of the prompt's last block, then the block's own
   //      rows, both from the end to the front, down to the first key's token.  The workgroups of a block
   //      start together and so meet each tile at about the same time, in one XCD's L2; walked from the
-  //      front, each starts at a row of its own and fetches its tiles alone (1692 MB per launch at 33,130
-  //      tokens where q^ and dO are 542) ---------------------------------------------------------------
+  //      front, each starts at a row of its own and fetches its tiles alone (1692 MB per launch at 33,746
+  //      tokens where q^ and dO are 553) ---------------------------------------------------------------
   const int n_rows_a = lk * Gq, n_rows_f = lf * Gq;
   const int n_f = (n_rows_f + kKvRows - 1) / kKvRows;
   const int n_t = n_f + (n_rows_a + kKvRows - 1) / kKvRows - (k0 * Gq) / kKvRows;

@@ -68,10 +68,10 @@ int32_t check_prompt_blocks(int32_t n_prompts, const int32_t *cu_blk, const int3
 // and split at D = 128): up to 64 splits, the merge priced by its rows.  32 splits at most / up to 64, us: 50
 // queries, 31,950 tokens: 4 over 4 heads of 64: 24.3 / 21.0, 8 over 2 of 64: 28.9 / 23.5, 4 over 1 of 128: 30.5 / 24.9;
 // 64,000: 6 over 6 of 64: 35.7 / 31.7, 7 over 7: 36.1 / 34.6, 16 over 4 of 128: 49.2 / 43.8.  At D = 128 five workgroups
-// gain only where the merge at its full price leaves a gain (20 over 5, 60 queries: 24,000 tokens 30.1 with 32, 30.9 with 51; 64,000
-// 52.4 / 50.2), six and seven hardly ever (28 over 7, one query: 16,000 24.9 / 25.6, 64,000 48.1 / 49.1).
-// From eight on, 32 splits fill the chip: more would only grow the partials, beyond the static scratch for
-// contexts of 400,000 tokens and more, and leave the shares by XCD speed (kMaxCutSplits).
+// gain only where the merge at its full price leaves a gain (20 over 5, 60 queries: 24,000 tokens 30.1 with 32,
+// 30.9 with 51; 64,000: 52.4 / 50.2), six and seven hardly ever (28 over 7, one query: 16,000: 24.9 / 25.6, 64,000:
+// 48.1 / 49.1).  From eight on, 32 splits fill the chip: more would only grow the partials, beyond the static
+// scratch for contexts of 400,000 tokens and more, and leave the shares by XCD speed (kMaxCutSplits).
 int choose_splits(int64_t base_wgs, int max_tiles, int n_cu, int head_dim) {
   if (base_wgs <= 0) return 1;
   if (n_cu < 1) n_cu = 1;
