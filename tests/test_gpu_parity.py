@@ -499,7 +499,8 @@ def test_late_keys_far_above_first_tile_move_the_reference(ba, where):
     the first tile has to move when the second arrives, and across KV splits the partials carry
     very different references.  The keys that matter have ordinary scores, so the usual
     tolerance applies."""
-    # (two query heads per KV head take the main schedule in per-block encoding, four the short-block one)
+    # (in per-block encoding two query heads per KV head take the main schedule here, with a block of 600 tokens and
+    # little work, four the short-block one)
     hq, hkv, d = (4, 2, 64) if where in ("final", "encode") else (8, 2, 64)
     th = oracle.theta(10000.0, d)
     f = oracle.bf16_bits_to_f64
