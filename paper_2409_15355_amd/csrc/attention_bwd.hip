@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   const int rowtile = (int)(id - (uint32_t)kvh * n_rowtiles);
   const int b = find_block(meta.tile_start, rowtile);
   const int q_tok0 = meta.start[b], lq = meta.len[b], k_tok0 = meta.kstart[b];
-  const int jt = rowtile - meta.tile_start[b];
+  int jt = rowtile - meta.tile_start[b];
   const int dq = q_tok0 - k_tok0;  // the block's first token, counted in keys
   const int lk = dq + lq;          // keys up to the block's end
 
@@ -182,9 +182,19 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   const int col = lane & 31, hf = lane >> 5;
   const int Gq = p.group;
   const int n_rows = lq * Gq;
+  // a block whose walk is shared (see the forward kernel): which split, of how many
+  int split = 0, n_splits = 1, n_rt = 0;
+  if (b < meta.n_split) {
+    n_rt = (n_rows + kShortTileRows - 1) / kShortTileRows;
+    n_splits = walk_splits((lk - 1) / kBKeys + 1, meta.chunk);
+    split = jt / n_rt;
+    jt -= split * n_rt;
+  }
   const int row0 = jt * kShortTileRows;
   const int last_row = min(n_rows, row0 + kShortTileRows) - 1;
-  const int n_t = (dq + (int)fast_div((uint32_t)last_row, p.group_div)) / kBKeys + 1;
+  TileRange walk = {0, (dq + (int)fast_div((uint32_t)last_row, p.group_div)) / kBKeys + 1};
+  if (n_splits > 1) walk = walk_split_range(walk.end, n_splits, split);
+  const int t0 = walk.begin, n_t = walk.end;
   const int wave_row0 = row0 + wave * 32;
   const int wave_last_row = min(n_rows, wave_row0 + 32) - 1;
   const int wave_n_t =
@@ -289,8 +299,8 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
       lds_dma16(tbase, tok * TROW + (uint32_t)((pc ^ (t & 7)) << 4), (uint32_t)(uintptr_t)smem + s_ofs + u * 1024);
     }
   }
-  issue_copy(0, 0);
-  if (1 < n_t) issue_copy(1, 1);
+  if (t0 < n_t) issue_copy(t0, 0);
+  if (t0 + 1 < n_t) issue_copy(t0 + 1, 1);
   __builtin_amdgcn_sched_barrier(0);
   dma_wait<0>();
 
@@ -347,7 +357,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     const int r_in_wave = min(col, max(wave_last_row - wave_row0, 0));  // (lanes beyond the block's rows: its last row)
     my_ld.y = *reinterpret_cast<const __attribute__((address_space(3))) float *>(smem + s_ofs + r_in_wave * 4);
     my_ld.x = my_lse * kLog2e;
-    if (wave_row0 + col < n_rows) {
+    if (split == 0 && wave_row0 + col < n_rows) {
       const int r = wave_row0 + col;
       float *dst = bp.ld + 2 * (((int64_t)kvh * bp.T + q_tok0) * bp.ld_group) + (r >> 2) * 8 + (r & 3);
       dst[hf * 4] = hf ? -my_ld.y : -my_ld.x;  // the two halves of the wave hold the same rows
@@ -360,7 +370,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     rows_to_frags(ld_q, raw);
     rotate_fragments<G::KCH>(raw, cs, p.rope_layout != 0);
     uint16_t *dst = bp.q_rot + ((int64_t)(q_tok0 + my_tok) * p.n_q_heads + kvh * Gq + (my_row - my_tok * Gq)) * D + hf * 8;
-    const bool mine = wave_row0 + col < n_rows;
+    const bool mine = split == 0 && wave_row0 + col < n_rows;
 #pragma unroll
     for (int kk = 0; kk < G::KCH; ++kk) {
       if (mine) *reinterpret_cast<u32x4_t *>(dst + kk * 16) = raw[kk];
@@ -383,9 +393,9 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   // ---- the walk over the key tiles ---------------------------------------------------------------
   int buf = 0;
 #pragma unroll 1
-  for (int i = 0; i < n_t; ++i) {
-    // (tiles 0 and 1 have landed; waiting here would be for the stores of q^)
-    if (i >= 2) {
+  for (int i = t0; i < n_t; ++i) {
+    // (the first two tiles have landed; waiting here would be for the stores of q^)
+    if (i >= t0 + 2) {
       if (i + 1 < n_t) dma_wait<kOpsPerTile>(); else dma_wait<0>();
     }
     wg_barrier();
@@ -445,6 +455,33 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   int ln = lane;
   asm volatile("" : "+v"(ln));
   const int ecol = ln & 31, ehf = ln >> 5;
+  if (n_splits > 1) {
+    // (a shared walk: the accumulators of all splits add up in their order)
+    const int64_t slot = ((int64_t)(rowtile - split * n_rt) * p.n_kv_heads + kvh) * kSplitWaves + wave;  // of split 0
+    const int64_t step = (int64_t)n_rt * p.n_kv_heads * kSplitWaves;                                     // to the next
+    float *const part_o = (float *)p.part_o;
+    const bool live = wave_row0 < n_rows;
+    if (live) leave_accumulators<D>(part_o, slot + split * step, ln, acc);
+    static_assert(kBWaves * G::TILEB + 16 <= 2 * kBBuf * G::TILEB, "a word behind the output staging");
+    if (!last_of_splits(p.part_idx + (int64_t)(rowtile - split * n_rt) * p.n_kv_heads + kvh, n_splits,
+                        smem + 2 * kBBuf * G::TILEB - 16))
+      return;
+    if (live) {
+#pragma unroll
+      for (int dt = 0; dt < G::DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
+#pragma unroll 1
+      for (int s = 0; s < n_splits; ++s) {
+        u32x4_t w[D / 8];
+        fetch_accumulators<D>(part_o, slot + s * step, ln, w);
+#pragma unroll
+        for (int k = 0; k < D / 8; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) *((float *)&acc[k >> 2] + (k & 3) * 4 + e) += __uint_as_float(w[k][e]);
+      }
+    }
+  }
   rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(q_tok0 + my_tok) * D), ehf,
                  p.rope_layout != 0, kLn2);
   lds_char *stage = smem + wave * G::TILEB;
@@ -452,7 +489,6 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
-      typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
       u32x2_t w;
       w[0] = pack_bf16(acc[dt][q4 * 4 + 0], acc[dt][q4 * 4 + 1]);
       w[1] = pack_bf16(acc[dt][q4 * 4 + 2], acc[dt][q4 * 4 + 3]);
@@ -743,7 +779,6 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
-      typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
       u32x2_t w;
       w[0] = pack_bf16(acc[dt][q4 * 4 + 0], acc[dt][q4 * 4 + 1]);
       w[1] = pack_bf16(acc[dt][q4 * 4 + 2], acc[dt][q4 * 4 + 3]);

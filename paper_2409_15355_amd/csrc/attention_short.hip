@@ -51,9 +51,15 @@ struct SGeo {
   static constexpr int IPW = kSKeys / RPI / kSWaves;  // such instructions per wave, tile and kind
   static constexpr size_t LDS = (size_t)2 * kSBuf * TILEB;
   static_assert(IPW >= 1, "every wave takes part in a tile copy");
-  static_assert((size_t)kSWaves * 32 * ROWB <= LDS, "the output staging must fit the tile buffers");
+  static_assert((size_t)kSWaves * 32 * ROWB + 16 <= LDS, "the output staging must fit the tile buffers, and a word behind it");
 };
 
+
+// (a table without shared walks has none)
+__device__ __forceinline__ int shared_blocks(const EncodeMeta &) { return 0; }
+__device__ __forceinline__ int shared_blocks(const PromptMeta &m) { return m.n_split; }
+__device__ __forceinline__ int shared_chunk(const EncodeMeta &) { return 1; }
+__device__ __forceinline__ int shared_chunk(const PromptMeta &m) { return m.chunk; }
 
 // Meta = EncodeMeta: a block sees its own tokens only (Section 2.1).  Meta = PromptMeta: a block's keys
 // start wherever the table says -- at the block itself for a passage, at the first token of the
@@ -97,7 +103,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   }
   const int dq = q_tok0 - k_tok0;  // the block's first token, counted in keys
   const int lk = dq + lq;          // keys up to the block's end
-  const int jt = rowtile - meta.tile_start[b];
+  int jt = rowtile - meta.tile_start[b];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -105,11 +111,21 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   const int hf = lane >> 5;   // which half of the wave
   const int Gq = p.group;
   const int n_rows = lq * Gq;
+  // a block whose walk is shared: which split, of how many
+  int split = 0, n_splits = 1, n_rt = 0;
+  if (kPrompt && b < shared_blocks(meta)) {
+    n_rt = (n_rows + kShortTileRows - 1) / kShortTileRows;
+    n_splits = walk_splits((lk - 1) / kSKeys + 1, shared_chunk(meta));
+    split = jt / n_rt;
+    jt -= split * n_rt;
+  }
   const int row0 = jt * kShortTileRows;
 
   // key tiles of the workgroup (up to its last row's token) and of this wave
   const int last_row = min(n_rows, row0 + kShortTileRows) - 1;
-  const int n_t = (dq + (int)fast_div((uint32_t)last_row, p.group_div)) / kSKeys + 1;
+  TileRange walk = {0, (dq + (int)fast_div((uint32_t)last_row, p.group_div)) / kSKeys + 1};
+  if (kPrompt && n_splits > 1) walk = walk_split_range(walk.end, n_splits, split);
+  const int t0 = kPrompt ? walk.begin : 0, n_t = walk.end;
   const int wave_row0 = row0 + wave * 32;
   const int wave_last_row = min(n_rows, wave_row0 + 32) - 1;
   const int wave_n_t =
@@ -234,8 +250,8 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     }
   };
   constexpr int kOpsPerTile = 2 * G::IPW;  // vector-memory operations of one wave per tile
-  issue_copy(0, 0);  // (buffer 2 holds the waves' slices until the first barrier)
-  if (1 < n_t) issue_copy(1, 1);
+  if (!kPrompt || t0 < n_t) issue_copy(t0, 0);  // (buffer 2 holds the waves' slices until the first barrier)
+  if (t0 + 1 < n_t) issue_copy(t0 + 1, 1);
   __builtin_amdgcn_sched_barrier(0);  // the copies go out before anything waits for the Q rows
 
   // ---- rotate (or just scale) the Q rows into the fragments ---------------------------------------
@@ -372,7 +388,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   //      overwrite that buffer ------------------------------------------------------------------------
   int buf = 0;
 #pragma unroll 1
-  for (int i = 0; i < n_t; ++i) {
+  for (int i = t0; i < n_t; ++i) {
     if (i + 1 < n_t) dma_wait<kOpsPerTile>(); else dma_wait<0>();  // tile i + 1 may still be on its way
     wg_barrier();
     if (i + 2 < n_t) issue_copy(i + 2, buf == 0 ? 2 : buf - 1);
@@ -381,13 +397,13 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
       // S'^T = K Q'^T - reference: the accumulator starts at minus the row's reference, so the MFMA
       // result is directly the base-2 exponent (as the main core: from the second tile of 64 keys on)
       f32x16_t sacc = scores(i, kofs, kAsCore && i < 2 ? 0.f : -mb);
-      if (i == 0) {
+      if (i == t0) {
         // the first tile sets the reference: its row maximum whatever the sign (nothing visible:
         // stay at 0), so a row's largest exponential so far is exactly 1
         const float mx = kAsCore ? fmaxf(mb, row_max(sacc)) : row_max(sacc);
         mb = mx == -INFINITY ? 0.f : mx;
       }
-      if (i < (kAsCore ? 2 : 1)) {
+      if (i < (kAsCore ? 2 : t0 + 1)) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) sacc[v] -= mb;
       }
@@ -440,7 +456,54 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   asm volatile("" : "+v"(ln));
   const int ecol = ln & 31, ehf = ln >> 5;
   lds_char *stage = smem + wave * (32 * G::ROWB);
-  const float l_tot = l_run + other_half(l_run);
+  float l_tot = l_run + other_half(l_run);
+  if (kPrompt && n_splits > 1) {
+    // The walk of this row tile is shared: a last block walks its whole prompt, 0.58 us a tile, and a call of a few
+    // prompts ends with that chain.  One block of 19 tokens behind 5,000: 157 tiles, 92 us of a launch whose
+    // passages take 35.  Leave (accumulators, reference, sum); the last workgroup to do so merges: rows of
+    // reference m_i and sum l_i come to sum_i 2^(m_i - m) o_i over sum_i 2^(m_i - m) l_i, m = max m_i.
+    const int64_t slot = ((int64_t)(rowtile - split * n_rt) * p.n_kv_heads + kvh) * kSplitWaves + wave;  // of split 0
+    const int64_t step = (int64_t)n_rt * p.n_kv_heads * kSplitWaves;                                     // to the next
+    float *const part_o = (float *)p.part_o;
+    char *const part_ml = (char *)p.part_ml;
+    const bool live = wave_row0 < n_rows;
+    if (live) {
+      leave_accumulators<D>(part_o, slot + split * step, ln, oacc);
+      if (ehf == 0) {
+        const u32x2_t ml = {__float_as_uint(l_tot > 0.f ? mb : -INFINITY), __float_as_uint(l_tot)};
+        __builtin_amdgcn_raw_buffer_store_b64(ml, shared_buffer(part_ml + (slot + split * step) * 256, 256), ecol * 8, 0, kAgentScope);
+      }
+    }
+    if (!last_of_splits(p.part_idx + (int64_t)(rowtile - split * n_rt) * p.n_kv_heads + kvh, n_splits, smem + G::LDS - 16)) return;
+    if (live) {
+      mb = -INFINITY;
+      l_tot = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < G::DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[dt][v] = 0.f;
+#pragma unroll 1
+      for (int s = 0; s < n_splits; ++s) {
+        u32x4_t w[D / 8];
+        const u32x2_t ml = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(
+            shared_buffer(part_ml + (slot + s * step) * 256, 256), ecol * 8, 0, kAgentScope));
+        fetch_accumulators<D>(part_o, slot + s * step, ln, w);
+        const float ms = __uint_as_float(ml[0]);
+        const float to = fmaxf(mb, ms);
+        const float keep = mb == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mb - to);
+        const float add = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - to);
+        mb = to;
+        l_tot = l_tot * keep + __uint_as_float(ml[1]) * add;
+#pragma unroll
+        for (int k = 0; k < D / 8; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float &o = *((float *)&oacc[k >> 2] + (k & 3) * 4 + e);
+            o = o * keep + __uint_as_float(w[k][e]) * add;
+          }
+      }
+    }
+  }
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
 #pragma unroll
   for (int dt = 0; dt < G::DT; ++dt)
@@ -449,7 +512,6 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
       // dims dt * 32 + q4 * 8 + hf * 4 + (0..3) of query row `col`
       const int col = ecol, hf = ehf;
       const int chunk = dt * 4 + q4;
-      typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
       u32x2_t w;
       w[0] = pack_bf16(oacc[dt][q4 * 4 + 0] * inv, oacc[dt][q4 * 4 + 1] * inv);
       w[1] = pack_bf16(oacc[dt][q4 * 4 + 2] * inv, oacc[dt][q4 * 4 + 3] * inv);

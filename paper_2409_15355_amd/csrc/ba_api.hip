@@ -164,7 +164,8 @@ int32_t run_reencode(ba::ReencParams p, const ba::RopeTable &rt, int n_blocks, c
 int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_tensor *q, uint16_t *q_rot,
                          const ba_tensor *k, const ba_tensor *k_rot, int n, const int32_t *start,
                          const int32_t *pos0, hipStream_t stream, const ba::RopeRots *rots,
-                         const ba::RopeRotsSmall *rots_small, float *rot_dst, int n_rot, float *q_table, int table_rows) {
+                         const ba::RopeRotsSmall *rots_small, float *rot_dst, int n_rot, float *q_table, int table_rows,
+                         int32_t *zero, int n_zero) {
   const int64_t tokens = (int64_t)start[n] - start[0];
   if (tokens <= 0) return BA_OK;
   ba::RopePrepassParams p;
@@ -200,6 +201,8 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
   p.do_k = 1;
   p.rot_dst = rot_dst;
   p.n_rot = n_rot;
+  p.zero = zero;
+  p.n_zero = n_zero;
   auto fill_and_launch = [&](auto &segs) {
     memset(&segs, 0, sizeof(segs));
     segs.n = n;

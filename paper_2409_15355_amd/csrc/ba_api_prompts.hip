@@ -63,6 +63,22 @@ int32_t move_heads(const ba_heads *h, const ba_tensor *real, void *padded, int64
   return BA_OK;
 }
 
+// Memory of the shared walks (plan_walk_shares); for the padded route what its groups of four want, if that is more.
+size_t shares_bytes(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
+  size_t bytes = ba::plan_walk_shares(h, n_prompts, cu_blk, block_offsets).total();
+  if (h->n_q_heads / h->n_kv_heads < kPadGroup) {
+    const ba_heads h4 = padded_heads(h);
+    bytes = std::max(bytes, ba::plan_walk_shares(&h4, n_prompts, cu_blk, block_offsets).total());
+  }
+  return bytes;
+}
+// Where a launch's shared walks leave their partial results, from wsp on.
+void place_shares(const ba::WalkShares &shares, char *wsp, ba::AttnParams *ap) {
+  ap->part_o = (uint16_t *)wsp;
+  ap->part_ml = (float *)(wsp + align256(shares.part_bytes));
+  ap->part_idx = (int32_t *)(wsp + align256(shares.part_bytes) + align256(shares.ml_bytes));
+}
+
 // rows of (log-sum-exp, delta) per token and KV head in the backward pass's workspace
 int32_t ld_group(int32_t group) { return (group + 3) & ~3; }
 
@@ -80,7 +96,8 @@ size_t ba_block_attention_prompts_workspace_bytes(const ba_heads *heads, int32_t
     pad_bytes = 2 * padded_rows_bytes(heads, T) + padded_lse_bytes(heads, T);
   if (rope_mode != BA_ROPE_APPLY) return pad_bytes;
   const size_t k_bytes = have_k_rot_out ? 0 : align256(T * heads->n_kv_heads * heads->head_dim * 2);
-  return pad_bytes + k_bytes + align256(T * heads->head_dim * 4);  // rotated K; scale * (cos, sin) per token and pair
+  // rotated K; scale * (cos, sin) per token and pair; partial results of shared walks
+  return pad_bytes + k_bytes + align256(T * heads->head_dim * 4) + shares_bytes(heads, n_prompts, cu_blk, block_offsets);
 }
 
 int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k, const ba_tensor *v,
@@ -146,6 +163,9 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
   build_rope_table(heads, &rt);
   ba_tensor k_use = *k;
   float *q_table = nullptr;
+  ba::WalkShares shares;  // (without rotation the call needs no workspace: no walk is shared)
+  ba::AttnParams ap;
+  memset(&ap, 0, sizeof(ap));
   if (rope_mode == BA_ROPE_APPLY) {
     if (!ws || ws_bytes < need || ((uintptr_t)ws & 255))
       return fail(BA_ERR_WORKSPACE, "whole prompts: 256-byte aligned workspace of %zu bytes needed, %zu given", need,
@@ -161,19 +181,20 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
       wsp += align256((size_t)T * heads->n_kv_heads * D * 2);
     }
     q_table = (float *)wsp;
+    wsp += align256((size_t)T * D * 4);
+    shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
+    place_shares(shares, wsp, &ap);
     // positions count from each prompt's first token: one segment per prompt
     std::vector<int32_t> starts(n_prompts + 1);
     for (int n = 0; n <= n_prompts; ++n) starts[n] = block_offsets[cu_blk[n]];
     for (int n0 = 0; n0 < n_prompts; n0 += ba::kRopeMaxSegs) {
       const int n = std::min(ba::kRopeMaxSegs, n_prompts - n0);
       if ((rc = run_rope_prepass(heads, rt, q, nullptr, k, &k_use, n, starts.data() + n0, nullptr, stream, nullptr,
-                                 nullptr, nullptr, 0, q_table)))
+                                 nullptr, nullptr, 0, q_table, 0, ap.part_idx, (int)(shares.count_bytes / 4))))
         return rc;
     }
   }
 
-  ba::AttnParams ap;
-  memset(&ap, 0, sizeof(ap));
   ap.q = (const uint16_t *)q->ptr;
   ap.q_st = q->stride_tok;
   ap.q_sh = q->stride_head;
@@ -207,13 +228,13 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
 
   // Blocks go to the kernel longest key range first (see the planner).
   std::vector<ba::PromptBlock> blks = ba::list_prompt_blocks(n_prompts, cu_blk, block_offsets);
-  ba::sort_by_key_range(&blks);
+  ba::sort_by_key_range(&blks, shares);
   const int n_live = (int)blks.size();
 
   for (int b0 = 0; b0 < n_live; b0 += ba::kEncMaxBlocks) {
     const int n = std::min(ba::kEncMaxBlocks, n_live - b0);
     ba::PromptMeta meta;
-    const int64_t tiles = ba::build_prompt_meta(blks, (size_t)b0, n, G, &meta);
+    const int64_t tiles = ba::build_prompt_meta(blks, (size_t)b0, n, G, shares, &meta);
     if (tiles < 0) return fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
     if (tiles == 0) continue;
     ap.total_tiles = (int32_t)tiles;
@@ -240,8 +261,9 @@ size_t ba_block_attention_prompts_backward_workspace_bytes(const ba_heads *heads
     hq = hkv * kPadGroup;
   }
   // rotated scaled q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row
+  // ... and the partial results of shared walks
   return pad_bytes + align256(T * hq * D * 2) + align256(T * hkv * D * 2) + align256(T * D * 4) +
-         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8 + 16);
+         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8 + 16) + shares_bytes(heads, n_prompts, cu_blk, block_offsets);
 }
 
 int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k,
@@ -318,6 +340,11 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   float *q_table = (float *)wsp;
   wsp += align256((size_t)T * D * 4);
   float *ld = (float *)wsp;
+  wsp += align256((size_t)T * hkv * ld_group(G) * 8 + 16);
+  const ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
+  ba::AttnParams ap;
+  memset(&ap, 0, sizeof(ap));
+  place_shares(shares, wsp, &ap);
 
   ba::RopeTable rt;
   build_rope_table(heads, &rt);
@@ -327,7 +354,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   for (int n0 = 0; n0 < n_prompts; n0 += ba::kRopeMaxSegs) {
     const int n = std::min(ba::kRopeMaxSegs, n_prompts - n0);
     if ((rc = run_rope_prepass(heads, rt, q, nullptr, k, &k_rot, n, starts.data() + n0, nullptr, stream, nullptr, nullptr,
-                               nullptr, 0, q_table)))
+                               nullptr, 0, q_table, 0, ap.part_idx, (int)(shares.count_bytes / 4))))
       return rc;
   }
 
@@ -355,8 +382,6 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   bp.dv_sh = dv_out->stride_head;
   hipError_t e;
 
-  ba::AttnParams ap;
-  memset(&ap, 0, sizeof(ap));
   ap.q = (const uint16_t *)q->ptr;
   ap.q_st = q->stride_tok;
   ap.q_sh = q->stride_head;
@@ -381,11 +406,11 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   typedef ba::PromptBlock Blk;
   // dq: query rows own the sums; longest key range first
   std::vector<Blk> by_q = blks;
-  ba::sort_by_key_range(&by_q);
+  ba::sort_by_key_range(&by_q, shares);
   for (size_t b0 = 0; b0 < by_q.size(); b0 += ba::kEncMaxBlocks) {
     const int n = (int)std::min<size_t>(ba::kEncMaxBlocks, by_q.size() - b0);
     ba::PromptMeta meta;
-    const int64_t tiles = ba::build_prompt_meta(by_q, b0, n, G, &meta);
+    const int64_t tiles = ba::build_prompt_meta(by_q, b0, n, G, shares, &meta);
     if (tiles < 0) return fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
     if (tiles == 0) continue;
     ap.total_tiles = (int32_t)tiles;

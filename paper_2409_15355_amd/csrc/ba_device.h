@@ -16,6 +16,7 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -38,6 +39,16 @@ template <bool kHint>
 __device__ __forceinline__ void store_row_piece(char *to, const u32x4_t &w) {
   u32x4_t *p = reinterpret_cast<u32x4_t *>(to);
   if (kHint) __builtin_nontemporal_store(w, p); else *p = w;
+}
+
+// Memory that workgroups of one launch hand to each other: accesses with the cache policy of agent-scope
+// atomics (sc1), which go past the L2 caches of the XCDs to where all of them meet.  No cache has to be written
+// back or invalidated for them, as fences of that scope would.
+// (Stores this wide keep the scalar offset at 0: with one in a register the compiler lets the next instruction
+// overwrite the data while it is still being read, and now and then the new value was stored.)
+constexpr int kAgentScope = 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t shared_buffer(char *base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
 }
 
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f) {

@@ -95,6 +95,8 @@ struct RopePrepassParams {
                      // do_q == 4: the table only, by position: row r = q_scale * (cos, sin) of position r,
                      //            r < table_rows (for calls all of whose segments start at position 0)
   int32_t table_rows;
+  int32_t *zero;     // n_zero words cleared on the way (counters of the attention launch behind this one)
+  int32_t n_zero;
 };
 
 // positions (in tokens) by which the rows of the rotation table turn
@@ -141,6 +143,17 @@ constexpr int kSmallGroupShortLen = 512;  // no block longer than this: small wo
 constexpr int kFixedTiles = 4;            // what a workgroup of the main core spends besides its walk, in key tiles
 constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 
+// Whole prompts: last blocks that walk more than kShareAbove key tiles have the walk shared by workgroups of
+// kShareChunk tiles or more: of load / (kShareCus * kShareLoad) where a launch is busy for longer than such a
+// walk anyway.  A shared walk pays for its partial results (some 2 us a split in the workgroup that merges).
+// Forward and backward, us, unshared / shared: 4 over 4 heads of 64, one prompt of 9 x 250-750 tokens: 164 / 73; 8 over 2
+// of 64, four of 18 x 135-400: 294 / 151; 32 over 8 of 128, two of 22 x 37-112: 155 / 121, two of 29 x 88-262: 458 /
+// 368, two of 3 x 134-402 (29 and 41 tiles): 129 / 128; eight of 20 x 100-300 (130 tiles, 85,000 walked in all): not
+// shared (955; 964 with chunks of 110).  Over 18 calls chunks of 12 to 28 tiles differ by less than 3 %.
+constexpr int kShareAbove = 36, kShareChunk = 16;
+constexpr int kShareCus = 256, kShareLoad = 2;
+constexpr size_t kShareMaxBytes = (size_t)256 << 20;
+
 struct AttnParams {
   const uint16_t *q;
   int64_t q_st, q_sh;
@@ -161,6 +174,8 @@ struct AttnParams {
   uint16_t *part_o;   // [n_splits][part_units][D / 16][64 lanes][8] fp16
   float *part_ml;     // [n_splits][part_units][32][2]  (reference in log2 units, sum of exponentials)
   int32_t *part_idx;  // [part_units][32]  output row (token * n_q_heads + head) of each packed row, -1: none
+  // (whole prompts, shared walks: part_o holds the accumulators in 32 bits, part_ml (reference, sum), per wave of
+  // (row tile of the launch, KV head); part_idx counts, per the same of a block's first split, who is done)
   int64_t part_units;
   int32_t tile_base;  // row tiles of the call's earlier launches
   int32_t n_q_heads, n_kv_heads, group, head_dim;
@@ -206,6 +221,9 @@ struct PromptMeta {
   int32_t len[kEncMaxBlocks];
   int32_t tile_start[kEncMaxBlocks + 1];  // in row tiles of kShortTileRows rows; INT_MAX beyond [n]
   int32_t kstart[kEncMaxBlocks];          // token offset of the first visible key
+  // The first n_split blocks' walks are shared out: a block whose last row walks w key tiles is taken by
+  // walk_splits(w, chunk) workgroups per row tile and KV head (all row tiles of split 0 first, then of split 1 ...)
+  int32_t n_split, chunk;
 };
 
 // ---------------------------------------------------------------- backward of whole prompts ----

@@ -148,4 +148,41 @@ __device__ __forceinline__ void dma_wait() {
   asm volatile("" ::: "memory");
 }
 
+// ---- row tiles whose walk several workgroups share (PromptMeta::n_split): each leaves its accumulators in
+//      32 bits, in the layout they have (1 KB of consecutive memory per wave instruction), and the one that
+//      is last to count itself in adds them up in the order of the splits --------------------------------
+constexpr int kSplitWaves = kShortTileRows / 32;
+template <int D>
+__device__ __forceinline__ void leave_accumulators(float *part, int64_t slot, int lane, const f32x16_t (&acc)[D / 32]) {
+  const auto to = shared_buffer((char *)part + slot * (32 * D * 4), 32 * D * 4);
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      u32x4_t w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(acc[dt][q4 * 4 + e]);
+      __builtin_amdgcn_raw_buffer_store_b128(w, to, lane * 16 + (dt * 4 + q4) * 1024, 0, kAgentScope);
+    }
+}
+template <int D>
+__device__ __forceinline__ void fetch_accumulators(float *part, int64_t slot, int lane, u32x4_t (&w)[D / 8]) {
+  const auto from = shared_buffer((char *)part + slot * (32 * D * 4), 32 * D * 4);
+#pragma unroll
+  for (int k = 0; k < D / 8; ++k)
+    w[k] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(from, lane * 16 + k * 1024, 0, kAgentScope));
+}
+// Counts this workgroup in; true (in every wave) if all n are in now.  told: a word of LDS nobody else uses.
+__device__ __forceinline__ bool last_of_splits(int32_t *counter, int n, lds_char *told_at) {
+  __attribute__((address_space(3))) volatile int *const told = (__attribute__((address_space(3))) volatile int *)told_at;
+  dma_wait<0>();  // this wave's stores have left its XCD
+  wg_barrier();   // every wave's have
+  if (threadIdx.x == 0) {
+    *told = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    lds_wait();
+  }
+  wg_barrier();
+  return __builtin_amdgcn_readfirstlane(*told) == n;
+}
+
 }  // namespace ba

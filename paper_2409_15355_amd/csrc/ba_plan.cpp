@@ -395,23 +395,82 @@ std::vector<PromptBlock> list_prompt_blocks(int32_t n_prompts, const int32_t *cu
   return blks;
 }
 
-void sort_by_key_range(std::vector<PromptBlock> *blks) {
+namespace {
+constexpr int kPromptKeys = 32;  // keys per tile of the forward and dq kernels
+int walk_tiles(int64_t keys) { return (int)((keys - 1) / kPromptKeys + 1); }
+// a last block that sees enough of its prompt for more than one workgroup per row tile
+int shared_splits(int64_t ctx, int64_t len, int chunk) {
+  if (ctx <= 0 || len <= 0) return 1;
+  const int w = walk_tiles(ctx + len);
+  return w > kShareAbove ? walk_splits(w, chunk) : 1;
+}
+}  // namespace
+
+WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
+  WalkShares ws;
+  const int64_t G = h->n_q_heads / h->n_kv_heads;
+  double load = 0.0;  // tiles walked by all workgroups, and kFixedTiles for each
+  int longest = 0;
+  for (int n = 0; n < n_prompts; ++n) {
+    const int last = cu_blk[n + 1] - 1;
+    for (int b = cu_blk[n]; b <= last; ++b) {
+      const int64_t len = block_offsets[b + 1] - block_offsets[b];
+      if (len == 0) continue;
+      const int64_t n_rt = (len * G + kShortTileRows - 1) / kShortTileRows;
+      const int64_t ctx = b == last ? block_offsets[b] - block_offsets[cu_blk[n]] : 0;
+      const int w = walk_tiles(ctx + len);
+      load += (double)n_rt * (ctx > 0 ? w : 0.5 * (w + 1));
+      load += (double)n_rt * kFixedTiles;
+      if (ctx > 0) longest = std::max(longest, w);
+    }
+  }
+  if (longest <= kShareAbove) return ws;
+  load *= h->n_kv_heads;
+  const int chunk = std::max(kShareChunk, (int)(load / (kShareCus * kShareLoad)));
+  for (int n = 0; n < n_prompts; ++n) {
+    const int last = cu_blk[n + 1] - 1;
+    const int64_t len = block_offsets[last + 1] - block_offsets[last];
+    const int s = shared_splits(block_offsets[last] - block_offsets[cu_blk[n]], len, chunk);
+    if (s < 2) continue;
+    ++ws.n_split;
+    ws.items += (len * G + kShortTileRows - 1) / kShortTileRows * s;
+  }
+  const size_t slots = (size_t)ws.items * h->n_kv_heads * (kShortTileRows / 32);
+  // (more such blocks than one launch lists, or partial results beyond any use: enough to run side by side)
+  if (ws.n_split == 0 || ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes) return WalkShares();
+  ws.chunk = chunk;
+  ws.part_bytes = slots * 32 * h->head_dim * 4;
+  ws.ml_bytes = slots * 256;
+  ws.count_bytes = (size_t)ws.items * h->n_kv_heads * 4;
+  return ws;
+}
+
+void sort_by_key_range(std::vector<PromptBlock> *blks, const WalkShares &shares) {
   // (a prompt's last block walks the whole prompt, and a launch should not end on a few of those)
-  std::stable_sort(blks->begin(), blks->end(), [](const PromptBlock &a, const PromptBlock &b) {
+  const auto shared = [&](const PromptBlock &b) {
+    return shares.n_split > 0 && shared_splits(b.start - b.kstart, b.len, shares.chunk) > 1;
+  };
+  std::stable_sort(blks->begin(), blks->end(), [&](const PromptBlock &a, const PromptBlock &b) {
+    const bool sa = shared(a), sb = shared(b);
+    if (sa != sb) return sa;
     return (int64_t)a.start + a.len - a.kstart > (int64_t)b.start + b.len - b.kstart;
   });
 }
 
-int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, PromptMeta *meta) {
+int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, const WalkShares &shares, PromptMeta *meta) {
   memset(meta, 0, sizeof(*meta));
   meta->n = n;
+  meta->n_split = b0 == 0 ? shares.n_split : 0;
+  meta->chunk = shares.chunk;
   int64_t tiles = 0;
   for (int i = 0; i < n; ++i) {
-    meta->start[i] = blks[b0 + i].start;
-    meta->len[i] = blks[b0 + i].len;
-    meta->kstart[i] = blks[b0 + i].kstart;
+    const PromptBlock &b = blks[b0 + i];
+    meta->start[i] = b.start;
+    meta->len[i] = b.len;
+    meta->kstart[i] = b.kstart;
     meta->tile_start[i] = (int32_t)tiles;
-    tiles += ((int64_t)blks[b0 + i].len * G + kShortTileRows - 1) / kShortTileRows;
+    const int64_t n_rt = ((int64_t)b.len * G + kShortTileRows - 1) / kShortTileRows;
+    tiles += n_rt * (i < meta->n_split ? walk_splits(walk_tiles((int64_t)b.start + b.len - b.kstart), shares.chunk) : 1);
     if (tiles > 0x3fffffff) return -1;
   }
   meta->tile_start[n] = (int32_t)tiles;
@@ -556,23 +615,32 @@ int64_t ba_schedule_prompts(const ba_heads *heads, int32_t n_prompts, const int3
   if ((rc = ba::check_heads(heads, true))) return rc;
   if ((rc = ba::check_prompt_blocks(n_prompts, cu_blk, block_offsets))) return rc;
   const int G = heads->n_q_heads / heads->n_kv_heads;
+  const ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
   std::vector<ba::PromptBlock> blks = ba::list_prompt_blocks(n_prompts, cu_blk, block_offsets);
-  ba::sort_by_key_range(&blks);
+  ba::sort_by_key_range(&blks, shares);
   ba::ItemSink sink{items, items ? max_items : 0};
   int launch = 0;
   for (size_t b0 = 0; b0 < blks.size(); b0 += ba::kEncMaxBlocks, ++launch) {
     const int n = (int)std::min<size_t>(ba::kEncMaxBlocks, blks.size() - b0);
     ba::PromptMeta meta;
-    const int64_t tiles = ba::build_prompt_meta(blks, b0, n, G, &meta);
+    const int64_t tiles = ba::build_prompt_meta(blks, b0, n, G, shares, &meta);
     if (tiles < 0) return ba::fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
     for (int64_t tile = 0; tile < tiles; ++tile) {
       const int i = ba::segment_of(meta.tile_start, meta.n, (int)tile);
       const int lq = meta.len[i], dq = meta.start[i] - meta.kstart[i];  // dq: earlier tokens of the prompt it sees
-      const int jt = (int)tile - meta.tile_start[i];
-      const int n_rows = lq * G, row0 = jt * ba::kShortTileRows;
+      int jt = (int)tile - meta.tile_start[i], split = 0, n_splits = 1;
+      const int n_rows = lq * G;
+      if (i < meta.n_split) {
+        const int n_rt = (n_rows + ba::kShortTileRows - 1) / ba::kShortTileRows;
+        n_splits = ba::walk_splits(ba::walk_tiles(dq + lq), meta.chunk);
+        split = jt / n_rt;
+        jt -= split * n_rt;
+      }
+      const int row0 = jt * ba::kShortTileRows;
       const int last_row = std::min(n_rows, row0 + ba::kShortTileRows) - 1;
       // keys counted from the first visible one: tiles up to the one that holds the last row's own token
-      const int keys_walked = ((dq + last_row / G) / 32 + 1) * 32;
+      const ba::TileRange walk = ba::walk_split_range((dq + last_row / G) / 32 + 1, n_splits, split);
+      const int k_begin = walk.begin * 32, k_end = walk.end * 32;
       ba_work_item w;
       memset(&w, 0, sizeof(w));
       w.kv_head = w.xcd = -1;
@@ -583,10 +651,12 @@ int64_t ba_schedule_prompts(const ba_heads *heads, int32_t n_prompts, const int3
       w.tile_keys = 32;
       w.row_begin = row0;
       w.row_end = last_row + 1;
-      w.n_splits = 1;
-      w.ctx_begin = 0;
-      w.ctx_end = std::min(dq, keys_walked);
-      w.self_end = std::min(lq, std::max(0, keys_walked - dq));
+      w.split = split;
+      w.n_splits = n_splits;
+      w.ctx_begin = std::min(dq, k_begin);
+      w.ctx_end = std::min(dq, k_end);
+      w.self_begin = std::min(lq, std::max(0, k_begin - dq));
+      w.self_end = std::min(lq, std::max(0, k_end - dq));
       sink.put(w);
     }
   }

@@ -107,9 +107,17 @@ struct PromptBlock {
   int32_t start, len, kstart, fin_start, fin_len, prompt;
 };
 std::vector<PromptBlock> list_prompt_blocks(int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets);
-// ... in the order the forward and dq kernels take them (longest key range first)
-void sort_by_key_range(std::vector<PromptBlock> *blks);
+// Which last blocks have their walks shared by several workgroups (PromptMeta::n_split), and the memory that takes.
+struct WalkShares {
+  int n_split = 0, chunk = 1;
+  int64_t items = 0;  // (row tile, split) pairs of those blocks
+  size_t part_bytes = 0, ml_bytes = 0, count_bytes = 0;
+  size_t total() const { return align256(part_bytes) + align256(ml_bytes) + align256(count_bytes); }
+};
+WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets);
+// ... in the order the forward and dq kernels take them: those of shared walks, then longest key range first
+void sort_by_key_range(std::vector<PromptBlock> *blks, const WalkShares &shares);
 // the table of one launch: blocks [b0, b0 + n) of the list.  Returns its row tiles, -1 if too many.
-int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, PromptMeta *meta);
+int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, const WalkShares &shares, PromptMeta *meta);
 
 }  // namespace ba

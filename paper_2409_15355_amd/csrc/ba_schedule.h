@@ -89,6 +89,16 @@ BA_HD TileRange split_tile_range(int n_ctx_tiles, int n_causal_tiles, int n_spli
   return r;
 }
 
+// Whole prompts: workgroups that share the walk of a block whose last row walks `tiles` key tiles, and the
+// tiles of split `split` of a row tile that walks n_t of them.
+BA_HD int walk_splits(int tiles, int chunk) { return (tiles + chunk - 1) / chunk; }
+BA_HD TileRange walk_split_range(int n_t, int n_splits, int split) {
+  TileRange r;
+  r.begin = (int)((unsigned)n_t * (unsigned)split / (unsigned)n_splits);
+  r.end = (int)((unsigned)n_t * (unsigned)(split + 1) / (unsigned)n_splits);
+  return r;
+}
+
 // Work item number -> (row tile, KV head, split) of a launch of the main core.  Row tiles run
 // fastest (the row tiles of one (KV head, split) share every K/V tile); above them the (KV head,
 // split) pairs are ordered by group of kv_group KV heads, then split, then head inside the group.

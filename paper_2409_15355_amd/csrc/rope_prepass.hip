@@ -54,6 +54,8 @@ __global__ __launch_bounds__(kThreads) void rope_prepass_kernel(RopePrepassParam
   constexpr int CH = D / VEC;
   constexpr int TPV = CH / 2;          // threads per head vector
   constexpr int TPP = kThreads / TPV;  // tokens per workgroup
+  if (blockIdx.y == 0)
+    for (int i = (int)(blockIdx.x * kThreads + threadIdx.x); i < p.n_zero; i += (int)gridDim.x * kThreads) p.zero[i] = 0;
   {
     // workgroup rows beyond the head groups fill a (small) table of rotations, one thread per entry
     const int head_groups = q_groups(p) + (p.do_k ? (p.n_kv_heads + p.heads_per_thread - 1) / p.heads_per_thread : 0);

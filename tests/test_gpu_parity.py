@@ -1247,6 +1247,55 @@ def test_whole_prompts_backward_medium_prompts(ba):
         assert_grad_close(gv[t0:t1], rv, av, f"dv, prompt {n}")
 
 
+SHARED_CASES = [("group1-d64", 2, 2, 64, [[1150, 37], [40, 9]]), ("group3-d128", 6, 2, 128, [[700, 420, 50]]),
+                ("group4-d128", 8, 2, 128, [[30, 5], [1300, 33]]), ("group4-d64", 4, 1, 64, [[1, 1500, 1]])]
+
+
+@pytest.mark.parametrize("case", SHARED_CASES, ids=[c[0] for c in SHARED_CASES])
+def test_whole_prompts_with_shared_walks_match_the_definition(ba, case):
+    """Last blocks of more than 36 key tiles: several workgroups share a row tile's walk and the last of them merges
+    (forward and dq).  One row tile and several, waves without rows, one token; outputs, log-sum-exps and gradients
+    against the oracle (the bounds of the unshared walks: partial results are in 32 bits), the same bits again,
+    whatever the workspace held."""
+    torch = torch_mod()
+    name, hq, hkv, d, prompts = case
+    lens = [l for p in prompts for l in p]
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    T = int(offs[-1])
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    assert max(w.n_splits for w in ba.ba_schedule_prompts(heads, cu_blk, offs)) > 1
+    qb, kb, vb = gen_qkv(700 + len(name), T, hq, hkv, d)
+    dob = wl.normal_bf16_bits(740 + len(name), (T, hq, d))
+    q, k, v, do = dev_bf16(qb), dev_bf16(kb), dev_bf16(vb), dev_bf16(dob)
+    fwd = ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False)
+    bwd = ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs)
+    outs = []
+    for fill in (255, 1, 0):
+        o, lse = torch.full_like(q, float("nan")), torch.full((T, hq), float("nan"), device="cuda")
+        dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, k, v))
+        ba.ba_block_attention_prompts(heads, q, k, v, o, None, lse, cu_blk, offs, 1, torch.full((fwd,), fill, dtype=torch.uint8, device="cuda"))
+        ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs,
+                                               torch.full((bwd,), fill, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        outs.append([host_bits(o), lse.cpu().numpy().view(np.int32), host_bits(dq), host_bits(dk), host_bits(dv)])
+    for again in outs[1:]:
+        for a, b in zip(outs[0], again):
+            assert np.array_equal(a, b)
+    f = oracle.bf16_bits_to_f64
+    th = oracle.theta(10000.0, d)
+    for n in range(len(prompts)):
+        t0, t1 = int(offs[cu_blk[n]]), int(offs[cu_blk[n + 1]])
+        po = offs[cu_blk[n]:cu_blk[n + 1] + 1] - t0
+        ro = oracle.masked_attention_bruteforce(f(qb[t0:t1]), f(kb[t0:t1]), f(vb[t0:t1]), po, th)
+        assert_attention_close(f(outs[0][0][t0:t1]), ro, f"{name} o, prompt {n}")
+        want = oracle_prompt_lse(f(qb[t0:t1]), f(kb[t0:t1]), po, th, 0, d ** -0.5)
+        assert np.abs(outs[0][1][t0:t1].view(np.float32) - want).max() < 2e-2, f"{name} log-sum-exp, prompt {n}"
+        (rq, rk, rv), (aq, ak, av) = oracle_grads(f(qb[t0:t1]), f(kb[t0:t1]), f(vb[t0:t1]), f(dob[t0:t1]), po, th)
+        for got, ref, size, what in ((outs[0][2], rq, aq, "dq"), (outs[0][3], rk, ak, "dk"), (outs[0][4], rv, av, "dv")):
+            assert_grad_close(f(got[t0:t1]), ref, size, f"{name} {what}, prompt {n}")
+
+
 def test_whole_prompts_forward_and_backward_on_strided_views(ba):
     """q, k, v as views into one fused [T, Hq + 2 Hkv, D] projection buffer, the gradients written
     into views of a buffer of the same shape, o and d_out with padded head strides: every tensor of

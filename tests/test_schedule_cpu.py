@@ -191,6 +191,42 @@ def test_whole_prompt_items_cover_the_mask_of_section_2_4_exactly(hq, hkv):
         assert np.array_equal(count, want), (case, lens, cu_blk)
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 64), (8, 2, 64), (32, 8, 128), (6, 2, 128)])
+def test_shared_walks_of_whole_prompts_cover_the_mask_once(hq, hkv, d):
+    """Last blocks behind long prompts: the splits of a row tile partition its walk, in order, and every visible
+    pair belongs to exactly one work item; prompts at the edge of the rule are left alone."""
+    G = hq // hkv
+    h = ba.Heads(hq, hkv, d, 10000.0)
+    seen = set()
+    for lens_of in ([[1152]], [[1120, 32]], [[1121, 32]], [[700, 0, 800, 33]], [[3000, 2500, 1]], [[5000, 70], [40, 7], [1300, 300]]):
+        cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in lens_of])])
+        offs = np.concatenate([[0], np.cumsum([n for p in lens_of for n in p])])
+        items = ba.ba_schedule_prompts(h, cu_blk, offs)
+        for n, p in enumerate(lens_of):
+            p0, last, lq = int(offs[cu_blk[n]]), int(offs[cu_blk[n + 1] - 1]), p[-1]
+            ctx = last - p0
+            tiles = {}
+            for w in items:
+                if w.problem == n and w.first_token == last:
+                    tiles.setdefault(w.row_begin, []).append(w)
+            assert sorted(tiles) == list(range(0, lq * G, 128))
+            for ws in tiles.values():
+                ws.sort(key=lambda w: w.split)
+                seen.add(ws[0].n_splits)
+                shared = ctx > 0 and (ctx + lq - 1) // 32 + 1 > 36
+                assert ws[0].n_splits == 1 or shared
+                assert ws[0].n_splits > 1 or not shared or len(lens_of) > 1  # (a busy launch shares less)
+                assert [w.split for w in ws] == list(range(ws[0].n_splits))
+                at = 0
+                for w in ws:
+                    begin, end = w.ctx_begin + w.self_begin, w.ctx_end + w.self_end
+                    assert begin == at and end >= begin
+                    at = end
+                last_tok = (ws[0].row_end - 1) // G
+                assert at == min(ctx + lq, ((ctx + last_tok) // 32 + 1) * 32)
+    assert 1 in seen and max(seen) >= (4 if hq <= 6 else 2)
+
+
 def test_split_range_arithmetic_partitions_every_walk():
     """split_tile_range through the final-block query: over split counts of 1 to 32 (eight KV heads, by varying the
     compute-unit count; more splits: below), the splits of a row tile partition its walk."""
