@@ -32,7 +32,7 @@ constexpr int kBWaves = 4;
 constexpr int kBThreads = kBWaves * 64;
 constexpr int kBKeys = 32;  // walked rows (keys, or packed query rows) per tile
 constexpr int kBBuf = 3;    // tile buffers
-constexpr int kKvRows = 32; // packed query rows per tile of the dk/dv kernel
+constexpr int kKvRows = kKvTileRows;
 constexpr float kLn2 = 0.6931471805599453f, kLog2e = 1.4426950408889634f;
 
 template <int D>
@@ -556,7 +556,15 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   const int b = find_block(meta.tile_start, keytile);
   const int k_tok0 = meta.start[b], lk = meta.len[b];  // the block that owns the keys
   const int f_tok0 = meta.fin_start[b], lf = meta.fin_len[b];  // its prompt's last block, if it is a passage
-  const int k0 = (keytile - meta.tile_start[b]) * kBwdTileKeys;  // the workgroup's first key, inside the block
+  // a block whose walks are shared: which split of which key tile
+  int split = 0, n_kt = 0, jt = keytile - meta.tile_start[b];
+  const bool shared = b < meta.n_split;
+  if (shared) {
+    n_kt = (lk + kBwdTileKeys - 1) / kBwdTileKeys;
+    split = jt / n_kt;
+    jt -= split * n_kt;
+  }
+  const int k0 = jt * kBwdTileKeys;  // the workgroup's first key, inside the block
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -575,7 +583,14 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   //      tokens where q^ and dO are 553) ---------------------------------------------------------------
   const int n_rows_a = lk * Gq, n_rows_f = lf * Gq;
   const int n_f = (n_rows_f + kKvRows - 1) / kKvRows;
-  const int n_t = n_f + (n_rows_a + kKvRows - 1) / kKvRows - (k0 * Gq) / kKvRows;
+  TileRange walk = {0, n_f + (n_rows_a + kKvRows - 1) / kKvRows - (k0 * Gq) / kKvRows};
+  int n_splits = 1;
+  if (shared) {
+    n_splits = walk_splits(walk.end, meta.chunk);
+    if (split >= n_splits) return;  // (the key tiles behind a block's first walk less and take fewer)
+    walk = walk_split_range(walk.end, n_splits, split);
+  }
+  const int t0 = walk.begin, n_t = walk.end;  // this workgroup's tiles
   const int own_last = ((n_rows_a - 1) / kKvRows) * kKvRows;  // first row of the block's last tile
   const int fin_last = (n_f - 1) * kKvRows;
 
@@ -626,7 +641,8 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
     c_base += (uint64_t)(uint32_t)(row0 / kKvRows) * c_step;
     l_base = (const char *)(bp.ld + 2 * (((int64_t)kvh * bp.T + tok0) * bp.ld_group)) + (uint32_t)row0 * 8u;
   };
-  if (n_f > 0) enter_block(f_tok0, fin_last, n_rows_f);
+  if (t0 < n_f) enter_block(f_tok0, fin_last - t0 * kKvRows, n_rows_f);
+  else enter_block(k_tok0, own_last - (t0 - n_f) * kKvRows, n_rows_a);
   auto issue_copy = [&](int t, int buf) __attribute__((always_inline)) {
     if (t == n_f) enter_block(k_tok0, own_last, n_rows_a);
     const uint32_t lds_tile = lds_copy + (uint32_t)buf * BUFB;
@@ -647,16 +663,16 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
     c_base -= c_step;
     l_base -= kKvRows * 8;
   };
-  if (0 < n_t) issue_copy(0, 0);
+  if (t0 < n_t) issue_copy(t0, t0 & 1);
   __builtin_amdgcn_sched_barrier(0);
   dma_wait<0>();
 
-  // ---- rows -> B-operand fragments through this wave's slice of buffer 1 (the first tile goes to buffer 0,
-  //      the second is asked for behind the first barrier) -----------------------------------------------
+  // ---- rows -> B-operand fragments through this wave's slice of the buffer that the first tile does not go to
+  //      (the second is asked for behind the first barrier) ----------------------------------------------
   static_assert(kBWaves * G::SLICEB <= 2 * TB, "the slices fit the tiles of one buffer");
   bf16x8_t kv[G::KCH];
   {
-    const uint32_t s_ofs = BUFB + wave * G::SLICEB;
+    const uint32_t s_ofs = (uint32_t)(~t0 & 1) * BUFB + wave * G::SLICEB;
     u32x4_t got[2][G::KCH];
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -692,7 +708,7 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   lds_char *const pex = smem + 2 * BUFB + pair * KG::PEXB + lane * 16;
   const uint32_t ofs1 = is_b ? TB : 0u, ofs2 = is_b ? 0u : TB;  // the tile of the products before the exchange, behind it
 #pragma unroll 1
-  for (int i = 0; i < n_t; ++i) {
+  for (int i = t0; i < n_t; ++i) {
     dma_wait<0>();
     wg_barrier();
     if (i + 1 < n_t) issue_copy(i + 1, (i + 1) & 1);
@@ -770,6 +786,30 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   int ln = lane;
   asm volatile("" : "+v"(ln));
   const int ecol = ln & 31, ehf = ln >> 5;
+  if (n_splits > 1) {
+    // (a shared walk: every wave leaves its half, the last workgroup adds the splits up in their order)
+    const int64_t slot = ((int64_t)(keytile - split * n_kt) * p.n_kv_heads + kvh) * kBWaves + wave;  // of split 0
+    const int64_t step = (int64_t)n_kt * p.n_kv_heads * kBWaves;                                     // to the next
+    float *const part_o = (float *)p.part_o;
+    if (wave_has_keys) leave_accumulators<D>(part_o, slot + split * step, ln, acc);
+    static_assert(kBWaves * (size_t)G::TILEB + 16 <= KG::LDS, "a word behind the output staging");
+    if (!last_of_splits(p.part_idx + (int64_t)(keytile - split * n_kt) * p.n_kv_heads + kvh, n_splits, smem + KG::LDS - 16)) return;
+    if (wave_has_keys) {
+#pragma unroll
+      for (int dt = 0; dt < G::DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
+#pragma unroll 1
+      for (int s = 0; s < n_splits; ++s) {
+        u32x4_t w[D / 8];
+        fetch_accumulators<D>(part_o, slot + s * step, ln, w);
+#pragma unroll
+        for (int k = 0; k < D / 8; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) *((float *)&acc[k >> 2] + (k & 3) * 4 + e) += __uint_as_float(w[k][e]);
+      }
+    }
+  }
   if (is_b)
     rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(k_tok0 + min(kw0 + ecol, lk - 1)) * D), ehf,
                    p.rope_layout != 0, kLn2 / p.scale_log2e);

@@ -1,6 +1,5 @@
 // C boundary, whole prompts under the Block-attention mask (Section 2.4): forward and backward entry
 // points, and the route through zero-padded phantom heads for groups of fewer than four query heads.
-#include <limits.h>
 #include <string.h>
 
 #include <algorithm>
@@ -69,6 +68,21 @@ size_t shares_bytes(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk,
   if (h->n_q_heads / h->n_kv_heads < kPadGroup) {
     const ba_heads h4 = padded_heads(h);
     bytes = std::max(bytes, ba::plan_walk_shares(&h4, n_prompts, cu_blk, block_offsets).total());
+  }
+  return bytes;
+}
+// ... of the backward pass: the dq and the dk/dv kernel use the partial results' memory one after the other
+size_t bwd_shares_bytes(const ba::WalkShares &dq, const ba::WalkShares &kv) {
+  return align256(std::max(dq.part_bytes, kv.part_bytes)) + align256(dq.count_bytes + kv.count_bytes);
+}
+size_t bwd_shares_bytes(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
+  const auto of = [&](const ba_heads *hh) {
+    return bwd_shares_bytes(ba::plan_walk_shares(hh, n_prompts, cu_blk, block_offsets), ba::plan_kv_shares(hh, n_prompts, cu_blk, block_offsets));
+  };
+  size_t bytes = of(h);
+  if (h->n_q_heads / h->n_kv_heads < kPadGroup) {
+    const ba_heads h4 = padded_heads(h);
+    bytes = std::max(bytes, of(&h4));
   }
   return bytes;
 }
@@ -263,7 +277,7 @@ size_t ba_block_attention_prompts_backward_workspace_bytes(const ba_heads *heads
   // rotated scaled q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row
   // ... and the partial results of shared walks
   return pad_bytes + align256(T * hq * D * 2) + align256(T * hkv * D * 2) + align256(T * D * 4) +
-         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8 + 16) + shares_bytes(heads, n_prompts, cu_blk, block_offsets);
+         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8 + 16) + bwd_shares_bytes(heads, n_prompts, cu_blk, block_offsets);
 }
 
 int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k,
@@ -344,7 +358,9 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   const ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
   ba::AttnParams ap;
   memset(&ap, 0, sizeof(ap));
-  place_shares(shares, wsp, &ap);
+  const ba::WalkShares kv_shares = ba::plan_kv_shares(heads, n_prompts, cu_blk, block_offsets);
+  ap.part_o = (uint16_t *)wsp;
+  ap.part_idx = (int32_t *)(wsp + align256(std::max(shares.part_bytes, kv_shares.part_bytes)));
 
   ba::RopeTable rt;
   build_rope_table(heads, &rt);
@@ -354,7 +370,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   for (int n0 = 0; n0 < n_prompts; n0 += ba::kRopeMaxSegs) {
     const int n = std::min(ba::kRopeMaxSegs, n_prompts - n0);
     if ((rc = run_rope_prepass(heads, rt, q, nullptr, k, &k_rot, n, starts.data() + n0, nullptr, stream, nullptr, nullptr,
-                               nullptr, 0, q_table, 0, ap.part_idx, (int)(shares.count_bytes / 4))))
+                               nullptr, 0, q_table, 0, ap.part_idx, (int)((shares.count_bytes + kv_shares.count_bytes) / 4))))
       return rc;
   }
 
@@ -423,24 +439,13 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   }
   // dk, dv: keys own the sums; most query rows first
   std::vector<Blk> by_k = blks;
-  std::stable_sort(by_k.begin(), by_k.end(),
-                   [](const Blk &a, const Blk &b) { return a.len + a.fin_len > b.len + b.fin_len; });
+  ba::sort_by_query_rows(&by_k, G, kv_shares);
+  ap.part_idx += shares.count_bytes / 4;  // (counters of its own)
   for (size_t b0 = 0; b0 < by_k.size(); b0 += ba::kEncMaxBlocks) {
     const int n = (int)std::min<size_t>(ba::kEncMaxBlocks, by_k.size() - b0);
     ba::BwdKvMeta meta;
-    memset(&meta, 0, sizeof(meta));
-    meta.n = n;
-    int64_t tiles = 0;
-    for (int i = 0; i < n; ++i) {
-      meta.start[i] = by_k[b0 + i].start;
-      meta.len[i] = by_k[b0 + i].len;
-      meta.fin_start[i] = by_k[b0 + i].fin_start;
-      meta.fin_len[i] = by_k[b0 + i].fin_len;
-      meta.tile_start[i] = (int32_t)tiles;
-      tiles += ((int64_t)by_k[b0 + i].len + ba::kBwdTileKeys - 1) / ba::kBwdTileKeys;
-    }
-    for (int i = n; i <= ba::kEncMaxBlocks; ++i) meta.tile_start[i] = i == n ? (int32_t)tiles : INT_MAX;
-    if (tiles > 0x3fffffff) return fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
+    const int64_t tiles = ba::build_kv_meta(by_k, b0, n, G, kv_shares, &meta);
+    if (tiles < 0) return fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
     if (tiles == 0) continue;
     ap.total_tiles = (int32_t)tiles;
     ap.tiles_div = ba::make_fast_div((uint32_t)tiles);

@@ -125,6 +125,7 @@ constexpr int kTileRows = 256;  // packed (token, head-in-group) query rows per 
 constexpr int kTileKeys = 64;   // keys per K/V tile
 constexpr int kShortTileRows = 128;  // packed query rows per workgroup of the short-block schedule
 constexpr int kBwdTileKeys = 64;     // keys per workgroup of the dk/dv kernel
+constexpr int kKvTileRows = 32;      // packed query rows per tile of its walk
 // Per-block encoding sends blocks up to this length through the short-block schedule (measured
 // crossover: beyond about 6,000 to 8,000 tokens the deep pipeline of the main core wins).
 constexpr int kShortMaxLen = 6144;
@@ -153,6 +154,12 @@ constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 constexpr int kShareAbove = 36, kShareChunk = 16;
 constexpr int kShareCus = 256, kShareLoad = 2;
 constexpr size_t kShareMaxBytes = (size_t)256 << 20;
+// ... and the same for the walks of the dk/dv kernel (0.73 us a tile; a key tile's rows are its block's and the last
+// block's).  Forward and backward, us, unshared / shared: 8 over 2 heads of 64, five prompts of 4 x 350-1040 tokens and
+// a last block of 100-300: 272 / 205, two of 16 x 70-200: 104 / 83; 32 over 8 of 128, two of 4 x 26-78 and 74-223: 76 / 69,
+// two of 3 x 134-402: 129 / 105; two of 29 x 88-262: 374 / 371.  From 16 tiles on instead of 20: 4 over 4 of 64, one of
+// 9 x 250-750 73 / 67, but 32 over 8, two of 22 x 37-112 120 / 122 and 16 over 8, four of 4 x 100-298 106 / 108.
+constexpr int kKvShareAbove = 20, kKvShareChunk = 12, kKvShareLoad = 3;
 
 struct AttnParams {
   const uint16_t *q;
@@ -252,6 +259,10 @@ struct BwdKvMeta {
   int32_t tile_start[kEncMaxBlocks + 1];  // in key tiles of kBwdTileKeys keys; INT_MAX beyond [n]
   int32_t fin_start[kEncMaxBlocks];
   int32_t fin_len[kEncMaxBlocks];          // 0: the block is its prompt's last
+  // The first n_split blocks' walks are shared out: a block whose first key is seen by w tiles of kKvTileRows packed rows
+  // has walk_splits(w, chunk) entries per key tile (all key tiles of split 0 first, then of split 1 ...), of which a key
+  // tile takes as many as its own walk wants
+  int32_t n_split, chunk;
 };
 
 hipError_t launch_bwd_dq(const AttnParams &p, const PromptMeta &meta, const BwdParams &bp, hipStream_t stream);

@@ -445,6 +445,83 @@ WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t 
   return ws;
 }
 
+namespace {
+// row tiles that see a block's first key
+int64_t kv_walk(int64_t len, int64_t fin_len, int64_t G) {
+  return (len * G + kKvTileRows - 1) / kKvTileRows + (fin_len * G + kKvTileRows - 1) / kKvTileRows;
+}
+int kv_splits(int64_t len, int64_t fin_len, int64_t G, int chunk) {
+  const int64_t w = kv_walk(len, fin_len, G);
+  return w > kKvShareAbove && w < (1 << 20) ? walk_splits((int)w, chunk) : 1;
+}
+int64_t key_tiles(int64_t len) { return (len + kBwdTileKeys - 1) / kBwdTileKeys; }
+}  // namespace
+
+WalkShares plan_kv_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
+  WalkShares ws;
+  const int64_t G = h->n_q_heads / h->n_kv_heads;
+  double load = 0.0;
+  int64_t longest = 0;
+  const auto each = [&](auto &&visit) {
+    for (int n = 0; n < n_prompts; ++n) {
+      const int last = cu_blk[n + 1] - 1;
+      const int64_t fin = block_offsets[last + 1] - block_offsets[last];
+      for (int b = cu_blk[n]; b <= last; ++b) {
+        const int64_t len = block_offsets[b + 1] - block_offsets[b];
+        if (len > 0) visit(len, b == last ? (int64_t)0 : fin);
+      }
+    }
+  };
+  each([&](int64_t len, int64_t fin) {
+    const double n_kt = (double)key_tiles(len);
+    load += n_kt * ((double)kv_walk(len, fin, G) - 0.5 * (double)len * (double)G / kKvTileRows + kFixedTiles);
+    longest = std::max(longest, kv_walk(len, fin, G));
+  });
+  if (longest <= kKvShareAbove) return ws;
+  const int chunk = std::max(kKvShareChunk, (int)std::min(1e6, load * h->n_kv_heads / (kShareCus * kKvShareLoad)));
+  each([&](int64_t len, int64_t fin) {
+    const int s = kv_splits(len, fin, G, chunk);
+    if (s < 2) return;
+    ++ws.n_split;
+    ws.items += key_tiles(len) * s;
+  });
+  const size_t slots = (size_t)ws.items * h->n_kv_heads * (kBwdTileKeys / 16);  // a pair of waves per 32 keys
+  if (ws.n_split == 0 || ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes) return WalkShares();
+  ws.chunk = chunk;
+  ws.part_bytes = slots * 32 * h->head_dim * 4;
+  ws.count_bytes = (size_t)ws.items * h->n_kv_heads * 4;
+  return ws;
+}
+
+void sort_by_query_rows(std::vector<PromptBlock> *blks, int G, const WalkShares &shares) {
+  const auto shared = [&](const PromptBlock &b) { return shares.n_split > 0 && kv_splits(b.len, b.fin_len, G, shares.chunk) > 1; };
+  std::stable_sort(blks->begin(), blks->end(), [&](const PromptBlock &a, const PromptBlock &b) {
+    const bool sa = shared(a), sb = shared(b);
+    if (sa != sb) return sa;
+    return a.len + a.fin_len > b.len + b.fin_len;
+  });
+}
+
+int64_t build_kv_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, const WalkShares &shares, BwdKvMeta *meta) {
+  memset(meta, 0, sizeof(*meta));
+  meta->n = n;
+  meta->n_split = b0 == 0 ? shares.n_split : 0;
+  meta->chunk = shares.chunk;
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    const PromptBlock &b = blks[b0 + i];
+    meta->start[i] = b.start;
+    meta->len[i] = b.len;
+    meta->fin_start[i] = b.fin_start;
+    meta->fin_len[i] = b.fin_len;
+    meta->tile_start[i] = (int32_t)tiles;
+    tiles += key_tiles(b.len) * (i < meta->n_split ? kv_splits(b.len, b.fin_len, G, shares.chunk) : 1);
+    if (tiles > 0x3fffffff) return -1;
+  }
+  for (int i = n; i <= kEncMaxBlocks; ++i) meta->tile_start[i] = i == n ? (int32_t)tiles : 0x7fffffff;
+  return tiles;
+}
+
 void sort_by_key_range(std::vector<PromptBlock> *blks, const WalkShares &shares) {
   // (a prompt's last block walks the whole prompt, and a launch should not end on a few of those)
   const auto shared = [&](const PromptBlock &b) {
