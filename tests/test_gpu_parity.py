@@ -1254,7 +1254,7 @@ SHARED_CASES = [("group1-d64", 2, 2, 64, [[1150, 37], [40, 9]]), ("group3-d128",
 @pytest.mark.parametrize("case", SHARED_CASES, ids=[c[0] for c in SHARED_CASES])
 def test_whole_prompts_with_shared_walks_match_the_definition(ba, case):
     """Last blocks of more than 36 key tiles: several workgroups share a row tile's walk and the last of them merges
-    (forward and dq; in the dk/dv kernel walks of more than 20 row tiles).  One row tile and several, waves without rows, one token; outputs, log-sum-exps and gradients
+    (forward and dq; in the dk/dv kernel walks of more than 21 row tiles).  One row tile and several, waves without rows, one token; outputs, log-sum-exps and gradients
     against the oracle (the bounds of the unshared walks: partial results are in 32 bits), the same bits again,
     whatever the workspace held."""
     torch = torch_mod()
