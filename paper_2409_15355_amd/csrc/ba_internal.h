@@ -156,10 +156,11 @@ constexpr int kShareCus = 256, kShareLoad = 2;
 constexpr size_t kShareMaxBytes = (size_t)256 << 20;
 // ... and the same for the walks of the dk/dv kernel (0.73 us a tile; a key tile's rows are its block's and the last
 // block's).  Forward and backward, us, unshared / shared: 8 over 2 heads of 64, five prompts of 4 x 350-1040 tokens and
-// a last block of 100-300: 272 / 205, two of 16 x 70-200: 104 / 83; 32 over 8 of 128, two of 4 x 26-78 and 74-223: 76 / 69,
-// two of 3 x 134-402: 129 / 105; two of 29 x 88-262: 374 / 371.  From 17 tiles on instead of 22: 4 over 4 of 64, one of
+// a last block of 100-300: 272 / 217, two of 16 x 70-200: 104 / 83; 32 over 8 of 128, two of 4 x 26-78 and 74-223: 76 / 69,
+// two of 3 x 134-402: 129 / 105; two of 29 x 88-262: 374 / 371;
+// three of 11 x 117-351 221 / 222 (232 with chunks a third shorter).  From 17 tiles on instead of 22: 4 over 4 of 64, one of
 // 9 x 250-750 73 / 67, but 32 over 8, two of 22 x 37-112 120 / 122 and 16 over 8, four of 4 x 100-298 106 / 108.
-constexpr int kKvShareAbove = 21, kKvShareChunk = 12, kKvShareLoad = 3;
+constexpr int kKvShareAbove = 21, kKvShareChunk = 12, kKvShareLoad = 2;
 
 struct AttnParams {
   const uint16_t *q;
