@@ -114,6 +114,7 @@ template <typename Blocks>
 static int32_t run_reencode_t(ba::ReencParams p, const ba::RopeTable &rt, int n_blocks, const int32_t *src_off,
                        const int32_t *dst_off, const int32_t *len, const int32_t *pos_old,
                        const int32_t *pos_new, hipStream_t stream) {
+  const int32_t table_end = p.table_end;
   std::vector<Blocks> tab(1);  // (the large table is too big for the stack of a small thread)
   Blocks &blk = tab[0];
   for (int b0 = 0; b0 < n_blocks; b0 += Blocks::kBlocks) {
@@ -133,6 +134,7 @@ static int32_t run_reencode_t(ba::ReencParams p, const ba::RopeTable &rt, int n_
     }
     if (!filled) continue;
     blk.n = filled;
+    if (p.row_table) p.table_end = b0 + n < n_blocks ? dst_off[b0 + n] : table_end;
     p.max_len = max_len;
     // few tokens: one head per thread (more workgroups, shorter dependent chains);
     // many tokens: all heads in one thread (sin/cos computed once per token)
@@ -227,6 +229,159 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
 }
 
 
+
+int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,
+                    const ba_tensor *k_f, const ba_tensor *v_f, const ba_tensor *o_out, const ba_tensor *k_f_rot_out,
+                    int32_t n_prompts, const int32_t *cu_q, const int32_t *cu_ctx, const int32_t *q_pos0,
+                    int32_t rope_mode, void *ws, size_t ws_bytes, void *stream_, const GatheredRows *rows) {
+  hipStream_t stream = (hipStream_t)stream_;
+  int32_t rc;
+  if ((rc = check_heads(heads, true))) return rc;
+  const int D = heads->head_dim;
+  if (rope_mode != BA_ROPE_NONE && rope_mode != BA_ROPE_APPLY)
+    return fail(BA_ERR_INVALID_ARG, "rope_mode %d unknown", rope_mode);
+  FinalPlan pl;
+  if ((rc = ba::plan_final(heads, n_prompts, cu_q, cu_ctx, rope_mode, k_f_rot_out != nullptr, num_cus(), &pl))) return rc;
+  if (n_prompts == 0) return BA_OK;
+  if ((rc = check_tensor(q_f, "q_f", false, D, heads->n_q_heads))) return rc;
+  if ((rc = check_tensor(k_f, "k_f", false, D, heads->n_kv_heads))) return rc;
+  if ((rc = check_tensor(v_f, "v_f", false, D, heads->n_kv_heads))) return rc;
+  if ((rc = check_tensor(o_out, "o_out", false, D, heads->n_q_heads))) return rc;
+  const bool any_ctx = cu_ctx[n_prompts] > cu_ctx[0];
+  if (any_ctx) {
+    if ((rc = check_tensor(k_ctx, "k_ctx", false, D, heads->n_kv_heads))) return rc;
+    if ((rc = check_tensor(v_ctx, "v_ctx", false, D, heads->n_kv_heads))) return rc;
+  }
+  if (k_f_rot_out) {
+    if (rope_mode != BA_ROPE_APPLY)
+      return fail(BA_ERR_INVALID_ARG, "k_f_rot_out needs rope_mode BA_ROPE_APPLY");
+    if ((rc = check_tensor(k_f_rot_out, "k_f_rot_out", false, D, heads->n_kv_heads))) return rc;
+  }
+  if (pl.total() > 0 && (!ws || ws_bytes < pl.total() || ((uintptr_t)ws & 255)))
+    return fail(BA_ERR_WORKSPACE, "final block: 256-byte aligned workspace of %zu bytes needed, %zu given",
+                pl.total(), ws_bytes);
+
+  char *wsp = (char *)ws;
+  void *kf_ws = wsp;
+  uint16_t *q_ws = (uint16_t *)(wsp + align256(pl.kf_bytes));
+  uint16_t *part_o = (uint16_t *)(wsp + align256(pl.kf_bytes) + align256(pl.q_bytes));
+  float *part_ml = (float *)(wsp + align256(pl.kf_bytes) + align256(pl.q_bytes) + align256(pl.part_o_bytes));
+  int32_t *part_idx = (int32_t *)((char *)part_ml + align256(pl.part_ml_bytes));
+
+  ba::RopeTable rt;
+  build_rope_table(heads, &rt);
+
+  std::vector<int32_t> pos0(n_prompts), lens(n_prompts), starts(n_prompts), zero(n_prompts, 0);
+  for (int n = 0; n < n_prompts; ++n) {
+    pos0[n] = q_pos0 ? q_pos0[n] : cu_ctx[n + 1] - cu_ctx[n];
+    lens[n] = cu_q[n + 1] - cu_q[n];
+    starts[n] = cu_q[n];
+  }
+
+  ba_tensor kf_use = *k_f;
+  if (rope_mode == BA_ROPE_APPLY) {
+    if (k_f_rot_out) {
+      kf_use = *k_f_rot_out;
+    } else {
+      kf_use.ptr = kf_ws;
+      kf_use.stride_head = D;
+      kf_use.stride_tok = (int64_t)heads->n_kv_heads * D;
+    }
+  }
+
+  const int G = heads->n_q_heads / heads->n_kv_heads;
+  ba::AttnParams ap;
+  memset(&ap, 0, sizeof(ap));
+  if (rope_mode == BA_ROPE_APPLY) {
+    ap.q = q_ws;
+    ap.q_st = (int64_t)heads->n_q_heads * D;
+    ap.q_sh = D;
+  } else {
+    ap.q = (const uint16_t *)q_f->ptr;
+    ap.q_st = q_f->stride_tok;
+    ap.q_sh = q_f->stride_head;
+  }
+  ap.kf = (const uint16_t *)kf_use.ptr;
+  ap.kf_st = kf_use.stride_tok;
+  ap.kf_sh = kf_use.stride_head;
+  ap.vf = (const uint16_t *)v_f->ptr;
+  ap.vf_st = v_f->stride_tok;
+  ap.vf_sh = v_f->stride_head;
+  if (any_ctx) {
+    ap.kc = (const uint16_t *)k_ctx->ptr;
+    ap.kc_st = k_ctx->stride_tok;
+    ap.kc_sh = k_ctx->stride_head;
+    ap.vc = (const uint16_t *)v_ctx->ptr;
+    ap.vc_st = v_ctx->stride_tok;
+    ap.vc_sh = v_ctx->stride_head;
+  } else {
+    ap.kc = ap.kf;
+    ap.kc_st = ap.kf_st;
+    ap.kc_sh = ap.kf_sh;
+    ap.vc = ap.vf;
+    ap.vc_st = ap.vf_st;
+    ap.vc_sh = ap.vf_sh;
+  }
+  ap.o = (uint16_t *)o_out->ptr;
+  ap.o_st = o_out->stride_tok;
+  ap.o_sh = o_out->stride_head;
+  ap.part_o = part_o;
+  ap.part_ml = part_ml;
+  ap.part_idx = part_idx;
+  ap.part_units = pl.total_tiles * heads->n_kv_heads * (ba::kTileRows / 32);
+  ap.n_q_heads = heads->n_q_heads;
+  ap.n_kv_heads = heads->n_kv_heads;
+  ap.group = G;
+  ap.group_div = ba::make_fast_div((uint32_t)G);
+  ap.head_dim = D;
+  ap.scale_log2e = scale_log2e(heads);
+  ap.q_ready = rope_mode == BA_ROPE_APPLY;
+  ap.rope_layout = heads->rope_layout;
+  ap.n_splits = pl.n_splits;
+  ap.wg_clock = ba::probe_clock();  // (null unless a probe of ba_probe.hip is the caller)
+
+  int64_t tile_base = 0;  // row tiles of the launches so far: the split partials are indexed by row tile
+  for (int n0 = 0; n0 < n_prompts; n0 += ba::kFinMaxPrompts) {
+    const int n = std::min(ba::kFinMaxPrompts, n_prompts - n0);
+    ba::FinalMeta meta;
+    const int64_t tiles = ba::build_final_meta(cu_q, cu_ctx, n0, n, G, &meta);
+    ap.tile_base = (int32_t)tile_base;
+    tile_base += tiles;
+    ap.total_tiles = (int32_t)tiles;
+    if ((rc = ba::plan_split_cuts(heads->xcd_speed, tiles, heads->n_kv_heads, pl.n_splits, pl.max_nt, num_cus(),
+                                  ba::final_q_bytes_per_kv_head(heads, pl.lq_total), ap.split_cut, &ap.use_cuts, &ap.kv_group,
+                                  &ap.xcd_runs)))
+      return rc;
+    if (rope_mode == BA_ROPE_APPLY) {  // absolute positions of the final block's tokens
+      if ((rc = run_rope_prepass(heads, rt, q_f, q_ws, k_f, &kf_use, n, meta.cu_q, pos0.data() + n0, stream)))
+        return rc;
+    }
+    hipError_t e;
+    {
+      ProfileScope ps(BA_PROFILE_ATTENTION, stream);
+      if (rows) {  // (one launch: the caller's check)
+        ba::FinalGatherMeta gm;
+        memset(&gm, 0, sizeof(gm));
+        static_cast<ba::FinalMeta &>(gm) = meta;
+        gm.rows = rows->rows;
+        for (int i = 0; i < n; ++i) gm.ctx0[i] = rows->ctx0[i];
+        e = ba::launch_attn_final_gathered(ap, gm, stream);
+      } else {
+        e = ba::launch_attn_final(ap, meta, stream);
+      }
+    }
+    if (e != hipSuccess) return device_fail(e, "final-block attention launch");
+  }
+  if (pl.n_splits > 1) {
+    hipError_t e;
+    {
+      ProfileScope ps(BA_PROFILE_COMBINE, stream);
+      e = ba::launch_combine(ap, stream);
+    }
+    if (e != hipSuccess) return device_fail(e, "split combine launch");
+  }
+  return BA_OK;
+}
 
 }  // namespace api
 }  // namespace ba
@@ -530,144 +685,8 @@ int32_t ba_final_block_attention(const ba_heads *heads, const ba_tensor *q_f, co
                                  const ba_tensor *o_out, const ba_tensor *k_f_rot_out, int32_t n_prompts,
                                  const int32_t *cu_q, const int32_t *cu_ctx, const int32_t *q_pos0,
                                  int32_t rope_mode, void *ws, size_t ws_bytes, void *stream_) {
-  hipStream_t stream = (hipStream_t)stream_;
-  int32_t rc;
-  if ((rc = check_heads(heads, true))) return rc;
-  const int D = heads->head_dim;
-  if (rope_mode != BA_ROPE_NONE && rope_mode != BA_ROPE_APPLY)
-    return fail(BA_ERR_INVALID_ARG, "rope_mode %d unknown", rope_mode);
-  FinalPlan pl;
-  if ((rc = ba::plan_final(heads, n_prompts, cu_q, cu_ctx, rope_mode, k_f_rot_out != nullptr, num_cus(), &pl))) return rc;
-  if (n_prompts == 0) return BA_OK;
-  if ((rc = check_tensor(q_f, "q_f", false, D, heads->n_q_heads))) return rc;
-  if ((rc = check_tensor(k_f, "k_f", false, D, heads->n_kv_heads))) return rc;
-  if ((rc = check_tensor(v_f, "v_f", false, D, heads->n_kv_heads))) return rc;
-  if ((rc = check_tensor(o_out, "o_out", false, D, heads->n_q_heads))) return rc;
-  const bool any_ctx = cu_ctx[n_prompts] > cu_ctx[0];
-  if (any_ctx) {
-    if ((rc = check_tensor(k_ctx, "k_ctx", false, D, heads->n_kv_heads))) return rc;
-    if ((rc = check_tensor(v_ctx, "v_ctx", false, D, heads->n_kv_heads))) return rc;
-  }
-  if (k_f_rot_out) {
-    if (rope_mode != BA_ROPE_APPLY)
-      return fail(BA_ERR_INVALID_ARG, "k_f_rot_out needs rope_mode BA_ROPE_APPLY");
-    if ((rc = check_tensor(k_f_rot_out, "k_f_rot_out", false, D, heads->n_kv_heads))) return rc;
-  }
-  if (pl.total() > 0 && (!ws || ws_bytes < pl.total() || ((uintptr_t)ws & 255)))
-    return fail(BA_ERR_WORKSPACE, "final block: 256-byte aligned workspace of %zu bytes needed, %zu given",
-                pl.total(), ws_bytes);
-
-  char *wsp = (char *)ws;
-  void *kf_ws = wsp;
-  uint16_t *q_ws = (uint16_t *)(wsp + align256(pl.kf_bytes));
-  uint16_t *part_o = (uint16_t *)(wsp + align256(pl.kf_bytes) + align256(pl.q_bytes));
-  float *part_ml = (float *)(wsp + align256(pl.kf_bytes) + align256(pl.q_bytes) + align256(pl.part_o_bytes));
-  int32_t *part_idx = (int32_t *)((char *)part_ml + align256(pl.part_ml_bytes));
-
-  ba::RopeTable rt;
-  build_rope_table(heads, &rt);
-
-  std::vector<int32_t> pos0(n_prompts), lens(n_prompts), starts(n_prompts), zero(n_prompts, 0);
-  for (int n = 0; n < n_prompts; ++n) {
-    pos0[n] = q_pos0 ? q_pos0[n] : cu_ctx[n + 1] - cu_ctx[n];
-    lens[n] = cu_q[n + 1] - cu_q[n];
-    starts[n] = cu_q[n];
-  }
-
-  ba_tensor kf_use = *k_f;
-  if (rope_mode == BA_ROPE_APPLY) {
-    if (k_f_rot_out) {
-      kf_use = *k_f_rot_out;
-    } else {
-      kf_use.ptr = kf_ws;
-      kf_use.stride_head = D;
-      kf_use.stride_tok = (int64_t)heads->n_kv_heads * D;
-    }
-  }
-
-  const int G = heads->n_q_heads / heads->n_kv_heads;
-  ba::AttnParams ap;
-  memset(&ap, 0, sizeof(ap));
-  if (rope_mode == BA_ROPE_APPLY) {
-    ap.q = q_ws;
-    ap.q_st = (int64_t)heads->n_q_heads * D;
-    ap.q_sh = D;
-  } else {
-    ap.q = (const uint16_t *)q_f->ptr;
-    ap.q_st = q_f->stride_tok;
-    ap.q_sh = q_f->stride_head;
-  }
-  ap.kf = (const uint16_t *)kf_use.ptr;
-  ap.kf_st = kf_use.stride_tok;
-  ap.kf_sh = kf_use.stride_head;
-  ap.vf = (const uint16_t *)v_f->ptr;
-  ap.vf_st = v_f->stride_tok;
-  ap.vf_sh = v_f->stride_head;
-  if (any_ctx) {
-    ap.kc = (const uint16_t *)k_ctx->ptr;
-    ap.kc_st = k_ctx->stride_tok;
-    ap.kc_sh = k_ctx->stride_head;
-    ap.vc = (const uint16_t *)v_ctx->ptr;
-    ap.vc_st = v_ctx->stride_tok;
-    ap.vc_sh = v_ctx->stride_head;
-  } else {
-    ap.kc = ap.kf;
-    ap.kc_st = ap.kf_st;
-    ap.kc_sh = ap.kf_sh;
-    ap.vc = ap.vf;
-    ap.vc_st = ap.vf_st;
-    ap.vc_sh = ap.vf_sh;
-  }
-  ap.o = (uint16_t *)o_out->ptr;
-  ap.o_st = o_out->stride_tok;
-  ap.o_sh = o_out->stride_head;
-  ap.part_o = part_o;
-  ap.part_ml = part_ml;
-  ap.part_idx = part_idx;
-  ap.part_units = pl.total_tiles * heads->n_kv_heads * (ba::kTileRows / 32);
-  ap.n_q_heads = heads->n_q_heads;
-  ap.n_kv_heads = heads->n_kv_heads;
-  ap.group = G;
-  ap.group_div = ba::make_fast_div((uint32_t)G);
-  ap.head_dim = D;
-  ap.scale_log2e = scale_log2e(heads);
-  ap.q_ready = rope_mode == BA_ROPE_APPLY;
-  ap.rope_layout = heads->rope_layout;
-  ap.n_splits = pl.n_splits;
-  ap.wg_clock = ba::probe_clock();  // (null unless a probe of ba_probe.hip is the caller)
-
-  int64_t tile_base = 0;  // row tiles of the launches so far: the split partials are indexed by row tile
-  for (int n0 = 0; n0 < n_prompts; n0 += ba::kFinMaxPrompts) {
-    const int n = std::min(ba::kFinMaxPrompts, n_prompts - n0);
-    ba::FinalMeta meta;
-    const int64_t tiles = ba::build_final_meta(cu_q, cu_ctx, n0, n, G, &meta);
-    ap.tile_base = (int32_t)tile_base;
-    tile_base += tiles;
-    ap.total_tiles = (int32_t)tiles;
-    if ((rc = ba::plan_split_cuts(heads->xcd_speed, tiles, heads->n_kv_heads, pl.n_splits, pl.max_nt, num_cus(),
-                                  ba::final_q_bytes_per_kv_head(heads, pl.lq_total), ap.split_cut, &ap.use_cuts, &ap.kv_group,
-                                  &ap.xcd_runs)))
-      return rc;
-    if (rope_mode == BA_ROPE_APPLY) {  // absolute positions of the final block's tokens
-      if ((rc = run_rope_prepass(heads, rt, q_f, q_ws, k_f, &kf_use, n, meta.cu_q, pos0.data() + n0, stream)))
-        return rc;
-    }
-    hipError_t e;
-    {
-      ProfileScope ps(BA_PROFILE_ATTENTION, stream);
-      e = ba::launch_attn_final(ap, meta, stream);
-    }
-    if (e != hipSuccess) return device_fail(e, "final-block attention launch");
-  }
-  if (pl.n_splits > 1) {
-    hipError_t e;
-    {
-      ProfileScope ps(BA_PROFILE_COMBINE, stream);
-      e = ba::launch_combine(ap, stream);
-    }
-    if (e != hipSuccess) return device_fail(e, "split combine launch");
-  }
-  return BA_OK;
+  return final_block(heads, q_f, k_ctx, v_ctx, k_f, v_f, o_out, k_f_rot_out, n_prompts, cu_q, cu_ctx, q_pos0, rope_mode, ws,
+                     ws_bytes, stream_, nullptr);
 }
 
 }  // extern "C"

@@ -68,5 +68,16 @@ int32_t run_rope_prepass(const ba_heads *h, const RopeTable &rt, const ba_tensor
                          const RopeRots *rots = nullptr, const RopeRotsSmall *rots_small = nullptr, float *rot_dst = nullptr,
                          int n_rot = 0, float *q_table = nullptr, int table_rows = 0, int32_t *zero = nullptr, int n_zero = 0);
 
+// ba_final_block_attention; rows: the context's keys are k_ctx's rows from ctx0[n] on, its values v_ctx's through a table
+// (FinalGatherMeta).
+struct GatheredRows {
+  const uint32_t *rows;
+  const int32_t *ctx0;
+};
+int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,
+                    const ba_tensor *k_f, const ba_tensor *v_f, const ba_tensor *o_out, const ba_tensor *k_f_rot_out,
+                    int32_t n_prompts, const int32_t *cu_q, const int32_t *cu_ctx, const int32_t *q_pos0,
+                    int32_t rope_mode, void *ws, size_t ws_bytes, void *stream_, const GatheredRows *rows);
+
 }  // namespace api
 }  // namespace ba

@@ -47,6 +47,12 @@ struct ReencParams {
   int32_t max_len;  // longest block in this launch
   int32_t heads_per_thread, n_head_groups;  // how the KV heads are split over workgroups
   int32_t copy_from_layer;  // layers from this one on are copied as they are (a gathered V rides along as a layer)
+  // Gathered contexts whose values stay where they are: row_table[destination token] = where its value row lies, in bytes
+  // (source token * row_bytes); destination tokens between a block's end and the next block's start (table_end
+  // behind the launch's last block) get the block's last row.
+  uint32_t *row_table;
+  uint32_t row_bytes;
+  int32_t table_end;
 };
 
 hipError_t launch_reencode(const ReencParams &p, const ReencBlocks &blocks, const RopeTable &rt,
@@ -277,6 +283,15 @@ struct FinalMeta {
   int32_t tile_start[kFinMaxPrompts + 1];
 };
 
+// Final block over a context whose keys have been gathered into one place (prompt n's from key row ctx0[n] on, a multiple
+// of kTileKeys) and whose value rows are fetched from the cache through a table: byte offset of context token
+// t's row at rows[ctx0[n] + t], entries up to the next multiple of kTileKeys holding some row that exists.
+constexpr int kRowTableTiles = 112;  // context tiles of one split at most: 16 rows of each per copying wave lie in LDS
+struct FinalGatherMeta : FinalMeta {
+  int32_t ctx0[kFinMaxPrompts];
+  const uint32_t *rows;
+};
+
 // Final block over a table of cached blocks (each at the positions it was encoded at).
 template <int NP, int NB>
 struct FinalBlocksMetaT {
@@ -327,6 +342,7 @@ hipError_t launch_attn_prompt_short(const AttnParams &p, const PromptMeta &meta,
 hipError_t launch_attn_final_blocks(const AttnParams &p, const FinalBlocksMeta &meta, hipStream_t stream);
 hipError_t launch_attn_final_blocks(const AttnParams &p, const FinalBlocksMetaSmall &meta, hipStream_t stream);
 hipError_t launch_attn_final(const AttnParams &p, const FinalMeta &meta, hipStream_t stream);
+hipError_t launch_attn_final_gathered(const AttnParams &p, const FinalGatherMeta &meta, hipStream_t stream);
 // Merge the split-KV partials of all p.part_units units into the bf16 output.
 hipError_t launch_combine(const AttnParams &p, hipStream_t stream);
 

@@ -61,6 +61,15 @@ __device__ __forceinline__ void rotate(float &a, float &b, float c, float s) {
   b = nb;
 }
 
+// The block's entries of ReencParams::row_table, by one workgroup.
+template <typename Blocks>
+__device__ __forceinline__ void write_row_table(const ReencParams &p, const Blocks &blocks, int b) {
+  const int len = blocks.len[b], at = blocks.dst_off[b];
+  const int next = b + 1 < blocks.n ? blocks.dst_off[b + 1] : p.table_end;
+  for (int u = threadIdx.x; u < next - at; u += kThreads)
+    p.row_table[at + u] = (uint32_t)(blocks.src_off[b] + min(u, len - 1)) * p.row_bytes;
+}
+
 template <typename T, int D, int LAYOUT, int MODE, int TOK_PER_WG, typename Blocks>
 __global__ __launch_bounds__(kThreads) void reencode_kernel(ReencParams p, Blocks blocks, RopeTable rt) {
   constexpr int VEC = Chunk<T>::VEC;
@@ -139,6 +148,7 @@ __global__ __launch_bounds__(kThreads) void reencode_kernel(ReencParams p, Block
       y.store(d0 + g * p.dst_sh + (CH / 2) * VEC);
     }
   }
+  if (p.row_table && layer == 0 && blockIdx.x == 0) write_row_table(p, blocks, b);
 }
 
 // Fast path: uniform shift (the angle depends on the block only), interleaved pairs (every pair
@@ -180,6 +190,7 @@ __global__ __launch_bounds__(kThreads) void reencode_shift_linear_kernel(ReencPa
     const int64_t L = first + (int64_t)k * kThreads;
     if (L < n_chunks) x[k].store(dst + L * VEC);
   }
+  if (p.row_table && layer == 0 && blockIdx.x == 0) write_row_table(p, blocks, b);
 }
 
 template <typename T, int D, typename Blocks>

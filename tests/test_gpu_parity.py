@@ -887,6 +887,54 @@ def test_final_block_from_block_cache_matches_oracle(ba, name, layout, cached_ro
     assert_reencode_bf16(host_bits(kf_rot), kf_ref, layout, "k_f_rot_out, " + name)
 
 
+GATHER_CASES = [  # (Hq, Hkv, D, tokens of each prompt's cached blocks, query tokens of each prompt)
+    (8, 2, 128, [[20, 60, 33, 1] * 12, [64, 64], [63]], [64, 1, 300]),
+    (4, 4, 64, [[7] * 150, [40, 90] * 9], [5, 130]),
+    (6, 2, 128, [[1], [30, 100, 200] * 20], [400, 9]),
+    (8, 1, 64, [[50] * 200], [1]),
+]
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("case", GATHER_CASES, ids=["three-prompts-d128", "tiny-blocks-d64", "one-token-context", "long-d64"])
+def test_gathered_calls_give_the_bits_of_a_context_gathered_by_hand(ba, case, layout):
+    """Short cached blocks: keys gathered by the call, value rows fetched through its table of where they lie.  The
+    same keys re-encoded into one context by the caller, the values copied there, must give the same bits: contexts
+    that end inside a key tile and at its edge, splits that hold no context tile, value rows of another stride
+    between rows of NaN, whatever the workspace held; several times, as tiles arrive in any order."""
+    torch = torch_mod()
+    hq, hkv, d, prompts, lqs = case
+    rng = np.random.default_rng(len(prompts) * 10 + layout)
+    lens = np.array([n for p in prompts for n in p], dtype=np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    cu_q = np.concatenate([[0], np.cumsum(lqs)]).astype(np.int32)
+    order = rng.permutation(len(lens))
+    off = np.zeros(len(lens), dtype=np.int32)
+    off[order] = np.concatenate([[0], np.cumsum(lens[order])[:-1]])
+    T, tq = int(lens.sum()), int(cu_q[-1])
+    kc, vc = dev_bf16(wl.normal_bf16_bits(1400, (T, hkv, d))), dev_bf16(wl.normal_bf16_bits(1401, (T, hkv, d)))
+    wide = torch.full((T, hkv + 1, d), float("nan"), dtype=torch.bfloat16, device="cuda")  # a row of NaN behind each token's heads
+    wide[:, :hkv] = vc
+    qb, kfb, vfb = gen_qkv(1402, tq, hq, hkv, d)
+    q, kf, vf = dev_bf16(qb), dev_bf16(kfb), dev_bf16(vfb)
+    heads = ba.Heads(hq, hkv, d, 10000.0, rope_layout=layout)
+    dst = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int32)
+    cu_ctx = np.concatenate([[0], np.cumsum(lens)])[cu_blk].astype(np.int32)
+    new0 = dst - np.repeat(cu_ctx[:-1], np.diff(cu_blk))
+    k_ctx, v_ctx = torch.empty_like(kc), torch.empty_like(vc)
+    ba.ba_reencode_positions(heads, kc, k_ctx, off, dst, lens, None, new0, ba.REENC_SHIFT)
+    for a, b, n in zip(off, dst, lens):
+        v_ctx[b:b + n] = vc[a:a + n]
+    want = host_bits(gpu_final(ba, heads, q, k_ctx, v_ctx, kf, vf, cu_q, cu_ctx))
+    need = ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens)
+    for fill in (255, 0, 255, 1):
+        o = torch.full_like(q, float("nan"))
+        ba.ba_final_block_attention_cached(heads, q, kc, wide[:, :hkv], kf, vf, o, None, cu_q, cu_blk, off, lens, None, None, None,
+                                           torch.full((need,), fill, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        assert np.array_equal(host_bits(o), want)
+
+
 def test_final_block_from_block_cache_agrees_with_two_step_path(ba, cached_route):
     """Same inputs through ba_reencode_positions + ba_final_block_attention: the two GPU routes differ
     only by where the extra bf16 rounding falls (re-encoded keys there, re-turned queries here)."""
