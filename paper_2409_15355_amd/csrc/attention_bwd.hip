@@ -4,7 +4,8 @@
 //   delta_r = sum_d dO_rd O_rd,   dV = P^T dO,   dP = dO V^T,   dS = P o (dP - delta),
 //   dq^ = scale * dS k^,          dk^ = scale * dS^T q^.
 // Nothing of the forward pass is kept but O and the rows' log-sum-exps L: P is recomputed as
-// exp(S - L).  Two kernels, so that every sum has one owner and no atomics are needed:
+// exp(S - L).  Two kernels, so that every sum has one owner (or owners that leave partial sums, which the last of
+// them adds up in a fixed order) and no atomics on gradients are needed:
 //   - bwd_dq_kernel: a workgroup owns 128 packed query rows (as the forward kernel for short items
 //     does) and walks the key tiles its rows see; it accumulates dq^.  It rotates its query rows itself and
 //     leaves them in memory for the other kernel, with -L / ln 2 and -delta of every row.
@@ -154,7 +155,8 @@ __device__ __forceinline__ void rotate_back(f32x16_t (&acc)[D / 32], const f32x4
 // row tiles where L2 has let go of them).  350 us on rows that a pre-pass of 125 us had rotated; 386 rotating
 // them itself; 357 with the rows that pass once marked non-temporal (kPast, in calls larger than the cache).  287
 // of it remain with one key tile each.
-template <int D, bool kPast>
+// kShared: the table has blocks whose walk is shared (a kernel of its own, as in the forward pass).
+template <int D, bool kPast, bool kShared>
 __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, PromptMeta meta, BwdParams bp) {
   using G = BGeo<D>;
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
@@ -183,17 +185,18 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   const int Gq = p.group;
   const int n_rows = lq * Gq;
   // a block whose walk is shared (see the forward kernel): which split, of how many
-  int split = 0, n_splits = 1, n_rt = 0;
-  if (b < meta.n_split) {
-    n_rt = (n_rows + kShortTileRows - 1) / kShortTileRows;
-    n_splits = walk_splits((lk - 1) / kBKeys + 1, meta.chunk);
-    split = jt / n_rt;
-    jt -= split * n_rt;
+  int split = 0, n_splits = 1;
+  if constexpr (kShared) {
+    if (b < meta.n_split) {
+      const WalkSplit ws = walk_split_of(n_rows, jt, meta.tile_start[b + 1] - meta.tile_start[b]);
+      split = ws.split, n_splits = ws.n_splits;
+      jt -= split * ws.n_row_tiles;
+    }
   }
   const int row0 = jt * kShortTileRows;
   const int last_row = min(n_rows, row0 + kShortTileRows) - 1;
   TileRange walk = {0, (dq + (int)fast_div((uint32_t)last_row, p.group_div)) / kBKeys + 1};
-  if (n_splits > 1) walk = walk_split_range(walk.end, n_splits, split);
+  if (kShared && n_splits > 1) walk = walk_split_range(walk.end, n_splits, split);
   const int t0 = walk.begin, n_t = walk.end;
   const int wave_row0 = row0 + wave * 32;
   const int wave_last_row = min(n_rows, wave_row0 + 32) - 1;
@@ -455,30 +458,37 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   int ln = lane;
   asm volatile("" : "+v"(ln));
   const int ecol = ln & 31, ehf = ln >> 5;
-  if (n_splits > 1) {
+  if constexpr (kShared) {
     // (a shared walk: the accumulators of all splits add up in their order)
-    const int64_t slot = ((int64_t)(rowtile - split * n_rt) * p.n_kv_heads + kvh) * kSplitWaves + wave;  // of split 0
-    const int64_t step = (int64_t)n_rt * p.n_kv_heads * kSplitWaves;                                     // to the next
-    float *const part_o = (float *)p.part_o;
-    const bool live = wave_row0 < n_rows;
-    if (live) leave_accumulators<D>(part_o, slot + split * step, ln, acc);
-    static_assert(kBWaves * G::TILEB + 16 <= 2 * kBBuf * G::TILEB, "a word behind the output staging");
-    if (!last_of_splits(p.part_idx + (int64_t)(rowtile - split * n_rt) * p.n_kv_heads + kvh, n_splits,
-                        smem + 2 * kBBuf * G::TILEB - 16))
-      return;
-    if (live) {
+    int bs = b;
+    asm volatile("" : "+s"(bs));  // (as in the forward kernel)
+    if (bs < meta.n_split) {
+      const int first = meta.tile_start[bs];
+      const WalkSplit ws = walk_split_of(n_rows, rowtile - first, meta.tile_start[bs + 1] - first);
+      const int tile0 = rowtile - ws.split * ws.n_row_tiles;                                   // of split 0
+      const int64_t slot = ((int64_t)tile0 * p.n_kv_heads + kvh) * kSplitWaves + wave;         // of split 0
+      const int64_t step = (int64_t)ws.n_row_tiles * p.n_kv_heads * kSplitWaves;               // to the next
+      float *const part_o = (float *)p.part_o;
+      const bool live = wave_row0 < n_rows;
+      if (live) leave_accumulators<D>(part_o, slot + ws.split * step, ln, acc);
+      static_assert(kBWaves * G::TILEB + 16 <= 2 * kBBuf * G::TILEB, "a word behind the output staging");
+      if (!last_of_splits(p.part_idx + (int64_t)tile0 * p.n_kv_heads + kvh, ws.n_splits,
+                          smem + 2 * kBBuf * G::TILEB - 16))
+        return;
+      if (live) {
 #pragma unroll
-      for (int dt = 0; dt < G::DT; ++dt)
+        for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
+          for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
 #pragma unroll 1
-      for (int s = 0; s < n_splits; ++s) {
-        u32x4_t w[D / 8];
-        fetch_accumulators<D>(part_o, slot + s * step, ln, w);
+        for (int s = 0; s < ws.n_splits; ++s) {
+          u32x4_t w[D / 8];
+          fetch_accumulators<D>(part_o, slot + s * step, ln, w);
 #pragma unroll
-        for (int k = 0; k < D / 8; ++k)
+          for (int k = 0; k < D / 8; ++k)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) *((float *)&acc[k >> 2] + (k & 3) * 4 + e) += __uint_as_float(w[k][e]);
+            for (int e = 0; e < 4; ++e) *((float *)&acc[k >> 2] + (k & 3) * 4 + e) += __uint_as_float(w[k][e]);
+        }
       }
     }
   }
@@ -534,7 +544,7 @@ struct KvGeo {
   static_assert(kKvRows == kBKeys && kBwdTileKeys == kBWaves / 2 * 32, "a tile of 32 packed query rows, a pair of waves per 32 keys");
 };
 
-template <int D>
+template <int D, bool kShared>
 __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, BwdKvMeta meta, BwdParams bp) {
   using G = BGeo<D>;
   using KG = KvGeo<D>;
@@ -558,7 +568,7 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   const int f_tok0 = meta.fin_start[b], lf = meta.fin_len[b];  // its prompt's last block, if it is a passage
   // a block whose walks are shared: which split of which key tile
   int split = 0, n_kt = 0, jt = keytile - meta.tile_start[b];
-  const bool shared = b < meta.n_split;
+  const bool shared = kShared && b < meta.n_split;
   if (shared) {
     n_kt = (lk + kBwdTileKeys - 1) / kBwdTileKeys;
     split = jt / n_kt;
@@ -845,11 +855,14 @@ hipError_t launch_dkv_t(const AttnParams &p, const BwdKvMeta &meta, const BwdPar
   if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
   constexpr size_t lds = KvGeo<D>::LDS;
   static_assert(lds <= 64 * 1024, "fits the default dynamic LDS limit");
-  hipLaunchKernelGGL((bwd_dkv_kernel<D>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
+  if (meta.n_split > 0)
+    hipLaunchKernelGGL((bwd_dkv_kernel<D, true>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
+  else
+    hipLaunchKernelGGL((bwd_dkv_kernel<D, false>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
   return hipGetLastError();
 }
 
-template <int D>
+template <int D, bool kShared>
 hipError_t launch_dq_t(const AttnParams &p, const PromptMeta &meta, const BwdParams &bp, hipStream_t stream) {
   const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads;
   if (n_wg == 0) return hipSuccess;
@@ -857,9 +870,9 @@ hipError_t launch_dq_t(const AttnParams &p, const PromptMeta &meta, const BwdPar
   constexpr size_t lds = (size_t)2 * kBBuf * BGeo<D>::TILEB;
   static_assert(lds <= 64 * 1024, "fits the default dynamic LDS limit");
   if (p.rows_past_cache)
-    hipLaunchKernelGGL((bwd_dq_kernel<D, true>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
+    hipLaunchKernelGGL((bwd_dq_kernel<D, true, kShared>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
   else
-    hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
+    hipLaunchKernelGGL((bwd_dq_kernel<D, false, kShared>), dim3((unsigned)n_wg), dim3(kBThreads), lds, stream, p, meta, bp);
   return hipGetLastError();
 }
 
@@ -872,8 +885,9 @@ hipError_t launch_bwd_dkv(const AttnParams &p, const BwdKvMeta &meta, const BwdP
 }
 
 hipError_t launch_bwd_dq(const AttnParams &p, const PromptMeta &meta, const BwdParams &bp, hipStream_t stream) {
-  if (p.head_dim == 128) return launch_dq_t<128>(p, meta, bp, stream);
-  if (p.head_dim == 64) return launch_dq_t<64>(p, meta, bp, stream);
+  const bool shared = meta.n_split > 0;
+  if (p.head_dim == 128) return shared ? launch_dq_t<128, true>(p, meta, bp, stream) : launch_dq_t<128, false>(p, meta, bp, stream);
+  if (p.head_dim == 64) return shared ? launch_dq_t<64, true>(p, meta, bp, stream) : launch_dq_t<64, false>(p, meta, bp, stream);
   return hipErrorInvalidValue;
 }
 

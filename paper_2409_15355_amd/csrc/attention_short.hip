@@ -54,12 +54,11 @@ struct SGeo {
   static_assert((size_t)kSWaves * 32 * ROWB + 16 <= LDS, "the output staging must fit the tile buffers, and a word behind it");
 };
 
-
-// (a table without shared walks has none)
-__device__ __forceinline__ int shared_blocks(const EncodeMeta &) { return 0; }
-__device__ __forceinline__ int shared_blocks(const PromptMeta &m) { return m.n_split; }
-__device__ __forceinline__ int shared_chunk(const EncodeMeta &) { return 1; }
-__device__ __forceinline__ int shared_chunk(const PromptMeta &m) { return m.chunk; }
+// A table with shared walks.  A kernel of its own: the code for them, never entered, was 3.5 us of 202 in a launch of
+// 1,134 row tiles of 32 heads of 128, and 0.8 of the 58 us of a small call's two passes.
+struct SharedPromptMeta : PromptMeta {
+  explicit SharedPromptMeta(const PromptMeta &m) : PromptMeta(m) {}
+};
 
 // Meta = EncodeMeta: a block sees its own tokens only (Section 2.1).  Meta = PromptMeta: a block's keys
 // start wherever the table says -- at the block itself for a passage, at the first token of the
@@ -70,7 +69,7 @@ __device__ __forceinline__ int shared_chunk(const PromptMeta &m) { return m.chun
 template <int D, typename Meta, bool kAsCore, bool kPast>
 __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p, Meta meta) {
   using G = SGeo<D>;
-  constexpr bool kPrompt = std::is_same<Meta, PromptMeta>::value;
+  constexpr bool kPrompt = std::is_base_of<PromptMeta, Meta>::value, kShared = std::is_same<Meta, SharedPromptMeta>::value;
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char *smem = (lds_char *)smem_generic;
   // LDS map: buffer b = bytes [2 b TB, 2 (b + 1) TB): its K tile, then its V tile
@@ -112,19 +111,20 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   const int Gq = p.group;
   const int n_rows = lq * Gq;
   // a block whose walk is shared: which split, of how many
-  int split = 0, n_splits = 1, n_rt = 0;
-  if (kPrompt && b < shared_blocks(meta)) {
-    n_rt = (n_rows + kShortTileRows - 1) / kShortTileRows;
-    n_splits = walk_splits((lk - 1) / kSKeys + 1, shared_chunk(meta));
-    split = jt / n_rt;
-    jt -= split * n_rt;
+  int split = 0, n_splits = 1;
+  if constexpr (kShared) {
+    if (b < meta.n_split) {
+      const WalkSplit ws = walk_split_of(n_rows, jt, meta.tile_start[b + 1] - meta.tile_start[b]);
+      split = ws.split, n_splits = ws.n_splits;
+      jt -= split * ws.n_row_tiles;
+    }
   }
   const int row0 = jt * kShortTileRows;
 
   // key tiles of the workgroup (up to its last row's token) and of this wave
   const int last_row = min(n_rows, row0 + kShortTileRows) - 1;
   TileRange walk = {0, (dq + (int)fast_div((uint32_t)last_row, p.group_div)) / kSKeys + 1};
-  if (kPrompt && n_splits > 1) walk = walk_split_range(walk.end, n_splits, split);
+  if (kShared && n_splits > 1) walk = walk_split_range(walk.end, n_splits, split);
   const int t0 = kPrompt ? walk.begin : 0, n_t = walk.end;
   const int wave_row0 = row0 + wave * 32;
   const int wave_last_row = min(n_rows, wave_row0 + 32) - 1;
@@ -457,50 +457,57 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   const int ecol = ln & 31, ehf = ln >> 5;
   lds_char *stage = smem + wave * (32 * G::ROWB);
   float l_tot = l_run + other_half(l_run);
-  if (kPrompt && n_splits > 1) {
+  if constexpr (kShared) {
     // The walk of this row tile is shared: a last block walks its whole prompt, 0.58 us a tile, and a call of a few
     // prompts ends with that chain.  One block of 19 tokens behind 5,000: 157 tiles, 92 us of a launch whose
     // passages take 35.  Leave (accumulators, reference, sum); the last workgroup to do so merges: rows of
     // reference m_i and sum l_i come to sum_i 2^(m_i - m) o_i over sum_i 2^(m_i - m) l_i, m = max m_i.
-    const int64_t slot = ((int64_t)(rowtile - split * n_rt) * p.n_kv_heads + kvh) * kSplitWaves + wave;  // of split 0
-    const int64_t step = (int64_t)n_rt * p.n_kv_heads * kSplitWaves;                                     // to the next
-    float *const part_o = (float *)p.part_o;
-    char *const part_ml = (char *)p.part_ml;
-    const bool live = wave_row0 < n_rows;
-    if (live) {
-      leave_accumulators<D>(part_o, slot + split * step, ln, oacc);
-      if (ehf == 0) {
-        const u32x2_t ml = {__float_as_uint(l_tot > 0.f ? mb : -INFINITY), __float_as_uint(l_tot)};
-        __builtin_amdgcn_raw_buffer_store_b64(ml, shared_buffer(part_ml + (slot + split * step) * 256, 256), ecol * 8, 0, kAgentScope);
+    int bs = b;
+    asm volatile("" : "+s"(bs));  // (its split is looked up anew: held over the loop it costs the loop its scalar registers)
+    if (bs < meta.n_split) {
+      const int first = meta.tile_start[bs];
+      const WalkSplit ws = walk_split_of(n_rows, rowtile - first, meta.tile_start[bs + 1] - first);
+      const int tile0 = rowtile - ws.split * ws.n_row_tiles;                                   // of split 0
+      const int64_t slot = ((int64_t)tile0 * p.n_kv_heads + kvh) * kSplitWaves + wave;         // of split 0
+      const int64_t step = (int64_t)ws.n_row_tiles * p.n_kv_heads * kSplitWaves;               // to the next
+      float *const part_o = (float *)p.part_o;
+      char *const part_ml = (char *)p.part_ml;
+      const bool live = wave_row0 < n_rows;
+      if (live) {
+        leave_accumulators<D>(part_o, slot + ws.split * step, ln, oacc);
+        if (ehf == 0) {
+          const u32x2_t ml = {__float_as_uint(l_tot > 0.f ? mb : -INFINITY), __float_as_uint(l_tot)};
+          __builtin_amdgcn_raw_buffer_store_b64(ml, shared_buffer(part_ml + (slot + ws.split * step) * 256, 256), ecol * 8, 0, kAgentScope);
+        }
       }
-    }
-    if (!last_of_splits(p.part_idx + (int64_t)(rowtile - split * n_rt) * p.n_kv_heads + kvh, n_splits, smem + G::LDS - 16)) return;
-    if (live) {
-      mb = -INFINITY;
-      l_tot = 0.f;
+      if (!last_of_splits(p.part_idx + (int64_t)tile0 * p.n_kv_heads + kvh, ws.n_splits, smem + G::LDS - 16)) return;
+      if (live) {
+        mb = -INFINITY;
+        l_tot = 0.f;
 #pragma unroll
-      for (int dt = 0; dt < G::DT; ++dt)
+        for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[dt][v] = 0.f;
+          for (int v = 0; v < 16; ++v) oacc[dt][v] = 0.f;
 #pragma unroll 1
-      for (int s = 0; s < n_splits; ++s) {
-        u32x4_t w[D / 8];
-        const u32x2_t ml = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(
-            shared_buffer(part_ml + (slot + s * step) * 256, 256), ecol * 8, 0, kAgentScope));
-        fetch_accumulators<D>(part_o, slot + s * step, ln, w);
-        const float ms = __uint_as_float(ml[0]);
-        const float to = fmaxf(mb, ms);
-        const float keep = mb == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mb - to);
-        const float add = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - to);
-        mb = to;
-        l_tot = l_tot * keep + __uint_as_float(ml[1]) * add;
+        for (int s = 0; s < ws.n_splits; ++s) {
+          u32x4_t w[D / 8];
+          const u32x2_t ml = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(
+              shared_buffer(part_ml + (slot + s * step) * 256, 256), ecol * 8, 0, kAgentScope));
+          fetch_accumulators<D>(part_o, slot + s * step, ln, w);
+          const float ms = __uint_as_float(ml[0]);
+          const float to = fmaxf(mb, ms);
+          const float keep = mb == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mb - to);
+          const float add = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - to);
+          mb = to;
+          l_tot = l_tot * keep + __uint_as_float(ml[1]) * add;
 #pragma unroll
-        for (int k = 0; k < D / 8; ++k)
+          for (int k = 0; k < D / 8; ++k)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float &o = *((float *)&oacc[k >> 2] + (k & 3) * 4 + e);
-            o = o * keep + __uint_as_float(w[k][e]) * add;
-          }
+            for (int e = 0; e < 4; ++e) {
+              float &o = *((float *)&oacc[k >> 2] + (k & 3) * 4 + e);
+              o = o * keep + __uint_as_float(w[k][e]) * add;
+            }
+        }
       }
     }
   }
@@ -573,8 +580,10 @@ hipError_t launch_attn_encode_short(const AttnParams &p, const EncodeMeta &meta,
 
 hipError_t launch_attn_prompt_short(const AttnParams &p, const PromptMeta &meta, hipStream_t stream) {
   if (p.n_splits != 1) return hipErrorInvalidValue;
-  if (p.head_dim == 128) return launch_short_t<128, false>(p, meta, stream);
-  if (p.head_dim == 64) return launch_short_t<64, false>(p, meta, stream);
+  const bool shared = meta.n_split > 0;
+  const SharedPromptMeta with(meta);
+  if (p.head_dim == 128) return shared ? launch_short_t<128, false>(p, with, stream) : launch_short_t<128, false>(p, meta, stream);
+  if (p.head_dim == 64) return shared ? launch_short_t<64, false>(p, with, stream) : launch_short_t<64, false>(p, meta, stream);
   return hipErrorInvalidValue;
 }
 

@@ -242,13 +242,13 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
 
   // Blocks go to the kernel longest key range first (see the planner).
   std::vector<ba::PromptBlock> blks = ba::list_prompt_blocks(n_prompts, cu_blk, block_offsets);
-  ba::sort_by_key_range(&blks, shares);
+  ba::sort_by_key_range(&blks, G, heads->n_kv_heads, shares);
   const int n_live = (int)blks.size();
 
   for (int b0 = 0; b0 < n_live; b0 += ba::kEncMaxBlocks) {
     const int n = std::min(ba::kEncMaxBlocks, n_live - b0);
     ba::PromptMeta meta;
-    const int64_t tiles = ba::build_prompt_meta(blks, (size_t)b0, n, G, shares, &meta);
+    const int64_t tiles = ba::build_prompt_meta(blks, (size_t)b0, n, G, heads->n_kv_heads, shares, &meta);
     if (tiles < 0) return fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
     if (tiles == 0) continue;
     ap.total_tiles = (int32_t)tiles;
@@ -422,11 +422,11 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   typedef ba::PromptBlock Blk;
   // dq: query rows own the sums; longest key range first
   std::vector<Blk> by_q = blks;
-  ba::sort_by_key_range(&by_q, shares);
+  ba::sort_by_key_range(&by_q, G, hkv, shares);
   for (size_t b0 = 0; b0 < by_q.size(); b0 += ba::kEncMaxBlocks) {
     const int n = (int)std::min<size_t>(ba::kEncMaxBlocks, by_q.size() - b0);
     ba::PromptMeta meta;
-    const int64_t tiles = ba::build_prompt_meta(by_q, b0, n, G, shares, &meta);
+    const int64_t tiles = ba::build_prompt_meta(by_q, b0, n, G, hkv, shares, &meta);
     if (tiles < 0) return fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
     if (tiles == 0) continue;
     ap.total_tiles = (int32_t)tiles;

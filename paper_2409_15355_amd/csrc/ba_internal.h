@@ -151,14 +151,13 @@ constexpr int kFixedTiles = 4;            // what a workgroup of the main core s
 constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 
 // Whole prompts: last blocks that walk more than kShareAbove key tiles have the walk shared by workgroups of
-// kShareChunk tiles or more: of load / (kShareCus * kShareLoad) where a launch is busy for longer than such a
-// walk anyway.  A shared walk pays for its partial results (some 2 us a split in the workgroup that merges).
-// Forward and backward, us, unshared / shared: 4 over 4 heads of 64, one prompt of 9 x 250-750 tokens: 164 / 73; 8 over 2
-// of 64, four of 18 x 135-400: 294 / 151; 32 over 8 of 128, two of 22 x 37-112: 155 / 121, two of 29 x 88-262: 458 /
-// 368, two of 3 x 134-402 (29 and 41 tiles): 129 / 128; eight of 20 x 100-300 (130 tiles, 85,000 walked in all): not
-// shared (955; 964 with chunks of 110).  Over 18 calls chunks of 12 to 28 tiles differ by less than 3 %.
-constexpr int kShareAbove = 36, kShareChunk = 16;
-constexpr int kShareCus = 256, kShareLoad = 2;
+// kShareChunk tiles or more, as many as come to kSharePairs workgroups for the block.  By the block's own sizes and not
+// by the call's load, so that a prompt's outputs and dq keep their bits in any batch.  Forward and backward, us,
+// unshared / 24 workgroups / 32 / 48: 4 over 4 heads of 64, one prompt of 20 x 161-477 tokens and 41-124 219 / 83 / 78 /
+// 76, eight of 20 x 100-300 and 32-128 224 / 141 / 144 / 150; 8 over 2, two of 6 x 370-1105 215 / 155 / 132 / 128; 32 over
+// 8 of 128, three of 11 x 117-351 and 13-40 252 / 241 / 223 / 225, two of 21 x 134-396 and 31-94 465 / 465 / 368 / 358.  But
+// eight of 20 x 100-300 and 32-128 there, which fill the chip by themselves, 967 / 967 / 972 / 974: hence 24.
+constexpr int kShareAbove = 36, kShareChunk = 16, kSharePairs = 24;
 constexpr size_t kShareMaxBytes = (size_t)256 << 20;
 // ... and the same for the walks of the dk/dv kernel (0.73 us a tile; a key tile's rows are its block's and the last
 // block's).  Forward and backward, us, unshared / shared: 8 over 2 heads of 64, five prompts of 4 x 350-1040 tokens and
@@ -166,7 +165,10 @@ constexpr size_t kShareMaxBytes = (size_t)256 << 20;
 // two of 3 x 134-402: 129 / 105; two of 29 x 88-262: 374 / 371;
 // three of 11 x 117-351 221 / 222 (232 with chunks a third shorter).  From 17 tiles on instead of 22: 4 over 4 of 64, one of
 // 9 x 250-750 73 / 67, but 32 over 8, two of 22 x 37-112 120 / 122 and 16 over 8, four of 4 x 100-298 106 / 108.
-constexpr int kKvShareAbove = 21, kKvShareChunk = 12, kKvShareLoad = 2;
+// In calls whose longest such walk is more than kKvShareLoad of what every one of kShareCus compute units has to do
+// (a call that fills the chip adds up in one order, whatever else is in the batch), in chunks of half of that.
+constexpr int kKvShareAbove = 21, kKvShareChunk = 12, kShareCus = 256;
+constexpr double kKvShareLoad = 0.75;
 
 struct AttnParams {
   const uint16_t *q;
@@ -236,8 +238,9 @@ struct PromptMeta {
   int32_t tile_start[kEncMaxBlocks + 1];  // in row tiles of kShortTileRows rows; INT_MAX beyond [n]
   int32_t kstart[kEncMaxBlocks];          // token offset of the first visible key
   // The first n_split blocks' walks are shared out: a block whose last row walks w key tiles is taken by
-  // walk_splits(w, chunk) workgroups per row tile and KV head (all row tiles of split 0 first, then of split 1 ...)
-  int32_t n_split, chunk;
+  // shared_walk_splits(w, kShareChunk, row tiles x KV heads, kSharePairs) workgroups per row tile and KV head (all row
+  // tiles of split 0 first, then of split 1 ...)
+  int32_t n_split;
 };
 
 // ---------------------------------------------------------------- backward of whole prompts ----

@@ -172,6 +172,17 @@ __device__ __forceinline__ void fetch_accumulators(float *part, int64_t slot, in
   for (int k = 0; k < D / 8; ++k)
     w[k] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(from, lane * 16 + k * 1024, 0, kAgentScope));
 }
+// Which split of a shared walk a row tile of the launch's list is: n_row_tiles of the block, n_splits times over.
+struct WalkSplit {
+  int n_row_tiles, n_splits, split;
+};
+__device__ __forceinline__ WalkSplit walk_split_of(int n_rows, int tile, int n_tiles) {
+  WalkSplit w;
+  w.n_row_tiles = (n_rows + kShortTileRows - 1) / kShortTileRows;
+  w.n_splits = n_tiles / w.n_row_tiles;
+  w.split = tile / w.n_row_tiles;
+  return w;
+}
 // Counts this workgroup in; true (in every wave) if all n are in now.  told: a word of LDS nobody else uses.
 __device__ __forceinline__ bool last_of_splits(int32_t *counter, int n, lds_char *told_at) {
   __attribute__((address_space(3))) volatile int *const told = (__attribute__((address_space(3))) volatile int *)told_at;

@@ -398,47 +398,30 @@ std::vector<PromptBlock> list_prompt_blocks(int32_t n_prompts, const int32_t *cu
 namespace {
 constexpr int kPromptKeys = 32;  // keys per tile of the forward and dq kernels
 int walk_tiles(int64_t keys) { return (int)((keys - 1) / kPromptKeys + 1); }
+int64_t short_row_tiles(int64_t len, int64_t G) { return (len * G + kShortTileRows - 1) / kShortTileRows; }
 // a last block that sees enough of its prompt for more than one workgroup per row tile
-int shared_splits(int64_t ctx, int64_t len, int chunk) {
+int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads) {
   if (ctx <= 0 || len <= 0) return 1;
   const int w = walk_tiles(ctx + len);
-  return w > kShareAbove ? walk_splits(w, chunk) : 1;
+  const int64_t pairs = short_row_tiles(len, G) * n_kv_heads;
+  return w > kShareAbove && pairs <= kSharePairs ? shared_walk_splits(w, kShareChunk, (int)pairs, kSharePairs) : 1;
 }
 }  // namespace
 
 WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
   WalkShares ws;
   const int64_t G = h->n_q_heads / h->n_kv_heads;
-  double load = 0.0;  // tiles walked by all workgroups, and kFixedTiles for each
-  int longest = 0;
-  for (int n = 0; n < n_prompts; ++n) {
-    const int last = cu_blk[n + 1] - 1;
-    for (int b = cu_blk[n]; b <= last; ++b) {
-      const int64_t len = block_offsets[b + 1] - block_offsets[b];
-      if (len == 0) continue;
-      const int64_t n_rt = (len * G + kShortTileRows - 1) / kShortTileRows;
-      const int64_t ctx = b == last ? block_offsets[b] - block_offsets[cu_blk[n]] : 0;
-      const int w = walk_tiles(ctx + len);
-      load += (double)n_rt * (ctx > 0 ? w : 0.5 * (w + 1));
-      load += (double)n_rt * kFixedTiles;
-      if (ctx > 0) longest = std::max(longest, w);
-    }
-  }
-  if (longest <= kShareAbove) return ws;
-  load *= h->n_kv_heads;
-  const int chunk = std::max(kShareChunk, (int)(load / (kShareCus * kShareLoad)));
   for (int n = 0; n < n_prompts; ++n) {
     const int last = cu_blk[n + 1] - 1;
     const int64_t len = block_offsets[last + 1] - block_offsets[last];
-    const int s = shared_splits(block_offsets[last] - block_offsets[cu_blk[n]], len, chunk);
+    const int s = shared_splits(block_offsets[last] - block_offsets[cu_blk[n]], len, G, h->n_kv_heads);
     if (s < 2) continue;
     ++ws.n_split;
-    ws.items += (len * G + kShortTileRows - 1) / kShortTileRows * s;
+    ws.items += short_row_tiles(len, G) * s;
   }
   const size_t slots = (size_t)ws.items * h->n_kv_heads * (kShortTileRows / 32);
   // (more such blocks than one launch lists, or partial results beyond any use: enough to run side by side)
   if (ws.n_split == 0 || ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes) return WalkShares();
-  ws.chunk = chunk;
   ws.part_bytes = slots * 32 * h->head_dim * 4;
   ws.ml_bytes = slots * 256;
   ws.count_bytes = (size_t)ws.items * h->n_kv_heads * 4;
@@ -477,8 +460,9 @@ WalkShares plan_kv_shares(const ba_heads *h, int32_t n_prompts, const int32_t *c
     load += n_kt * ((double)kv_walk(len, fin, G) - 0.5 * (double)len * (double)G / kKvTileRows + kFixedTiles);
     longest = std::max(longest, kv_walk(len, fin, G));
   });
-  if (longest <= kKvShareAbove) return ws;
-  const int chunk = std::max(kKvShareChunk, (int)std::min(1e6, load * h->n_kv_heads / (kShareCus * kKvShareLoad)));
+  load *= h->n_kv_heads / (double)kShareCus;  // ... per compute unit
+  if (longest <= kKvShareAbove || (double)longest < kKvShareLoad * load) return ws;
+  const int chunk = std::max(kKvShareChunk, (int)std::min(1e6, 0.5 * load));
   each([&](int64_t len, int64_t fin) {
     const int s = kv_splits(len, fin, G, chunk);
     if (s < 2) return;
@@ -522,10 +506,10 @@ int64_t build_kv_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, in
   return tiles;
 }
 
-void sort_by_key_range(std::vector<PromptBlock> *blks, const WalkShares &shares) {
+void sort_by_key_range(std::vector<PromptBlock> *blks, int G, int n_kv_heads, const WalkShares &shares) {
   // (a prompt's last block walks the whole prompt, and a launch should not end on a few of those)
   const auto shared = [&](const PromptBlock &b) {
-    return shares.n_split > 0 && shared_splits(b.start - b.kstart, b.len, shares.chunk) > 1;
+    return shares.n_split > 0 && shared_splits(b.start - b.kstart, b.len, G, n_kv_heads) > 1;
   };
   std::stable_sort(blks->begin(), blks->end(), [&](const PromptBlock &a, const PromptBlock &b) {
     const bool sa = shared(a), sb = shared(b);
@@ -534,11 +518,11 @@ void sort_by_key_range(std::vector<PromptBlock> *blks, const WalkShares &shares)
   });
 }
 
-int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, const WalkShares &shares, PromptMeta *meta) {
+int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, int n_kv_heads, const WalkShares &shares,
+                          PromptMeta *meta) {
   memset(meta, 0, sizeof(*meta));
   meta->n = n;
   meta->n_split = b0 == 0 ? shares.n_split : 0;
-  meta->chunk = shares.chunk;
   int64_t tiles = 0;
   for (int i = 0; i < n; ++i) {
     const PromptBlock &b = blks[b0 + i];
@@ -546,8 +530,7 @@ int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n
     meta->len[i] = b.len;
     meta->kstart[i] = b.kstart;
     meta->tile_start[i] = (int32_t)tiles;
-    const int64_t n_rt = ((int64_t)b.len * G + kShortTileRows - 1) / kShortTileRows;
-    tiles += n_rt * (i < meta->n_split ? walk_splits(walk_tiles((int64_t)b.start + b.len - b.kstart), shares.chunk) : 1);
+    tiles += short_row_tiles(b.len, G) * (i < meta->n_split ? shared_splits((int64_t)b.start - b.kstart, b.len, G, n_kv_heads) : 1);
     if (tiles > 0x3fffffff) return -1;
   }
   meta->tile_start[n] = (int32_t)tiles;
@@ -694,13 +677,13 @@ int64_t ba_schedule_prompts(const ba_heads *heads, int32_t n_prompts, const int3
   const int G = heads->n_q_heads / heads->n_kv_heads;
   const ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
   std::vector<ba::PromptBlock> blks = ba::list_prompt_blocks(n_prompts, cu_blk, block_offsets);
-  ba::sort_by_key_range(&blks, shares);
+  ba::sort_by_key_range(&blks, G, heads->n_kv_heads, shares);
   ba::ItemSink sink{items, items ? max_items : 0};
   int launch = 0;
   for (size_t b0 = 0; b0 < blks.size(); b0 += ba::kEncMaxBlocks, ++launch) {
     const int n = (int)std::min<size_t>(ba::kEncMaxBlocks, blks.size() - b0);
     ba::PromptMeta meta;
-    const int64_t tiles = ba::build_prompt_meta(blks, b0, n, G, shares, &meta);
+    const int64_t tiles = ba::build_prompt_meta(blks, b0, n, G, heads->n_kv_heads, shares, &meta);
     if (tiles < 0) return ba::fail(BA_ERR_INVALID_ARG, "too many row tiles in one call");
     for (int64_t tile = 0; tile < tiles; ++tile) {
       const int i = ba::segment_of(meta.tile_start, meta.n, (int)tile);
@@ -709,7 +692,7 @@ int64_t ba_schedule_prompts(const ba_heads *heads, int32_t n_prompts, const int3
       const int n_rows = lq * G;
       if (i < meta.n_split) {
         const int n_rt = (n_rows + ba::kShortTileRows - 1) / ba::kShortTileRows;
-        n_splits = ba::walk_splits(ba::walk_tiles(dq + lq), meta.chunk);
+        n_splits = ba::shared_walk_splits(ba::walk_tiles(dq + lq), ba::kShareChunk, n_rt * heads->n_kv_heads, ba::kSharePairs);
         split = jt / n_rt;
         jt -= split * n_rt;
       }

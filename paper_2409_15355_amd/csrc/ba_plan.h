@@ -109,7 +109,8 @@ struct PromptBlock {
 std::vector<PromptBlock> list_prompt_blocks(int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets);
 // Which last blocks have their walks shared by several workgroups (PromptMeta::n_split), and the memory that takes.
 struct WalkShares {
-  int n_split = 0, chunk = 1;
+  int n_split = 0;
+  int chunk = 1;      // (dk/dv kernel: row tiles per workgroup)
   int64_t items = 0;  // (row tile, split) pairs of those blocks
   size_t part_bytes = 0, ml_bytes = 0, count_bytes = 0;
   size_t total() const { return align256(part_bytes) + align256(ml_bytes) + align256(count_bytes); }
@@ -118,9 +119,10 @@ WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t 
 // The same for the dk/dv kernel (BwdKvMeta::n_split): items are (key tile, split) entries.
 WalkShares plan_kv_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets);
 // ... in the order the forward and dq kernels take them: those of shared walks, then longest key range first
-void sort_by_key_range(std::vector<PromptBlock> *blks, const WalkShares &shares);
+void sort_by_key_range(std::vector<PromptBlock> *blks, int G, int n_kv_heads, const WalkShares &shares);
 // the table of one launch: blocks [b0, b0 + n) of the list.  Returns its row tiles, -1 if too many.
-int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, const WalkShares &shares, PromptMeta *meta);
+int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, int n_kv_heads, const WalkShares &shares,
+                          PromptMeta *meta);
 // ... and the dk/dv kernel's order (shared walks first, then most query rows) and table.  Returns the key tile entries.
 void sort_by_query_rows(std::vector<PromptBlock> *blks, int G, const WalkShares &shares);
 int64_t build_kv_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, int G, const WalkShares &shares, BwdKvMeta *meta);

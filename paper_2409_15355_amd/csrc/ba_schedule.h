@@ -89,9 +89,13 @@ BA_HD TileRange split_tile_range(int n_ctx_tiles, int n_causal_tiles, int n_spli
   return r;
 }
 
-// Whole prompts: workgroups that share the walk of a block whose last row walks `tiles` key tiles, and the
-// tiles of split `split` of a row tile that walks n_t of them.
+// Whole prompts: workgroups that share the walk of a block whose last row walks `tiles` key tiles, with `pairs` row
+// tiles times KV heads, and the tiles of split `split` of a row tile that walks n_t of them.
 BA_HD int walk_splits(int tiles, int chunk) { return (tiles + chunk - 1) / chunk; }
+BA_HD int shared_walk_splits(int tiles, int chunk, int pairs, int most_pairs) {
+  const int by_tiles = walk_splits(tiles, chunk), by_pairs = most_pairs / pairs;
+  return by_pairs < 2 ? 1 : (by_tiles < by_pairs ? by_tiles : by_pairs);
+}
 BA_HD TileRange walk_split_range(int n_t, int n_splits, int split) {
   TileRange r;
   r.begin = (int)((unsigned)n_t * (unsigned)split / (unsigned)n_splits);
