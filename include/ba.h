@@ -316,9 +316,9 @@ size_t ba_final_block_attention_cached_workspace_bytes(const ba_heads *heads, in
  * as local positions plus re-encoding -- and the rotated keys go to k_rot_out if non-null; with
  * BA_ROPE_NONE q and k are used as given.  lse_out (device, nullable): [T][n_q_heads] floats, the
  * natural-log sum of exp(scale * <q^, k^>) over each row's visible keys, as a backward pass needs.
- * Built for training-sized prompts: every row tile walks its key range alone (no KV splits), so a
- * short last block behind tens of thousands of context tokens is better served by
- * ba_final_block_attention.  Any number of query heads per KV head; with fewer than four the workspace
+ * Built for training-sized prompts: at most a few workgroups share the walk of a last block's row
+ * tile (with rope_mode BA_ROPE_APPLY; their partial results lie in ws), so a short last block behind
+ * tens of thousands of context tokens is better served by ba_final_block_attention.  Any number of query heads per KV head; with fewer than four the workspace
  * also has room for padded copies of q and o, which are used only where a block's row offsets (tokens
  * x strides) do not fit 32 bits: such a call runs as a group of four with zero phantom heads, at up to
  * four times the attention work.
@@ -345,8 +345,8 @@ size_t ba_block_attention_prompts_workspace_bytes(const ba_heads *heads, int32_t
  *
  * q, k, v, cu_blk, block_offsets: as given to the forward call.  o [T, n_q_heads, D] and lse
  * (device, [T][n_q_heads] floats): its outputs.  d_out [T, n_q_heads, D]; dq_out like q, dk_out and
- * dv_out like k and v; all bf16, fully overwritten.  Deterministic: every sum has one owner, no
- * atomics.  Fewer than four query heads per KV head at strides beyond 32-bit row offsets: run as
+ * dv_out like k and v; all bf16, fully overwritten.  Deterministic: every sum has one owner, or
+ * parts in ws that one workgroup adds up in a fixed order.  Fewer than four query heads per KV head at strides beyond 32-bit row offsets: run as
  * groups of four, as in the forward call (phantom heads have a zero output gradient and add nothing
  * to dk and dv).  ws: 256-byte aligned, at least
  * ba_block_attention_prompts_backward_workspace_bytes() bytes.
