@@ -318,11 +318,15 @@ size_t ba_final_block_attention_cached_workspace_bytes(const ba_heads *heads, in
  * natural-log sum of exp(scale * <q^, k^>) over each row's visible keys, as a backward pass needs.
  * Built for training-sized prompts: at most a few workgroups share the walk of a last block's row
  * tile (with rope_mode BA_ROPE_APPLY; their partial results lie in ws), so a short last block behind
- * tens of thousands of context tokens is better served by ba_final_block_attention.  Any number of query heads per KV head; with fewer than four the workspace
- * also has room for padded copies of q and o, which are used only where a block's row offsets (tokens
- * x strides) do not fit 32 bits: such a call runs as a group of four with zero phantom heads, at up to
- * four times the attention work.
- * ws: 256-byte aligned, at least ba_block_attention_prompts_workspace_bytes() bytes.
+ * tens of thousands of context tokens is better served by ba_final_block_attention.  Any number of
+ * query heads per KV head; with fewer than four the workspace also has room for padded copies of q
+ * and o, which are used only where a block's row offsets (tokens x strides) do not fit 32 bits: such
+ * a call runs as a group of four with zero phantom heads, at up to four times the attention work.
+ * ws: 256-byte aligned.  With ba_block_attention_prompts_workspace_bytes() bytes every walk that is
+ * worth it is shared.  Partial results are optional: without room for them the walks are not shared,
+ * which changes the order of their sums and nothing else.  What a call cannot do without grows with
+ * its tokens alone: a workspace for a call of at least as many tokens (same heads, rope_mode and
+ * presence of k_rot_out) is always enough, although the query may name a larger size for a smaller call.
  */
 int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k,
                                    const ba_tensor *v, const ba_tensor *o_out,
@@ -346,10 +350,15 @@ size_t ba_block_attention_prompts_workspace_bytes(const ba_heads *heads, int32_t
  * q, k, v, cu_blk, block_offsets: as given to the forward call.  o [T, n_q_heads, D] and lse
  * (device, [T][n_q_heads] floats): its outputs.  d_out [T, n_q_heads, D]; dq_out like q, dk_out and
  * dv_out like k and v; all bf16, fully overwritten.  Deterministic: every sum has one owner, or
- * parts in ws that one workgroup adds up in a fixed order.  Fewer than four query heads per KV head at strides beyond 32-bit row offsets: run as
- * groups of four, as in the forward call (phantom heads have a zero output gradient and add nothing
- * to dk and dv).  ws: 256-byte aligned, at least
- * ba_block_attention_prompts_backward_workspace_bytes() bytes.
+ * parts in ws that one workgroup adds up in a fixed order.  Fewer than four query heads per KV head
+ * at strides beyond 32-bit row offsets: run as groups of four, as in the forward call (phantom heads
+ * have a zero output gradient and add nothing to dk and dv).
+ * ws: 256-byte aligned.  With ba_block_attention_prompts_backward_workspace_bytes() bytes every walk
+ * that is worth it is shared; as in the forward call the partial results of shared walks are optional
+ * and a workspace for a call of at least as many tokens is always enough.  They can be most of the
+ * size the query names: a call of few prompts, which leaves compute units idle, cuts the walks of its
+ * key tiles into the more parts (32 over 8 heads of 128, ten blocks of 200 tokens and one of 64: 82 MB
+ * for one prompt, 22 of them needed; 43 for two, all needed), up to 256 MB.
  */
 int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tensor *q,
                                             const ba_tensor *k, const ba_tensor *v,

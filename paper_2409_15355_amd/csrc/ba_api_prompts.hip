@@ -62,6 +62,9 @@ int32_t move_heads(const ba_heads *h, const ba_tensor *real, void *padded, int64
   return BA_OK;
 }
 
+// rows of (log-sum-exp, delta) per token and KV head in the backward pass's workspace
+int32_t ld_group(int32_t group) { return (group + 3) & ~3; }
+
 // Memory of the shared walks (plan_walk_shares); for the padded route what its groups of four want, if that is more.
 size_t shares_bytes(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
   size_t bytes = ba::plan_walk_shares(h, n_prompts, cu_blk, block_offsets).total();
@@ -86,15 +89,34 @@ size_t bwd_shares_bytes(const ba_heads *h, int32_t n_prompts, const int32_t *cu_
   }
   return bytes;
 }
+// Bytes a call does not run without: they grow with its tokens and nothing else, so a workspace that was large enough
+// for one call is large enough for every call of no more tokens.  What the queries return beyond them is the partial results of
+// shared walks, which follow other rules (a call that leaves the chip idle has more of them): optional.
+size_t least_bytes(const ba_heads *h, size_t T, int32_t rope_mode, bool have_k_rot_out) {
+  size_t bytes = 0;
+  if (h->n_q_heads / h->n_kv_heads < kPadGroup)  // padded q and o, padded log-sum-exps (see head_pad.hip)
+    bytes = 2 * padded_rows_bytes(h, T) + padded_lse_bytes(h, T);
+  if (rope_mode != BA_ROPE_APPLY) return bytes;
+  if (!have_k_rot_out) bytes += align256(T * h->n_kv_heads * h->head_dim * 2);  // rotated K
+  return bytes + align256(T * h->head_dim * 4);                                 // scale * (cos, sin) per token and pair
+}
+size_t bwd_least_bytes(const ba_heads *h, size_t T) {
+  const size_t D = h->head_dim, hkv = h->n_kv_heads;
+  size_t hq = h->n_q_heads, pad_bytes = 0;
+  if (hq / hkv < (size_t)kPadGroup) {  // padded q, o, d_out and dq, padded log-sum-exps; the rest for groups of four
+    pad_bytes = 4 * padded_rows_bytes(h, T) + padded_lse_bytes(h, T);
+    hq = hkv * kPadGroup;
+  }
+  // rotated scaled q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row
+  return pad_bytes + align256(T * hq * D * 2) + align256(T * hkv * D * 2) + align256(T * D * 4) +
+         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8 + 16);
+}
 // Where a launch's shared walks leave their partial results, from wsp on.
 void place_shares(const ba::WalkShares &shares, char *wsp, ba::AttnParams *ap) {
   ap->part_o = (uint16_t *)wsp;
   ap->part_ml = (float *)(wsp + align256(shares.part_bytes));
   ap->part_idx = (int32_t *)(wsp + align256(shares.part_bytes) + align256(shares.ml_bytes));
 }
-
-// rows of (log-sum-exp, delta) per token and KV head in the backward pass's workspace
-int32_t ld_group(int32_t group) { return (group + 3) & ~3; }
 
 }  // namespace
 
@@ -105,13 +127,8 @@ size_t ba_block_attention_prompts_workspace_bytes(const ba_heads *heads, int32_t
                                                   int32_t have_k_rot_out) {
   if (check_heads(heads, true) != BA_OK || check_prompt_blocks(n_prompts, cu_blk, block_offsets) != BA_OK) return 0;
   const size_t T = (size_t)block_offsets[cu_blk[n_prompts]];
-  size_t pad_bytes = 0;
-  if (heads->n_q_heads / heads->n_kv_heads < kPadGroup)  // padded q and o, padded log-sum-exps (see head_pad.hip)
-    pad_bytes = 2 * padded_rows_bytes(heads, T) + padded_lse_bytes(heads, T);
-  if (rope_mode != BA_ROPE_APPLY) return pad_bytes;
-  const size_t k_bytes = have_k_rot_out ? 0 : align256(T * heads->n_kv_heads * heads->head_dim * 2);
-  // rotated K; scale * (cos, sin) per token and pair; partial results of shared walks
-  return pad_bytes + k_bytes + align256(T * heads->head_dim * 4) + shares_bytes(heads, n_prompts, cu_blk, block_offsets);
+  const size_t least = least_bytes(heads, T, rope_mode, have_k_rot_out != 0);
+  return rope_mode == BA_ROPE_APPLY ? least + shares_bytes(heads, n_prompts, cu_blk, block_offsets) : least;
 }
 
 int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k, const ba_tensor *v,
@@ -144,8 +161,7 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
   const int64_t widest = std::max(std::max(q->stride_tok, o_out->stride_tok),
                                   (int64_t)G * std::max(q->stride_head, o_out->stride_head));
   const bool fits32 = (max_len + 1) * widest < 0x40000000 && max_len * G <= 0x3fffffff;
-  const size_t need =
-      ba_block_attention_prompts_workspace_bytes(heads, n_prompts, cu_blk, block_offsets, rope_mode, k_rot_out != nullptr);
+  const size_t need = least_bytes(heads, (size_t)T, rope_mode, k_rot_out != nullptr);
   if (G < kPadGroup && (!ws || ws_bytes < need || ((uintptr_t)ws & 255)))
     return fail(BA_ERR_WORKSPACE, "whole prompts: 256-byte aligned workspace of %zu bytes needed, %zu given", need, ws_bytes);
   if (G < kPadGroup && !fits32) {
@@ -197,6 +213,7 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
     q_table = (float *)wsp;
     wsp += align256((size_t)T * D * 4);
     shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
+    if ((size_t)(wsp - (char *)ws) + shares.total() > ws_bytes) shares = ba::WalkShares();
     place_shares(shares, wsp, &ap);
     // positions count from each prompt's first token: one segment per prompt
     std::vector<int32_t> starts(n_prompts + 1);
@@ -268,16 +285,7 @@ size_t ba_block_attention_prompts_backward_workspace_bytes(const ba_heads *heads
                                                            const int32_t *cu_blk, const int32_t *block_offsets) {
   if (check_heads(heads, true) != BA_OK || check_prompt_blocks(n_prompts, cu_blk, block_offsets) != BA_OK) return 0;
   const size_t T = (size_t)block_offsets[cu_blk[n_prompts]];
-  const size_t D = heads->head_dim, hkv = heads->n_kv_heads;
-  size_t hq = heads->n_q_heads, pad_bytes = 0;
-  if (hq / hkv < (size_t)kPadGroup) {  // padded q, o, d_out and dq, padded log-sum-exps; the rest for groups of four
-    pad_bytes = 4 * padded_rows_bytes(heads, T) + padded_lse_bytes(heads, T);
-    hq = hkv * kPadGroup;
-  }
-  // rotated scaled q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row
-  // ... and the partial results of shared walks
-  return pad_bytes + align256(T * hq * D * 2) + align256(T * hkv * D * 2) + align256(T * D * 4) +
-         align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8 + 16) + bwd_shares_bytes(heads, n_prompts, cu_blk, block_offsets);
+  return bwd_least_bytes(heads, T) + bwd_shares_bytes(heads, n_prompts, cu_blk, block_offsets);
 }
 
 int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k,
@@ -309,7 +317,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   const int64_t widest =
       std::max(std::max((int64_t)hq * D, std::max(std::max(d_out->stride_tok, o->stride_tok), dq_out->stride_tok)),
                (int64_t)G * std::max((int64_t)D, std::max(std::max(d_out->stride_head, o->stride_head), dq_out->stride_head)));
-  const size_t need = ba_block_attention_prompts_backward_workspace_bytes(heads, n_prompts, cu_blk, block_offsets);
+  const size_t need = bwd_least_bytes(heads, (size_t)T);
   if (!ws || ws_bytes < need || ((uintptr_t)ws & 255))
     return fail(BA_ERR_WORKSPACE, "whole prompts, backward: 256-byte aligned workspace of %zu bytes needed, %zu given",
                 need, ws_bytes);
@@ -355,10 +363,14 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   wsp += align256((size_t)T * D * 4);
   float *ld = (float *)wsp;
   wsp += align256((size_t)T * hkv * ld_group(G) * 8 + 16);
-  const ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
+  // (what the workspace has room for: the dk/dv kernel's partial results are the larger ones and go first)
+  const size_t room = ws_bytes - (size_t)(wsp - (char *)ws);
+  ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
+  ba::WalkShares kv_shares = ba::plan_kv_shares(heads, n_prompts, cu_blk, block_offsets);
+  if (bwd_shares_bytes(shares, kv_shares) > room) kv_shares = ba::WalkShares();
+  if (bwd_shares_bytes(shares, kv_shares) > room) shares = ba::WalkShares();
   ba::AttnParams ap;
   memset(&ap, 0, sizeof(ap));
-  const ba::WalkShares kv_shares = ba::plan_kv_shares(heads, n_prompts, cu_blk, block_offsets);
   ap.part_o = (uint16_t *)wsp;
   ap.part_idx = (int32_t *)(wsp + align256(std::max(shares.part_bytes, kv_shares.part_bytes)));
 

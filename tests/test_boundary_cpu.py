@@ -233,6 +233,41 @@ def test_whole_prompts_backward_rejects_bad_arguments_and_sizes_workspace(lib):
     assert call(h, [0, 2], [0, 0, 0]) == 0                    # no tokens: legal no-op
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 2, 64), (4, 4, 64)])
+def test_a_workspace_for_a_batch_of_prompts_is_enough_for_every_smaller_call(lib, hq, hkv, d):
+    """A trainer sizes one buffer for its largest step: a call of no more tokens must not ask for more, however many
+    partial results of shared walks its query would like (a call of one prompt more than one of two)."""
+    h = ba.Heads(hq, hkv, d, 500000.0)
+    t = fake()
+    i32 = lambda x: np.asarray(x, dtype=np.int32)
+    r, lse = ctypes.byref(t), ctypes.c_void_p(256)
+    p = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+
+    def needed(backward, cb, of):  # what the refusal of a call without a workspace names
+        if backward:
+            rc = lib.ba_block_attention_prompts_backward(ctypes.byref(h.c), r, r, r, r, lse, r, r, r, r, len(cb) - 1, p(cb),
+                                                         p(of), None, 0, None)
+        else:
+            rc = lib.ba_block_attention_prompts(ctypes.byref(h.c), r, r, r, r, None, lse, len(cb) - 1, p(cb), p(of),
+                                                ba.ROPE_APPLY, None, 0, None)
+        assert rc == -4
+        return int(re.search(r"workspace of (\d+) bytes needed", lib.ba_last_error().decode()).group(1))
+
+    for prompt in ([200] * 10 + [64], [1300, 30], [5000, 1], [6000], [40, 900, 8], [300] * 3 + [20]):
+        for n_prompts in (1, 2, 3, 8):
+            lens = prompt * n_prompts
+            of = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+            cb = (np.arange(n_prompts + 1) * len(prompt)).astype(np.int32)
+            sized = [ba.ba_block_attention_prompts_workspace_bytes(h, cb, of),
+                     ba.ba_block_attention_prompts_backward_workspace_bytes(h, cb, of)]
+            smaller = [(cb[:n + 1], of[:cb[n] + 1]) for n in range(1, n_prompts + 1)]
+            T = int(of[-1])  # ... and other cuts of as many tokens: one block, one long and one short
+            smaller += [(i32([0, 1]), i32([0, T])), (i32([0, 2]), i32([0, T - 1, T])), (i32([0, 2]), i32([0, T // 2, T]))]
+            for cb1, of1 in smaller:
+                for backward in (0, 1):
+                    assert needed(backward, cb1, of1) <= sized[backward], (prompt, n_prompts, of1[-1], backward)
+
+
 def test_header_is_plain_c(tmp_path):
     """include/ba.h is the boundary of a C-ABI library: a C99 compiler takes it as it is, with
     warnings as errors, and the structs it declares have the layout the Python face assumes."""

@@ -1344,6 +1344,67 @@ def test_whole_prompts_with_shared_walks_match_the_definition(ba, case):
             assert_grad_close(f(got[t0:t1]), ref, size, f"{name} {what}, prompt {n}")
 
 
+@pytest.mark.parametrize("case", [SHARED_CASES[0], SHARED_CASES[2]], ids=["group1-d64", "group4-d128"])
+def test_whole_prompts_in_a_workspace_without_room_for_partial_results(ba, case):
+    """The walks of a call that could share them, in workspaces with room for none of the partial results and, backward,
+    for those of the dq kernel only: accepted, right, and nothing written past the size given."""
+    import re
+    torch = torch_mod()
+    name, hq, hkv, d, prompts = case
+    lens = [l for p in prompts for l in p]
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    T = int(offs[-1])
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    qb, kb, vb = gen_qkv(760 + len(name), T, hq, hkv, d)
+    dob = wl.normal_bf16_bits(763 + len(name), (T, hq, d))
+    q, k, v, do = dev_bf16(qb), dev_bf16(kb), dev_bf16(vb), dev_bf16(dob)
+
+    def least(call):  # what the refusal of a call with hardly any workspace names
+        with pytest.raises(ba.BaError) as e:
+            call(torch.empty(256, dtype=torch.uint8, device="cuda"))
+        return int(re.search(r"workspace of (\d+) bytes needed", str(e.value)).group(1))
+
+    def guarded(n):
+        big = torch.full((n + 4096,), 171, dtype=torch.uint8, device="cuda")
+        return big, big[:n]
+
+    o, lse = torch.full_like(q, float("nan")), torch.full((T, hq), float("nan"), device="cuda")
+    forward = lambda ws: ba.ba_block_attention_prompts(heads, q, k, v, o, None, lse, cu_blk, offs, 1, ws)
+    full_f = ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False)
+    full_b = ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs)
+    least_f = least(forward)
+    assert least_f < full_f
+    big, ws = guarded(least_f)
+    forward(ws)
+    torch.cuda.synchronize()
+    assert bool((big[least_f:] == 171).all())
+    grads = [torch.full_like(x, float("nan")) for x in (q, k, v)]
+    backward = lambda ws: ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, *grads, cu_blk, offs, ws)
+    least_b = least(backward)
+    sizes = [least_b, least_b + full_f - least_f]
+    assert sizes[1] < full_b
+    f = oracle.bf16_bits_to_f64
+    th = oracle.theta(10000.0, d)
+    refs = []
+    for n in range(len(prompts)):
+        t0, t1 = int(offs[cu_blk[n]]), int(offs[cu_blk[n + 1]])
+        po = offs[cu_blk[n]:cu_blk[n + 1] + 1] - t0
+        ro = oracle.masked_attention_bruteforce(f(qb[t0:t1]), f(kb[t0:t1]), f(vb[t0:t1]), po, th)
+        assert_attention_close(host_f64(o)[t0:t1], ro, f"{name} o, prompt {n}")
+        refs.append((t0, t1, oracle_grads(f(qb[t0:t1]), f(kb[t0:t1]), f(vb[t0:t1]), f(dob[t0:t1]), po, th)))
+    for size in sizes:
+        for g in grads:
+            g.fill_(float("nan"))
+        big, ws = guarded(size)
+        backward(ws)
+        torch.cuda.synchronize()
+        assert bool((big[size:] == 171).all())
+        for t0, t1, (r, a) in refs:
+            for got, ref, span, what in zip(grads, r, a, ("dq", "dk", "dv")):
+                assert_grad_close(host_f64(got)[t0:t1], ref, span, f"{name} {what}, workspace {size}")
+
+
 def test_whole_prompts_forward_and_backward_on_strided_views(ba):
     """q, k, v as views into one fused [T, Hq + 2 Hkv, D] projection buffer, the gradients written
     into views of a buffer of the same shape, o and d_out with padded head strides: every tensor of
