@@ -151,13 +151,20 @@ constexpr int kFixedTiles = 4;            // what a workgroup of the main core s
 constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 
 // Whole prompts: last blocks that walk more than kShareAbove key tiles have the walk shared by workgroups of
-// kShareChunk tiles or more, as many as come to kSharePairs workgroups for the block.  By the block's own sizes and not
-// by the call's load, so that a prompt's outputs and dq keep their bits in any batch.  Forward and backward, us,
+// kShareChunk tiles or more, as many as come to kSharePairs workgroups for the block.  Forward and backward, us,
 // unshared / 24 workgroups / 32 / 48: 4 over 4 heads of 64, one prompt of 20 x 161-477 tokens and 41-124 219 / 83 / 78 /
 // 76, eight of 20 x 100-300 and 32-128 224 / 141 / 144 / 150; 8 over 2, two of 6 x 370-1105 215 / 155 / 132 / 128; 32 over
 // 8 of 128, three of 11 x 117-351 and 13-40 252 / 241 / 223 / 225, two of 21 x 134-396 and 31-94 465 / 465 / 368 / 358.  But
 // eight of 20 x 100-300 and 32-128 there, which fill the chip by themselves, 967 / 967 / 972 / 974: hence 24.
+// Into how many parts a walk is cut follows from the block's own sizes; whether any is cut, from the call: only if
+// the longest of them is kShareLoad or more of what each compute unit has to do.  A launch that fills the chip hides a long walk
+// and pays for cutting it (each part loads and turns its query rows again, and K and V are read in a burst): 64
+// prompts of 6 x 200 + 20 tokens, 32 over 8 heads of 128, forward kernel 280 -> 316 us, of that 20 without any exchange
+// of partial results.  110 calls of 2 to 50 prompts, walk / load and time shared / unshared: 0.26-0.57 0.95-1.05, in the
+// mean 1.00; 0.62 1.007, 0.63 0.996 and 0.95, 0.66 1.005, 0.69 0.99, 0.70 1.00 and 1.03, 0.71 0.99, 0.72 0.86, 0.73 0.87,
+// 0.74 0.83, 0.75 0.92 and 0.86; beyond, 0.80 in the mean of 69, two of them slower (1.01, 1.07).
 constexpr int kShareAbove = 36, kShareChunk = 16, kSharePairs = 24;
+constexpr double kShareLoad = 0.65;
 constexpr size_t kShareMaxBytes = (size_t)256 << 20;
 // ... and the same for the walks of the dk/dv kernel (0.73 us a tile; a key tile's rows are its block's and the last
 // block's).  Forward and backward, us, unshared / shared: 8 over 2 heads of 64, five prompts of 4 x 350-1040 tokens and

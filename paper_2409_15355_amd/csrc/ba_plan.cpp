@@ -411,17 +411,28 @@ int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads) {
 WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
   WalkShares ws;
   const int64_t G = h->n_q_heads / h->n_kv_heads;
+  double load = 0.0;  // of the launch, in key tiles
+  int longest = 0;
+  const auto add = [&](int64_t ctx, int64_t len) {
+    load += (double)short_row_tiles(len, G) * (((double)ctx + 0.5 * (double)len) / kPromptKeys + 0.5 + kFixedTiles);
+  };
   for (int n = 0; n < n_prompts; ++n) {
     const int last = cu_blk[n + 1] - 1;
-    const int64_t len = block_offsets[last + 1] - block_offsets[last];
-    const int s = shared_splits(block_offsets[last] - block_offsets[cu_blk[n]], len, G, h->n_kv_heads);
+    for (int b = cu_blk[n]; b < last; ++b) add(0, block_offsets[b + 1] - block_offsets[b]);
+    const int64_t len = block_offsets[last + 1] - block_offsets[last], ctx = block_offsets[last] - block_offsets[cu_blk[n]];
+    add(ctx, len);
+    const int s = shared_splits(ctx, len, G, h->n_kv_heads);
     if (s < 2) continue;
     ++ws.n_split;
     ws.items += short_row_tiles(len, G) * s;
+    longest = std::max(longest, walk_tiles(ctx + len));
   }
+  load *= h->n_kv_heads / (double)kShareCus;  // ... per compute unit
   const size_t slots = (size_t)ws.items * h->n_kv_heads * (kShortTileRows / 32);
-  // (more such blocks than one launch lists, or partial results beyond any use: enough to run side by side)
-  if (ws.n_split == 0 || ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes) return WalkShares();
+  // (More shared blocks than one launch lists, or more bytes, would take over 170 prompts, whose load is far beyond the
+  // line; the tables rely on it.)
+  if (ws.n_split == 0 || longest < kShareLoad * load || ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes)
+    return WalkShares();
   ws.part_bytes = slots * 32 * h->head_dim * 4;
   ws.ml_bytes = slots * 256;
   ws.count_bytes = (size_t)ws.items * h->n_kv_heads * 4;

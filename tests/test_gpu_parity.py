@@ -1344,6 +1344,41 @@ def test_whole_prompts_with_shared_walks_match_the_definition(ba, case):
             assert_grad_close(f(got[t0:t1]), ref, size, f"{name} {what}, prompt {n}")
 
 
+def test_a_prompt_with_a_shared_walk_gives_the_same_bits_in_a_batch(ba):
+    """The parts of a walk follow from its own block: a prompt alone, and the same prompt between others with and
+    without shared walks, in a call that shares walks too."""
+    torch = torch_mod()
+    hq, hkv, d = 8, 2, 64
+    prompts = [[800, 420, 30], [64, 9], [30, 1300, 33], [1100, 300, 300], [1280, 16]]
+    lens = [l for p in prompts for l in p]
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    full = [torch.randn((int(offs[-1]), h, d), generator=gen, device="cuda").to(torch.bfloat16) for h in (hq, hkv, hkv, hq)]
+
+    def run(offs, cu_blk, t0, t1):
+        q, k, v, do = (x[t0:t1] for x in full)
+        o, lse, dq = torch.empty_like(q), torch.empty(q.shape[:2], device="cuda"), torch.empty_like(q)
+        scratch = lambda n: torch.empty(n, dtype=torch.uint8, device="cuda")
+        ba.ba_block_attention_prompts(heads, q, k, v, o, None, lse, cu_blk, offs, 1,
+                                      scratch(ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False)))
+        ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, torch.empty_like(k), torch.empty_like(v), cu_blk, offs,
+                                               scratch(ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs)))
+        return o, lse, dq
+
+    whole = run(offs, cu_blk, 0, int(offs[-1]))
+    for n, p in enumerate(prompts):
+        t0, t1 = int(offs[cu_blk[n]]), int(offs[cu_blk[n + 1]])
+        part = offs[cu_blk[n]:cu_blk[n + 1] + 1] - t0
+        alone = np.array([0, len(p)], dtype=np.int32)
+        splits = [max(w.n_splits for w in ba.ba_schedule_prompts(heads, c, o) if w.problem == i)
+                  for c, o, i in ((cu_blk, offs, n), (alone, part, 0))]
+        assert splits[0] == splits[1] and (splits[0] > 1) == (n in (0, 2, 4))
+        for a, b in zip(whole, run(part, alone, t0, t1)):
+            assert torch.equal(a[t0:t1], b), n
+
+
 @pytest.mark.parametrize("case", [SHARED_CASES[0], SHARED_CASES[2]], ids=["group1-d64", "group4-d128"])
 def test_whole_prompts_in_a_workspace_without_room_for_partial_results(ba, case):
     """The walks of a call that could share them, in workspaces with room for none of the partial results and, backward,

@@ -227,6 +227,29 @@ def test_shared_walks_of_whole_prompts_cover_the_mask_once(hq, hkv, d):
     assert 1 in seen and max(seen) >= (4 if hq <= 6 else 2)
 
 
+@pytest.mark.parametrize("hq,hkv,d,prompt,below,above", [(32, 8, 128, [200] * 6 + [20], 5, 6), (16, 8, 128, [200] * 20 + [64], 8, 9),
+                                                         (4, 4, 64, [200] * 6 + [20], 24, 32)])
+def test_walks_are_shared_only_where_the_call_leaves_the_chip_idle(hq, hkv, d, prompt, below, above):
+    """The longest shared walk against 0.65 of what every compute unit has to do: one more prompt than the line allows
+    and no walk of the call is shared.  Into how many parts a walk is cut does not depend on the batch."""
+    h = ba.Heads(hq, hkv, d, 10000.0)
+    G = hq // hkv
+
+    def splits(n_prompts):
+        offs = np.concatenate([[0], np.cumsum(prompt * n_prompts)])
+        cu_blk = np.arange(n_prompts + 1) * len(prompt)
+        return {w.n_splits for w in ba.ba_schedule_prompts(h, cu_blk, offs) if w.first_token == offs[cu_blk[w.problem + 1] - 1]}
+
+    def load(n_prompts):  # key tiles of 32 per compute unit, four for what a workgroup does besides
+        ctx = sum(prompt[:-1])
+        tiles = [-(-n * G // 128) * (0.5 * n / 32 + 4.5) for n in prompt[:-1]] + [-(-prompt[-1] * G // 128) * ((ctx + 0.5 * prompt[-1]) / 32 + 4.5)]
+        return n_prompts * sum(tiles) * hkv / 256
+
+    walk = (sum(prompt) - 1) // 32 + 1
+    assert splits(1) == splits(below) == {3} and walk >= 0.65 * load(below)
+    assert splits(above) == splits(64) == {1} and walk < 0.65 * load(above)
+
+
 def test_split_range_arithmetic_partitions_every_walk():
     """split_tile_range through the final-block query: over split counts of 1 to 32 (eight KV heads, by varying the
     compute-unit count; more splits: below), the splits of a row tile partition its walk."""
