@@ -110,11 +110,13 @@ float scale_log2e(const ba_heads *h) {
 
 
 // Run the rotation kernel over a list of blocks, a launch per table-full of them.
-template <typename Blocks>
-static int32_t run_reencode_t(ba::ReencParams p, const ba::RopeTable &rt, int n_blocks, const int32_t *src_off,
+template <typename Blocks, typename Params>
+static int32_t run_reencode_t(Params p, const ba::RopeTable &rt, int n_blocks, const int32_t *src_off,
                        const int32_t *dst_off, const int32_t *len, const int32_t *pos_old,
                        const int32_t *pos_new, hipStream_t stream) {
-  const int32_t table_end = p.table_end;
+  constexpr bool kRows = std::is_same<Params, ba::ReencRowsParams>::value;
+  int32_t table_end = 0;
+  if constexpr (kRows) table_end = p.table_end;
   std::vector<Blocks> tab(1);  // (the large table is too big for the stack of a small thread)
   Blocks &blk = tab[0];
   for (int b0 = 0; b0 < n_blocks; b0 += Blocks::kBlocks) {
@@ -134,7 +136,7 @@ static int32_t run_reencode_t(ba::ReencParams p, const ba::RopeTable &rt, int n_
     }
     if (!filled) continue;
     blk.n = filled;
-    if (p.row_table) p.table_end = b0 + n < n_blocks ? dst_off[b0 + n] : table_end;
+    if constexpr (kRows) p.table_end = b0 + n < n_blocks ? dst_off[b0 + n] : table_end;
     p.max_len = max_len;
     // few tokens: one head per thread (more workgroups, shorter dependent chains);
     // many tokens: all heads in one thread (sin/cos computed once per token)
@@ -153,13 +155,18 @@ static int32_t run_reencode_t(ba::ReencParams p, const ba::RopeTable &rt, int n_
   return BA_OK;
 }
 
-int32_t run_reencode(ba::ReencParams p, const ba::RopeTable &rt, int n_blocks, const int32_t *src_off,
+template <typename Params>
+int32_t run_reencode(Params p, const ba::RopeTable &rt, int n_blocks, const int32_t *src_off,
                      const int32_t *dst_off, const int32_t *len, const int32_t *pos_old,
                      const int32_t *pos_new, hipStream_t stream) {
   if (n_blocks > ba::kReencMaxBlocks)
     return run_reencode_t<ba::ReencBlocksLarge>(p, rt, n_blocks, src_off, dst_off, len, pos_old, pos_new, stream);
   return run_reencode_t<ba::ReencBlocks>(p, rt, n_blocks, src_off, dst_off, len, pos_old, pos_new, stream);
 }
+template int32_t run_reencode(ba::ReencParams, const ba::RopeTable &, int, const int32_t *, const int32_t *, const int32_t *,
+                              const int32_t *, const int32_t *, hipStream_t);
+template int32_t run_reencode(ba::ReencRowsParams, const ba::RopeTable &, int, const int32_t *, const int32_t *,
+                              const int32_t *, const int32_t *, const int32_t *, hipStream_t);
 
 // Rotate fresh Q (into q_rot, packed, pre-scaled) and fresh K (into k_rot) for segments
 // [seg0, seg0 + n) given by start offsets and first positions.

@@ -208,7 +208,7 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
         for (; at < nb && dst[at] < pl.cu_ctx[n + 1]; ++at) dst[at] += ctx0[n] - pl.cu_ctx[n];
       ba::RopeTable rt;
       build_rope_table(heads, &rt);
-      ba::ReencParams rp;
+      ba::ReencRowsParams rp;
       memset(&rp, 0, sizeof(rp));
       rp.src = k_cache->ptr;
       rp.dst = kg.ptr;

@@ -59,7 +59,8 @@ int32_t check_tensor(const ba_tensor *t, const char *name, bool allow_f32, int32
 // theta_j / (2 pi) as a Q0.64 fraction, from extended-precision host arithmetic
 void build_rope_table(const ba_heads *h, RopeTable *rt);
 float scale_log2e(const ba_heads *h);  // softmax scale * log2(e)
-int32_t run_reencode(ReencParams p, const RopeTable &rt, int n_blocks, const int32_t *src_off, const int32_t *dst_off,
+template <typename Params>  // ReencParams or ReencRowsParams
+int32_t run_reencode(Params p, const RopeTable &rt, int n_blocks, const int32_t *src_off, const int32_t *dst_off,
                      const int32_t *len, const int32_t *pos_old, const int32_t *pos_new, hipStream_t stream);
 // Rotate fresh Q (into q_rot, packed, pre-scaled) and fresh K (into k_rot) for segments
 // [seg0, seg0 + n) given by start offsets and first positions.

@@ -47,18 +47,22 @@ struct ReencParams {
   int32_t max_len;  // longest block in this launch
   int32_t heads_per_thread, n_head_groups;  // how the KV heads are split over workgroups
   int32_t copy_from_layer;  // layers from this one on are copied as they are (a gathered V rides along as a layer)
-  // Gathered contexts whose values stay where they are: row_table[destination token] = where its value row lies, in bytes
-  // (source token * row_bytes); destination tokens between a block's end and the next block's start (table_end
-  // behind the launch's last block) get the block's last row.
+};
+
+// The keys of a gathered context whose values stay where they are (bf16, uniform shift): row_table[destination token] =
+// where its value row lies, in bytes (source token * row_bytes); destination tokens between a block's end and the next
+// block's start (table_end behind the launch's last block) get the block's last row.
+// Kernels of their own: in the others the code for it, never entered, took up to 0.2 us of a launch of 4 to 12 (one layer of
+// 40 x 40 tokens, 8 heads of 128, absolute: 4.5 us with it, 4.3 without; 160 x 200, 4 heads of 64, half pairs: 12.5, 12.4).
+struct ReencRowsParams : ReencParams {
   uint32_t *row_table;
   uint32_t row_bytes;
   int32_t table_end;
 };
 
-hipError_t launch_reencode(const ReencParams &p, const ReencBlocks &blocks, const RopeTable &rt,
-                           hipStream_t stream);
-hipError_t launch_reencode(const ReencParams &p, const ReencBlocksLarge &blocks, const RopeTable &rt,
-                           hipStream_t stream);
+// Params = ReencParams or ReencRowsParams, Blocks = ReencBlocks or ReencBlocksLarge
+template <typename Params, typename Blocks>
+hipError_t launch_reencode(const Params &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream);
 
 // Final block over a block table: prompts and cached blocks per launch.  Two capacities, because
 // the tables travel by value in the kernel arguments and many large argument blocks in flight

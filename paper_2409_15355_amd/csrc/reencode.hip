@@ -8,6 +8,8 @@
 // heads, so its VEC (cos, sin) pairs are computed once per token (ABSOLUTE mode) or
 // once per workgroup (SHIFT mode: the angle depends on the block only) and reused for
 // every head.  CH/2 neighbouring lanes cover half a head vector contiguously.
+#include <type_traits>
+
 #include "ba_device.h"
 
 namespace ba {
@@ -61,17 +63,17 @@ __device__ __forceinline__ void rotate(float &a, float &b, float c, float s) {
   b = nb;
 }
 
-// The block's entries of ReencParams::row_table, by one workgroup.
+// The block's entries of ReencRowsParams::row_table, by one workgroup.
 template <typename Blocks>
-__device__ __forceinline__ void write_row_table(const ReencParams &p, const Blocks &blocks, int b) {
+__device__ __forceinline__ void write_row_table(const ReencRowsParams &p, const Blocks &blocks, int b) {
   const int len = blocks.len[b], at = blocks.dst_off[b];
   const int next = b + 1 < blocks.n ? blocks.dst_off[b + 1] : p.table_end;
   for (int u = threadIdx.x; u < next - at; u += kThreads)
     p.row_table[at + u] = (uint32_t)(blocks.src_off[b] + min(u, len - 1)) * p.row_bytes;
 }
 
-template <typename T, int D, int LAYOUT, int MODE, int TOK_PER_WG, typename Blocks>
-__global__ __launch_bounds__(kThreads) void reencode_kernel(ReencParams p, Blocks blocks, RopeTable rt) {
+template <typename T, int D, int LAYOUT, int MODE, int TOK_PER_WG, typename Params, typename Blocks>
+__global__ __launch_bounds__(kThreads) void reencode_kernel(Params p, Blocks blocks, RopeTable rt) {
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int CH = D / VEC;           // chunks per head vector
   constexpr int TPV = CH / 2;           // threads per head vector
@@ -148,7 +150,8 @@ __global__ __launch_bounds__(kThreads) void reencode_kernel(ReencParams p, Block
       y.store(d0 + g * p.dst_sh + (CH / 2) * VEC);
     }
   }
-  if (p.row_table && layer == 0 && blockIdx.x == 0) write_row_table(p, blocks, b);
+  if constexpr (std::is_same<Params, ReencRowsParams>::value)
+    if (layer == 0 && blockIdx.x == 0) write_row_table(p, blocks, b);
 }
 
 // Fast path: uniform shift (the angle depends on the block only), interleaved pairs (every pair
@@ -156,8 +159,8 @@ __global__ __launch_bounds__(kThreads) void reencode_kernel(ReencParams p, Block
 // contiguous run of chunks, and because the workgroup size is a multiple of the chunks per head
 // vector, a thread that walks the run with stride 256 always meets the same four frequencies:
 // a pure streaming pass, every wave instruction moving 1 KB of consecutive memory.
-template <typename T, int D, int UNROLL, typename Blocks>
-__global__ __launch_bounds__(kThreads) void reencode_shift_linear_kernel(ReencParams p, Blocks blocks, RopeTable rt) {
+template <typename T, int D, int UNROLL, typename Params, typename Blocks>
+__global__ __launch_bounds__(kThreads) void reencode_shift_linear_kernel(Params p, Blocks blocks, RopeTable rt) {
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int CH = D / VEC;
   static_assert(kThreads % CH == 0, "a thread must keep its chunk position inside the head vector");
@@ -190,64 +193,62 @@ __global__ __launch_bounds__(kThreads) void reencode_shift_linear_kernel(ReencPa
     const int64_t L = first + (int64_t)k * kThreads;
     if (L < n_chunks) x[k].store(dst + L * VEC);
   }
-  if (p.row_table && layer == 0 && blockIdx.x == 0) write_row_table(p, blocks, b);
+  if constexpr (std::is_same<Params, ReencRowsParams>::value)
+    if (layer == 0 && blockIdx.x == 0) write_row_table(p, blocks, b);
 }
 
-template <typename T, int D, typename Blocks>
-hipError_t launch_linear(const ReencParams &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
+template <typename T, int D, typename Params, typename Blocks>
+hipError_t launch_linear(const Params &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
   constexpr int UNROLL = 8;
   constexpr int CH = D / Chunk<T>::VEC;
   const int64_t max_chunks = (int64_t)p.max_len * p.n_kv_heads * CH;
   dim3 grid((unsigned)((max_chunks + UNROLL * kThreads - 1) / (UNROLL * kThreads)), blocks.n, p.n_layers);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return hipSuccess;
-  hipLaunchKernelGGL((reencode_shift_linear_kernel<T, D, UNROLL, Blocks>), grid, dim3(kThreads), 0, stream, p, blocks, rt);
+  hipLaunchKernelGGL((reencode_shift_linear_kernel<T, D, UNROLL, Params, Blocks>), grid, dim3(kThreads), 0, stream, p, blocks, rt);
   return hipGetLastError();
 }
 
-template <typename T, int D, int LAYOUT, int MODE, typename Blocks>
-hipError_t launch_t(const ReencParams &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
+template <typename T, int D, int LAYOUT, int MODE, typename Params, typename Blocks>
+hipError_t launch_t(const Params &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int TPP = kThreads / (D / VEC / 2);
   constexpr int TOK_PER_WG = TPP;
   dim3 grid(((p.max_len + TOK_PER_WG - 1) / TOK_PER_WG) * p.n_head_groups, blocks.n, p.n_layers);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return hipSuccess;
-  hipLaunchKernelGGL((reencode_kernel<T, D, LAYOUT, MODE, TOK_PER_WG, Blocks>), grid, dim3(kThreads), 0,
+  hipLaunchKernelGGL((reencode_kernel<T, D, LAYOUT, MODE, TOK_PER_WG, Params, Blocks>), grid, dim3(kThreads), 0,
                      stream, p, blocks, rt);
   return hipGetLastError();
 }
 
-template <typename T, int D, typename Blocks>
-hipError_t launch_d(const ReencParams &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
+template <typename T, int D, typename Params, typename Blocks>
+hipError_t launch_d(const Params &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
   const bool packed = p.src_sh == D && p.dst_sh == D && p.src_st == (int64_t)p.n_kv_heads * D &&
                       p.dst_st == (int64_t)p.n_kv_heads * D;
   if (p.layout == 0 && p.mode == 0 && packed) return launch_linear<T, D>(p, blocks, rt, stream);
-  if (p.layout == 0)
-    return p.mode == 0 ? launch_t<T, D, 0, 0>(p, blocks, rt, stream)
-                       : launch_t<T, D, 0, 1>(p, blocks, rt, stream);
-  return p.mode == 0 ? launch_t<T, D, 1, 0>(p, blocks, rt, stream)
-                     : launch_t<T, D, 1, 1>(p, blocks, rt, stream);
+  if (p.mode == 0)
+    return p.layout == 0 ? launch_t<T, D, 0, 0>(p, blocks, rt, stream) : launch_t<T, D, 1, 0>(p, blocks, rt, stream);
+  if constexpr (std::is_same<Params, ReencParams>::value)
+    return p.layout == 0 ? launch_t<T, D, 0, 1>(p, blocks, rt, stream) : launch_t<T, D, 1, 1>(p, blocks, rt, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-template <typename Blocks>
-hipError_t launch_reencode_any(const ReencParams &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
+template <typename Params, typename Blocks>
+hipError_t launch_reencode(const Params &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
   if (p.dtype == 0) {
     if (p.head_dim == 128) return launch_d<uint16_t, 128>(p, blocks, rt, stream);
     if (p.head_dim == 64) return launch_d<uint16_t, 64>(p, blocks, rt, stream);
-  } else {
+  } else if constexpr (std::is_same<Params, ReencParams>::value) {
     if (p.head_dim == 128) return launch_d<float, 128>(p, blocks, rt, stream);
     if (p.head_dim == 64) return launch_d<float, 64>(p, blocks, rt, stream);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_reencode(const ReencParams &p, const ReencBlocks &blocks, const RopeTable &rt, hipStream_t stream) {
-  return launch_reencode_any(p, blocks, rt, stream);
-}
-hipError_t launch_reencode(const ReencParams &p, const ReencBlocksLarge &blocks, const RopeTable &rt,
-                           hipStream_t stream) {
-  return launch_reencode_any(p, blocks, rt, stream);
-}
+template hipError_t launch_reencode(const ReencParams &, const ReencBlocks &, const RopeTable &, hipStream_t);
+template hipError_t launch_reencode(const ReencParams &, const ReencBlocksLarge &, const RopeTable &, hipStream_t);
+template hipError_t launch_reencode(const ReencRowsParams &, const ReencBlocks &, const RopeTable &, hipStream_t);
+template hipError_t launch_reencode(const ReencRowsParams &, const ReencBlocksLarge &, const RopeTable &, hipStream_t);
 
 }  // namespace ba
