@@ -892,11 +892,15 @@ GATHER_CASES = [  # (Hq, Hkv, D, tokens of each prompt's cached blocks, query to
     (4, 4, 64, [[7] * 150, [40, 90] * 9], [5, 130]),
     (6, 2, 128, [[1], [30, 100, 200] * 20], [400, 9]),
     (8, 1, 64, [[50] * 200], [1]),
+    # more blocks than one launch of the gather lists (1,024), the second launch's first inside a prompt and at its start
+    (4, 1, 64, [[5, 9, 2] * 200, [11] * 500], [33, 4]),
+    (8, 2, 128, [[3] * 1024, [9] * 30], [7, 64]),
 ]
 
 
 @pytest.mark.parametrize("layout", [0, 1])
-@pytest.mark.parametrize("case", GATHER_CASES, ids=["three-prompts-d128", "tiny-blocks-d64", "one-token-context", "long-d64"])
+@pytest.mark.parametrize("case", GATHER_CASES, ids=["three-prompts-d128", "tiny-blocks-d64", "one-token-context", "long-d64",
+                                                      "two-launches-d64", "two-launches-d128"])
 def test_gathered_calls_give_the_bits_of_a_context_gathered_by_hand(ba, case, layout):
     """Short cached blocks: keys gathered by the call, value rows fetched through its table of where they lie.  The
     same keys re-encoded into one context by the caller, the values copied there, must give the same bits: contexts
@@ -933,6 +937,45 @@ def test_gathered_calls_give_the_bits_of_a_context_gathered_by_hand(ba, case, la
                                            torch.full((need,), fill, dtype=torch.uint8, device="cuda"))
         torch.cuda.synchronize()
         assert np.array_equal(host_bits(o), want)
+
+
+@pytest.mark.parametrize("why", ["splits", "rows", "speeds"])
+def test_gathered_calls_that_copy_their_values(ba, why):
+    """Short cached blocks whose values the call copies next to the keys: a split's stretch of the context is longer than
+    the kernel's table of value rows (112 key tiles), 32 bits do not reach every row of the cache, or the call brings
+    XCD speeds.  The bits of a context gathered by hand."""
+    torch = torch_mod()
+    hq, hkv, d, lens, lq, stride, speeds = {
+        "splits": (32, 8, 64, [50] * 160, 2048, 8 * 64, None),  # 32 row tiles x 8 KV heads: one split of 157 key tiles
+        "rows": (8, 2, 64, [30, 40] * 30, 20, 1 << 20, None),
+        "speeds": (8, 2, 128, [30, 40] * 30, 20, 2 * 128, [1.03, 0.97, 1.02, 0.97, 1.03, 1.0, 1.02, 0.96])}[why]
+    lens = np.array(lens, dtype=np.int32)
+    T = int(lens.sum())
+    if why == "rows":
+        assert T * stride * 2 >= 1 << 32
+    heads = ba.Heads(hq, hkv, d, 10000.0, xcd_speed=speeds)
+    cu_q, cu_blk, cu_ctx = (np.array([0, n], dtype=np.int32) for n in (lq, len(lens), T))
+    if why == "splits":
+        items = ba.ba_schedule_final_block(heads, cu_q, cu_ctx)
+        assert max((w.ctx_end - w.ctx_begin) // 64 for w in items) > 112
+    dst = (np.cumsum(lens) - lens).astype(np.int32)
+    off = (T - np.cumsum(lens)).astype(np.int32)  # the cache holds the blocks in the other order
+    kc, vc = dev_bf16(wl.normal_bf16_bits(1410, (T, hkv, d))), dev_bf16(wl.normal_bf16_bits(1411, (T, hkv, d)))
+    v_cache = torch.zeros((T - 1) * stride + hkv * d, dtype=torch.bfloat16, device="cuda").as_strided((T, hkv, d), (stride, d, 1))
+    v_cache.copy_(vc)
+    qb, kfb, vfb = gen_qkv(1412, lq, hq, hkv, d)
+    q, kf, vf = dev_bf16(qb), dev_bf16(kfb), dev_bf16(vfb)
+    k_ctx, v_ctx = torch.empty_like(kc), torch.empty_like(vc)
+    ba.ba_reencode_positions(heads, kc, k_ctx, off, dst, lens, None, dst, ba.REENC_SHIFT)
+    for a, b, n in zip(off, dst, lens):
+        v_ctx[b:b + n] = vc[a:a + n]
+    want = host_bits(gpu_final(ba, heads, q, k_ctx, v_ctx, kf, vf, cu_q, cu_ctx))
+    o = torch.full_like(q, float("nan"))
+    ba.ba_final_block_attention_cached(heads, q, kc, v_cache, kf, vf, o, None, cu_q, cu_blk, off, lens, None, None, None,
+                                       torch.full((ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens),), 255,
+                                                  dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert np.array_equal(host_bits(o), want)
 
 
 def test_final_block_from_block_cache_agrees_with_two_step_path(ba, cached_route):
@@ -1438,6 +1481,168 @@ def test_whole_prompts_in_a_workspace_without_room_for_partial_results(ba, case)
         for t0, t1, (r, a) in refs:
             for got, ref, span, what in zip(grads, r, a, ("dq", "dk", "dv")):
                 assert_grad_close(host_f64(got)[t0:t1], ref, span, f"{name} {what}, workspace {size}")
+
+
+def assert_prompts_close(got, bits, cu_blk, offs, th, layout=0, what=""):
+    """(o, lse, dq, dk, dv) of whole prompts against the oracle, prompt by prompt."""
+    f = oracle.bf16_bits_to_f64
+    o, lse, dq, dk, dv = (host_f64(t.contiguous()) for t in got)
+    for n in range(len(cu_blk) - 1):
+        t0, t1 = int(offs[cu_blk[n]]), int(offs[cu_blk[n + 1]])
+        po = offs[cu_blk[n]:cu_blk[n + 1] + 1] - t0
+        x = [f(b[t0:t1]) for b in bits]
+        assert_attention_close(o[t0:t1], oracle.masked_attention_bruteforce(*x[:3], po, th, layout=layout), f"{what} o, prompt {n}")
+        want = oracle_prompt_lse(x[0], x[1], po, th, layout, x[0].shape[-1] ** -0.5)
+        assert np.abs(lse[t0:t1] - want).max() < 2e-2, f"{what} log-sum-exp, prompt {n}"
+        refs, sizes = oracle_grads(*x, po, th, layout=layout)
+        for g, ref, size, name in zip((dq, dk, dv), refs, sizes, ("dq", "dk", "dv")):
+            assert_grad_close(g[t0:t1], ref, size, f"{what} {name}, prompt {n}")
+
+
+def prompt_inputs(seed, prompts, hq, hkv, d):
+    offs = np.concatenate([[0], np.cumsum([n for p in prompts for n in p])]).astype(np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    T = int(offs[-1])
+    return offs, cu_blk, T, (*gen_qkv(seed, T, hq, hkv, d), wl.normal_bf16_bits(seed + 3, (T, hq, d)))
+
+
+def dirty(n):
+    return torch_mod().full((int(n),), 255, dtype=torch_mod().uint8, device="cuda")
+
+
+def test_shared_walks_with_half_pairs_strided_views_and_rotated_keys(ba):
+    """Shared walks, forward and backward, where every tensor has strides of its own and the rotated keys go out;
+    memory between the views' rows stays as it was."""
+    torch = torch_mod()
+    hq, hkv, d, base = 8, 2, 128, 500000.0
+    offs, cu_blk, T, bits = prompt_inputs(770, [[64, 9], [900, 380, 33]], hq, hkv, d)
+    heads = ba.Heads(hq, hkv, d, base, rope_layout=1)
+    assert max(w.n_splits for w in ba.ba_schedule_prompts(heads, cu_blk, offs)) > 1
+    fused = torch.zeros((T, hq + 2 * hkv, d), dtype=torch.bfloat16, device="cuda")
+    fused[:, :hq], fused[:, hq:hq + hkv], fused[:, hq + hkv:] = (dev_bf16(b) for b in bits[:3])
+    q, k, v = fused[:, :hq], fused[:, hq:hq + hkv], fused[:, hq + hkv:]
+    o_big = torch.full((T, hq, 2, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    k_rot_big = torch.full((T, 2 * hkv, d), 3.0, dtype=torch.bfloat16, device="cuda")
+    do_big = torch.zeros((T + 3, hq + 1, d), dtype=torch.bfloat16, device="cuda")
+    do_big[3:, 1:] = dev_bf16(bits[3])
+    grads = torch.full((T, hq + 2 * hkv + 1, d), 5.0, dtype=torch.bfloat16, device="cuda")
+    o, k_rot, do = o_big[:, :, 1], k_rot_big[:, ::2], do_big[3:, 1:]
+    dv, dq, dk = grads[:, :hkv], grads[:, hkv:hkv + hq], grads[:, hkv + hq:-1]
+    lse = torch.full((T, hq), float("nan"), dtype=torch.float32, device="cuda")
+    ba.ba_block_attention_prompts(heads, q, k, v, o, k_rot, lse, cu_blk, offs, 1,
+                                  dirty(ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, True)))
+    ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs,
+                                           dirty(ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs)))
+    torch.cuda.synchronize()
+    assert bool((o_big[:, :, 0] == 7).all()) and bool((k_rot_big[:, 1::2] == 3).all()) and bool((grads[:, -1] == 5).all())
+    th = oracle.theta(base, d)
+    assert_prompts_close((o, lse, dq, dk, dv), bits, cu_blk, offs, th, layout=1)
+    for n in range(len(cu_blk) - 1):
+        t0, t1 = int(offs[cu_blk[n]]), int(offs[cu_blk[n + 1]])
+        ref = oracle.rope_dense(oracle.bf16_bits_to_f64(bits[1][t0:t1]), np.arange(t1 - t0), th, 1)
+        assert_reencode_bf16(host_bits(k_rot)[t0:t1], ref, 1, f"rotated keys, prompt {n}")
+
+
+def test_shared_walks_in_the_first_of_several_launches(ba):
+    """More blocks than one launch's table holds: the shared walks are the first launch's, the second has none."""
+    torch = torch_mod()
+    hq, hkv, d, base = 4, 1, 64, 10000.0
+    rng = np.random.default_rng(93)
+    prompts = [[200, *rng.integers(3, 10, 180).tolist(), 24] for _ in range(2)]
+    offs, cu_blk, T, bits = prompt_inputs(780, prompts, hq, hkv, d)
+    heads = ba.Heads(hq, hkv, d, base)
+    launches = {}
+    for w in ba.ba_schedule_prompts(heads, cu_blk, offs):
+        launches.setdefault(w.launch, set()).add(w.n_splits)
+    assert sorted(launches) == [0, 1] and max(launches[0]) > 1 and launches[1] == {1}
+    q, k, v, do = (dev_bf16(b) for b in bits)
+    o, dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, q, k, v))
+    lse = torch.full((T, hq), float("nan"), dtype=torch.float32, device="cuda")
+    ba.ba_block_attention_prompts(heads, q, k, v, o, None, lse, cu_blk, offs, 1,
+                                  dirty(ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False)))
+    ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs,
+                                           dirty(ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs)))
+    torch.cuda.synchronize()
+    assert_prompts_close((o, lse, dq, dk, dv), bits, cu_blk, offs, oracle.theta(base, d))
+
+
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (6, 2)])
+def test_shared_walks_of_small_groups_beyond_32_bit_row_offsets(ba, hq, hkv):
+    """o and d_out at a token stride of 2^20 elements: fewer than four query heads per KV head go through padded copies
+    as groups of four, whose walks are shared by the padded call's own plan and workspace."""
+    torch = torch_mod()
+    d, base = 64, 10000.0
+    offs, cu_blk, T, bits = prompt_inputs(790 + hq, [[1200, 10]], hq, hkv, d)
+    heads, padded = ba.Heads(hq, hkv, d, base), ba.Heads(4 * hkv, hkv, d, base)
+    assert max(w.n_splits for w in ba.ba_schedule_prompts(padded, cu_blk, offs)) > 1
+    q, k, v, do_packed = (dev_bf16(b) for b in bits)
+
+    def wide():
+        return torch.full(((T - 1) * (1 << 20) + hq * d,), float("nan"), dtype=torch.bfloat16, device="cuda").as_strided((T, hq, d), (1 << 20, d, 1))
+
+    o, do = wide(), wide()
+    do.copy_(do_packed)
+    dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, k, v))
+    lse = torch.full((T, hq), float("nan"), dtype=torch.float32, device="cuda")
+    ba.ba_block_attention_prompts(heads, q, k, v, o, None, lse, cu_blk, offs, 1,
+                                  dirty(ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False)))
+    ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs,
+                                           dirty(ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs)))
+    torch.cuda.synchronize()
+    assert_prompts_close((o, lse, dq, dk, dv), bits, cu_blk, offs, oracle.theta(base, d))
+
+
+def test_shared_walks_and_gathered_contexts_can_be_captured_in_a_hip_graph(ba):
+    """The counters of shared walks are cleared, and the table of value rows written, by kernels of the call itself:
+    every replay of a captured call gives the eager bits, with eager calls in between."""
+    torch = torch_mod()
+    hq, hkv, d = 8, 2, 64
+    offs, cu_blk, T, bits = prompt_inputs(800, [[800, 420, 30], [64, 9]], hq, hkv, d)
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    q, k, v, do = (dev_bf16(b) for b in bits)
+    outs = [torch.empty_like(x) for x in (q, q, k, v)]
+    o, dq, dk, dv = outs
+    lse = torch.empty((T, hq), device="cuda")
+    ws_f = dirty(ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False))
+    ws_b = dirty(ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs))
+    lens = np.array([40, 7, 100] * 8, dtype=np.int32)
+    off = (np.cumsum(lens) - lens).astype(np.int32)[::-1].copy()
+    lens_b = lens[::-1].copy()
+    cu_q, cu_b = np.array([0, 30], dtype=np.int32), np.array([0, len(lens)], dtype=np.int32)
+    qf, kf, vf = q[:30], k[:30], v[:30]
+    of = torch.empty_like(qf)
+    ws_c = dirty(ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_b, lens_b))
+    outs += [lse, of]
+
+    def calls():
+        ba.ba_block_attention_prompts(heads, q, k, v, o, None, lse, cu_blk, offs, 1, ws_f)
+        ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs, ws_b)
+        ba.ba_final_block_attention_cached(heads, qf, k, v, kf, vf, of, None, cu_q, cu_b, off, lens_b, None, None, None, ws_c)
+
+    calls()
+    torch.cuda.synchronize()
+    want = [t.clone() for t in outs]
+    assert all(bool(torch.isfinite(t).all()) for t in want)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    for rep in range(3):
+        for t in outs:
+            t.zero_()
+        for ws in (ws_f, ws_b, ws_c):
+            ws.fill_(255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, ref in zip(outs, want):
+            assert torch.equal(got, ref), f"replay {rep}"
+        calls()
+        torch.cuda.synchronize()
 
 
 def test_whole_prompts_forward_and_backward_on_strided_views(ba):

@@ -440,3 +440,119 @@ def test_bad_xcd_speeds_are_rejected():
         ba.ba_schedule_final_block(h, [0, 256], [0, 31744], 256)
     with pytest.raises(ValueError):
         ba.Heads(32, 8, 128, xcd_speed=[1.0] * 7)
+
+
+KV_PLAN = r'''
+// Prints the dk/dv kernel's work of a call: "shares n_split items part_slots counters", then per launch and table entry
+// "launch block key_tile split n_splits begin end walk".
+#include <cstdio>
+#include <cstdlib>
+#include "ba_plan.h"
+#include "ba_schedule.h"
+int main(int, char **a) {  // n_q_heads n_kv_heads head_dim n_prompts {n_blocks {len}}
+  ba_heads h = {};
+  h.n_q_heads = atoi(a[1]), h.n_kv_heads = atoi(a[2]), h.head_dim = atoi(a[3]);
+  std::vector<int32_t> cu(1, 0), offs(1, 0);
+  const int n_prompts = atoi(a[4]);
+  a += 5;
+  for (int n = 0; n < n_prompts; ++n) {
+    const int nb = atoi(*a++);
+    cu.push_back(cu.back() + nb);
+    for (int b = 0; b < nb; ++b) offs.push_back(offs.back() + atoi(*a++));
+  }
+  const int G = h.n_q_heads / h.n_kv_heads;
+  const ba::WalkShares s = ba::plan_kv_shares(&h, n_prompts, cu.data(), offs.data());
+  printf("shares %d %lld %zu %zu\n", s.n_split, (long long)s.items, s.part_bytes / (32 * 4 * (size_t)h.head_dim), s.count_bytes / 4);
+  std::vector<ba::PromptBlock> blks = ba::list_prompt_blocks(n_prompts, cu.data(), offs.data());
+  ba::sort_by_query_rows(&blks, G, s);
+  int launch = 0;
+  for (size_t b0 = 0; b0 < blks.size(); b0 += ba::kEncMaxBlocks, ++launch) {
+    const int n = (int)std::min<size_t>(ba::kEncMaxBlocks, blks.size() - b0);
+    ba::BwdKvMeta m;
+    const int64_t tiles = ba::build_kv_meta(blks, b0, n, G, s, &m);
+    for (int e = 0; e < tiles; ++e) {  // (the kernel's own arithmetic, from its entry on)
+      int b = 0;
+      while (m.tile_start[b + 1] <= e) ++b;
+      int split = 0, jt = e - m.tile_start[b], n_splits = 1;
+      const bool shared = b < m.n_split;
+      if (shared) {
+        const int n_kt = (m.len[b] + ba::kBwdTileKeys - 1) / ba::kBwdTileKeys;
+        split = jt / n_kt;
+        jt -= split * n_kt;
+      }
+      const int rows_a = m.len[b] * G, rows_f = m.fin_len[b] * G, R = ba::kKvTileRows;
+      ba::TileRange w = {0, (rows_f + R - 1) / R + (rows_a + R - 1) / R - jt * ba::kBwdTileKeys * G / R};
+      const int walk = w.end;
+      if (shared) {
+        n_splits = ba::walk_splits(walk, m.chunk);
+        if (split >= n_splits) continue;
+        w = ba::walk_split_range(walk, n_splits, split);
+      }
+      printf("%d %d %d %d %d %d %d %d %d\n", launch, m.start[b], jt, split, n_splits, w.begin, w.end, walk, shared ? e : -1);
+    }
+  }
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def kv_plan(tmp_path_factory):
+    import os
+    import shutil
+    import subprocess
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no C++ compiler here")
+    csrc = os.path.join(os.path.dirname(ba.LIB_PATH), "csrc")
+    d = tmp_path_factory.mktemp("kv_plan")
+    (d / "kv_plan.cpp").write_text("#include <algorithm>\n#include <vector>\n" + KV_PLAN)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", csrc, str(d / "kv_plan.cpp"),
+                    os.path.join(csrc, "ba_plan.cpp"), "-o", str(d / "kv_plan")], check=True)
+
+    def plan(hq, hkv, d_, prompts):
+        args = [hq, hkv, d_, len(prompts)]
+        for p in prompts:
+            args += [len(p), *p]
+        out = subprocess.run([str(d / "kv_plan"), *map(str, args)], check=True, capture_output=True, text=True).stdout.splitlines()
+        return [int(x) for x in out[0].split()[1:]], [tuple(int(x) for x in l.split()) for l in out[1:]]
+
+    return plan
+
+
+def test_shared_walks_of_key_tiles_cover_every_row_tile_once(kv_plan):
+    """The dk/dv kernel's plan: the splits of a key tile partition the row tiles that see it, none of them empty, whether
+    the block is shared or not; a shared entry's partial results and counter lie inside the memory planned for them.
+    Drawn calls, and the ones whose gradients the GPU tests compare: their walks are shared."""
+    gpu_cases = [(2, 2, 64, [[1150, 37], [40, 9]]), (6, 2, 128, [[700, 420, 50]]), (8, 2, 128, [[30, 5], [1300, 33]]),
+                 (4, 1, 64, [[1, 1500, 1]]), (8, 2, 128, [[64, 9], [900, 380, 33]]), (4, 1, 64, [[200, *[6] * 180, 24]] * 2),
+                 (8, 2, 64, [[1200, 10]]), (8, 2, 64, [[800, 420, 30], [64, 9]])]
+    rng = np.random.default_rng(5)
+    drawn = []
+    for _ in range(60):
+        hq, hkv, d = [(4, 4, 64), (8, 2, 64), (32, 8, 128), (16, 8, 128), (6, 2, 128), (1, 1, 64)][int(rng.integers(6))]
+        hi = int(rng.choice([60, 300, 2000]))
+        drawn.append((hq, hkv, d, [[*rng.integers(0, hi, int(rng.integers(0, 9))).tolist(), int(rng.integers(0, 300))] for _ in range(int(rng.integers(1, 9)))]))
+    seen = set()
+    for i, (hq, hkv, d, prompts) in enumerate(gpu_cases + drawn):
+        G = hq // hkv
+        (n_split, items, slots, counters), entries = kv_plan(hq, hkv, d, prompts)
+        seen.add(n_split > 0)
+        assert i >= len(gpu_cases) or n_split > 0
+        assert slots == items * hkv * 4 and counters == items * hkv
+        tiles = {}
+        for launch, start, jt, split, n_splits, begin, end, walk, entry in entries:
+            assert begin < end and (n_splits == 1 or launch == 0) and entry < items
+            tiles.setdefault((start, jt), []).append((split, n_splits, begin, end, walk))
+        t0, want = 0, {}
+        for p in prompts:
+            for b, n in enumerate(p):
+                fin = p[-1] if b < len(p) - 1 else 0
+                for jt in range(-(-n // 64)):
+                    want[t0, jt] = -(-fin * G // 32) + -(-n * G // 32) - jt * 64 * G // 32
+                t0 += n
+        assert {k: v[0][4] for k, v in tiles.items()} == want
+        for k, parts in tiles.items():
+            parts.sort()
+            assert [x[0] for x in parts] == list(range(parts[0][1]))
+            assert [x[2] for x in parts] + [want[k]] == [0] + [x[3] for x in parts]
+    assert seen == {True, False}
