@@ -167,8 +167,19 @@ constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 // of partial results.  110 calls of 2 to 50 prompts, walk / load and time shared / unshared: 0.26-0.57 0.95-1.05, in the
 // mean 1.00; 0.62 1.007, 0.63 0.996 and 0.95, 0.66 1.005, 0.69 0.99, 0.70 1.00 and 1.03, 0.71 0.99, 0.72 0.86, 0.73 0.87,
 // 0.74 0.83, 0.75 0.92 and 0.86; beyond, 0.80 in the mean of 69, two of them slower (1.01, 1.07).
+// (At head_dim 128 every part beyond a walk's first counts as kSharePartTiles in that: 64 KB of partial results out and in,
+// and the forward and dq kernels' times in the call of 64 prompts above, 25 and 12 tiles a part.  Without it 13 prompts
+// of 16 x 111 + 124 or 19 x 83 + 97 tokens, 8 over 8 heads, and 24 of 13 x 101 + 45, 8 over 1, were 3, 4 and 6 % slower shared; six
+// other calls that it leaves alone, 0.99 to 1.01.  At 64 calls down to 0.65 of the load with as many parts take 0.76 to 0.97 shared.)
+// ... and only if the longest of them is longer by 1 / kShareLead than every walk that stays: a last block of
+// too many row tiles or a passage as long leaves the launch no shorter.  Thirteen calls where one was as long, 1 to 11
+// prompts: 1.02 in the mean, 0.94 to 1.08 (8 over 1 of 128, eight prompts of 650-1520 tokens and 120-260, forward kernel 52 us
+// unshared and 59 shared, dq 76 and 91); with a lead of one tile of 37 to 86 0.97 to 1.02, of two to five 0.92 to
+// 1.01.  (Calls of hardly any work, a load of less than a quarter of the walk, either way: 1.00 to 1.02.)
 constexpr int kShareAbove = 36, kShareChunk = 16, kSharePairs = 24;
-constexpr double kShareLoad = 0.65;
+constexpr double kShareLoad = 0.64;
+constexpr double kSharePartTiles = 24.0;  // head_dim 128
+constexpr int kShareLead = 100;
 constexpr size_t kShareMaxBytes = (size_t)256 << 20;
 // ... and the same for the walks of the dk/dv kernel (0.73 us a tile; a key tile's rows are its block's and the last
 // block's).  Forward and backward, us, unshared / shared: 8 over 2 heads of 64, five prompts of 4 x 350-1040 tokens and

@@ -411,28 +411,31 @@ int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads) {
 WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
   WalkShares ws;
   const int64_t G = h->n_q_heads / h->n_kv_heads;
-  double load = 0.0;  // of the launch, in key tiles
-  int longest = 0;
-  const auto add = [&](int64_t ctx, int64_t len) {
-    load += (double)short_row_tiles(len, G) * (((double)ctx + 0.5 * (double)len) / kPromptKeys + 0.5 + kFixedTiles);
+  const double part_tiles = h->head_dim == 128 ? kSharePartTiles : 0.0;
+  double load = 0.0;  // of the launch with its walks cut, in key tiles
+  int longest = 0, longest_left = 0;  // of the walks that would be cut, and of the others
+  const auto add = [&](int64_t ctx, int64_t len, int s) {
+    load += (double)short_row_tiles(len, G) * (((double)ctx + 0.5 * (double)len) / kPromptKeys + 0.5 + kFixedTiles + part_tiles * (s - 1));
+    int &most = s > 1 ? longest : longest_left;
+    if (len > 0) most = std::max(most, walk_tiles(ctx + len));
   };
   for (int n = 0; n < n_prompts; ++n) {
     const int last = cu_blk[n + 1] - 1;
-    for (int b = cu_blk[n]; b < last; ++b) add(0, block_offsets[b + 1] - block_offsets[b]);
+    for (int b = cu_blk[n]; b < last; ++b) add(0, block_offsets[b + 1] - block_offsets[b], 1);
     const int64_t len = block_offsets[last + 1] - block_offsets[last], ctx = block_offsets[last] - block_offsets[cu_blk[n]];
-    add(ctx, len);
     const int s = shared_splits(ctx, len, G, h->n_kv_heads);
+    add(ctx, len, s);
     if (s < 2) continue;
     ++ws.n_split;
     ws.items += short_row_tiles(len, G) * s;
-    longest = std::max(longest, walk_tiles(ctx + len));
   }
   load *= h->n_kv_heads / (double)kShareCus;  // ... per compute unit
   const size_t slots = (size_t)ws.items * h->n_kv_heads * (kShortTileRows / 32);
-  // (More shared blocks than one launch lists, or more bytes, would take over 170 prompts, whose load is far beyond the
-  // line; the tables rely on it.)
-  if (ws.n_split == 0 || longest < kShareLoad * load || ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes)
-    return WalkShares();
+  if (ws.n_split == 0 || longest < kShareLoad * load) return WalkShares();
+  if (longest <= longest_left + longest_left / kShareLead && longest <= 4 * load) return WalkShares();
+  // (the tables need the first: the shared blocks are in the first launch's.  With 8 KV heads it would take over 170 prompts, whose
+  // load is far beyond the line)
+  if (ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes) return WalkShares();
   ws.part_bytes = slots * 32 * h->head_dim * 4;
   ws.ml_bytes = slots * 256;
   ws.count_bytes = (size_t)ws.items * h->n_kv_heads * 4;
