@@ -189,8 +189,14 @@ constexpr size_t kShareMaxBytes = (size_t)256 << 20;
 // 9 x 250-750 73 / 67, but 32 over 8, two of 22 x 37-112 120 / 122 and 16 over 8, four of 4 x 100-298 106 / 108.
 // In calls whose longest such walk is more than kKvShareLoad of what every one of kShareCus compute units has to do
 // (a call that fills the chip adds up in one order, whatever else is in the batch), in chunks of half of that.
-constexpr int kKvShareAbove = 21, kKvShareChunk = 12, kShareCus = 256;
-constexpr double kKvShareLoad = 0.75;
+// Four query heads and more per KV head of 128, where that walk is less than kKvShareLight of that load: only if it is
+// kKvShareLead tiles longer than what is left when it is cut (the longest part, the longest walk that stays,
+// kKvShareLoad of the load).  The 64 KB of every part, out past the caches and in again, take the time of some ten
+// tiles.  52 calls of 1 to 15 prompts, tiles gained and time shared / unshared of forward and backward: below 9 0.96 to 1.09 (64
+// over 8, ten prompts of 4 x 45-135 + 5, dk/dv 164 us of a call and 14 more of it; 32 over 8, three of 5 x 140-195 + 12, 34 us and 37), a third of
+// them slower; from 9 on 0.71 to 0.99, one 1.02.  Smaller groups and head_dim 64 gain below 9 too: 24 calls, 0.88 to 1.00.
+constexpr int kKvShareAbove = 21, kKvShareChunk = 12, kShareCus = 256, kKvShareLead = 9;
+constexpr double kKvShareLoad = 0.75, kKvShareLight = 1.5;
 
 struct AttnParams {
   const uint16_t *q;

@@ -477,12 +477,15 @@ WalkShares plan_kv_shares(const ba_heads *h, int32_t n_prompts, const int32_t *c
   load *= h->n_kv_heads / (double)kShareCus;  // ... per compute unit
   if (longest <= kKvShareAbove || (double)longest < kKvShareLoad * load) return ws;
   const int chunk = std::max(kKvShareChunk, (int)std::min(1e6, 0.5 * load));
+  double left = kKvShareLoad * load;  // what the launch takes with its walks cut
   each([&](int64_t len, int64_t fin) {
     const int s = kv_splits(len, fin, G, chunk);
+    left = std::max(left, (double)((kv_walk(len, fin, G) + s - 1) / s));
     if (s < 2) return;
     ++ws.n_split;
     ws.items += key_tiles(len) * s;
   });
+  if (h->head_dim == 128 && G >= 4 && (double)longest < kKvShareLight * load && (double)longest < left + kKvShareLead) return WalkShares();
   const size_t slots = (size_t)ws.items * h->n_kv_heads * (kBwdTileKeys / 16);  // a pair of waves per 32 keys
   if (ws.n_split == 0 || ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes) return WalkShares();
   ws.chunk = chunk;

@@ -572,3 +572,12 @@ def test_shared_walks_of_key_tiles_cover_every_row_tile_once(kv_plan):
             assert [x[0] for x in parts] == list(range(parts[0][1]))
             assert [x[2] for x in parts] + [want[k]] == [0] + [x[3] for x in parts]
     assert seen == {True, False}
+
+
+@pytest.mark.parametrize("hq,hkv,d,prompts,shared", [
+    (64, 8, 128, [[90] * 4 + [5]] * 10, False), (64, 8, 128, [[90] * 4 + [5]], True), (32, 8, 128, [[166] * 5 + [12]] * 3, False),
+    (32, 8, 128, [[290, 290, 3]] * 5, True), (16, 8, 128, [[418] * 4 + [36]] * 2, True), (8, 2, 64, [[300] * 6 + [20]] * 8, True)])
+def test_walks_of_key_tiles_are_shared_only_where_the_launch_gets_shorter(kv_plan, hq, hkv, d, prompts, shared):
+    """Groups of four and more at head_dim 128 whose launch is hardly longer than its load or than the walks that stay;
+    the same prompt alone, longer walks, smaller groups and head_dim 64 are shared as ever."""
+    assert (kv_plan(hq, hkv, d, prompts)[0][0] > 0) == shared
