@@ -185,8 +185,8 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
     vg = kg;
     vg.ptr = (char *)ws + align256(pl.gather_kv_bytes);
     const int nb = (int)src.size();
-    // Values need no rotation: where 32 bits reach every row of the cache and a split's share of the table fits in
-    // LDS, only the keys are gathered, next to a table of where each context token's value row lies.  512 blocks of
+    // Values need no rotation: where there are enough of them, 32 bits reach every row of the cache and a split's share of
+    // the table fits in LDS, only the keys are gathered, next to a table of where each context token's value row lies.  512 blocks of
     // 20 to 60 tokens at 32 over 8 heads of 128: 80 us with the values gathered as well (172 MB through memory, 42 us
     // of it), 62 so; 1 over 1 and up, 14 calls of 300 to 26,000 context tokens: 1.0 to 1.5 times as fast.
     FinalPlan fp;
@@ -200,7 +200,8 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
     }
     for (int b = 0; b < nb; ++b) reach = std::max<int64_t>(reach, (int64_t)src[b] + len[b]);
     const size_t table_at = align256((size_t)padded * row_b);
-    if (n_prompts <= ba::kFinMaxPrompts && !heads->xcd_speed && (fp.max_nt + fp.max_nt / (2 * fp.n_splits)) / fp.n_splits + 2 <= ba::kRowTableTiles &&
+    if (n_prompts <= ba::kFinMaxPrompts && !heads->xcd_speed && nb <= ba::kRowTableBlocks &&
+        (size_t)pl.cu_ctx[n_prompts] * row_b >= ba::kRowTableBytes && (fp.max_nt + fp.max_nt / (2 * fp.n_splits)) / fp.n_splits + 2 <= ba::kRowTableTiles &&
         reach * v_cache->stride_tok * 2 < ((int64_t)1 << 32) - 65536 &&
         table_at + (size_t)padded * 4 <= 2 * align256(pl.gather_kv_bytes)) {
       int at = 0;

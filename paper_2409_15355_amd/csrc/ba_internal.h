@@ -318,6 +318,12 @@ struct FinalMeta {
 // of kTileKeys) and whose value rows are fetched from the cache through a table: byte offset of context token
 // t's row at rows[ctx0[n] + t], entries up to the next multiple of kTileKeys holding some row that exists.
 constexpr int kRowTableTiles = 112;  // context tiles of one split at most: 16 rows of each per copying wave lie in LDS
+// ... for contexts of this many bytes of values at least: a workgroup waits for its part of the table before it asks for
+// the first values, 1 to 2 us of a call, and copying a few MB takes less.  200 drawn calls of 1 to 20 prompts, time with
+// the table / with copied values: below 1 MB 0.99 to 1.10, in the mean 1.05; 1 to 2.5 MB 1.02; 2.5 to 5 MB 1.01; 5 to 10 0.97; beyond 0.91.
+// And of this many blocks at most, eight launches of the gather: beyond, 0.89, 0.96, 1.05 and 1.21 (26,514 blocks).
+constexpr size_t kRowTableBytes = (size_t)4 << 20;
+constexpr int kRowTableBlocks = 8 * kReencMaxBlocksLarge;
 struct FinalGatherMeta : FinalMeta {
   int32_t ctx0[kFinMaxPrompts];
   const uint32_t *rows;

@@ -893,14 +893,24 @@ GATHER_CASES = [  # (Hq, Hkv, D, tokens of each prompt's cached blocks, query to
     (6, 2, 128, [[1], [30, 100, 200] * 20], [400, 9]),
     (8, 1, 64, [[50] * 200], [1]),
     # more blocks than one launch of the gather lists (1,024), the second launch's first inside a prompt and at its start
-    (4, 1, 64, [[5, 9, 2] * 200, [11] * 500], [33, 4]),
-    (8, 2, 128, [[3] * 1024, [9] * 30], [7, 64]),
+    (8, 8, 64, [[5, 9, 2] * 200, [11] * 500], [33, 4]),
+    (16, 8, 128, [[3] * 1024, [9] * 30], [7, 64]),
+    # the first four again with enough KV heads for the table (4 MB of values; with less they are copied)
+    (32, 8, 128, [[20, 60, 33, 1] * 18, [64, 64], [63]], [64, 1, 300]),
+    (16, 16, 64, [[7] * 250, [40, 90] * 9], [5, 130]),
+    (24, 8, 128, [[1], [30, 100, 200] * 20], [400, 9]),
+    (64, 8, 64, [[50] * 200], [1]),
+    # values of just 4 MB, and one token less
+    (8, 8, 128, [[32] * 64], [70]),
+    (8, 8, 128, [[32] * 63 + [31]], [70]),
 ]
 
 
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("case", GATHER_CASES, ids=["three-prompts-d128", "tiny-blocks-d64", "one-token-context", "long-d64",
-                                                      "two-launches-d64", "two-launches-d128"])
+                                                      "two-launches-d64", "two-launches-d128", "three-prompts-d128-table",
+                                                      "tiny-blocks-d64-table", "one-token-context-table", "long-d64-table",
+                                                      "table-from-here", "copied-to-here"])
 def test_gathered_calls_give_the_bits_of_a_context_gathered_by_hand(ba, case, layout):
     """Short cached blocks: keys gathered by the call, value rows fetched through its table of where they lie.  The
     same keys re-encoded into one context by the caller, the values copied there, must give the same bits: contexts
@@ -947,10 +957,11 @@ def test_gathered_calls_that_copy_their_values(ba, why):
     torch = torch_mod()
     hq, hkv, d, lens, lq, stride, speeds = {
         "splits": (32, 8, 64, [50] * 160, 2048, 8 * 64, None),  # 32 row tiles x 8 KV heads: one split of 157 key tiles
-        "rows": (8, 2, 64, [30, 40] * 30, 20, 1 << 20, None),
-        "speeds": (8, 2, 128, [30, 40] * 30, 20, 2 * 128, [1.03, 0.97, 1.02, 0.97, 1.03, 1.0, 1.02, 0.96])}[why]
+        "rows": (32, 8, 128, [30, 40] * 30, 20, 1 << 20, None),
+        "speeds": (32, 8, 128, [30, 40] * 30, 20, 8 * 128, [1.03, 0.97, 1.02, 0.97, 1.03, 1.0, 1.02, 0.96])}[why]
     lens = np.array(lens, dtype=np.int32)
     T = int(lens.sum())
+    assert T * hkv * d * 2 >= 4 << 20  # (less is copied in any case)
     if why == "rows":
         assert T * stride * 2 >= 1 << 32
     heads = ba.Heads(hq, hkv, d, 10000.0, xcd_speed=speeds)
@@ -1605,19 +1616,21 @@ def test_shared_walks_and_gathered_contexts_can_be_captured_in_a_hip_graph(ba):
     lse = torch.empty((T, hq), device="cuda")
     ws_f = dirty(ba.ba_block_attention_prompts_workspace_bytes(heads, cu_blk, offs, 1, False))
     ws_b = dirty(ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs))
-    lens = np.array([40, 7, 100] * 8, dtype=np.int32)
+    lens = np.array([40, 7, 100] * 15, dtype=np.int32)
     off = (np.cumsum(lens) - lens).astype(np.int32)[::-1].copy()
     lens_b = lens[::-1].copy()
     cu_q, cu_b = np.array([0, 30], dtype=np.int32), np.array([0, len(lens)], dtype=np.int32)
-    qf, kf, vf = q[:30], k[:30], v[:30]
+    heads_c = ba.Heads(32, 8, 128, 10000.0)
+    qf, kf, vf = (dev_bf16(b) for b in gen_qkv(810, 30, 32, 8, 128))
+    kc, vc = (dev_bf16(wl.normal_bf16_bits(s, (int(lens.sum()), 8, 128))) for s in (815, 816))
     of = torch.empty_like(qf)
-    ws_c = dirty(ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_b, lens_b))
+    ws_c = dirty(ba.ba_final_block_attention_cached_workspace_bytes(heads_c, cu_q, cu_b, lens_b))
     outs += [lse, of]
 
     def calls():
         ba.ba_block_attention_prompts(heads, q, k, v, o, None, lse, cu_blk, offs, 1, ws_f)
         ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs, ws_b)
-        ba.ba_final_block_attention_cached(heads, qf, k, v, kf, vf, of, None, cu_q, cu_b, off, lens_b, None, None, None, ws_c)
+        ba.ba_final_block_attention_cached(heads_c, qf, kc, vc, kf, vf, of, None, cu_q, cu_b, off, lens_b, None, None, None, ws_c)
 
     calls()
     torch.cuda.synchronize()
