@@ -188,7 +188,7 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
     // Values need no rotation: where there are enough of them, 32 bits reach every row of the cache and a split's share of
     // the table fits in LDS, only the keys are gathered, next to a table of where each context token's value row lies.  512 blocks of
     // 20 to 60 tokens at 32 over 8 heads of 128: 80 us with the values gathered as well (172 MB through memory, 42 us
-    // of it), 62 so; 1 over 1 and up, 14 calls of 300 to 26,000 context tokens: 1.0 to 1.5 times as fast.
+    // of it), 62 so; how many are enough: kRowTableBytes.
     FinalPlan fp;
     if ((rc = ba::plan_final(heads, n_prompts, cu_q, pl.cu_ctx.data(), BA_ROPE_APPLY, k_f_rot_out != nullptr, num_cus(), &fp))) return rc;
     const size_t row_b = (size_t)heads->n_kv_heads * D * 2;

@@ -160,6 +160,9 @@ constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 // 76, eight of 20 x 100-300 and 32-128 224 / 141 / 144 / 150; 8 over 2, two of 6 x 370-1105 215 / 155 / 132 / 128; 32 over
 // 8 of 128, three of 11 x 117-351 and 13-40 252 / 241 / 223 / 225, two of 21 x 134-396 and 31-94 465 / 465 / 368 / 358.  But
 // eight of 20 x 100-300 and 32-128 there, which fill the chip by themselves, 967 / 967 / 972 / 974: hence 24.
+// (Sharing does not stop to pay at kShareAbove either: 48 calls of one and two prompts with walks of 18 to 36 tiles take
+// 0.74 to 0.94 of the time when theirs are shared too.  It lies above the 35 tiles up to which ba_schedule_prompts
+// has always listed one item per row tile.)
 // Into how many parts a walk is cut follows from the block's own sizes; whether any is cut, from the call: only if
 // the longest of them is kShareLoad or more of what each compute unit has to do.  A launch that fills the chip hides a long walk
 // and pays for cutting it (each part loads and turns its query rows again, and K and V are read in a burst): 64
@@ -182,19 +185,20 @@ constexpr double kSharePartTiles = 24.0;  // head_dim 128
 constexpr int kShareLead = 100;
 constexpr size_t kShareMaxBytes = (size_t)256 << 20;
 // ... and the same for the walks of the dk/dv kernel (0.73 us a tile; a key tile's rows are its block's and the last
-// block's).  Forward and backward, us, unshared / shared: 8 over 2 heads of 64, five prompts of 4 x 350-1040 tokens and
-// a last block of 100-300: 272 / 217, two of 16 x 70-200: 104 / 83; 32 over 8 of 128, two of 4 x 26-78 and 74-223: 76 / 69,
-// two of 3 x 134-402: 129 / 105; two of 29 x 88-262: 374 / 371;
-// three of 11 x 117-351 221 / 222 (232 with chunks a third shorter).  From 17 tiles on instead of 22: 4 over 4 of 64, one of
-// 9 x 250-750 73 / 67, but 32 over 8, two of 22 x 37-112 120 / 122 and 16 over 8, four of 4 x 100-298 106 / 108.
+// block's).  Forward and backward, us, dk/dv unshared / shared: 8 over 2 heads of 64, five prompts of 4 x 700 tokens and a last
+// block of 200 244 / 221, two of 16 x 135 + 64 70 / 64; 32 over 8 of 128, two of 4 x 52 + 150 73 / 69, two of 3 x 268 + 144
+// 133 / 120, one of 3 x 164 + 4 72 / 65; three of 11 x 234 + 26 256 / 256.  Sharing does not stop to pay at kKvShareAbove:
+// 80 calls of one and two prompts with walks of 14 to 21 tiles take 0.88 to 1.00 of the time when theirs are shared too.
+// It lies where calls of short passages (100 tokens, a last block of 64) ask for no more workspace than without.
 // In calls whose longest such walk is more than kKvShareLoad of what every one of kShareCus compute units has to do
 // (a call that fills the chip adds up in one order, whatever else is in the batch), in chunks of half of that.
 // Four query heads and more per KV head of 128, where that walk is less than kKvShareLight of that load: only if it is
 // kKvShareLead tiles longer than what is left when it is cut (the longest part, the longest walk that stays,
 // kKvShareLoad of the load).  The 64 KB of every part, out past the caches and in again, take the time of some ten
-// tiles.  52 calls of 1 to 15 prompts, tiles gained and time shared / unshared of forward and backward: below 9 0.96 to 1.09 (64
-// over 8, ten prompts of 4 x 45-135 + 5, dk/dv 164 us of a call and 14 more of it; 32 over 8, three of 5 x 140-195 + 12, 34 us and 37), a third of
-// them slower; from 9 on 0.71 to 0.99, one 1.02.  Smaller groups and head_dim 64 gain below 9 too: 24 calls, 0.88 to 1.00.
+// tiles.  52 calls of 1 to 15 prompts, tiles gained and time shared / unshared of forward and backward: below 9 0.96 to
+// 1.09, a third of them slower (64 over 8, ten prompts of 4 x 45-135 + 5 tokens 176 / 160 us; 32 over 8, three of 5 x 140-195
+// + 12, the dk/dv kernel 37 / 34); from 9 on 0.71 to 0.99, one 1.02.  Smaller groups and head_dim 64 gain below 9 too: 24
+// calls, 0.88 to 1.00.
 constexpr int kKvShareAbove = 21, kKvShareChunk = 12, kShareCus = 256, kKvShareLead = 9;
 constexpr double kKvShareLoad = 0.75, kKvShareLight = 1.5;
 
