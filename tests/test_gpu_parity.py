@@ -912,8 +912,8 @@ GATHER_CASES = [  # (Hq, Hkv, D, tokens of each prompt's cached blocks, query to
                                                       "tiny-blocks-d64-table", "one-token-context-table", "long-d64-table",
                                                       "table-from-here", "copied-to-here"])
 def test_gathered_calls_give_the_bits_of_a_context_gathered_by_hand(ba, case, layout):
-    """Short cached blocks: keys gathered by the call, value rows fetched through its table of where they lie.  The
-    same keys re-encoded into one context by the caller, the values copied there, must give the same bits: contexts
+    """Short cached blocks: keys gathered by the call, value rows fetched through its table of where they lie (from 4 MB
+    of them on; less is copied with the keys).  The same keys re-encoded into one context by the caller, the values copied there, must give the same bits: contexts
     that end inside a key tile and at its edge, splits that hold no context tile, value rows of another stride
     between rows of NaN, whatever the workspace held; several times, as tiles arrive in any order."""
     torch = torch_mod()
