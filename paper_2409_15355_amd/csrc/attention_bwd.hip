@@ -175,6 +175,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   const int rowtile = (int)(id - (uint32_t)kvh * n_rowtiles);
   const int b = find_block(meta.tile_start, rowtile);
   const int q_tok0 = meta.start[b], lq = meta.len[b], k_tok0 = meta.kstart[b];
+  const int pos0 = meta.pos0[b];  // position of the block's first token
   int jt = rowtile - meta.tile_start[b];
   const int dq = q_tok0 - k_tok0;  // the block's first token, counted in keys
   const int lk = dq + lq;          // keys up to the block's end
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   const uint32_t s_ofs = 2 * (2 * TB) + wave * G::SLICEB;
   const int first_tok_wave = first_key_wave - dq;
   if (Gq >= 4) {
-    const char *tbase = (const char *)(p.q_table + (int64_t)q_tok0 * D);
+    const char *tbase = (const char *)(p.q_table + (int64_t)pos0 * D);
 #pragma unroll
     for (int u = 0; u < kTabOps; ++u) {
       const int t = u * (1024 / TROW) + lane / TCH, pc = lane % TCH;
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   // ---- whole rows -> B-operand fragments (lane = row), 16 rows at a time through this wave's slice ----
   f32x4_t cs[2 * G::KCH];
   if (Gq < 4) {
-    const f32x4_t *row = reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(q_tok0 + my_tok) * D);
+    const f32x4_t *row = reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(pos0 + my_tok) * D);
 #pragma unroll
     for (int j = 0; j < 2 * G::KCH; ++j) cs[j] = row[fragment_table_piece(j, hf, p.rope_layout != 0)];
   } else {
@@ -492,7 +493,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
       }
     }
   }
-  rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(q_tok0 + my_tok) * D), ehf,
+  rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(pos0 + my_tok) * D), ehf,
                  p.rope_layout != 0, kLn2);
   lds_char *stage = smem + wave * G::TILEB;
 #pragma unroll
@@ -821,7 +822,7 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
     }
   }
   if (is_b)
-    rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(k_tok0 + min(kw0 + ecol, lk - 1)) * D), ehf,
+    rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(meta.pos0[b] + min(kw0 + ecol, lk - 1)) * D), ehf,
                    p.rope_layout != 0, kLn2 / p.scale_log2e);
   static_assert(kBWaves * (size_t)G::TILEB <= KG::LDS, "the output staging fits");
   lds_char *stage = smem + wave * G::TILEB;

@@ -91,10 +91,12 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   const int rowtile = kPrompt ? (int)id_lo : (int)(n_rowtiles - 1 - id_lo);
   const int b = find_block(meta.tile_start, rowtile);
   int q_tok0, lq, k_tok0;  // the block's first token, its length, the first key it sees
+  int pos0 = 0;            // position of the block's first token
   if constexpr (kPrompt) {
     q_tok0 = meta.start[b];
     lq = meta.len[b];
     k_tok0 = meta.kstart[b];
+    pos0 = meta.pos0[b];
   } else {
     q_tok0 = meta.offs[b];
     lq = meta.offs[b + 1] - q_tok0;
@@ -191,8 +193,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     if (p.q_table && Gq >= 4) {
       // The rows of a wave span at most 8 tokens.  Chunk c of token row t sits at chunk c ^ (t & 7),
       // which keeps the reads of different tokens off each other's banks.
-      // (a row per token of the call, or, for per-block encoding, a row per position inside the block)
-      const char *tbase = (const char *)(p.q_table + (p.q_table_by_pos ? (int64_t)0 : (int64_t)q_tok0 * D));
+      const char *tbase = (const char *)(p.q_table + (int64_t)pos0 * D);
 #pragma unroll
       for (int u = 0; u < kTabOps; ++u) {
         const int t = u * (1024 / TROW) + lane / TCH, pc = lane % TCH;
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
     // Fewer heads than that share a token's row of the table, down to one: hardly any of it would be read
     // twice, so every lane takes its pieces from where they lie.
     const int tok = (int)fast_div((uint32_t)min(my_row, n_rows - 1), p.group_div);
-    const f32x4_t *row = reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)((p.q_table_by_pos ? 0 : q_tok0) + tok) * D);
+    const f32x4_t *row = reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(pos0 + tok) * D);
 #pragma unroll
     for (int j = 0; j < 2 * G::KCH; ++j) cs[j] = row[fragment_table_piece(j, hf, p.rope_layout != 0)];
   } else if (p.q_table) {

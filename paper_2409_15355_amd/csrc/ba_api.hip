@@ -199,14 +199,11 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
   p.layout = h->rope_layout;
   // few tokens: one head per thread (more, shorter threads); many: sin/cos shared by several heads
   p.heads_per_thread = tokens >= 16384 ? 8 : (tokens >= 2048 ? 2 : 1);
-  p.do_q = q_table ? 2 : 1;  // a table of factors for the attention core, or rotated rows
+  // rotated rows; or a table of factors by position for the attention core; or (the table of this call is already
+  // written) keys only
+  p.do_q = !q_table ? 1 : (table_rows > 0 ? 2 : 0);
   p.q_table = q_table;
-  if (table_rows > 0) {  // the table by position (every segment starts at position 0), no rotated rows
-    p.do_q = 4;
-    p.table_rows = table_rows;
-  } else if (table_rows < 0) {  // keys only: the table of this call is already written
-    p.do_q = 0;
-  }
+  p.table_rows = table_rows;
   p.do_k = 1;
   p.rot_dst = rot_dst;
   p.n_rot = n_rot;
@@ -528,7 +525,6 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
   ap.q_st = q->stride_tok;
   ap.q_sh = q->stride_head;
   ap.q_table = q_table;
-  ap.q_table_by_pos = 1;
   ap.kf = (const uint16_t *)k_use.ptr;
   ap.kf_st = k_use.stride_tok;
   ap.kf_sh = k_use.stride_head;
@@ -573,7 +569,7 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
       // local positions: every block starts at 0, so one table of factors by position serves all blocks
       // (as many rows as the longest block has tokens; written by the first launch)
       if ((rc = run_rope_prepass(heads, rt, q, nullptr, k, &k_use, n, meta[0].offs, nullptr, stream, nullptr, nullptr,
-                                 nullptr, 0, q_table, table_written ? -1 : (int)longest_block)))
+                                 nullptr, 0, q_table, table_written ? 0 : (int)longest_block)))
         return rc;
       table_written = true;
     }

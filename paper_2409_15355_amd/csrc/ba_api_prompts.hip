@@ -98,7 +98,7 @@ size_t least_bytes(const ba_heads *h, size_t T, int32_t rope_mode, bool have_k_r
     bytes = 2 * padded_rows_bytes(h, T) + padded_lse_bytes(h, T);
   if (rope_mode != BA_ROPE_APPLY) return bytes;
   if (!have_k_rot_out) bytes += align256(T * h->n_kv_heads * h->head_dim * 2);  // rotated K
-  return bytes + align256(T * h->head_dim * 4);                                 // scale * (cos, sin) per token and pair
+  return bytes + align256(T * h->head_dim * 4);                                 // scale * (cos, sin) per position and pair (at most T)
 }
 size_t bwd_least_bytes(const ba_heads *h, size_t T) {
   const size_t D = h->head_dim, hkv = h->n_kv_heads;
@@ -110,6 +110,27 @@ size_t bwd_least_bytes(const ba_heads *h, size_t T) {
   // rotated scaled q, rotated k, the table of rotation factors, (log-sum-exp, delta) per row
   return pad_bytes + align256(T * hq * D * 2) + align256(T * hkv * D * 2) + align256(T * D * 4) +
          align256(T * hkv * ld_group((int32_t)(hq / hkv)) * 8 + 16);
+}
+// RoPE pre-pass of whole prompts: rotated keys, positions counting from each prompt's first token (one segment per prompt);
+// the table of factors by position, as many rows as the longest prompt has tokens, written by the first launch that has any.
+int32_t rotate_prompts(const ba_heads *h, const ba::RopeTable &rt, const ba_tensor *q, const ba_tensor *k, const ba_tensor *k_rot,
+                       int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets, hipStream_t stream, float *q_table,
+                       int32_t *zero, int n_zero) {
+  std::vector<int32_t> starts(n_prompts + 1);
+  int32_t rows = 0;
+  for (int n = 0; n <= n_prompts; ++n) {
+    starts[n] = block_offsets[cu_blk[n]];
+    if (n > 0) rows = std::max(rows, starts[n] - starts[n - 1]);
+  }
+  for (int n0 = 0; n0 < n_prompts; n0 += ba::kRopeMaxSegs) {
+    const int n = std::min(ba::kRopeMaxSegs, n_prompts - n0);
+    if (starts[n0 + n] == starts[n0]) continue;
+    const int32_t rc = run_rope_prepass(h, rt, q, nullptr, k, k_rot, n, starts.data() + n0, nullptr, stream, nullptr, nullptr,
+                                        nullptr, 0, q_table, rows, zero, n_zero);
+    if (rc) return rc;
+    rows = 0;
+  }
+  return BA_OK;
 }
 // Where a launch's shared walks leave their partial results, from wsp on.
 void place_shares(const ba::WalkShares &shares, char *wsp, ba::AttnParams *ap) {
@@ -215,15 +236,9 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
     shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
     if ((size_t)(wsp - (char *)ws) + shares.total() > ws_bytes) shares = ba::WalkShares();
     place_shares(shares, wsp, &ap);
-    // positions count from each prompt's first token: one segment per prompt
-    std::vector<int32_t> starts(n_prompts + 1);
-    for (int n = 0; n <= n_prompts; ++n) starts[n] = block_offsets[cu_blk[n]];
-    for (int n0 = 0; n0 < n_prompts; n0 += ba::kRopeMaxSegs) {
-      const int n = std::min(ba::kRopeMaxSegs, n_prompts - n0);
-      if ((rc = run_rope_prepass(heads, rt, q, nullptr, k, &k_use, n, starts.data() + n0, nullptr, stream, nullptr,
-                                 nullptr, nullptr, 0, q_table, 0, ap.part_idx, (int)(shares.count_bytes / 4))))
-        return rc;
-    }
+    if ((rc = rotate_prompts(heads, rt, q, k, &k_use, n_prompts, cu_blk, block_offsets, stream, q_table, ap.part_idx,
+                             (int)(shares.count_bytes / 4))))
+      return rc;
   }
 
   ap.q = (const uint16_t *)q->ptr;
@@ -376,15 +391,9 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
 
   ba::RopeTable rt;
   build_rope_table(heads, &rt);
-  // positions count from each prompt's first token: one segment per prompt
-  std::vector<int32_t> starts(n_prompts + 1);
-  for (int n = 0; n <= n_prompts; ++n) starts[n] = block_offsets[cu_blk[n]];
-  for (int n0 = 0; n0 < n_prompts; n0 += ba::kRopeMaxSegs) {
-    const int n = std::min(ba::kRopeMaxSegs, n_prompts - n0);
-    if ((rc = run_rope_prepass(heads, rt, q, nullptr, k, &k_rot, n, starts.data() + n0, nullptr, stream, nullptr, nullptr,
-                               nullptr, 0, q_table, 0, ap.part_idx, (int)((shares.count_bytes + kv_shares.count_bytes) / 4))))
-      return rc;
-  }
+  if ((rc = rotate_prompts(heads, rt, q, k, &k_rot, n_prompts, cu_blk, block_offsets, stream, q_table, ap.part_idx,
+                           (int)((shares.count_bytes + kv_shares.count_bytes) / 4))))
+    return rc;
 
   ba::BwdParams bp;
   memset(&bp, 0, sizeof(bp));

@@ -101,9 +101,8 @@ struct RopePrepassParams {
   int32_t do_q, do_k;
   float *rot_dst;    // [n_rot][D/2][2]: (cos, sin) of rot_angle[b] * theta_j, or null
   int32_t n_rot;
-  float *q_table;    // do_q == 2: instead of rotating Q rows, write q_scale * (cos, sin) per token: [tokens][D/2][2];
-                     // do_q == 4: the table only, by position: row r = q_scale * (cos, sin) of position r,
-                     //            r < table_rows (for calls all of whose segments start at position 0)
+  float *q_table;    // do_q == 2: instead of rotating Q rows, write q_scale * (cos, sin) by position: [table_rows][D/2][2]
+                     // (for calls all of whose segments start at position 0)
   int32_t table_rows;
   int32_t *zero;     // n_zero words cleared on the way (counters of the attention launch behind this one)
   int32_t n_zero;
@@ -231,10 +230,11 @@ struct AttnParams {
   float scale_log2e;  // softmax scale * log2(e)
   int32_t q_ready;    // q is already rotated and multiplied by scale_log2e (the RoPE pre-pass ran)
   int32_t q_rows_fit32;  // main core, filled at the launch: 32 tokens and a group of heads of q span less than 2^32 bytes
-  const float *q_table;  // else, if non-null: [tokens][D/2][2] = scale_log2e * (cos, sin) of each
-                         // token's position times theta_j; the kernel rotates q with it
-  int32_t q_table_by_pos;  // ... or, if set, [positions][D/2][2]: a row per position inside the block (per-block
-                           // encoding, where every block starts at position 0 and the blocks share one table)
+  // else, if non-null: [positions][D/2][2] = scale_log2e * (cos, sin) of the position times theta_j; the kernel rotates q with
+  // it.  A row per position, not per token, so that blocks (per-block encoding, where all start at 0) and prompts share
+  // them: every XCD reads the rows for its own KV heads, and 2 MB by position stay in its L2 where 17 MB by token (eight prompts,
+  // 33,746 tokens, head_dim 128) did not: forward and backward 967 -> 957 us, of that 6 in the two pre-passes that write it.
+  const float *q_table;
   int32_t rope_layout;
   const float *blk_rot;  // block table only: [blocks][D/2][2] (cos, sin) of minus each block's shift
   int32_t n_splits;
@@ -269,6 +269,7 @@ struct PromptMeta {
   int32_t len[kEncMaxBlocks];
   int32_t tile_start[kEncMaxBlocks + 1];  // in row tiles of kShortTileRows rows; INT_MAX beyond [n]
   int32_t kstart[kEncMaxBlocks];          // token offset of the first visible key
+  int32_t pos0[kEncMaxBlocks];            // position of the first token inside its prompt
   // The first n_split blocks' walks are shared out: a block whose last row walks w key tiles is taken by
   // shared_walk_splits(w, kShareChunk, row tiles x KV heads, kSharePairs) workgroups per row tile and KV head (all row
   // tiles of split 0 first, then of split 1 ...)
@@ -298,6 +299,7 @@ struct BwdKvMeta {
   int32_t n;
   int32_t start[kEncMaxBlocks];
   int32_t len[kEncMaxBlocks];
+  int32_t pos0[kEncMaxBlocks];            // position of the first token inside its prompt
   int32_t tile_start[kEncMaxBlocks + 1];  // in key tiles of kBwdTileKeys keys; INT_MAX beyond [n]
   int32_t fin_start[kEncMaxBlocks];
   int32_t fin_len[kEncMaxBlocks];          // 0: the block is its prompt's last

@@ -389,7 +389,7 @@ std::vector<PromptBlock> list_prompt_blocks(int32_t n_prompts, const int32_t *cu
       if (len == 0) continue;
       // first key a block sees: its own first token, or for a prompt's last block the prompt's
       blks.push_back({block_offsets[b], len, b == last ? block_offsets[cu_blk[n]] : block_offsets[b], fs,
-                      b == last ? 0 : fl, n});
+                      b == last ? 0 : fl, n, block_offsets[b] - block_offsets[cu_blk[n]]});
     }
   }
   return blks;
@@ -513,6 +513,7 @@ int64_t build_kv_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, in
     const PromptBlock &b = blks[b0 + i];
     meta->start[i] = b.start;
     meta->len[i] = b.len;
+    meta->pos0[i] = b.pos0;
     meta->fin_start[i] = b.fin_start;
     meta->fin_len[i] = b.fin_len;
     meta->tile_start[i] = (int32_t)tiles;
@@ -546,6 +547,7 @@ int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n
     meta->start[i] = b.start;
     meta->len[i] = b.len;
     meta->kstart[i] = b.kstart;
+    meta->pos0[i] = b.pos0;
     meta->tile_start[i] = (int32_t)tiles;
     tiles += short_row_tiles(b.len, G) * (i < meta->n_split ? shared_splits((int64_t)b.start - b.kstart, b.len, G, n_kv_heads) : 1);
     if (tiles > 0x3fffffff) return -1;

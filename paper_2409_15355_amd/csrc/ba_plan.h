@@ -104,7 +104,7 @@ int64_t encode_short_max(const ba_heads *h, int32_t n_blocks, const int32_t *off
 // Whole prompts (Section 2.4): non-empty blocks with the first key they see and (for passages) their
 // prompt's last block.
 struct PromptBlock {
-  int32_t start, len, kstart, fin_start, fin_len, prompt;
+  int32_t start, len, kstart, fin_start, fin_len, prompt, pos0;  // pos0: position of the first token inside its prompt
 };
 std::vector<PromptBlock> list_prompt_blocks(int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets);
 // Which last blocks have their walks shared by several workgroups (PromptMeta::n_split), and the memory that takes.

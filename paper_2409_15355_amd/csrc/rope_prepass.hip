@@ -76,8 +76,8 @@ __global__ __launch_bounds__(kThreads) void rope_prepass_kernel(RopePrepassParam
   const bool is_q = (int)blockIdx.y < groups_q;
   int t = segs.start[0] + blockIdx.x * TPP + threadIdx.x / TPV;
   int pos;
-  if (is_q && p.do_q == 4) {
-    // the table by position: this thread's row is a position, not a token
+  if (is_q && p.do_q == 2) {
+    // the table of factors: this thread's row is a position, not a token
     t = blockIdx.x * TPP + threadIdx.x / TPV;
     if (t >= p.table_rows) return;
     pos = t;
@@ -113,8 +113,8 @@ __global__ __launch_bounds__(kThreads) void rope_prepass_kernel(RopePrepassParam
       sn[e] *= scale;
     }
   }
-  if (is_q && p.do_q != 1) {
-    // the factors themselves, for the attention core to rotate q with: entry j at [t][j] = (cos, sin)
+  if (is_q && p.do_q == 2) {
+    // the factors themselves, for the attention core to rotate q with: entry j at [position][j] = (cos, sin)
     float2 *row = reinterpret_cast<float2 *>(p.q_table) + (int64_t)t * (D / 2);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
@@ -161,8 +161,8 @@ hipError_t launch_d(RopePrepassParams p, const Segs &segs, const RopeTable &rt, 
   const int64_t tokens = (int64_t)segs.start[segs.n] - segs.start[0];
   const int groups = q_groups(p) + (p.do_k ? (p.n_kv_heads + p.heads_per_thread - 1) / p.heads_per_thread : 0);
   if (tokens <= 0 || groups == 0) return hipSuccess;
-  // (a table by position has rows of its own to cover; it never has more of them than the call has tokens)
-  const int64_t span = std::max<int64_t>(tokens, p.do_q == 4 ? p.table_rows : 0);
+  // (a table has rows of its own to cover, perhaps more than this launch has tokens)
+  const int64_t span = std::max<int64_t>(tokens, p.do_q == 2 ? p.table_rows : 0);
   const unsigned gx = (unsigned)((span + TPP - 1) / TPP);
   RopeRotsSmall none;
   unsigned rot_rows = 0;

@@ -1210,6 +1210,35 @@ def test_whole_prompts_agree_with_the_three_step_path(ba):
     assert np.max(np.abs(host_f64(o2) - og)) <= 2e-2
 
 
+@pytest.mark.parametrize("empty", [320, 333])
+def test_whole_prompts_whose_table_of_factors_comes_from_a_later_launch(ba, empty):
+    """The pre-pass takes 320 prompts a launch and writes the table by position once: with the first that has
+    tokens, for the longest prompt of all.  Empty prompts ahead, the longest in the launch behind: the bits of the
+    call without the empty ones."""
+    torch = torch_mod()
+    hq, hkv, d = 4, 2, 64
+    prompts = [[33, 20], [70, 0, 40, 31], [5]]
+    seen = []
+    for lead in (0, empty):
+        lens = [0] * lead + [l for p in prompts[:1] for l in p] + [0] * lead + [l for p in prompts[1:] for l in p]
+        offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        cnt = [1] * lead + [len(prompts[0])] + [1] * lead + [len(p) for p in prompts[1:]]
+        cu_blk = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32)
+        T = int(offs[-1])
+        qb, kb, vb = gen_qkv(330, T, hq, hkv, d)
+        heads = ba.Heads(hq, hkv, d, 10000.0)
+        o, k_rot, lse = gpu_prompts(ba, heads, qb, kb, vb, cu_blk, offs)
+        do = dev_bf16(wl.normal_bf16_bits(331, (T, hq, d)))
+        q, k, v = dev_bf16(qb), dev_bf16(kb), dev_bf16(vb)
+        grads = [torch.full_like(x, float("nan")) for x in (q, k, v)]
+        n = ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs)
+        ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, *grads, cu_blk, offs,
+                                               torch.full((n,), 0xff, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        seen.append([t.view(torch.uint8).cpu() for t in (o, k_rot, lse, *grads)])
+    assert all(torch.equal(a, b) for a, b in zip(*seen))
+
+
 def test_whole_prompts_config_3_sampled(ba):
     """Config 3's eight prompts (20 ragged passages each) with their query blocks appended, in one
     call; sampled rows against the oracle's per-block encoding (passages) and final-block attention
