@@ -109,42 +109,48 @@ float scale_log2e(const ba_heads *h) {
 }
 
 
+// Blocks [b0, b0 + n) of the list into the table of one launch (empty ones dropped), and how that launch spreads them.
+template <typename Blocks, typename Params>
+static void fill_blocks(Params *p, Blocks *blk, int n_blocks, int b0, int n, int32_t table_end, const int32_t *src_off, const int32_t *dst_off,
+                        const int32_t *len, const int32_t *pos_old, const int32_t *pos_new) {
+  memset(blk, 0, sizeof(*blk));
+  int filled = 0, max_len = 0;
+  for (int i = 0; i < n; ++i) {
+    const int b = b0 + i;
+    if (len[b] == 0) continue;
+    blk->src_off[filled] = src_off[b];
+    blk->dst_off[filled] = dst_off[b];
+    blk->len[filled] = len[b];
+    blk->pos_old[filled] = pos_old ? pos_old[b] : 0;
+    blk->pos_new[filled] = pos_new ? pos_new[b] : dst_off[b];
+    max_len = std::max(max_len, len[b]);
+    ++filled;
+  }
+  blk->n = filled;
+  if constexpr (std::is_same<Params, ba::ReencRowsParams>::value) p->table_end = b0 + n < n_blocks ? dst_off[b0 + n] : table_end;
+  p->max_len = max_len;
+  // few tokens: one head per thread (more workgroups, shorter dependent chains);
+  // many tokens: all heads in one thread (sin/cos computed once per token)
+  int64_t tokens = 0;
+  for (int i = 0; i < filled; ++i) tokens += blk->len[i];
+  tokens *= p->n_layers;
+  p->heads_per_thread = tokens >= 65536 ? p->n_kv_heads : (tokens >= 8192 ? std::min(p->n_kv_heads, 4) : 1);
+  p->n_head_groups = (p->n_kv_heads + p->heads_per_thread - 1) / p->heads_per_thread;
+}
+
 // Run the rotation kernel over a list of blocks, a launch per table-full of them.
 template <typename Blocks, typename Params>
 static int32_t run_reencode_t(Params p, const ba::RopeTable &rt, int n_blocks, const int32_t *src_off,
                        const int32_t *dst_off, const int32_t *len, const int32_t *pos_old,
                        const int32_t *pos_new, hipStream_t stream) {
-  constexpr bool kRows = std::is_same<Params, ba::ReencRowsParams>::value;
   int32_t table_end = 0;
-  if constexpr (kRows) table_end = p.table_end;
+  if constexpr (std::is_same<Params, ba::ReencRowsParams>::value) table_end = p.table_end;
   std::vector<Blocks> tab(1);  // (the large table is too big for the stack of a small thread)
   Blocks &blk = tab[0];
   for (int b0 = 0; b0 < n_blocks; b0 += Blocks::kBlocks) {
-    memset(&blk, 0, sizeof(blk));
     const int n = std::min(Blocks::kBlocks, n_blocks - b0);
-    int filled = 0, max_len = 0;
-    for (int i = 0; i < n; ++i) {
-      const int b = b0 + i;
-      if (len[b] == 0) continue;
-      blk.src_off[filled] = src_off[b];
-      blk.dst_off[filled] = dst_off[b];
-      blk.len[filled] = len[b];
-      blk.pos_old[filled] = pos_old ? pos_old[b] : 0;
-      blk.pos_new[filled] = pos_new ? pos_new[b] : dst_off[b];
-      max_len = std::max(max_len, len[b]);
-      ++filled;
-    }
-    if (!filled) continue;
-    blk.n = filled;
-    if constexpr (kRows) p.table_end = b0 + n < n_blocks ? dst_off[b0 + n] : table_end;
-    p.max_len = max_len;
-    // few tokens: one head per thread (more workgroups, shorter dependent chains);
-    // many tokens: all heads in one thread (sin/cos computed once per token)
-    int64_t tokens = 0;
-    for (int i = 0; i < filled; ++i) tokens += blk.len[i];
-    tokens *= p.n_layers;
-    p.heads_per_thread = tokens >= 65536 ? p.n_kv_heads : (tokens >= 8192 ? std::min(p.n_kv_heads, 4) : 1);
-    p.n_head_groups = (p.n_kv_heads + p.heads_per_thread - 1) / p.heads_per_thread;
+    fill_blocks(&p, &blk, n_blocks, b0, n, table_end, src_off, dst_off, len, pos_old, pos_new);
+    if (!blk.n) continue;
     hipError_t e;
     {
       ProfileScope ps(BA_PROFILE_REENCODE, stream);
@@ -168,15 +174,8 @@ template int32_t run_reencode(ba::ReencParams, const ba::RopeTable &, int, const
 template int32_t run_reencode(ba::ReencRowsParams, const ba::RopeTable &, int, const int32_t *, const int32_t *,
                               const int32_t *, const int32_t *, const int32_t *, hipStream_t);
 
-// Rotate fresh Q (into q_rot, packed, pre-scaled) and fresh K (into k_rot) for segments
-// [seg0, seg0 + n) given by start offsets and first positions.
-int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_tensor *q, uint16_t *q_rot,
-                         const ba_tensor *k, const ba_tensor *k_rot, int n, const int32_t *start,
-                         const int32_t *pos0, hipStream_t stream, const ba::RopeRots *rots,
-                         const ba::RopeRotsSmall *rots_small, float *rot_dst, int n_rot, float *q_table, int table_rows,
-                         int32_t *zero, int n_zero) {
-  const int64_t tokens = (int64_t)start[n] - start[0];
-  if (tokens <= 0) return BA_OK;
+static ba::RopePrepassParams prepass_params(const ba_heads *h, const ba_tensor *q, uint16_t *q_rot, const ba_tensor *k,
+                                            const ba_tensor *k_rot, int64_t tokens) {
   ba::RopePrepassParams p;
   memset(&p, 0, sizeof(p));
   const int D = h->head_dim;
@@ -199,24 +198,42 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
   p.layout = h->rope_layout;
   // few tokens: one head per thread (more, shorter threads); many: sin/cos shared by several heads
   p.heads_per_thread = tokens >= 16384 ? 8 : (tokens >= 2048 ? 2 : 1);
+  p.do_q = 1;
+  p.do_k = 1;
+  return p;
+}
+template <typename Segs>
+static void fill_segments(Segs *segs, int n, const int32_t *start, const int32_t *pos0) {
+  memset(segs, 0, sizeof(*segs));
+  segs->n = n;
+  for (int i = 0; i < n; ++i) {
+    segs->start[i] = start[i];
+    segs->pos0[i] = pos0 ? pos0[i] : 0;
+  }
+  segs->start[n] = start[n];
+}
+
+// Rotate fresh Q (into q_rot, packed, pre-scaled) and fresh K (into k_rot) for segments
+// [seg0, seg0 + n) given by start offsets and first positions.
+int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_tensor *q, uint16_t *q_rot,
+                         const ba_tensor *k, const ba_tensor *k_rot, int n, const int32_t *start,
+                         const int32_t *pos0, hipStream_t stream, const ba::RopeRots *rots,
+                         const ba::RopeRotsSmall *rots_small, float *rot_dst, int n_rot, float *q_table, int table_rows,
+                         int32_t *zero, int n_zero) {
+  const int64_t tokens = (int64_t)start[n] - start[0];
+  if (tokens <= 0) return BA_OK;
+  ba::RopePrepassParams p = prepass_params(h, q, q_rot, k, k_rot, tokens);
   // rotated rows; or a table of factors by position for the attention core; or (the table of this call is already
   // written) keys only
   p.do_q = !q_table ? 1 : (table_rows > 0 ? 2 : 0);
   p.q_table = q_table;
   p.table_rows = table_rows;
-  p.do_k = 1;
   p.rot_dst = rot_dst;
   p.n_rot = n_rot;
   p.zero = zero;
   p.n_zero = n_zero;
   auto fill_and_launch = [&](auto &segs) {
-    memset(&segs, 0, sizeof(segs));
-    segs.n = n;
-    for (int i = 0; i < n; ++i) {
-      segs.start[i] = start[i];
-      segs.pos0[i] = pos0 ? pos0[i] : 0;
-    }
-    segs.start[n] = start[n];
+    fill_segments(&segs, n, start, pos0);
     ProfileScope ps(BA_PROFILE_REENCODE, stream);
     return ba::launch_rope_prepass(p, segs, rots, rots_small, rt, stream);
   };
@@ -233,11 +250,40 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
 }
 
 
+// The gather of a final block's context and the pre-pass of its first launch's prompts, together.
+template <typename Blocks, typename Params>
+static int32_t run_gather_prepass_t(Params gp, const Gather &g, const ba::RopePrepassParams &pp, const ba::RopeSegsGather &segs,
+                                    const ba::RopeTable &rt, hipStream_t stream) {
+  std::vector<Blocks> tab(1);
+  int32_t table_end = 0;
+  if constexpr (std::is_same<Params, ba::ReencRowsParams>::value) table_end = gp.table_end;
+  fill_blocks(&gp, &tab[0], g.n_blocks, 0, g.n_blocks, table_end, g.src_off, g.dst_off, g.len, g.pos_old, g.pos_new);
+  hipError_t e;
+  {
+    ProfileScope ps(BA_PROFILE_REENCODE, stream);
+    e = ba::launch_gather_prepass(gp, tab[0], pp, segs, rt, stream);
+  }
+  if (e != hipSuccess) return device_fail(e, "gather launch");
+  return BA_OK;
+}
+static int32_t run_gather_prepass(const ba_heads *h, const Gather &g, const ba::RopeTable &rt, const ba_tensor *q, uint16_t *q_rot,
+                                  const ba_tensor *k, const ba_tensor *k_rot, int n, const int32_t *start, const int32_t *pos0,
+                                  hipStream_t stream) {
+  const ba::RopePrepassParams pp = prepass_params(h, q, q_rot, k, k_rot, (int64_t)start[n] - start[0]);
+  ba::RopeSegsGather segs;
+  fill_segments(&segs, n, start, pos0);
+  const ba::ReencParams &plain = g.p;
+  if (g.n_blocks <= ba::kReencMaxBlocks)
+    return g.p.row_table ? run_gather_prepass_t<ba::ReencBlocks>(g.p, g, pp, segs, rt, stream)
+                         : run_gather_prepass_t<ba::ReencBlocks>(plain, g, pp, segs, rt, stream);
+  return g.p.row_table ? run_gather_prepass_t<ba::ReencBlocksLarge>(g.p, g, pp, segs, rt, stream)
+                       : run_gather_prepass_t<ba::ReencBlocksLarge>(plain, g, pp, segs, rt, stream);
+}
 
 int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,
                     const ba_tensor *k_f, const ba_tensor *v_f, const ba_tensor *o_out, const ba_tensor *k_f_rot_out,
                     int32_t n_prompts, const int32_t *cu_q, const int32_t *cu_ctx, const int32_t *q_pos0,
-                    int32_t rope_mode, void *ws, size_t ws_bytes, void *stream_, const GatheredRows *rows) {
+                    int32_t rope_mode, void *ws, size_t ws_bytes, void *stream_, const Gather *gather) {
   hipStream_t stream = (hipStream_t)stream_;
   int32_t rc;
   if ((rc = check_heads(heads, true))) return rc;
@@ -357,18 +403,21 @@ int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor
                                   &ap.xcd_runs)))
       return rc;
     if (rope_mode == BA_ROPE_APPLY) {  // absolute positions of the final block's tokens
-      if ((rc = run_rope_prepass(heads, rt, q_f, q_ws, k_f, &kf_use, n, meta.cu_q, pos0.data() + n0, stream)))
-        return rc;
+      if (gather && n0 == 0 && gather->n_blocks > 0)
+        rc = run_gather_prepass(heads, *gather, rt, q_f, q_ws, k_f, &kf_use, n, meta.cu_q, pos0.data(), stream);
+      else
+        rc = run_rope_prepass(heads, rt, q_f, q_ws, k_f, &kf_use, n, meta.cu_q, pos0.data() + n0, stream);
+      if (rc) return rc;
     }
     hipError_t e;
     {
       ProfileScope ps(BA_PROFILE_ATTENTION, stream);
-      if (rows) {  // (one launch: the caller's check)
+      if (gather && gather->p.row_table) {  // (one launch: the caller's check)
         ba::FinalGatherMeta gm;
         memset(&gm, 0, sizeof(gm));
         static_cast<ba::FinalMeta &>(gm) = meta;
-        gm.rows = rows->rows;
-        for (int i = 0; i < n; ++i) gm.ctx0[i] = rows->ctx0[i];
+        gm.rows = gather->p.row_table;
+        for (int i = 0; i < n; ++i) gm.ctx0[i] = gather->ctx0[i];
         e = ba::launch_attn_final_gathered(ap, gm, stream);
       } else {
         e = ba::launch_attn_final(ap, meta, stream);

@@ -200,64 +200,12 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
     }
     for (int b = 0; b < nb; ++b) reach = std::max<int64_t>(reach, (int64_t)src[b] + len[b]);
     const size_t table_at = align256((size_t)padded * row_b);
-    if (n_prompts <= ba::kFinMaxPrompts && !heads->xcd_speed && nb <= ba::kRowTableBlocks &&
+    const bool table = n_prompts <= ba::kFinMaxPrompts && !heads->xcd_speed && nb <= ba::kRowTableBlocks &&
         (size_t)pl.cu_ctx[n_prompts] * row_b >= ba::kRowTableBytes && (fp.max_nt + fp.max_nt / (2 * fp.n_splits)) / fp.n_splits + 2 <= ba::kRowTableTiles &&
         reach * v_cache->stride_tok * 2 < ((int64_t)1 << 32) - 65536 &&
-        table_at + (size_t)padded * 4 <= 2 * align256(pl.gather_kv_bytes)) {
-      int at = 0;
-      for (int n = 0; n < n_prompts; ++n)
-        for (; at < nb && dst[at] < pl.cu_ctx[n + 1]; ++at) dst[at] += ctx0[n] - pl.cu_ctx[n];
-      ba::RopeTable rt;
-      build_rope_table(heads, &rt);
-      ba::ReencRowsParams rp;
-      memset(&rp, 0, sizeof(rp));
-      rp.src = k_cache->ptr;
-      rp.dst = kg.ptr;
-      rp.src_st = k_cache->stride_tok;
-      rp.src_sh = k_cache->stride_head;
-      rp.dst_st = kg.stride_tok;
-      rp.dst_sh = kg.stride_head;
-      rp.n_layers = 1;
-      rp.n_kv_heads = heads->n_kv_heads;
-      rp.head_dim = D;
-      rp.dtype = BA_DTYPE_BF16;
-      rp.layout = heads->rope_layout;
-      rp.mode = BA_REENC_SHIFT;
-      rp.copy_from_layer = 0x7fffffff;
-      rp.row_table = (uint32_t *)((char *)ws + table_at);
-      rp.row_bytes = (uint32_t)(v_cache->stride_tok * 2);
-      rp.table_end = (int32_t)padded;
-      if ((rc = run_reencode(rp, rt, nb, src.data(), dst.data(), len.data(), oldp.data(), newp.data(), stream))) return rc;
-      const GatheredRows rows = {rp.row_table, ctx0.data()};
-      return final_block(heads, q_f, &kg, v_cache, k_f, v_f, o_out, k_f_rot_out, n_prompts, cu_q, pl.cu_ctx.data(), q_pos0,
-                         BA_ROPE_APPLY, (char *)ws + 2 * align256(pl.gather_kv_bytes), pl.gather_final_bytes, stream_, &rows);
-    }
-    const int64_t v_after_k = ((const char *)v_cache->ptr - (const char *)k_cache->ptr) / 2;  // in elements
-    if (k_cache->stride_tok == v_cache->stride_tok && k_cache->stride_head == v_cache->stride_head) {
-      // One launch for both: the values ride along as a second "layer" of the key cache (the layer
-      // strides are the distances between the two tensors) that is copied, not rotated.
-      ba::RopeTable rt;
-      build_rope_table(heads, &rt);
-      ba::ReencParams rp;
-      memset(&rp, 0, sizeof(rp));
-      rp.src = k_cache->ptr;
-      rp.dst = kg.ptr;
-      rp.src_st = k_cache->stride_tok;
-      rp.src_sh = k_cache->stride_head;
-      rp.dst_st = kg.stride_tok;
-      rp.dst_sh = kg.stride_head;
-      rp.src_sl = v_after_k;
-      rp.dst_sl = (int64_t)(align256(pl.gather_kv_bytes) / 2);
-      rp.n_layers = 2;
-      rp.n_kv_heads = heads->n_kv_heads;
-      rp.head_dim = D;
-      rp.dtype = BA_DTYPE_BF16;
-      rp.layout = heads->rope_layout;
-      rp.mode = BA_REENC_SHIFT;
-      rp.copy_from_layer = 1;
-      if ((rc = run_reencode(rp, rt, nb, src.data(), dst.data(), len.data(), oldp.data(), newp.data(), stream)))
-        return rc;
-    } else {
+        table_at + (size_t)padded * 4 <= 2 * align256(pl.gather_kv_bytes);
+    void *const ws_final = (char *)ws + 2 * align256(pl.gather_kv_bytes);
+    if (!table && (k_cache->stride_tok != v_cache->stride_tok || k_cache->stride_head != v_cache->stride_head)) {
       if ((rc = ba_reencode_positions(heads, k_cache, &kg, 1, 0, 0, nb, src.data(), dst.data(), len.data(), oldp.data(),
                                       newp.data(), BA_REENC_SHIFT, stream_)))
         return rc;
@@ -265,10 +213,57 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
       if ((rc = ba_reencode_positions(heads, v_cache, &vg, 1, 0, 0, nb, src.data(), dst.data(), len.data(), zero.data(),
                                       zero.data(), BA_REENC_SHIFT, stream_)))
         return rc;
+      return ba_final_block_attention(heads, q_f, &kg, &vg, k_f, v_f, o_out, k_f_rot_out, n_prompts, cu_q, pl.cu_ctx.data(), q_pos0,
+                                      BA_ROPE_APPLY, ws_final, pl.gather_final_bytes, stream_);
     }
-    return ba_final_block_attention(heads, q_f, &kg, &vg, k_f, v_f, o_out, k_f_rot_out, n_prompts, cu_q,
-                                    pl.cu_ctx.data(), q_pos0, BA_ROPE_APPLY,
-                                    (char *)ws + 2 * align256(pl.gather_kv_bytes), pl.gather_final_bytes, stream_);
+    Gather g;
+    memset(&g, 0, sizeof(g));
+    g.p.src = k_cache->ptr;
+    g.p.dst = kg.ptr;
+    g.p.src_st = k_cache->stride_tok;
+    g.p.src_sh = k_cache->stride_head;
+    g.p.dst_st = kg.stride_tok;
+    g.p.dst_sh = kg.stride_head;
+    g.p.n_kv_heads = heads->n_kv_heads;
+    g.p.head_dim = D;
+    g.p.dtype = BA_DTYPE_BF16;
+    g.p.layout = heads->rope_layout;
+    g.p.mode = BA_REENC_SHIFT;
+    if (table) {
+      int at = 0;
+      for (int n = 0; n < n_prompts; ++n)
+        for (; at < nb && dst[at] < pl.cu_ctx[n + 1]; ++at) dst[at] += ctx0[n] - pl.cu_ctx[n];
+      g.p.n_layers = 1;
+      g.p.copy_from_layer = 0x7fffffff;
+      g.p.row_table = (uint32_t *)((char *)ws + table_at);
+      g.p.row_bytes = (uint32_t)(v_cache->stride_tok * 2);
+      g.p.table_end = (int32_t)padded;
+      g.ctx0 = ctx0.data();
+    } else {
+      // One launch for both: the values ride along as a second "layer" of the key cache (the layer
+      // strides are the distances between the two tensors) that is copied, not rotated.
+      g.p.src_sl = ((const char *)v_cache->ptr - (const char *)k_cache->ptr) / 2;  // in elements
+      g.p.dst_sl = (int64_t)(align256(pl.gather_kv_bytes) / 2);
+      g.p.n_layers = 2;
+      g.p.copy_from_layer = 1;
+    }
+    // all but the last table-full of blocks in launches ahead of the final block's
+    const int ahead = nb > 0 ? (nb - 1) / ba::kReencMaxBlocksLarge * ba::kReencMaxBlocksLarge : 0;
+    if (ahead > 0) {
+      ba::RopeTable rt;
+      build_rope_table(heads, &rt);
+      ba::ReencRowsParams p = g.p;
+      p.table_end = dst[ahead];
+      const ba::ReencParams &plain = p;
+      rc = table ? run_reencode(p, rt, ahead, src.data(), dst.data(), len.data(), oldp.data(), newp.data(), stream)
+                 : run_reencode(plain, rt, ahead, src.data(), dst.data(), len.data(), oldp.data(), newp.data(), stream);
+      if (rc) return rc;
+    }
+    g.n_blocks = nb - ahead;
+    g.src_off = src.data() + ahead, g.dst_off = dst.data() + ahead, g.len = len.data() + ahead;
+    g.pos_old = oldp.data() + ahead, g.pos_new = newp.data() + ahead;
+    return final_block(heads, q_f, &kg, table ? v_cache : &vg, k_f, v_f, o_out, k_f_rot_out, n_prompts, cu_q, pl.cu_ctx.data(),
+                       q_pos0, BA_ROPE_APPLY, ws_final, pl.gather_final_bytes, stream_, &g);
   }
 
   char *wsp = (char *)ws;

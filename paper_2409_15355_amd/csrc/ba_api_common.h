@@ -69,16 +69,19 @@ int32_t run_rope_prepass(const ba_heads *h, const RopeTable &rt, const ba_tensor
                          const RopeRots *rots = nullptr, const RopeRotsSmall *rots_small = nullptr, float *rot_dst = nullptr,
                          int n_rot = 0, float *q_table = nullptr, int table_rows = 0, int32_t *zero = nullptr, int n_zero = 0);
 
-// ba_final_block_attention; rows: the context's keys are k_ctx's rows from ctx0[n] on, its values v_ctx's through a table
-// (FinalGatherMeta).
-struct GatheredRows {
-  const uint32_t *rows;
-  const int32_t *ctx0;
+// A context of cached blocks that a final block's first launch gathers (keys re-encoded; values copied as a second layer, or
+// left where they are and fetched through a table).
+struct Gather {
+  ReencRowsParams p;    // (row_table null: no table)
+  const int32_t *ctx0;  // with a table: prompt n's keys from row ctx0[n] of k_ctx on (FinalGatherMeta)
+  int n_blocks;         // the last of them, at most kReencMaxBlocksLarge (the others: launches before)
+  const int32_t *src_off, *dst_off, *len, *pos_old, *pos_new;
 };
+// ba_final_block_attention, its context gathered first if so asked
 int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,
                     const ba_tensor *k_f, const ba_tensor *v_f, const ba_tensor *o_out, const ba_tensor *k_f_rot_out,
                     int32_t n_prompts, const int32_t *cu_q, const int32_t *cu_ctx, const int32_t *q_pos0,
-                    int32_t rope_mode, void *ws, size_t ws_bytes, void *stream_, const GatheredRows *rows);
+                    int32_t rope_mode, void *ws, size_t ws_bytes, void *stream_, const Gather *gather);
 
 }  // namespace api
 }  // namespace ba

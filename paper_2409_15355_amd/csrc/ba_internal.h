@@ -116,6 +116,13 @@ struct RopeRotsT {
 using RopeRots = RopeRotsT<kBlkMaxBlocks>;
 using RopeRotsSmall = RopeRotsT<kBlkSmallBlocks>;
 
+// A gathered context's re-encoding (bf16, uniform shift, one or two layers) and the pre-pass of the query block's rows
+// (rotated q and k; no table of rotations, nothing to clear) in one launch.  Params = ReencParams or ReencRowsParams.
+using RopeSegsGather = RopeSegsT<64>;
+template <typename Params, typename Blocks>
+hipError_t launch_gather_prepass(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
+                                 const RopeTable &rt, hipStream_t stream);
+
 // rots / rots_small: at most one non-null, and only with p.rot_dst
 hipError_t launch_rope_prepass(const RopePrepassParams &p, const RopeSegs &segs, const RopeRots *rots,
                                const RopeRotsSmall *rots_small, const RopeTable &rt, hipStream_t stream);
@@ -313,6 +320,7 @@ hipError_t launch_bwd_dq(const AttnParams &p, const PromptMeta &meta, const BwdP
 hipError_t launch_bwd_dkv(const AttnParams &p, const BwdKvMeta &meta, const BwdParams &bp, hipStream_t stream);
 
 constexpr int kFinMaxPrompts = 64;
+static_assert(RopeSegsGather::kSegs >= kFinMaxPrompts, "a launch's prompts are segments of its pre-pass");
 struct FinalMeta {
   int32_t n;
   int32_t cu_q[kFinMaxPrompts + 1];

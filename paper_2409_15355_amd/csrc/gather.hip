@@ -1,0 +1,92 @@
+// Gather of a context of short cached blocks and RoPE pre-pass of the query block behind it, in one launch.
+//
+// The two are independent of each other and the attention core waits for both.  The pre-pass is 4 us of latency for a few
+// hundred kilobytes of rows; as the first workgroups of the gather's launch it is done before the gather is, and a
+// dependent launch is saved: 8 blocks of 46 to 138 tokens, 16 over 8 heads of 128, 25.5 -> 19.5 us, 25 calls of 100 to 20,000
+// context tokens 0.76 to 0.98 of the time.
+// The gather is bound by memory and by how fast it gets going.  What it writes is read by the next kernel and what it
+// reads may still be in the caches, so neither goes past them, and a thread moves two pieces, not eight (four times the
+// workgroups): 512 blocks of 20 to 60 tokens, 32 over 8 heads of 128, 42 MB in and out: the call 62.1 -> 52.1 us, 66 -> 58
+// with eight such caches in turn.  (Four pieces 56, with the hint 59; one piece 50, but then the compiler fuses the other
+// product of a rotation and last bits move.)
+#include "ba_rotate.h"
+#include "ba_schedule.h"
+
+namespace ba {
+namespace {
+
+constexpr int kUnroll = 2;  // 16-byte pieces of a run per thread
+
+struct GatherGrid {
+  uint32_t n_pre, pre_x;  // workgroups of the pre-pass, and of one of its head groups
+  FastDiv pre_div;        // division by pre_x
+  uint32_t x;             // workgroups per block and layer of the gather
+  FastDiv x_div;
+};
+
+// kRuns: packed keys of interleaved pairs, where a block is one run of 16-byte pieces
+template <int D, int LAYOUT, bool kRuns, typename Params, typename Blocks>
+__global__ __launch_bounds__(kRotThreads) void gather_prepass_kernel(Params gp, Blocks blocks, RopePrepassParams pp,
+                                                                     RopeSegsGather segs, RopeTable rt, GatherGrid g) {
+  uint32_t id = blockIdx.x;
+  if (id < g.n_pre) {
+    const uint32_t by = fast_div(id, g.pre_div);
+    rope_prepass_rows<D, LAYOUT>(pp, segs, rt, (int)(id - by * g.pre_x), (int)by);
+    return;
+  }
+  id -= g.n_pre;
+  const uint32_t row = fast_div(id, g.x_div);
+  const uint32_t bx = id - row * g.x;
+  const int layer = (int)row >= blocks.n ? 1 : 0, b = (int)row - layer * blocks.n;
+  if constexpr (kRuns)
+    reencode_run<Chunk<uint16_t, false, false>, D, kUnroll>(gp, blocks, rt, bx, b, layer);
+  else
+    reencode_tokens<Chunk<uint16_t, false, false>, D, LAYOUT, 0, kRotThreads / (D / 16)>(gp, blocks, rt, bx, b, layer);
+}
+
+template <int D, int LAYOUT, bool kRuns, typename Params, typename Blocks>
+hipError_t launch_t(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
+                    const RopeTable &rt, hipStream_t stream) {
+  constexpr int TPP = kRotThreads / (D / 16);  // tokens per workgroup, of either pass
+  GatherGrid g;
+  g.pre_x = (uint32_t)((segs.start[segs.n] - segs.start[0] + TPP - 1) / TPP);
+  const uint32_t groups = (uint32_t)(q_groups(pp) + (pp.n_kv_heads + pp.heads_per_thread - 1) / pp.heads_per_thread);
+  g.n_pre = g.pre_x * groups;
+  if (kRuns)
+    g.x = (uint32_t)(((int64_t)gp.max_len * gp.n_kv_heads * (D / 8) + kUnroll * kRotThreads - 1) / (kUnroll * kRotThreads));
+  else
+    g.x = (uint32_t)((gp.max_len + TPP - 1) / TPP * gp.n_head_groups);
+  if (g.pre_x == 0 || g.x == 0 || gp.n_layers > 2) return hipErrorInvalidValue;
+  const int64_t n_wg = (int64_t)g.n_pre + (int64_t)g.x * blocks.n * gp.n_layers;
+  if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
+  g.pre_div = make_fast_div(g.pre_x);
+  g.x_div = make_fast_div(g.x);
+  hipLaunchKernelGGL((gather_prepass_kernel<D, LAYOUT, kRuns, Params, Blocks>), dim3((unsigned)n_wg), dim3(kRotThreads), 0, stream,
+                     gp, blocks, pp, segs, rt, g);
+  return hipGetLastError();
+}
+
+template <int D, typename Params, typename Blocks>
+hipError_t launch_d(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
+                    const RopeTable &rt, hipStream_t stream) {
+  const bool packed = gp.src_sh == D && gp.dst_sh == D && gp.src_st == (int64_t)gp.n_kv_heads * D && gp.dst_st == (int64_t)gp.n_kv_heads * D;
+  if (gp.layout != 0) return launch_t<D, 1, false>(gp, blocks, pp, segs, rt, stream);
+  return packed ? launch_t<D, 0, true>(gp, blocks, pp, segs, rt, stream) : launch_t<D, 0, false>(gp, blocks, pp, segs, rt, stream);
+}
+
+}  // namespace
+
+template <typename Params, typename Blocks>
+hipError_t launch_gather_prepass(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
+                                 const RopeTable &rt, hipStream_t stream) {
+  if (gp.head_dim == 128) return launch_d<128>(gp, blocks, pp, segs, rt, stream);
+  if (gp.head_dim == 64) return launch_d<64>(gp, blocks, pp, segs, rt, stream);
+  return hipErrorInvalidValue;
+}
+
+template hipError_t launch_gather_prepass(const ReencParams &, const ReencBlocks &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
+template hipError_t launch_gather_prepass(const ReencParams &, const ReencBlocksLarge &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
+template hipError_t launch_gather_prepass(const ReencRowsParams &, const ReencBlocks &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
+template hipError_t launch_gather_prepass(const ReencRowsParams &, const ReencBlocksLarge &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
+
+}  // namespace ba

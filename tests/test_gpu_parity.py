@@ -903,6 +903,11 @@ GATHER_CASES = [  # (Hq, Hkv, D, tokens of each prompt's cached blocks, query to
     # values of just 4 MB, and one token less
     (8, 8, 128, [[32] * 64], [70]),
     (8, 8, 128, [[32] * 63 + [31]], [70]),
+    # more prompts than one launch of the final block lists (64): the gather runs with the first one's pre-pass
+    (8, 2, 64, [[30, 20]] * 70, [3] * 70),
+    # as many blocks as one and as two launches of the gather list
+    (4, 4, 64, [[3] * 1024], [9]),
+    (8, 8, 128, [[3] * 2048], [9]),
 ]
 
 
@@ -910,7 +915,8 @@ GATHER_CASES = [  # (Hq, Hkv, D, tokens of each prompt's cached blocks, query to
 @pytest.mark.parametrize("case", GATHER_CASES, ids=["three-prompts-d128", "tiny-blocks-d64", "one-token-context", "long-d64",
                                                       "two-launches-d64", "two-launches-d128", "three-prompts-d128-table",
                                                       "tiny-blocks-d64-table", "one-token-context-table", "long-d64-table",
-                                                      "table-from-here", "copied-to-here"])
+                                                      "table-from-here", "copied-to-here", "many-prompts",
+                                                      "one-table-full", "two-tables-full"])
 def test_gathered_calls_give_the_bits_of_a_context_gathered_by_hand(ba, case, layout):
     """Short cached blocks: keys gathered by the call, value rows fetched through its table of where they lie (from 4 MB
     of them on; less is copied with the keys).  The same keys re-encoded into one context by the caller, the values copied there, must give the same bits: contexts
@@ -947,6 +953,35 @@ def test_gathered_calls_give_the_bits_of_a_context_gathered_by_hand(ba, case, la
                                            torch.full((need,), fill, dtype=torch.uint8, device="cuda"))
         torch.cuda.synchronize()
         assert np.array_equal(host_bits(o), want)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("hkv,d", [(2, 64), (8, 128)])
+def test_gathered_calls_on_a_cache_of_interleaved_keys_and_values(ba, layout, hkv, d):
+    """Keys and values as views of one buffer: strides that are not packed, values copied next to the keys (2, 64) or fetched
+    through the table (8, 128).  The bits of a context gathered by hand."""
+    torch = torch_mod()
+    lens = np.array([40, 1, 64, 33, 100] * 10, dtype=np.int32)
+    T, lq = int(lens.sum()), 37
+    off = (T - np.cumsum(lens)).astype(np.int32)
+    dst = (np.cumsum(lens) - lens).astype(np.int32)
+    both = dev_bf16(wl.normal_bf16_bits(1420, (T, 2 * hkv, d)))
+    kc, vc = both[:, :hkv], both[:, hkv:]
+    qb, kfb, vfb = gen_qkv(1421, lq, 2 * hkv, hkv, d)
+    q, kf, vf = dev_bf16(qb), dev_bf16(kfb), dev_bf16(vfb)
+    heads = ba.Heads(2 * hkv, hkv, d, 10000.0, rope_layout=layout)
+    cu_q, cu_blk, cu_ctx = (np.array([0, n], dtype=np.int32) for n in (lq, len(lens), T))
+    k_ctx, v_ctx = (torch.empty((T, hkv, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    ba.ba_reencode_positions(heads, kc, k_ctx, off, dst, lens, None, dst, ba.REENC_SHIFT)
+    for a, b, n in zip(off, dst, lens):
+        v_ctx[b:b + n] = vc[a:a + n]
+    want = host_bits(gpu_final(ba, heads, q, k_ctx, v_ctx, kf, vf, cu_q, cu_ctx))
+    o = torch.full_like(q, float("nan"))
+    n = ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens)
+    ba.ba_final_block_attention_cached(heads, q, kc, vc, kf, vf, o, None, cu_q, cu_blk, off, lens, None, None, None,
+                                       torch.full((n,), 255, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert np.array_equal(host_bits(o), want)
 
 
 @pytest.mark.parametrize("why", ["splits", "rows", "speeds"])
