@@ -46,13 +46,24 @@ hipError_t launch_t(const Params &p, const Blocks &blocks, const RopeTable &rt, 
   return hipGetLastError();
 }
 
+// Which loads and how much per thread, by the bytes of a launch (read and written).  The rotated keys go past the caches, but
+// the keys as cached may still lie there.  Time with plain loads / with the hint, one cache re-encoded over and over and
+// eight in turn (880 MB to 2 GB, nothing of which is found again):
+//   - runs, two pieces per thread instead of eight (four times the workgroups): 157 MB 0.78 and 0.92, 128 MB 0.74 and 0.87
+//     (of that the two pieces alone 0.87 and 0.90, 0.80 and 0.84); 412 MB 1.00 and 1.00.  In launches beyond the cache eight.
+//   - the others: 39 MB 0.91 and 0.90, 45 MB 0.96 and 0.84; but 110 MB 0.87 and 1.02, 157 MB 0.87 and 1.03, 262 MB 0.86 and
+//     1.02, and with three in turn 262 MB is 1.02 as well: plain up to a quarter of the cache.
 template <typename T, int D, typename Params, typename Blocks>
 hipError_t launch_d(const Params &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
   typedef Chunk<T, true, true> Past;
+  typedef Chunk<T, false, true> Near;
   const bool packed = p.src_sh == D && p.dst_sh == D && p.src_st == (int64_t)p.n_kv_heads * D &&
                       p.dst_st == (int64_t)p.n_kv_heads * D;
+  int64_t tokens = 0;
+  for (int i = 0; i < blocks.n; ++i) tokens += blocks.len[i];
+  const int64_t bytes = tokens * p.n_layers * p.n_kv_heads * D * (int64_t)sizeof(T) * 2;
   if (p.layout == 0 && p.mode == 0 && packed)
-    return launch_linear<Past, D, 8>(p, blocks, rt, stream);
+    return bytes > kCacheBytes ? launch_linear<Past, D, 8>(p, blocks, rt, stream) : launch_linear<Near, D, 2>(p, blocks, rt, stream);
   const auto launch = [&](auto ch) {
     typedef decltype(ch) Ch;
     if (p.mode == 0)
@@ -61,7 +72,7 @@ hipError_t launch_d(const Params &p, const Blocks &blocks, const RopeTable &rt, 
       return p.layout == 0 ? launch_t<Ch, D, 0, 1>(p, blocks, rt, stream) : launch_t<Ch, D, 1, 1>(p, blocks, rt, stream);
     return hipErrorInvalidValue;
   };
-  return launch(Past{});
+  return bytes > kCacheBytes / 4 ? launch(Past{}) : launch(Near{});
 }
 
 }  // namespace

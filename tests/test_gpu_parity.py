@@ -116,6 +116,28 @@ def test_reencode_f32_relative_error(ba, layout, mode):
     assert rel <= REENC_F32_REL_TOL, f"relative error {rel:.3e}"
 
 
+@pytest.mark.parametrize("layout,mode,total", [(0, 0, 66000), (1, 0, 17000), (0, 1, 17000), (1, 1, 17000)])
+def test_reencode_larger_than_the_caches_gives_the_bits_of_its_parts(ba, layout, mode, total):
+    """Just above 256 MB read and written (runs) and 64 MB (the others) a call's loads go past the caches and a thread's share
+    changes; calls of half the blocks each lie below."""
+    torch = torch_mod()
+    heads = ba.Heads(8, 8, 128, 10000.0, rope_layout=layout)
+    line = 256 << 20 if (layout, mode) == (0, 0) else 64 << 20
+    assert total * 8 * 128 * 4 > line > total * 8 * 128 * 2
+    n = 50
+    lens = np.full(n, total // n, dtype=np.int32)
+    off = (np.cumsum(lens) - lens).astype(np.int32)
+    new0 = np.arange(n, dtype=np.int32) * 7
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    k = torch.randn((total, 8, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    whole, parts = torch.zeros_like(k), torch.zeros_like(k)
+    ba.ba_reencode_positions(heads, k, whole, off, off, lens, None, new0, mode)
+    for s in (slice(0, n // 2), slice(n // 2, n)):
+        ba.ba_reencode_positions(heads, k, parts, off[s], off[s], lens[s], None, new0[s], mode)
+    torch.cuda.synchronize()
+    assert torch.equal(whole.view(torch.int16), parts.view(torch.int16))
+
+
 def test_reencode_2500_blocks_in_one_call(ba):
     """More blocks than the larger of the two block tables holds (three launches), gathered into the
     reverse order, two layers."""
