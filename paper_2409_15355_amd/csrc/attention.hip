@@ -911,6 +911,14 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
     const int64_t unit = ((int64_t)(BA_ARG(tile_base) + rowtile) * BA_ARG(n_kv_heads) + kvh) * kWaves + wave;
     const int64_t slot = (int64_t)split * BA_ARG(part_units) + unit;
     char *dst = (char *)BA_ARG(part_o) + slot * (int64_t)(32 * D * 2) + lane * 16;
+    // (a wave without rows leaves nothing but that, from split 0: 7 of 8 waves of a query block of a few tokens)
+    bool any_rows = wave_has_rows;
+    if constexpr (kBlocks) {
+      int wave_row = wave * 32;
+      asm volatile("" : "+s"(wave_row));
+      any_rows = row0 + wave_row < n_rows;
+    }
+    if (any_rows)
 #pragma unroll
     for (int dt = 0; dt < G::DT; ++dt)
 #pragma unroll
@@ -926,7 +934,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
       }
     if (hf == 0) {
       float2 ml = {l_tot > 0.f ? mb : -INFINITY, l_tot};  // reference in log2 units; -inf: nothing visible
-      *reinterpret_cast<float2 *>(BA_ARG(part_ml) + (slot * 32 + col) * 2) = ml;
+      if (any_rows) *reinterpret_cast<float2 *>(BA_ARG(part_ml) + (slot * 32 + col) * 2) = ml;
       if (split == 0) {
         // (the row's token is worked out again, from a copy of the row number the compiler cannot
         // see through: kept from before the walk it would be spilled)
@@ -1006,6 +1014,19 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
 
 #undef BA_ARG
 
+// What the merge needs of AttnParams, two cache lines of arguments.
+struct CombineParams {
+  const uint16_t *part_o;
+  const float *part_ml;
+  const int32_t *part_idx;
+  int64_t part_units;
+  int32_t n_splits, merge_rows;
+  FastDiv merge_div;
+  int32_t merge_sparse, n_q_heads;
+  uint16_t *o;
+  int64_t o_st, o_sh;
+};
+
 // Merge split partials in split order.  Split i holds its own normalised output o_i (fp16), its
 // reference m_i (log2 units; -inf if it saw no key) and its sum l_i:
 //   m = max m_i,  w_i = 2^(m_i - m) l_i,  o = sum_i w_i o_i / sum_i w_i.
@@ -1015,42 +1036,67 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
 // reads 1 KB of consecutive memory per split.  SG = 1: a thread merges all splits one after the
 // other.  SG = 4 (many splits, few rows): four groups of threads take every fourth split each, so that
 // all loads of a row are in flight at once, and the groups' sums are merged through LDS, group 0 first.
+// Bound by latency: arguments, then everything a thread reads in one go (it was three to five round trips one behind the other:
+// the index, tested before anything else, the references, the outputs), and no more of it than there are splits and rows.  Two
+// splits of 14 row tiles and 8 KV heads 7.9 -> 6.0 us; with the partials of waves without rows neither written nor read, calls of
+// a few query tokens 0.83 to 0.97 of their time, others 0.97 to 1.00.
 template <int D, int SG>
-__global__ __launch_bounds__(kCombineThreads) void combine_kernel(AttnParams p) {
+__global__ __launch_bounds__(kCombineThreads) void combine_kernel(CombineParams p) {
   constexpr int K = D / 16;                          // 16-byte stores per lane of the layout
   constexpr int KPB = kCombineThreads / (64 * SG);   // layout stores (k values) per workgroup
   static_assert(KPB >= 1 && K % KPB == 0, "a workgroup covers whole k values of one unit");
   constexpr int BPU = K / KPB;                       // workgroups per unit
-  const int g = threadIdx.x / (64 * KPB);            // which group of splits
-  const int kl = (threadIdx.x / 64) % KPB;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = wave / KPB;                          // which group of splits
+  const int kl = wave % KPB;
   const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
   const int64_t unit = blockIdx.x / BPU;
+  // Units without rows have nothing but their indices written, and a load of the indices ahead of the others is a round trip to
+  // memory more: with one prompt its rows tell (no load at all); with several the indices come first where most units have none.
+  if (p.merge_rows > 0) {
+    const uint32_t u = blockIdx.x / BPU, tile = fast_div(u, p.merge_div);
+    if ((int)(tile * kTileRows + (u & (kWaves - 1)) * 32) >= p.merge_rows) return;
+  }
   const int k = (int)(blockIdx.x % BPU) * KPB + kl;
   // all loads are unconditional and independent, so they go out together
   const int n_mine = (p.n_splits - g + SG - 1) / SG;  // splits g, g + SG, ...
-  const float2 *ml = reinterpret_cast<const float2 *>(p.part_ml) + unit * 32 + col;
-  const char *po = (const char *)p.part_o + unit * (int64_t)(32 * D * 2) + k * 1024 + lane * 16;
-  const int64_t ml_stride = p.part_units * 32, o_stride = p.part_units * (int64_t)(32 * D * 2);
+  // (wave-uniform, so that the addresses below cost scalar additions and each load a lane's offset)
+  const char *ml = (const char *)p.part_ml + (g * p.part_units + unit) * 256;
+  const char *po = (const char *)p.part_o + (g * p.part_units + unit) * (int64_t)(32 * D * 2) + k * 1024;
+  const int64_t ml_step = SG * p.part_units * 256, o_step = SG * p.part_units * (int64_t)(32 * D * 2);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float l = 0.f, m = -INFINITY;
   // every load of the thread is requested before anything is used; a split beyond the thread's last
   // reads its last one again with weight zero
+  int idx = p.part_idx[unit * 32 + col];
+  if (p.merge_rows == 0 && p.merge_sparse) {
+    int now = idx;
+    asm volatile("" : "+v"(now));  // (waited for in here only)
+    if (__builtin_amdgcn_ballot_w64(now >= 0) == 0) return;
+  }
   auto merge = [&](auto capacity) __attribute__((always_inline)) {
     constexpr int CAP = decltype(capacity)::value;
-    float2 mls[CAP];
+    f32x2_t mls[CAP];
     u32x4_t os[CAP];
 #pragma unroll
     for (int j = 0; j < CAP; ++j) {
-      const int s = g + min(j, n_mine - 1) * SG;
-      mls[j] = ml[s * ml_stride];
-      os[j] = *reinterpret_cast<const u32x4_t *>(po + s * o_stride);
+      mls[j] = *reinterpret_cast<const f32x2_t *>(ml + (uint32_t)col * 8u);
+      os[j] = *reinterpret_cast<const u32x4_t *>(po + (uint32_t)lane * 16u);
+      const int64_t go_on = -(int64_t)(j + 1 < n_mine);
+      ml += ml_step & go_on;
+      po += o_step & go_on;
     }
+    // (the empty asm holds them all: or the compiler moves the test of idx to the front, then the loads of the references,
+    // and puts the outputs behind their maximum, three round trips to memory one after the other)
+    asm volatile("" : "+v"(idx));
+#pragma unroll
+    for (int j = 0; j < CAP; ++j) asm volatile("" : "+v"(mls[j]), "+v"(os[j]));
 #pragma unroll
     for (int j = 0; j < CAP; ++j)
-      if (j < n_mine) m = fmaxf(m, mls[j].x);
+      if (j < n_mine) m = fmaxf(m, mls[j][0]);
 #pragma unroll
     for (int j = 0; j < CAP; ++j) {
-      const float w = (j >= n_mine || mls[j].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mls[j].x - m) * mls[j].y;
+      const float w = (j >= n_mine || mls[j][0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mls[j][0] - m) * mls[j][1];
       l += w;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -1060,8 +1106,10 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(AttnParams p) 
     }
   };
   static_assert(kMaxSplits <= 16 * 4 && kOneGroupSplits <= 8, "a thread's share of the splits fits its registers");
-  if (SG == 1 || n_mine <= 8) merge(std::integral_constant<int, 8>{}); else merge(std::integral_constant<int, 16>{});
-  const int idx = p.part_idx[unit * 32 + col];
+  if (n_mine <= 2) merge(std::integral_constant<int, 2>{});
+  else if (n_mine <= 4) merge(std::integral_constant<int, 4>{});
+  else if (SG == 1 || n_mine <= 8) merge(std::integral_constant<int, 8>{});
+  else merge(std::integral_constant<int, 16>{});
   if constexpr (SG > 1) {
     // (reference, sum, eight partial outputs) of every thread; group 0 merges them in group order
     __shared__ float part[SG][64 * KPB][10 + 1];
@@ -1167,7 +1215,8 @@ hipError_t launch_attn_final_blocks(const AttnParams &p, const FinalBlocksMetaSm
 template <int D, int SG>
 void launch_combine_t(const AttnParams &p, hipStream_t stream) {
   constexpr int BPU = (D / 16) / (kCombineThreads / (64 * SG));  // workgroups per unit
-  hipLaunchKernelGGL((combine_kernel<D, SG>), dim3((unsigned)(p.part_units * BPU)), dim3(kCombineThreads), 0, stream, p);
+  const CombineParams c = {p.part_o, p.part_ml, p.part_idx, p.part_units, p.n_splits, p.merge_rows, p.merge_div, p.merge_sparse, p.n_q_heads, p.o, p.o_st, p.o_sh};
+  hipLaunchKernelGGL((combine_kernel<D, SG>), dim3((unsigned)(p.part_units * BPU)), dim3(kCombineThreads), 0, stream, c);
 }
 
 hipError_t launch_combine(const AttnParams &p, hipStream_t stream) {

@@ -328,6 +328,7 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
   ap.n_q_heads = heads->n_q_heads;
   ap.n_kv_heads = heads->n_kv_heads;
   ap.group = G;
+  set_merge_rows(&ap, n_prompts, cu_q, G);
   ap.group_div = ba::make_fast_div((uint32_t)G);
   ap.head_dim = D;
   ap.scale_log2e = scale_log2e(heads);

@@ -69,6 +69,18 @@ int32_t run_rope_prepass(const ba_heads *h, const RopeTable &rt, const ba_tensor
                          const RopeRots *rots = nullptr, const RopeRotsSmall *rots_small = nullptr, float *rot_dst = nullptr,
                          int n_rot = 0, float *q_table = nullptr, int table_rows = 0, int32_t *zero = nullptr, int n_zero = 0);
 
+// What the merge of the split partials knows of the rows (AttnParams::merge_rows, merge_sparse).
+inline void set_merge_rows(AttnParams *ap, int n_prompts, const int32_t *cu_q, int G) {
+  int64_t live = 0, units = 0;  // per KV head
+  for (int n = 0; n < n_prompts; ++n) {
+    const int64_t rows = (int64_t)(cu_q[n + 1] - cu_q[n]) * G;
+    live += (rows + 31) / 32;
+    units += (rows + kTileRows - 1) / kTileRows * (kTileRows / 32);
+  }
+  ap->merge_rows = n_prompts == 1 ? (cu_q[1] - cu_q[0]) * G : 0;
+  ap->merge_div = make_fast_div((uint32_t)(ap->n_kv_heads * (kTileRows / 32)));
+  ap->merge_sparse = 2 * live < units;
+}
 // A context of cached blocks that a final block's first launch gathers (keys re-encoded; values copied as a second layer, or
 // left where they are and fetched through a table).
 struct Gather {

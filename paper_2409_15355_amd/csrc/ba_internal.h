@@ -232,6 +232,9 @@ struct AttnParams {
   // (row tile of the launch, KV head); part_idx counts, per the same of a block's first split, who is done)
   int64_t part_units;
   int32_t tile_base;  // row tiles of the call's earlier launches
+  int32_t merge_rows;    // merge of the partials: packed rows of the call's only prompt, 0 if it has several
+  FastDiv merge_div;     // ... division by a row tile's units
+  int32_t merge_sparse;  // ... most units have no rows
   int32_t n_q_heads, n_kv_heads, group, head_dim;
   FastDiv group_div;  // division by `group`
   float scale_log2e;  // softmax scale * log2(e)

@@ -2268,6 +2268,33 @@ def test_many_splits_for_few_kv_heads(ba, hq, hkv, d, ctx, nq):
         assert_attention_close(host_f64(o), ref, f"speeds {speeds}")
 
 
+@pytest.mark.parametrize("hq,hkv,d,lqs,ctx,splits", [
+    # one prompt: its rows tell which units of 32 rows there are; groups of one to four splits a thread
+    (4, 1, 64, [130], 300, 2), (4, 1, 64, [1], 700, 3), (8, 2, 128, [9], 1300, 5), (4, 1, 64, [1], 2300, 8),
+    (4, 1, 64, [70], 4300, 14), (8, 1, 128, [130], 8000, 22), (4, 4, 64, [9], 8000, 26),
+    # several: most units without rows (the indices come first), and most with
+    (4, 1, 64, [1, 130, 9], 300, 2), (4, 4, 64, [1] * 9, 2300, 7), (4, 1, 64, [1, 2, 3], 4300, 14),
+    (16, 4, 128, [70, 64, 1], 4300, 14), (8, 2, 64, [130] * 3, 4300, 12), (6, 2, 128, [70, 86, 3], 8000, 22)])
+def test_split_merge_with_and_without_rows(ba, hq, hkv, d, lqs, ctx, splits):
+    """Partials of units without rows are neither written nor read: a workspace full of NaN patterns."""
+    torch = torch_mod()
+    cu_q = np.concatenate([[0], np.cumsum(lqs)]).astype(np.int32)
+    cu_ctx = (np.arange(len(lqs) + 1) * ctx).astype(np.int32)
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    assert max(w.n_splits for w in ba.ba_schedule_final_block(heads, cu_q, cu_ctx)) == splits
+    tq, tc = int(cu_q[-1]), int(cu_ctx[-1])
+    _, kc, vc = gen_qkv(1030 + splits, tc, hq, hkv, d)
+    qb, kb, vb = gen_qkv(1031 + splits, tq, hq, hkv, d)
+    f = oracle.bf16_bits_to_f64
+    ref = oracle.final_block(f(qb), f(kc), f(vc), f(kb), f(vb), cu_q, cu_ctx, oracle.theta(10000.0, d))
+    o = torch.full((tq, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    n = ba.ba_final_block_attention_workspace_bytes(heads, cu_q, cu_ctx)
+    ba.ba_final_block_attention(heads, dev_bf16(qb), dev_bf16(kc), dev_bf16(vc), dev_bf16(kb), dev_bf16(vb), o, None, cu_q, cu_ctx,
+                                None, 1, torch.full((n,), 0xff, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert_attention_close(host_f64(o), ref)
+
+
 @pytest.mark.parametrize("hq,hkv,d,n_prompts", [(32, 8, 128, 4), (16, 8, 128, 6), (64, 16, 64, 4), (32, 16, 64, 6)])
 def test_a_call_larger_than_the_cache_gives_the_bits_of_its_parts(ba, hq, hkv, d, n_prompts):
     """Calls whose rows exceed the cache (256 MB) move them with other loads and stores; which loads must not
