@@ -735,7 +735,7 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
   lds_char *const pex = smem + 2 * BUFB + pair * KG::PEXB + lane * 16;
   const uint32_t ofs1 = is_b ? TB : 0u, ofs2 = is_b ? 0u : TB;  // the tile of the products before the exchange, behind it
-  // What bounds a tile is the chain of its products, not the matrix pipe (39 % busy) nor LDS.  Left to itself the
+  // What bounds a tile is the chain of its products, not the matrix pipe (by its operations some 40 % busy) nor LDS.  Left to itself the
   // compiler asks for two fragments, waits, multiplies and asks for the next two: four LDS latencies in a row
   // ahead of the exchange and one or two behind it.  So both halves hold a rolling window of fragments,
   // as many as the registers left by the accumulators take (five of rows, four transposed), the first two
