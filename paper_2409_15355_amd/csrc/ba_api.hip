@@ -250,10 +250,11 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
 }
 
 
-// The gather of a final block's context and the pre-pass of its first launch's prompts, together.
+// The gather of a final block's context and the pre-pass of its first launch's prompts, together (or, where one launch
+// does not take both, one after the other).
 template <typename Blocks, typename Params>
 static int32_t run_gather_prepass_t(Params gp, const Gather &g, const ba::RopePrepassParams &pp, const ba::RopeSegsGather &segs,
-                                    const ba::RopeTable &rt, hipStream_t stream) {
+                                    const ba::RopeTable &rt, bool *apart, hipStream_t stream) {
   std::vector<Blocks> tab(1);
   int32_t table_end = 0;
   if constexpr (std::is_same<Params, ba::ReencRowsParams>::value) table_end = gp.table_end;
@@ -262,6 +263,10 @@ static int32_t run_gather_prepass_t(Params gp, const Gather &g, const ba::RopePr
   {
     ProfileScope ps(BA_PROFILE_REENCODE, stream);
     e = ba::launch_gather_prepass(gp, tab[0], pp, segs, rt, stream);
+  }
+  if (e == hipErrorNotSupported) {
+    *apart = true;
+    return run_reencode_t<Blocks>(gp, rt, g.n_blocks, g.src_off, g.dst_off, g.len, g.pos_old, g.pos_new, stream);
   }
   if (e != hipSuccess) return device_fail(e, "gather launch");
   return BA_OK;
@@ -273,11 +278,15 @@ static int32_t run_gather_prepass(const ba_heads *h, const Gather &g, const ba::
   ba::RopeSegsGather segs;
   fill_segments(&segs, n, start, pos0);
   const ba::ReencParams &plain = g.p;
+  bool apart = false;
+  int32_t rc;
   if (g.n_blocks <= ba::kReencMaxBlocks)
-    return g.p.row_table ? run_gather_prepass_t<ba::ReencBlocks>(g.p, g, pp, segs, rt, stream)
-                         : run_gather_prepass_t<ba::ReencBlocks>(plain, g, pp, segs, rt, stream);
-  return g.p.row_table ? run_gather_prepass_t<ba::ReencBlocksLarge>(g.p, g, pp, segs, rt, stream)
-                       : run_gather_prepass_t<ba::ReencBlocksLarge>(plain, g, pp, segs, rt, stream);
+    rc = g.p.row_table ? run_gather_prepass_t<ba::ReencBlocks>(g.p, g, pp, segs, rt, &apart, stream)
+                       : run_gather_prepass_t<ba::ReencBlocks>(plain, g, pp, segs, rt, &apart, stream);
+  else
+    rc = g.p.row_table ? run_gather_prepass_t<ba::ReencBlocksLarge>(g.p, g, pp, segs, rt, &apart, stream)
+                       : run_gather_prepass_t<ba::ReencBlocksLarge>(plain, g, pp, segs, rt, &apart, stream);
+  return rc || !apart ? rc : run_rope_prepass(h, rt, q, q_rot, k, k_rot, n, start, pos0, stream);
 }
 
 int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,

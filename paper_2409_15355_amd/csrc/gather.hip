@@ -57,8 +57,10 @@ hipError_t launch_t(const Params &gp, const Blocks &blocks, const RopePrepassPar
   else
     g.x = (uint32_t)((gp.max_len + TPP - 1) / TPP * gp.n_head_groups);
   if (g.pre_x == 0 || g.x == 0 || gp.n_layers > 2) return hipErrorInvalidValue;
+  // The caller launches the two passes one after the other where one long block among a thousand short ones takes the
+  // one dimension used here beyond the 2^32 threads that the runtime launches.
   const int64_t n_wg = (int64_t)g.n_pre + (int64_t)g.x * blocks.n * gp.n_layers;
-  if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
+  if (n_wg * kRotThreads > 0xffffffffll) return hipErrorNotSupported;
   g.pre_div = make_fast_div(g.pre_x);
   g.x_div = make_fast_div(g.x);
   hipLaunchKernelGGL((gather_prepass_kernel<D, LAYOUT, kRuns, Params, Blocks>), dim3((unsigned)n_wg), dim3(kRotThreads), 0, stream,

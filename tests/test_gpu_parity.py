@@ -1046,6 +1046,32 @@ def test_gathered_calls_that_copy_their_values(ba, why):
     assert np.array_equal(host_bits(o), want)
 
 
+def test_gathered_context_whose_gather_is_a_launch_of_its_own(ba):
+    """One long block among a table-full of short ones: gather and pre-pass do not fit one launch's grid.  Against
+    re-encode + final block on the same inputs: the same kernels' arithmetic, so the same bits."""
+    torch = torch_mod()
+    hq, hkv, d = 8, 8, 128
+    lens, lq = [70000] + [60] * 1023, [5]
+    heads = ba.Heads(hq, hkv, d, 500000.0)
+    gen = torch.Generator(device="cuda").manual_seed(1310)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cu_q = np.concatenate([[0], np.cumsum(lq)]).astype(np.int32)
+    cu_blk = (np.arange(len(lq) + 1) * (len(lens) // len(lq))).astype(np.int32)
+    T, tq = int(offs[-1]), int(cu_q[-1])
+    kc, vc, q, kf, vf = draw(T, hkv, d), draw(T, hkv, d), draw(tq, hq, d), draw(tq, hkv, d), draw(tq, hkv, d)
+    first = np.repeat(offs[cu_blk[:-1]], np.diff(cu_blk))  # of each block's prompt
+    k_ctx = torch.empty_like(kc)
+    ba.ba_reencode_positions(heads, kc, k_ctx, offs[:-1], offs[:-1], lens, None, offs[:-1] - first, ba.REENC_SHIFT)
+    want = gpu_final(ba, heads, q, k_ctx, vc, kf, vf, cu_q, offs[cu_blk])
+    got = torch.full_like(want, float("nan"))
+    n = ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens)
+    ba.ba_final_block_attention_cached(heads, q, kc, vc, kf, vf, got, None, cu_q, cu_blk, offs[:-1], lens, None, None, None,
+                                       torch.empty(n, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+
+
 def test_final_block_from_block_cache_agrees_with_two_step_path(ba, cached_route):
     """Same inputs through ba_reencode_positions + ba_final_block_attention: the two GPU routes differ
     only by where the extra bf16 rounding falls (re-encoded keys there, re-turned queries here)."""
