@@ -548,9 +548,10 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
 // eight products before and eight behind the exchange, and fit three waves to a SIMD.
 // Eight prompts of 20 passages of 100 to 300 tokens and a query block (33,746 tokens, 32 query heads over 8 of
 // 128, 208 GFLOP in four products): 470 us as one wave per 32 keys with the mask tests among the exponentials,
-// 370 with straight code per tile, 315 to 345 as it is; 990 MB read (q^ and dO once are 553), 138 written.  What is
-// left is waiting, for the exchange and between the barriers: without the tile copies 287, without the
-// exponentials 331; a third buffer does not fit three workgroups, and asking for lines two tiles ahead cost 14.
+// 370 with straight code per tile, 315 to 340 as it is; 990 MB read (q^ and dO once are 553), 138 written.  What is
+// left is waiting: waves wait 38 % of their time for memory and at barriers and 33 % to issue, with the matrix pipes 36 % and
+// LDS 33 % busy.  Without the tile copies 287, without the exponentials 331; with B's products moved off the exchange no
+// change; a third buffer does not fit three workgroups, and asking for lines two tiles ahead cost 14.
 template <int D>
 struct KvGeo {
   using G = BGeo<D>;
@@ -735,9 +736,8 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
   lds_char *const pex = smem + 2 * BUFB + pair * KG::PEXB + lane * 16;
   const uint32_t ofs1 = is_b ? TB : 0u, ofs2 = is_b ? 0u : TB;  // the tile of the products before the exchange, behind it
-  // What bounds a tile is the chain of its products, not the matrix pipe (by its operations some 40 % busy) nor LDS.  Left to itself the
-  // compiler asks for two fragments, waits, multiplies and asks for the next two: four LDS latencies in a row
-  // ahead of the exchange and one or two behind it.  So both halves hold a rolling window of fragments,
+  // Left to itself the compiler asks for two fragments, waits, multiplies and asks for the next two: four LDS latencies
+  // in a row ahead of the exchange and one or two behind it.  So both halves hold a rolling window of fragments,
   // as many as the registers left by the accumulators take (five of rows, four transposed), the first two
   // transposed ones asked for ahead of the second barrier.  Forward and backward of eight prompts of 20
   // passages, 32 over 8 heads of 128: 968 -> 958 us; of small calls 0.93 to 0.98 of the time.
