@@ -42,12 +42,15 @@ struct Chunk {
   }
 };
 
-// y = R(angle) x on one (a, b) pair: [[c, -s], [s, c]] (Eq. 1 / Eq. 3).
+// y = R(angle) x on one (x, y) pair: [[c, -s], [s, c]] (Eq. 1 / Eq. 3).  Which product is the fused one is written out: left
+// to the compiler it changes with the code around it, and with it the last bit of a key now and then.  (It did: packed fp32
+// keys, a third of them, came out with other last bits than the same keys with strides.)
+__device__ __forceinline__ float rot_x(float x, float y, float c, float s) { return __builtin_fmaf(c, x, -(s * y)); }
+__device__ __forceinline__ float rot_y(float x, float y, float c, float s) { return __builtin_fmaf(s, x, c * y); }
 __device__ __forceinline__ void rotate(float &a, float &b, float c, float s) {
-  float na = c * a - s * b;
-  float nb = s * a + c * b;
+  const float na = rot_x(a, b, c, s);
+  b = rot_y(a, b, c, s);
   a = na;
-  b = nb;
 }
 
 // The block's entries of ReencRowsParams::row_table, by one workgroup.
@@ -184,10 +187,6 @@ __device__ __forceinline__ void reencode_run(const Params &p, const Blocks &bloc
 }
 
 // ---- RoPE pre-pass -------------------------------------------------------------------------------------
-// Eq. 1 on one pair.  Which product is the fused one is written out: left to the compiler it changes with
-// the code around it, and with it the last bit of a key now and then.
-__device__ __forceinline__ float rot_x(float x, float y, float c, float s) { return __builtin_fmaf(c, x, -(s * y)); }
-__device__ __forceinline__ float rot_y(float x, float y, float c, float s) { return __builtin_fmaf(s, x, c * y); }
 __device__ __forceinline__ uint32_t rotated(float x, float y, float c, float s) {
   return pack_bf16(rot_x(x, y, c, s), rot_y(x, y, c, s));
 }

@@ -7,8 +7,8 @@
 // The gather is bound by memory and by how fast it gets going.  What it writes is read by the next kernel and what it
 // reads may still be in the caches, so neither goes past them, and a thread moves two pieces, not eight (four times the
 // workgroups): 512 blocks of 20 to 60 tokens, 32 over 8 heads of 128, 42 MB in and out: the call 62.1 -> 52.1 us, 66 -> 58
-// with eight such caches in turn.  (Four pieces 56, with the hint 59; one piece 50, but then the compiler fuses the other
-// product of a rotation and last bits move.)
+// with eight such caches in turn.  (Four pieces 56, with the hint 59; one piece 50, at twice the workgroups where block
+// lengths differ.)
 #include "ba_rotate.h"
 #include "ba_schedule.h"
 

@@ -116,26 +116,60 @@ def test_reencode_f32_relative_error(ba, layout, mode):
     assert rel <= REENC_F32_REL_TOL, f"relative error {rel:.3e}"
 
 
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "bf16"), (128, "f32"), (64, "f32")])
 @pytest.mark.parametrize("layout,mode,total", [(0, 0, 66000), (1, 0, 17000), (0, 1, 17000), (1, 1, 17000)])
-def test_reencode_larger_than_the_caches_gives_the_bits_of_its_parts(ba, layout, mode, total):
+def test_reencode_larger_than_the_caches_gives_the_bits_of_its_parts(ba, layout, mode, total, d, dtype):
     """Just above 256 MB read and written (runs) and 64 MB (the others) a call's loads go past the caches and a thread's share
-    changes; calls of half the blocks each lie below."""
+    changes; calls of half the blocks each lie below.  First and last rows of some blocks against the oracle."""
     torch = torch_mod()
-    heads = ba.Heads(8, 8, 128, 10000.0, rope_layout=layout)
+    size = 2 if dtype == "bf16" else 4
+    total = total * 128 * 2 // (d * size)
+    heads = ba.Heads(8, 8, d, 10000.0, rope_layout=layout)
     line = 256 << 20 if (layout, mode) == (0, 0) else 64 << 20
-    assert total * 8 * 128 * 4 > line > total * 8 * 128 * 2
+    assert total * 8 * d * size * 2 > line > total * 8 * d * size
     n = 50
     lens = np.full(n, total // n, dtype=np.int32)
     off = (np.cumsum(lens) - lens).astype(np.int32)
     new0 = np.arange(n, dtype=np.int32) * 7
     gen = torch.Generator(device="cuda").manual_seed(5)
-    k = torch.randn((total, 8, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    k = torch.randn((total, 8, d), generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
     whole, parts = torch.zeros_like(k), torch.zeros_like(k)
     ba.ba_reencode_positions(heads, k, whole, off, off, lens, None, new0, mode)
     for s in (slice(0, n // 2), slice(n // 2, n)):
         ba.ba_reencode_positions(heads, k, parts, off[s], off[s], lens[s], None, new0[s], mode)
     torch.cuda.synchronize()
-    assert torch.equal(whole.view(torch.int16), parts.view(torch.int16))
+    as_int = torch.int16 if dtype == "bf16" else torch.int32
+    assert torch.equal(whole.view(as_int), parts.view(as_int))
+    for b in (0, 24, 49):
+        for u in (0, int(lens[b]) - 9):
+            rows = slice(int(off[b]) + u, int(off[b]) + u + 9)
+            at = np.array([new0[b] + (u if mode else 0)], dtype=np.int32)  # a row's own position, or the block's shift
+            ref = oracle.reencode(host_f64(k[rows])[None], [0], [0], [9], oracle.theta(10000.0, d), new_pos0=at, mode=mode, layout=layout)[0]
+            if dtype == "bf16":
+                assert_reencode_bf16(host_bits(whole[rows]), ref, layout, f"block {b}")
+            else:
+                assert pair_norm_rel_err(host_f64(whole[rows]), ref, layout) <= REENC_F32_REL_TOL
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,layout,mode", [(64, 0, 0), (128, 0, 0), (64, 1, 0), (128, 1, 1), (128, 0, 1)])
+def test_reencode_gives_packed_keys_the_bits_of_keys_with_strides(ba, d, layout, mode, dtype):
+    """Packed keys take the streaming kernel (interleaved pairs, uniform shift), the same keys as every other head of a wider
+    tensor the general one: which product of a rotation is the fused one must not depend on that."""
+    torch = torch_mod()
+    hkv, lens = 4, np.array([77, 300, 5, 130], dtype=np.int32)
+    off = (np.cumsum(lens) - lens).astype(np.int32)
+    new = np.array([31744, 250, 0, 7], dtype=np.int32)
+    heads = ba.Heads(hkv, hkv, d, 500000.0, rope_layout=layout)
+    gen = torch.Generator(device="cuda").manual_seed(15)
+    wide = torch.randn((int(lens.sum()), 2 * hkv, d), generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    seen = []
+    for k in (wide[:, ::2], wide[:, ::2].contiguous()):
+        out = torch.zeros((len(wide), hkv, d), dtype=wide.dtype, device="cuda")
+        ba.ba_reencode_positions(heads, k, out, off, off, lens, None, new, mode)
+        torch.cuda.synchronize()
+        seen.append(out.view(torch.uint8).cpu())
+    assert torch.equal(*seen)
 
 
 def test_reencode_2500_blocks_in_one_call(ba):
