@@ -250,8 +250,24 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
 }
 
 
-// The gather of a final block's context and the pre-pass of its first launch's prompts, together (or, where one launch
-// does not take both, one after the other).
+// Whether rotated keys of rows [t0, t1) go where the gather reads (a slot of the cache used again for the query block's
+// keys): the gather has to be done first then.  By whole rows: heads far apart count as touching where nothing is shared.
+static bool writes_gathered_rows(const Gather &g, const ba_tensor *k_rot, int64_t t0, int64_t t1) {
+  const auto row = [&](const void *base, int64_t st, int64_t t) { return (uintptr_t)base + (uintptr_t)(t * st * 2); };
+  const auto row_bytes = [&](int64_t sh) { return (uintptr_t)((g.p.n_kv_heads - 1) * sh + g.p.head_dim) * 2; };
+  const uintptr_t lo = row(k_rot->ptr, k_rot->stride_tok, t0);
+  const uintptr_t hi = row(k_rot->ptr, k_rot->stride_tok, t1 - 1) + row_bytes(k_rot->stride_head);
+  for (int layer = 0; layer < g.p.n_layers; ++layer) {
+    const char *base = (const char *)g.p.src + layer * g.p.src_sl * 2;
+    for (int b = 0; b < g.n_blocks; ++b)
+      if (row(base, g.p.src_st, g.src_off[b]) < hi &&
+          lo < row(base, g.p.src_st, (int64_t)g.src_off[b] + g.len[b] - 1) + row_bytes(g.p.src_sh))
+        return true;
+  }
+  return false;
+}
+// The gather of a final block's context and the pre-pass of its first launch's prompts, together or, where one launch
+// does not take both, one after the other.
 template <typename Blocks, typename Params>
 static int32_t run_gather_prepass_t(Params gp, const Gather &g, const ba::RopePrepassParams &pp, const ba::RopeSegsGather &segs,
                                     const ba::RopeTable &rt, bool *apart, hipStream_t stream) {
@@ -259,14 +275,14 @@ static int32_t run_gather_prepass_t(Params gp, const Gather &g, const ba::RopePr
   int32_t table_end = 0;
   if constexpr (std::is_same<Params, ba::ReencRowsParams>::value) table_end = gp.table_end;
   fill_blocks(&gp, &tab[0], g.n_blocks, 0, g.n_blocks, table_end, g.src_off, g.dst_off, g.len, g.pos_old, g.pos_new);
+  if (*apart || !ba::gather_takes_prepass(gp, tab[0], pp, segs)) {
+    *apart = true;
+    return run_reencode_t<Blocks>(gp, rt, g.n_blocks, g.src_off, g.dst_off, g.len, g.pos_old, g.pos_new, stream);
+  }
   hipError_t e;
   {
     ProfileScope ps(BA_PROFILE_REENCODE, stream);
     e = ba::launch_gather_prepass(gp, tab[0], pp, segs, rt, stream);
-  }
-  if (e == hipErrorNotSupported) {
-    *apart = true;
-    return run_reencode_t<Blocks>(gp, rt, g.n_blocks, g.src_off, g.dst_off, g.len, g.pos_old, g.pos_new, stream);
   }
   if (e != hipSuccess) return device_fail(e, "gather launch");
   return BA_OK;
@@ -278,7 +294,7 @@ static int32_t run_gather_prepass(const ba_heads *h, const Gather &g, const ba::
   ba::RopeSegsGather segs;
   fill_segments(&segs, n, start, pos0);
   const ba::ReencParams &plain = g.p;
-  bool apart = false;
+  bool apart = writes_gathered_rows(g, k_rot, start[0], start[n]);
   int32_t rc;
   if (g.n_blocks <= ba::kReencMaxBlocks)
     rc = g.p.row_table ? run_gather_prepass_t<ba::ReencBlocks>(g.p, g, pp, segs, rt, &apart, stream)

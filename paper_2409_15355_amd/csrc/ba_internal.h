@@ -119,6 +119,9 @@ using RopeRotsSmall = RopeRotsT<kBlkSmallBlocks>;
 // A gathered context's re-encoding (bf16, uniform shift, one or two layers) and the pre-pass of the query block's rows
 // (rotated q and k; no table of rotations, nothing to clear) in one launch.  Params = ReencParams or ReencRowsParams.
 using RopeSegsGather = RopeSegsT<64>;
+// ... where one launch takes both; else the caller launches the two passes one after the other
+template <typename Params, typename Blocks>
+bool gather_takes_prepass(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs);
 template <typename Params, typename Blocks>
 hipError_t launch_gather_prepass(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
                                  const RopeTable &rt, hipStream_t stream);

@@ -44,23 +44,34 @@ __global__ __launch_bounds__(kRotThreads) void gather_prepass_kernel(Params gp, 
     reencode_tokens<Chunk<uint16_t, false, false>, D, LAYOUT, 0, kRotThreads / (D / 16)>(gp, blocks, rt, bx, b, layer);
 }
 
+// packed keys of interleaved pairs
+template <typename Params>
+bool is_runs(const Params &gp) {
+  const int64_t D = gp.head_dim, row = gp.n_kv_heads * D;
+  return gp.layout == 0 && gp.src_sh == D && gp.dst_sh == D && gp.src_st == row && gp.dst_st == row;
+}
+
+// the grid, and how many workgroups it has in all
+template <typename Params, typename Blocks>
+int64_t make_grid(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs, GatherGrid *g) {
+  const int TPP = kRotThreads / (gp.head_dim / 16);  // tokens per workgroup, of either pass
+  const int64_t pre_x = ((int64_t)segs.start[segs.n] - segs.start[0] + TPP - 1) / TPP;
+  const int64_t n_pre = pre_x * (q_groups(pp) + (pp.n_kv_heads + pp.heads_per_thread - 1) / pp.heads_per_thread);
+  constexpr int kWgPieces = kUnroll * kRotThreads;
+  const int64_t x = is_runs(gp) ? ((int64_t)gp.max_len * gp.n_kv_heads * (gp.head_dim / 8) + kWgPieces - 1) / kWgPieces
+                                : ((int64_t)gp.max_len + TPP - 1) / TPP * gp.n_head_groups;
+  g->pre_x = (uint32_t)pre_x;
+  g->n_pre = (uint32_t)n_pre;
+  g->x = (uint32_t)x;
+  return n_pre + x * blocks.n * gp.n_layers;
+}
+
 template <int D, int LAYOUT, bool kRuns, typename Params, typename Blocks>
 hipError_t launch_t(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
                     const RopeTable &rt, hipStream_t stream) {
-  constexpr int TPP = kRotThreads / (D / 16);  // tokens per workgroup, of either pass
   GatherGrid g;
-  g.pre_x = (uint32_t)((segs.start[segs.n] - segs.start[0] + TPP - 1) / TPP);
-  const uint32_t groups = (uint32_t)(q_groups(pp) + (pp.n_kv_heads + pp.heads_per_thread - 1) / pp.heads_per_thread);
-  g.n_pre = g.pre_x * groups;
-  if (kRuns)
-    g.x = (uint32_t)(((int64_t)gp.max_len * gp.n_kv_heads * (D / 8) + kUnroll * kRotThreads - 1) / (kUnroll * kRotThreads));
-  else
-    g.x = (uint32_t)((gp.max_len + TPP - 1) / TPP * gp.n_head_groups);
+  const int64_t n_wg = make_grid(gp, blocks, pp, segs, &g);
   if (g.pre_x == 0 || g.x == 0 || gp.n_layers > 2) return hipErrorInvalidValue;
-  // The caller launches the two passes one after the other where one long block among a thousand short ones takes the
-  // one dimension used here beyond the 2^32 threads that the runtime launches.
-  const int64_t n_wg = (int64_t)g.n_pre + (int64_t)g.x * blocks.n * gp.n_layers;
-  if (n_wg * kRotThreads > 0xffffffffll) return hipErrorNotSupported;
   g.pre_div = make_fast_div(g.pre_x);
   g.x_div = make_fast_div(g.x);
   hipLaunchKernelGGL((gather_prepass_kernel<D, LAYOUT, kRuns, Params, Blocks>), dim3((unsigned)n_wg), dim3(kRotThreads), 0, stream,
@@ -71,12 +82,19 @@ hipError_t launch_t(const Params &gp, const Blocks &blocks, const RopePrepassPar
 template <int D, typename Params, typename Blocks>
 hipError_t launch_d(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
                     const RopeTable &rt, hipStream_t stream) {
-  const bool packed = gp.src_sh == D && gp.dst_sh == D && gp.src_st == (int64_t)gp.n_kv_heads * D && gp.dst_st == (int64_t)gp.n_kv_heads * D;
   if (gp.layout != 0) return launch_t<D, 1, false>(gp, blocks, pp, segs, rt, stream);
-  return packed ? launch_t<D, 0, true>(gp, blocks, pp, segs, rt, stream) : launch_t<D, 0, false>(gp, blocks, pp, segs, rt, stream);
+  return is_runs(gp) ? launch_t<D, 0, true>(gp, blocks, pp, segs, rt, stream) : launch_t<D, 0, false>(gp, blocks, pp, segs, rt, stream);
 }
 
 }  // namespace
+
+// Not where one long block among a thousand short ones takes the one dimension used here beyond the 2^32 threads that the
+// runtime launches.
+template <typename Params, typename Blocks>
+bool gather_takes_prepass(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs) {
+  GatherGrid g;
+  return make_grid(gp, blocks, pp, segs, &g) * kRotThreads <= 0xffffffffll;
+}
 
 template <typename Params, typename Blocks>
 hipError_t launch_gather_prepass(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
@@ -86,9 +104,13 @@ hipError_t launch_gather_prepass(const Params &gp, const Blocks &blocks, const R
   return hipErrorInvalidValue;
 }
 
+template bool gather_takes_prepass(const ReencParams &, const ReencBlocks &, const RopePrepassParams &, const RopeSegsGather &);
 template hipError_t launch_gather_prepass(const ReencParams &, const ReencBlocks &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
+template bool gather_takes_prepass(const ReencParams &, const ReencBlocksLarge &, const RopePrepassParams &, const RopeSegsGather &);
 template hipError_t launch_gather_prepass(const ReencParams &, const ReencBlocksLarge &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
+template bool gather_takes_prepass(const ReencRowsParams &, const ReencBlocks &, const RopePrepassParams &, const RopeSegsGather &);
 template hipError_t launch_gather_prepass(const ReencRowsParams &, const ReencBlocks &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
+template bool gather_takes_prepass(const ReencRowsParams &, const ReencBlocksLarge &, const RopePrepassParams &, const RopeSegsGather &);
 template hipError_t launch_gather_prepass(const ReencRowsParams &, const ReencBlocksLarge &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
 
 }  // namespace ba

@@ -1080,6 +1080,34 @@ def test_gathered_calls_that_copy_their_values(ba, why):
     assert np.array_equal(host_bits(o), want)
 
 
+@pytest.mark.parametrize("d,hkv,n,layout", [(128, 8, 100, 0), (64, 2, 20, 0), (128, 8, 100, 1)])
+def test_gathered_call_whose_rotated_keys_replace_a_cached_block(ba, d, hkv, n, layout):
+    """The query block's rotated keys take the place of a block that the call itself still reads: the context is gathered
+    before they are written (two launches).  Next to the blocks nothing has to wait (one)."""
+    torch = torch_mod()
+    lens = np.full(n, 40, dtype=np.int32)
+    T, lq, hq = int(lens.sum()), 70, 2 * hkv
+    off = (np.cumsum(lens) - lens).astype(np.int32)
+    heads = ba.Heads(hq, hkv, d, 10000.0, rope_layout=layout)
+    gen = torch.Generator(device="cuda").manual_seed(1440)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    cache, vc, q, kf, vf = draw(T + lq, hkv, d), draw(T, hkv, d), draw(lq, hq, d), draw(lq, hkv, d), draw(lq, hkv, d)
+    cu_q, cu_blk = np.array([0, lq], dtype=np.int32), np.array([0, n], dtype=np.int32)
+    ws = torch.empty(ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens, True), dtype=torch.uint8, device="cuda")
+    seen = []
+    for at, launches in ((None, 1), (T, 1), (T - 50, 2), (25, 2)):
+        kc = cache.clone()
+        rot = torch.empty_like(kf) if at is None else kc[at:at + lq]
+        o = torch.full_like(q, float("nan"))
+        ba.ba_profile_begin()
+        ba.ba_final_block_attention_cached(heads, q, kc, vc, kf, vf, o, rot, cu_q, cu_blk, off, lens, None, None, None, ws)
+        torch.cuda.synchronize()
+        assert ba.ba_profile_end()[1][ba.PROFILE_REENCODE] == launches
+        seen.append((host_bits(o), host_bits(rot)))
+    for o, rot in seen[1:]:
+        assert np.array_equal(o, seen[0][0]) and np.array_equal(rot, seen[0][1])
+
+
 def test_gathered_context_whose_gather_is_a_launch_of_its_own(ba):
     """One long block among a table-full of short ones: gather and pre-pass do not fit one launch's grid.  Against
     re-encode + final block on the same inputs: the same kernels' arithmetic, so the same bits."""
