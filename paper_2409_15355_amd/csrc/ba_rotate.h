@@ -42,6 +42,15 @@ struct Chunk {
   }
 };
 
+// A launch has as many workgroups per block and layer as its longest block needs, and those of the shorter blocks find nothing
+// to do.  Where one long block lies among many short ones these are nearly all, and starting them, four to five a
+// nanosecond, is what the launch takes; two pieces per thread instead of eight make four times as many.  A launch of few
+// workgroups does not feel them, nor one whose memory traffic takes as long: eight idle ones for each that works, and 32,768.
+// Re-encoding, one block among n of 60 tokens at 8 heads of 128, two pieces / eight: 1,920 among 90 (42,000 idle) 14.5 / 14.5 us,
+// 3,840 among 90 (85,000) 20.9 / 14.9; 480 among 500 (52,000 idle, 7,600 work) 22.8 / 27.4, 960 (112,000) 30.2 / 28.8,
+// 3,840 (473,000) 105 / 42; 3,200 among 31 of 200, four layers (93,000, 9,400) 26.1 / 32.3, 6,400 (191,000, 12,600) 51.8 / 40.4.
+inline bool mostly_idle(int64_t launched, int64_t needed) { return launched - needed > 32768 + 8 * needed; }
+
 // y = R(angle) x on one (x, y) pair: [[c, -s], [s, c]] (Eq. 1 / Eq. 3).  Which product is the fused one is written out: left
 // to the compiler it changes with the code around it, and with it the last bit of a key now and then.  (It did: packed fp32
 // keys, a third of them, came out with other last bits than the same keys with strides.)

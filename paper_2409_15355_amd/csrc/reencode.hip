@@ -26,10 +26,12 @@ __global__ __launch_bounds__(kRotThreads) void reencode_shift_linear_kernel(Para
 }
 
 template <typename Ch, int D, int UNROLL, typename Params, typename Blocks>
-hipError_t launch_linear(const Params &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
-  constexpr int CH = D / Ch::VEC;
-  const int64_t max_chunks = (int64_t)p.max_len * p.n_kv_heads * CH;
-  dim3 grid((unsigned)((max_chunks + UNROLL * kRotThreads - 1) / (UNROLL * kRotThreads)), blocks.n, p.n_layers);
+dim3 linear_grid(const Params &p, const Blocks &blocks) {
+  const int64_t max_chunks = (int64_t)p.max_len * p.n_kv_heads * (D / Ch::VEC);
+  return dim3((unsigned)((max_chunks + UNROLL * kRotThreads - 1) / (UNROLL * kRotThreads)), blocks.n, p.n_layers);
+}
+template <typename Ch, int D, int UNROLL, typename Params, typename Blocks>
+hipError_t launch_linear(const Params &p, const Blocks &blocks, const RopeTable &rt, dim3 grid, hipStream_t stream) {
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return hipSuccess;
   hipLaunchKernelGGL((reencode_shift_linear_kernel<Ch, D, UNROLL, Params, Blocks>), grid, dim3(kRotThreads), 0, stream, p, blocks, rt);
   return hipGetLastError();
@@ -50,9 +52,11 @@ hipError_t launch_t(const Params &p, const Blocks &blocks, const RopeTable &rt, 
 // the keys as cached may still lie there.  Time with plain loads / with the hint, one cache re-encoded over and over and
 // eight in turn (880 MB to 2 GB, nothing of which is found again):
 //   - runs, two pieces per thread instead of eight (four times the workgroups): 157 MB 0.78 and 0.92, 128 MB 0.74 and 0.87
-//     (of that the two pieces alone 0.87 and 0.90, 0.80 and 0.84); 412 MB 1.00 and 1.00.  In launches beyond the cache eight.
+//     (of that the two pieces alone 0.87 and 0.90, 0.80 and 0.84); 412 MB 1.00 and 1.00.  In launches beyond the cache eight,
+//     and where a launch is mostly_idle, with the hint as beyond the cache.
 //   - the others: 39 MB 0.91 and 0.90, 45 MB 0.96 and 0.84; but 110 MB 0.87 and 1.02, 157 MB 0.87 and 1.03, 262 MB 0.86 and
 //     1.02, and with three in turn 262 MB is 1.02 as well: plain up to a quarter of the cache.
+// (By launch, not by call: eight caches in turn are what a longer list is, several launches of such a size.)
 template <typename T, int D, typename Params, typename Blocks>
 hipError_t launch_d(const Params &p, const Blocks &blocks, const RopeTable &rt, hipStream_t stream) {
   typedef Chunk<T, true, true> Past;
@@ -62,8 +66,17 @@ hipError_t launch_d(const Params &p, const Blocks &blocks, const RopeTable &rt, 
   int64_t tokens = 0;
   for (int i = 0; i < blocks.n; ++i) tokens += blocks.len[i];
   const int64_t bytes = tokens * p.n_layers * p.n_kv_heads * D * (int64_t)sizeof(T) * 2;
-  if (p.layout == 0 && p.mode == 0 && packed)
-    return bytes > kCacheBytes ? launch_linear<Past, D, 8>(p, blocks, rt, stream) : launch_linear<Near, D, 2>(p, blocks, rt, stream);
+  if (p.layout == 0 && p.mode == 0 && packed) {
+    const dim3 two = linear_grid<Near, D, 2>(p, blocks);
+    const int64_t needed = (tokens * p.n_kv_heads * (D / Near::VEC) / (2 * kRotThreads) + blocks.n) * p.n_layers;
+    const bool idle = mostly_idle((int64_t)two.x * two.y * two.z, needed);
+    if (bytes <= kCacheBytes && !idle) return launch_linear<Near, D, 2>(p, blocks, rt, two, stream);
+    dim3 eight = linear_grid<Past, D, 8>(p, blocks);
+    // (an odd number per block: workgroups go to the XCDs in turn, and the first few of every block, all that short blocks
+    // need, went to the same ones: 1,280 among 500 of 20 tokens, four layers: 80 per block 218 us, 81 54, two pieces 140)
+    if (idle) eight.x |= 1;
+    return launch_linear<Past, D, 8>(p, blocks, rt, eight, stream);
+  }
   const auto launch = [&](auto ch) {
     typedef decltype(ch) Ch;
     if (p.mode == 0)

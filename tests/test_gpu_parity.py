@@ -172,6 +172,30 @@ def test_reencode_gives_packed_keys_the_bits_of_keys_with_strides(ba, d, layout,
     assert torch.equal(*seen)
 
 
+@pytest.mark.parametrize("long,n,short,layers,d,dtype", [
+    # (idle workgroups below and above the line at which a thread takes eight pieces)
+    (1900, 90, 60, 1, 128, "bf16"), (3840, 90, 60, 1, 128, "bf16"), (640, 500, 7, 3, 128, "bf16"), (300, 500, 7, 3, 128, "bf16"),
+    (8000, 90, 1, 1, 64, "bf16"), (2000, 90, 60, 1, 128, "f32"), (4001, 90, 33, 1, 64, "f32")])
+def test_reencode_of_one_long_block_among_short_ones(ba, long, n, short, layers, d, dtype):
+    """The bits of two calls, one with the long block and one with the others, neither with idle workgroups."""
+    torch = torch_mod()
+    lens = np.full(n + 1, short, dtype=np.int32)
+    at = n // 3
+    lens[at] = long
+    off = (np.cumsum(lens) - lens).astype(np.int32)
+    new0 = (np.arange(n + 1) * 11).astype(np.int32)
+    heads = ba.Heads(8, 8, d, 10000.0)
+    gen = torch.Generator(device="cuda").manual_seed(16)
+    k = torch.randn((layers, int(lens.sum()), 8, d), generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    whole, parts = torch.zeros_like(k), torch.zeros_like(k)
+    ba.ba_reencode_positions(heads, k, whole, off, off, lens, None, new0)
+    for s in ([at], [b for b in range(n + 1) if b != at]):
+        ba.ba_reencode_positions(heads, k, parts, off[s], off[s], lens[s], None, new0[s])
+    torch.cuda.synchronize()
+    as_int = torch.int16 if dtype == "bf16" else torch.int32
+    assert torch.equal(whole.view(as_int), parts.view(as_int))
+
+
 def test_reencode_2500_blocks_in_one_call(ba):
     """More blocks than the larger of the two block tables holds (three launches), gathered into the
     reverse order, two layers."""
