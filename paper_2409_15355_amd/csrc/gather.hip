@@ -16,6 +16,7 @@ namespace ba {
 namespace {
 
 constexpr int kUnroll = 2;  // 16-byte pieces of a run per thread
+constexpr int kWgPieces = kUnroll * kRotThreads;
 
 struct GatherGrid {
   uint32_t n_pre, pre_x;  // workgroups of the pre-pass, and of one of its head groups
@@ -57,7 +58,6 @@ int64_t make_grid(const Params &gp, const Blocks &blocks, const RopePrepassParam
   const int TPP = kRotThreads / (gp.head_dim / 16);  // tokens per workgroup, of either pass
   const int64_t pre_x = ((int64_t)segs.start[segs.n] - segs.start[0] + TPP - 1) / TPP;
   const int64_t n_pre = pre_x * (q_groups(pp) + (pp.n_kv_heads + pp.heads_per_thread - 1) / pp.heads_per_thread);
-  constexpr int kWgPieces = kUnroll * kRotThreads;
   const int64_t x = is_runs(gp) ? ((int64_t)gp.max_len * gp.n_kv_heads * (gp.head_dim / 8) + kWgPieces - 1) / kWgPieces
                                 : ((int64_t)gp.max_len + TPP - 1) / TPP * gp.n_head_groups;
   g->pre_x = (uint32_t)pre_x;
@@ -88,12 +88,20 @@ hipError_t launch_d(const Params &gp, const Blocks &blocks, const RopePrepassPar
 
 }  // namespace
 
-// Not where one long block among a thousand short ones takes the one dimension used here beyond the 2^32 threads that the
-// runtime launches.
+// Where the two are one launch.  Not where one long block lies among many short ones and the launch would be mostly_idle (or, further
+// on, beyond the 2^32 threads that the runtime launches in the one dimension used here): the re-encode kernels have the
+// eight pieces a thread for that, and an idle workgroup costs less with their arguments.  One block among n of 30 tokens, 8
+// heads of 128, together / apart: 700 among 255 (43,000 idle, 2,400 work) 38.6 / 43, 1,000 (62,000) 42.3 / 41.8, 3,000 (190,000) 73.7 / 49.3;
+// 400 among 1,023 (93,000, 8,800) 73.9 / 73.1, 1,000 (247,000) 107 / 81; half pairs 1,000 among 255 53.8 / 55, 3,000 47.3 / 44.9.
 template <typename Params, typename Blocks>
 bool gather_takes_prepass(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs) {
   GatherGrid g;
-  return make_grid(gp, blocks, pp, segs, &g) * kRotThreads <= 0xffffffffll;
+  const int64_t n_wg = make_grid(gp, blocks, pp, segs, &g);
+  int64_t tokens = 0;
+  for (int b = 0; b < blocks.n; ++b) tokens += blocks.len[b];
+  const int64_t pieces = tokens * gp.n_kv_heads * (gp.head_dim / 8);  // of 16 bytes, of one layer
+  const int64_t needed = (is_runs(gp) ? pieces / kWgPieces + blocks.n : (tokens / (kRotThreads / (gp.head_dim / 16)) + blocks.n) * gp.n_head_groups) * gp.n_layers;
+  return n_wg * kRotThreads <= 0xffffffffll && !mostly_idle(n_wg - g.n_pre, needed);
 }
 
 template <typename Params, typename Blocks>

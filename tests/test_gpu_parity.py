@@ -1158,6 +1158,36 @@ def test_gathered_context_whose_gather_is_a_launch_of_its_own(ba):
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("long,n,short,layout,copied,launches", [
+    # idle workgroups below and above the line at which gather and pre-pass go apart
+    (700, 255, 30, 0, False, 1), (1000, 255, 30, 0, False, 2), (400, 255, 30, 1, False, 1), (3000, 255, 30, 1, False, 2),
+    (300, 255, 30, 0, True, 1), (700, 255, 30, 0, True, 2), (70000, 1023, 60, 0, True, 2)])
+def test_gathered_contexts_of_one_long_block_among_short_ones(ba, long, n, short, layout, copied, launches):
+    """The bits of a context gathered by hand, with value rows fetched through the table and (a call with XCD speeds) with the
+    values copied as a second layer."""
+    torch = torch_mod()
+    hq, hkv, d, lq = 8, 8, 128, 5
+    lens = np.full(n + 1, short, dtype=np.int32)
+    lens[n // 2] = long
+    heads = ba.Heads(hq, hkv, d, 500000.0, rope_layout=layout, xcd_speed=[1.03, 0.97, 1.02, 0.97, 1.03, 1.0, 1.02, 0.96] if copied else None)
+    T = int(lens.sum())
+    off = (np.cumsum(lens) - lens).astype(np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(1450)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    kc, vc, q, kf, vf = draw(T, hkv, d), draw(T, hkv, d), draw(lq, hq, d), draw(lq, hkv, d), draw(lq, hkv, d)
+    cu_q, cu_blk = np.array([0, lq], dtype=np.int32), np.array([0, n + 1], dtype=np.int32)
+    k_ctx = torch.empty_like(kc)
+    ba.ba_reencode_positions(heads, kc, k_ctx, off, off, lens, None, off, ba.REENC_SHIFT)
+    want = gpu_final(ba, heads, q, k_ctx, vc, kf, vf, cu_q, np.array([0, T], dtype=np.int32))
+    got = torch.full_like(want, float("nan"))
+    ws = torch.full((ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens),), 255, dtype=torch.uint8, device="cuda")
+    ba.ba_profile_begin()
+    ba.ba_final_block_attention_cached(heads, q, kc, vc, kf, vf, got, None, cu_q, cu_blk, off, lens, None, None, None, ws)
+    torch.cuda.synchronize()
+    assert ba.ba_profile_end()[1][ba.PROFILE_REENCODE] == launches
+    assert torch.equal(got, want)
+
+
 def test_final_block_from_block_cache_agrees_with_two_step_path(ba, cached_route):
     """Same inputs through ba_reencode_positions + ba_final_block_attention: the two GPU routes differ
     only by where the extra bf16 rounding falls (re-encoded keys there, re-turned queries here)."""
