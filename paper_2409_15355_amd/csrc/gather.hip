@@ -93,6 +93,9 @@ hipError_t launch_d(const Params &gp, const Blocks &blocks, const RopePrepassPar
 // eight pieces a thread for that, and an idle workgroup costs less with their arguments.  One block among n of 30 tokens, 8
 // heads of 128, together / apart: 700 among 255 (43,000 idle, 2,400 work) 38.6 / 43, 1,000 (62,000) 42.3 / 41.8, 3,000 (190,000) 73.7 / 49.3;
 // 400 among 1,023 (93,000, 8,800) 73.9 / 73.1, 1,000 (247,000) 107 / 81; half pairs 1,000 among 255 53.8 / 55, 3,000 47.3 / 44.9.
+// And not where it reads and writes more than the cache holds: plain loads and stores lose there.  1,024 blocks, together / apart, also with
+// four such caches in turn: of 60 tokens (252 MB) 111 / 117, of 80 (336 MB) 148 / 146, of 130 233 / 227, of 200 350 / 336; half pairs 110 / 115,
+// 147 / 150, 242 / 232, 363 / 342.
 template <typename Params, typename Blocks>
 bool gather_takes_prepass(const Params &gp, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs) {
   GatherGrid g;
@@ -101,7 +104,7 @@ bool gather_takes_prepass(const Params &gp, const Blocks &blocks, const RopePrep
   for (int b = 0; b < blocks.n; ++b) tokens += blocks.len[b];
   const int64_t pieces = tokens * gp.n_kv_heads * (gp.head_dim / 8);  // of 16 bytes, of one layer
   const int64_t needed = (is_runs(gp) ? pieces / kWgPieces + blocks.n : (tokens / (kRotThreads / (gp.head_dim / 16)) + blocks.n) * gp.n_head_groups) * gp.n_layers;
-  return n_wg * kRotThreads <= 0xffffffffll && !mostly_idle(n_wg - g.n_pre, needed);
+  return n_wg * kRotThreads <= 0xffffffffll && !mostly_idle(n_wg - g.n_pre, needed) && pieces * gp.n_layers * 32 <= kCacheBytes;
 }
 
 template <typename Params, typename Blocks>
