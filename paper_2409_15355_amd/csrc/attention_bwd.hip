@@ -741,7 +741,11 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   // as many as the registers left by the accumulators take (five of rows, four transposed), the first two
   // transposed ones asked for ahead of the second barrier.  Forward and backward of eight prompts of 20
   // passages, 32 over 8 heads of 128: 968 -> 958 us; of small calls 0.93 to 0.98 of the time.
-  constexpr int kRowWin = G::KCH < 5 ? G::KCH : 5, kTrWin = 4, kTrAhead = 2;
+  // At head_dim 64 there are half as many fragments and five waves fit a SIMD as long as 96 registers do; a window takes the
+  // kernel beyond that.  One fragment and the compiler's own order there: 300 passages of 40 to 160 tokens, 16 over 2 heads,
+  // 61 us, 72 with the windows; eight prompts of 20 passages, 32 over 8, 173 and 183.
+  constexpr int kRowWin = D == 128 ? 5 : 1, kTrWin = D == 128 ? 4 : 1, kTrAhead = D == 128 ? 2 : 0, kPWin = D == 128 ? 4 : 1;
+  const auto fence = []() __attribute__((always_inline)) { if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0); };
 #pragma unroll 1
   for (int i = t0; i < n_t; ++i) {
     dma_wait<0>();
@@ -768,12 +772,12 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
       bf16x8_t fr[kRowWin];
 #pragma unroll
       for (int kk = 0; kk < kRowWin; ++kk) fr[kk] = row_frag<D>(buf + ofs1 + r_rd[kk / 2], kk);
-      __builtin_amdgcn_sched_barrier(0);
+      fence();
 #pragma unroll
       for (int kk = 0; kk < G::KCH; ++kk) {
         x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk % kRowWin], kv[kk], x, 0, 0, 0);
         if (kk + kRowWin < G::KCH) fr[kk % kRowWin] = row_frag<D>(buf + ofs1 + r_rd[(kk + kRowWin) / 2], kk + kRowWin);
-        __builtin_amdgcn_sched_barrier(0);
+        fence();
       }
       // Rows this key may not see: rows beyond the block, and (own block) tokens before the key; their P and
       // dS become 0 whatever the products gave.  Under one branch, which most tiles do not take.
@@ -804,12 +808,15 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
     wg_barrier();
     if (active) {
       if (is_b) {
-        f32x4_t four[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) four[j] = *(const lds_f32x4 *)(pex + j * 1024);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int j0 = 0; j0 < 4; j0 += kPWin) {
+          f32x4_t four[kPWin];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) x[v] *= four[v >> 2][v & 3];
+          for (int j = 0; j < kPWin; ++j) four[j] = *(const lds_f32x4 *)(pex + (j0 + j) * 1024);
+          fence();
+#pragma unroll
+          for (int v = 0; v < 4 * kPWin; ++v) x[4 * j0 + v] *= four[v >> 2][v & 3];
+        }
       }
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
@@ -820,13 +827,13 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
       }
 #pragma unroll
       for (int st = kTrAhead; st < kTrWin; ++st) tr[st] = tr_frag<D>(buf + ofs2 + t_rd[st % G::DT], st / G::DT);
-      __builtin_amdgcn_sched_barrier(0);
+      fence();
 #pragma unroll
       for (int st = 0; st < 2 * G::DT; ++st) {
         acc[st % G::DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr[st % kTrWin], pf[st / G::DT], acc[st % G::DT], 0, 0, 0);
         if (st + kTrWin < 2 * G::DT)
           tr[st % kTrWin] = tr_frag<D>(buf + ofs2 + t_rd[(st + kTrWin) % G::DT], (st + kTrWin) / G::DT);
-        __builtin_amdgcn_sched_barrier(0);
+        fence();
       }
     }
   }
