@@ -912,8 +912,10 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
     const int64_t unit = ((int64_t)(BA_ARG(tile_base) + rowtile) * BA_ARG(n_kv_heads) + kvh) * kWaves + wave;
     const int64_t slot = (int64_t)split * BA_ARG(part_units) + unit;
     char *dst = (char *)BA_ARG(part_o) + slot * (int64_t)(32 * D * 2) + lane * 16;
-    // (a wave without rows leaves nothing but that, from split 0: 7 of 8 waves of a query block of a few tokens)
-    bool any_rows = wave_has_rows;
+    // (a wave without rows leaves nothing but that, from split 0: 7 of 8 waves of a query block of a few tokens.  Not asked in
+    // per-block encoding, which has no splits: the question alone changes the registers of the walk, one block of 16,000 tokens,
+    // 4 heads of 64, 232 -> 246 us)
+    bool any_rows = std::is_same<Meta, EncodeMeta>::value || wave_has_rows;
     if constexpr (kBlocks) {
       int wave_row = wave * 32;
       asm volatile("" : "+s"(wave_row));
