@@ -243,7 +243,8 @@ size_t ba_final_block_attention_workspace_bytes(const ba_heads *heads, int32_t n
  * ba_final_block_attention_workspace_bytes() exceeds BA_STATIC_SCRATCH_BYTES returns
  * BA_ERR_WORKSPACE and launches nothing.  All calls on one GPU share that GPU's array: calls that
  * overlap in time on one GPU (two streams, two threads) race; calls on one stream are safe.
- * Nothing in the array has to be cleared between calls: a call writes every byte it later reads.
+ * Nothing in the array has to be cleared between calls: no result depends on a byte that the call has
+ * not written (the merge may load the partial result of 32 rows that no prompt has, and drops it).
  */
 #define BA_STATIC_SCRATCH_BYTES (32u << 20)
 int32_t ba_final_block_attention_static(const ba_heads *heads, const ba_tensor *q_f,
