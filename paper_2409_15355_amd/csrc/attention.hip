@@ -691,7 +691,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
     };
     if (!BA_ARG(q_ready)) {
       if (BA_ARG(q_table)) {
-        // un-rotated rows and the pre-pass's table of scale * (cos, sin) per token: rotate here, so that
+        // un-rotated rows and the pre-pass's table of scale * (cos, sin) by position: rotate here, so that
         // the rotated queries never make a round trip through memory
         // (lanes beyond the problem's rows hold zeros: any row of the table will do, take an existing one)
         rotate_by(reinterpret_cast<const f32x4_t *>(

@@ -540,7 +540,7 @@ size_t ba_encode_blocks_workspace_bytes(const ba_heads *heads, int32_t n_blocks,
   if (rope_mode != BA_ROPE_APPLY) return 0;
   const size_t T = (size_t)block_offsets[n_blocks];
   const size_t k_bytes = have_k_local_out ? 0 : align256(T * heads->n_kv_heads * heads->head_dim * 2);
-  return k_bytes + align256(T * heads->head_dim * 4);  // rotated K; scale * (cos, sin) per token and pair
+  return k_bytes + align256(T * heads->head_dim * 4);  // rotated K; scale * (cos, sin) per position and pair (as many as the longest block has; T bounds them)
 }
 
 int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k,

@@ -70,6 +70,9 @@ int32_t run_rope_prepass(const ba_heads *h, const RopeTable &rt, const ba_tensor
                          int n_rot = 0, float *q_table = nullptr, int table_rows = 0, int32_t *zero = nullptr, int n_zero = 0);
 
 // What the merge of the split partials knows of the rows (AttnParams::merge_rows, merge_sparse).
+// Sparse: the indices are waited for ahead of the other loads, to skip units without rows.  Calls of eight prompts over 2,000
+// context tokens, 32 over 8 heads of 128, sparse / not, by the share of units with rows: 1/8 24.9 / 26.0 us, 3/8 26.3 / 27.2, 4/8
+// 27.1 / 28.2, 5/8 29.5 / 29.9, 6/8 31.3 / 31.2, all 34.7 / 34.7; 8 over 2 of 64 1/8 16.2 / 16.0, 4/8 17.8 / 17.5, all 19.9 / 19.8.
 inline void set_merge_rows(AttnParams *ap, int n_prompts, const int32_t *cu_q, int G) {
   int64_t live = 0, units = 0;  // per KV head
   for (int n = 0; n < n_prompts; ++n) {

@@ -92,6 +92,8 @@ size_t bwd_shares_bytes(const ba_heads *h, int32_t n_prompts, const int32_t *cu_
 // Bytes a call does not run without: they grow with its tokens and nothing else, so a workspace that was large enough
 // for one call is large enough for every call of no more tokens.  What the queries return beyond them is the partial results of
 // shared walks, which follow other rules (a call that leaves the chip idle has more of them): optional.
+// (The table of factors has as many rows as the longest prompt has tokens.  T is kept as its bound: what a call needs then grows
+// with its tokens alone, and a workspace for as many tokens is enough however they are cut into prompts.)
 size_t least_bytes(const ba_heads *h, size_t T, int32_t rope_mode, bool have_k_rot_out) {
   size_t bytes = 0;
   if (h->n_q_heads / h->n_kv_heads < kPadGroup)  // padded q and o, padded log-sum-exps (see head_pad.hip)

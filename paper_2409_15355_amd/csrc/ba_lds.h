@@ -21,7 +21,8 @@ __device__ __forceinline__ int find_segment(const int32_t *tile_start, int n, in
 // that no candidate needs a bounds check: the number of starts behind the first that are at or below the tile, a lane
 // per start and five loads that go out together.  It is the first link of the chain that a short work item spends most of its
 // time in (table, block, query rows, walk, store), and was three dependent rounds of scalar loads: forward and backward of small
-// calls 0.96 to 0.98 of the time, of calls that fill the chip 0.98 to 0.99, the encode kernel of two blocks of 128 tokens 8.9 -> 8.3 us.
+// calls 0.96 to 0.98 of the time, of calls that fill the chip 0.98 to 0.99, the encode kernel of two blocks of 128 tokens 8.9 -> 8.3 us
+// (its call by less than two runs of it differ).
 // (In the main core's tables of prompts and blocks it changes nothing: 20 calls 1.003.)
 __device__ __forceinline__ int find_block(const int32_t *tile_start, int tile) {
   static_assert(kEncMaxBlocks == 5 * 64, "a lane per start");

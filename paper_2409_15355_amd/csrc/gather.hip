@@ -6,9 +6,9 @@
 // context tokens 0.76 to 0.98 of the time.
 // The gather is bound by memory and by how fast it gets going.  What it writes is read by the next kernel and what it
 // reads may still be in the caches, so neither goes past them, and a thread moves two pieces, not eight (four times the
-// workgroups): 512 blocks of 20 to 60 tokens, 32 over 8 heads of 128, 42 MB in and out: the call 62.1 -> 52.1 us, 66 -> 58
-// with eight such caches in turn.  (Four pieces 56, with the hint 59; one piece 50, at twice the workgroups where block
-// lengths differ.)
+// workgroups): 512 blocks of 20 to 60 tokens, 32 over 8 heads of 128, 42 MB in and out: the call 61.7 -> 54.3 us (57.7 -> 46.6 on
+// one cache over and over).  (On one box, where two pieces took 52.1: four 56, with the hint 59; one piece 50, at twice the
+// workgroups where block lengths differ.)
 #include "ba_rotate.h"
 #include "ba_schedule.h"
 

@@ -1161,7 +1161,9 @@ def test_gathered_context_whose_gather_is_a_launch_of_its_own(ba):
 @pytest.mark.parametrize("long,n,short,layout,copied,launches", [
     # idle workgroups below and above the line at which gather and pre-pass go apart
     (700, 255, 30, 0, False, 1), (1000, 255, 30, 0, False, 2), (400, 255, 30, 1, False, 1), (3000, 255, 30, 1, False, 2),
-    (300, 255, 30, 0, True, 1), (700, 255, 30, 0, True, 2), (70000, 1023, 60, 0, True, 2),
+    (300, 255, 30, 0, True, 1), (700, 255, 30, 0, True, 2),
+    # (one launch's grid would not take these)
+    (70000, 1023, 60, 0, False, 2), (70000, 1023, 60, 0, True, 2),
     # 256 MB read and written, and one token more
     (64, 1023, 64, 0, False, 1), (65, 1023, 64, 0, False, 2), (64, 1023, 64, 1, False, 1), (65, 1023, 64, 1, False, 2)])
 def test_gathered_contexts_of_one_long_block_among_short_ones(ba, long, n, short, layout, copied, launches):
