@@ -188,7 +188,18 @@ constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 // prompts: 1.02 in the mean, 0.94 to 1.08 (8 over 1 of 128, eight prompts of 650-1520 tokens and 120-260, forward kernel 52 us
 // unshared and 59 shared, dq 76 and 91); with a lead of one tile of 37 to 86 0.97 to 1.02, of two to five 0.92 to
 // 1.01.  (Calls of hardly any work, a load of less than a quarter of the walk, either way: 1.00 to 1.02.)
+// Last blocks of more than kSharePairs / 2 row tiles times KV heads (a query block of 64 tokens at 32 over 8 heads has 16): their
+// walks were never cut, and a call of one or two such prompts took as long as one workgroup walks, 0.77 us a tile in the forward
+// kernel and 0.85 in the dq kernel (one prompt of 4,400 tokens at 32 over 8 heads of 128: 101 and 111 us, as long as two prompts).  From
+// kShareManyAbove + 1 tiles on they are cut into parts of kShareManyChunk tiles (kShareChunk at head_dim 64), at most
+// kShareManyPairs workgroups a block, in calls that the rules below let share.  Forward and backward, us, unshared / shared, prompts
+// of 20 x 100-300 and 32-128: one 280 / 168, two 336 / 282, at 16 over 8 heads 255 / 120 and 294 / 194; one of 6 x 300-800 and 200-256
+// 238 / 183; 8 over 2 of 64, one of 20 x 100-300 and 200-256 191 / 79.  Parts of 16, 20 and 32 tiles: 170, 169 and 170, 285, 281 and 282;
+// at 64 79 with 16, 85 with 24, 90 with 32.  At most 96, 128 and 256 workgroups: 238, 186 and 182 where 192 take 183.  60 drawn calls of 1 to 6
+// prompts whose walks are as long: 0.48 to 1.01 of the time, 0.85 in the mean.  Not with more than kShareManyHeads KV heads: a prompt of
+// 16 (20 x 200 and 64 tokens, head_dim 64) has the same bits alone and in a batch that fills the chip, and keeps them.
 constexpr int kShareAbove = 36, kShareChunk = 16, kSharePairs = 24;
+constexpr int kShareManyAbove = 55, kShareManyChunk = 24, kShareManyPairs = 192, kShareManyHeads = 8;
 constexpr double kShareLoad = 0.64;
 constexpr double kSharePartTiles = 24.0;  // head_dim 128
 constexpr int kShareLead = 100;
@@ -283,9 +294,8 @@ struct PromptMeta {
   int32_t tile_start[kEncMaxBlocks + 1];  // in row tiles of kShortTileRows rows; INT_MAX beyond [n]
   int32_t kstart[kEncMaxBlocks];          // token offset of the first visible key
   int32_t pos0[kEncMaxBlocks];            // position of the first token inside its prompt
-  // The first n_split blocks' walks are shared out: a block whose last row walks w key tiles is taken by
-  // shared_walk_splits(w, kShareChunk, row tiles x KV heads, kSharePairs) workgroups per row tile and KV head (all row
-  // tiles of split 0 first, then of split 1 ...)
+  // The first n_split blocks' walks are shared out, each by as many workgroups per row tile and KV head as it has
+  // times its row tiles in tile_start (all row tiles of split 0 first, then of split 1 ...)
   int32_t n_split;
 };
 

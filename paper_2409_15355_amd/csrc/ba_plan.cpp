@@ -400,16 +400,20 @@ constexpr int kPromptKeys = 32;  // keys per tile of the forward and dq kernels
 int walk_tiles(int64_t keys) { return (int)((keys - 1) / kPromptKeys + 1); }
 int64_t short_row_tiles(int64_t len, int64_t G) { return (len * G + kShortTileRows - 1) / kShortTileRows; }
 // a last block that sees enough of its prompt for more than one workgroup per row tile
-int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads) {
+int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads, int many_chunk) {
   if (ctx <= 0 || len <= 0) return 1;
   const int w = walk_tiles(ctx + len);
   const int64_t pairs = short_row_tiles(len, G) * n_kv_heads;
-  return w > kShareAbove && pairs <= kSharePairs ? shared_walk_splits(w, kShareChunk, (int)pairs, kSharePairs) : 1;
+  if (w <= kShareAbove) return 1;
+  if (pairs <= kSharePairs / 2) return shared_walk_splits(w, kShareChunk, (int)pairs, kSharePairs);
+  if (w <= kShareManyAbove || pairs > kShareManyPairs || n_kv_heads > kShareManyHeads) return 1;
+  return shared_walk_splits(w, many_chunk, (int)pairs, kShareManyPairs);
 }
 }  // namespace
 
 WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
   WalkShares ws;
+  ws.chunk = h->head_dim == 128 ? kShareManyChunk : kShareChunk;
   const int64_t G = h->n_q_heads / h->n_kv_heads;
   const double part_tiles = h->head_dim == 128 ? kSharePartTiles : 0.0;
   double load = 0.0;  // of the launch with its walks cut, in key tiles
@@ -423,7 +427,7 @@ WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t 
     const int last = cu_blk[n + 1] - 1;
     for (int b = cu_blk[n]; b < last; ++b) add(0, block_offsets[b + 1] - block_offsets[b], 1);
     const int64_t len = block_offsets[last + 1] - block_offsets[last], ctx = block_offsets[last] - block_offsets[cu_blk[n]];
-    const int s = shared_splits(ctx, len, G, h->n_kv_heads);
+    const int s = shared_splits(ctx, len, G, h->n_kv_heads, ws.chunk);
     add(ctx, len, s);
     if (s < 2) continue;
     ++ws.n_split;
@@ -527,7 +531,7 @@ int64_t build_kv_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, in
 void sort_by_key_range(std::vector<PromptBlock> *blks, int G, int n_kv_heads, const WalkShares &shares) {
   // (a prompt's last block walks the whole prompt, and a launch should not end on a few of those)
   const auto shared = [&](const PromptBlock &b) {
-    return shares.n_split > 0 && shared_splits(b.start - b.kstart, b.len, G, n_kv_heads) > 1;
+    return shares.n_split > 0 && shared_splits(b.start - b.kstart, b.len, G, n_kv_heads, shares.chunk) > 1;
   };
   std::stable_sort(blks->begin(), blks->end(), [&](const PromptBlock &a, const PromptBlock &b) {
     const bool sa = shared(a), sb = shared(b);
@@ -549,7 +553,7 @@ int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n
     meta->kstart[i] = b.kstart;
     meta->pos0[i] = b.pos0;
     meta->tile_start[i] = (int32_t)tiles;
-    tiles += short_row_tiles(b.len, G) * (i < meta->n_split ? shared_splits((int64_t)b.start - b.kstart, b.len, G, n_kv_heads) : 1);
+    tiles += short_row_tiles(b.len, G) * (i < meta->n_split ? shared_splits((int64_t)b.start - b.kstart, b.len, G, n_kv_heads, shares.chunk) : 1);
     if (tiles > 0x3fffffff) return -1;
   }
   meta->tile_start[n] = (int32_t)tiles;
@@ -711,7 +715,7 @@ int64_t ba_schedule_prompts(const ba_heads *heads, int32_t n_prompts, const int3
       const int n_rows = lq * G;
       if (i < meta.n_split) {
         const int n_rt = (n_rows + ba::kShortTileRows - 1) / ba::kShortTileRows;
-        n_splits = ba::shared_walk_splits(ba::walk_tiles(dq + lq), ba::kShareChunk, n_rt * heads->n_kv_heads, ba::kSharePairs);
+        n_splits = ba::shared_splits(dq, lq, G, heads->n_kv_heads, shares.chunk);
         split = jt / n_rt;
         jt -= split * n_rt;
       }

@@ -110,7 +110,7 @@ std::vector<PromptBlock> list_prompt_blocks(int32_t n_prompts, const int32_t *cu
 // Which last blocks have their walks shared by several workgroups (PromptMeta::n_split), and the memory that takes.
 struct WalkShares {
   int n_split = 0;
-  int chunk = 1;      // (dk/dv kernel: row tiles per workgroup)
+  int chunk = 1;      // tiles per workgroup (forward, dq: of blocks with many row tiles; dk/dv: of any)
   int64_t items = 0;  // (row tile, split) pairs of those blocks
   size_t part_bytes = 0, ml_bytes = 0, count_bytes = 0;
   size_t total() const { return align256(part_bytes) + align256(ml_bytes) + align256(count_bytes); }

@@ -227,6 +227,33 @@ def test_shared_walks_of_whole_prompts_cover_the_mask_once(hq, hkv, d):
     assert 1 in seen and max(seen) >= (4 if hq <= 6 else 2)
 
 
+@pytest.mark.parametrize("hq,hkv,d,prompt,parts", [
+    (32, 8, 128, [880, 860, 51], 3), (32, 8, 128, [880, 861, 51], 3), (32, 8, 128, [880, 828, 51], 1),  # 56, 56 and 55 key tiles
+    (8, 1, 64, [1600, 192], 2), (8, 1, 64, [1600, 193], 4),                           # 12 row tiles times KV heads, 13
+    (32, 8, 128, [1500, 1500, 1500, 260], 2), (32, 8, 128, [1500, 1500, 1500, 400], 1),  # 72 and 104: at most 192 workgroups
+    (4, 4, 64, [2000, 2000, 1700], 3), (16, 16, 64, [1500, 1500, 100], 1)])
+def test_walks_of_many_row_tiles_are_shared_from_56_key_tiles_on(hq, hkv, d, prompt, parts):
+    """More than twelve row tiles times KV heads: parts of 24 key tiles (16 at head_dim 64), at most 192 workgroups, at most 8 KV heads; the
+    parts of a row tile partition its walk."""
+    h, G = ba.Heads(hq, hkv, d, 10000.0), hq // hkv
+    offs = np.concatenate([[0], np.cumsum(prompt)])
+    last = int(offs[-2])
+    tiles = {}
+    for w in ba.ba_schedule_prompts(h, [0, len(prompt)], offs):
+        if w.first_token == last:
+            tiles.setdefault(w.row_begin, []).append(w)
+    assert sorted(tiles) == list(range(0, prompt[-1] * G, 128))
+    for ws in tiles.values():
+        ws.sort(key=lambda w: w.split)
+        assert [w.split for w in ws] == list(range(parts)) and {w.n_splits for w in ws} == {parts}
+        at = 0
+        for w in ws:
+            assert w.ctx_begin + w.self_begin == at
+            at = w.ctx_end + w.self_end
+        last_tok = (ws[0].row_end - 1) // G
+        assert at == min(last + prompt[-1], ((last + last_tok) // 32 + 1) * 32)
+
+
 @pytest.mark.parametrize("hq,hkv,d,prompt,below,above", [(32, 8, 128, [200] * 6 + [20], 4, 5), (16, 8, 128, [200] * 20 + [64], 8, 9),
                                                          (4, 4, 64, [200] * 6 + [20], 24, 32)])
 def test_walks_are_shared_only_where_the_call_leaves_the_chip_idle(hq, hkv, d, prompt, below, above):
