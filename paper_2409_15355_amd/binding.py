@@ -1,6 +1,7 @@
 """Thin ctypes face of the HIP library: argument marshalling only.
 
-Function names and argument order follow ``include/ba.h``.  Tensors are torch CUDA
+Function names and argument order follow ``include/ba.h``.  Plain arguments (torch tensors, int32 arrays) are taken
+apart by native code (``csrc/face.cpp``); the functions here do it for everything else, and raise the errors.  Tensors are torch CUDA
 tensors (PyTorch is used for device memory and streams, nothing else); metadata are
 host sequences of ints.  Every step of the hot path runs inside ``libba_hip.so``; if
 the library is missing, loading fails loudly -- there is no fallback.
@@ -15,6 +16,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libba_hip.so")
+FACE_PATH = os.path.join(_HERE, "_face.so")
 
 BA_OK = 0
 DTYPE_BF16, DTYPE_F32 = 0, 1
@@ -61,6 +63,7 @@ class BaError(RuntimeError):
 
 
 _lib = None
+_native = None  # the native half of this face (csrc/face.cpp)
 _I32P = ctypes.c_void_p  # const int32_t*: host arrays travel as bytes (numpy's typed pointers cost microseconds each)
 _TP = ctypes.POINTER(BaTensor)
 _HP = ctypes.POINTER(BaHeads)
@@ -68,14 +71,16 @@ _HP = ctypes.POINTER(BaHeads)
 
 def load():
     """dlopen libba_hip.so (built by ``paper_2409_15355_amd.build``)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     # PyTorch ships its own HIP runtime; the process must use exactly one, and the device
     # memory handed to this library is torch's, so torch's runtime has to be loaded first.
     import torch  # noqa: F401
-    if not os.path.exists(LIB_PATH):
-        raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2409_15355_amd.build`")
+    for path in (LIB_PATH, FACE_PATH):
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: build it with `python -m paper_2409_15355_amd.build`")
+    from . import _face
     lib = ctypes.CDLL(LIB_PATH)
     lib.ba_version.restype = ctypes.c_int32
     lib.ba_status_string.restype = ctypes.c_char_p
@@ -143,8 +148,27 @@ def load():
                                                ctypes.c_size_t, ctypes.c_void_p]
     lib.ba_measure_xcd_speed_workspace_bytes.restype = ctypes.c_size_t
     lib.ba_measure_xcd_speed_workspace_bytes.argtypes = []
+    _face.setup(Heads, getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None),
+                tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in
+                      ("ba_encode_blocks", "ba_reencode_positions", "ba_final_block_attention", "ba_final_block_attention_static",
+                       "ba_final_block_attention_cached", "ba_block_attention_prompts", "ba_block_attention_prompts_backward")))
+    _native = _face
     _lib = lib
     return lib
+
+
+def _face():
+    if _native is None:
+        load()
+    return _native
+
+
+def _done(status: Optional[int]) -> bool:
+    """Whether the native half has made the call.  If not (None), some argument is not the plain case -- a list, a view of
+    another type, a shape that does not fit -- and the checks below convert it or say what is wrong."""
+    if status:
+        _check(status)
+    return status is not None
 
 
 def _check(status: int) -> None:
@@ -312,6 +336,8 @@ def ba_encode_blocks_workspace_bytes(heads: Heads, block_offsets, rope_mode: int
 
 def ba_encode_blocks(heads: Heads, q, k, v, o_out, k_local_out, block_offsets, rope_mode: int = ROPE_APPLY,
                      ws=None, stream=None) -> None:
+    if _done(_face().encode_blocks(heads, q, k, v, o_out, k_local_out, block_offsets, rope_mode, ws, stream)):
+        return
     offs = _ints(block_offsets)
     wp, wb = _ws(ws)
     T, hq, hkv, d = _last(offs), heads.n_q_heads, heads.n_kv_heads, heads.head_dim
@@ -324,6 +350,8 @@ def ba_encode_blocks(heads: Heads, q, k, v, o_out, k_local_out, block_offsets, r
 def ba_reencode_positions(heads: Heads, k_src, k_dst, src_tok_off, dst_tok_off, lens, old_pos0=None,
                           new_pos0=None, mode: int = REENC_SHIFT, stream=None) -> None:
     """k_src / k_dst: [layers, tokens, heads, D] (or [tokens, heads, D] for one layer)."""
+    if _done(_face().reencode_positions(heads, k_src, k_dst, src_tok_off, dst_tok_off, lens, old_pos0, new_pos0, mode, stream)):
+        return
     if k_src.dim() == 3:
         k_src, k_dst = k_src[None], k_dst[None]
     if k_src.dim() != 4 or k_dst.dim() != 4 or k_src.shape[0] != k_dst.shape[0]:
@@ -361,6 +389,8 @@ def ba_final_block_attention_workspace_bytes(heads: Heads, cu_q, cu_ctx, rope_mo
 
 def ba_final_block_attention(heads: Heads, q_f, k_ctx, v_ctx, k_f, v_f, o_out, k_f_rot_out, cu_q, cu_ctx,
                              q_pos0=None, rope_mode: int = ROPE_APPLY, ws=None, stream=None) -> None:
+    if _done(_face().final_block(heads, q_f, k_ctx, v_ctx, k_f, v_f, o_out, k_f_rot_out, cu_q, cu_ctx, q_pos0, rope_mode, ws, stream)):
+        return
     cq, cc, qp = _ints(cu_q), _ints(cu_ctx), _ints(q_pos0)
     wp, wb = _ws(ws)
     tq, tkc, tvc, tkf, tvf, to, tkr = _final_tensors(heads, q_f, k_ctx, v_ctx, k_f, v_f, o_out, k_f_rot_out, cq, cc, qp)
@@ -375,6 +405,9 @@ STATIC_SCRATCH_BYTES = 32 << 20
 def ba_final_block_attention_static(heads: Heads, q_f, k_ctx, v_ctx, k_f, v_f, o_out, k_f_rot_out, cu_q, cu_ctx,
                                     q_pos0=None, rope_mode: int = ROPE_APPLY, stream=None) -> None:
     """ba_final_block_attention with the workspace in the library's static device array (no allocation)."""
+    if _done(_face().final_block_static(heads, q_f, k_ctx, v_ctx, k_f, v_f, o_out, k_f_rot_out, cu_q, cu_ctx, q_pos0, rope_mode,
+                                        stream)):
+        return
     cq, cc, qp = _ints(cu_q), _ints(cu_ctx), _ints(q_pos0)
     tq, tkc, tvc, tkf, tvf, to, tkr = _final_tensors(heads, q_f, k_ctx, v_ctx, k_f, v_f, o_out, k_f_rot_out, cq, cc, qp)
     _check(load().ba_final_block_attention_static(ctypes.byref(heads.c), _ref(tq), _ref(tkc), _ref(tvc), _ref(tkf),
@@ -399,6 +432,9 @@ def ba_final_block_attention_cached(heads: Heads, q_f, k_cache, v_cache, k_f, v_
                                     ws=None, stream=None, gather_below: int = GATHER_DEFAULT) -> None:
     """gather_below: mean cached-block length (tokens) below which the context is gathered first
     (GATHER_DEFAULT: 256; 0: never); pass the same value to the workspace query."""
+    if _done(_face().final_block_cached(heads, q_f, k_cache, v_cache, k_f, v_f, o_out, k_f_rot_out, cu_q, cu_blk, blk_tok_off, blk_len,
+                                        blk_old_pos0, blk_new_pos0, q_pos0, ws, stream, gather_below)):
+        return
     cq, cb = _ints(cu_q), _ints(cu_blk)
     bo, bl, op, npos, qp = _ints(blk_tok_off), _ints(blk_len), _ints(blk_old_pos0), _ints(blk_new_pos0), _ints(q_pos0)
     wp, wb = _ws(ws)
@@ -426,6 +462,8 @@ def ba_block_attention_prompts_workspace_bytes(heads: Heads, cu_blk, block_offse
 def ba_block_attention_prompts(heads: Heads, q, k, v, o_out, k_rot_out, lse_out, cu_blk, block_offsets,
                                rope_mode: int = ROPE_APPLY, ws=None, stream=None) -> None:
     """lse_out: float32 tensor [T, n_q_heads] (contiguous) or None."""
+    if _done(_face().prompts(heads, q, k, v, o_out, k_rot_out, lse_out, cu_blk, block_offsets, rope_mode, ws, stream)):
+        return
     cb, offs = _ints(cu_blk), _ints(block_offsets)
     wp, wb = _ws(ws)
     if _last(cb) != len(offs) - 1:
@@ -448,6 +486,8 @@ def ba_block_attention_prompts_backward_workspace_bytes(heads: Heads, cu_blk, bl
 def ba_block_attention_prompts_backward(heads: Heads, q, k, v, o, lse, d_out, dq_out, dk_out, dv_out, cu_blk,
                                         block_offsets, ws=None, stream=None) -> None:
     """lse: the forward call's float32 [T, n_q_heads] tensor."""
+    if _done(_face().prompts_backward(heads, q, k, v, o, lse, d_out, dq_out, dk_out, dv_out, cu_blk, block_offsets, ws, stream)):
+        return
     cb, offs = _ints(cu_blk), _ints(block_offsets)
     wp, wb = _ws(ws)
     if _last(cb) != len(offs) - 1:

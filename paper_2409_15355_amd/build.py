@@ -1,5 +1,5 @@
 """Build the HIP library in-tree: hipcc for gfx950, one object per source, one shared
-object ``libba_hip.so`` next to this file."""
+object ``libba_hip.so`` next to this file; and ``_face.so``, the native half of the Python face."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libba_hip.so")
+FACE = os.path.join(HERE, "_face.so")
 SOURCES = ["ba_api.hip", "ba_api_prompts.hip", "ba_api_cached.hip", "ba_probe.hip", "ba_plan.cpp", "reencode.hip", "rope_prepass.hip", "gather.hip", "attention.hip", "attention_short.hip", "attention_bwd.hip", "head_pad.hip", "diag.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -31,6 +32,23 @@ def _filter(stderr: str) -> str:
     return "\n".join(l for l in stderr.splitlines() if "packed-fp32-ops" not in l)
 
 
+def build_face() -> None:
+    """csrc/face.cpp -> _face.so, a Python extension with torch's and NumPy's headers, by the host compiler."""
+    import sysconfig
+
+    import numpy
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", numpy.get_include(), "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "face.cpp"), "-o", FACE, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"the Python face's native half failed to build:\n{r.stderr}")
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
     objs = []
@@ -50,8 +68,10 @@ def build(verbose: bool = False) -> str:
             print(_filter(r.stderr), file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        face = ex.submit(build_face)
         objs = list(ex.map(compile_one, SOURCES))
+        face.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -2480,3 +2480,56 @@ def test_a_call_larger_than_the_cache_gives_the_bits_of_its_parts(ba, hq, hkv, d
         part = everything(rows, offs1, np.array([0, len(block)], dtype=np.int32))
         for name, a, b in zip(("encode", "prompts", "lse", "dq", "dk", "dv"), whole, part):
             assert torch.equal(a[rows], b), (name, n)
+
+
+def test_plain_and_converted_arguments_make_the_same_call(ba, monkeypatch):
+    """Every call with int32 arrays (taken apart natively) and with lists and a tensor subclass (by the Python face): the
+    same bits, strided views and one-layer tensors among them, on a given stream; what neither takes is refused."""
+    torch = torch_mod()
+
+    class Sub(torch.Tensor):
+        pass
+
+    taken = []
+    done = ba._done
+    monkeypatch.setattr(ba, "_done", lambda status: taken.append(status) or done(status))
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    heads = ba.Heads(8, 2, 64, 10000.0)
+    wide = torch.randn((210, 16, 64), generator=gen, device="cuda").to(torch.bfloat16)
+    q, k, v, do, o1 = wide[:, :8], wide[:, 8:10], wide[:, 10:12], wide[3:193, 4:12], wide[:, 2:10]
+    i32 = lambda *x: np.array(x, dtype=np.int32)
+    offs, cu_blk, cu_q, cu_ctx = i32(0, 100, 170, 190), i32(0, 3), i32(0, 20), i32(0, 170)
+    start, lens = i32(0, 100), i32(100, 70)
+    ws = torch.zeros(8 << 20, dtype=torch.uint8, device="cuda")
+    lse = torch.randn((190, 8), generator=gen, device="cuda") + 8
+
+    def calls(conv, sub, stream):
+        new = lambda t: torch.zeros(t.shape, dtype=t.dtype, device="cuda")
+        x = [new(q), new(k), new(q), new(k), new(q), new(q), new(q), new(q), new(lse), new(q), new(k), new(k)]
+        c = [conv(a) for a in (offs, cu_blk, cu_q, cu_ctx, start, lens)]
+        qs = q.as_subclass(Sub) if sub else q
+        kc = k if not sub else k.as_subclass(Sub)
+        ba.ba_encode_blocks(heads, qs, k, v, x[0], x[1], c[0], ba.ROPE_APPLY, ws, stream)
+        ba.ba_reencode_positions(heads, kc, x[3], c[4], c[4], c[5], None, c[4], ba.REENC_SHIFT, stream)
+        ba.ba_final_block_attention(heads, qs[170:], k, v, k[170:], v[170:], x[4], None, c[2], c[3], None, ba.ROPE_APPLY, ws, stream)
+        ba.ba_final_block_attention_static(heads, qs[170:], k, v, k[170:], v[170:], x[5], None, c[2], c[3], c[2][1:], ba.ROPE_APPLY, stream)
+        ba.ba_final_block_attention_cached(heads, qs[170:], k, v, k[170:], v[170:], x[6], None, c[2], conv(i32(0, 2)), c[4], c[5], None,
+                                           None, None, ws, stream)
+        ba.ba_block_attention_prompts(heads, qs, k, v, x[7], None, x[8], c[1], c[0], ba.ROPE_APPLY, ws, stream)
+        ba.ba_block_attention_prompts_backward(heads, qs[:190], k, v, o1, lse, do, x[9], x[10], x[11], c[1], c[0], ws, stream)
+        torch.cuda.synchronize()
+        return x
+
+    native = calls(lambda a: a, False, None)
+    assert taken == [0] * 7
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for conv, sub, stream in ((list, True, None), (lambda a: a, False, side), (lambda a: a.astype(np.int64), False, side)):
+        taken.clear()
+        for a, b in zip(native, calls(conv, sub, stream)):
+            assert torch.equal(a, b)
+        assert taken == ([0] * 7 if conv(offs) is offs else [None] * 7)
+    with pytest.raises(ValueError, match="tokens"):
+        ba.ba_encode_blocks(heads, q[:189], k, v, torch.empty_like(q), None, offs, ba.ROPE_APPLY, ws)
+    with pytest.raises(ba.BaError):  # (refused by the library itself: the status comes back through the native half)
+        ba.ba_encode_blocks(heads, q, k, v, torch.empty_like(q), None, offs, 7, ws)
