@@ -9,7 +9,7 @@
 //   - bwd_dq_kernel: a workgroup owns 128 packed query rows (as the forward kernel for short items
 //     does) and walks the key tiles its rows see; it accumulates dq^.  It rotates its query rows itself and
 //     leaves them in memory for the other kernel, with -L / ln 2 and -delta of every row.
-//   - bwd_dkv_kernel: a workgroup owns 64 keys of one block and KV head and walks the 32-row
+//   - bwd_dkv_kernel: a workgroup owns 64 keys (16 a wave) of one block and KV head and walks the 32-row
 //     query tiles that see them (the rest of its own block, and the prompt's last block if it is a
 //     passage); it accumulates dk^ and dV over all query heads of the group.
 // Each turns its gradient of the rotated tensor back to the un-rotated frame in its epilogue, with the
@@ -17,7 +17,7 @@
 // minus the angle).
 //
 // Operand layouts are the forward kernel's: products are computed transposed with
-// v_mfma_f32_32x32x16_bf16, the owner's side along lanes and in registers as B operands, the
+// v_mfma_f32_32x32x16_bf16 (dk/dv: 16x16x32), the owner's side along lanes and in registers as B operands, the
 // walked side from LDS tiles as A operands (16-byte row reads for the products that contract over
 // head_dim, LDS transpose reads for those that contract over the walked index), and a probability
 // tile in accumulator layout is directly the B operand of the next product.
@@ -541,37 +541,159 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
 }
 
 // ---------------------------------------------------------------------------------------------------
-// dk and dV.  The accumulators of 32 keys (dK^ and dV: 128 registers) and their rows (K^ and V: 64) leave
-// one wave no registers to look ahead with and a SIMD no room for more than two such waves, so a pair of
-// waves shares 32 keys, each with half of everything:
-//   wave A: S = q^ K^^T, P = 2^S -> LDS, dV^T += dO^T P        wave B: dP = dO V^T, dS = P o dP, dK^^T += q^^T dS
-// P passes between them in 32 bits, lane for lane (both hold the pair's tile in one layout); the two have
-// eight products before and eight behind the exchange, and fit three waves to a SIMD.
+// dk and dV.  A wave owns 16 keys with both sums (dK^ and dV: 64 registers) and both operands (K^ and V: 32), which with
+// 16x16x32 products leaves three waves a SIMD room for windows of fragments; per tile of 32 packed rows it forms
+//   S = q^ K^^T - L,  dP = dO V^T - delta,  P = 2^S,  dS = P o dP,  dV^T += dO^T P,  dK^^T += q^^T dS
+// from its own registers and the tile, with one barrier.  (Waves of 32 keys have no registers left to look ahead with, two to a SIMD:
+// 370 us.  Split between a pair of waves, S and dV here, dP and dK^ there, with P handed over through LDS behind a
+// second barrier: 325.)  Each fragment of a tile feeds half as many products as with 32 keys, so LDS is read twice as much, 44 %
+// of the time: the price of doing without the exchange.
 // Eight prompts of 20 passages of 100 to 300 tokens and a query block (33,746 tokens, 32 query heads over 8 of
-// 128, 208 GFLOP in four products): 470 us as one wave per 32 keys with the mask tests among the exponentials,
-// 370 with straight code per tile, 315 to 340 as it is; 990 MB read (q^ and dO once are 553), 138 written.  What is
-// left is waiting: waves wait 38 % of their time for memory and at barriers and 33 % to issue, with the matrix pipes 36 % and
-// LDS 33 % busy.  Without the tile copies 287, without the exponentials 331; with B's products moved off the exchange no
-// change; a third buffer does not fit three workgroups, and asking for lines two tiles ahead cost 14.
+// 128, 208 GFLOP in four products): 320 -> 285 us, forward and backward 940 -> 903; 32 over 8 of 64 524 -> 486; two
+// prompts there 282 -> 270.  990 MB read (q^ and dO once are 553), 138 written.  What is left is waiting, 38 % of the waves' time for
+// memory and at barriers and 27 % to issue; a third tile buffer, which now fits three workgroups, changes nothing.
 template <int D>
 struct KvGeo {
-  using G = BGeo<D>;
-  static constexpr uint32_t TB = G::TILEB;
-  static constexpr uint32_t BUFB = 2 * TB + kBWaves * 128;  // a q^ tile, a dO tile, per wave its rows' -L or -delta
-  static constexpr int IPW = kBKeys / G::RPI / 2;           // LDS-direct loads of one wave per tile (one tensor's half)
-  static constexpr uint32_t PEXB = 4096;                    // a pair's P: 32 x 32 floats
-  static constexpr size_t LDS = 2 * (size_t)BUFB + kBWaves / 2 * PEXB;
-  static_assert(kKvRows == kBKeys && kBwdTileKeys == kBWaves / 2 * 32, "a tile of 32 packed query rows, a pair of waves per 32 keys");
+  static constexpr int KK = D / 32;                   // k-steps of the products over head_dim
+  static constexpr int DT = D / 16;                   // 16-row slabs of dV^T and dK^^T
+  static constexpr int CPR = D / 8;                   // 16-byte chunks per row
+  static constexpr uint32_t ROWB = D * 2;
+  static constexpr uint32_t TB = kKvRows * ROWB;      // a tile of q^ or dO
+  static constexpr uint32_t BUFB = 2 * TB + kKvRows * 8;  // ... of both, and their rows' -L and -delta
+  static constexpr int RPI = 1024 / ROWB;             // rows filled by one LDS-direct wave instruction
+  static constexpr int IPW = kKvRows / RPI / 2;       // such instructions of one wave per tile (one tensor's half)
+  static constexpr int KEYS = kBwdTileKeys / kBWaves; // a wave's keys
+  static constexpr size_t LDS = 2 * (size_t)BUFB;
+  static_assert(KEYS == 16 && kKvRows == 32 && BUFB % 256 == 0, "16x16x32 products, two row halves a tile, transpose reads");
 };
 
+typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
+typedef __attribute__((address_space(3))) u32x2_t lds_u32x2;
+typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8;
+
+// Where row `row` of a tile keeps its 16-byte chunk `chunk`: XORed with a number that depends on the row's place among
+// sixteen (a row of LDS banks holds one row at D = 128, two at 64), so that both kinds of reads spread over all banks.  A row
+// read (lane = row, four neighbouring chunks to the lane groups) goes through the banks in four rounds, the first of
+// lanes 0-3, 12-15, 20-23 and 24-27: rows 0-3 and 12-15 of one chunk, 4-11 of the next, so either set's numbers come in
+// pairs that differ in the lowest bit.  A transpose read takes two neighbouring chunks of eight rows a round, whose numbers
+// differ above the lowest bit.  (Numbers that only differ over sixteen rows: a third of the LDS cycles were conflicts.)
+template <int D>
+__device__ __forceinline__ uint32_t kv_xor(int row) {
+  const uint32_t s = (uint32_t)(D == 128 ? row : row >> 1);
+  constexpr int kLow = D == 128 ? 2 : 1;  // bits that tell neighbours apart
+  const uint32_t lo = s & ((1u << kLow) - 1), a = (s >> kLow) & 1u, b = (s >> (kLow + 1)) & 1u;
+  return lo << 1 | (a ^ b) << (kLow + 1) | b;
+}
+template <int D>
+__device__ __forceinline__ uint32_t kv_ofs(int row, int chunk) {
+  return (uint32_t)row * KvGeo<D>::ROWB + (((uint32_t)chunk ^ kv_xor<D>(row)) << 4);
+}
+
+// 16x16x32 products.  Row read, step st of the four products over head_dim that go side by side (of tensor st >> 1 & 1, TB
+// apart, rows 16 (st & 1) + lane % 16, k-step st / 4): at[k-step] + kv_row_ofs(st).
+template <int D>
+__device__ __forceinline__ void kv_row_bases(uint32_t (&at)[D / 32], int col, int g) {
+#pragma unroll
+  for (int kk = 0; kk < D / 32; ++kk) at[kk] = kv_ofs<D>(col, kk * 4 + g);
+}
+template <int D>
+__device__ __forceinline__ constexpr uint32_t kv_row_ofs(int st) {
+  return (uint32_t)((st >> 1) & 1) * KvGeo<D>::TB + (uint32_t)(st & 1) * 16u * KvGeo<D>::ROWB;
+}
+// Transpose read of slab dt (16 head dims) of a tile: kv_tr_frag(tile + (kv_tr_base ^ 32 dt)), for tiles 256-byte aligned in
+// LDS.  Its k-slots are rows 4 g + 0..3 and 16 + 4 g + 0..3: the order in which two accumulators of 16 rows hold theirs.
+template <int D>
+__device__ __forceinline__ uint32_t kv_tr_base(int lane) {
+  return kv_ofs<D>(4 * (lane >> 4) + ((lane & 15) >> 2), (lane >> 1) & 1) + (lane & 1) * 8;
+}
+template <int D>
+__device__ __forceinline__ bf16x8_t kv_tr_frag(lds_char *at) {
+  typedef __attribute__((address_space(3))) s16x4_t lds_s16x4;
+  typedef short s16x8_t __attribute__((ext_vector_type(8)));
+  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at);
+  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at + 16 * KvGeo<D>::ROWB));
+  const s16x8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8_t, both);
+}
+// two accumulators of 16 rows each -> the B operand of the next product (see kv_tr_frag)
+__device__ __forceinline__ bf16x8_t pack_rows(const f32x4_t &lo, const f32x4_t &hi) {
+  const u32x4_t w = {pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]), pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
+  return __builtin_bit_cast(bf16x8_t, w);
+}
+
+// rotate_back for sums in this kernel's layout (lane = key `col`, register v of slab dt = head dim 16 dt + 4 g + v).
+template <int D>
+__device__ __forceinline__ void rotate_back_keys(f32x4_t (&acc)[D / 16], const f32x4_t *tab, int g, bool halves, float mul) {
+  constexpr int DT = D / 16;
+  if (!halves) {
+    // pairs (d, d + 1): slab dt holds pairs 8 dt + 2 g and the next
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const f32x4_t t = tab[dt * 4 + g];
+#pragma unroll
+      for (int h2 = 0; h2 < 2; ++h2) {
+        const float c = t[2 * h2] * mul, sn = t[2 * h2 + 1] * mul;
+        const float x = acc[dt][2 * h2], y = acc[dt][2 * h2 + 1];
+        acc[dt][2 * h2] = c * x + sn * y;
+        acc[dt][2 * h2 + 1] = c * y - sn * x;
+      }
+    }
+  } else {
+    // pairs (d, d + D/2): slab dt pairs with slab dt + DT/2, pairs 16 dt + 4 g + (0..3)
+#pragma unroll
+    for (int dt = 0; dt < DT / 2; ++dt)
+#pragma unroll
+      for (int h2 = 0; h2 < 2; ++h2) {
+        const f32x4_t t = tab[dt * 8 + g * 2 + h2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const float c = t[2 * e] * mul, sn = t[2 * e + 1] * mul;
+          const float x = acc[dt][2 * h2 + e], y = acc[dt + DT / 2][2 * h2 + e];
+          acc[dt][2 * h2 + e] = c * x + sn * y;
+          acc[dt + DT / 2][2 * h2 + e] = c * y - sn * x;
+        }
+      }
+  }
+}
+// A sum's 16 rows into LDS, as kv_ofs has them, to leave as whole rows.
+template <int D>
+__device__ __forceinline__ void stage_rows(lds_char *stage, const f32x4_t (&acc)[D / 16], int col, int g) {
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt) {
+    const u32x2_t w = {pack_bf16(acc[dt][0], acc[dt][1]), pack_bf16(acc[dt][2], acc[dt][3])};
+    *(lds_u32x2 *)(stage + kv_ofs<D>(col, dt * 2 + (g >> 1)) + (g & 1) * 8) = w;
+  }
+}
+// Partial sums of a shared walk: N registers of 16 bytes a lane, a kilobyte of consecutive memory each, past the L2 caches.
+template <int N>
+__device__ __forceinline__ void leave_sums(char *at, int lane, int first, const f32x4_t (&acc)[N]) {
+  const auto to = shared_buffer(at, (first + N) * 1024);
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[k]), to, lane * 16 + (first + k) * 1024, 0, kAgentScope);
+}
+template <int N>
+__device__ __forceinline__ void add_sums(char *at, int lane, f32x4_t (&a)[N], f32x4_t (&b)[N]) {
+  const auto from = shared_buffer(at, 2 * N * 1024);
+  f32x4_t w[2 * N];
+#pragma unroll
+  for (int k = 0; k < 2 * N; ++k)
+    w[k] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(from, lane * 16 + k * 1024, 0, kAgentScope));
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    a[k] += w[k];
+    b[k] += w[N + k];
+  }
+}
+
 template <int D, bool kShared>
-__global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, BwdKvMeta meta, BwdParams bp) {
-  using G = BGeo<D>;
+__global__ __launch_bounds__(kBThreads, D == 128 ? 3 : 5) void bwd_dkv_kernel(AttnParams p, BwdKvMeta meta, BwdParams bp) {
   using KG = KvGeo<D>;
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char *smem = (lds_char *)smem_generic;
-  // LDS map: two buffers of BUFB, then the pairs' exchange
-  constexpr uint32_t TB = KG::TB, BUFB = KG::BUFB;
+  // LDS map: two buffers of BUFB: the tile of q^, of dO, -L and -delta of their rows (four of the one, four of the other in turn)
+  constexpr uint32_t TB = KG::TB, BUFB = KG::BUFB, ROWB = KG::ROWB;
   constexpr int IPW = KG::IPW;
 
   uint32_t id = blockIdx.x;
@@ -598,11 +720,9 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int pair = wave >> 1;
-  const bool is_b = wave & 1;
-  const int col = lane & 31, hf = lane >> 5;
+  const int col = lane & 15, g = lane >> 4;
   const int Gq = p.group;
-  const int kw0 = k0 + pair * 32;  // this pair's first key
+  const int kw0 = k0 + wave * KG::KEYS;  // this wave's first key
   const bool wave_has_keys = kw0 < lk;
   const int my_key = kw0 + col;    // (may lie beyond the block: such columns are never stored)
 
@@ -624,50 +744,34 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   const int own_last = ((n_rows_a - 1) / kKvRows) * kKvRows;  // first row of the block's last tile
   const int fin_last = (n_f - 1) * kKvRows;
 
-  // ---- this wave's operand: the pair's K^ rows (A) or V rows (B), whole, then fragments through LDS ----
-  u32x4_t ld_kv[G::KCH];
-  {
-    const int64_t st = is_b ? p.vf_st : p.kf_st, sh = is_b ? p.vf_sh : p.kf_sh;
-    const char *base = (const char *)((is_b ? p.vf : p.kf) + (int64_t)k_tok0 * st + (int64_t)kvh * sh);
-#pragma unroll
-    for (int u = 0; u < G::KCH; ++u) {
-      const uint32_t tok = (uint32_t)min(kw0 + u * G::QRPI + lane / G::CPR, lk - 1);
-      ld_kv[u] = *reinterpret_cast<const u32x4_t *>(base + ((uint64_t)tok * (uint64_t)st + (uint32_t)(lane % G::CPR) * 8u) * 2u);
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);
-
-  uint32_t r_rd[G::DT], t_rd[G::DT];
-  row_read_bases<D>(r_rd, col, hf);
-  tr_read_bases<D>(t_rd, lane);
-
-  // ---- tile fill: kKvRows packed query rows of q^ (the A waves) and of dO (the B waves), and per wave the
-  //      rows' -L / ln 2 or -delta.  Where the group divides 32, every tile begins with a token's first
+  // ---- tile fill: kKvRows packed query rows of q^ (the even waves) and of dO (the odd ones), and the
+  //      rows' -L / ln 2 and -delta.  Where the group divides 32, every tile begins with a token's first
   //      head and its rows lie at the same distances from there: the lanes' offsets are worked out once and
-  //      a tile moves one pointer (the copy goes out between two barriers, ahead of the products; with the
+  //      a tile moves one pointer (the copy goes out between the barrier and the products; with the
   //      rows divided out per instruction a wave spent 180 scalar instructions on a tile).  Otherwise, and
   //      in the last tile of a block (rows beyond the block repeat its last row), every lane finds its own ----
-  const uint32_t c_st = is_b ? (uint32_t)bp.do_st : (uint32_t)(p.n_q_heads * D), c_sh = is_b ? (uint32_t)bp.do_sh : (uint32_t)D;
-  const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + (is_b ? TB : 0u) + pair * IPW * G::GRPB;
-  const uint32_t lds_ld = (uint32_t)(uintptr_t)smem + 2 * TB + wave * 128;
-  const int c_row = pair * IPW * G::RPI + lane / G::CPR;  // this lane's row of the wave's first instruction
-  const uint32_t c_chunk = (uint32_t)((lane % G::CPR) ^ (granule_xor<D>(lane / G::CPR) << 2) ^ low_xor<D>(lane / G::CPR)) << 4;
-  auto row_ofs = [&](uint32_t r) __attribute__((always_inline)) {  // packed row r, in bytes from its block's first
-    const uint32_t tok = fast_div(r, p.group_div), g = r - tok * (uint32_t)Gq;
-    return (tok * c_st + g * c_sh) * 2u + c_chunk;
+  const bool of_do = wave & 1;
+  const int half = wave >> 1;
+  const uint32_t c_st = of_do ? (uint32_t)bp.do_st : (uint32_t)(p.n_q_heads * D), c_sh = of_do ? (uint32_t)bp.do_sh : (uint32_t)D;
+  const uint32_t lds_copy = (uint32_t)(uintptr_t)smem + (of_do ? TB : 0u) + half * IPW * 1024;
+  const uint32_t lds_ld = (uint32_t)(uintptr_t)smem + 2 * TB + wave * 64;
+  auto c_row = [&](int u) __attribute__((always_inline)) { return (half * IPW + u) * KG::RPI + lane / KG::CPR; };  // this lane's row of instruction u
+  auto row_ofs = [&](uint32_t r, int u) __attribute__((always_inline)) {  // packed row r, in bytes from its block's first; this lane's chunk
+    const uint32_t tok = fast_div(r, p.group_div), gh = r - tok * (uint32_t)Gq;
+    return (tok * c_st + gh * c_sh) * 2u + (((uint32_t)(lane % KG::CPR) ^ kv_xor<D>(c_row(u))) << 4);
   };
   const bool regular = kKvRows % Gq == 0;
   const uint32_t c_step = regular ? (uint32_t)(kKvRows / Gq) * c_st * 2u : 0u;  // bytes from tile to tile
   uint32_t c_in[IPW];
 #pragma unroll
-  for (int u = 0; u < IPW; ++u) c_in[u] = row_ofs((uint32_t)(c_row + u * G::RPI));
+  for (int u = 0; u < IPW; ++u) c_in[u] = row_ofs((uint32_t)c_row(u), u);
   const char *c_base = nullptr, *l_base = nullptr;  // the next tile's rows (their block's first, if not regular); its -L, -delta
   int c_row0 = 0, c_rows = 0;                       // its first packed row inside its block; the block's rows
   auto enter_block = [&](int tok0, int row0, int rows) __attribute__((always_inline)) {
     c_row0 = row0;
     c_rows = rows;
-    c_base = is_b ? (const char *)(bp.dout + (int64_t)tok0 * bp.do_st + (int64_t)(kvh * Gq) * bp.do_sh)
-                  : (const char *)(bp.q_rot + ((int64_t)tok0 * p.n_q_heads + kvh * Gq) * D);
+    c_base = of_do ? (const char *)(bp.dout + (int64_t)tok0 * bp.do_st + (int64_t)(kvh * Gq) * bp.do_sh)
+                   : (const char *)(bp.q_rot + ((int64_t)tok0 * p.n_q_heads + kvh * Gq) * D);
     c_base += (uint64_t)(uint32_t)(row0 / kKvRows) * c_step;
     l_base = (const char *)(bp.ld + 2 * (((int64_t)kvh * bp.T + tok0) * bp.ld_group)) + (uint32_t)row0 * 8u;
   };
@@ -678,164 +782,126 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
     const uint32_t lds_tile = lds_copy + (uint32_t)buf * BUFB;
     if (regular && c_row0 + kKvRows <= c_rows) {
 #pragma unroll
-      for (int u = 0; u < IPW; ++u) lds_dma16(c_base, c_in[u], lds_tile + u * G::GRPB);
+      for (int u = 0; u < IPW; ++u) lds_dma16(c_base, c_in[u], lds_tile + u * 1024);
     } else {
       const uint32_t from = regular ? (uint32_t)c_row0 : 0u;  // the row that c_base is at
 #pragma unroll
       for (int u = 0; u < IPW; ++u)
-        lds_dma16(c_base, row_ofs((uint32_t)min(c_row0 + c_row + u * G::RPI, c_rows - 1) - from), lds_tile + u * G::GRPB);
+        lds_dma16(c_base, row_ofs((uint32_t)min(c_row0 + c_row(u), c_rows - 1) - from, u), lds_tile + u * 1024);
     }
     // four rows of -L and four of -delta in turn, 16 bytes each (the block's last four perhaps partly
-    // unwritten; beyond them the last are read again): eight lanes fetch this wave's kind
-    if (lane < 8)
-      lds_dma16(l_base, (uint32_t)(min(lane, (c_rows - 1 - c_row0) >> 2) * 2 + (is_b ? 1 : 0)) * 16u, lds_ld + (uint32_t)buf * BUFB);
+    // unwritten; beyond them the last are read again)
+    if (lane < 4)
+      lds_dma16(l_base, (uint32_t)(min(wave * 2 + (lane >> 1), (c_rows - 1 - c_row0) >> 2) * 2 + (lane & 1)) * 16u, lds_ld + (uint32_t)buf * BUFB);
     c_row0 -= kKvRows;
     c_base -= c_step;
     l_base -= kKvRows * 8;
   };
-  if (t0 < n_t) issue_copy(t0, t0 & 1);
+  if (t0 < n_t) issue_copy(t0, 0);
+
+  // ---- this wave's operands: fragments of its K^ and V rows (B operands: column = key, k-step kk holds chunk 4 kk + g) ----
+  bf16x8_t kf[KG::KK], vf[KG::KK];
+  {
+    const uint64_t tok = (uint64_t)(uint32_t)min(my_key, lk - 1);
+    const char *kp = (const char *)(p.kf + (int64_t)k_tok0 * p.kf_st + (int64_t)kvh * p.kf_sh) + tok * (uint64_t)p.kf_st * 2u + g * 16;
+    const char *vp = (const char *)(p.vf + (int64_t)k_tok0 * p.vf_st + (int64_t)kvh * p.vf_sh) + tok * (uint64_t)p.vf_st * 2u + g * 16;
+#pragma unroll
+    for (int kk = 0; kk < KG::KK; ++kk) kf[kk] = *reinterpret_cast<const bf16x8_t *>(kp + kk * 64);
+#pragma unroll
+    for (int kk = 0; kk < KG::KK; ++kk) vf[kk] = *reinterpret_cast<const bf16x8_t *>(vp + kk * 64);
+  }
   __builtin_amdgcn_sched_barrier(0);
   dma_wait<0>();
+#pragma unroll
+  for (int kk = 0; kk < KG::KK; ++kk) asm volatile("" : "+v"(kf[kk]), "+v"(vf[kk]));  // (waited for here, not inside the loop)
 
-  // ---- rows -> B-operand fragments through this wave's slice of the buffer that the first tile does not go to
-  //      (the second is asked for behind the first barrier) ----------------------------------------------
-  static_assert(kBWaves * G::SLICEB <= 2 * TB, "the slices fit the tiles of one buffer");
-  bf16x8_t kv[G::KCH];
-  {
-    const uint32_t s_ofs = (uint32_t)(~t0 & 1) * BUFB + wave * G::SLICEB;
-    u32x4_t got[2][G::KCH];
+  f32x4_t dv[KG::DT], dk[KG::DT];
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-      for (int u = 0; u < G::KCH / 2; ++u)
-        *reinterpret_cast<__attribute__((address_space(3))) u32x4_t *>(
-            smem + s_ofs + tile_ofs<D>(u * G::QRPI + lane / G::CPR, lane % G::CPR)) = ld_kv[pass * (G::KCH / 2) + u];
-#pragma unroll
-      for (int kk = 0; kk < G::KCH; ++kk)
-        got[pass][kk] = *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t *>(
-            smem + s_ofs + tile_ofs<D>(col & 15, kk * 2 + hf));
-    }
-#pragma unroll
-    for (int kk = 0; kk < G::KCH; ++kk) {
-      u32x4_t w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (col >> 4) ? got[1][kk][e] : got[0][kk][e];
-      asm volatile("" : "+v"(w));
-      kv[kk] = __builtin_bit_cast(bf16x8_t, w);
-    }
-  }
+  for (int dt = 0; dt < KG::DT; ++dt) dv[dt] = dk[dt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
-  f32x16_t acc[G::DT];  // A: dV^T, B: dK^^T
-#pragma unroll
-  for (int dt = 0; dt < G::DT; ++dt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
+  uint32_t r_rd[KG::KK];
+  kv_row_bases<D>(r_rd, col, g);
+  const uint32_t t_rd = kv_tr_base<D>(lane);
 
-  // ---- the walk over the query row tiles: tile i lives in buffer i % 2.  Its first barrier says that
-  //      every wave's share of tile i has landed and that all are done with tile i - 1 and its P, so the
-  //      copy of tile i + 1 may overwrite that buffer; its second that the A waves' P lies in LDS ----------
-  typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
-  lds_char *const pex = smem + 2 * BUFB + pair * KG::PEXB + lane * 16;
-  const uint32_t ofs1 = is_b ? TB : 0u, ofs2 = is_b ? 0u : TB;  // the tile of the products before the exchange, behind it
-  // Left to itself the compiler asks for two fragments, waits, multiplies and asks for the next two: four LDS latencies
-  // in a row ahead of the exchange and one or two behind it.  So both halves hold a rolling window of fragments,
-  // as many as the registers left by the accumulators take (five of rows, four transposed), the first two
-  // transposed ones asked for ahead of the second barrier.  Forward and backward of eight prompts of 20
-  // passages, 32 over 8 heads of 128: 968 -> 958 us; of small calls 0.93 to 0.98 of the time.
-  // At head_dim 64 there are half as many fragments and five waves fit a SIMD as long as 96 registers do; a window takes the
-  // kernel beyond that.  One fragment and the compiler's own order there: 300 passages of 40 to 160 tokens, 16 over 2 heads,
-  // 61 us, 72 with the windows; eight prompts of 20 passages, 32 over 8, 173 and 183.
-  constexpr int kRowWin = D == 128 ? 5 : 1, kTrWin = D == 128 ? 4 : 1, kTrAhead = D == 128 ? 2 : 0, kPWin = D == 128 ? 4 : 1;
-  const auto fence = []() __attribute__((always_inline)) { if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0); };
+  // ---- the walk over the query row tiles, two buffers in turn.  A tile's barrier says that every wave's share of it
+  //      has landed and that all are done with the tile before, so the copy of the next may overwrite that buffer ----
+  // Fragments come through rolling windows, as many as the registers take: three waves a SIMD at D = 128 (168), five at 64
+  // (96; with four of either and four waves 219 and 502 us where two and five take 211 and 486: prompts of 30 passages of 40 to
+  // 160 tokens at 16 over 2 heads, of 20 of 100 to 300 at 32 over 8).  At 128 four of either take 921 us a step where six take 919.
+  constexpr int kRowWin = D == 128 ? 6 : 2, kTrWin = D == 128 ? 6 : 2, kTrAhead = D == 128 ? 2 : 0;  // (kTrAhead: ahead of the exponentials)
+  const auto fence = []() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
+  uint32_t cur = 0;  // this tile's buffer
 #pragma unroll 1
-  for (int i = t0; i < n_t; ++i) {
+  for (int i = t0; i < n_t; ++i, cur ^= BUFB) {
     dma_wait<0>();
     wg_barrier();
-    if (i + 1 < n_t) issue_copy(i + 1, (i + 1) & 1);
+    if (i + 1 < n_t) issue_copy(i + 1, cur == 0);
     const bool own = i >= n_f;
     const int r0 = own ? own_last - (i - n_f) * kKvRows : fin_last - i * kKvRows;  // the tile's first packed row, inside its block
     const int n_rows = own ? n_rows_a : n_rows_f;
-    lds_char *const buf = smem + (uint32_t)(i & 1) * BUFB;
-    // a tile of the block's own rows whose tokens all lie before this pair's first key sees none of them
+    // a tile of the block's own rows whose tokens all lie before this wave's first key sees none of them
     // (row = token * group + head: row r's token is at or behind key k exactly if r >= k * group)
-    const bool active = wave_has_keys && !(own && min(r0 + kKvRows, n_rows) <= kw0 * Gq);
-    f32x16_t x;  // A: S - L, then P;  B: dP - delta
-    bf16x8_t pf[2];
-    if (active) {
-      // The accumulator starts at minus the rows' log-sum-exp or delta, so that the products come out as
-      // the exponent of P and as dP - delta.  Register v is row (v >> 2) * 8 + hf * 4 + (v & 3).
+    if (!wave_has_keys || (own && min(r0 + kKvRows, n_rows) <= kw0 * Gq)) continue;
+    lds_char *const buf = smem + cur;
+    // The accumulators start at minus the rows' log-sum-exp or delta, so that the products come out as
+    // the exponent of P and as dP - delta.  Half rt, register v is row 16 rt + 4 g + v.
+    f32x4_t x[4];  // S - L of both halves, then P; dP - delta of both halves, then dS
 #pragma unroll
-      for (int run = 0; run < 4; ++run) {
-        const f32x4_t n4 = *(const lds_f32x4 *)(buf + 2 * TB + wave * 128 + run * 32 + hf * 16);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[run * 4 + e] = n4[e];
-      }
-      bf16x8_t fr[kRowWin];
-#pragma unroll
-      for (int kk = 0; kk < kRowWin; ++kk) fr[kk] = row_frag<D>(buf + ofs1 + r_rd[kk / 2], kk);
-      fence();
-#pragma unroll
-      for (int kk = 0; kk < G::KCH; ++kk) {
-        x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk % kRowWin], kv[kk], x, 0, 0, 0);
-        if (kk + kRowWin < G::KCH) fr[kk % kRowWin] = row_frag<D>(buf + ofs1 + r_rd[(kk + kRowWin) / 2], kk + kRowWin);
-        fence();
-      }
-      // Rows this key may not see: rows beyond the block, and (own block) tokens before the key; their P and
-      // dS become 0 whatever the products gave.  Under one branch, which most tiles do not take.
-      if (r0 + kKvRows > n_rows || (own && r0 < (kw0 + 31) * Gq)) {
-        const int lo = own ? max(my_key * Gq - r0, 0) : 0;
-        const uint32_t span = (uint32_t)max(n_rows - r0 - lo, 0);
-        const float nothing = is_b ? 0.f : -INFINITY;
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          x[v] = (uint32_t)((v >> 2) * 8 + (v & 3) + hf * 4 - lo) >= span ? nothing : x[v];
-      }
-      if (!is_b) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) x[v] = __builtin_amdgcn_exp2f(x[v]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const f32x4_t four = {x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3]};
-          *(lds_f32x4 *)(pex + j * 1024) = four;
-        }
-      }
+    for (int rt = 0; rt < 2; ++rt) {
+      x[rt] = *(const lds_f32x4 *)(buf + 2 * TB + (rt * 4 + g) * 32);
+      x[2 + rt] = *(const lds_f32x4 *)(buf + 2 * TB + (rt * 4 + g) * 32 + 16);
     }
-    lds_wait();
+    auto row_frag_of = [&](int st) __attribute__((always_inline)) {  // step st: k-step st / 4 of x[st % 4]
+      return *(const lds_bf16x8 *)(buf + r_rd[st / 4] + kv_row_ofs<D>(st));
+    };
+    bf16x8_t fr[kRowWin];
+#pragma unroll
+    for (int st = 0; st < kRowWin; ++st) fr[st] = row_frag_of(st);
+    fence();
+#pragma unroll
+    for (int st = 0; st < 4 * KG::KK; ++st) {
+      x[st & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[st % kRowWin], (st & 2) ? vf[st / 4] : kf[st / 4], x[st & 3], 0, 0, 0);
+      if (st + kRowWin < 4 * KG::KK) fr[st % kRowWin] = row_frag_of(st + kRowWin);
+      fence();
+    }
+    // transposed fragments: slab st % DT of dO^T, then of q^^T; rows in the order that P and dS have (4 g + 0..3 of either half)
+    auto tr_frag_of = [&](int st) __attribute__((always_inline)) {
+      return kv_tr_frag<D>(smem + ((cur + t_rd) ^ (uint32_t)((st % KG::DT) * 32)) + (st < KG::DT ? TB : 0u));
+    };
     bf16x8_t tr[kTrWin];
-    if (active) {
 #pragma unroll
-      for (int st = 0; st < kTrAhead; ++st) tr[st] = tr_frag<D>(buf + ofs2 + t_rd[st % G::DT], st / G::DT);
-    }
-    wg_barrier();
-    if (active) {
-      if (is_b) {
+    for (int st = 0; st < kTrAhead; ++st) tr[st] = tr_frag_of(st);
+    fence();
+    // Rows this key may not see: rows beyond the block, and (own block) tokens before the key; their P and
+    // dS become 0 whatever the products gave.  Under one branch, which most tiles do not take.
+    if (r0 + kKvRows > n_rows || (own && r0 < (kw0 + KG::KEYS - 1) * Gq)) {
+      const int lo = own ? max(my_key * Gq - r0, 0) : 0;
+      const uint32_t span = (uint32_t)max(n_rows - r0 - lo, 0);
 #pragma unroll
-        for (int j0 = 0; j0 < 4; j0 += kPWin) {
-          f32x4_t four[kPWin];
+      for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-          for (int j = 0; j < kPWin; ++j) four[j] = *(const lds_f32x4 *)(pex + (j0 + j) * 1024);
-          fence();
-#pragma unroll
-          for (int v = 0; v < 4 * kPWin; ++v) x[4 * j0 + v] *= four[v >> 2][v & 3];
+        for (int v = 0; v < 4; ++v) {
+          const bool hidden = (uint32_t)(rt * 16 + 4 * g + v - lo) >= span;
+          x[rt][v] = hidden ? -INFINITY : x[rt][v];
+          x[2 + rt][v] = hidden ? 0.f : x[2 + rt][v];
         }
-      }
+    }
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        u32x4_t w;
+    for (int rt = 0; rt < 2; ++rt) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) w[j] = pack_bf16(x[e * 8 + 2 * j], x[e * 8 + 2 * j + 1]);
-        pf[e] = __builtin_bit_cast(bf16x8_t, w);
-      }
+      for (int v = 0; v < 4; ++v) x[rt][v] = __builtin_amdgcn_exp2f(x[rt][v]);
+      x[2 + rt] *= x[rt];
+    }
+    const bf16x8_t pf = pack_rows(x[0], x[1]), dsf = pack_rows(x[2], x[3]);
 #pragma unroll
-      for (int st = kTrAhead; st < kTrWin; ++st) tr[st] = tr_frag<D>(buf + ofs2 + t_rd[st % G::DT], st / G::DT);
+    for (int st = kTrAhead; st < kTrWin; ++st) tr[st] = tr_frag_of(st);
+    fence();
+#pragma unroll
+    for (int st = 0; st < 2 * KG::DT; ++st) {
+      if (st < KG::DT) dv[st % KG::DT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr[st % kTrWin], pf, dv[st % KG::DT], 0, 0, 0);
+      else dk[st % KG::DT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr[st % kTrWin], dsf, dk[st % KG::DT], 0, 0, 0);
+      if (st + kTrWin < 2 * KG::DT) tr[st % kTrWin] = tr_frag_of(st + kTrWin);
       fence();
-#pragma unroll
-      for (int st = 0; st < 2 * G::DT; ++st) {
-        acc[st % G::DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr[st % kTrWin], pf[st / G::DT], acc[st % G::DT], 0, 0, 0);
-        if (st + kTrWin < 2 * G::DT)
-          tr[st % kTrWin] = tr_frag<D>(buf + ofs2 + t_rd[(st + kTrWin) % G::DT], (st + kTrWin) / G::DT);
-        fence();
-      }
     }
   }
 
@@ -845,56 +911,47 @@ __global__ __launch_bounds__(kBThreads, 3) void bwd_dkv_kernel(AttnParams p, Bwd
   wg_barrier();
   int ln = lane;
   asm volatile("" : "+v"(ln));
-  const int ecol = ln & 31, ehf = ln >> 5;
+  const int ecol = ln & 15, eg = ln >> 4;
   if (n_splits > 1) {
-    // (a shared walk: every wave leaves its half, the last workgroup adds the splits up in their order)
+    // (a shared walk: every wave leaves its sums, the last workgroup adds the splits up in their order)
     const int64_t slot = ((int64_t)(keytile - split * n_kt) * p.n_kv_heads + kvh) * kBWaves + wave;  // of split 0
     const int64_t step = (int64_t)n_kt * p.n_kv_heads * kBWaves;                                     // to the next
-    float *const part_o = (float *)p.part_o;
-    if (wave_has_keys) leave_accumulators<D>(part_o, slot + split * step, ln, acc);
-    static_assert(kBWaves * (size_t)G::TILEB + 16 <= KG::LDS, "a word behind the output staging");
+    char *const part = (char *)p.part_o;
+    constexpr int kBytes = 32 * D * 4;  // of one wave: both sums of 16 keys
+    static_assert(2 * KG::DT * 64 * 16 == kBytes, "a kilobyte per slab");
+    if (wave_has_keys) {
+      leave_sums(part + (slot + split * step) * kBytes, ln, 0, dv);
+      leave_sums(part + (slot + split * step) * kBytes, ln, KG::DT, dk);
+    }
     if (!last_of_splits(p.part_idx + (int64_t)(keytile - split * n_kt) * p.n_kv_heads + kvh, n_splits, smem + KG::LDS - 16)) return;
     if (wave_has_keys) {
 #pragma unroll
-      for (int dt = 0; dt < G::DT; ++dt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
+      for (int dt = 0; dt < KG::DT; ++dt) dv[dt] = dk[dt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-      for (int s = 0; s < n_splits; ++s) {
-        u32x4_t w[D / 8];
-        fetch_accumulators<D>(part_o, slot + s * step, ln, w);
-#pragma unroll
-        for (int k = 0; k < D / 8; ++k)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) *((float *)&acc[k >> 2] + (k & 3) * 4 + e) += __uint_as_float(w[k][e]);
-      }
+      for (int s = 0; s < n_splits; ++s) add_sums(part + (slot + s * step) * kBytes, ln, dv, dk);
     }
   }
-  if (is_b)
-    rotate_back<D>(acc, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(meta.pos0[b] + min(kw0 + ecol, lk - 1)) * D), ehf,
-                   p.rope_layout != 0, kLn2 / p.scale_log2e);
-  static_assert(kBWaves * (size_t)G::TILEB <= KG::LDS, "the output staging fits");
-  lds_char *stage = smem + wave * G::TILEB;
-#pragma unroll
-  for (int dt = 0; dt < G::DT; ++dt)
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      u32x2_t w;
-      w[0] = pack_bf16(acc[dt][q4 * 4 + 0], acc[dt][q4 * 4 + 1]);
-      w[1] = pack_bf16(acc[dt][q4 * 4 + 2], acc[dt][q4 * 4 + 3]);
-      *reinterpret_cast<__attribute__((address_space(3))) u32x2_t *>(stage + tile_ofs<D>(ecol, dt * 4 + q4) + ehf * 8) = w;
-    }
+  rotate_back_keys<D>(dk, reinterpret_cast<const f32x4_t *>(p.q_table + (int64_t)(meta.pos0[b] + min(kw0 + ecol, lk - 1)) * D), eg,
+                 p.rope_layout != 0, kLn2 / p.scale_log2e);
+  static_assert(kBWaves * 2 * KG::KEYS * (size_t)ROWB <= KG::LDS, "the output staging fits");
+  lds_char *stage = smem + wave * (2 * KG::KEYS * ROWB);  // this wave's rows of dV, then of dk
+  stage_rows<D>(stage, dv, ecol, eg);
+  stage_rows<D>(stage + KG::KEYS * ROWB, dk, ecol, eg);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  uint16_t *dst = is_b ? bp.dk : bp.dv;
-  const int64_t st = is_b ? bp.dk_st : bp.dv_st, sh = is_b ? bp.dk_sh : bp.dv_sh;
+  constexpr int QRPI = 64 / KG::CPR;  // whole rows per store instruction
 #pragma unroll
-  for (int u = 0; u < G::KCH; ++u) {
-    const int rr = u * G::QRPI + ln / G::CPR;
-    const u32x4_t w = *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t *>(stage + tile_ofs<D>(rr, ln % G::CPR));
-    if (kw0 + rr < lk)
-      *reinterpret_cast<u32x4_t *>(dst + (int64_t)(k_tok0 + kw0 + rr) * st + (int64_t)kvh * sh + (ln % G::CPR) * 8) = w;
+  for (int t = 0; t < 2; ++t) {
+    uint16_t *dst = t ? bp.dk : bp.dv;
+    const int64_t st = t ? bp.dk_st : bp.dv_st, sh = t ? bp.dk_sh : bp.dv_sh;
+#pragma unroll
+    for (int u = 0; u < KG::KEYS / QRPI; ++u) {
+      const int rr = u * QRPI + ln / KG::CPR;
+      const u32x4_t w = *(const lds_u32x4 *)(stage + t * KG::KEYS * ROWB + kv_ofs<D>(rr, ln % KG::CPR));
+      if (kw0 + rr < lk)
+        *reinterpret_cast<u32x4_t *>(dst + (int64_t)(k_tok0 + kw0 + rr) * st + (int64_t)kvh * sh + (ln % KG::CPR) * 8) = w;
+    }
   }
 }
 

@@ -1581,6 +1581,34 @@ def test_whole_prompts_backward_medium_prompts(ba):
         assert_grad_close(gv[t0:t1], rv, av, f"dv, prompt {n}")
 
 
+@pytest.mark.parametrize("hq,hkv,d,layout", [(4, 4, 64, 0), (8, 2, 64, 1), (10, 2, 64, 0), (2, 2, 128, 1), (8, 2, 128, 0), (6, 2, 128, 1), (8, 1, 128, 0)])
+def test_gradients_at_the_edges_of_key_and_row_tiles(ba, hq, hkv, d, layout):
+    """Blocks of 1, 15 to 17, 31 to 33, 47, 63 to 65 and 128 keys (waves of 16 keys, workgroups of 64), groups that divide a
+    tile of 32 packed rows and groups that do not, last blocks of one row tile and of part of one."""
+    torch = torch_mod()
+    prompts = [[1, 15, 16, 17, 5], [31, 33, 63, 1], [64, 0, 65, 47, 9], [128]]
+    offs = np.concatenate([[0], np.cumsum([n for p in prompts for n in p])]).astype(np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    T = int(offs[-1])
+    heads = ba.Heads(hq, hkv, d, 10000.0, rope_layout=layout)
+    qb, kb, vb = gen_qkv(760 + hq, T, hq, hkv, d)
+    dob = wl.normal_bf16_bits(790 + hq, (T, hq, d))
+    q, k, v, do = dev_bf16(qb), dev_bf16(kb), dev_bf16(vb), dev_bf16(dob)
+    o, _, lse = gpu_prompts(ba, heads, qb, kb, vb, cu_blk, offs, want_k_rot=False)
+    dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, k, v))
+    ws = torch.full((ba.ba_block_attention_prompts_backward_workspace_bytes(heads, cu_blk, offs),), 255, dtype=torch.uint8, device="cuda")
+    ba.ba_block_attention_prompts_backward(heads, q, k, v, o, lse, do, dq, dk, dv, cu_blk, offs, ws)
+    torch.cuda.synchronize()
+    f = oracle.bf16_bits_to_f64
+    th = oracle.theta(10000.0, d)
+    for n in range(len(prompts)):
+        t0, t1 = int(offs[cu_blk[n]]), int(offs[cu_blk[n + 1]])
+        po = offs[cu_blk[n]:cu_blk[n + 1] + 1] - t0
+        refs, sizes = oracle_grads(f(qb[t0:t1]), f(kb[t0:t1]), f(vb[t0:t1]), f(dob[t0:t1]), po, th, layout)
+        for got, ref, size, what in zip((dq, dk, dv), refs, sizes, ("dq", "dk", "dv")):
+            assert_grad_close(host_f64(got[t0:t1]), ref, size, f"{what}, prompt {n}")
+
+
 SHARED_CASES = [("group1-d64", 2, 2, 64, [[1150, 37], [40, 9]]), ("group3-d128", 6, 2, 128, [[700, 420, 50]]),
                 ("group4-d128", 8, 2, 128, [[30, 5], [1300, 33]]), ("group4-d64", 4, 1, 64, [[1, 1500, 1]]),
                 # more than twelve row tiles times KV heads
