@@ -126,7 +126,9 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   constexpr bool kBlocks = std::is_same<Meta, FinalBlocksMeta>::value || std::is_same<Meta, FinalBlocksMetaSmall>::value;
   // context keys gathered, value rows through a table of where they lie (waves 4..7 keep their part of it in LDS)
   constexpr bool kRows = std::is_same<Meta, FinalGatherMeta>::value;
-  constexpr bool kFinal = std::is_same<Meta, FinalMeta>::value || kBlocks || kRows;
+  // query rows and keys of the final block as the caller gave them
+  constexpr bool kFresh = std::is_same<Meta, FinalFreshMeta>::value;
+  constexpr bool kFinal = std::is_same<Meta, FinalMeta>::value || kBlocks || kRows || kFresh;
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char *smem = (lds_char *)smem_generic;
   // LDS map: kNumKBuf K buffers from byte 0, then kNumVBuf V buffers, TILEB bytes each (then the row table).
@@ -762,12 +764,135 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
     }
     q_finish(raw, my_tok, rot);
   };
+  // Rows that no pre-pass has turned (few query tokens, launches of one workgroup per compute unit at most).  The (cos, sin) of
+  // the prompt's tokens are worked out here, into the LDS behind the tile buffers, while tile 0 and the rows are on their way; the
+  // workgroup that walks the final block's own key tile turns those keys as well, into a tile that then takes the table's place
+  // (the tile copy still fetches them as they are, into a buffer that nobody reads: the walk's waits count its loads).
+  // The pre-pass, its launch included, is 3.9 us of a call on the device (and 2.6 on the host); this adds 0.3 (a token or two) to
+  // 2.3 us (64) to a workgroup's start.  Calls of 1 to 4 tokens 18 -> 14 us, of 50 over 31,950 tokens of context, 32 over 8 heads of
+  // 128, 44.2 -> 42.6; with 64 tokens over 2,000 the gain is down to 0.6.  The table of longer blocks, and the keys of more than
+  // one tile, would not fit, and in launches of several rounds of workgroups each round would pay.
+  constexpr uint32_t FRESH = (uint32_t)G::LDS;  // the table, then the tile
+  constexpr uint32_t TROW = D * 4;              // bytes of a table row: D / 2 pairs
+  static_assert(!kFresh || (kFreshTokens * TROW <= 32 * 1024 && TB <= kFreshTokens * TROW), "the table fits, and the tile in its place");
+  auto load_q_fresh = [&]() __attribute__((always_inline)) {
+    if constexpr (kFresh) {
+      // the query rows, whole, as in load_q_first
+      const uint32_t slice = (role_b ? VBASE : 0u) + TB + (uint32_t)(wave & (kWaves / 2 - 1)) * (32 * G::ROWB);
+      const int wave_row0 = row0 + wave * 32;
+      const int tok_first = (int)fast_div((uint32_t)min(wave_row0, n_rows - 1), p.group_div);  // wave-uniform
+      const char *qbase = (const char *)(p.q + (int64_t)(pr.q_tok0 + tok_first) * p.q_st + (int64_t)(kvh * Gq) * p.q_sh);
+      const uint32_t st_b = (uint32_t)p.q_st * 2u, sh_b = (uint32_t)p.q_sh * 2u;  // (the host checked that they fit)
+#pragma unroll
+      for (int j = 0; j < 32 / G::RPI; ++j) {
+        const int r_in = j * G::RPI + lane / G::CPR, pos = lane % G::CPR;
+        const int r = min(wave_row0 + r_in, n_rows - 1);  // rows beyond the problem: its last row, zeroed below
+        const int tok = (int)fast_div((uint32_t)r, p.group_div);
+        const uint32_t off = (uint32_t)(tok - tok_first) * st_b + (uint32_t)(r - tok * Gq) * sh_b +
+                             ((uint32_t)(pos ^ ((r_in / G::LPR) & (G::CPR - 1))) << 4);
+        lds_dma16(qbase, off, (uint32_t)(uintptr_t)smem + slice + j * 1024);
+      }
+      // this thread's two chunks of the final block's keys: c and c + CPR / 2 of row k_row (rows beyond the block: its last)
+      constexpr int HC = G::CPR / 2;
+      const bool has_keys = t_end > n_ctx_tiles && n_t > 0;
+      const int k_row = (int)threadIdx.x / HC, k_c = (int)threadIdx.x % HC, k_tok = min(k_row, pr.lq - 1);
+      const bool turns_keys = has_keys && k_row < kTileKeys;
+      u32x4_t ka = {0u, 0u, 0u, 0u}, kb = ka;
+      if (turns_keys) {
+        const uint16_t *from = p.kf + (int64_t)(pr.q_tok0 + k_tok) * p.kf_st + (int64_t)kvh * p.kf_sh + k_c * 8;
+        ka = *reinterpret_cast<const u32x4_t *>(from);
+        kb = *reinterpret_cast<const u32x4_t *>(from + HC * 8);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // the table: pairs 2 i and 2 i + 1 of token t are 16-byte piece i of its row, kept at piece i ^ (t & 7)
+      typedef __attribute__((address_space(3))) f32x2_t lds_f32x2;
+      typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+      auto piece = [&](int t, int i) __attribute__((always_inline)) { return FRESH + (uint32_t)t * TROW + ((uint32_t)(i ^ (t & 7)) << 4); };
+      {
+        static_assert(kThreads % (D / 2) == 0, "a thread keeps its frequency");
+        const int j = (int)threadIdx.x % (D / 2);
+        const uint64_t turns = meta.rt.turns[j];
+        const int pos0 = meta.pos0[rowtile];
+        for (int t = (int)threadIdx.x / (D / 2); t < pr.lq; t += kThreads / (D / 2)) {
+          float c, sn;
+          sincos_phase(rope_phase(pos0 + t, turns), c, sn);
+          *(lds_f32x2 *)(smem + piece(t, j >> 1) + (j & 1) * 8) = f32x2_t{c, sn};
+        }
+      }
+      dma_wait<0>();  // tile 0 (this wave's share), the query rows and the keys
+      lds_wait();
+      wg_barrier();   // the table is whole
+      u32x4_t raw[G::KCH];
+      f32x4_t cs[2 * G::KCH];
+      const int t_q = min(my_tok, pr.lq - 1);
+      const bool halves = p.rope_layout != 0;
+#pragma unroll
+      for (int i = 0; i < 2 * G::KCH; ++i) {
+        cs[i] = *(const lds_f32x4 *)(smem + piece(t_q, fragment_table_piece(i, hf, halves)));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cs[i][e] *= p.scale_log2e;
+      }
+#pragma unroll
+      for (int kk = 0; kk < G::KCH; ++kk) {
+        raw[kk] = *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t *>(smem + slice + k_rd[kk]);
+        if (!row_ok) raw[kk] = u32x4_t{0u, 0u, 0u, 0u};
+      }
+      rotate_fragments<G::KCH, true>(raw, cs, halves);  // (the pre-pass's products: the same bits)
+#pragma unroll
+      for (int kk = 0; kk < G::KCH; ++kk) {
+        asm volatile("" : "+v"(raw[kk]));
+        qf[kk] = __builtin_bit_cast(bf16x8_t, raw[kk]);
+      }
+      if (has_keys) {  // (the whole workgroup or none of it)
+        u32x4_t ya, yb;
+        if (turns_keys) {
+          if (!halves) {
+            // chunk c holds pairs 4 c .. 4 c + 3
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const f32x4_t ta = *(const lds_f32x4 *)(smem + piece(k_tok, k_c * 2 + h)), tb = *(const lds_f32x4 *)(smem + piece(k_tok, (k_c + HC) * 2 + h));
+#pragma unroll
+              for (int e = 0; e < 2; ++e) {
+                const float ax = bf16_lo(ka[2 * h + e]), ay = bf16_hi(ka[2 * h + e]), bx = bf16_lo(kb[2 * h + e]), by = bf16_hi(kb[2 * h + e]);
+                ya[2 * h + e] = pack_bf16(__builtin_fmaf(ta[2 * e], ax, -(ta[2 * e + 1] * ay)), __builtin_fmaf(ta[2 * e + 1], ax, ta[2 * e] * ay));
+                yb[2 * h + e] = pack_bf16(__builtin_fmaf(tb[2 * e], bx, -(tb[2 * e + 1] * by)), __builtin_fmaf(tb[2 * e + 1], bx, tb[2 * e] * by));
+              }
+            }
+          } else {
+            // element e of chunk c pairs with element e of chunk c + CPR / 2: pairs 8 c .. 8 c + 7
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const f32x4_t t = *(const lds_f32x4 *)(smem + piece(k_tok, k_c * 4 + e));
+              const float a0 = bf16_lo(ka[e]), a1 = bf16_hi(ka[e]), b0 = bf16_lo(kb[e]), b1 = bf16_hi(kb[e]);
+              ya[e] = pack_bf16(__builtin_fmaf(t[0], a0, -(t[1] * b0)), __builtin_fmaf(t[2], a1, -(t[3] * b1)));
+              yb[e] = pack_bf16(__builtin_fmaf(t[1], a0, t[0] * b0), __builtin_fmaf(t[3], a1, t[2] * b1));
+            }
+          }
+        }
+        lds_wait();
+        wg_barrier();  // nobody reads the table any more
+        if (turns_keys) {
+          typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
+          const int swz = (k_row / G::LPR) & (G::CPR - 1);
+          *(lds_u32x4 *)(smem + FRESH + k_row * G::ROWB + ((k_c ^ swz) << 4)) = ya;
+          *(lds_u32x4 *)(smem + FRESH + k_row * G::ROWB + (((k_c + HC) ^ swz) << 4)) = yb;
+        }
+        lds_wait();  // (published by the walk's first barrier)
+      }
+    }
+  };
+  // K tile of tile i + 1 of the walk, whose softmax's tile is under cm
+  auto next_k = [&](const Cursor &c, uint32_t buf_ofs) __attribute__((always_inline)) {
+    return kFresh && c.seg < n_ctx_segs && c.rem == 1 ? FRESH : buf_ofs;
+  };
   Cursor cm = cursor_at(t_begin);  // the tile whose softmax comes next
   auto rot_of = [&](int sg) __attribute__((always_inline)) {
     if constexpr (kBlocks) return sg < n_ctx_segs ? meta.rot_base + pr.blk0 + sg : -1;
     return -1;
   };
-  if (p.q_rows_fit32) {
+  if constexpr (kFresh) {
+    load_q_fresh();
+  } else if (p.q_rows_fit32) {
     load_q_first(rot_of(cm.seg));
   } else {
     load_q(rot_of(cm.seg));
@@ -780,11 +905,12 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   bf16x8_t pf[4];
   bf16x8_t fr[W];
   if (n_t > 0) {
+    const uint32_t first_k = kFresh && cm.seg >= n_ctx_segs ? FRESH : 0u;
     if (!role_b) {
       wg_barrier();  // tile 0 of both kinds is visible
       first_copy(1);
       first_copy(2);
-      if (wave_has_rows) qk_first(0, sacc);
+      if (wave_has_rows) qk_first(first_k, sacc);
       wg_barrier();
     } else {
       wg_barrier();
@@ -794,7 +920,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
         if (n_t > 2) dma_wait<2 * G::IPW>(); else if (n_t > 1) dma_wait<G::IPW>(); else dma_wait<0>();
       }
       wg_barrier();
-      if (wave_has_rows) qk_first(0, sacc);
+      if (wave_has_rows) qk_first(first_k, sacc);
       wg_barrier();
     }
     // One iteration.  The copy of tile i+3 is prepared here, in the softmax half, where scalar
@@ -863,7 +989,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
       const uint32_t vofs = VBASE + (i & (kNumVBuf - 1)) * TB;
       if (wave_has_rows) preload(vofs, fr);
       wg_barrier();
-      if (wave_has_rows) mfma_block(vofs, ((i + 1) & (kNumKBuf - 1)) * TB, steady || i + 1 < n_t, pf, sacc, fr);
+      if (wave_has_rows) mfma_block(vofs, steady ? ((i + 1) & (kNumKBuf - 1)) * TB : next_k(cm, ((i + 1) & (kNumKBuf - 1)) * TB), steady || i + 1 < n_t, pf, sacc, fr);
       if constexpr (kBlocks && !steady) {
         advance(cm);
         if (role_b && i + 2 < n_t && cm.rem == 1) {  // (QK of tile i+1 is done: the fragments are free)
@@ -1159,7 +1285,8 @@ hipError_t launch_attn_t(const AttnParams &p, const Meta &meta, hipStream_t stre
   const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads * p.n_splits;
   if (n_wg == 0) return hipSuccess;
   if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
-  constexpr size_t lds = Geo<D>::LDS + (std::is_same<Meta, FinalGatherMeta>::value ? (size_t)kWaves / 2 * kRowTableTiles * 64 : 0);
+  constexpr size_t lds = Geo<D>::LDS + (std::is_same<Meta, FinalGatherMeta>::value ? (size_t)kWaves / 2 * kRowTableTiles * 64 : 0) +
+                         (std::is_same<Meta, FinalFreshMeta>::value ? (size_t)kFreshTokens * D * 4 : 0);
   static_assert((size_t)kWaves * 32 * D * 2 <= lds, "epilogue staging must fit the tile buffers");
   static_assert(lds <= 160 * 1024, "gfx950 has 160 KB of LDS per workgroup");
   // more than 64 KB of dynamic LDS has to be asked for once per kernel (setting it twice, from two
@@ -1195,6 +1322,12 @@ hipError_t launch_attn_encode(const AttnParams &p, const EncodeMeta &meta, hipSt
 hipError_t launch_attn_final(const AttnParams &p, const FinalMeta &meta, hipStream_t stream) {
   if (p.head_dim == 128) return launch_attn_t<128, FinalMeta>(p, meta, stream);
   if (p.head_dim == 64) return launch_attn_t<64, FinalMeta>(p, meta, stream);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_attn_final_fresh(const AttnParams &p, const FinalFreshMeta &meta, hipStream_t stream) {
+  if (p.head_dim == 128) return launch_attn_t<128, FinalFreshMeta>(p, meta, stream);
+  if (p.head_dim == 64) return launch_attn_t<64, FinalFreshMeta>(p, meta, stream);
   return hipErrorInvalidValue;
 }
 

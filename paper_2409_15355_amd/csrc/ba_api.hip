@@ -305,6 +305,30 @@ static int32_t run_gather_prepass(const ba_heads *h, const Gather &g, const ba::
   return rc || !apart ? rc : run_rope_prepass(h, rt, q, q_rot, k, k_rot, n, start, pos0, stream);
 }
 
+// Whether all n prompts' query blocks are one row tile and one key tile each.
+static bool fresh_prompts(const int32_t *cu_q, int n, int G) {
+  for (int i = 0; i < n; ++i) {
+    const int64_t lq = (int64_t)cu_q[i + 1] - cu_q[i];
+    if (lq > ba::kFreshTokens || lq * G > ba::kTileRows) return false;
+  }
+  return true;
+}
+// Whether a call's attention kernel may read the query rows and keys as they are while it writes o: with the pre-pass they are
+// read before it starts.  (o over q itself is fine: a workgroup reads its rows before it writes them.)
+static bool fresh_apart(const ba_tensor *q_f, const ba_tensor *k_f, const ba_tensor *o, int64_t t0, int64_t t1, const ba_heads *h) {
+  struct Span {
+    uintptr_t lo, hi;
+  };
+  const auto span = [&](const ba_tensor *t, int heads) {
+    const uintptr_t lo = (uintptr_t)t->ptr + (uintptr_t)(t0 * t->stride_tok * 2);
+    return Span{lo, lo + (uintptr_t)(((t1 - t0 - 1) * t->stride_tok + (heads - 1) * t->stride_head + h->head_dim) * 2)};
+  };
+  const auto touch = [](const Span &a, const Span &b) { return a.lo < b.hi && b.lo < a.hi; };
+  const Span so = span(o, h->n_q_heads);
+  const bool same = o->ptr == q_f->ptr && o->stride_tok == q_f->stride_tok && o->stride_head == q_f->stride_head;
+  return !touch(so, span(k_f, h->n_kv_heads)) && (same || !touch(so, span(q_f, h->n_q_heads)));
+}
+
 int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,
                     const ba_tensor *k_f, const ba_tensor *v_f, const ba_tensor *o_out, const ba_tensor *k_f_rot_out,
                     int32_t n_prompts, const int32_t *cu_q, const int32_t *cu_ctx, const int32_t *q_pos0,
@@ -416,6 +440,10 @@ int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor
   ap.n_splits = pl.n_splits;
   ap.wg_clock = ba::probe_clock();  // (null unless a probe of ba_probe.hip is the caller)
 
+  // (rotated keys as an output, rows of q further apart than 32-bit offsets, outputs that lie over what is read: by the pre-pass)
+  const bool fresh_ok = rope_mode == BA_ROPE_APPLY && !gather && !k_f_rot_out && !ap.wg_clock && q_f->stride_tok <= 1 << 24 &&
+                        32 * q_f->stride_tok * 2 + (int64_t)G * q_f->stride_head * 2 < (int64_t)1 << 32 &&
+                        fresh_apart(q_f, k_f, o_out, cu_q[0], cu_q[n_prompts], heads);
   int64_t tile_base = 0;  // row tiles of the launches so far: the split partials are indexed by row tile
   for (int n0 = 0; n0 < n_prompts; n0 += ba::kFinMaxPrompts) {
     const int n = std::min(ba::kFinMaxPrompts, n_prompts - n0);
@@ -428,6 +456,33 @@ int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor
                                   ba::final_q_bytes_per_kv_head(heads, pl.lq_total), ap.split_cut, &ap.use_cuts, &ap.kv_group,
                                   &ap.xcd_runs)))
       return rc;
+    // few query tokens, one workgroup per compute unit at most: no pre-pass, the attention kernel turns the rows itself
+    if (fresh_ok && tiles * heads->n_kv_heads * pl.n_splits <= num_cus() && fresh_prompts(cu_q + n0, n, G)) {
+      ba::FinalFreshMeta fm;
+      memset(&fm, 0, sizeof(fm));
+      static_cast<ba::FinalMeta &>(fm) = meta;
+      for (int i = 0; i < n; ++i) fm.pos0[meta.tile_start[i]] = pos0[n0 + i];
+      fm.rt = rt;
+      ba::AttnParams fp = ap;
+      fp.q = (const uint16_t *)q_f->ptr;
+      fp.q_st = q_f->stride_tok;
+      fp.q_sh = q_f->stride_head;
+      fp.kf = (const uint16_t *)k_f->ptr;
+      fp.kf_st = k_f->stride_tok;
+      fp.kf_sh = k_f->stride_head;
+      if (!any_ctx) {
+        fp.kc = fp.kf;
+        fp.kc_st = fp.kf_st;
+        fp.kc_sh = fp.kf_sh;
+      }
+      hipError_t e;
+      {
+        ProfileScope ps(BA_PROFILE_ATTENTION, stream);
+        e = ba::launch_attn_final_fresh(fp, fm, stream);
+      }
+      if (e != hipSuccess) return device_fail(e, "final-block attention launch");
+      continue;
+    }
     if (rope_mode == BA_ROPE_APPLY) {  // absolute positions of the final block's tokens
       if (gather && n0 == 0 && gather->n_blocks > 0)
         rc = run_gather_prepass(heads, *gather, rt, q_f, q_ws, k_f, &kf_use, n, meta.cu_q, pos0.data(), stream);

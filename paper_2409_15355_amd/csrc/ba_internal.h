@@ -359,6 +359,14 @@ struct FinalGatherMeta : FinalMeta {
   const uint32_t *rows;
 };
 
+// Final block whose query rows and keys are as the caller gave them: no RoPE pre-pass has run, the kernel turns them itself
+// (see attn_kernel).  Every prompt has one row tile and one key tile of its own.
+constexpr int kFreshTokens = kTileKeys;
+struct FinalFreshMeta : FinalMeta {
+  int32_t pos0[kFinMaxPrompts];  // position of a row tile's first token
+  RopeTable rt;
+};
+
 // Final block over a table of cached blocks (each at the positions it was encoded at).
 template <int NP, int NB>
 struct FinalBlocksMetaT {
@@ -409,6 +417,7 @@ hipError_t launch_attn_prompt_short(const AttnParams &p, const PromptMeta &meta,
 hipError_t launch_attn_final_blocks(const AttnParams &p, const FinalBlocksMeta &meta, hipStream_t stream);
 hipError_t launch_attn_final_blocks(const AttnParams &p, const FinalBlocksMetaSmall &meta, hipStream_t stream);
 hipError_t launch_attn_final(const AttnParams &p, const FinalMeta &meta, hipStream_t stream);
+hipError_t launch_attn_final_fresh(const AttnParams &p, const FinalFreshMeta &meta, hipStream_t stream);
 hipError_t launch_attn_final_gathered(const AttnParams &p, const FinalGatherMeta &meta, hipStream_t stream);
 // Merge the split-KV partials of all p.part_units units into the bf16 output.
 hipError_t launch_combine(const AttnParams &p, hipStream_t stream);

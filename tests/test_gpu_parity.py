@@ -2561,3 +2561,45 @@ def test_plain_and_converted_arguments_make_the_same_call(ba, monkeypatch):
         ba.ba_encode_blocks(heads, q[:189], k, v, torch.empty_like(q), None, offs, ba.ROPE_APPLY, ws)
     with pytest.raises(ba.BaError):  # (refused by the library itself: the status comes back through the native half)
         ba.ba_encode_blocks(heads, q, k, v, torch.empty_like(q), None, offs, 7, ws)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("hq,hkv,d,lqs,ctxs", [(8, 2, 128, [64], [0]), (8, 2, 128, [1, 64, 33], [1, 700, 0]), (32, 8, 128, [50], [31950]),
+                                               (4, 4, 64, [64, 2], [63, 64]), (8, 2, 64, [31], [5000]), (16, 2, 128, [32, 32], [65, 129]),
+                                               (5, 1, 64, [51, 7], [2000, 30]), (8, 2, 128, [64, 65], [700, 700]), (16, 2, 128, [33], [300])])
+def test_final_blocks_of_few_tokens_turn_their_own_rows(ba, hq, hkv, d, lqs, ctxs, layout):
+    """One row tile and one key tile of its own per prompt: the attention kernel turns q and k_f itself (64 tokens at most,
+    256 packed rows; the last two shapes are beyond).  The bits of the call that also returns the rotated keys, which runs the
+    pre-pass; strided rows, given positions, the output over the queries, and over half of the keys (the pre-pass again)."""
+    torch = torch_mod()
+    cu_q = np.concatenate([[0], np.cumsum(lqs)]).astype(np.int32)
+    cu_ctx = np.concatenate([[0], np.cumsum(ctxs)]).astype(np.int32)
+    tq, tc = int(cu_q[-1]), int(cu_ctx[-1])
+    heads = ba.Heads(hq, hkv, d, 10000.0, rope_layout=layout)
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    wide = torch.randn((tq + 1, hq + 3 * hkv, d), generator=gen, device="cuda").to(torch.bfloat16)
+    q, kf, vf = wide[:tq, :hq], wide[:tq, hq:hq + hkv], wide[:tq, hq + hkv:hq + 2 * hkv]
+    kc, vc = (torch.randn((max(tc, 1), hkv, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    ws = lambda rot: torch.full((max(256, ba.ba_final_block_attention_workspace_bytes(heads, cu_q, cu_ctx, 1, rot)),), 255, dtype=torch.uint8, device="cuda")
+    for pos in (None, np.array([100000 + 7 * i for i in range(len(lqs))], dtype=np.int32)):
+        k_rot = torch.empty((tq, hkv, d), dtype=torch.bfloat16, device="cuda")
+        want, got = (torch.full((tq, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        ba.ba_final_block_attention(heads, q, kc, vc, kf, vf, want, k_rot, cu_q, cu_ctx, pos, 1, ws(True))
+        for _ in range(2):
+            ba.ba_final_block_attention(heads, q, kc, vc, kf, vf, got, None, cu_q, cu_ctx, pos, 1, ws(False))
+            assert torch.equal(got, want)
+        over = q.clone()
+        ba.ba_final_block_attention(heads, over, kc, vc, kf, vf, over, None, cu_q, cu_ctx, pos, 1, ws(False))
+        assert torch.equal(over, want)
+    both = torch.zeros((tq + 8, hq, d), dtype=torch.bfloat16, device="cuda")  # o and, in its memory, the keys
+    inside = both.view(-1)[:tq * hkv * d].view(tq, hkv, d)
+    inside.copy_(kf)
+    ba.ba_final_block_attention(heads, q, kc, vc, inside, vf, both[:tq], None, cu_q, cu_ctx, pos, 1, ws(False))
+    assert torch.equal(both[:tq], want)
+    if tc < 6000:
+        bits = lambda t: host_bits(t.contiguous())
+        f = oracle.bf16_bits_to_f64
+        got.fill_(float("nan"))
+        ba.ba_final_block_attention(heads, q, kc, vc, kf, vf, got, None, cu_q, cu_ctx, None, 1, ws(False))
+        ref = oracle.final_block(f(bits(q)), f(bits(kc[:tc])), f(bits(vc[:tc])), f(bits(kf)), f(bits(vf)), cu_q, cu_ctx, oracle.theta(10000.0, d), layout=layout)
+        assert_attention_close(host_f64(got), ref)
