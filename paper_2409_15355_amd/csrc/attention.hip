@@ -118,14 +118,38 @@ __device__ __forceinline__ Problem locate(const FinalBlocksMetaT<NP, NB> &m, int
   return pr;
 }
 
+// Chunks c and c + CPR / 2 of a row of keys, turned.  t: the pieces of the row's (cos, sin) that the two need -- interleaved pairs: pairs
+// 4 c .. 4 c + 3 lie in the first chunk, 4 (c + CPR / 2) .. in the other; half-split: element e of the one pairs with element e of
+// the other, pairs 8 c .. 8 c + 7.
+__device__ __forceinline__ void turn_chunks(const u32x4_t &a, const u32x4_t &b, const f32x4_t (&t)[4], bool halves, u32x4_t &ya, u32x4_t &yb) {
+  auto x_of = [](float x, float y, float c, float s) { return __builtin_fmaf(c, x, -(s * y)); };
+  auto y_of = [](float x, float y, float c, float s) { return __builtin_fmaf(s, x, c * y); };
+  if (!halves) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float ca = t[e / 2][(e & 1) * 2], sa = t[e / 2][(e & 1) * 2 + 1], cb = t[2 + e / 2][(e & 1) * 2], sb = t[2 + e / 2][(e & 1) * 2 + 1];
+      ya[e] = pack_bf16(x_of(bf16_lo(a[e]), bf16_hi(a[e]), ca, sa), y_of(bf16_lo(a[e]), bf16_hi(a[e]), ca, sa));
+      yb[e] = pack_bf16(x_of(bf16_lo(b[e]), bf16_hi(b[e]), cb, sb), y_of(bf16_lo(b[e]), bf16_hi(b[e]), cb, sb));
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a0 = bf16_lo(a[e]), a1 = bf16_hi(a[e]), b0 = bf16_lo(b[e]), b1 = bf16_hi(b[e]);
+      ya[e] = pack_bf16(x_of(a0, b0, t[e][0], t[e][1]), x_of(a1, b1, t[e][2], t[e][3]));
+      yb[e] = pack_bf16(y_of(a0, b0, t[e][0], t[e][1]), y_of(a1, b1, t[e][2], t[e][3]));
+    }
+  }
+}
 
 template <int D, typename Meta>
 __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta) {
   using G = Geo<D>;
   // context = table of cached blocks
   constexpr bool kBlocks = std::is_same<Meta, FinalBlocksMeta>::value || std::is_same<Meta, FinalBlocksMetaSmall>::value;
-  // context keys gathered, value rows through a table of where they lie (waves 4..7 keep their part of it in LDS)
-  constexpr bool kRows = std::is_same<Meta, FinalGatherMeta>::value;
+  // context keys gathered, value rows through a table of where they lie (the waves that copy keep their part of it in LDS)
+  // ... or keys and values through the table, the keys turned here
+  constexpr bool kTurn = std::is_same<Meta, FinalTurnMeta>::value;
+  constexpr bool kRows = std::is_same<Meta, FinalGatherMeta>::value || kTurn;
   // query rows and keys of the final block as the caller gave them
   constexpr bool kFresh = std::is_same<Meta, FinalFreshMeta>::value;
   constexpr bool kFinal = std::is_same<Meta, FinalMeta>::value || kBlocks || kRows || kFresh;
@@ -227,7 +251,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   const int64_t c_st = role_b ? p.vc_st : p.kc_st, c_sh = role_b ? p.vc_sh : p.kc_sh;
   const int64_t f_st = role_b ? p.vf_st : p.kf_st, f_sh = role_b ? p.vf_sh : p.kf_sh;
   const char *c_base = (const char *)(c_ptr + (int64_t)pr.ctx0 * c_st + (int64_t)kvh * c_sh);    // context segment
-  if constexpr (kRows) c_base = role_b ? (const char *)(c_ptr + (int64_t)kvh * c_sh) : c_base;   // (the table counts from the cache's first row)
+  if constexpr (kRows) c_base = role_b || kTurn ? (const char *)(c_ptr + (int64_t)kvh * c_sh) : c_base;   // (the table counts from the cache's first row)
   const char *f_base = (const char *)(f_ptr + (int64_t)pr.q_tok0 * f_st + (int64_t)kvh * f_sh);  // causal segment
   const uint32_t c_rb = (uint32_t)c_st * 2u, f_rb = (uint32_t)f_st * 2u;  // row strides, bytes
   // Full tiles of segments with the "primary" row stride (the context's if there is one, else the
@@ -245,7 +269,8 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   };
   uint32_t g_src[G::IPW];  // full per-lane byte offsets inside a full tile of primary stride
 #pragma unroll
-  for (int i = 0; i < G::IPW; ++i) g_src[i] = (uint32_t)copy_row(i) * prim_rb + copy_chunk(i);
+  for (int i = 0; i < G::IPW; ++i) g_src[i] = kTurn ? 0u : (uint32_t)copy_row(i) * prim_rb + copy_chunk(i);
+  // (with the table none but the few tiles of the final block itself would use them, and there are no registers for that)
   const uint32_t lds_copy =
       (uint32_t)(uintptr_t)smem + (role_b ? VBASE : 0u) + (wave & (kWaves / 2 - 1)) * G::IPW * 1024;
 
@@ -314,7 +339,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
     j.rb = c.seg >= n_ctx_segs ? f_rb : c_rb;
     j.ptr = c.base + (uint64_t)(uint32_t)c.ts * (uint64_t)(j.rb * (uint32_t)kTileKeys);
     j.valid = min(kTileKeys, c.len - c.ts * kTileKeys);
-    j.full = j.valid == kTileKeys && j.rb == prim_rb;
+    j.full = !kTurn && j.valid == kTileKeys && j.rb == prim_rb;
     return j;
   };
   auto copy_part = [&](const CopyJob &c, int i) __attribute__((always_inline)) {
@@ -331,8 +356,10 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   // ---- value rows through the table: a copying wave's RPW rows of every context tile of this split lie in LDS as
   //      byte offsets, 64 bytes a tile; a lane's chunk of a row is the same for all its pieces of a tile ---------------
   static_assert(!kRows || G::RPW == 16, "sixteen entries of a tile per copying wave");
-  constexpr uint32_t kTableW = kRowTableTiles * 64;  // a wave's part of the table
-  const uint32_t row_tab = (uint32_t)G::LDS + (uint32_t)(wave & (kWaves / 2 - 1)) * kTableW + (uint32_t)(lane / G::CPR) * 4;
+  // (a wave's part of the table)
+  uint32_t table_w = kRowTableTiles * 64;
+  if constexpr (kTurn) table_w = meta.blk_at / (kWaves / 2);
+  const uint32_t row_tab = (uint32_t)G::LDS + (uint32_t)(wave & (kWaves / 2 - 1)) * table_w + (uint32_t)(lane / G::CPR) * 4;
   uint32_t row_chunk = 0;
   if constexpr (kRows) row_chunk = copy_chunk(0);
   auto fetch_row_table = [&]() __attribute__((always_inline)) {
@@ -340,21 +367,78 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
       const int n_tab = min(t_end, n_ctx_tiles) - t_begin;
       for (int j = 0; j < n_tab; j += 16) {
         const uint32_t tile = (uint32_t)(t_begin + min(j + (lane >> 2), n_tab - 1));
-        lds_dma16((const char *)meta.rows,
-                  ((uint32_t)pr.ctx0 + tile * kTileKeys + (uint32_t)(wave & (kWaves / 2 - 1)) * G::RPW + (uint32_t)(lane & 3) * 4) * 4u,
-                  (uint32_t)(uintptr_t)smem + (uint32_t)G::LDS + (uint32_t)(wave & (kWaves / 2 - 1)) * kTableW + (uint32_t)j * 64);
+        const uint32_t from = ((uint32_t)pr.ctx0 + tile * kTileKeys + (uint32_t)(wave & (kWaves / 2 - 1)) * G::RPW + (uint32_t)(lane & 3) * 4) * 4u;
+        const uint32_t to = (uint32_t)(uintptr_t)smem + (uint32_t)G::LDS + (uint32_t)(wave & (kWaves / 2 - 1)) * table_w + (uint32_t)j * 64;
+        lds_dma16((const char *)meta.rows, from, to);
+        if constexpr (kTurn)
+          if (!role_b) lds_dma16((const char *)meta.blk, from, to + meta.blk_at);
       }
     }
   };
-  // copy of context tile ts (of this wave's kind: values) into buffer `buf`
+  // copy of context tile ts (of this wave's kind) into buffer `buf`
   auto copy_through_table = [&](int ts, int buf) __attribute__((always_inline)) {
     uint32_t off[G::IPW];
 #pragma unroll
     for (int u = 0; u < G::IPW; ++u)
       off[u] = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(
-                   smem + row_tab + (uint32_t)(ts - t_begin) * 64 + u * G::RPI * 4) + row_chunk;
+                   smem + row_tab + (uint32_t)(ts - t_begin) * 64 + u * G::RPI * 4) + (row_chunk ^ (kTurn && !role_b ? (uint32_t)u << 6 : 0u));
 #pragma unroll
     for (int u = 0; u < G::IPW; ++u) lds_dma16(c_base, off[u], lds_copy + (uint32_t)buf * TB + u * 1024);
+  };
+
+  // ---- keys of context tile ts in K buffer `buf`, turned by a wave that copies keys: the rows it has copied itself, so that all it
+  //      has to wait for is its own copy.  A lane takes 16-byte chunks c and c + CPR / 2 of a row (the pairs of either
+  //      layout); its row is a permutation of lane / (CPR / 2) that keeps a round of reads off each other's banks.  The products are
+  //      the re-encode kernels': the same bits as keys that were copied.  In place, in the softmax half of the tile before, by the waves
+  //      that copy keys: 0.2 to 0.3 us a tile, a workgroup of 512 blocks of 20 to 60 tokens, 32 over 8 heads of 128, walks ten.  That call
+  //      53.6 -> 44.4 us (gather and pre-pass 16 us -> tables and pre-pass 4), 30 drawn ones with 18 MB of keys and more 0.67 to 1.00, 0.84 in the mean --------
+  int blk_first = 0, blk_last = 0;  // the split's first block (row 0 of the rotations in LDS), its last
+  auto turn_tile = [&](int ts, int buf) __attribute__((always_inline)) {
+    if constexpr (kTurn) {
+      constexpr int HC = G::CPR / 2;
+      constexpr int STEPS = G::RPW * HC / 64;
+      typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+      typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
+      const bool halves = p.rope_layout != 0;
+      int ln = lane;  // (opaque: the addresses below are worked out for each tile, there is no register to keep them in)
+      asm volatile("" : "+v"(ln));
+      const int c = ln % HC;
+      const uint32_t idx_at = (uint32_t)G::LDS + meta.blk_at + (uint32_t)wave * table_w + (uint32_t)(ts - t_begin) * 64;
+      uint32_t blk[STEPS], at[STEPS];
+      uint32_t seen_plain = kTurnPlain;
+#pragma unroll
+      for (int u = 0; u < STEPS; ++u) {
+        const int l = u * (64 / HC) + ln / HC;
+        const int r = (l & 1) | ((l >> 2) & 1) << 1 | ((l >> 3) & 1) << 2 | ((l >> 1) & 1) << 3;
+        blk[u] = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(smem + idx_at + r * 4);
+        const int row = wave * G::RPW + r, swz = (row / G::LPR) & (G::CPR - 1);
+        at[u] = (uint32_t)buf * TB + (uint32_t)row * G::ROWB + (uint32_t)((c ^ swz) << 4);  // (chunk c + HC: HC << 4 flipped)
+        seen_plain &= blk[u];
+      }
+      if (__builtin_amdgcn_ballot_w64(seen_plain == 0) == 0) return;  // none of the rows moves
+      f32x4_t cs[4];
+#pragma unroll
+      for (int u = 0; u < STEPS; ++u) {
+        if (u == 0 || __builtin_amdgcn_ballot_w64(blk[u] != blk[0]) != 0) {
+          const uint32_t row = (uint32_t)G::LDS + meta.rot_at + ((blk[u] & ~kTurnPlain) - (uint32_t)blk_first) * (D * 4);
+#pragma unroll
+          for (int h = 0; h < 4; ++h)
+            cs[h] = *(const lds_f32x4 *)(smem + row + (uint32_t)((halves ? c * 4 + h : (h < 2 ? c * 2 + h : (c + HC) * 2 + h - 2)) << 4));
+        }
+        const u32x4_t xa = *(const lds_u32x4 *)(smem + at[u]), xb = *(const lds_u32x4 *)(smem + (at[u] ^ (HC << 4)));
+        u32x4_t ya, yb;
+        turn_chunks(xa, xb, cs, halves, ya, yb);
+        const bool plain = (blk[u] & kTurnPlain) != 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ya[e] = plain ? xa[e] : ya[e];
+          yb[e] = plain ? xb[e] : yb[e];
+        }
+        *(lds_u32x4 *)(smem + at[u]) = ya;
+        *(lds_u32x4 *)(smem + (at[u] ^ (HC << 4))) = yb;
+      }
+      lds_wait();  // (published by the barrier that follows)
+    }
   };
 
   // ---- running state -----------------------------------------------------------------------------
@@ -368,8 +452,9 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   // start from.  Kept (not rebuilt from mb by sixteen moves inside every MFMA block, where each vector
   // instruction of this wave delays the next MFMA) and rebuilt only when the reference moves.
   // (not with a block table: kept across the reloads of the query fragments they would spill, and kept but made again
-  // behind each reload they gained nothing: 31 cached blocks of 1,024 tokens 135.4 us against 135.9, less than runs differ)
-  constexpr bool kKeepNegmb = !kBlocks;
+  // behind each reload they gained nothing: 31 cached blocks of 1,024 tokens 135.4 us against 135.9, less than runs differ; nor where the
+  // keys are turned, whose addresses would go to scratch)
+  constexpr bool kKeepNegmb = !kBlocks && !kTurn;
   f32x16_t negmb;
   auto set_negmb = [&]() __attribute__((always_inline)) {
     if constexpr (kKeepNegmb) {
@@ -583,7 +668,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   const char *cp_ptr = nullptr;    // where the tile after the last copied one starts (same segment)
   auto first_copy = [&](int j) __attribute__((always_inline)) {  // tile j = 0, 1, 2 of the walk, before the loop
     if constexpr (kRows)
-      if (role_b && j < n_t && cp.seg < n_ctx_segs) {
+      if ((role_b || kTurn) && j < n_t && cp.seg < n_ctx_segs) {
         copy_through_table(cp.ts, j);
         advance(cp);
         return;
@@ -591,7 +676,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
     if (j < n_t) {
       // (as in the loop: a full tile that follows the last copied one in memory needs the pointer only)
       const uint32_t rb = cp.seg >= n_ctx_segs ? f_rb : c_rb;
-      if (j > 0 && cp.ts > 0 && rb == prim_rb && (cp.ts + 1) * kTileKeys <= cp.len) {
+      if (!kTurn && j > 0 && cp.ts > 0 && rb == prim_rb && (cp.ts + 1) * kTileKeys <= cp.len) {
         const uint32_t dst = lds_copy + (uint32_t)j * TB;
 #pragma unroll
         for (int i = 0; i < G::IPW; ++i) lds_dma16(cp_ptr, g_src[i], dst + i * 1024);
@@ -613,7 +698,15 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   // and the first exponentials are worked out (the loop's own waits cover them, as every later tile).
   // (values through the table: the table is asked for here, tile 0 of them once it has landed)
   if constexpr (kRows) {
-    if (role_b) fetch_row_table(); else first_copy(0);
+    if (role_b || kTurn) fetch_row_table(); else first_copy(0);
+    if constexpr (kTurn) {
+      const int n_tab = min(t_end, n_ctx_tiles) - t_begin;
+      const uint32_t first_row = (uint32_t)pr.ctx0 + (uint32_t)t_begin * kTileKeys;
+      if (n_tab > 0) {
+        blk_first = (int)(meta.blk[first_row] & ~kTurnPlain);
+        blk_last = (int)(meta.blk[first_row + (uint32_t)n_tab * kTileKeys - 1] & ~kTurnPlain);
+      }
+    }
   } else {
     first_copy(0);
   }
@@ -846,28 +939,11 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
       if (has_keys) {  // (the whole workgroup or none of it)
         u32x4_t ya, yb;
         if (turns_keys) {
-          if (!halves) {
-            // chunk c holds pairs 4 c .. 4 c + 3
+          f32x4_t ct[4];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const f32x4_t ta = *(const lds_f32x4 *)(smem + piece(k_tok, k_c * 2 + h)), tb = *(const lds_f32x4 *)(smem + piece(k_tok, (k_c + HC) * 2 + h));
-#pragma unroll
-              for (int e = 0; e < 2; ++e) {
-                const float ax = bf16_lo(ka[2 * h + e]), ay = bf16_hi(ka[2 * h + e]), bx = bf16_lo(kb[2 * h + e]), by = bf16_hi(kb[2 * h + e]);
-                ya[2 * h + e] = pack_bf16(__builtin_fmaf(ta[2 * e], ax, -(ta[2 * e + 1] * ay)), __builtin_fmaf(ta[2 * e + 1], ax, ta[2 * e] * ay));
-                yb[2 * h + e] = pack_bf16(__builtin_fmaf(tb[2 * e], bx, -(tb[2 * e + 1] * by)), __builtin_fmaf(tb[2 * e + 1], bx, tb[2 * e] * by));
-              }
-            }
-          } else {
-            // element e of chunk c pairs with element e of chunk c + CPR / 2: pairs 8 c .. 8 c + 7
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const f32x4_t t = *(const lds_f32x4 *)(smem + piece(k_tok, k_c * 4 + e));
-              const float a0 = bf16_lo(ka[e]), a1 = bf16_hi(ka[e]), b0 = bf16_lo(kb[e]), b1 = bf16_hi(kb[e]);
-              ya[e] = pack_bf16(__builtin_fmaf(t[0], a0, -(t[1] * b0)), __builtin_fmaf(t[2], a1, -(t[3] * b1)));
-              yb[e] = pack_bf16(__builtin_fmaf(t[1], a0, t[0] * b0), __builtin_fmaf(t[3], a1, t[2] * b1));
-            }
-          }
+          for (int h = 0; h < 4; ++h)
+            ct[h] = *(const lds_f32x4 *)(smem + piece(k_tok, halves ? k_c * 4 + h : (h < 2 ? k_c * 2 + h : (k_c + HC) * 2 + h - 2)));
+          turn_chunks(ka, kb, ct, halves, ya, yb);
         }
         lds_wait();
         wg_barrier();  // nobody reads the table any more
@@ -899,7 +975,22 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
     dma_wait<0>();
   }
   if constexpr (kRows)
-    if (role_b) first_copy(0);  // (into V buffer 0: the query rows' slices lie in buffers 1 and 2)
+    if (role_b || kTurn) first_copy(0);  // (into buffer 0: the query rows' slices lie in buffers 1 and 2)
+  if constexpr (kTurn) {
+    // the rotations of the split's blocks, whole rows of the table, 1 KB per wave instruction (the table ends on a whole one)
+    const int n_tab = min(t_end, n_ctx_tiles) - t_begin;  // (the same in all waves)
+    if (n_tab > 0) {
+      const int n_kb = ((blk_last + 1 - blk_first) * (D * 4) + 1023) / 1024;
+      for (int j = wave; j < n_kb; j += kWaves)  // (asked for next to tile 0)
+        lds_dma16((const char *)(meta.rot + (int64_t)blk_first * D), (uint32_t)(j * 1024 + lane * 16),
+                  (uint32_t)(uintptr_t)smem + (uint32_t)G::LDS + meta.rot_at + (uint32_t)j * 1024);
+      dma_wait<0>();
+      wg_barrier();
+      if (!role_b) turn_tile(t_begin, 0);
+    } else {
+      dma_wait<0>();  // (tile 0, a tile of the final block itself: published by the walk's first barrier)
+    }
+  }
   probe_mark(6);
   f32x16_t sacc[2];
   bf16x8_t pf[4];
@@ -948,7 +1039,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
       // that ended at or before that barrier for every wave).
       const bool copy = steady || i + 3 < n_t;
       bool through_table = false;
-      if constexpr (kRows) through_table = role_b && cp.seg < n_ctx_segs;
+      if constexpr (kRows) through_table = (role_b || kTurn) && ((kTurn && steady) || cp.seg < n_ctx_segs);
       if (kRows && copy && through_table) {
         if constexpr (kRows) {
           copy_through_table(cp.ts, (i + 3) & (kNumVBuf - 1));
@@ -965,7 +1056,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
 #pragma unroll
         for (int u = 0; u < G::IPW; ++u) cp_off[u] = g_src[u];
         const uint32_t rb = cp.seg >= n_ctx_segs ? f_rb : c_rb;
-        if (steady || (cp.ts > 0 && rb == prim_rb && (cp.ts + 1) * kTileKeys <= cp.len)) {
+        if (!kTurn && (steady || (cp.ts > 0 && rb == prim_rb && (cp.ts + 1) * kTileKeys <= cp.len))) {
           cp_ptr += tile_bytes;
         } else {
           asm volatile("" ::: "memory");
@@ -986,6 +1077,8 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
       if (steady || copy) dma_wait<2 * G::IPW>();
       else if (i + 2 < n_t) dma_wait<G::IPW>();
       else dma_wait<0>();
+      if constexpr (kTurn)
+        if (!role_b && (steady || i + 1 < n_t) && cm.seg < n_ctx_segs && cm.rem > 1) turn_tile(cm.ts + 1, (i + 1) & (kNumKBuf - 1));
       const uint32_t vofs = VBASE + (i & (kNumVBuf - 1)) * TB;
       if (wave_has_rows) preload(vofs, fr);
       wg_barrier();
@@ -1010,6 +1103,8 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
       const int full_tiles = cp.len / kTileKeys;  // of the segment the copy cursor is in
       const bool fast = (cp.seg >= n_ctx_segs ? f_rb : c_rb) == prim_rb && cp.ts > 0;
       n_steady = fast ? max(0, min(min(n_t - 3, full_tiles - cp.ts), cm.rem - 1)) : 0;
+      // (through the table any tile of the context is a full one)
+      if constexpr (kTurn) n_steady = cp.seg < n_ctx_segs ? max(0, min(min(n_t - 3, cp.rem), cm.rem - 1)) : 0;
     }
     int i = 0;
 #pragma unroll 1
@@ -1286,7 +1381,8 @@ hipError_t launch_attn_t(const AttnParams &p, const Meta &meta, hipStream_t stre
   if (n_wg == 0) return hipSuccess;
   if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
   constexpr size_t lds = Geo<D>::LDS + (std::is_same<Meta, FinalGatherMeta>::value ? (size_t)kWaves / 2 * kRowTableTiles * 64 : 0) +
-                         (std::is_same<Meta, FinalFreshMeta>::value ? (size_t)kFreshTokens * D * 4 : 0);
+                         (std::is_same<Meta, FinalFreshMeta>::value ? (size_t)kFreshTokens * D * 4 : 0) +
+                         (std::is_same<Meta, FinalTurnMeta>::value ? (size_t)kTurnLds : 0);
   static_assert((size_t)kWaves * 32 * D * 2 <= lds, "epilogue staging must fit the tile buffers");
   static_assert(lds <= 160 * 1024, "gfx950 has 160 KB of LDS per workgroup");
   // more than 64 KB of dynamic LDS has to be asked for once per kernel (setting it twice, from two
@@ -1334,6 +1430,12 @@ hipError_t launch_attn_final_fresh(const AttnParams &p, const FinalFreshMeta &me
 hipError_t launch_attn_final_gathered(const AttnParams &p, const FinalGatherMeta &meta, hipStream_t stream) {
   if (p.head_dim == 128) return launch_attn_t<128, FinalGatherMeta>(p, meta, stream);
   if (p.head_dim == 64) return launch_attn_t<64, FinalGatherMeta>(p, meta, stream);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_attn_final_turned(const AttnParams &p, const FinalTurnMeta &meta, hipStream_t stream) {
+  if (p.head_dim == 128) return launch_attn_t<128, FinalTurnMeta>(p, meta, stream);
+  if (p.head_dim == 64) return launch_attn_t<64, FinalTurnMeta>(p, meta, stream);
   return hipErrorInvalidValue;
 }
 

@@ -250,18 +250,18 @@ int32_t run_rope_prepass(const ba_heads *h, const ba::RopeTable &rt, const ba_te
 }
 
 
-// Whether rotated keys of rows [t0, t1) go where the gather reads (a slot of the cache used again for the query block's
-// keys): the gather has to be done first then.  By whole rows: heads far apart count as touching where nothing is shared.
-static bool writes_gathered_rows(const Gather &g, const ba_tensor *k_rot, int64_t t0, int64_t t1) {
+// Whether rows [t0, t1) of a tensor that the call writes lie where the gather reads (rotated keys: a slot of the cache used again
+// for the query block's keys): the gather has to be done first then.  By whole rows: heads far apart count as touching where nothing is shared.
+bool writes_gathered_rows(const Gather &g, const ba_tensor *k_rot, int n_heads, int64_t t0, int64_t t1) {
   const auto row = [&](const void *base, int64_t st, int64_t t) { return (uintptr_t)base + (uintptr_t)(t * st * 2); };
-  const auto row_bytes = [&](int64_t sh) { return (uintptr_t)((g.p.n_kv_heads - 1) * sh + g.p.head_dim) * 2; };
+  const auto row_bytes = [&](int64_t sh, int heads) { return (uintptr_t)((heads - 1) * sh + g.p.head_dim) * 2; };
   const uintptr_t lo = row(k_rot->ptr, k_rot->stride_tok, t0);
-  const uintptr_t hi = row(k_rot->ptr, k_rot->stride_tok, t1 - 1) + row_bytes(k_rot->stride_head);
+  const uintptr_t hi = row(k_rot->ptr, k_rot->stride_tok, t1 - 1) + row_bytes(k_rot->stride_head, n_heads);
   for (int layer = 0; layer < g.p.n_layers; ++layer) {
     const char *base = (const char *)g.p.src + layer * g.p.src_sl * 2;
     for (int b = 0; b < g.n_blocks; ++b)
       if (row(base, g.p.src_st, g.src_off[b]) < hi &&
-          lo < row(base, g.p.src_st, (int64_t)g.src_off[b] + g.len[b] - 1) + row_bytes(g.p.src_sh))
+          lo < row(base, g.p.src_st, (int64_t)g.src_off[b] + g.len[b] - 1) + row_bytes(g.p.src_sh, g.p.n_kv_heads))
         return true;
   }
   return false;
@@ -287,6 +287,21 @@ static int32_t run_gather_prepass_t(Params gp, const Gather &g, const ba::RopePr
   if (e != hipSuccess) return device_fail(e, "gather launch");
   return BA_OK;
 }
+// The tables of a context that is not copied, and the pre-pass.
+template <typename Blocks>
+static int32_t run_turn_tables(const Gather &g, const ba::RopePrepassParams &pp, const ba::RopeSegsGather &segs, const ba::RopeTable &rt,
+                               hipStream_t stream) {
+  std::vector<Blocks> tab(1);
+  ba::ReencParams plain = g.p;
+  fill_blocks(&plain, &tab[0], g.n_blocks, 0, g.n_blocks, 0, g.src_off, g.dst_off, g.len, g.pos_old, g.pos_new);
+  hipError_t e;
+  {
+    ProfileScope ps(BA_PROFILE_REENCODE, stream);
+    e = ba::launch_turn_tables(g.turned, tab[0], pp, segs, rt, stream);
+  }
+  if (e != hipSuccess) return device_fail(e, "block tables launch");
+  return BA_OK;
+}
 static int32_t run_gather_prepass(const ba_heads *h, const Gather &g, const ba::RopeTable &rt, const ba_tensor *q, uint16_t *q_rot,
                                   const ba_tensor *k, const ba_tensor *k_rot, int n, const int32_t *start, const int32_t *pos0,
                                   hipStream_t stream) {
@@ -294,8 +309,11 @@ static int32_t run_gather_prepass(const ba_heads *h, const Gather &g, const ba::
   ba::RopeSegsGather segs;
   fill_segments(&segs, n, start, pos0);
   const ba::ReencParams &plain = g.p;
-  bool apart = writes_gathered_rows(g, k_rot, start[0], start[n]);
+  bool apart = !g.turn && writes_gathered_rows(g, k_rot, g.p.n_kv_heads, start[0], start[n]);
   int32_t rc;
+  if (g.turn)
+    return g.n_blocks <= ba::kReencMaxBlocks ? run_turn_tables<ba::ReencBlocks>(g, pp, segs, rt, stream)
+                                             : run_turn_tables<ba::ReencBlocksLarge>(g, pp, segs, rt, stream);
   if (g.n_blocks <= ba::kReencMaxBlocks)
     rc = g.p.row_table ? run_gather_prepass_t<ba::ReencBlocks>(g.p, g, pp, segs, rt, &apart, stream)
                        : run_gather_prepass_t<ba::ReencBlocks>(plain, g, pp, segs, rt, &apart, stream);
@@ -493,7 +511,18 @@ int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor
     hipError_t e;
     {
       ProfileScope ps(BA_PROFILE_ATTENTION, stream);
-      if (gather && gather->p.row_table) {  // (one launch: the caller's check)
+      if (gather && gather->turn) {  // (one launch: the caller's check)
+        ba::FinalTurnMeta tm;
+        memset(&tm, 0, sizeof(tm));
+        static_cast<ba::FinalMeta &>(tm) = meta;
+        tm.rows = gather->turned.rows;
+        for (int i = 0; i < n; ++i) tm.ctx0[i] = gather->ctx0[i];
+        tm.blk = gather->turned.blk;
+        tm.rot = gather->turned.rot;
+        tm.blk_at = gather->blk_at;
+        tm.rot_at = gather->rot_at;
+        e = ba::launch_attn_final_turned(ap, tm, stream);
+      } else if (gather && gather->p.row_table) {  // (likewise)
         ba::FinalGatherMeta gm;
         memset(&gm, 0, sizeof(gm));
         static_cast<ba::FinalMeta &>(gm) = meta;

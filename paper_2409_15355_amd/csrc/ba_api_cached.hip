@@ -114,6 +114,36 @@ int32_t run_final_blocks(const BlocksCall &c, ba::AttnParams ap) {
   return BA_OK;
 }
 
+// Where a split's part of the tables of FinalTurnMeta lies in LDS, and whether it fits: the longest split's tiles (tables are fetched
+// sixteen tiles at a time), the rotations of the blocks that the most mixed one meets.
+bool turn_layout(const ba_heads *h, int32_t n_prompts, const int32_t *cu_q, const int32_t *cu_ctx, const int32_t *ctx0,
+                 const std::vector<int32_t> &first_row, int n_splits, uint32_t *blk_at, uint32_t *rot_at) {
+  const int G = h->n_q_heads / h->n_kv_heads;
+  int most_tiles = 1, most_blocks = 1;
+  const auto block_of = [&](int64_t row) { return (int)(std::upper_bound(first_row.begin(), first_row.end(), (int32_t)row) - first_row.begin()) - 1; };
+  for (int n = 0; n < n_prompts; ++n) {
+    const int ctx_tiles = (cu_ctx[n + 1] - cu_ctx[n] + ba::kTileKeys - 1) / ba::kTileKeys;
+    const int64_t n_rows = (int64_t)(cu_q[n + 1] - cu_q[n]) * G;
+    for (int64_t row0 = 0; row0 < n_rows; row0 += ba::kTileRows) {
+      const int causal = ba::causal_key_tiles((int)((std::min(n_rows, row0 + ba::kTileRows) - 1) / G), ba::kTileKeys);
+      for (int s = 0; s < n_splits; ++s) {
+        const ba::TileRange r = ba::split_tile_range(ctx_tiles, causal, n_splits, s);
+        const int end = std::min(r.end, ctx_tiles);
+        if (end <= r.begin) continue;
+        most_tiles = std::max(most_tiles, end - r.begin);
+        most_blocks = std::max(most_blocks, block_of((int64_t)ctx0[n] + (int64_t)end * ba::kTileKeys - 1) -
+                                                block_of((int64_t)ctx0[n] + (int64_t)r.begin * ba::kTileKeys) + 1);
+      }
+    }
+  }
+  const int64_t table = (int64_t)(most_tiles + 15) / 16 * 16 * ba::kTileKeys * 4;  // of either table
+  const int64_t rots = ((int64_t)most_blocks * h->head_dim * 4 + 1023) / 1024 * 1024;
+  if (2 * table + rots > (int64_t)ba::kTurnLds) return false;
+  *blk_at = (uint32_t)table;
+  *rot_at = (uint32_t)(2 * table);
+  return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -200,22 +230,9 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
     }
     for (int b = 0; b < nb; ++b) reach = std::max<int64_t>(reach, (int64_t)src[b] + len[b]);
     const size_t table_at = align256((size_t)padded * row_b);
-    const bool table = n_prompts <= ba::kFinMaxPrompts && !heads->xcd_speed && nb <= ba::kRowTableBlocks &&
-        (size_t)pl.cu_ctx[n_prompts] * row_b >= ba::kRowTableBytes && (fp.max_nt + fp.max_nt / (2 * fp.n_splits)) / fp.n_splits + 2 <= ba::kRowTableTiles &&
-        reach * v_cache->stride_tok * 2 < ((int64_t)1 << 32) - 65536 &&
-        table_at + (size_t)padded * 4 <= 2 * align256(pl.gather_kv_bytes);
+    const bool rows32 = n_prompts <= ba::kFinMaxPrompts && !heads->xcd_speed && reach * v_cache->stride_tok * 2 < ((int64_t)1 << 32) - 65536;
+    const size_t ctx_bytes = (size_t)pl.cu_ctx[n_prompts] * row_b;
     void *const ws_final = (char *)ws + 2 * align256(pl.gather_kv_bytes);
-    if (!table && (k_cache->stride_tok != v_cache->stride_tok || k_cache->stride_head != v_cache->stride_head)) {
-      if ((rc = ba_reencode_positions(heads, k_cache, &kg, 1, 0, 0, nb, src.data(), dst.data(), len.data(), oldp.data(),
-                                      newp.data(), BA_REENC_SHIFT, stream_)))
-        return rc;
-      // (a shift of zero positions is a plain copy)
-      if ((rc = ba_reencode_positions(heads, v_cache, &vg, 1, 0, 0, nb, src.data(), dst.data(), len.data(), zero.data(),
-                                      zero.data(), BA_REENC_SHIFT, stream_)))
-        return rc;
-      return ba_final_block_attention(heads, q_f, &kg, &vg, k_f, v_f, o_out, k_f_rot_out, n_prompts, cu_q, pl.cu_ctx.data(), q_pos0,
-                                      BA_ROPE_APPLY, ws_final, pl.gather_final_bytes, stream_);
-    }
     Gather g;
     memset(&g, 0, sizeof(g));
     g.p.src = k_cache->ptr;
@@ -229,16 +246,55 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
     g.p.dtype = BA_DTYPE_BF16;
     g.p.layout = heads->rope_layout;
     g.p.mode = BA_REENC_SHIFT;
-    if (table) {
+    g.p.n_layers = 1;
+    g.p.row_bytes = (uint32_t)(v_cache->stride_tok * 2);
+    g.p.table_end = (int32_t)padded;
+    g.ctx0 = ctx0.data();
+    const auto padded_rows = [&]() {  // the blocks' places with every prompt on a whole tile
       int at = 0;
       for (int n = 0; n < n_prompts; ++n)
         for (; at < nb && dst[at] < pl.cu_ctx[n + 1]; ++at) dst[at] += ctx0[n] - pl.cu_ctx[n];
-      g.p.n_layers = 1;
+    };
+    // Nothing is copied at all where the attention kernel can turn the keys as they arrive: one stride for keys and values, so that
+    // one table serves both, tables and rotations of a split's blocks in LDS, and nothing written that the walk still reads.
+    if (rows32 && nb <= ba::kReencMaxBlocksLarge && ctx_bytes >= ba::kTurnBytes + ba::kTurnBytesTile * (size_t)fp.total_tiles / (size_t)n_prompts &&
+        k_cache->stride_tok == v_cache->stride_tok &&
+        2 * align256((size_t)padded * 4) + (size_t)nb * D * 4 + 1024 <= 2 * align256(pl.gather_kv_bytes)) {
+      const std::vector<int32_t> close = dst;
+      padded_rows();
+      g.n_blocks = nb;
+      g.src_off = src.data(), g.dst_off = dst.data(), g.len = len.data(), g.pos_old = oldp.data(), g.pos_new = newp.data();
+      if (turn_layout(heads, n_prompts, cu_q, pl.cu_ctx.data(), ctx0.data(), dst, fp.n_splits, &g.blk_at, &g.rot_at) &&
+          !writes_gathered_rows(g, o_out, heads->n_q_heads, cu_q[0], cu_q[n_prompts]) &&
+          !(k_f_rot_out && writes_gathered_rows(g, k_f_rot_out, heads->n_kv_heads, cu_q[0], cu_q[n_prompts]))) {
+        g.turn = true;
+        g.turned.rows = (uint32_t *)ws;
+        g.turned.blk = (uint32_t *)((char *)ws + align256((size_t)padded * 4));
+        g.turned.rot = (float *)((char *)ws + 2 * align256((size_t)padded * 4));
+        g.turned.row_bytes = g.p.row_bytes;
+        g.turned.table_end = (int32_t)padded;
+        return final_block(heads, q_f, k_cache, v_cache, k_f, v_f, o_out, k_f_rot_out, n_prompts, cu_q, pl.cu_ctx.data(),
+                           q_pos0, BA_ROPE_APPLY, ws_final, pl.gather_final_bytes, stream_, &g);
+      }
+      dst = close;
+    }
+    const bool table = rows32 && nb <= ba::kRowTableBlocks && ctx_bytes >= ba::kRowTableBytes && (fp.max_nt + fp.max_nt / (2 * fp.n_splits)) / fp.n_splits + 2 <= ba::kRowTableTiles &&
+        table_at + (size_t)padded * 4 <= 2 * align256(pl.gather_kv_bytes);
+    if (!table && (k_cache->stride_tok != v_cache->stride_tok || k_cache->stride_head != v_cache->stride_head)) {
+      if ((rc = ba_reencode_positions(heads, k_cache, &kg, 1, 0, 0, nb, src.data(), dst.data(), len.data(), oldp.data(),
+                                      newp.data(), BA_REENC_SHIFT, stream_)))
+        return rc;
+      // (a shift of zero positions is a plain copy)
+      if ((rc = ba_reencode_positions(heads, v_cache, &vg, 1, 0, 0, nb, src.data(), dst.data(), len.data(), zero.data(),
+                                      zero.data(), BA_REENC_SHIFT, stream_)))
+        return rc;
+      return ba_final_block_attention(heads, q_f, &kg, &vg, k_f, v_f, o_out, k_f_rot_out, n_prompts, cu_q, pl.cu_ctx.data(), q_pos0,
+                                      BA_ROPE_APPLY, ws_final, pl.gather_final_bytes, stream_);
+    }
+    if (table) {
+      padded_rows();
       g.p.copy_from_layer = 0x7fffffff;
       g.p.row_table = (uint32_t *)((char *)ws + table_at);
-      g.p.row_bytes = (uint32_t)(v_cache->stride_tok * 2);
-      g.p.table_end = (int32_t)padded;
-      g.ctx0 = ctx0.data();
     } else {
       // One launch for both: the values ride along as a second "layer" of the key cache (the layer
       // strides are the distances between the two tensors) that is copied, not rotated.

@@ -91,7 +91,12 @@ struct Gather {
   const int32_t *ctx0;  // with a table: prompt n's keys from row ctx0[n] of k_ctx on (FinalGatherMeta)
   int n_blocks;         // the last of them, at most kReencMaxBlocksLarge (the others: launches before)
   const int32_t *src_off, *dst_off, *len, *pos_old, *pos_new;
+  // nothing is copied, the attention kernel turns the keys (p.row_table and p.dst unused)
+  bool turn;
+  ba::TurnTables turned;
+  uint32_t blk_at, rot_at;  // of FinalTurnMeta
 };
+bool writes_gathered_rows(const Gather &g, const ba_tensor *k_rot, int n_heads, int64_t t0, int64_t t1);
 // ba_final_block_attention, its context gathered first if so asked
 int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,
                     const ba_tensor *k_f, const ba_tensor *v_f, const ba_tensor *o_out, const ba_tensor *k_f_rot_out,

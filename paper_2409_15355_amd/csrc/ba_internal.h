@@ -359,6 +359,33 @@ struct FinalGatherMeta : FinalMeta {
   const uint32_t *rows;
 };
 
+// Final block over short cached blocks none of which is copied: keys and values are fetched through the table of rows (one
+// stride for both), and the attention kernel turns a tile's keys in LDS by the shift of the block they belong to: blk[] names it
+// for every entry of rows[], a row of rot = (cos, sin) of the shift per frequency.  LDS behind the tile buffers: a split's
+// part of rows[], from blk_at on its part of blk[], from rot_at on the rotations of its blocks.
+// Saved: the keys' way out to memory and back (84 of 168 MB for 20,000 tokens of 8 heads of 128; the gather took 16 us of 54).
+// Paid: 2 to 3 us of start-up (table, then first tile and rotations, then the turning of it, one behind the other) and
+// 0.2 to 0.3 us a key tile, by every row tile anew.  So for contexts of kTurnBytes of keys and kTurnBytesTile more for each row tile that
+// a prompt has in the mean.  Copied / turned, 32 over 8 heads of 128, blocks of 40 to 200: one row tile, 8 MB 22.2 / 24.5 us, 16 MB
+// 30.1 / 31.2, 20 MB 33.9 / 30.8, 33 MB 44.0 / 35.5, 40 MB 49.8 / 41.3, 60 MB 64.2 / 51.1; two, 16 MB 34.7 / 36.7, 20 MB 41.2 / 40.8, 33 MB 56.6 / 53.2,
+// 50 MB 73.5 / 70.1; four, 33 MB 85.7 / 85.4, 40 MB 102.9 / 109.2.  8 over 2 heads of 64: four, 8 MB 35.7 / 40.7.  One block of 3,000 among 500 of 30:
+// 59.1 / 34.0.
+constexpr size_t kTurnBytes = (size_t)12 << 20, kTurnBytesTile = (size_t)9 << 20;
+constexpr uint32_t kTurnLds = 32 * 1024;
+constexpr uint32_t kTurnPlain = 0x80000000u;  // in blk[]: a shift of zero, the key stays as it is
+struct FinalTurnMeta : FinalGatherMeta {
+  const uint32_t *blk;
+  const float *rot;
+  uint32_t blk_at, rot_at;
+};
+// What the tables are written from: shift of block b = blocks.pos_new[b] - blocks.pos_old[b].
+struct TurnTables {
+  uint32_t *rows, *blk;
+  float *rot;          // [blocks.n][head_dim / 2][2]
+  uint32_t row_bytes;  // of the caches
+  int32_t table_end;   // as in ReencRowsParams
+};
+
 // Final block whose query rows and keys are as the caller gave them: no RoPE pre-pass has run, the kernel turns them itself
 // (see attn_kernel).  Every prompt has one row tile and one key tile of its own.
 constexpr int kFreshTokens = kTileKeys;
@@ -419,6 +446,11 @@ hipError_t launch_attn_final_blocks(const AttnParams &p, const FinalBlocksMetaSm
 hipError_t launch_attn_final(const AttnParams &p, const FinalMeta &meta, hipStream_t stream);
 hipError_t launch_attn_final_fresh(const AttnParams &p, const FinalFreshMeta &meta, hipStream_t stream);
 hipError_t launch_attn_final_gathered(const AttnParams &p, const FinalGatherMeta &meta, hipStream_t stream);
+hipError_t launch_attn_final_turned(const AttnParams &p, const FinalTurnMeta &meta, hipStream_t stream);
+// the tables of FinalTurnMeta, and the pre-pass of the query block's rows as in launch_gather_prepass
+template <typename Blocks>
+hipError_t launch_turn_tables(const TurnTables &t, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
+                              const RopeTable &rt, hipStream_t stream);
 // Merge the split-KV partials of all p.part_units units into the bf16 output.
 hipError_t launch_combine(const AttnParams &p, hipStream_t stream);
 

@@ -7,8 +7,10 @@
 // The gather is bound by memory and by how fast it gets going.  What it writes is read by the next kernel and what it
 // reads may still be in the caches, so neither goes past them, and a thread moves two pieces, not eight (four times the
 // workgroups): 512 blocks of 20 to 60 tokens, 32 over 8 heads of 128, 42 MB in and out: the call 61.7 -> 54.3 us (57.7 -> 46.6 on
-// one cache over and over).  (On one box, where two pieces took 52.1: four 56, with the hint 59; one piece 50, at twice the
-// workgroups where block lengths differ.)
+// one cache over and over; contexts of that size are mostly not copied any more, see FinalTurnMeta).  (On one box, where two
+// pieces took 52.1: four 56, with the hint 59; one piece 50, at twice the workgroups where block lengths differ.)
+#include <string.h>
+
 #include "ba_rotate.h"
 #include "ba_schedule.h"
 
@@ -86,7 +88,60 @@ hipError_t launch_d(const Params &gp, const Blocks &blocks, const RopePrepassPar
   return is_runs(gp) ? launch_t<D, 0, true>(gp, blocks, pp, segs, rt, stream) : launch_t<D, 0, false>(gp, blocks, pp, segs, rt, stream);
 }
 
+// The tables with which the attention kernel fetches and turns the cached keys itself (FinalTurnMeta), a workgroup per block, next to
+// the pre-pass.  A few hundred kilobytes at most: latency.
+template <int D, int LAYOUT, typename Blocks>
+__global__ __launch_bounds__(kRotThreads) void turn_tables_kernel(TurnTables tt, Blocks blocks, RopePrepassParams pp,
+                                                                  RopeSegsGather segs, RopeTable rt, GatherGrid g) {
+  if (blockIdx.x < g.n_pre) {
+    const uint32_t by = fast_div(blockIdx.x, g.pre_div);
+    rope_prepass_rows<D, LAYOUT>(pp, segs, rt, (int)(blockIdx.x - by * g.pre_x), (int)by);
+    return;
+  }
+  const int b = (int)(blockIdx.x - g.n_pre);
+  const int len = blocks.len[b], at = blocks.dst_off[b], src = blocks.src_off[b];
+  const int next = b + 1 < blocks.n ? blocks.dst_off[b + 1] : tt.table_end;
+  const int shift = blocks.pos_new[b] - blocks.pos_old[b];
+  for (int u = threadIdx.x; u < next - at; u += kRotThreads) {
+    tt.rows[at + u] = (uint32_t)(src + min(u, len - 1)) * tt.row_bytes;
+    tt.blk[at + u] = (uint32_t)b | (shift == 0 ? kTurnPlain : 0u);
+  }
+  if ((int)threadIdx.x < D / 2) {
+    float c, s;
+    sincos_phase(rope_phase(shift, rt.turns[threadIdx.x]), c, s);
+    reinterpret_cast<float2 *>(tt.rot)[b * (D / 2) + (int)threadIdx.x] = make_float2(c, s);
+  }
+}
+
+template <int D, typename Blocks>
+hipError_t launch_turn_d(const TurnTables &tt, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
+                         const RopeTable &rt, hipStream_t stream) {
+  constexpr int TPP = kRotThreads / (D / 16);
+  GatherGrid g;
+  memset(&g, 0, sizeof(g));
+  g.pre_x = (uint32_t)(((int64_t)segs.start[segs.n] - segs.start[0] + TPP - 1) / TPP);
+  if (g.pre_x == 0) return hipErrorInvalidValue;
+  g.n_pre = g.pre_x * (uint32_t)(q_groups(pp) + (pp.n_kv_heads + pp.heads_per_thread - 1) / pp.heads_per_thread);
+  g.pre_div = make_fast_div(g.pre_x);
+  const dim3 grid(g.n_pre + (unsigned)blocks.n);
+  if (pp.layout == 0)
+    hipLaunchKernelGGL((turn_tables_kernel<D, 0, Blocks>), grid, dim3(kRotThreads), 0, stream, tt, blocks, pp, segs, rt, g);
+  else
+    hipLaunchKernelGGL((turn_tables_kernel<D, 1, Blocks>), grid, dim3(kRotThreads), 0, stream, tt, blocks, pp, segs, rt, g);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+template <typename Blocks>
+hipError_t launch_turn_tables(const TurnTables &tt, const Blocks &blocks, const RopePrepassParams &pp, const RopeSegsGather &segs,
+                              const RopeTable &rt, hipStream_t stream) {
+  if (pp.head_dim == 128) return launch_turn_d<128>(tt, blocks, pp, segs, rt, stream);
+  if (pp.head_dim == 64) return launch_turn_d<64>(tt, blocks, pp, segs, rt, stream);
+  return hipErrorInvalidValue;
+}
+template hipError_t launch_turn_tables(const TurnTables &, const ReencBlocks &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
+template hipError_t launch_turn_tables(const TurnTables &, const ReencBlocksLarge &, const RopePrepassParams &, const RopeSegsGather &, const RopeTable &, hipStream_t);
 
 // Where the two are one launch.  Not where one long block lies among many short ones and the launch would be mostly_idle (or, further
 // on, beyond the 2^32 threads that the runtime launches in the one dimension used here): the re-encode kernels have the

@@ -1104,6 +1104,63 @@ def test_gathered_calls_that_copy_their_values(ba, why):
     assert np.array_equal(host_bits(o), want)
 
 
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("case", [
+    # (Hq, Hkv, D, tokens of each prompt's cached blocks, query tokens of each prompt, whether nothing is copied)
+    (32, 8, 128, [[20, 60, 33, 1] * 100], [64], True), (32, 32, 128, [[64] * 30, [7, 90, 130] * 8], [200, 1], True),
+    (32, 32, 64, [[40, 90] * 45], [130], True), (64, 16, 128, [[100] * 85, [3]], [100, 17], True),
+    # two row tiles a prompt (30 MiB of keys are asked for), blocks whose rotations do not fit, keys of 21 MiB, and a token less
+    (64, 16, 128, [[50] * 150], [100], False), (32, 32, 128, [[1] * 1000, [64] * 30], [9, 9], False),
+    (32, 32, 64, [[96] * 56], [5], True), (32, 32, 64, [[96] * 55 + [95]], [5], False)],
+    ids=["ragged", "two-prompts", "d64", "row-tiles", "many-row-tiles", "tiny-blocks", "turned-from-here", "copied-to-here"])
+def test_cached_keys_turned_by_the_attention_kernel(ba, case, layout):
+    """Short cached blocks, many of them: keys fetched through the table of rows and turned as they arrive.  The bits of a context
+    re-encoded by hand; blocks in any order, some of them at the places they were encoded at (one with a key that a rotation by
+    nothing would spoil), keys and values as views of one buffer, and with rotated keys or outputs over what the call reads."""
+    torch = torch_mod()
+    hq, hkv, d, prompts, lqs, turned = case
+    rng = np.random.default_rng(1470 + layout)
+    lens = np.array([n for p in prompts for n in p], dtype=np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    cu_q = np.concatenate([[0], np.cumsum(lqs)]).astype(np.int32)
+    order = rng.permutation(len(lens))
+    off = np.zeros(len(lens), dtype=np.int32)
+    off[order] = np.concatenate([[0], np.cumsum(lens[order])[:-1]])
+    T, tq = int(lens.sum()), int(cu_q[-1])
+    dst = (np.cumsum(lens) - lens).astype(np.int32)
+    cu_ctx = np.concatenate([[0], np.cumsum(lens)])[cu_blk].astype(np.int32)
+    new0 = (dst - np.repeat(cu_ctx[:-1], np.diff(cu_blk))).astype(np.int32)
+    old0 = np.where(np.arange(len(lens)) % 3 == 1, new0, rng.integers(0, 5000, len(lens))).astype(np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(1471)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    both, q, kf, vf = draw(T, 2 * hkv, d), draw(tq, hq, d), draw(tq, hkv, d), draw(tq, hkv, d)
+    both[off[1], 0, 3] = float("inf")  # (scores of plus and minus infinity, by the sign of the query)
+    heads = ba.Heads(hq, hkv, d, 10000.0, rope_layout=layout)
+    k_ctx, v_ctx = (torch.empty((T, hkv, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    ba.ba_reencode_positions(heads, both[:, :hkv], k_ctx, off, dst, lens, old0, new0, ba.REENC_SHIFT)
+    for a, b, n in zip(off, dst, lens):
+        v_ctx[b:b + n] = both[a:a + n, hkv:]
+    want = gpu_final(ba, heads, q, k_ctx, v_ctx, kf, vf, cu_q, cu_ctx)
+    finite = torch.isfinite(want.float())
+    assert 0 < int((~finite).sum()) < want.numel() // 8
+    need = ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens, True)
+    need = max(need, ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens))
+    for where in ("apart", "rot over a block", "o over a block", "apart"):
+        cache = both.clone()
+        o, rot = torch.full_like(q, float("nan")), None
+        if where == "rot over a block":
+            rot = cache[off[5]:off[5] + tq, :hkv] if off[5] + tq <= T else cache[T - tq:, :hkv]
+        elif where == "o over a block":
+            o = cache.view(-1)[:q.numel()].view(q.shape)
+        ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+        ba.ba_final_block_attention_cached(heads, q, cache[:, :hkv], cache[:, hkv:] if where == "apart" else both[:, hkv:], kf, vf, o, rot,
+                                           cu_q, cu_blk, off, lens, old0, new0, None, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(torch.isfinite(o.float()), finite) and torch.equal(o[finite], want[finite]), where
+        table = int(off[0]) * 4 * hkv * d + 4 * hkv * d * np.arange(lens[0])
+        assert np.array_equal(ws[:4 * int(lens[0])].view(torch.int32).cpu().numpy(), table) == (turned and where == "apart"), where
+
+
 @pytest.mark.parametrize("d,hkv,n,layout", [(128, 8, 100, 0), (64, 2, 20, 0), (128, 8, 100, 1)])
 def test_gathered_call_whose_rotated_keys_replace_a_cached_block(ba, d, hkv, n, layout):
     """The query block's rotated keys take the place of a block that the call itself still reads: the context is gathered
