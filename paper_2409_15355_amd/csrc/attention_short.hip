@@ -24,6 +24,7 @@
 //     passage's output must not change with its neighbours there: kAsCore gives the main core's numbers,
 //     bit for bit as long as no reference has to move.  (Larger groups take the schedule by a block's own
 //     length, whole prompts have this one only: they keep the cheaper order.)
+#include <atomic>
 #include <type_traits>
 
 #include "ba_device.h"
@@ -67,9 +68,10 @@ struct SharedPromptMeta : PromptMeta {
 // kAsCore: the numbers of the main core (the reference from the first 64 keys, sums by 64 keys).
 // kPast: rows of q and o go past the caches (see kCacheBytes).
 template <int D, typename Meta, bool kAsCore, bool kPast>
-__global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p, Meta meta) {
+__global__ __launch_bounds__(kSThreads, (std::is_same<Meta, EncodeFreshMeta>::value ? 1 : 3)) void encode_short_kernel(AttnParams p, Meta meta) {
   using G = SGeo<D>;
   constexpr bool kPrompt = std::is_base_of<PromptMeta, Meta>::value, kShared = std::is_same<Meta, SharedPromptMeta>::value;
+  constexpr bool kFresh = std::is_same<Meta, EncodeFreshMeta>::value;  // query rows and keys as the caller gave them
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char *smem = (lds_char *)smem_generic;
   // LDS map: buffer b = bytes [2 b TB, 2 (b + 1) TB): its K tile, then its V tile
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
       const uint32_t o = wr_r0 < n_rows - u * QRPI ? off : last_off;
       ld[u] = load_row_piece<kPast>(qbase + (o * 2u + (uint32_t)(lane % G::CPR) * 16u));
     });
-    if (p.q_table && Gq >= 4) {
+    if (!kFresh && p.q_table && Gq >= 4) {
       // The rows of a wave span at most 8 tokens.  Chunk c of token row t sits at chunk c ^ (t & 7),
       // which keeps the reads of different tokens off each other's banks.
       const char *tbase = (const char *)(p.q_table + (int64_t)pos0 * D);
@@ -250,16 +252,80 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
       lds_dma16(vp, row * v_rb + c_vchunk[u], lds_copy + (uint32_t)buf * (2 * TB) + TB + u * 1024);
     }
   };
+  // ---- rows that no pre-pass has turned (small calls: one workgroup per compute unit at most).  (cos, sin) of the block's positions are
+  //      worked out into the LDS behind the tile buffers while the query rows and the first tiles are on their way; a wave turns
+  //      the rows of a key tile that it has copied itself, before the barrier that publishes the tile, and in the block's last row tile, which
+  //      walks all of them, leaves them in k_out as well.  The products are the pre-pass's: the same bits.  Bound by latency, the pre-pass's
+  //      launch saved: two blocks of 128 tokens, 4 over 4 heads of 64, 12.5 -> 10.0 us, one of 32 12.5 -> 6.1 -------------------
+  constexpr uint32_t FRESH = (uint32_t)G::LDS;
+  typedef __attribute__((address_space(3))) f32x2_t lds_f32x2;
+  typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+  typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
+  // pairs 2 i and 2 i + 1 of position t are 16-byte piece i of its row
+  auto piece = [&](int t, int i) __attribute__((always_inline)) { return FRESH + (uint32_t)t * TROW + ((uint32_t)(i ^ (t & 7)) << 4); };
+  const int last_tok = (int)fast_div((uint32_t)last_row, p.group_div);  // the positions wanted: up to the last row's
+  auto turn_tile = [&](int t, int buf) __attribute__((always_inline)) {
+    if constexpr (kFresh) {
+      constexpr int HC = G::CPR / 2, ROWS = kSKeys / kSWaves;  // a wave's rows
+      static_assert(ROWS * HC <= 64, "one step of the wave");
+      const bool halves = p.rope_layout != 0;
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      const int c = ln % HC, row = wave * ROWS + ln / HC;
+      if (ln / HC < ROWS) {
+        const uint32_t at = (uint32_t)buf * (2 * TB) + (uint32_t)row * G::ROWB + (uint32_t)((c ^ ((row / G::LPR) & (G::CPR - 1))) << 4);
+        const u32x4_t xa = *(const lds_u32x4 *)(smem + at), xb = *(const lds_u32x4 *)(smem + (at ^ (HC << 4)));
+        const int tok = min(t * kSKeys + row, last_tok);  // (rows behind it are masked)
+        f32x4_t ct[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          ct[h] = *(const lds_f32x4 *)(smem + piece(tok, halves ? c * 4 + h : (h < 2 ? c * 2 + h : (c + HC) * 2 + h - 2)));
+        u32x4_t ya, yb;
+        turn_chunks(xa, xb, ct, halves, ya, yb);
+        *(lds_u32x4 *)(smem + at) = ya;
+        *(lds_u32x4 *)(smem + (at ^ (HC << 4))) = yb;
+        if (meta.k_out && last_row == n_rows - 1 && t * kSKeys + row < lq) {
+          uint16_t *out = meta.k_out + (int64_t)(q_tok0 + t * kSKeys + row) * meta.k_out_st + (int64_t)kvh * meta.k_out_sh + c * 8;
+          *reinterpret_cast<u32x4_t *>(out) = ya;
+          *reinterpret_cast<u32x4_t *>(out + HC * 8) = yb;
+        }
+      }
+      lds_wait();  // (published by the next barrier)
+    }
+  };
   constexpr int kOpsPerTile = 2 * G::IPW;  // vector-memory operations of one wave per tile
   if (!kPrompt || t0 < n_t) issue_copy(t0, 0);  // (buffer 2 holds the waves' slices until the first barrier)
   if (t0 + 1 < n_t) issue_copy(t0 + 1, 1);
   __builtin_amdgcn_sched_barrier(0);  // the copies go out before anything waits for the Q rows
+  if constexpr (kFresh) {
+    static_assert(kSThreads % (D / 2) == 0, "a thread keeps its frequency");
+    const int j = (int)threadIdx.x % (D / 2);
+    const uint64_t turns = meta.rt.turns[j];
+    for (int t = (int)threadIdx.x / (D / 2); t <= last_tok; t += kSThreads / (D / 2)) {
+      float c, sn;
+      sincos_phase(rope_phase(t, turns), c, sn);
+      *(lds_f32x2 *)(smem + piece(t, j >> 1) + (j & 1) * 8) = f32x2_t{c, sn};
+    }
+  }
 
   // ---- rotate (or just scale) the Q rows into the fragments ---------------------------------------
   dma_wait<0>();  // the table rows and the first tile (this wave's share) have landed
   // the table first
   f32x4_t cs[2 * G::KCH];
-  if (p.q_table && Gq < 4) {
+  if constexpr (kFresh) {
+    lds_wait();
+    wg_barrier();  // the table is whole (and every wave's share of the first two tiles has landed)
+    turn_tile(0, 0);
+    if (1 < n_t) turn_tile(1, 1);
+    const int tok = (int)fast_div((uint32_t)min(my_row, n_rows - 1), p.group_div);
+    const int t_q = min(tok, last_tok);
+#pragma unroll
+    for (int j = 0; j < 2 * G::KCH; ++j) {
+      cs[j] = *(const lds_f32x4 *)(smem + piece(t_q, fragment_table_piece(j, hf, p.rope_layout != 0)));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cs[j][e] *= p.scale_log2e;
+    }
+  } else if (p.q_table && Gq < 4) {
     // Fewer heads than that share a token's row of the table, down to one: hardly any of it would be read
     // twice, so every lane takes its pieces from where they lie.
     const int tok = (int)fast_div((uint32_t)min(my_row, n_rows - 1), p.group_div);
@@ -301,7 +367,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
       for (int e = 0; e < 4; ++e) raw[kk][e] = (col >> 4) ? got[1][kk][e] : got[0][kk][e];
   }
   bf16x8_t qf[G::KCH];
-  if (p.q_table) {
+  if (kFresh || p.q_table) {
     rotate_fragments<G::KCH, kAsCore>(raw, cs, p.rope_layout != 0);
   } else if (!p.q_ready) {
     const float c2 = p.scale_log2e;
@@ -405,6 +471,7 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
 #pragma unroll 1
   for (int i = t0; i < n_t; ++i) {
     if (i + 1 < n_t) dma_wait<kOpsPerTile>(); else dma_wait<0>();  // tile i + 1 may still be on its way
+    if (kFresh && i >= 2) turn_tile(i, buf);
     wg_barrier();
     if (i + 2 < n_t) issue_copy(i + 2, buf == 0 ? 2 : buf - 1);
     if (i < wave_n_t) {
@@ -580,6 +647,23 @@ __global__ __launch_bounds__(kSThreads, 3) void encode_short_kernel(AttnParams p
   }
 }
 
+template <int D, bool kAsCore>
+hipError_t launch_fresh_t(const AttnParams &p, const EncodeFreshMeta &meta, hipStream_t stream) {
+  const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads;
+  if (n_wg == 0) return hipSuccess;
+  if (n_wg > 0x7fffffff || p.rows_past_cache) return hipErrorInvalidValue;
+  constexpr size_t lds = SGeo<D>::LDS + kEncFreshLds;
+  static std::atomic<bool> raised{false};  // (set twice, from two host threads at once: harmless)
+  if (lds > 64 * 1024 && !raised.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&encode_short_kernel<D, EncodeFreshMeta, kAsCore, false>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    raised.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((encode_short_kernel<D, EncodeFreshMeta, kAsCore, false>), dim3((unsigned)n_wg), dim3(kSThreads), lds, stream, p, meta);
+  return hipGetLastError();
+}
+
 template <int D, bool kAsCore, typename Meta>
 hipError_t launch_short_t(const AttnParams &p, const Meta &meta, hipStream_t stream) {
   const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads;
@@ -601,6 +685,14 @@ hipError_t launch_attn_encode_short(const AttnParams &p, const EncodeMeta &meta,
   const bool as_core = p.group < kSmallGroup;
   if (p.head_dim == 128) return as_core ? launch_short_t<128, true>(p, meta, stream) : launch_short_t<128, false>(p, meta, stream);
   if (p.head_dim == 64) return as_core ? launch_short_t<64, true>(p, meta, stream) : launch_short_t<64, false>(p, meta, stream);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_attn_encode_fresh(const AttnParams &p, const EncodeFreshMeta &meta, hipStream_t stream) {
+  if (p.n_splits != 1) return hipErrorInvalidValue;
+  const bool as_core = p.group < kSmallGroup;
+  if (p.head_dim == 128) return as_core ? launch_fresh_t<128, true>(p, meta, stream) : launch_fresh_t<128, false>(p, meta, stream);
+  if (p.head_dim == 64) return as_core ? launch_fresh_t<64, true>(p, meta, stream) : launch_fresh_t<64, false>(p, meta, stream);
   return hipErrorInvalidValue;
 }
 

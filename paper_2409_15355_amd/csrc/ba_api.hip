@@ -333,18 +333,25 @@ static bool fresh_prompts(const int32_t *cu_q, int n, int G) {
 }
 // Whether a call's attention kernel may read the query rows and keys as they are while it writes o: with the pre-pass they are
 // read before it starts.  (o over q itself is fine: a workgroup reads its rows before it writes them.)
-static bool fresh_apart(const ba_tensor *q_f, const ba_tensor *k_f, const ba_tensor *o, int64_t t0, int64_t t1, const ba_heads *h) {
-  struct Span {
-    uintptr_t lo, hi;
-  };
-  const auto span = [&](const ba_tensor *t, int heads) {
-    const uintptr_t lo = (uintptr_t)t->ptr + (uintptr_t)(t0 * t->stride_tok * 2);
-    return Span{lo, lo + (uintptr_t)(((t1 - t0 - 1) * t->stride_tok + (heads - 1) * t->stride_head + h->head_dim) * 2)};
-  };
-  const auto touch = [](const Span &a, const Span &b) { return a.lo < b.hi && b.lo < a.hi; };
+struct Span {
+  uintptr_t lo, hi;
+};
+static Span span_of(const ba_tensor *t, int heads, int D, int64_t t0, int64_t t1) {
+  const uintptr_t lo = (uintptr_t)t->ptr + (uintptr_t)(t0 * t->stride_tok * 2);
+  return Span{lo, lo + (uintptr_t)(((t1 - t0 - 1) * t->stride_tok + (heads - 1) * t->stride_head + D) * 2)};
+}
+static bool touch(const Span &a, const Span &b) { return a.lo < b.hi && b.lo < a.hi; }
+bool fresh_apart(const ba_tensor *q_f, const ba_tensor *k_f, const ba_tensor *o, int64_t t0, int64_t t1, const ba_heads *h) {
+  const auto span = [&](const ba_tensor *t, int heads) { return span_of(t, heads, h->head_dim, t0, t1); };
   const Span so = span(o, h->n_q_heads);
   const bool same = o->ptr == q_f->ptr && o->stride_tok == q_f->stride_tok && o->stride_head == q_f->stride_head;
   return !touch(so, span(k_f, h->n_kv_heads)) && (same || !touch(so, span(q_f, h->n_q_heads)));
+}
+// Likewise the turned keys of a per-block encoding: apart from everything that other workgroups read or write.
+bool encode_keys_apart(const ba_heads *h, const ba_tensor *q, const ba_tensor *k, const ba_tensor *v, const ba_tensor *o, const ba_tensor *k_out, int64_t T) {
+  const auto span = [&](const ba_tensor *t, int heads) { return span_of(t, heads, h->head_dim, 0, T); };
+  const Span out = span(k_out, h->n_kv_heads);
+  return !touch(out, span(q, h->n_q_heads)) && !touch(out, span(k, h->n_kv_heads)) && !touch(out, span(v, h->n_kv_heads)) && !touch(out, span(o, h->n_q_heads));
 }
 
 int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,
@@ -724,6 +731,34 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
     int64_t tiles[2];
     if ((rc = ba::build_encode_metas(block_offsets, b0, n, G, short_max, meta, tiles))) return rc;
     if (tiles[0] + tiles[1] == 0) continue;
+    // a small call of short blocks: one launch, the attention kernel turns rows and keys itself
+    if (rope_mode == BA_ROPE_APPLY && n == n_blocks && tiles[0] == 0 && tiles[1] * heads->n_kv_heads <= num_cus() &&
+        longest_block * D * 4 <= ba::kEncFreshLds && fresh_apart(q, k, o_out, block_offsets[0], T, heads) &&
+        (!k_local_out || encode_keys_apart(heads, q, k, v, o_out, k_local_out, T))) {
+      ba::EncodeFreshMeta fm;
+      memset(&fm, 0, sizeof(fm));
+      static_cast<ba::EncodeMeta &>(fm) = meta[1];
+      fm.rt = rt;
+      if (k_local_out) {
+        fm.k_out = (uint16_t *)k_local_out->ptr;
+        fm.k_out_st = k_local_out->stride_tok;
+        fm.k_out_sh = k_local_out->stride_head;
+      }
+      ba::AttnParams fp = ap;
+      fp.kf = (const uint16_t *)k->ptr;
+      fp.kf_st = k->stride_tok;
+      fp.kf_sh = k->stride_head;
+      fp.q_table = nullptr;
+      fp.total_tiles = (int32_t)tiles[1];
+      fp.tiles_div = ba::make_fast_div((uint32_t)tiles[1]);
+      hipError_t e;
+      {
+        ProfileScope ps(BA_PROFILE_ATTENTION, stream);
+        e = ba::launch_attn_encode_fresh(fp, fm, stream);
+      }
+      if (e != hipSuccess) return device_fail(e, "encode attention launch");
+      continue;
+    }
     if (rope_mode == BA_ROPE_APPLY) {
       // local positions: every block starts at 0, so one table of factors by position serves all blocks
       // (as many rows as the longest block has tokens; written by the first launch)

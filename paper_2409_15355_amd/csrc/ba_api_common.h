@@ -96,6 +96,8 @@ struct Gather {
   ba::TurnTables turned;
   uint32_t blk_at, rot_at;  // of FinalTurnMeta
 };
+bool fresh_apart(const ba_tensor *q_f, const ba_tensor *k_f, const ba_tensor *o, int64_t t0, int64_t t1, const ba_heads *h);
+bool encode_keys_apart(const ba_heads *h, const ba_tensor *q, const ba_tensor *k, const ba_tensor *v, const ba_tensor *o, const ba_tensor *k_out, int64_t T);
 bool writes_gathered_rows(const Gather &g, const ba_tensor *k_rot, int n_heads, int64_t t0, int64_t t1);
 // ba_final_block_attention, its context gathered first if so asked
 int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor *k_ctx, const ba_tensor *v_ctx,

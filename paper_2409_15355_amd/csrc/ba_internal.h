@@ -437,9 +437,22 @@ hipError_t launch_mfma_ceiling(int reads_per_two, int n_wg, int iters, void *ws,
 // n pseudo-random bf16 values (synthetic operands of the XCD speed probe)
 hipError_t launch_fill_random_bf16(uint16_t *dst, int64_t n, uint32_t seed, hipStream_t stream);
 
+// Per-block encoding whose query rows and keys are as the caller gave them: no RoPE pre-pass has run, the kernel turns them itself
+// and leaves the turned keys in k_out, if that is given.  One workgroup per compute unit at most; the table of a block's positions
+// in LDS.  Working it out grows with the block, the pre-pass and its launch, some 4 us of latency, do not: pre-pass / here, 4
+// over 4 heads of 64, blocks of 96 tokens 12.4 / 8.8 us, 128 12.5 / 10.0, 160 13.5 / 10.6, 200 12.6 / 11.7, 250 14.2 / 14.6; 32 over 8 of 128,
+// 64 12.0 / 9.3, 80 12.4 / 10.6, 100 12.6 / 11.3, 128 12.9 / 12.7.  Blocks of 104 tokens of 128 dimensions, 208 of 64.
+constexpr int kEncFreshLds = 52 * 1024;
+struct EncodeFreshMeta : EncodeMeta {
+  RopeTable rt;
+  uint16_t *k_out;
+  int64_t k_out_st, k_out_sh;
+};
+
 hipError_t launch_attn_encode(const AttnParams &p, const EncodeMeta &meta, hipStream_t stream);
 // the same for short blocks: meta.tile_start counts row tiles of kShortTileRows rows
 hipError_t launch_attn_encode_short(const AttnParams &p, const EncodeMeta &meta, hipStream_t stream);
+hipError_t launch_attn_encode_fresh(const AttnParams &p, const EncodeFreshMeta &meta, hipStream_t stream);
 hipError_t launch_attn_prompt_short(const AttnParams &p, const PromptMeta &meta, hipStream_t stream);
 hipError_t launch_attn_final_blocks(const AttnParams &p, const FinalBlocksMeta &meta, hipStream_t stream);
 hipError_t launch_attn_final_blocks(const AttnParams &p, const FinalBlocksMetaSmall &meta, hipStream_t stream);

@@ -141,6 +141,29 @@ __device__ __forceinline__ void dma_wait() {
   asm volatile("" ::: "memory");
 }
 
+// Chunks c and c + CPR / 2 of a row of keys, turned.  t: the pieces of the row's (cos, sin) that the two need -- interleaved pairs: pairs
+// 4 c .. 4 c + 3 lie in the first chunk, 4 (c + CPR / 2) .. in the other; half-split: element e of the one pairs with element e of
+// the other, pairs 8 c .. 8 c + 7.
+__device__ __forceinline__ void turn_chunks(const u32x4_t &a, const u32x4_t &b, const f32x4_t (&t)[4], bool halves, u32x4_t &ya, u32x4_t &yb) {
+  auto x_of = [](float x, float y, float c, float s) { return __builtin_fmaf(c, x, -(s * y)); };
+  auto y_of = [](float x, float y, float c, float s) { return __builtin_fmaf(s, x, c * y); };
+  if (!halves) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float ca = t[e / 2][(e & 1) * 2], sa = t[e / 2][(e & 1) * 2 + 1], cb = t[2 + e / 2][(e & 1) * 2], sb = t[2 + e / 2][(e & 1) * 2 + 1];
+      ya[e] = pack_bf16(x_of(bf16_lo(a[e]), bf16_hi(a[e]), ca, sa), y_of(bf16_lo(a[e]), bf16_hi(a[e]), ca, sa));
+      yb[e] = pack_bf16(x_of(bf16_lo(b[e]), bf16_hi(b[e]), cb, sb), y_of(bf16_lo(b[e]), bf16_hi(b[e]), cb, sb));
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a0 = bf16_lo(a[e]), a1 = bf16_hi(a[e]), b0 = bf16_lo(b[e]), b1 = bf16_hi(b[e]);
+      ya[e] = pack_bf16(x_of(a0, b0, t[e][0], t[e][1]), x_of(a1, b1, t[e][2], t[e][3]));
+      yb[e] = pack_bf16(y_of(a0, b0, t[e][0], t[e][1]), y_of(a1, b1, t[e][2], t[e][3]));
+    }
+  }
+}
+
 // ---- row tiles whose walk several workgroups share (PromptMeta::n_split): each leaves its accumulators in
 //      32 bits, in the layout they have (1 KB of consecutive memory per wave instruction), and the one that
 //      is last to count itself in adds them up in the order of the splits --------------------------------

@@ -1105,6 +1105,49 @@ def test_gathered_calls_that_copy_their_values(ba, why):
 
 
 @pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("hq,hkv,d,lens,launches", [
+    (4, 4, 64, [1, 31, 0, 33, 208, 64], 0), (4, 4, 64, [209, 40], 1), (8, 2, 64, [130, 7, 32], 0), (5, 1, 64, [96, 101], 0),
+    (16, 8, 128, [104, 1, 65], 0), (32, 8, 128, [32, 97, 104], 0), (32, 8, 128, [105, 32], 1)])
+def test_small_encodes_turn_their_own_rows(ba, hq, hkv, d, lens, launches, layout):
+    """Per-block encoding of a few short blocks in one launch.  The bits, outputs and kept keys, that the same blocks have in a call of
+    many more, whose rows a pre-pass turns; and where keys or outputs lie over what the call reads, which the pre-pass has to read first."""
+    torch = torch_mod()
+    many = np.concatenate([lens, [60] * 300]).astype(np.int32)
+    offs, all_offs = (np.concatenate([[0], np.cumsum(n)]).astype(np.int32) for n in (lens, many))
+    T, T_all = int(offs[-1]), int(all_offs[-1])
+    gen = torch.Generator(device="cuda").manual_seed(1480 + layout)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    q, k, v = draw(T_all, hq, d), draw(T_all, hkv, d), draw(T_all, hkv, d)
+    heads = ba.Heads(hq, hkv, d, 10000.0, rope_layout=layout)
+
+    def encode(q, k, v, o, k_local, offs):
+        need = ba.ba_encode_blocks_workspace_bytes(heads, offs, ba.ROPE_APPLY, k_local is not None)
+        ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+        ba.ba_profile_begin()
+        ba.ba_encode_blocks(heads, q, k, v, o, k_local, offs, ba.ROPE_APPLY, ws)
+        torch.cuda.synchronize()
+        return ba.ba_profile_end()[1][ba.PROFILE_REENCODE]
+
+    want, want_k = torch.empty_like(q), torch.empty_like(k)
+    assert encode(q, k, v, want, want_k, all_offs) == 1
+    want, want_k = host_bits(want[:T]), host_bits(want_k[:T])
+    q, k, v = q[:T].contiguous(), k[:T].contiguous(), v[:T].contiguous()
+    o, k_local = torch.full_like(q, float("nan")), torch.full_like(k, float("nan"))
+    for _ in range(3):
+        assert encode(q, k, v, o, k_local, offs) == launches
+        assert np.array_equal(host_bits(o), want) and np.array_equal(host_bits(k_local), want_k)
+    assert encode(q, k, v, o.fill_(float("nan")), None, offs) == launches
+    assert np.array_equal(host_bits(o), want)
+    k_in = k.clone()
+    assert encode(q, k_in, v, o.fill_(float("nan")), k_in, offs) == 1
+    assert np.array_equal(host_bits(o), want) and np.array_equal(host_bits(k_in), want_k)
+    if hq == hkv:
+        k_in = k.clone()
+        assert encode(q, k_in, v, k_in, k_local.fill_(float("nan")), offs) == 1
+        assert np.array_equal(host_bits(k_in), want) and np.array_equal(host_bits(k_local), want_k)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("case", [
     # (Hq, Hkv, D, tokens of each prompt's cached blocks, query tokens of each prompt, whether nothing is copied)
     (32, 8, 128, [[20, 60, 33, 1] * 100], [64], True), (32, 32, 128, [[64] * 30, [7, 90, 130] * 8], [200, 1], True),
