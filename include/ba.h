@@ -280,7 +280,8 @@ int32_t ba_final_block_attention_static(const ba_heads *heads, const ba_tensor *
  * copy of the context an amount per token; when the mean length of the call's non-empty blocks is
  * below this many tokens (BA_GATHER_DEFAULT = 256 tokens; 0 = never gather) the call gathers the
  * context into its workspace first (keys re-encoded on the way, a few MB of values copied, more of
- * them read from where they lie; the cache itself stays as it is) and continues as ba_final_block_attention.  Same results either way, to
+ * them read from where they lie; the cache itself stays as it is) and continues as ba_final_block_attention; of some tens of MB nothing
+ * is copied, the keys are re-encoded as they arrive, with the same bits.  Same results either way, to
  * rounding.  The two routes need different workspaces: pass the same value to the size query.
  * At most 1024 non-empty blocks per prompt when the kernel reads the block table
  * (BA_ERR_UNSUPPORTED beyond); no such limit on the gathered route.
@@ -317,8 +318,8 @@ size_t ba_final_block_attention_cached_workspace_bytes(const ba_heads *heads, in
  * as local positions plus re-encoding -- and the rotated keys go to k_rot_out if non-null; with
  * BA_ROPE_NONE q and k are used as given.  lse_out (device, nullable): [T][n_q_heads] floats, the
  * natural-log sum of exp(scale * <q^, k^>) over each row's visible keys, as a backward pass needs.
- * Built for training-sized prompts: at most a few workgroups share the walk of a last block's row
- * tile (with rope_mode BA_ROPE_APPLY; their partial results lie in ws), so a short last block behind
+ * Built for training-sized prompts: the workgroups that share the walk of a last block's row
+ * tile are limited in number (with rope_mode BA_ROPE_APPLY; their partial results lie in ws), so a short last block behind
  * tens of thousands of context tokens is better served by ba_final_block_attention.  Any number of
  * query heads per KV head; with fewer than four the workspace also has room for padded copies of q
  * and o, which are used only where a block's row offsets (tokens x strides) do not fit 32 bits: such

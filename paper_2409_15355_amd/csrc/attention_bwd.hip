@@ -57,7 +57,7 @@ struct BGeo {
 // XOR), and what is left tells the rows apart inside it: at D = 128 the 16 bytes by which the groups of
 // four rows are spaced beyond their 1 KB, at D = 64 the 32 bytes between groups of eight and one more
 // XOR of the chunk's low bit.  (With the XOR of the row number over all chunk bits, the four rows of a
-// transpose read shared one granule's banks: half of the dk/dv kernel's LDS cycles were conflicts.)
+// transpose read shared one granule's banks.  The dk/dv kernel, whose products have another shape, has a layout of its own.)
 // The XORs reach a chunk's granule and lowest bit only, so the two chunk pairs of a granule, the 16-row
 // steps of a transpose read and the tiles of a buffer lie at constant distances from each other: a
 // kernel keeps one address per granule, and the rest are offsets inside the instructions.
@@ -341,8 +341,8 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
   };
   // delta of this wave's rows: a row's CPR lanes add up their pieces, one of them hands the sum over
   // through the slice to the lane that owns the row; -L / ln 2 and -delta also go to memory in packed-row
-  // order per KV head, four rows of the one and four of the other in turn: the dk/dv kernel's
-  // accumulators start at them, and read them from its tile as they lie
+  // order per KV head, four rows of the one and four of the other in turn: as the dk/dv kernel's
+  // lanes read them from its tile
   float2 my_ld;
   {
     float mine = 0.f;  // lane j of a run of CPR lanes takes the sum of the run's j-th row
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
     for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
 
   // ---- the walk over the key tiles ---------------------------------------------------------------
-  // (windows of LDS fragments as in the dk/dv kernel: the first four transposed ones are asked for ahead of the
+  // (rolling windows of LDS fragments: the first four transposed ones are asked for ahead of the
   // exponentials.  Six row fragments instead of four would spill.  The same call 958 -> 953 us.  At head_dim 64, whose kernel
   // has the registers for it, no difference.)
   constexpr int kRowWin = 4, kTrWin = 4;
