@@ -52,6 +52,7 @@ struct SGeo {
   static constexpr int IPW = kSKeys / RPI / kSWaves;  // such instructions per wave, tile and kind
   static constexpr size_t LDS = (size_t)2 * kSBuf * TILEB;
   static_assert(IPW >= 1, "every wave takes part in a tile copy");
+  static_assert(LDS == (size_t)6 * 32 * D * 2, "as encode_fresh_per_cu has it");
   static_assert((size_t)kSWaves * 32 * ROWB + 16 <= LDS, "the output staging must fit the tile buffers, and a word behind it");
 };
 
@@ -68,7 +69,7 @@ struct SharedPromptMeta : PromptMeta {
 // kAsCore: the numbers of the main core (the reference from the first 64 keys, sums by 64 keys).
 // kPast: rows of q and o go past the caches (see kCacheBytes).
 template <int D, typename Meta, bool kAsCore, bool kPast>
-__global__ __launch_bounds__(kSThreads, (std::is_same<Meta, EncodeFreshMeta>::value ? 1 : 3)) void encode_short_kernel(AttnParams p, Meta meta) {
+__global__ __launch_bounds__(kSThreads, (std::is_same<Meta, EncodeFreshMeta>::value ? 2 : 3)) void encode_short_kernel(AttnParams p, Meta meta) {
   using G = SGeo<D>;
   constexpr bool kPrompt = std::is_base_of<PromptMeta, Meta>::value, kShared = std::is_same<Meta, SharedPromptMeta>::value;
   constexpr bool kFresh = std::is_same<Meta, EncodeFreshMeta>::value;  // query rows and keys as the caller gave them
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(kSThreads, (std::is_same<Meta, EncodeFreshMeta>::va
       lds_dma16(vp, row * v_rb + c_vchunk[u], lds_copy + (uint32_t)buf * (2 * TB) + TB + u * 1024);
     }
   };
-  // ---- rows that no pre-pass has turned (small calls: one workgroup per compute unit at most).  (cos, sin) of the block's positions are
+  // ---- rows that no pre-pass has turned (small calls: one round of workgroups at most).  (cos, sin) of the block's positions are
   //      worked out into the LDS behind the tile buffers while the query rows and the first tiles are on their way; a wave turns
   //      the rows of a key tile that it has copied itself, before the barrier that publishes the tile, and in the block's last row tile, which
   //      walks all of them, leaves them in k_out as well.  The products are the pre-pass's: the same bits.  Bound by latency, the pre-pass's
@@ -652,11 +653,12 @@ hipError_t launch_fresh_t(const AttnParams &p, const EncodeFreshMeta &meta, hipS
   const int64_t n_wg = (int64_t)p.total_tiles * p.n_kv_heads;
   if (n_wg == 0) return hipSuccess;
   if (n_wg > 0x7fffffff || p.rows_past_cache) return hipErrorInvalidValue;
-  constexpr size_t lds = SGeo<D>::LDS + kEncFreshLds;
+  const size_t lds = SGeo<D>::LDS + (size_t)meta.table_rows * D * 4;
+  if (lds > SGeo<D>::LDS + kEncFreshLds) return hipErrorInvalidValue;
   static std::atomic<bool> raised{false};  // (set twice, from two host threads at once: harmless)
-  if (lds > 64 * 1024 && !raised.load(std::memory_order_acquire)) {
+  if (SGeo<D>::LDS + kEncFreshLds > 64 * 1024 && !raised.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&encode_short_kernel<D, EncodeFreshMeta, kAsCore, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)(SGeo<D>::LDS + kEncFreshLds));
     if (e != hipSuccess) return e;
     raised.store(true, std::memory_order_release);
   }

@@ -732,13 +732,14 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
     if ((rc = ba::build_encode_metas(block_offsets, b0, n, G, short_max, meta, tiles))) return rc;
     if (tiles[0] + tiles[1] == 0) continue;
     // a small call of short blocks: one launch, the attention kernel turns rows and keys itself
-    if (rope_mode == BA_ROPE_APPLY && n == n_blocks && tiles[0] == 0 && tiles[1] * heads->n_kv_heads <= num_cus() &&
-        longest_block * D * 4 <= ba::kEncFreshLds && fresh_apart(q, k, o_out, block_offsets[0], T, heads) &&
+    if (rope_mode == BA_ROPE_APPLY && n == n_blocks && tiles[0] == 0 && tiles[1] * heads->n_kv_heads <= (int64_t)num_cus() * ba::encode_fresh_per_cu(D, longest_block) &&
+         fresh_apart(q, k, o_out, block_offsets[0], T, heads) &&
         (!k_local_out || encode_keys_apart(heads, q, k, v, o_out, k_local_out, T))) {
       ba::EncodeFreshMeta fm;
       memset(&fm, 0, sizeof(fm));
       static_cast<ba::EncodeMeta &>(fm) = meta[1];
       fm.rt = rt;
+      fm.table_rows = (int32_t)longest_block;
       if (k_local_out) {
         fm.k_out = (uint16_t *)k_local_out->ptr;
         fm.k_out_st = k_local_out->stride_tok;

@@ -438,13 +438,23 @@ hipError_t launch_mfma_ceiling(int reads_per_two, int n_wg, int iters, void *ws,
 hipError_t launch_fill_random_bf16(uint16_t *dst, int64_t n, uint32_t seed, hipStream_t stream);
 
 // Per-block encoding whose query rows and keys are as the caller gave them: no RoPE pre-pass has run, the kernel turns them itself
-// and leaves the turned keys in k_out, if that is given.  One workgroup per compute unit at most; the table of a block's positions
+// and leaves the turned keys in k_out, if that is given.  One round of workgroups at most; the table of a block's positions
 // in LDS.  Working it out grows with the block, the pre-pass and its launch, some 4 us of latency, do not: pre-pass / here, 4
 // over 4 heads of 64, blocks of 96 tokens 12.4 / 8.8 us, 128 12.5 / 10.0, 160 13.5 / 10.6, 200 12.6 / 11.7, 250 14.2 / 14.6; 32 over 8 of 128,
 // 64 12.0 / 9.3, 80 12.4 / 10.6, 100 12.6 / 11.3, 128 12.9 / 12.7.  Blocks of 104 tokens of 128 dimensions, 208 of 64.
 constexpr int kEncFreshLds = 52 * 1024;
+// Workgroups that a compute unit holds at once, by registers and LDS; none if the table is too large.  Beyond one round every further one
+// works its factors out again.  Pre-pass / here, one round and more than one: 32 over 8 of 128, 20 and 40 blocks of 64 15.5 / 13.5 and
+// 19.8 / 20.7 us, 8 and 12 of 100 13.8 / 12.3 and 15.6 / 20.1; 4 over 4 of 64, 200 of 32 13.2 / 8.4, 80 of 128 16.1 / 13.3, 80 of 200 19.0 / 25.9.
+constexpr int encode_fresh_per_cu(int head_dim, int64_t longest) {
+  const int64_t table = longest * head_dim * 4, tiles = 6 * 32 * head_dim * 2;  // (three tiles of 32 keys and values)
+  if (table > kEncFreshLds) return 0;
+  const int64_t by_lds = (160 * 1024) / (tiles + table), by_registers = head_dim == 128 ? 2 : 4;
+  return (int)(by_lds < by_registers ? by_lds : by_registers);
+}
 struct EncodeFreshMeta : EncodeMeta {
   RopeTable rt;
+  int32_t table_rows;  // positions of the longest block
   uint16_t *k_out;
   int64_t k_out_st, k_out_sh;
 };

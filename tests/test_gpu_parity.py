@@ -1107,12 +1107,14 @@ def test_gathered_calls_that_copy_their_values(ba, why):
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("hq,hkv,d,lens,launches", [
     (4, 4, 64, [1, 31, 0, 33, 208, 64], 0), (4, 4, 64, [209, 40], 1), (8, 2, 64, [130, 7, 32], 0), (5, 1, 64, [96, 101], 0),
-    (16, 8, 128, [104, 1, 65], 0), (32, 8, 128, [32, 97, 104], 0), (32, 8, 128, [105, 32], 1)])
+    (16, 8, 128, [104, 1, 65], 0), (32, 8, 128, [32, 97, 104], 0), (32, 8, 128, [105, 32], 1),
+    # several workgroups to a compute unit, and one more than a round
+    (4, 4, 64, [64] * 56 + [32] * 200, 0), (16, 8, 128, [64] * 64, 0), (16, 8, 128, [64] * 64 + [1], 1)])
 def test_small_encodes_turn_their_own_rows(ba, hq, hkv, d, lens, launches, layout):
     """Per-block encoding of a few short blocks in one launch.  The bits, outputs and kept keys, that the same blocks have in a call of
     many more, whose rows a pre-pass turns; and where keys or outputs lie over what the call reads, which the pre-pass has to read first."""
     torch = torch_mod()
-    many = np.concatenate([lens, [60] * 300]).astype(np.int32)
+    many = np.concatenate([lens, [60] * 500]).astype(np.int32)
     offs, all_offs = (np.concatenate([[0], np.cumsum(n)]).astype(np.int32) for n in (lens, many))
     T, T_all = int(offs[-1]), int(all_offs[-1])
     gen = torch.Generator(device="cuda").manual_seed(1480 + layout)
@@ -1129,7 +1131,7 @@ def test_small_encodes_turn_their_own_rows(ba, hq, hkv, d, lens, launches, layou
         return ba.ba_profile_end()[1][ba.PROFILE_REENCODE]
 
     want, want_k = torch.empty_like(q), torch.empty_like(k)
-    assert encode(q, k, v, want, want_k, all_offs) == 1
+    assert encode(q, k, v, want, want_k, all_offs) >= 1
     want, want_k = host_bits(want[:T]), host_bits(want_k[:T])
     q, k, v = q[:T].contiguous(), k[:T].contiguous(), v[:T].contiguous()
     o, k_local = torch.full_like(q, float("nan")), torch.full_like(k, float("nan"))
