@@ -255,9 +255,11 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
       for (int n = 0; n < n_prompts; ++n)
         for (; at < nb && dst[at] < pl.cu_ctx[n + 1]; ++at) dst[at] += ctx0[n] - pl.cu_ctx[n];
     };
-    // Nothing is copied at all where the attention kernel can turn the keys as they arrive: one stride for keys and values, so that
+    const bool table = rows32 && nb <= ba::kRowTableBlocks && ctx_bytes >= ba::kRowTableBytes && (fp.max_nt + fp.max_nt / (2 * fp.n_splits)) / fp.n_splits + 2 <= ba::kRowTableTiles &&
+        table_at + (size_t)padded * 4 <= 2 * align256(pl.gather_kv_bytes);
+    // Nothing is copied at all where, with values through the table, the attention kernel can turn the keys as they arrive: one stride for keys and values, so that
     // one table serves both, tables and rotations of a split's blocks in LDS, and nothing written that the walk still reads.
-    if (rows32 && nb <= ba::kReencMaxBlocksLarge && ctx_bytes >= ba::kTurnBytes + ba::kTurnBytesTile * (size_t)fp.total_tiles / (size_t)n_prompts &&
+    if (table && nb <= ba::kReencMaxBlocksLarge && ctx_bytes >= ba::kTurnBytes + ba::kTurnBytesTile * (size_t)fp.total_tiles / (size_t)n_prompts &&
         k_cache->stride_tok == v_cache->stride_tok &&
         2 * align256((size_t)padded * 4) + (size_t)nb * D * 4 + 1024 <= 2 * align256(pl.gather_kv_bytes)) {
       const std::vector<int32_t> close = dst;
@@ -278,8 +280,6 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
       }
       dst = close;
     }
-    const bool table = rows32 && nb <= ba::kRowTableBlocks && ctx_bytes >= ba::kRowTableBytes && (fp.max_nt + fp.max_nt / (2 * fp.n_splits)) / fp.n_splits + 2 <= ba::kRowTableTiles &&
-        table_at + (size_t)padded * 4 <= 2 * align256(pl.gather_kv_bytes);
     if (!table && (k_cache->stride_tok != v_cache->stride_tok || k_cache->stride_head != v_cache->stride_head)) {
       if ((rc = ba_reencode_positions(heads, k_cache, &kg, 1, 0, 0, nb, src.data(), dst.data(), len.data(), oldp.data(),
                                       newp.data(), BA_REENC_SHIFT, stream_)))
