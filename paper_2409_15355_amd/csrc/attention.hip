@@ -230,7 +230,10 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   const char *c_base = (const char *)(c_ptr + (int64_t)pr.ctx0 * c_st + (int64_t)kvh * c_sh);    // context segment
   if constexpr (kRows) c_base = role_b || kTurn ? (const char *)(c_ptr + (int64_t)kvh * c_sh) : c_base;   // (the table counts from the cache's first row)
   const char *f_base = (const char *)(f_ptr + (int64_t)pr.q_tok0 * f_st + (int64_t)kvh * f_sh);  // causal segment
-  const uint32_t c_rb = (uint32_t)c_st * 2u, f_rb = (uint32_t)f_st * 2u;  // row strides, bytes
+  uint32_t c_rb = (uint32_t)c_st * 2u, f_rb = (uint32_t)f_st * 2u;  // row strides, bytes
+  // (kept apart from the sixteen scalars that the strides arrive in: these are read again where they are wanted, but the
+  // compiler leaves them a spill slot, and every dispatch would ask for 68 bytes of scratch a lane that nothing touches)
+  if constexpr (kTurn) asm volatile("" : "+s"(c_rb), "+s"(f_rb));
   // Full tiles of segments with the "primary" row stride (the context's if there is one, else the
   // causal segment's) take a short path with cached lane offsets.
   const uint32_t prim_rb = n_ctx_segs > 0 ? c_rb : f_rb;
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p, Meta meta)
   // instruction of this wave delays the next MFMA) and rebuilt only when the reference moves.
   // (not with a block table: kept across the reloads of the query fragments they would spill, and kept but made again
   // behind each reload they gained nothing: 31 cached blocks of 1,024 tokens 135.4 us against 135.9, less than runs differ; nor where the
-  // keys are turned, whose addresses would go to scratch)
+  // keys are turned: that kernel has no sixteen registers left and would spill)
   constexpr bool kKeepNegmb = !kBlocks && !kTurn;
   f32x16_t negmb;
   auto set_negmb = [&]() __attribute__((always_inline)) {
