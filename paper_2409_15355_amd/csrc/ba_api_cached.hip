@@ -1,9 +1,9 @@
 // C boundary, the final block straight from a table of cached blocks (Section 2.3 Eq. 2-3 folded into
 // Section 2.5): the block-table launches, and the gathered route for short blocks.
-#include <math.h>
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <vector>
 
@@ -114,16 +114,21 @@ int32_t run_final_blocks(const BlocksCall &c, ba::AttnParams ap) {
   return BA_OK;
 }
 
-// Where a split's part of the tables of FinalTurnMeta lies in LDS, and whether it fits: the longest split's tiles (tables are fetched
-// sixteen tiles at a time), the rotations of the blocks that the most mixed one meets.
+// Whether the attention kernel turns a context's keys itself: where that pays (turn_pays) and a split's part of the tables of FinalTurnMeta
+// fits in LDS, and where it lies there: the longest split's tiles (tables are fetched sixteen tiles at a time), the rotations of the
+// blocks that the most mixed one meets.
 bool turn_layout(const ba_heads *h, int32_t n_prompts, const int32_t *cu_q, const int32_t *cu_ctx, const int32_t *ctx0,
                  const std::vector<int32_t> &first_row, int n_splits, uint32_t *blk_at, uint32_t *rot_at) {
   const int G = h->n_q_heads / h->n_kv_heads;
   int most_tiles = 1, most_blocks = 1;
+  double turned = 0.0, walked = 0.0;  // tokens whose keys a row tile turns, tiles in the walks of all row tiles
   const auto block_of = [&](int64_t row) { return (int)(std::upper_bound(first_row.begin(), first_row.end(), (int32_t)row) - first_row.begin()) - 1; };
   for (int n = 0; n < n_prompts; ++n) {
     const int ctx_tiles = (cu_ctx[n + 1] - cu_ctx[n] + ba::kTileKeys - 1) / ba::kTileKeys;
     const int64_t n_rows = (int64_t)(cu_q[n + 1] - cu_q[n]) * G;
+    const double row_tiles = (double)((n_rows + ba::kTileRows - 1) / ba::kTileRows);
+    turned += row_tiles * (double)(cu_ctx[n + 1] - cu_ctx[n]);
+    walked += row_tiles * (double)ctx_tiles;
     for (int64_t row0 = 0; row0 < n_rows; row0 += ba::kTileRows) {
       const int causal = ba::causal_key_tiles((int)((std::min(n_rows, row0 + ba::kTileRows) - 1) / G), ba::kTileKeys);
       for (int s = 0; s < n_splits; ++s) {
@@ -136,6 +141,9 @@ bool turn_layout(const ba_heads *h, int32_t n_prompts, const int32_t *cu_q, cons
       }
     }
   }
+  const double tokens = cu_ctx[n_prompts];
+  const double mean = std::ceil(walked * h->n_kv_heads / num_cus());
+  if (!ba::turn_pays(tokens * h->n_kv_heads * h->head_dim * 2.0, turned / tokens, most_tiles, mean)) return false;
   const int64_t table = (int64_t)(most_tiles + 15) / 16 * 16 * ba::kTileKeys * 4;  // of either table
   const int64_t rots = ((int64_t)most_blocks * h->head_dim * 4 + 1023) / 1024 * 1024;
   if (2 * table + rots > (int64_t)ba::kTurnLds) return false;
@@ -259,7 +267,7 @@ int32_t ba_final_block_attention_cached(const ba_heads *heads, const ba_tensor *
         table_at + (size_t)padded * 4 <= 2 * align256(pl.gather_kv_bytes);
     // Nothing is copied at all where, with values through the table, the attention kernel can turn the keys as they arrive: one stride for keys and values, so that
     // one table serves both, tables and rotations of a split's blocks in LDS, and nothing written that the walk still reads.
-    if (table && nb <= ba::kReencMaxBlocksLarge && ctx_bytes >= ba::kTurnBytes + ba::kTurnBytesTile * (size_t)fp.total_tiles / (size_t)n_prompts &&
+    if (table && nb <= ba::kReencMaxBlocksLarge && (double)ctx_bytes >= ba::kTurnBytes &&
         k_cache->stride_tok == v_cache->stride_tok &&
         2 * align256((size_t)padded * 4) + (size_t)nb * D * 4 + 1024 <= 2 * align256(pl.gather_kv_bytes)) {
       const std::vector<int32_t> close = dst;

@@ -364,13 +364,28 @@ struct FinalGatherMeta : FinalMeta {
 // for every entry of rows[], a row of rot = (cos, sin) of the shift per frequency.  LDS behind the tile buffers: a split's
 // part of rows[], from blk_at on its part of blk[], from rot_at on the rotations of its blocks.
 // Saved: the keys' way out to memory and back (84 of 168 MB for 20,000 tokens of 8 heads of 128; the gather took 16 us of 54).
-// Paid: 2 to 3 us of start-up (table, then first tile and rotations, then the turning of it, one behind the other) and
-// 0.2 to 0.3 us a key tile, by every row tile anew.  So for contexts of kTurnBytes of keys and kTurnBytesTile more for each row tile that
-// a prompt has in the mean.  Copied / turned, 32 over 8 heads of 128, blocks of 40 to 200: one row tile, 8 MB 22.2 / 24.5 us, 16 MB
-// 30.1 / 31.2, 20 MB 33.9 / 30.8, 33 MB 44.0 / 35.5, 40 MB 49.8 / 41.3, 60 MB 64.2 / 51.1; two, 16 MB 34.7 / 36.7, 20 MB 41.2 / 40.8, 33 MB 56.6 / 53.2,
-// 50 MB 73.5 / 70.1; four, 33 MB 85.7 / 85.4, 40 MB 102.9 / 109.2.  8 over 2 heads of 64: four, 8 MB 35.7 / 40.7.  One block of 3,000 among 500 of 30:
-// 59.1 / 34.0.
-constexpr size_t kTurnBytes = (size_t)12 << 20, kTurnBytesTile = (size_t)9 << 20;
+// Paid: 2 to 3 us of start-up (table, then first tile and rotations, then the turning of it, one behind the other) and some 0.3 us a key
+// tile that a workgroup walks, by every row tile anew.  So only
+//   - where a key is turned by kTurnRowTiles row tiles at most, in the mean over the context (each prompt by its share of the tokens);
+//   - for contexts of kTurnBytes of keys and kTurnBytesTile more for each of those row tiles;
+//   - where the longest walk is no more than kTurnUneven times what every compute unit walks in the mean (else it ends the launch
+//     alone, some 0.55 us a tile longer), nor longer than a tile for every kTurnBytesWalk of keys.
+// Copied / turned, us.  32 over 8 heads of 128, blocks of 60 to 180 and more, one row tile: 8 MiB 22.2 / 24.5, 16 MiB 29.8 / 29.6, 22 MiB 36.2 / 32.7, 44 MiB
+// 54.9 / 44.9, 90 MiB 88.9 / 70.8; two, 16 MiB 34.7 / 36.7, 32 MiB 58.4 / 54.3, 44 MiB 71.8 / 67.6, 64 MiB 94.6 / 89.2; three, 23 MiB 57.7 / 56.9, 32 MiB 74.1 /
+// 75.9, 44 MiB 91.2 / 94.4; four, 23 MiB 65.3 / 67.0, 38 MiB 102.9 / 109.2; six, 15 MiB 62.6 / 70.0.  32 over 32 of 64: one, 22 MiB
+// 36.7 / 34.7, 69 MiB 83.5 / 74.3; two, 42 tiles of 44 MiB, 84.3 / 88.7; three, 44 MiB 124 / 141, 72 MiB 184 / 205.
+// Few KV heads, whose splits are 64 at most: 8 over 1 of 128, 22 tiles of 22 MiB, 5.5 in the mean, 50.5 / 58.8; 8 over 2 of 64, 22 tiles and 11
+// 47.1 / 50.6; 8 over 2 of 128, 17 tiles and 8 of 32 MiB 52.3 / 49.3.  Several prompts: 180 query tokens over 3,000 and 30 over 16,000 (37
+// MiB, 32 tiles, 12 in the mean) 65.5 / 74.9; over 4,000 and 16,000 (32 and 14) 66.8 / 75.8; 180 over 7,000 and two of 30 over 9,000 (49 MiB, 24
+// and 19) 66.4 / 63.1; 60 over 16,000 and 60 over 3,000 (37 MiB, 16 and 9) 57.8 / 52.3.  What the line leaves on the turned side all the same: 16 KV
+// heads of 128, two row tiles, 28 tiles of 33 MiB 65.5 / 68.6; 180 over 6,000 and 30 over 16,000 (43 MiB, 32 and 17) 69.7 / 75.4; 8 over 2 of
+// 128, 11 tiles of 22 MiB 39.5 / 40.2.  One block of 3,000 among 500 of 30: 59.1 / 34.0.
+constexpr double kTurnRowTiles = 2.0, kTurnUneven = 2.25;
+constexpr double kTurnBytes = 12 << 20, kTurnBytesTile = 9 << 20, kTurnBytesWalk = 7.0 / 6.0 * (1 << 20);
+inline bool turn_pays(double key_bytes, double row_tiles, double longest_walk, double mean_walk) {
+  return row_tiles <= kTurnRowTiles && key_bytes >= kTurnBytes + kTurnBytesTile * row_tiles && longest_walk <= kTurnUneven * mean_walk &&
+         key_bytes >= kTurnBytesWalk * longest_walk;
+}
 constexpr uint32_t kTurnLds = 32 * 1024;
 constexpr uint32_t kTurnPlain = 0x80000000u;  // in blk[]: a shift of zero, the key stays as it is
 struct FinalTurnMeta : FinalGatherMeta {

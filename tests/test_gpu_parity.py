@@ -1206,6 +1206,44 @@ def test_cached_keys_turned_by_the_attention_kernel(ba, case, layout):
         assert np.array_equal(ws[:4 * int(lens[0])].view(torch.int32).cpu().numpy(), table) == (turned and where == "apart"), where
 
 
+@pytest.mark.parametrize("hq,hkv,d,prompts,lqs,turned", [
+    # three row tiles a prompt: every one of them would turn the keys again
+    (32, 32, 64, [[200] * 58], [700], False), (32, 8, 128, [[220] * 105], [190], False),
+    # two, with keys to spare, and two where a workgroup walks as many tiles as there are MiB of keys
+    (32, 8, 128, [[200] * 82], [128], True), (32, 32, 64, [[200] * 52], [500], False),
+    # the splits of one or two KV heads are long
+    (8, 1, 128, [[220] * 410], [20], False), (8, 2, 64, [[220] * 410], [20], False), (8, 2, 128, [[220] * 298], [20], True),
+    # row tiles count by the context that they turn: most of it behind three of them, or hardly any
+    (32, 8, 128, [[200] * 100, [200], [200], [200]], [190, 20, 20, 20], False),
+    (32, 8, 128, [[200] * 35, [200] * 45, [200] * 45], [180, 30, 30], True),
+    # ... and the walk of the prompt that has one row tile decides
+    (32, 8, 128, [[200] * 15, [200] * 80], [180, 30], False)])
+def test_contexts_are_turned_where_that_pays(ba, hq, hkv, d, prompts, lqs, turned):
+    """Which contexts of short cached blocks the attention kernel turns itself, by row tiles and by the longest walk; either way the
+    bits of a context re-encoded by hand."""
+    torch = torch_mod()
+    lens = np.array([n for p in prompts for n in p], dtype=np.int32)
+    cu_blk = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    cu_q = np.concatenate([[0], np.cumsum(lqs)]).astype(np.int32)
+    off = (np.cumsum(lens) - lens).astype(np.int32)
+    cu_ctx = np.concatenate([[0], np.cumsum(lens)])[cu_blk].astype(np.int32)
+    T, tq = int(lens.sum()), int(cu_q[-1])
+    gen = torch.Generator(device="cuda").manual_seed(1490)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    k, v, q, kf, vf = draw(T, hkv, d), draw(T, hkv, d), draw(tq, hq, d), draw(tq, hkv, d), draw(tq, hkv, d)
+    heads = ba.Heads(hq, hkv, d, 10000.0)
+    k_ctx = torch.empty_like(k)
+    ba.ba_reencode_positions(heads, k, k_ctx, off, off, lens, None, (off - np.repeat(cu_ctx[:-1], np.diff(cu_blk))).astype(np.int32), ba.REENC_SHIFT)
+    want = gpu_final(ba, heads, q, k_ctx, v, kf, vf, cu_q, cu_ctx)
+    ws = torch.full((ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_blk, lens),), 255, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, float("nan"))
+    ba.ba_final_block_attention_cached(heads, q, k, v, kf, vf, o, None, cu_q, cu_blk, off, lens, None, None, None, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(o, want)
+    table = 2 * hkv * d * np.arange(lens[0])  # (what the workspace begins with where nothing is copied)
+    assert np.array_equal(ws[:4 * int(lens[0])].view(torch.int32).cpu().numpy(), table) == turned
+
+
 @pytest.mark.parametrize("d,hkv,n,layout", [(128, 8, 100, 0), (64, 2, 20, 0), (128, 8, 100, 1)])
 def test_gathered_call_whose_rotated_keys_replace_a_cached_block(ba, d, hkv, n, layout):
     """The query block's rotated keys take the place of a block that the call itself still reads: the context is gathered
