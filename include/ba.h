@@ -329,8 +329,9 @@ size_t ba_final_block_attention_cached_workspace_bytes(const ba_heads *heads, in
  * which changes the order of their sums and nothing else.  What a call cannot do without grows with
  * its tokens alone: a workspace for a call of at least as many tokens (same heads, rope_mode and
  * presence of k_rot_out) is always enough, although the query may name a larger size for a smaller call.
- * Two calls with the same arguments give the same bits.  The same prompt in another batch may differ in
- * the last bits: walks are shared only in calls that leave compute units idle.
+ * Two calls with the same arguments give the same bits.  With up to twelve KV heads the same prompt in another
+ * batch may differ in the last bits: walks are shared only in calls that leave compute units idle.  With more KV heads
+ * none is shared, and a prompt's outputs do not depend on what else the call holds.
  */
 int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, const ba_tensor *k,
                                    const ba_tensor *v, const ba_tensor *o_out,
@@ -362,8 +363,9 @@ size_t ba_block_attention_prompts_workspace_bytes(const ba_heads *heads, int32_t
  * and a workspace for a call of at least as many tokens is always enough.  They can be most of the
  * size the query names: a call of few prompts, which leaves compute units idle, cuts the walks of its
  * key tiles into the more parts (32 over 8 heads of 128, ten blocks of 200 tokens and one of 64: 82 MB
- * for one prompt, 22 of them needed; 43 for two, all needed), up to 256 MB.  As in the forward call a
- * prompt's gradients may differ in the last bits with what else the call holds.
+ * for one prompt, 22 of them needed; 49 for two, 43 needed), up to 256 MB.  A prompt's gradients may
+ * differ in the last bits with what else the call holds; dq only with up to twelve KV heads, as the outputs of
+ * the forward call.
  */
 int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tensor *q,
                                             const ba_tensor *k, const ba_tensor *v,

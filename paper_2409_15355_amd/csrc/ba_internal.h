@@ -196,10 +196,15 @@ constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 // of 20 x 100-300 and 32-128: one 280 / 168, two 336 / 282, at 16 over 8 heads 255 / 120 and 294 / 194; one of 6 x 300-800 and 200-256
 // 238 / 183; 8 over 2 of 64, one of 20 x 100-300 and 200-256 191 / 79.  Parts of 16, 20 and 32 tiles: 170, 169 and 170, 285, 281 and 282;
 // at 64 79 with 16, 85 with 24, 90 with 32.  At most 96, 128 and 256 workgroups: 238, 186 and 182 where 192 take 183.  60 drawn calls of 1 to 6
-// prompts whose walks are as long: 0.48 to 1.01 of the time, 0.85 in the mean.  Not with more than kShareManyHeads KV heads: a prompt of
-// 16 (20 x 200 and 64 tokens, head_dim 64) has the same bits alone and in a batch that fills the chip, and keeps them.
+// prompts whose walks are as long: 0.48 to 1.01 of the time, 0.85 in the mean.
+// With more than kSharePairs / 2 KV heads no walk is cut, whatever the block: one row tile of it is too many pairs for the first rule, and
+// the second goes no further.  So with 13 KV heads and more a prompt's output, log-sum-exps and dq are the same bits in every
+// batch (ba.h says so).  What that costs, prompts of 20 x 200 + 64 tokens, forward and backward, us, as they are / cut: 64 over 16 heads of 64 one
+// 89 and 141 / 42 and 104, two 113 and 207 / 71 and 188; 64 over 16 of 128 121 and 226 / 72 and 187, 154 and 349 / 117 and 346; 32 over 32 of
+// 128 124 and 205 / 74 and 155, 172 and 333 / 120 and 295; four of any of these nothing.  Up to twelve: 48 over 12 of 128 117 and 215 / 65 and
+// 160, 151 and 311 / 100 and 274, four 200 and 529 / 201 and 528.
 constexpr int kShareAbove = 36, kShareChunk = 16, kSharePairs = 24;
-constexpr int kShareManyAbove = 55, kShareManyChunk = 24, kShareManyPairs = 192, kShareManyHeads = 8;
+constexpr int kShareManyAbove = 55, kShareManyChunk = 24, kShareManyPairs = 192;
 constexpr double kShareLoad = 0.64;
 constexpr double kSharePartTiles = 24.0;  // head_dim 128
 constexpr int kShareLead = 100;

@@ -406,7 +406,7 @@ int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads, int many_
   const int64_t pairs = short_row_tiles(len, G) * n_kv_heads;
   if (w <= kShareAbove) return 1;
   if (pairs <= kSharePairs / 2) return shared_walk_splits(w, kShareChunk, (int)pairs, kSharePairs);
-  if (w <= kShareManyAbove || pairs > kShareManyPairs || n_kv_heads > kShareManyHeads) return 1;
+  if (w <= kShareManyAbove || pairs > kShareManyPairs || n_kv_heads > kSharePairs / 2) return 1;
   return shared_walk_splits(w, many_chunk, (int)pairs, kShareManyPairs);
 }
 }  // namespace

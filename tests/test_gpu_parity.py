@@ -1752,7 +1752,8 @@ def test_gradients_at_the_edges_of_key_and_row_tiles(ba, hq, hkv, d, layout):
 SHARED_CASES = [("group1-d64", 2, 2, 64, [[1150, 37], [40, 9]]), ("group3-d128", 6, 2, 128, [[700, 420, 50]]),
                 ("group4-d128", 8, 2, 128, [[30, 5], [1300, 33]]), ("group4-d64", 4, 1, 64, [[1, 1500, 1]]),
                 # more than twelve row tiles times KV heads
-                ("group8-d64-many", 8, 1, 64, [[1600, 200]]), ("group4-d128-many", 4, 1, 128, [[30, 5], [1410, 401]])]
+                ("group8-d64-many", 8, 1, 64, [[1600, 200]]), ("group4-d128-many", 4, 1, 128, [[30, 5], [1410, 401]]),
+                ("twelve-heads-many", 12, 12, 64, [[1690, 140]])]
 
 
 @pytest.mark.parametrize("case", SHARED_CASES, ids=[c[0] for c in SHARED_CASES])

@@ -233,7 +233,7 @@ def test_shared_walks_of_whole_prompts_cover_the_mask_once(hq, hkv, d):
     (32, 8, 128, [1500, 1500, 1500, 260], 2), (32, 8, 128, [1500, 1500, 1500, 400], 1),  # 72 and 104: at most 192 workgroups
     (4, 4, 64, [2000, 2000, 1700], 3), (16, 16, 64, [1500, 1500, 100], 1)])
 def test_walks_of_many_row_tiles_are_shared_from_56_key_tiles_on(hq, hkv, d, prompt, parts):
-    """More than twelve row tiles times KV heads: parts of 24 key tiles (16 at head_dim 64), at most 192 workgroups, at most 8 KV heads; the
+    """More than twelve row tiles times KV heads: parts of 24 key tiles (16 at head_dim 64), at most 192 workgroups, at most twelve KV heads; the
     parts of a row tile partition its walk."""
     h, G = ba.Heads(hq, hkv, d, 10000.0), hq // hkv
     offs = np.concatenate([[0], np.cumsum(prompt)])
@@ -252,6 +252,17 @@ def test_walks_of_many_row_tiles_are_shared_from_56_key_tiles_on(hq, hkv, d, pro
             at = w.ctx_end + w.self_end
         last_tok = (ws[0].row_end - 1) // G
         assert at == min(last + prompt[-1], ((last + last_tok) // 32 + 1) * 32)
+
+
+@pytest.mark.parametrize("hkv", [8, 9, 12, 13, 16, 32])
+@pytest.mark.parametrize("d", [64, 128])
+def test_walks_are_shared_up_to_twelve_kv_heads(hkv, d):
+    """... whatever the last block: with more a prompt is computed the same way in every batch.  With up to twelve, blocks of many row tiles
+    as well as few."""
+    for group, last in ((4, 64), (2, 200), (4, 20), (1, 50)):
+        h, prompt = ba.Heads(hkv * group, hkv, d, 10000.0), [200] * 20 + [last]
+        offs = np.concatenate([[0], np.cumsum(prompt)])
+        assert (max(w.n_splits for w in ba.ba_schedule_prompts(h, [0, 21], offs)) > 1) == (hkv <= 12), (group, last)
 
 
 @pytest.mark.parametrize("hq,hkv,d,prompt,below,above", [(32, 8, 128, [200] * 6 + [20], 4, 5), (16, 8, 128, [200] * 20 + [64], 8, 9),
