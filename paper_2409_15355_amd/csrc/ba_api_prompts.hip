@@ -67,10 +67,10 @@ int32_t ld_group(int32_t group) { return (group + 3) & ~3; }
 
 // Memory of the shared walks (plan_walk_shares); for the padded route what its groups of four want, if that is more.
 size_t shares_bytes(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
-  size_t bytes = ba::plan_walk_shares(h, n_prompts, cu_blk, block_offsets).total();
+  size_t bytes = ba::plan_walk_shares(h, n_prompts, cu_blk, block_offsets, false).total();
   if (h->n_q_heads / h->n_kv_heads < kPadGroup) {
     const ba_heads h4 = padded_heads(h);
-    bytes = std::max(bytes, ba::plan_walk_shares(&h4, n_prompts, cu_blk, block_offsets).total());
+    bytes = std::max(bytes, ba::plan_walk_shares(&h4, n_prompts, cu_blk, block_offsets, false).total());
   }
   return bytes;
 }
@@ -80,7 +80,7 @@ size_t bwd_shares_bytes(const ba::WalkShares &dq, const ba::WalkShares &kv) {
 }
 size_t bwd_shares_bytes(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
   const auto of = [&](const ba_heads *hh) {
-    return bwd_shares_bytes(ba::plan_walk_shares(hh, n_prompts, cu_blk, block_offsets), ba::plan_kv_shares(hh, n_prompts, cu_blk, block_offsets));
+    return bwd_shares_bytes(ba::plan_walk_shares(hh, n_prompts, cu_blk, block_offsets, true), ba::plan_kv_shares(hh, n_prompts, cu_blk, block_offsets));
   };
   size_t bytes = of(h);
   if (h->n_q_heads / h->n_kv_heads < kPadGroup) {
@@ -235,7 +235,7 @@ int32_t ba_block_attention_prompts(const ba_heads *heads, const ba_tensor *q, co
     }
     q_table = (float *)wsp;
     wsp += align256((size_t)T * D * 4);
-    shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
+    shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets, false);
     if ((size_t)(wsp - (char *)ws) + shares.total() > ws_bytes) shares = ba::WalkShares();
     place_shares(shares, wsp, &ap);
     if ((rc = rotate_prompts(heads, rt, q, k, &k_use, n_prompts, cu_blk, block_offsets, stream, q_table, ap.part_idx,
@@ -382,7 +382,7 @@ int32_t ba_block_attention_prompts_backward(const ba_heads *heads, const ba_tens
   wsp += align256((size_t)T * hkv * ld_group(G) * 8 + 16);
   // (what the workspace has room for: the dk/dv kernel's partial results are the larger ones and go first)
   const size_t room = ws_bytes - (size_t)(wsp - (char *)ws);
-  ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
+  ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets, true);
   ba::WalkShares kv_shares = ba::plan_kv_shares(heads, n_prompts, cu_blk, block_offsets);
   if (bwd_shares_bytes(shares, kv_shares) > room) kv_shares = ba::WalkShares();
   if (bwd_shares_bytes(shares, kv_shares) > room) shares = ba::WalkShares();

@@ -203,9 +203,24 @@ constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 // 89 and 141 / 42 and 104, two 113 and 207 / 71 and 188; 64 over 16 of 128 121 and 226 / 72 and 187, 154 and 349 / 117 and 346; 32 over 32 of
 // 128 124 and 205 / 74 and 155, 172 and 333 / 120 and 295; four of any of these nothing.  Up to twelve: 48 over 12 of 128 117 and 215 / 65 and
 // 160, 151 and 311 / 100 and 274, four 200 and 529 / 201 and 528.
+// The dq kernel pays more for a cut (each part reads its q, dO and o rows again) and gains later: where the longest walk is 0.64 to 1.1 of
+// the load, its call took up to 1.15 of the time (8 over 8 heads of 64, ten prompts of 28 x 115 + 268), the forward pass 0.6 to
+// 1.0.  So in calls with such blocks it shares from dq_share_load of the load on, and walks of kShareLongWalk tiles and more are cut into parts of
+// kShareLongChunk (head_dim 128, groups of four and more, four KV heads and more: the fewer parts are as fast in a prompt alone and
+// half the loss among four; 8 over 2 of 128 0.79 -> 0.84, 16 over 8 0.59 -> 0.65).  Backward, shared / unshared, by walk / load (without the parts' own):
+// groups of one and two at 128 0.93 1.04, 1.06 1.01, 1.18 1.02, 1.27 0.96, 1.43 0.99, at 64 0.64 1.08, 0.76 1.15, 0.95 1.00, 1.05 1.04, 1.22 0.95;
+// of four at 128 0.75 to 1.2 0.99 to 1.04 in parts of 24 and 0.99 to 1.02 in parts of 48, 1.28 0.97, at 64 0.71 1.07, 0.77 1.05, 0.79 0.99, 0.81 1.04,
+// 0.85 0.98, 0.90 0.93; of eight 0.45 to 1.0 0.92 to 1.02.  (Four at 128 could begin higher, but a prompt of 20 x 200 + 64 tokens, 0.70 of it
+// alone, has the same bits in dq among four, 0.77 of the load.)
 constexpr int kShareAbove = 36, kShareChunk = 16, kSharePairs = 24;
 constexpr int kShareManyAbove = 55, kShareManyChunk = 24, kShareManyPairs = 192;
+constexpr int kShareLongWalk = 96, kShareLongChunk = 48;
 constexpr double kShareLoad = 0.64;
+constexpr double dq_share_load(int head_dim, int64_t group) {
+  if (group >= 8) return kShareLoad;
+  if (group >= kSmallGroup) return head_dim == 64 ? 0.8 : 0.7;
+  return head_dim == 64 ? 1.1 : 0.86;
+}
 constexpr double kSharePartTiles = 24.0;  // head_dim 128
 constexpr int kShareLead = 100;
 constexpr size_t kShareMaxBytes = (size_t)256 << 20;

@@ -400,24 +400,29 @@ constexpr int kPromptKeys = 32;  // keys per tile of the forward and dq kernels
 int walk_tiles(int64_t keys) { return (int)((keys - 1) / kPromptKeys + 1); }
 int64_t short_row_tiles(int64_t len, int64_t G) { return (len * G + kShortTileRows - 1) / kShortTileRows; }
 // a last block that sees enough of its prompt for more than one workgroup per row tile
-int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads, int many_chunk) {
+int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads, const WalkShares &ws) {
   if (ctx <= 0 || len <= 0) return 1;
   const int w = walk_tiles(ctx + len);
   const int64_t pairs = short_row_tiles(len, G) * n_kv_heads;
   if (w <= kShareAbove) return 1;
   if (pairs <= kSharePairs / 2) return shared_walk_splits(w, kShareChunk, (int)pairs, kSharePairs);
-  if (w <= kShareManyAbove || pairs > kShareManyPairs || n_kv_heads > kSharePairs / 2) return 1;
-  return shared_walk_splits(w, many_chunk, (int)pairs, kShareManyPairs);
+  if (ws.chunk == 0 || w <= kShareManyAbove || pairs > kShareManyPairs || n_kv_heads > kSharePairs / 2) return 1;
+  return shared_walk_splits(w, w >= kShareLongWalk ? ws.long_chunk : ws.chunk, (int)pairs, kShareManyPairs);
 }
-}  // namespace
 
-WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets) {
+// many: last blocks of many row tiles too.
+WalkShares plan_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets, bool dq, bool many) {
   WalkShares ws;
-  ws.chunk = h->head_dim == 128 ? kShareManyChunk : kShareChunk;
   const int64_t G = h->n_q_heads / h->n_kv_heads;
-  const double part_tiles = h->head_dim == 128 ? kSharePartTiles : 0.0;
+  const bool wide = h->head_dim == 128;
+  if (many) {
+    ws.chunk = wide ? kShareManyChunk : kShareChunk;
+    ws.long_chunk = dq && wide && G >= kSmallGroup && h->n_kv_heads >= 4 ? kShareLongChunk : ws.chunk;
+  }
+  const double part_tiles = wide ? kSharePartTiles : 0.0;
   double load = 0.0;  // of the launch with its walks cut, in key tiles
   int longest = 0, longest_left = 0;  // of the walks that would be cut, and of the others
+  bool any_many = false;
   const auto add = [&](int64_t ctx, int64_t len, int s) {
     load += (double)short_row_tiles(len, G) * (((double)ctx + 0.5 * (double)len) / kPromptKeys + 0.5 + kFixedTiles + part_tiles * (s - 1));
     int &most = s > 1 ? longest : longest_left;
@@ -427,15 +432,17 @@ WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t 
     const int last = cu_blk[n + 1] - 1;
     for (int b = cu_blk[n]; b < last; ++b) add(0, block_offsets[b + 1] - block_offsets[b], 1);
     const int64_t len = block_offsets[last + 1] - block_offsets[last], ctx = block_offsets[last] - block_offsets[cu_blk[n]];
-    const int s = shared_splits(ctx, len, G, h->n_kv_heads, ws.chunk);
+    const int s = shared_splits(ctx, len, G, h->n_kv_heads, ws);
     add(ctx, len, s);
     if (s < 2) continue;
     ++ws.n_split;
     ws.items += short_row_tiles(len, G) * s;
+    any_many = any_many || short_row_tiles(len, G) * h->n_kv_heads > kSharePairs / 2;
   }
   load *= h->n_kv_heads / (double)kShareCus;  // ... per compute unit
   const size_t slots = (size_t)ws.items * h->n_kv_heads * (kShortTileRows / 32);
-  if (ws.n_split == 0 || longest < kShareLoad * load) return WalkShares();
+  const double least = dq && any_many ? dq_share_load(h->head_dim, G) : kShareLoad;
+  if (ws.n_split == 0 || longest < least * load) return WalkShares();
   if (longest <= longest_left + longest_left / kShareLead && longest <= 4 * load) return WalkShares();
   // (the tables need the first: the shared blocks are in the first launch's.  With 8 KV heads it would take over 170 prompts, whose
   // load is far beyond the line)
@@ -444,6 +451,12 @@ WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t 
   ws.ml_bytes = slots * 256;
   ws.count_bytes = (size_t)ws.items * h->n_kv_heads * 4;
   return ws;
+}
+}  // namespace
+
+WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets, bool dq) {
+  const WalkShares ws = plan_shares(h, n_prompts, cu_blk, block_offsets, dq, true);
+  return ws.n_split > 0 ? ws : plan_shares(h, n_prompts, cu_blk, block_offsets, dq, false);
 }
 
 namespace {
@@ -531,7 +544,7 @@ int64_t build_kv_meta(const std::vector<PromptBlock> &blks, size_t b0, int n, in
 void sort_by_key_range(std::vector<PromptBlock> *blks, int G, int n_kv_heads, const WalkShares &shares) {
   // (a prompt's last block walks the whole prompt, and a launch should not end on a few of those)
   const auto shared = [&](const PromptBlock &b) {
-    return shares.n_split > 0 && shared_splits(b.start - b.kstart, b.len, G, n_kv_heads, shares.chunk) > 1;
+    return shares.n_split > 0 && shared_splits(b.start - b.kstart, b.len, G, n_kv_heads, shares) > 1;
   };
   std::stable_sort(blks->begin(), blks->end(), [&](const PromptBlock &a, const PromptBlock &b) {
     const bool sa = shared(a), sb = shared(b);
@@ -553,7 +566,7 @@ int64_t build_prompt_meta(const std::vector<PromptBlock> &blks, size_t b0, int n
     meta->kstart[i] = b.kstart;
     meta->pos0[i] = b.pos0;
     meta->tile_start[i] = (int32_t)tiles;
-    tiles += short_row_tiles(b.len, G) * (i < meta->n_split ? shared_splits((int64_t)b.start - b.kstart, b.len, G, n_kv_heads, shares.chunk) : 1);
+    tiles += short_row_tiles(b.len, G) * (i < meta->n_split ? shared_splits((int64_t)b.start - b.kstart, b.len, G, n_kv_heads, shares) : 1);
     if (tiles > 0x3fffffff) return -1;
   }
   meta->tile_start[n] = (int32_t)tiles;
@@ -698,7 +711,7 @@ int64_t ba_schedule_prompts(const ba_heads *heads, int32_t n_prompts, const int3
   if ((rc = ba::check_heads(heads, true))) return rc;
   if ((rc = ba::check_prompt_blocks(n_prompts, cu_blk, block_offsets))) return rc;
   const int G = heads->n_q_heads / heads->n_kv_heads;
-  const ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets);
+  const ba::WalkShares shares = ba::plan_walk_shares(heads, n_prompts, cu_blk, block_offsets, false);
   std::vector<ba::PromptBlock> blks = ba::list_prompt_blocks(n_prompts, cu_blk, block_offsets);
   ba::sort_by_key_range(&blks, G, heads->n_kv_heads, shares);
   ba::ItemSink sink{items, items ? max_items : 0};
@@ -715,7 +728,7 @@ int64_t ba_schedule_prompts(const ba_heads *heads, int32_t n_prompts, const int3
       const int n_rows = lq * G;
       if (i < meta.n_split) {
         const int n_rt = (n_rows + ba::kShortTileRows - 1) / ba::kShortTileRows;
-        n_splits = ba::shared_splits(dq, lq, G, heads->n_kv_heads, shares.chunk);
+        n_splits = ba::shared_splits(dq, lq, G, heads->n_kv_heads, shares);
         split = jt / n_rt;
         jt -= split * n_rt;
       }

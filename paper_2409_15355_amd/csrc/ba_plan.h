@@ -110,12 +110,14 @@ std::vector<PromptBlock> list_prompt_blocks(int32_t n_prompts, const int32_t *cu
 // Which last blocks have their walks shared by several workgroups (PromptMeta::n_split), and the memory that takes.
 struct WalkShares {
   int n_split = 0;
-  int chunk = 1;      // tiles per workgroup (forward, dq: of blocks with many row tiles; dk/dv: of any)
+  int chunk = 0;      // tiles per workgroup (forward, dq: of blocks with many row tiles, 0: not cut; dk/dv: of any)
+  int long_chunk = 0;  // ... of such blocks that walk kShareLongWalk tiles and more
   int64_t items = 0;  // (row tile, split) pairs of those blocks
   size_t part_bytes = 0, ml_bytes = 0, count_bytes = 0;
   size_t total() const { return align256(part_bytes) + align256(ml_bytes) + align256(count_bytes); }
 };
-WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets);
+// dq: of the dq kernel, else of the forward kernel.
+WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets, bool dq);
 // The same for the dk/dv kernel (BwdKvMeta::n_split): items are (key tile, split) entries.
 WalkShares plan_kv_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets);
 // ... in the order the forward and dq kernels take them: those of shared walks, then longest key range first

@@ -265,6 +265,30 @@ def test_walks_are_shared_up_to_twelve_kv_heads(hkv, d):
         assert (max(w.n_splits for w in ba.ba_schedule_prompts(h, [0, 21], offs)) > 1) == (hkv <= 12), (group, last)
 
 
+@pytest.mark.parametrize("hq,hkv,d,prompt,most", [
+    # groups of four: from 0.7 of the load on at head_dim 128, 0.8 at 64 (the forward pass: 0.64)
+    (32, 8, 128, [200] * 20 + [64], 4), (32, 8, 64, [200] * 20 + [64], 3),
+    # of one and two from 0.86 and from 1.1 on, of eight as the forward pass
+    (16, 8, 128, [200] * 20 + [100], 4), (8, 8, 64, [115] * 28 + [268], 6), (16, 2, 64, [200] * 20 + [150], 7),
+    # up to twelve KV heads
+    (48, 12, 128, [200] * 20 + [64], 2), (52, 13, 128, [200] * 20 + [64], 0), (64, 16, 64, [200] * 20 + [64], 0)])
+def test_the_dq_kernel_shares_walks_of_many_row_tiles_by_a_line_of_its_own(hq, hkv, d, prompt, most):
+    """Of up to how many such prompts a backward call shares the walks: what its query names beyond what the call cannot do without is the
+    partial results (the dk/dv kernel alone asks for none in calls of these prompts)."""
+    up = lambda n: (n + 255) // 256 * 256
+
+    def least(T):
+        padded, g = 0, hq // hkv
+        if g < 4:
+            padded, g = 4 * up(T * hkv * 4 * d * 2) + up(T * hkv * 16), 4
+        return padded + up(T * hkv * g * d * 2) + up(T * hkv * d * 2) + up(T * d * 4) + up(T * hkv * ((g + 3) // 4 * 4) * 8 + 16)
+
+    for n in range(1, 11):
+        offs = np.concatenate([[0], np.cumsum(prompt * n)])
+        size = ba.ba_block_attention_prompts_backward_workspace_bytes(ba.Heads(hq, hkv, d, 10000.0), np.arange(n + 1) * len(prompt), offs)
+        assert (size > least(int(offs[-1]))) == (n <= most), n
+
+
 @pytest.mark.parametrize("hq,hkv,d,prompt,below,above", [(32, 8, 128, [200] * 6 + [20], 4, 5), (16, 8, 128, [200] * 20 + [64], 8, 9),
                                                          (4, 4, 64, [200] * 6 + [20], 24, 32)])
 def test_walks_are_shared_only_where_the_call_leaves_the_chip_idle(hq, hkv, d, prompt, below, above):
