@@ -12,8 +12,11 @@
 #include <numpy/arrayobject.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cxxabi.h>
+
 #include <algorithm>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "../../include/ba.h"
@@ -172,24 +175,40 @@ void *stream_of(PyObject *o) {
   return s;
 }
 
+// An exception out of the library: its call may have launched something, so it is an error and never "not the plain case".
+struct Threw {
+  bool memory;
+};
 // body() makes the call and returns its status.
 template <typename Body>
 PyObject *guarded(Py_ssize_t n, Py_ssize_t want, Body &&body) {
-  if (n == want) {
-    try {
-      return PyLong_FromLong(body());
-    } catch (...) {
-      PyErr_Clear();  // (the Python function meets the same argument again and raises what there is to raise)
-    }
+  if (n != want) Py_RETURN_NONE;
+  try {
+    return PyLong_FromLong(body());
+  } catch (const Threw &t) {
+    PyErr_SetString(t.memory ? PyExc_MemoryError : PyExc_RuntimeError, "an exception inside the library");
+    return nullptr;
+  } catch (abi::__forced_unwind &) {  // (a thread that ends with the interpreter, waiting for its lock)
+    throw;
+  } catch (...) {
+    PyErr_Clear();  // (the Python function meets the same argument again and raises what there is to raise)
   }
   Py_RETURN_NONE;
 }
 template <typename Call>
 int32_t unlocked(Call &&call) {
-  int32_t rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = call();
-  Py_END_ALLOW_THREADS
+  int32_t rc = 0;
+  int threw = 0;
+  PyThreadState *const state = PyEval_SaveThread();
+  try {
+    rc = call();
+  } catch (const std::bad_alloc &) {
+    threw = 2;
+  } catch (...) {
+    threw = 1;
+  }
+  PyEval_RestoreThread(state);
+  if (threw) throw Threw{threw == 2};
   return rc;
 }
 
