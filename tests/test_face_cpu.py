@@ -1,12 +1,44 @@
-"""The Python face's native half where there is no GPU: exceptions out of the library."""
+"""The Python face's native half where there is no GPU: arguments that it leaves to the Python functions, exceptions out of the
+library."""
 import os
 import subprocess
 import sys
+import time
+
+import numpy as np
+import pytest
+
+from paper_2409_15355_amd import binding as ba
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CALLS = {"encode_blocks": (10, 6), "reencode_positions": (10, 3), "final_block": (14, 8), "final_block_static": (13, 8),
+         "final_block_cached": (18, 8), "prompts": (12, 7), "prompts_backward": (14, 10)}  # arguments, the first array
+
 
 def run(code, *args):
     return subprocess.run([sys.executable, "-W", "always", "-c", code, *map(str, args)], cwd=ROOT, capture_output=True, text=True, timeout=300)
+
+
+@pytest.mark.parametrize("call", CALLS)
+@pytest.mark.parametrize("array", [[0, 100], np.array([0, 100]), np.array([0, 7, 100], dtype=np.int32)[::2], (0, 100)])
+def test_lists_and_other_arrays_are_left_to_the_python_function_without_an_exception(call, array):
+    """Looking at them costs a few calls of nothing, not the microseconds of a C++ exception (some forty of them)."""
+    n_args, at = CALLS[call]
+    take = getattr(ba._face(), call)
+    heads = ba.Heads(8, 2, 64)
+    args = [heads] + [None] * (at - 1) + [array] + [None] * (n_args - at - 1)
+    assert take(*args) is None
+
+    def once(*a):
+        best = float("inf")
+        for _ in range(20):
+            t = time.perf_counter()
+            for _ in range(200):
+                take(*a)
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    assert once(*args) < 12 * once()  # (no arguments: refused at once)
 
 
 def test_an_exception_inside_the_library_is_raised(tmp_path):
