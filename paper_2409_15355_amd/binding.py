@@ -77,10 +77,8 @@ def load():
     # PyTorch ships its own HIP runtime; the process must use exactly one, and the device
     # memory handed to this library is torch's, so torch's runtime has to be loaded first.
     import torch  # noqa: F401
-    for path in (LIB_PATH, FACE_PATH):
-        if not os.path.exists(path):
-            raise ImportError(f"{path} is missing: build it with `python -m paper_2409_15355_amd.build`")
-    from . import _face
+    if not os.path.exists(LIB_PATH):
+        raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2409_15355_amd.build`")
     lib = ctypes.CDLL(LIB_PATH)
     lib.ba_version.restype = ctypes.c_int32
     lib.ba_status_string.restype = ctypes.c_char_p
@@ -148,13 +146,43 @@ def load():
                                                ctypes.c_size_t, ctypes.c_void_p]
     lib.ba_measure_xcd_speed_workspace_bytes.restype = ctypes.c_size_t
     lib.ba_measure_xcd_speed_workspace_bytes.argtypes = []
-    _face.setup(Heads, getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None),
-                tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in
-                      ("ba_encode_blocks", "ba_reencode_positions", "ba_final_block_attention", "ba_final_block_attention_static",
-                       "ba_final_block_attention_cached", "ba_block_attention_prompts", "ba_block_attention_prompts_backward")))
-    _native = _face
+    _native = _load_native(lib)
     _lib = lib
     return lib
+
+
+class _NoNative:
+    """Stands in for the native half: no argument is the plain case, the functions below take all of them apart."""
+
+    def __getattr__(self, name):
+        return self._take
+
+    @staticmethod
+    def _take(*args):
+        return None
+
+
+def _load_native(lib):
+    """csrc/face.cpp as a module, if it was built (it needs the headers of torch and NumPy) and for the torch that is here."""
+    import torch
+    why = f"{FACE_PATH} is missing"
+    if os.path.exists(FACE_PATH):
+        try:
+            from . import _face
+        except ImportError as e:
+            why = str(e)
+        else:
+            built_for = getattr(_face, "torch_version", "another")
+            if torch.__version__.split("+")[0] == built_for:
+                _face.setup(Heads, getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None),
+                            tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in
+                                  ("ba_encode_blocks", "ba_reencode_positions", "ba_final_block_attention", "ba_final_block_attention_static",
+                                   "ba_final_block_attention_cached", "ba_block_attention_prompts", "ba_block_attention_prompts_backward")))
+                return _face
+            why = f"it was built for torch {built_for}, this is {torch.__version__}"
+    import warnings
+    warnings.warn(f"calls take their arguments apart in Python, some microseconds each: no native half ({why})", RuntimeWarning, stacklevel=3)
+    return _NoNative()
 
 
 def _face():

@@ -1,6 +1,7 @@
 """The Python face's native half where there is no GPU: arguments that it leaves to the Python functions, exceptions out of the
-library."""
+library, and a package without it or with one for another torch."""
 import os
+import shutil
 import subprocess
 import sys
 import time
@@ -64,3 +65,33 @@ for name, kind in (("memory", MemoryError), ("other", RuntimeError)):
             print("raised")
 """, lib)
     assert r.returncode == 0 and r.stdout.split("\n")[:-1] == ["raised"] * 6, (r.returncode, r.stdout, r.stderr)
+
+
+USE = """
+import sys
+sys.path.insert(0, sys.argv[1])
+import numpy as np, torch
+if len(sys.argv) > 2:
+    torch.__version__ = sys.argv[2]
+from paper_2409_15355_amd import binding as ba
+heads, q = ba.Heads(4, 4, 64), torch.zeros((4, 4, 64), dtype=torch.bfloat16)
+assert ba.ba_encode_blocks_workspace_bytes(heads, [0, 4]) > 0 and ba._face().prompts() is None
+try:
+    ba.ba_encode_blocks(heads, q, q, q, q, None, np.array([0, 4], dtype=np.int32))
+except ValueError as e:
+    print(type(ba._face()).__name__, "|", e)
+"""
+
+
+def test_the_package_works_without_its_native_half(tmp_path):
+    pkg = tmp_path / "paper_2409_15355_amd"
+    shutil.copytree(os.path.join(ROOT, "paper_2409_15355_amd"), pkg, ignore=shutil.ignore_patterns("_face.so", "_build", "csrc", "__pycache__"))
+    r = run(USE, tmp_path)
+    assert r.returncode == 0 and "_NoNative | q: expected a tensor in GPU memory" in r.stdout and "is missing" in r.stderr, (r.stdout, r.stderr)
+
+
+def test_a_native_half_for_another_torch_is_left_alone():
+    r = run(USE, ROOT, "1.2.3+x")
+    assert r.returncode == 0 and "_NoNative | q: expected" in r.stdout and "this is 1.2.3+x" in r.stderr, (r.stdout, r.stderr)
+    r = run(USE, ROOT)
+    assert r.returncode == 0 and "module | q: expected" in r.stdout and "RuntimeWarning" not in r.stderr, (r.stdout, r.stderr)
