@@ -465,8 +465,9 @@ int32_t final_block(const ba_heads *heads, const ba_tensor *q_f, const ba_tensor
   ap.n_splits = pl.n_splits;
   ap.wg_clock = ba::probe_clock();  // (null unless a probe of ba_probe.hip is the caller)
 
-  // (rotated keys as an output, rows of q further apart than 32-bit offsets, outputs that lie over what is read: by the pre-pass)
-  const bool fresh_ok = rope_mode == BA_ROPE_APPLY && !gather && !k_f_rot_out && !ap.wg_clock && q_f->stride_tok <= 1 << 24 && k_f->stride_tok <= 1 << 24 &&
+  // (rotated keys as an output, heads of q further apart than 32-bit offsets reach, outputs that lie over what is read: by the pre-pass;
+  // 32 tokens are within 2^30 bytes in any call, see check_tensor)
+  const bool fresh_ok = rope_mode == BA_ROPE_APPLY && !gather && !k_f_rot_out && !ap.wg_clock &&
                         32 * q_f->stride_tok * 2 + (int64_t)G * q_f->stride_head * 2 < (int64_t)1 << 32 &&
                         fresh_apart(q_f, k_f, o_out, cu_q[0], cu_q[n_prompts], heads);
   int64_t tile_base = 0;  // row tiles of the launches so far: the split partials are indexed by row tile
@@ -731,10 +732,9 @@ int32_t ba_encode_blocks(const ba_heads *heads, const ba_tensor *q, const ba_ten
     int64_t tiles[2];
     if ((rc = ba::build_encode_metas(block_offsets, b0, n, G, short_max, meta, tiles))) return rc;
     if (tiles[0] + tiles[1] == 0) continue;
-    // a small call of short blocks: one launch, the attention kernel turns rows and keys itself (its tile copies reach 32 rows of
-    // keys with 32-bit offsets; the pre-pass takes any stride)
+    // a small call of short blocks: one launch, the attention kernel turns rows and keys itself
     if (rope_mode == BA_ROPE_APPLY && n == n_blocks && tiles[0] == 0 && tiles[1] * heads->n_kv_heads <= (int64_t)num_cus() * ba::encode_fresh_per_cu(D, longest_block) &&
-         k->stride_tok <= 1 << 24 && fresh_apart(q, k, o_out, block_offsets[0], T, heads) &&
+        fresh_apart(q, k, o_out, block_offsets[0], T, heads) &&
         (!k_local_out || encode_keys_apart(heads, q, k, v, o_out, k_local_out, T))) {
       ba::EncodeFreshMeta fm;
       memset(&fm, 0, sizeof(fm));

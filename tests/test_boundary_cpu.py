@@ -268,6 +268,21 @@ def test_a_workspace_for_a_batch_of_prompts_is_enough_for_every_smaller_call(lib
                     assert needed(backward, cb1, of1) <= sized[backward], (prompt, n_prompts, of1[-1], backward)
 
 
+def test_token_strides_beyond_32_bit_offsets_are_refused(lib):
+    """... for every tensor of a call, so that no route has to ask again."""
+    h, t, far = ba.Heads(8, 2, 128), fake(), fake(st=1 << 24)
+    last = fake(st=(1 << 24) - 8)
+    for i in range(4):
+        assert call_encode(lib, h, *[far if i == j else t for j in range(4)], None, [0, 4]) == -2
+        assert b"token stride" in lib.ba_last_error()
+    assert call_encode(lib, h, t, t, t, t, far, [0, 4]) == -2
+    assert call_encode(lib, h, t, last, last, t, None, [0, 4]) == -4  # (taken: the workspace is missing)
+    cu = (ctypes.c_int32 * 2)(0, 4)
+    for i in range(7):
+        args = [ctypes.byref(far if i == j else t) for j in range(7)]
+        assert lib.ba_final_block_attention(ctypes.byref(h.c), *args, 1, cu, cu, None, 1, None, 0, None) == -2
+
+
 def test_header_is_plain_c(tmp_path):
     """include/ba.h is the boundary of a C-ABI library: a C99 compiler takes it as it is, with
     warnings as errors, and the structs it declares have the layout the Python face assumes."""
