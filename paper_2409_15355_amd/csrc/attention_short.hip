@@ -52,7 +52,7 @@ struct SGeo {
   static constexpr int IPW = kSKeys / RPI / kSWaves;  // such instructions per wave, tile and kind
   static constexpr size_t LDS = (size_t)2 * kSBuf * TILEB;
   static_assert(IPW >= 1, "every wave takes part in a tile copy");
-  static_assert(LDS == (size_t)6 * 32 * D * 2, "as encode_fresh_per_cu has it");
+  static_assert(LDS == (size_t)6 * 32 * D * 2 && kSWaves == 4, "as encode_fresh_per_cu has it");
   static_assert((size_t)kSWaves * 32 * ROWB + 16 <= LDS, "the output staging must fit the tile buffers, and a word behind it");
 };
 
@@ -69,7 +69,7 @@ struct SharedPromptMeta : PromptMeta {
 // kAsCore: the numbers of the main core (the reference from the first 64 keys, sums by 64 keys).
 // kPast: rows of q and o go past the caches (see kCacheBytes).
 template <int D, typename Meta, bool kAsCore, bool kPast>
-__global__ __launch_bounds__(kSThreads, (std::is_same<Meta, EncodeFreshMeta>::value ? 2 : 3)) void encode_short_kernel(AttnParams p, Meta meta) {
+__global__ __launch_bounds__(kSThreads, (std::is_same<Meta, EncodeFreshMeta>::value ? encode_fresh_by_registers(D) : 3)) void encode_short_kernel(AttnParams p, Meta meta) {
   using G = SGeo<D>;
   constexpr bool kPrompt = std::is_base_of<PromptMeta, Meta>::value, kShared = std::is_same<Meta, SharedPromptMeta>::value;
   constexpr bool kFresh = std::is_same<Meta, EncodeFreshMeta>::value;  // query rows and keys as the caller gave them

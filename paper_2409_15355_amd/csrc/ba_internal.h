@@ -481,10 +481,11 @@ constexpr int kEncFreshLds = 52 * 1024;
 // Workgroups that a compute unit holds at once, by registers and LDS; none if the table is too large.  Beyond one round every further one
 // works its factors out again.  Pre-pass / here, one round and more than one: 32 over 8 of 128, 20 and 40 blocks of 64 15.5 / 13.5 and
 // 19.8 / 20.7 us, 8 and 12 of 100 13.8 / 12.3 and 15.6 / 20.1; 4 over 4 of 64, 200 of 32 13.2 / 8.4, 80 of 128 16.1 / 13.3, 80 of 200 19.0 / 25.9.
+constexpr int encode_fresh_by_registers(int head_dim) { return head_dim == 128 ? 2 : 4; }  // (a wave a SIMD each; the kernel's launch bounds)
 constexpr int encode_fresh_per_cu(int head_dim, int64_t longest) {
   const int64_t table = longest * head_dim * 4, tiles = 6 * 32 * head_dim * 2;  // (three tiles of 32 keys and values)
   if (table > kEncFreshLds) return 0;
-  const int64_t by_lds = (160 * 1024) / (tiles + table), by_registers = head_dim == 128 ? 2 : 4;
+  const int64_t by_lds = (160 * 1024) / (tiles + table), by_registers = encode_fresh_by_registers(head_dim);
   return (int)(by_lds < by_registers ? by_lds : by_registers);
 }
 struct EncodeFreshMeta : EncodeMeta {

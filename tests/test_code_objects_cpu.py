@@ -33,3 +33,12 @@ def test_no_kernel_asks_for_scratch():
     kernels = kernel_notes()
     assert sum("attn_kernel" in name for name, _ in kernels) >= 10
     assert [(name, k[".private_segment_fixed_size"]) for name, k in kernels if k[".private_segment_fixed_size"]] == []
+
+
+def test_small_encodes_fit_a_compute_unit_as_often_as_their_rule_reckons():
+    """One launch per block row and KV head, a wave a SIMD each: four workgroups to a compute unit at head_dim 64, two at 128."""
+    fresh = [(name, k) for name, k in kernel_notes() if "encode_short_kernel" in name and "EncodeFreshMeta" in name]
+    assert len(fresh) == 4
+    for name, k in fresh:
+        most = 128 if "ILi64E" in name else 256
+        assert k[".vgpr_count"] <= most and k[".max_flat_workgroup_size"] == 256, (name, k[".vgpr_count"])
