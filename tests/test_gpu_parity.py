@@ -2061,6 +2061,59 @@ def test_shared_walks_and_gathered_contexts_can_be_captured_in_a_hip_graph(ba):
         torch.cuda.synchronize()
 
 
+def test_calls_without_a_pre_pass_can_be_captured_in_a_hip_graph(ba):
+    """The calls that turn rows and keys in the attention kernel -- a large context of short cached blocks, a final block of few
+    tokens, a small per-block encoding: every replay gives the eager bits, with eager calls in between."""
+    torch = torch_mod()
+    heads = ba.Heads(32, 8, 128, 10000.0)
+    gen = torch.Generator(device="cuda").manual_seed(811)
+    draw = lambda n, h: torch.randn((n, h, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    lens = np.array([40, 7, 130, 61] * 50, dtype=np.int32)
+    T = int(lens.sum())
+    off = (np.cumsum(lens) - lens).astype(np.int32)
+    cu_q, cu_b, cu_ctx = (np.array([0, n], dtype=np.int32) for n in (30, len(lens), 3000))
+    offs = np.array([0, 30], dtype=np.int32)
+    q, kf, vf, kc, vc = draw(30, 32), draw(30, 8), draw(30, 8), draw(T, 8), draw(T, 8)
+    o_c, o_f, o_e, k_local = torch.empty_like(q), torch.empty_like(q), torch.empty_like(q), torch.empty_like(kf)
+    ws_c = dirty(ba.ba_final_block_attention_cached_workspace_bytes(heads, cu_q, cu_b, lens))
+    ws_f = dirty(ba.ba_final_block_attention_workspace_bytes(heads, cu_q, cu_ctx))
+    ws_e = dirty(ba.ba_encode_blocks_workspace_bytes(heads, offs, ba.ROPE_APPLY, True))
+    outs = (o_c, o_f, o_e, k_local)
+
+    def calls():
+        ba.ba_final_block_attention_cached(heads, q, kc, vc, kf, vf, o_c, None, cu_q, cu_b, off, lens, None, None, None, ws_c)
+        ba.ba_final_block_attention(heads, q, kc, vc, kf, vf, o_f, None, cu_q, cu_ctx, None, ba.ROPE_APPLY, ws_f)
+        ba.ba_encode_blocks(heads, q, kf, vf, o_e, k_local, offs, ba.ROPE_APPLY, ws_e)
+
+    ba.ba_profile_begin()
+    calls()
+    torch.cuda.synchronize()
+    assert ba.ba_profile_end()[1][ba.PROFILE_REENCODE] == 1  # (the tables of the first)
+    assert np.array_equal(ws_c[:4 * int(lens[0])].view(torch.int32).cpu().numpy(), 2048 * np.arange(lens[0]))  # nothing was copied
+    want = [t.clone() for t in outs]
+    assert all(bool(torch.isfinite(t.float()).all()) for t in want)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    for rep in range(3):
+        for t in outs:
+            t.zero_()
+        for ws in (ws_c, ws_f, ws_e):
+            ws.fill_(255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, ref in zip(outs, want):
+            assert torch.equal(got, ref), f"replay {rep}"
+        calls()
+        torch.cuda.synchronize()
+
+
 def test_whole_prompts_forward_and_backward_on_strided_views(ba):
     """q, k, v as views into one fused [T, Hq + 2 Hkv, D] projection buffer, the gradients written
     into views of a buffer of the same shape, o and d_out with padded head strides: every tensor of
@@ -2711,36 +2764,50 @@ def test_plain_and_converted_arguments_make_the_same_call(ba, monkeypatch):
 def test_final_blocks_of_few_tokens_turn_their_own_rows(ba, hq, hkv, d, lqs, ctxs, layout):
     """One row tile and one key tile of its own per prompt: the attention kernel turns q and k_f itself (64 tokens at most,
     256 packed rows; the last two shapes are beyond).  The bits of the call that also returns the rotated keys, which runs the
-    pre-pass; strided rows, given positions, the output over the queries, and over half of the keys (the pre-pass again)."""
+    pre-pass; strided rows, given positions, splits sized by XCD speeds, the output over the queries, and over half of the keys
+    (the pre-pass again).  Which route ran: the launches counted as position encoding."""
     torch = torch_mod()
     cu_q = np.concatenate([[0], np.cumsum(lqs)]).astype(np.int32)
     cu_ctx = np.concatenate([[0], np.cumsum(ctxs)]).astype(np.int32)
     tq, tc = int(cu_q[-1]), int(cu_ctx[-1])
-    heads = ba.Heads(hq, hkv, d, 10000.0, rope_layout=layout)
+    pre_pass = 0 if max(lqs) <= 64 and max(lqs) * (hq // hkv) <= 256 else 1
     gen = torch.Generator(device="cuda").manual_seed(17)
     wide = torch.randn((tq + 1, hq + 3 * hkv, d), generator=gen, device="cuda").to(torch.bfloat16)
     q, kf, vf = wide[:tq, :hq], wide[:tq, hq:hq + hkv], wide[:tq, hq + hkv:hq + 2 * hkv]
     kc, vc = (torch.randn((max(tc, 1), hkv, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
     ws = lambda rot: torch.full((max(256, ba.ba_final_block_attention_workspace_bytes(heads, cu_q, cu_ctx, 1, rot)),), 255, dtype=torch.uint8, device="cuda")
-    for pos in (None, np.array([100000 + 7 * i for i in range(len(lqs))], dtype=np.int32)):
-        k_rot = torch.empty((tq, hkv, d), dtype=torch.bfloat16, device="cuda")
-        want, got = (torch.full((tq, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
-        ba.ba_final_block_attention(heads, q, kc, vc, kf, vf, want, k_rot, cu_q, cu_ctx, pos, 1, ws(True))
-        for _ in range(2):
-            ba.ba_final_block_attention(heads, q, kc, vc, kf, vf, got, None, cu_q, cu_ctx, pos, 1, ws(False))
-            assert torch.equal(got, want)
-        over = q.clone()
-        ba.ba_final_block_attention(heads, over, kc, vc, kf, vf, over, None, cu_q, cu_ctx, pos, 1, ws(False))
-        assert torch.equal(over, want)
-    both = torch.zeros((tq + 8, hq, d), dtype=torch.bfloat16, device="cuda")  # o and, in its memory, the keys
-    inside = both.view(-1)[:tq * hkv * d].view(tq, hkv, d)
-    inside.copy_(kf)
-    ba.ba_final_block_attention(heads, q, kc, vc, inside, vf, both[:tq], None, cu_q, cu_ctx, pos, 1, ws(False))
-    assert torch.equal(both[:tq], want)
+
+    def final(launches, q, k_ctx, v_ctx, k, v, o, rot, pos):
+        room = ws(rot is not None)
+        ba.ba_profile_begin()
+        ba.ba_final_block_attention(heads, q, k_ctx, v_ctx, k, v, o, rot, cu_q, cu_ctx, pos, 1, room)
+        torch.cuda.synchronize()
+        assert ba.ba_profile_end()[1][ba.PROFILE_REENCODE] == launches
+
+    for speed in (None, [1.0, 0.8, 1.2, 0.9, 1.1, 1.0, 0.7, 1.3]):
+        heads = ba.Heads(hq, hkv, d, 10000.0, rope_layout=layout, xcd_speed=speed)
+        if speed and tc > 6000 and hkv <= 8:
+            shares = {w.n_splits: w for w in ba.ba_schedule_final_block(heads, cu_q, cu_ctx)}
+            assert max(shares) > 1  # (so that there is something to size)
+        for pos in (None, np.array([100000 + 7 * i for i in range(len(lqs))], dtype=np.int32)):
+            k_rot = torch.empty((tq, hkv, d), dtype=torch.bfloat16, device="cuda")
+            want, got = (torch.full((tq, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+            final(1, q, kc, vc, kf, vf, want, k_rot, pos)
+            for _ in range(2):
+                final(pre_pass, q, kc, vc, kf, vf, got, None, pos)
+                assert torch.equal(got, want)
+            over = q.clone()
+            final(pre_pass, over, kc, vc, kf, vf, over, None, pos)
+            assert torch.equal(over, want)
+        both = torch.zeros((tq + 8, hq, d), dtype=torch.bfloat16, device="cuda")  # o and, in its memory, the keys
+        inside = both.view(-1)[:tq * hkv * d].view(tq, hkv, d)
+        inside.copy_(kf)
+        final(1, q, kc, vc, inside, vf, both[:tq], None, pos)
+        assert torch.equal(both[:tq], want)
     if tc < 6000:
         bits = lambda t: host_bits(t.contiguous())
         f = oracle.bf16_bits_to_f64
         got.fill_(float("nan"))
-        ba.ba_final_block_attention(heads, q, kc, vc, kf, vf, got, None, cu_q, cu_ctx, None, 1, ws(False))
+        final(pre_pass, q, kc, vc, kf, vf, got, None, None)
         ref = oracle.final_block(f(bits(q)), f(bits(kc[:tc])), f(bits(vc[:tc])), f(bits(kf)), f(bits(vf)), cu_q, cu_ctx, oracle.theta(10000.0, d), layout=layout)
         assert_attention_close(host_f64(got), ref)
