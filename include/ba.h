@@ -280,8 +280,8 @@ int32_t ba_final_block_attention_static(const ba_heads *heads, const ba_tensor *
  * copy of the context an amount per token; when the mean length of the call's non-empty blocks is
  * below this many tokens (BA_GATHER_DEFAULT = 256 tokens; 0 = never gather) the call gathers the
  * context into its workspace first (keys re-encoded on the way, a few MB of values copied, more of
- * them read from where they lie; the cache itself stays as it is) and continues as ba_final_block_attention; of some tens of MB nothing
- * is copied, the keys are re-encoded as they arrive, with the same bits.  Same results either way, to
+ * them read from where they lie; the cache itself stays as it is) and continues as ba_final_block_attention; of some tens of MB, under
+ * few query tokens, nothing is copied, the keys are re-encoded as they arrive, with the same bits.  Same results either way, to
  * rounding.  The two routes need different workspaces: pass the same value to the size query.
  * At most 1024 non-empty blocks per prompt when the kernel reads the block table
  * (BA_ERR_UNSUPPORTED beyond); no such limit on the gathered route.

@@ -546,12 +546,12 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
 //   S = q^ K^^T - L,  dP = dO V^T - delta,  P = 2^S,  dS = P o dP,  dV^T += dO^T P,  dK^^T += q^^T dS
 // from its own registers and the tile, with one barrier.  (Waves of 32 keys have no registers left to look ahead with, two to a SIMD:
 // 370 us.  Split between a pair of waves, S and dV here, dP and dK^ there, with P handed over through LDS behind a
-// second barrier: 325.)  Each fragment of a tile feeds half as many products as with 32 keys, so LDS is read twice as much, 44 %
+// second barrier: 320.)  Each fragment of a tile feeds half as many products as with 32 keys, so LDS is read twice as much, 44 %
 // of the time: the price of doing without the exchange.
 // Eight prompts of 20 passages of 100 to 300 tokens and a query block (33,746 tokens, 32 query heads over 8 of
 // 128, 208 GFLOP in four products): 320 -> 285 us, forward and backward 940 -> 903; 32 over 8 of 64 524 -> 486; two
 // prompts there 282 -> 270.  990 MB read (q^ and dO once are 553), 138 written.  What is left is waiting, 38 % of the waves' time for
-// memory and at barriers and 27 % to issue; a third tile buffer, which now fits three workgroups, changes nothing.
+// memory and at barriers and 30 % to issue; a third tile buffer, which now fits three workgroups, changes nothing.
 template <int D>
 struct KvGeo {
   static constexpr int KK = D / 32;                   // k-steps of the products over head_dim

@@ -410,8 +410,8 @@ int shared_splits(int64_t ctx, int64_t len, int64_t G, int n_kv_heads, const Wal
   return shared_walk_splits(w, w >= kShareLongWalk ? ws.long_chunk : ws.chunk, (int)pairs, kShareManyPairs);
 }
 
-// many: last blocks of many row tiles too.
-WalkShares plan_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets, bool dq, bool many) {
+// many: last blocks of many row tiles too; any_many: whether the call has any.
+WalkShares plan_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets, bool dq, bool many, bool *any_many) {
   WalkShares ws;
   const int64_t G = h->n_q_heads / h->n_kv_heads;
   const bool wide = h->head_dim == 128;
@@ -422,7 +422,7 @@ WalkShares plan_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_b
   const double part_tiles = wide ? kSharePartTiles : 0.0;
   double load = 0.0;  // of the launch with its walks cut, in key tiles
   int longest = 0, longest_left = 0;  // of the walks that would be cut, and of the others
-  bool any_many = false;
+  *any_many = false;
   const auto add = [&](int64_t ctx, int64_t len, int s) {
     load += (double)short_row_tiles(len, G) * (((double)ctx + 0.5 * (double)len) / kPromptKeys + 0.5 + kFixedTiles + part_tiles * (s - 1));
     int &most = s > 1 ? longest : longest_left;
@@ -437,11 +437,11 @@ WalkShares plan_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_b
     if (s < 2) continue;
     ++ws.n_split;
     ws.items += short_row_tiles(len, G) * s;
-    any_many = any_many || short_row_tiles(len, G) * h->n_kv_heads > kSharePairs / 2;
+    *any_many = *any_many || short_row_tiles(len, G) * h->n_kv_heads > kSharePairs / 2;
   }
   load *= h->n_kv_heads / (double)kShareCus;  // ... per compute unit
   const size_t slots = (size_t)ws.items * h->n_kv_heads * (kShortTileRows / 32);
-  const double least = dq && any_many ? dq_share_load(h->head_dim, G) : kShareLoad;
+  const double least = dq && *any_many ? dq_share_load(h->head_dim, G) : kShareLoad;
   if (ws.n_split == 0 || longest < least * load) return WalkShares();
   if (longest <= longest_left + longest_left / kShareLead && longest <= 4 * load) return WalkShares();
   // (the tables need the first: the shared blocks are in the first launch's.  With 8 KV heads it would take over 170 prompts, whose
@@ -455,8 +455,10 @@ WalkShares plan_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_b
 }  // namespace
 
 WalkShares plan_walk_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_blk, const int32_t *block_offsets, bool dq) {
-  const WalkShares ws = plan_shares(h, n_prompts, cu_blk, block_offsets, dq, true);
-  return ws.n_split > 0 ? ws : plan_shares(h, n_prompts, cu_blk, block_offsets, dq, false);
+  bool any_many;
+  const WalkShares ws = plan_shares(h, n_prompts, cu_blk, block_offsets, dq, true, &any_many);
+  if (ws.n_split > 0 || !any_many) return ws;
+  return plan_shares(h, n_prompts, cu_blk, block_offsets, dq, false, &any_many);
 }
 
 namespace {

@@ -71,7 +71,7 @@ bool is_int32_array(PyObject *o) {
   PyArrayObject *a = (PyArrayObject *)o;
   return PyArray_TYPE(a) == NPY_INT32 && PyArray_NDIM(a) == 1 && PyArray_ISCARRAY_RO(a);
 }
-// int32 host array, copied: the call runs without the interpreter's lock.
+// int32 host array (as guarded has seen) or None, copied: the call runs without the interpreter's lock.
 struct Ints {
   int32_t few[96];
   std::vector<int32_t> many;
@@ -79,7 +79,6 @@ struct Ints {
   int64_t n = 0;
   explicit Ints(PyObject *o) {
     if (o == Py_None) return;
-    need(is_int32_array(o));
     PyArrayObject *a = (PyArrayObject *)o;
     n = PyArray_DIM(a, 0);
     const int32_t *from = (const int32_t *)PyArray_DATA(a);
