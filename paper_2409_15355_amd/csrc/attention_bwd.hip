@@ -550,7 +550,7 @@ __global__ __launch_bounds__(kBThreads, 2) void bwd_dq_kernel(AttnParams p, Prom
 // of the time: the price of doing without the exchange.
 // Eight prompts of 20 passages of 100 to 300 tokens and a query block (33,746 tokens, 32 query heads over 8 of
 // 128, 208 GFLOP in four products): 320 -> 285 us, forward and backward 940 -> 903; 32 over 8 of 64 524 -> 486; two
-// prompts there 282 -> 270.  990 MB read (q^ and dO once are 553), 138 written.  What is left is waiting, 38 % of the waves' time for
+// prompts there 282 -> 270.  1.0 GB read (q^ and dO once are 553 MB), 138 MB written.  What is left is waiting, 38 % of the waves' time for
 // memory and at barriers and 30 % to issue; a third tile buffer, which now fits three workgroups, changes nothing.
 template <int D>
 struct KvGeo {
