@@ -388,23 +388,26 @@ struct FinalGatherMeta : FinalMeta {
 // tile that a workgroup walks, by every row tile anew.  So only
 //   - where a key is turned by kTurnRowTiles row tiles at most, in the mean over the context (each prompt by its share of the tokens);
 //   - for contexts of kTurnBytes of keys and kTurnBytesTile more for each of those row tiles;
-//   - where the longest walk is no more than kTurnUneven times what every compute unit walks in the mean (else it ends the launch
-//     alone, some 0.55 us a tile longer), nor longer than a tile for every kTurnBytesWalk of keys.
-// Copied / turned, us.  32 over 8 heads of 128, blocks of 60 to 180 and more, one row tile: 8 MiB 22.2 / 24.5, 16 MiB 29.8 / 29.6, 22 MiB 36.2 / 32.7, 44 MiB
-// 54.9 / 44.9, 90 MiB 88.9 / 70.8; two, 16 MiB 34.7 / 36.7, 32 MiB 58.4 / 54.3, 44 MiB 71.8 / 67.6, 64 MiB 94.6 / 89.2; three, 23 MiB 57.7 / 56.9, 32 MiB 74.1 /
-// 75.9, 44 MiB 91.2 / 94.4; four, 23 MiB 65.3 / 67.0, 38 MiB 102.9 / 109.2; six, 15 MiB 62.6 / 70.0.  32 over 32 of 64: one, 22 MiB
-// 36.7 / 34.7, 69 MiB 83.5 / 74.3; two, 42 tiles of 44 MiB, 84.3 / 88.7; three, 44 MiB 124 / 141, 72 MiB 184 / 205.
-// Few KV heads, whose splits are 64 at most: 8 over 1 of 128, 22 tiles of 22 MiB, 5.5 in the mean, 50.5 / 58.8; 8 over 2 of 64, 22 tiles and 11
-// 47.1 / 50.6; 8 over 2 of 128, 17 tiles and 8 of 32 MiB 52.3 / 49.3.  Several prompts: 180 query tokens over 3,000 and 30 over 16,000 (37
-// MiB, 32 tiles, 12 in the mean) 65.5 / 74.9; over 4,000 and 16,000 (32 and 14) 66.8 / 75.8; 180 over 7,000 and two of 30 over 9,000 (49 MiB, 24
-// and 19) 66.4 / 63.1; 60 over 16,000 and 60 over 3,000 (37 MiB, 16 and 9) 57.8 / 52.3.  What the line leaves on the turned side all the same: 16 KV
-// heads of 128, two row tiles, 28 tiles of 33 MiB 65.5 / 68.6; 180 over 6,000 and 30 over 16,000 (43 MiB, 32 and 17) 69.7 / 75.4; 8 over 2 of
-// 128, 11 tiles of 22 MiB 39.5 / 40.2.  One block of 3,000 among 500 of 30: 59.1 / 34.0.
-constexpr double kTurnRowTiles = 2.0, kTurnUneven = 2.25;
-constexpr double kTurnBytes = 12 << 20, kTurnBytesTile = 9 << 20, kTurnBytesWalk = 7.0 / 6.0 * (1 << 20);
+//   - of kTurnBytesWalk of keys or more for every tile of the longest walk, and of what a compute unit walks in the mean, which is more
+//     in several rounds of workgroups.  (With all compute units at work it is head_dim / 32 MiB over the row tiles: at head_dim
+//     64 one row tile only, at 128 two where the walks are nearly as long as each other);
+//   - where the longest walk is no more than kTurnUneven times the mean (else it ends the launch alone, some 0.55 us a tile longer).
+// Copied / turned, us.  32 over 8 heads of 128, blocks of 130, one row tile: 16 MiB 31.0 / 30.8, 22 MiB 35.0 / 33.6, 44 MiB 50.9 / 46.7, 90 MiB
+// 91.1 / 74.7; two, 16 MiB 37.0 / 37.7, 22 MiB 43.5 / 43.4, 32 MiB 54.8 / 54.5, 44 MiB 68.2 / 67.2; blocks of 60 to 180 and more, three, 23 MiB 57.7 / 56.9,
+// 32 MiB 74.1 / 75.9, 44 MiB 91.2 / 94.4; four, 23 MiB 65.3 / 67.0, 38 MiB 102.9 / 109.2; six, 15 MiB 62.6 / 70.0.  32 over 32 of 64: one, 22 MiB
+// 35.9 / 35.4, 90 MiB 98.2 / 87.7; two, 22 MiB 49.8 / 53.6, 44 MiB 82.1 / 87.4.
+// Few KV heads, whose splits are 64 at most: 8 over 1 of 128, 22 tiles of 22 MiB, 5.5 in the mean, 50.9 / 58.4; 8 over 2 of 64 46.4 / 50.2; 8 over 2
+// of 128, 17 tiles and 8 of 32 MiB, 47.5 / 49.5 and 52.3 / 49.3.  Several prompts: 180 query tokens over 3,000 and 30 over 16,000 (37
+// MiB, 32 tiles, 12 in the mean) 65.5 / 74.9; over 4,000 and 16,000 (32 and 14) 66.8 / 75.8; over 6,000 and 16,000 (43 MiB, 32 and 17) 69.7 /
+// 75.4; 180 over 7,000 and two of 30 over 9,000 (49 MiB, 24 and 19) 66.4 / 63.1; 60 over 16,000 and 60 over 3,000 (37 MiB, 16 and 9) 57.8 / 52.3; 8 over 1
+// of 128, three of 17,000 and two row tiles (49 MiB, 34 and 25) 72.8 / 80.5; 32 over 32 of 64, three of 2,600 and two (31 MiB, 13 and 31: three
+// rounds) 84.7 / 90.1.  1,387 drawn calls of 20 to 90 MiB, one and two row tiles: 984 are turned, 0.90 of a copy's time in the mean, 0.63 to 1.06
+// (up to 1.05 where both sides copy).  One block of 3,000 among 500 of 30: 59.1 / 34.0.
+constexpr double kTurnRowTiles = 2.0, kTurnUneven = 1.8;
+constexpr double kTurnBytes = 12 << 20, kTurnBytesTile = 9 << 20, kTurnBytesWalk = 1.5 * (1 << 20);
 inline bool turn_pays(double key_bytes, double row_tiles, double longest_walk, double mean_walk) {
   return row_tiles <= kTurnRowTiles && key_bytes >= kTurnBytes + kTurnBytesTile * row_tiles && longest_walk <= kTurnUneven * mean_walk &&
-         key_bytes >= kTurnBytesWalk * longest_walk;
+         key_bytes >= kTurnBytesWalk * (longest_walk > mean_walk ? longest_walk : mean_walk);
 }
 constexpr uint32_t kTurnLds = 32 * 1024;
 constexpr uint32_t kTurnPlain = 0x80000000u;  // in blk[]: a shift of zero, the key stays as it is

@@ -1153,11 +1153,13 @@ def test_small_encodes_turn_their_own_rows(ba, hq, hkv, d, lens, launches, layou
 @pytest.mark.parametrize("case", [
     # (Hq, Hkv, D, tokens of each prompt's cached blocks, query tokens of each prompt, whether nothing is copied)
     (32, 8, 128, [[20, 60, 33, 1] * 100], [64], True), (32, 32, 128, [[64] * 30, [7, 90, 130] * 8], [200, 1], True),
-    (32, 32, 64, [[40, 90] * 45], [130], True), (64, 16, 128, [[100] * 85, [3]], [100, 17], True),
+    (32, 32, 64, [[40, 90] * 45], [130], True), (64, 16, 128, [[100] * 78, [100] * 77 + [3]], [100, 117], True),
+    # a prompt of hardly any context next to one of two row tiles, whose walks are long for that
+    (64, 16, 128, [[100] * 85, [3]], [100, 17], False),
     # two row tiles a prompt (30 MiB of keys are asked for), blocks whose rotations do not fit, keys of 21 MiB, and a token less
     (64, 16, 128, [[50] * 150], [100], False), (32, 32, 128, [[1] * 1000, [64] * 30], [9, 9], False),
     (32, 32, 64, [[96] * 56], [5], True), (32, 32, 64, [[96] * 55 + [95]], [5], False)],
-    ids=["ragged", "two-prompts", "d64", "row-tiles", "many-row-tiles", "tiny-blocks", "turned-from-here", "copied-to-here"])
+    ids=["ragged", "two-prompts", "d64", "even-row-tiles", "row-tiles", "many-row-tiles", "tiny-blocks", "turned-from-here", "copied-to-here"])
 def test_cached_keys_turned_by_the_attention_kernel(ba, case, layout):
     """Short cached blocks, many of them: keys fetched through the table of rows and turned as they arrive.  The bits of a context
     re-encoded by hand; blocks in any order, some of them at the places they were encoded at (one with a key that a rotation by
@@ -1212,10 +1214,12 @@ def test_cached_keys_turned_by_the_attention_kernel(ba, case, layout):
     # two, with keys to spare, and two where a workgroup walks as many tiles as there are MiB of keys
     (32, 8, 128, [[200] * 82], [128], True), (32, 32, 64, [[200] * 52], [500], False),
     # the splits of one or two KV heads are long
-    (8, 1, 128, [[220] * 410], [20], False), (8, 2, 64, [[220] * 410], [20], False), (8, 2, 128, [[220] * 298], [20], True),
+    (8, 1, 128, [[220] * 410], [20], False), (8, 2, 64, [[220] * 410], [20], False), (8, 2, 128, [[220] * 298], [20], False),
     # row tiles count by the context that they turn: most of it behind three of them, or hardly any
     (32, 8, 128, [[200] * 100, [200], [200], [200]], [190, 20, 20, 20], False),
     (32, 8, 128, [[200] * 35, [200] * 45, [200] * 45], [180, 30, 30], True),
+    # prompts whose splits leave a quarter of the chip idle, and three rounds of workgroups
+    (32, 16, 128, [[60] * 46] * 3, [169] * 3, False), (32, 32, 64, [[84] * 31] * 3, [430] * 3, False),
     # ... and the walk of the prompt that has one row tile decides
     (32, 8, 128, [[200] * 15, [200] * 80], [180, 30], False)])
 def test_contexts_are_turned_where_that_pays(ba, hq, hkv, d, prompts, lqs, turned):
