@@ -2,6 +2,7 @@
 library, and a package without it or with one for another torch."""
 import os
 import shutil
+import struct
 import subprocess
 import sys
 import time
@@ -81,6 +82,17 @@ try:
 except ValueError as e:
     print(type(ba._face()).__name__, "|", e)
 """
+
+
+def test_the_native_half_has_no_thread_locals():
+    """... which would slow down everybody else's, see build_face."""
+    ba.load()
+    with open(ba.FACE_PATH, "rb") as f:
+        elf = f.read()
+    at, = struct.unpack_from("<Q", elf, 32)
+    size, n = struct.unpack_from("<HH", elf, 54)
+    kinds = [struct.unpack_from("<I", elf, at + i * size)[0] for i in range(n)]
+    assert 1 in kinds and 7 not in kinds  # PT_LOAD, PT_TLS
 
 
 def test_the_package_works_without_its_native_half(tmp_path):
