@@ -197,6 +197,12 @@ constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 // 238 / 183; 8 over 2 of 64, one of 20 x 100-300 and 200-256 191 / 79.  Parts of 16, 20 and 32 tiles: 170, 169 and 170, 285, 281 and 282;
 // at 64 79 with 16, 85 with 24, 90 with 32.  At most 96, 128 and 256 workgroups: 238, 186 and 182 where 192 take 183.  60 drawn calls of 1 to 6
 // prompts whose walks are as long: 0.48 to 1.01 of the time, 0.85 in the mean.
+// Next to a walk that stays and is nearly as long they are not: the launch gets no shorter, and its parts, many and all early, hold up the
+// long ones.  Forward kernel, unshared / shared, us, a passage and a query block: 8 over 1 of 128, 5,000 and 900 tokens (longest walk 1.18 of
+// the longest that stays) 170 / 238, 6,750 and 250 (1.04) 197 / 258; 14 over 2 of 64, 5,700 and 270 (1.04) 149 / 167; 16 over 8
+// of 128, 3,450 and 105 (1.03) 95 / 98.  From 1.23 on 0.69 to 1.01, below 0.79 to 1.40, 1.01 in the mean of 50.  So only if the longest is longer
+// by 1 / kShareManyLead, or more than kShareManyAnyway times the load: beyond that 0.86 to 1.00 with any lead.  (The dq kernel, whose
+// parts cost more, has kShareAnyway there: 410 us unshared and 426 at 2.1 of the load, 3 over 3 of 128.)
 // With more than kSharePairs / 2 KV heads no walk is cut, whatever the block: one row tile of it is too many pairs for the first rule, and
 // the second goes no further.  So with 13 KV heads and more a prompt's output, log-sum-exps and dq are the same bits in every
 // batch (ba.h says so).  What that costs, prompts of 20 x 200 + 64 tokens, forward and backward, us, as they are / cut: 64 over 16 heads of 64 one
@@ -222,7 +228,8 @@ constexpr double dq_share_load(int head_dim, int64_t group) {
   return head_dim == 64 ? 1.1 : 0.86;
 }
 constexpr double kSharePartTiles = 24.0;  // head_dim 128
-constexpr int kShareLead = 100;
+constexpr int kShareLead = 100, kShareManyLead = 4;
+constexpr double kShareAnyway = 4.0, kShareManyAnyway = 1.5;
 constexpr size_t kShareMaxBytes = (size_t)256 << 20;
 // ... and the same for the walks of the dk/dv kernel (0.73 us a tile; a key tile's rows are its block's and the last
 // block's).  Forward and backward, us, dk/dv unshared / shared: 8 over 2 heads of 64, five prompts of 4 x 700 tokens and a last

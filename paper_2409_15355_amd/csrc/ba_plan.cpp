@@ -443,7 +443,8 @@ WalkShares plan_shares(const ba_heads *h, int32_t n_prompts, const int32_t *cu_b
   const size_t slots = (size_t)ws.items * h->n_kv_heads * (kShortTileRows / 32);
   const double least = dq && *any_many ? dq_share_load(h->head_dim, G) : kShareLoad;
   if (ws.n_split == 0 || longest < least * load) return WalkShares();
-  if (longest <= longest_left + longest_left / kShareLead && longest <= 4 * load) return WalkShares();
+  const int lead = longest_left / (*any_many ? kShareManyLead : kShareLead);
+  if (longest <= longest_left + lead && longest <= (*any_many && !dq ? kShareManyAnyway : kShareAnyway) * load) return WalkShares();
   // (the tables need the first: the shared blocks are in the first launch's.  With 8 KV heads it would take over 170 prompts, whose
   // load is far beyond the line)
   if (ws.n_split > kEncMaxBlocks || slots * 32 * h->head_dim * 4 > kShareMaxBytes) return WalkShares();

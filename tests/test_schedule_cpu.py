@@ -289,6 +289,16 @@ def test_the_dq_kernel_shares_walks_of_many_row_tiles_by_a_line_of_its_own(hq, h
         assert (size > least(int(offs[-1]))) == (n <= most), n
 
 
+@pytest.mark.parametrize("hq,hkv,d,prompt,parts", [
+    # a passage nearly as long as the whole prompt, whose walk stays: shared only from a quarter more on ...
+    (8, 1, 128, [5000, 900], 1), (8, 1, 128, [4000, 1200], 2), (14, 2, 64, [5150, 268], 1), (16, 8, 128, [3450, 105], 1), (14, 2, 64, [2500, 2500, 268], 6),
+    # ... or where the chip has little else to do
+    (8, 2, 64, [1600, 200], 4), (8, 1, 128, [2000, 400], 4)])
+def test_walks_of_many_row_tiles_are_shared_where_no_passage_is_nearly_as_long(hq, hkv, d, prompt, parts):
+    offs = np.concatenate([[0], np.cumsum(prompt)])
+    assert max(w.n_splits for w in ba.ba_schedule_prompts(ba.Heads(hq, hkv, d, 10000.0), [0, len(prompt)], offs)) == parts
+
+
 @pytest.mark.parametrize("hq,hkv,d,prompt,below,above", [(32, 8, 128, [200] * 6 + [20], 4, 5), (16, 8, 128, [200] * 20 + [64], 8, 9),
                                                          (4, 4, 64, [200] * 6 + [20], 24, 32)])
 def test_walks_are_shared_only_where_the_call_leaves_the_chip_idle(hq, hkv, d, prompt, below, above):
