@@ -200,7 +200,7 @@ constexpr int kEncodeCus = 256;           // compute units the rule reckons with
 // Next to a walk that stays and is nearly as long they are not: the launch gets no shorter, and its parts, many and all early, hold up the
 // long ones.  Forward kernel, unshared / shared, us, a passage and a query block: 8 over 1 of 128, 5,000 and 900 tokens (longest walk 1.18 of
 // the longest that stays) 170 / 238, 6,750 and 250 (1.04) 197 / 258; 14 over 2 of 64, 5,700 and 270 (1.04) 149 / 167; 16 over 8
-// of 128, 3,450 and 105 (1.03) 95 / 98.  From 1.23 on 0.69 to 1.01, below 0.79 to 1.40, 1.01 in the mean of 50.  So only if the longest is longer
+// of 128, 3,450 and 105 (1.03) 95 / 98.  From 1.23 on 0.55 to 1.01, below 0.79 to 1.40, 1.02 in the mean of 52.  So only if the longest is longer
 // by 1 / kShareManyLead, or more than kShareManyAnyway times the load: beyond that 0.86 to 1.00 with any lead.  (The dq kernel, whose
 // parts cost more, has kShareAnyway there: 410 us unshared and 426 at 2.1 of the load, 3 over 3 of 128.)
 // With more than kSharePairs / 2 KV heads no walk is cut, whatever the block: one row tile of it is too many pairs for the first rule, and
